@@ -114,6 +114,52 @@ struct SlotTables {
   const int32_t* ints;      // DEVICE
 };
 
+// Tables of the two-pass list evaluation (rows.hip, timing.hip).  `ints` = [timing rows][order rows][dev]:
+//   timing rows [kNKinds * 4][D, the even devices first] x 4 ints, addressed by the top five bits of the op word and
+//   the device:
+//     0 (latency of the first input << 8) - tag expected on it (kEmptySlot's tag if the op starts a class, kOwnTag if
+//       it has no cross-stage edge); 1: the op never issues
+//     1 dur << 8 | tag it leaves: its stage, or kOwnTag
+//     2 byte offset of its slot for micro-batch 0 | mask of the bits of (word << 2) that are added to it << 16
+//     3 if the op has a second input or output: byte offset of a second row | kRowTwoOut | sign bit: two inputs.  An op
+//       with two inputs waits for its second one first: words 0 and 2 are then the second input's.
+//   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 unused
+//   Slots of a candidate, in dwords: [0, D) the devices' own words, D + 1
+//   for the makespan, then from list_slots_at(D) on class * m for backward values, (classes + class) * m for forward
+//   values; finish << 8 | producer stage, kEmptySlot at first.
+//   order rows [kNKinds * 4][D] x 2 ints:
+//     0 next state | required state << 8 | units allocated << 16 | units freed << 24   1 dur
+//     Rows of words that may not appear on the device require kNoState.
+//   dev [D] x 2: chunks on the device, memory cap / unit_scale
+// Memory units are divided by their greatest common divisor (unit_scale) and must then fit a byte.
+struct ListTables {
+  int32_t D, m;
+  int32_t cands_per_wave;   // candidates of one wavefront of the timing pass: ceil(D / 2) lanes each
+  int32_t cand_slots;       // dwords per candidate, a multiple of 4
+  int32_t wave_bytes;       // LDS of one wavefront of the timing pass: op windows, then slots
+  int32_t n_time_ints;      // timing rows, padded to a multiple of 8
+  int32_t off_check;        // order rows, in ints
+  int32_t n_check_ints;
+  int32_t check_shared_bytes;   // order rows and dev rows in LDS, a multiple of 16
+  int32_t off_dev;          // in ints
+  int32_t state_bytes;      // states of one row in the order pass: an odd number of dwords
+  int32_t check_wave_bytes; // LDS of one wavefront of the order pass, a multiple of 16
+  int32_t terminal;         // state of a consumed activation
+  int32_t unit_scale;
+  const int32_t* ints;      // DEVICE
+};
+constexpr unsigned kRowTwoOut = 1u << 30;
+constexpr unsigned kOwnTag = 0xfeu;   // (no stage's op looks at a device's own word)
+constexpr int list_slots_at(int D) { return (D + 2 + 3) & ~3; }
+constexpr unsigned kNoState = 15u;
+// the upper half of what the order pass leaves per row: the position at which the list stops (its END word, the end
+// of the row, or the first op that may not issue there), and
+constexpr unsigned kRowStop = 0x0fffffffu;
+constexpr unsigned kRowStuck = 1u << 28;       // the list stops at an op that can never issue
+constexpr unsigned kRowMalformed = 1u << 29;   // ... whose word is malformed
+constexpr unsigned kRowIncomplete = 1u << 30;  // not every activation is consumed at the stop
+constexpr unsigned kRowOverCap = 1u << 31;     // the peak exceeds the device's cap
+
 // Tables of the evaluation with synchronisation stages and dependency pairs (eval_sync.hip).  Every
 // dependency of an item -- the edges of the stage DAG and the user's pairs alike -- is one entry of a list
 // per (kind, stage): which finish-time table it looks into (0 forward, 1 backward, 2 weight gradient), the

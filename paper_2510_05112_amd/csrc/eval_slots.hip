@@ -1,5 +1,6 @@
-// Slot evaluation kernel: the main path.  Any per-device op order, any stage DAG with
-// at most two inputs and two outputs per stage, a few KB of LDS per candidate.
+// Slot evaluation kernel: the variants of the cost model and the sliding pass (the modes below; the plain model is
+// rows.hip and timing.hip).  Any per-device op order, any stage DAG with at most two inputs and two outputs per
+// stage, a few KB of LDS per candidate.
 //
 // Mapping: a wavefront carries `cands_per_wave` candidate segments, lane = device inside
 // a segment; the wavefronts of a workgroup are independent and only share one LDS copy
@@ -50,34 +51,11 @@
 #include <stdint.h>
 
 #include "kernels.h"
+#include "lds_access.h"
 
 namespace fpsched {
 
 namespace {
-
-// LDS accesses by 32-bit LDS address (the per-lane addresses are kept as integers so that ring
-// positions and table offsets can be OR-ed / multiplied into them)
-#define FPSCHED_LDS __attribute__((address_space(3)))
-template <class T>
-__device__ __forceinline__ T lds_read(unsigned a) {
-  return *reinterpret_cast<const FPSCHED_LDS T*>(a);
-}
-typedef int lds_int4 __attribute__((ext_vector_type(4)));
-typedef int lds_int2 __attribute__((ext_vector_type(2)));
-template <>
-__device__ __forceinline__ int4 lds_read<int4>(unsigned a) {
-  const lds_int4 v = *reinterpret_cast<const FPSCHED_LDS lds_int4*>(a);
-  return make_int4(v.x, v.y, v.z, v.w);
-}
-template <>
-__device__ __forceinline__ int2 lds_read<int2>(unsigned a) {
-  const lds_int2 v = *reinterpret_cast<const FPSCHED_LDS lds_int2*>(a);
-  return make_int2(v.x, v.y);
-}
-template <class T>
-__device__ __forceinline__ void lds_write(unsigned a, T v) {
-  *reinterpret_cast<FPSCHED_LDS T*>(a) = v;
-}
 
 // One value per chunk of a device, kept as ONE vector value: as an array of four ints the compiler turns the
 // select chain below into a load with a variable index and puts the array into scratch memory.
@@ -104,8 +82,8 @@ constexpr int kPrimeChunks = 3;
 
 }  // namespace
 
-__global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value) {
-  if (threadIdx.x == 0) *counter = value;
+__global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2) {
+  if (threadIdx.x == 0) { counter[0] = value; counter[1] = value2; }
 }
 
 // MODE kSlotTimes (TIMES below) is the first pass of the weight-gradient sliding (wslide.hip): the tables then
@@ -886,7 +864,6 @@ __global__ __launch_bounds__(kSlotMaxThreads) void eval_slot_kernel(
       SlotTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*,          \
       unsigned long long*, int, uint32_t*, int32_t*, const int32_t*, uint32_t*, int);
 #define FPSCHED_INSTANTIATE(V, G, O)               \
-  FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotPlain)    \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotTimes)    \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotPerMicrobatch) \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotPerMicrobatchLds) \

@@ -29,8 +29,8 @@ struct fpsched_problem {
   int32_t max_degree = 0;          // largest in- or out-degree of a stage in the DAG
   int32_t n_cu = 0;                // compute units of the device
   void* d_static_scratch = nullptr; // this device's copy of the library's static scratch array
-  bool general_ok = false, slots_ok = false;  // which kernels fit this problem in LDS
-  bool use_slots = false;          // selected kernel: slot kernel (default when it fits) or general
+  bool general_ok = false, slots_ok = false;  // which kernels fit this problem in LDS (slots_ok: the forms of eval_slots.hip)
+  bool use_slots = false;          // selected kernels: those with mail slots (default when they fit) or the general one
   int32_t slot_v = 0;              // template bound on chunks per device
   bool slot_deg2 = false;          // some stage has two inputs or two outputs
   int32_t slot_lds_bytes = 0;      // dynamic LDS of one slot-kernel workgroup
@@ -49,6 +49,13 @@ struct fpsched_problem {
   SlotTables stab{};
   std::vector<int32_t> slot_ints;
   int32_t* d_slot_ints = nullptr;
+  // the two-pass list evaluation: order pass, timing pass
+  bool lists_ok = false;
+  bool lists_deg2 = false;
+  ListTables ltab{};
+  int32_t* d_list_ints = nullptr;
+  int32_t check_rows_per_wave = 0, check_waves = 0, check_grid = 0, check_vbits = 0;
+  int32_t time_waves = 0, time_grid = 0;   // wavefronts per workgroup, resident workgroups
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
   int64_t max_comm = 0;
   bool mb_set = false;
@@ -158,7 +165,6 @@ SlotKernel slot_kernel_of(int v, bool deg2, bool one_class) {
   return v == 1 ? &eval_slot_kernel<1, false, false, MODE>
                 : (v == 2 ? &eval_slot_kernel<2, false, false, MODE> : &eval_slot_kernel<4, false, false, MODE>);
 }
-SlotKernel slot_kernel_ptr(int v, bool deg2, bool one_class) { return slot_kernel_of<kSlotPlain>(v, deg2, one_class); }
 
 // Launch shape of the slot kernel for a batch: `waves` wavefronts per workgroup and `grid` workgroups fill the
 // chip; a batch too small for that is spread over as many compute units as it has wavefronts' worth of
@@ -202,10 +208,159 @@ SlotGeometry slot_geometry(int64_t n_shared_ints, int lanes_per_cand, int state_
   return SlotGeometry{scpw, (int)wave_ints, best_waves, std::max(best_groups, 1)};
 }
 
+// Wavefronts per workgroup and workgroups per compute unit that keep the most wavefronts resident, for a shared part
+// of `shared` bytes of LDS per workgroup and `per_wave` bytes per wavefront (0 = does not fit).  At equal numbers the
+// fewer workgroups win: each has a copy of the shared part to fetch.
+struct WorkgroupShape { int waves, groups; };
+// max_waves: of a workgroup; per_simd: resident wavefronts per SIMD that the registers allow; even: keep the four SIMDs
+// of a compute unit equally loaded (for kernels whose wavefronts are given equal shares of the work).
+WorkgroupShape workgroup_shape(int64_t shared, int64_t per_wave, int64_t max_lds, int max_waves = 16, int per_simd = 8,
+                               bool even = false) {
+  WorkgroupShape best{0, 1};
+  for (int groups = 1; groups <= 8; ++groups) {
+    const int64_t room = max_lds / groups - shared - 512;   // allocation slack
+    int waves = room > 0 ? (int)std::min<int64_t>(room / per_wave, max_waves) : 0;
+    waves = std::min(waves, 4 * per_simd / groups);   // 4 SIMDs per compute unit
+    if (even && waves > 4) waves &= ~3;
+    if (waves * groups > best.waves * best.groups) best = WorkgroupShape{waves, groups};
+  }
+  // tuning knob: FPSCHED_SLOT_WAVES=n caps the wavefronts per workgroup (one workgroup per CU)
+  if (const char* env = getenv("FPSCHED_SLOT_WAVES")) {
+    const int cap = atoi(env);
+    if (cap >= 1 && cap < best.waves * best.groups) best = WorkgroupShape{std::min(cap, best.waves), 1};
+  }
+  return best;
+}
+
 int next_pow2(int x) {
   int p = 1;
   while (p < x) p <<= 1;
   return p;
+}
+
+using CheckKernel = void (*)(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+CheckKernel check_kernel_of(int vbits) {
+  return vbits == 0 ? &check_rows_kernel<0> : (vbits == 1 ? &check_rows_kernel<1> : &check_rows_kernel<2>);
+}
+
+// What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
+struct StageEdge { int32_t cls, tag, latency; };
+struct StageEdges { std::vector<StageEdge> in[2], out[2]; };
+
+// Table image of the two-pass list evaluation (layout: device_tables.h) and the launch shapes of its kernels.
+// Leaves lists_ok false if the problem does not fit: more than two inputs or outputs of a stage, times, latencies,
+// stages or slots beyond the widths of their fields, or no room in LDS.
+void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, const std::vector<StageEdges>& edges,
+                       int n_classes, int64_t bound, std::vector<int32_t>* image) {
+  const int D = p->D, S = p->S, m = p->m;
+  int64_t unit_scale = 0;
+  for (int s = 0; s < S; ++s) unit_scale = std::gcd<int64_t, int64_t>(unit_scale, desc->mem_units[s]);
+  unit_scale = std::max<int64_t>(unit_scale, 1);
+  const int64_t cand_slots = (list_slots_at(D) + 2ll * n_classes * m + 3) & ~3ll;
+  if (4 * cand_slots > 0xffff || S > 255 || p->max_comm >= (1ll << 16) || bound >= (1ll << 24)) return;
+  bool deg2 = false;
+  for (int s = 0; s < S; ++s) {
+    if (desc->mem_units[s] / unit_scale > 0xff) return;
+    for (int dir = 0; dir < 2; ++dir) {
+      // (an output edge continues the class of the input edge of the same number: see the slot classes)
+      for (size_t e = 0; e < std::min(edges[s].in[dir].size(), edges[s].out[dir].size()); ++e)
+        if (edges[s].in[dir][e].cls != edges[s].out[dir][e].cls) return;
+      const size_t n = std::max(edges[s].in[dir].size(), edges[s].out[dir].size());
+      if (n > 2) return;
+      deg2 = deg2 || n > 1;
+    }
+  }
+  const int row_ints = 4;
+  ListTables& T = p->ltab;
+  T.D = D; T.m = m;
+  // (F, FD and B rows of a stage may each have a second row)
+  int n_second = 0;
+  for (int s = 0; s < S; ++s)
+    for (int dir = 0; dir < 2; ++dir)
+      if (std::max(edges[s].in[dir].size(), edges[s].out[dir].size()) > 1) n_second += dir == 0 ? 2 : 1;
+  T.n_time_ints = (kNKinds * kMaxChunks * D * row_ints + n_second * 4 + 7) & ~7;
+  if (4ll * T.n_time_ints > 0xffff) return;
+  int second_at = kNKinds * kMaxChunks * D * row_ints;
+  T.off_check = T.n_time_ints;
+  T.n_check_ints = kNKinds * kMaxChunks * D * 2;
+  T.off_dev = T.off_check + T.n_check_ints;
+  T.check_shared_bytes = (4 * (T.n_check_ints + 2 * D) + 15) & ~15;
+  T.cand_slots = (int32_t)cand_slots;
+  T.terminal = p->has_w ? kDone : kBDone;
+  T.unit_scale = (int32_t)unit_scale;
+  int max_chunks = 1;
+  for (int d = 0; d < D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
+  p->check_vbits = max_chunks <= 1 ? 0 : (max_chunks <= 2 ? 1 : 2);
+  T.state_bytes = ((((m + 1) * (1 << p->check_vbits) + 3) / 4) | 1) * 4;
+  std::vector<int32_t>& J = *image;
+  J.assign((size_t)T.off_dev + 2 * D, 0);
+  static const int need_of[kNKinds] = {(int)kNoState, kAbsent, kRes, kBDone, kDisc, kRes, kOff, kAbsent};
+  static const int next_of[kNKinds] = {0, kRes, kBDone, kDone, kRes, kOff, kRes, kDisc};
+  for (int kind = 0; kind < kNKinds; ++kind)
+    for (int c = 0; c < kMaxChunks; ++c)
+      for (int d = 0; d < D; ++d) {
+        const size_t row = ((size_t)kind * kMaxChunks + c) * D;
+        int32_t* t = &J[(row + (d & 1) * ((D + 1) / 2) + d / 2) * row_ints];   // even devices first
+        int32_t* o = &J[(size_t)T.off_check + (row + d) * 2];
+        t[0] = 1;
+        t[2] = 4 * d;
+        o[0] = (int32_t)(kNoState << 8);
+        if (c >= p->n_chunks[d] || kind == kEnd || (kind == kW && !p->has_w)) continue;
+        const int s = p->local_stage[(size_t)d * kMaxChunks + c];
+        const unsigned units = (unsigned)(desc->mem_units[s] / unit_scale);
+        const bool allocs = kind == kF || kind == kFD || kind == kR || kind == kL;
+        const bool frees = kind == kFD || kind == kO || kind == (p->has_w ? kW : kB);
+        o[0] = (int32_t)((unsigned)next_of[kind] | ((unsigned)need_of[kind] << 8) | ((allocs ? units : 0u) << 16) | ((frees ? units : 0u) << 24));
+        o[1] = desc->dur[kind * S + s];
+        const int dir = kind == kF || kind == kFD ? 0 : (kind == kB ? 1 : -1);
+        const std::vector<StageEdge> none;
+        const std::vector<StageEdge>& in = dir < 0 ? none : edges[s].in[dir];
+        const std::vector<StageEdge>& out_edges = dir < 0 ? none : edges[s].out[dir];
+        const bool crosses = !in.empty() || !out_edges.empty();
+        t[1] = (int32_t)(((unsigned)desc->dur[kind * S + s] << 8) | (crosses ? (unsigned)s : kOwnTag));
+        if (!crosses) { t[0] = -(int32_t)kOwnTag; continue; }
+        const int base = list_slots_at(D) + (dir == 0 ? n_classes * m : 0);
+        for (size_t e = 0; e < std::max(in.size(), out_edges.size()); ++e) {
+          const int cls = e < in.size() ? in[e].cls : out_edges[e].cls;
+          const int32_t slot = (int32_t)((unsigned)(4 * (base + cls * m)) | (0x1ffcu << 16));
+          const int32_t wait = e < in.size() ? (int32_t)(((unsigned)in[e].latency << 8) - (unsigned)in[e].tag) : -(int32_t)(kEmptySlot & 0xffu);
+          if (e == 0) { t[0] = wait; t[2] = slot; continue; }
+          int32_t* second = &J[second_at];
+          second[0] = t[0]; second[1] = t[2]; second[2] = slot;
+          t[3] = (int32_t)((unsigned)(4 * second_at) | (e < out_edges.size() ? kRowTwoOut : 0u) | (e < in.size() ? 1u << 31 : 0u));
+          if (e < in.size()) { t[0] = wait; t[2] = slot; }
+          second_at += 4;
+        }
+      }
+  for (int d = 0; d < D; ++d) {
+    J[(size_t)T.off_dev + 2 * d] = p->n_chunks[d];
+    J[(size_t)T.off_dev + 2 * d + 1] = (int32_t)(desc->mem_cap[d] / unit_scale);   // peak > cap  <=>  peak / scale > floor(cap / scale)
+  }
+  // order pass: as many rows per wavefront as the states leave room for
+  WorkgroupShape check{0, 1};
+  int rows = 64;
+  for (; rows >= 4; rows >>= 1) {
+    T.check_wave_bytes = (rows * T.state_bytes + 15) & ~15;
+    check = workgroup_shape(T.check_shared_bytes, T.check_wave_bytes, p->max_lds, kCheckMaxThreads / 64, kCheckWavesPerSimd, true);
+    if (check.waves >= 1) break;
+  }
+  // timing pass: as many candidates per wavefront as its lanes and LDS hold
+  WorkgroupShape time{0, 1};
+  int cpw = 64 / ((D + 1) / 2);
+  for (; cpw >= 1; --cpw) {
+    T.wave_bytes = (int32_t)((kTimeWindowBytes + cpw * 4 * cand_slots + 31) & ~31ll);   // (rings are 32-byte aligned)
+    time = workgroup_shape(4ll * T.n_time_ints, T.wave_bytes, p->max_lds);
+    if (time.waves >= 1) break;
+  }
+  if (check.waves < 1 || time.waves < 1) return;
+  T.cands_per_wave = cpw;
+  p->check_rows_per_wave = rows;
+  p->check_waves = check.waves;
+  p->check_grid = p->n_cu * check.groups;
+  p->time_waves = time.waves;
+  p->time_grid = p->n_cu * time.groups;
+  p->lists_deg2 = deg2;
+  p->lists_ok = true;
 }
 
 }  // namespace
@@ -556,19 +711,39 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       p->slot_grid = n_cu * std::max(best_groups, 1);
       p->n_cu = n_cu;
     }
-    if (!p->general_ok && !p->slots_ok) { delete p; return FPSCHED_EUNSUPPORTED; }
-    p->use_slots = p->slots_ok;
+    std::vector<int32_t> list_image;
+    {
+      std::vector<StageEdges> se(S);
+      for (int e = 0; e < E; ++e) {
+        const int a = desc->edge_src[e], b = desc->edge_dst[e];
+        const int32_t lat = p->stage_device[a] != p->stage_device[b] ? desc->edge_comm[e] : 0;
+        se[a].out[0].push_back({edge_cls[e], b, lat});
+        se[b].in[0].push_back({edge_cls[e], a, lat});
+        se[a].in[1].push_back({edge_cls[e], b, lat});
+        se[b].out[1].push_back({edge_cls[e], a, lat});
+      }
+      build_list_tables(p, desc, se, n_classes, (int64_t)D * max_stride_words * (max_dur + max_comm), &list_image);
+    }
+    if (!p->general_ok && !p->lists_ok) { delete p; return FPSCHED_EUNSUPPORTED; }
+    p->use_slots = p->lists_ok;
     if (hipMalloc(&p->d_ints, I.size() * sizeof(int32_t)) != hipSuccess) { delete p; return FPSCHED_ENOMEM; }
     bool ok = hipMemcpy(p->d_ints, I.data(), I.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
     if (ok && p->general_ok)
       ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&eval_general_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
+    if (ok && p->lists_ok) {
+      ok = hipMalloc(&p->d_list_ints, list_image.size() * sizeof(int32_t)) == hipSuccess &&
+           hipMemcpy(p->d_list_ints, list_image.data(), list_image.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
+      for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits)),
+                                 reinterpret_cast<const void*>(&time_lists_kernel<false>),
+                                 reinterpret_cast<const void*>(&time_lists_kernel<true>)})
+        ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
+      p->ltab.ints = p->d_list_ints;
+    }
     if (ok && p->slots_ok) {
       ok = hipMalloc(&p->d_slot_ints, p->slot_ints.size() * sizeof(int32_t)) == hipSuccess &&
            hipMemcpy(p->d_slot_ints, p->slot_ints.data(), p->slot_ints.size() * sizeof(int32_t),
-                     hipMemcpyHostToDevice) == hipSuccess &&
-           hipFuncSetAttribute(reinterpret_cast<const void*>(slot_kernel_ptr(p->slot_v, p->slot_deg2, p->stab.n_classes == 1)),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
+                     hipMemcpyHostToDevice) == hipSuccess;
       p->stab.ints = p->d_slot_ints;
       // The sliding pass times the lists without their W items with the evaluation kernel's TIMES
       // form: the same tables, except that a W word is a no-op (any state, no cost, no memory) and a
@@ -640,10 +815,9 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
     }
     if (!ok) {
       (void)hipFree(p->d_ints);
+      if (p->d_list_ints) (void)hipFree(p->d_list_ints);
       if (p->d_slot_ints) (void)hipFree(p->d_slot_ints);
-    if (p->d_sync_slot_image) (void)hipFree(p->d_sync_slot_image);
       if (p->d_times_ints) (void)hipFree(p->d_times_ints);
-    if (p->d_slide_ints) (void)hipFree(p->d_slide_ints);
       if (p->d_slide_ints) (void)hipFree(p->d_slide_ints);
       delete p;
       return FPSCHED_EHIP;
@@ -659,7 +833,9 @@ void fpsched_problem_destroy(fpsched_problem* p) {
   if (p->d_ints || p->d_slot_ints || p->d_sync_ints) {
     DeviceGuard g(p->device_id);
     if (p->d_ints) (void)hipFree(p->d_ints);
+    if (p->d_list_ints) (void)hipFree(p->d_list_ints);
     if (p->d_slot_ints) (void)hipFree(p->d_slot_ints);
+    if (p->d_slide_ints) (void)hipFree(p->d_slide_ints);
     if (p->d_sync_slot_image) (void)hipFree(p->d_sync_slot_image);
     if (p->d_times_ints) (void)hipFree(p->d_times_ints);
     if (p->d_mb_raw) (void)hipFree(p->d_mb_raw);
@@ -679,17 +855,17 @@ int fpsched_problem_info(const fpsched_problem* p, int32_t* lanes_per_candidate,
   if (!p) return FPSCHED_EINVAL;
   const bool slots = p->use_slots;
   if (lanes_per_candidate) *lanes_per_candidate = p->tables.lanes_per_cand;
-  if (candidates_per_wave) *candidates_per_wave = slots ? p->stab.cands_per_wave : p->tables.cands_per_wave;
-  if (lds_bytes_per_wave) *lds_bytes_per_wave = slots ? p->slot_lds_bytes / std::max(p->slot_waves, 1) : p->lds_bytes;
+  if (candidates_per_wave) *candidates_per_wave = slots ? p->ltab.cands_per_wave : p->tables.cands_per_wave;
+  if (lds_bytes_per_wave) *lds_bytes_per_wave = slots ? 4 * p->ltab.n_time_ints / std::max(p->time_waves, 1) + p->ltab.wave_bytes : p->lds_bytes;
   return FPSCHED_OK;
 }
 
 int fpsched_problem_select_kernel(fpsched_problem* p, int which) {
   if (!p) return FPSCHED_EINVAL;
   if (p->device_id < 0) return FPSCHED_ENODEV;
-  if (which == FPSCHED_KERNEL_AUTO) p->use_slots = p->slots_ok;
+  if (which == FPSCHED_KERNEL_AUTO) p->use_slots = p->lists_ok;
   else if (which == FPSCHED_KERNEL_GENERAL) { if (!p->general_ok) return FPSCHED_EUNSUPPORTED; p->use_slots = false; }
-  else if (which == FPSCHED_KERNEL_SLOTS) { if (!p->slots_ok) return FPSCHED_EUNSUPPORTED; p->use_slots = true; }
+  else if (which == FPSCHED_KERNEL_SLOTS) { if (!p->lists_ok) return FPSCHED_EUNSUPPORTED; p->use_slots = true; }
   else return FPSCHED_EINVAL;
   return FPSCHED_OK;
 }
@@ -717,6 +893,50 @@ size_t fpsched_workspace_bytes(const fpsched_problem* p, int64_t n_cand, int32_t
   int64_t a = 0, b = 0;
   const int64_t keys = k > 0 ? topk_level_sizes(n_cand, std::min(k, 1024), &a, &b) : 0;
   return (size_t)(256 + keys * (int64_t)sizeof(Key));
+}
+
+// Candidates per atomic draw from a launch's work counter.  Atomics on one address complete at some 8e7 per second; a
+// batch of long candidates stays far below that and is drawn one by one (best balance at the end of the batch), short
+// rows are drawn several at a time: about one draw per 12 K op words.
+static int draws_at_a_time(const fpsched_problem* p, int32_t stride_words, int cands_per_wave) {
+  const int64_t row_words = (int64_t)p->D * stride_words;
+  return (int)std::clamp<int64_t>((12288 + row_words - 1) / row_words, 1, cands_per_wave);
+}
+
+// the two-pass list evaluation: the order pass over all rows, then the timing pass on a persistent grid
+static int run_list_evaluation(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_cand, int32_t stride_words,
+                               const fpsched_results& out, unsigned long long* counter, hipStream_t st) {
+  const ListTables& T = p->ltab;
+  const int64_t n_rows = n_cand * p->D, rpw = p->check_rows_per_wave;
+  // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
+  const int64_t row_waves = (n_rows + rpw - 1) / rpw;
+  const int cw = (int)std::clamp<int64_t>((row_waves + p->check_grid - 1) / p->check_grid, 1, p->check_waves);
+  const int64_t check_blocks = std::min<int64_t>((row_waves + cw - 1) / cw, p->check_grid);
+  const int64_t cpw = T.cands_per_wave, grid = p->time_grid;
+  const int tw = (int)std::clamp<int64_t>((n_cand + cpw * grid - 1) / (cpw * grid), 1, p->time_waves);
+  const int64_t time_blocks = std::min<int64_t>((n_cand + cpw * tw - 1) / (cpw * tw), grid);
+  long long* idle = reinterpret_cast<long long*>(out.idle);
+  // segment g starts on candidate g, wavefront w of the order pass on block w of rows; the counters hand out those behind
+  const unsigned long long first_drawn = (unsigned long long)(time_blocks * cpw * tw);
+  // (about four draws per wavefront even out the last blocks; with as many as there are blocks the counter's address is
+  // what the pass waits for, 1001 instead of 870 us for 262,144 candidates of 16 rows.  A few blocks per wavefront are
+  // shared out equally.)
+  const int64_t check_waves = check_blocks * cw, per_wave = (row_waves + check_waves - 1) / check_waves;
+  const int draw_blocks = (int)(per_wave <= 8 ? per_wave : per_wave / 4);
+  const bool dynamic = row_waves > check_waves * draw_blocks;
+  if (dynamic) {
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, first_drawn, (unsigned long long)(check_waves * draw_blocks));
+    if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
+  }
+  hipLaunchKernelGGL(check_kernel_of(p->check_vbits), dim3((unsigned)check_blocks), dim3(64 * cw),
+                     (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
+                     (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
+  if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
+  hipLaunchKernelGGL(p->lists_deg2 ? time_lists_kernel<true> : time_lists_kernel<false>, dim3((unsigned)time_blocks),
+                     dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
+                     (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
+                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave));
+  return check_hip(hipGetLastError());
 }
 
 int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_cand,
@@ -748,6 +968,8 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
+    if (!copy_on_slots && !sync_on_slots && !p->mb_set && !p->links_on)
+      return run_list_evaluation(p, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     // costs per micro-batch: their own table image and workgroup shape when the table sits in LDS
     const bool mb_lds = p->mb_set && p->mb_in_lds;
     const bool combo = p->links_on && p->mb_set;   // both variants: the setters made sure the tables exist
@@ -768,13 +990,12 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     const int draw_block = (int)std::clamp<int64_t>((12288 + row_words - 1) / row_words, 1, tab.cands_per_wave);
     // segment g starts on candidate g; the counter hands out the candidates after those
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(hip_stream), counter,
-                       (unsigned long long)(blocks * per_block));
+                       (unsigned long long)(blocks * per_block), 0ull);
     const bool one_class = tab.n_classes == 1;
     const SlotKernel kernel = sync_on_slots ? slot_kernel_of<kSlotSync>(p->slot_v, p->sync_deg2, one_class)
                               : copy_on_slots ? slot_kernel_of<kSlotCopy>(p->slot_v, p->slot_deg2, one_class)
                               : combo ? slot_kernel_of<kSlotPerMicrobatchLdsLinks>(p->slot_v, p->slot_deg2, one_class)
                               : links ? slot_kernel_of<kSlotLinks>(p->slot_v, p->slot_deg2, one_class)
-                              : !p->mb_set ? slot_kernel_ptr(p->slot_v, p->slot_deg2, one_class)
                               : (mb_lds ? slot_kernel_of<kSlotPerMicrobatchLds>(p->slot_v, p->slot_deg2, one_class)
                                         : slot_kernel_of<kSlotPerMicrobatch>(p->slot_v, p->slot_deg2, one_class));
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * L.waves), L.lds_bytes,
@@ -1561,7 +1782,7 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
   // segment g starts on set g; the counter hands out the sets after those
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(hip_stream), counter,
-                     (unsigned long long)(blocks * cpw));
+                     (unsigned long long)(blocks * cpw), 0ull);
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), (size_t)lds_bytes,
                      static_cast<hipStream_t>(hip_stream), p->tables, reinterpret_cast<const int32_t*>(d_policy),
                      d_inflight, reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets, (int)stride_words,
@@ -1654,7 +1875,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(hip_stream), counter,
-                     (unsigned long long)(blocks * best_waves * cpw));
+                     (unsigned long long)(blocks * best_waves * cpw), 0ull);
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * best_waves), (size_t)lds_bytes,
                      static_cast<hipStream_t>(hip_stream), tables, reinterpret_cast<const int32_t*>(d_policy),
                      d_inflight, nullptr, (long long)n_sets, (long long)n_sets, 0, nullptr, d_steps, d_status, counter,
@@ -1840,7 +2061,7 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   const int64_t row_words = (int64_t)p->D * stride_words;
   const int draw_block = (int)std::clamp<int64_t>((12288 + row_words - 1) / row_words, 1, times_tab.cands_per_wave);
   const bool one_class = p->stab.n_classes == 1;
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)(blocks * per_block));
+  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)(blocks * per_block), 0ull);
   hipLaunchKernelGGL(links ? slot_kernel_of<kSlotTimesLinks>(p->slot_v, p->slot_deg2, one_class)
                            : slot_kernel_of<kSlotTimes>(p->slot_v, p->slot_deg2, one_class),
                      dim3((unsigned)blocks), dim3(64 * L.waves), L.lds_bytes, st, times_tab, d_ops, (long long)n_cand,
@@ -1883,7 +2104,7 @@ int fpsched_wslide_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int
   const int64_t blocks = L.blocks;
   const int64_t row_words = (int64_t)p->D * stride_words;
   const int draw_block = (int)std::clamp<int64_t>((12288 + row_words - 1) / row_words, 1, tab.cands_per_wave);
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)(blocks * per_block));
+  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)(blocks * per_block), 0ull);
   hipLaunchKernelGGL(links ? slot_kernel_of<kSlotSlideLinks>(p->slot_v, p->slot_deg2, tab.n_classes == 1)
                            : slot_kernel_of<kSlotSlide>(p->slot_v, p->slot_deg2, tab.n_classes == 1), dim3((unsigned)blocks),
                      dim3(64 * L.waves), L.lds_bytes, st, tab, d_ops, (long long)n_cand,

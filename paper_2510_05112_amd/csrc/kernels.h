@@ -55,7 +55,7 @@ constexpr int kSlotMaxThreads = 64 * kSlotMaxWaves;
 // per chunk the micro-batches per item | items << 16.
 // MODE kSlotSlide: the weight-gradient sliding pass without its lists: the results of the lists the two-pass form
 // would write, in one kernel (tables as for kSlotTimes plus the W items' costs at T.off_w; 16 bytes of LDS more).
-constexpr int kSlotPlain = 0, kSlotTimes = 1, kSlotPerMicrobatch = 2, kSlotPerMicrobatchLds = 3, kSlotLinks = 4,
+constexpr int kSlotTimes = 1, kSlotPerMicrobatch = 2, kSlotPerMicrobatchLds = 3, kSlotLinks = 4,
               kSlotTimesLinks = 5, kSlotPerMicrobatchLdsLinks = 6, kSlotCopy = 7, kSlotSync = 8, kSlotSlide = 9,
               kSlotSlideLinks = 10;   // kSlotSlide under the link model
 constexpr int kSlotCopyWords = 32;
@@ -66,7 +66,25 @@ __global__ void eval_slot_kernel(SlotTables T, const uint16_t* ops, long long n_
                                  uint32_t* out_start8, int32_t* out_stop, const int32_t* mb_rows,
                                  uint32_t* out_escape, int escape_cap);
 
-__global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value);
+// The list evaluation in two passes.  check_rows_kernel: one lane per (candidate, device) row, rows_per_wave of them per
+// wavefront; per row out_info (kRow* | stop, then the busy time in the low half) and out_peak.  dynamic: more blocks of
+// rows than resident wavefronts, taken draw_blocks at a time, the further ones from counter[1]; else it sets *counter for the timing pass.
+// time_lists_kernel: reads out_info from out_idle, writes the results.  DEG2 = some stage has two inputs or outputs.
+constexpr int kCheckMaxThreads = 512;
+constexpr int kCheckWavesPerSimd = 3;
+constexpr int kTimeMaxThreads = 1024;
+constexpr int kTimeWindowBytes = 2 * 64 * 32;   // op windows of a wavefront of the timing pass
+template <int VBITS>   // 0, 1, 2: up to 1, 2, 4 stages per device
+__global__ void check_rows_kernel(ListTables T, const uint16_t* ops, long long n_rows, int stride, int rows_per_wave,
+                                  long long* out_info, int* out_peak, unsigned long long* counter,
+                                  unsigned long long counter_value, int draw_blocks, int dynamic);
+template <bool DEG2>
+__global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
+                                  long long* out_makespan, long long* out_idle, int* out_peak,
+                                  unsigned char* out_flags, unsigned long long* next_candidate, int draw_block);
+
+// counter[0] = value, counter[1] = value2
+__global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2 = 0);
 
 // V as above; DEG = bound on the in- and out-degree of a stage (1, 2, or 0 = any).  One wavefront per
 // workgroup, 64 / lanes_per_cand parameter sets per wavefront at a time; next_set: a counter in

@@ -1,0 +1,246 @@
+// Order pass of the list evaluation: everything about a device's list that does not depend on time.
+//
+// Whether the ops of a list respect the activation state machine, the peak of the resident memory and the summed
+// durations are functions of the order of the list alone: only a device's own ops change the states of its
+// activations, and an op that is not legal where it stands can never issue.  So this pass walks every row on its
+// own, one lane per (candidate, device) row and 64 rows per wavefront, no lane ever waiting for another, and
+// leaves per row where the list stops, why, its peak and its busy time.  What is left for the timing pass
+// (timing.hip), where most lanes wait for inputs most of the time, are the dependencies between devices.
+//
+// Per word: its table row (8 bytes in LDS, addressed by the top five bits of the word and the device) and its
+// activation state, one byte per (chunk, micro-batch) in lane-private LDS.  A legal op's next state does not
+// depend on the state found, so the eight words of a group read the old state and write the new one in list order
+// without waiting for each other, and the comparisons follow when all have arrived.  A group in which some lane's
+// list stops (its END word, or an op that is not legal) is gone over again for those lanes: the states behind the
+// stop are put back, the sums taken up to it.
+//
+// Bounds: about ten vector instructions and ten clocks of LDS per 64 words, and the op words once from HBM.  A lane
+// reads its row 64 bytes at a time.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels.h"
+#include "lds_access.h"
+
+namespace fpsched {
+
+namespace {
+
+typedef unsigned short u16_pair __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned bits_of(u16_pair v) { return __builtin_bit_cast(unsigned, v); }
+__device__ __forceinline__ u16_pair pair_of(unsigned v) { return __builtin_bit_cast(u16_pair, v); }
+
+constexpr unsigned kPadState = 14u;   // state of the byte behind a chunk's last micro-batch: no op requires it
+
+}  // namespace
+
+// VBITS: bits of the chunk field that select a chunk's states (0, 1, 2: up to 1, 2, 4 stages per device)
+template <int VBITS>
+__global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_eu(kCheckWavesPerSimd, kCheckWavesPerSimd))) void check_rows_kernel(
+    ListTables T, const uint16_t* __restrict__ ops, long long n_rows, int stride, int rows_per_wave,
+    long long* __restrict__ out_info, int* __restrict__ out_peak, unsigned long long* __restrict__ counter,
+    unsigned long long counter_value, int draw_blocks, int dynamic) {
+  extern __shared__ int32_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // where the timing pass draws its candidates from (dynamic: set, with the counter of this pass behind it, by a kernel
+  // in front of this one)
+  if (!dynamic && blockIdx.x == 0 && tid == 0) *counter = counter_value;
+  for (int i = tid; i < T.n_check_ints + 2 * T.D; i += blockDim.x) lds[i] = T.ints[T.off_check + i];
+  const unsigned lds0 = lds_address(lds);
+  const int m = T.m;
+  // the states of this wavefront's rows, then of this lane's: one byte per (chunk, micro-batch), m + 1 bytes per chunk
+  const unsigned wave_states = lds0 + (unsigned)T.check_shared_bytes + (unsigned)wave * (unsigned)T.check_wave_bytes;
+  const unsigned state = wave_states + (unsigned)(lane < rows_per_wave ? lane : 0) * (unsigned)T.state_bytes;
+  __syncthreads();
+  // The wavefronts of the resident workgroups take blocks of rows from a counter, none waiting for another: as one
+  // workgroup per few blocks, a compute unit's LDS stays with the workgroup until its last row has ended, and with equal
+  // shares the slowest wavefronts took a third longer than the average one.
+  const long long n_blocks = (n_rows + rows_per_wave - 1) / rows_per_wave;
+  const unsigned row_bytes = (unsigned)T.D * 8u;
+  const unsigned dev_table = lds0 + (unsigned)T.n_check_ints * 4u;
+  // the row that this lane walks, the next one, and the words of either that are on their way or in registers: 64 bytes
+  // of the row at a time, the next ones requested when their walk begins
+  long long r = 0;
+  int d = 0;
+  bool active = false;
+  const uint16_t* row = ops;
+  constexpr int kGroups = 4;
+  uint4 first[kGroups], second[kGroups];
+  auto request = [&](uint4 (&piece)[kGroups], int at) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g)
+      if (at + 8 * g < stride) piece[g] = *reinterpret_cast<const uint4*>(row + at + 8 * g);
+  };
+  auto take = [&](long long block) {
+    r = block * rows_per_wave + lane;
+    active = lane < rows_per_wave && r < n_rows;
+    r = active ? r : 0;
+    d = n_rows >> 31 ? (int)(r % T.D) : (int)((unsigned)r % (unsigned)T.D);
+    row = ops + (size_t)r * (size_t)stride;
+    request(first, 0);
+  };
+  // (drawn several at a time: atomics on one address complete at some 8e7 per second)
+  long long block = ((long long)blockIdx.x * (blockDim.x >> 6) + wave) * draw_blocks;
+  int left = draw_blocks;
+  if (block < n_blocks) take(block);
+  while (block < n_blocks) {
+  // the next block's number is on its way during the walk, its first words during the end of this block
+  long long drawn = n_blocks;
+  const bool draw = --left == 0;
+  if (draw && dynamic && lane == 0) drawn = (long long)atomicAdd(counter + 1, (unsigned long long)draw_blocks);
+  for (int i = lane * 16; i < T.check_wave_bytes; i += 1024) lds_write<lds_int4>(wave_states + i, lds_int4{0, 0, 0, 0});
+  const lds_int2 dev = lds_read<lds_int2>(dev_table + (unsigned)d * 8u);
+  const int n_chunks = dev.x, cap = dev.y;
+  if (active)
+    for (int c = 0; c < n_chunks; ++c) lds_write<uint8_t>(state + c * (m + 1) + m, (uint8_t)kPadState);
+  const unsigned meta = lds0 + (unsigned)d * 8u;
+  int mem = 0, pk = 0;
+  unsigned busy = 0u;
+  bool alive = active;
+  int stop = stride;
+  unsigned status = 0u;
+
+  // A group is eight words, in three stages: fetch the table rows; read the old states and write the new ones, in list
+  // order; compare and sum up.  The rows of a group are fetched before the comparisons of the group in front of it,
+  // which cover their latency, as the fetching of the next rows covers that of the states.
+  struct Group {
+    uint4 q;
+    unsigned x[8], y[8], old[8];
+  };
+  auto pair_word = [](const uint4& q, int k) -> unsigned { return k < 2 ? q.x : (k < 4 ? q.y : (k < 6 ? q.z : q.w)); };
+  auto word_of = [&](const uint4& q, int k) -> unsigned { return (k & 1) ? pair_word(q, k) >> 16 : pair_word(q, k) & 0xffffu; };
+  const unsigned m1 = (unsigned)m + 1u;
+  const unsigned state1 = state + m1;
+  const u16_pair limit = {(unsigned short)m, (unsigned short)m};
+  auto row_of = [&](const uint4& q, int k) -> unsigned { return __umul24(word_of(q, k) >> 11, row_bytes) + meta; };
+  auto fetch = [&](Group& G, const uint4& q) {
+    G.q = q;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const lds_int2 M = lds_read<lds_int2>(row_of(q, k));
+      G.x[k] = (unsigned)M.x;
+      G.y[k] = (unsigned)M.y;
+    }
+  };
+  // where the state of a word's activation is: a micro-batch out of range looks at the byte behind its chunk, a chunk that
+  // the device does not have at some chunk's bytes -- the op is found out either way and its write taken back
+  auto state_of = [&](const uint4& q, int k) -> unsigned {
+    const unsigned two = bits_of(__builtin_elementwise_min(pair_of(pair_word(q, k) & 0x07ff07ffu), limit));
+    unsigned at_chunk = state;
+    if (VBITS == 1) {   // (all ones where the chunk bit is set)
+      const unsigned second = (unsigned)((int)(pair_word(q, k) << ((k & 1) ? 4 : 20)) >> 31);
+      at_chunk = (second & state1) | (~second & state);
+    }
+    if (VBITS == 2) at_chunk = __umul24((word_of(q, k) >> 11) & 3u, m1) + state;
+    asm("" : "+v"(at_chunk));   // (one addition with a half-word operand remains)
+    return at_chunk + ((k & 1) ? two >> 16 : two & 0xffffu);
+  };
+  auto exchange = [&](Group& G) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const unsigned at = state_of(G.q, k);
+      G.old[k] = lds_read<uint8_t>(at);
+      lds_write<uint8_t>(at, (uint8_t)G.x[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) busy += G.y[k];
+  };
+  auto compare = [&](Group& G, int at) {
+    const int mem0 = mem, pk0 = pk;
+    unsigned long long bad[8], any = 0ull;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      asm volatile("v_cmp_ne_u32_sdwa %0, %1, %2 src0_sel:DWORD src1_sel:BYTE_1" : "=s"(bad[k]) : "v"(G.old[k]), "v"(G.x[k]));
+      any |= bad[k];
+      mem += (int)((G.x[k] >> 16) & 0xffu);
+      pk = max(pk, mem);
+      mem -= (int)(G.x[k] >> 24);
+    }
+    if (any != 0ull && __builtin_amdgcn_inverse_ballot_w64(any)) {
+      // the list stops in this group: put back the states from the stop on, take the sums up to it
+      int first_bad = 0;
+#pragma unroll
+      for (int k = 7; k >= 0; --k) first_bad = __builtin_amdgcn_inverse_ballot_w64(bad[k]) ? k : first_bad;
+      mem = mem0; pk = pk0;
+      unsigned stop_row = 0u, stop_word = 0u;
+#pragma unroll
+      for (int k = 7; k >= 0; --k)
+        if (k >= first_bad) {
+          lds_write<uint8_t>(state_of(G.q, k), (uint8_t)G.old[k]);
+          busy -= lds_read<uint32_t>(row_of(G.q, k) + 4u);
+        }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (k < first_bad) {
+          mem += (int)((G.x[k] >> 16) & 0xffu);
+          pk = max(pk, mem);
+          mem -= (int)(G.x[k] >> 24);
+        }
+        if (k == first_bad) {
+          stop_row = G.x[k];
+          stop_word = word_of(G.q, k);
+        }
+      }
+      // (an END word ends the list whatever its low bits are)
+      if ((stop_word >> 13) != 0u)
+        status = kRowStuck | ((((stop_row >> 8) & 0xffu) == kNoState || (int)(stop_word & 0x7ffu) >= m) ? kRowMalformed : 0u);
+      stop = at + first_bad;
+      alive = false;
+    }
+  };
+
+  Group A, B;
+  auto walk = [&](uint4 (&piece)[kGroups], uint4 (&next)[kGroups], int at) {
+    request(next, at + 8 * kGroups);
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      Group& now = (g & 1) ? B : A;
+      Group& then = (g & 1) ? A : B;
+      // (behind the end of the row this fetches rows of whatever words the registers hold, which nobody looks at)
+      fetch(then, g + 1 < kGroups ? piece[g + 1] : next[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (alive) compare(now, at + 8 * g);
+      alive = alive && at + 8 * g + 8 < stride;
+      if (alive) exchange(then);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  fetch(A, first[0]);
+  if (alive) exchange(A);
+  for (int at = 0;; at += 16 * kGroups) {
+    walk(first, second, at);
+    if (__ballot(alive) == 0ull) break;
+    walk(second, first, at + 8 * kGroups);
+    if (__ballot(alive) == 0ull) break;
+  }
+  // (a list that fills its row stops at the row's end: stop is the stride)
+  const long long r_done = r;
+  const bool was_active = active;
+  block = draw ? __shfl(drawn, 0) : block + 1;
+  if (draw) left = draw_blocks;
+  if (block < n_blocks) take(block);
+  if (was_active) {
+  // every activation consumed?  (the byte behind each chunk is set to the final state first)
+  for (int c = 0; c < n_chunks; ++c) lds_write<uint8_t>(state + c * (m + 1) + m, (uint8_t)T.terminal);
+  const unsigned want = (unsigned)T.terminal * 0x01010101u;
+  const int n_bytes = n_chunks * (m + 1);
+  unsigned differ = 0u;
+  int i = 0;
+  for (; i + 32 <= n_bytes; i += 32)
+#pragma unroll
+    for (int k = 0; k < 32; k += 4) differ |= lds_read<uint32_t>(state + i + k) ^ want;
+  for (; i + 4 <= n_bytes; i += 4) differ |= lds_read<uint32_t>(state + i) ^ want;
+  if (i < n_bytes) differ |= (lds_read<uint32_t>(state + i) ^ want) & ((1u << (8 * (n_bytes - i))) - 1u);
+  if (differ != 0u) status |= kRowIncomplete;
+  if (pk > cap) status |= kRowOverCap;
+  out_info[r_done] = (long long)(((unsigned long long)((unsigned)stop | status) << 32) | busy);
+  out_peak[r_done] = pk * T.unit_scale;
+  }
+  }
+}
+
+template __global__ void check_rows_kernel<0>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+template __global__ void check_rows_kernel<1>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+template __global__ void check_rows_kernel<2>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+
+}  // namespace fpsched

@@ -1,0 +1,378 @@
+// Timing pass of the list evaluation: start and finish times across the devices, for lists the order pass (rows.hip)
+// has walked.  Any per-device op order, any stage DAG with at most two inputs and two outputs per stage.
+//
+// Mapping: lane = (candidate, pair of neighbouring devices), ceil(D / 2) lanes per candidate, as many candidates per
+// wavefront as fit its 64 lanes; the wavefronts of a workgroup are independent and only share one LDS copy of the op
+// table.  The grid is persistent: a segment (the lanes of one candidate) that finishes takes the next unevaluated
+// candidate, from a global counter through a small pool per wavefront, while the other segments keep going.  A lane
+// walks the lists of its two devices with cursors in registers, in turn: the even devices issue in one step (every
+// device whose next op has its inputs), the odd ones in the next.  A pair of steps in which no lane of a segment moves
+// ends that candidate (lists exhausted, or deadlock).
+//
+// Why in turn: a step costs the wavefront the same instructions however few of its lanes issue, and what a schedule's
+// steps are spent on are chains of dependencies from device to neighbouring device, forward down the pipeline,
+// backward up again.  With all devices in every step such a chain takes a step per device and most lanes wait; with
+// even and odd devices in turn each link of the chain is the other half's turn, so twice as many candidates per
+// wavefront move at the same speed along the chains, and only ops that follow each other on one device take two steps.
+// Counted on the CPU over the candidates of the benchmark configurations: 1.25 to 1.9 times fewer wavefront steps.
+//
+// Finish times travel through per-micro-batch mail slots in LDS.  The edges of the stage DAG are split on the host
+// into classes (chains of edges in which each edge starts at the stage the previous one ends in; a plain pipeline is
+// one class).  For one micro-batch at most one edge of a class carries a live value at a time -- the value of F(a,j)
+// on edge a->b is dead once F(b,j) has issued, and only then can the next edge of the class be produced -- so a
+// class needs ONE slot per micro-batch and direction, tagged with the stage that produced it:
+// slot[dir][class][j] = finish << 8 | producer stage.  A consumer finds its input iff the tag names its upstream
+// stage.  No order of micro-batches is assumed and a producer never has to wait for room.
+//
+// Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
+// of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
+//
+// What bounds it: LDS and vector issue, about equally (counters of one launch over 65,536 candidates of 32 devices, 128
+// micro-batches, two chunks: LDS busy 85 % of the time, vector units 73 %).  Everything that does not need the order
+// between devices is the order pass's, which also says where each list stops, so that no word in front of that needs
+// a check.  A step is five vector instructions to decide (the slot's address from the row; an addition that gives the
+// ready time with a low byte that is zero iff the slot carries the expected tag; one byte compare) and nine to issue and
+// to decode the next word; in LDS the slot read (random addresses: half of it bank conflicts), the row, the next word
+// and the slot written.  The row is fetched when the device issues and first looked at in its next step, so the other
+// half's step covers the wait.  That batch took 4.88 ms when one kernel with all devices in every round did the order
+// pass's work as well; now 1.07 ms (rows.hip) + 2.06 ms.
+//
+// Op words reach a device through a ring of sixteen words in LDS that is topped up every eighth round, eight words at a
+// time, where at most seven are unread.  A device that issues one op per round so never runs dry (it reads the word two
+// behind the one it issues; after every top-up eight or more are unread), and sixteen places hold the words unread, at
+// most fifteen, and the END word that is planted behind a full row.  Words are requested 32 bytes at a time, as soon as
+// the registers they arrive in are free: with the rows of a compute unit's candidates in flight the lines do not stay in
+// the L2 cache from one request to the next, and requests of 16 bytes fetched every line six times (24 GB for a 3.8 GB
+// batch).  (Rings of 32 words leave room for 11 instead of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth
+// round: 2.19 ms.)
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels.h"
+#include "lds_access.h"
+
+namespace fpsched {
+
+namespace {
+
+constexpr unsigned kRounds = 8;          // rounds (a step of either half) between two top-ups
+constexpr unsigned kRingBytes = 32u;     // ring of sixteen words
+constexpr unsigned kPieceBytes = 16u;    // what is landed at a time; a request is two of them
+constexpr unsigned kLandAt = 16u;        // land where at most seven words are unread: loaded - cursor <= 16 bytes
+constexpr unsigned kWindowBytes = 64u * kRingBytes;   // the rings of one half of a wavefront's devices
+
+}  // namespace
+
+template <bool DEG2>
+__global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
+    ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
+    long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
+    unsigned long long* __restrict__ next_candidate, int draw_block) {
+  constexpr unsigned kRowBytes = 16u;
+  extern __shared__ int32_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
+  for (int i = tid; i < T.n_time_ints; i += blockDim.x) lds[i] = T.ints[i];
+  const unsigned lds0 = lds_address(lds);
+  const int seg = lane / P, pair = lane - seg * P;
+  const bool lane_ok = seg < cpw;
+  const int d0 = 2 * pair;
+  const bool has_odd = d0 + 1 < D;
+  const unsigned wave_at = lds0 + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)T.wave_bytes;
+  unsigned slot_base = wave_at + 2u * kWindowBytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * 4u;
+  asm volatile("" : "+v"(slot_base));   // one register, not a sum to be re-associated every round
+  const unsigned own_word = slot_base + (unsigned)(lane_ok ? d0 : 0) * 4u;
+  const int own_at = (lane_ok ? d0 : 0) * 4;   // that word as a row's slot field
+  const unsigned at_max = slot_base + ((unsigned)D + 1u) * 4u;
+  lds_write<uint32_t>(own_word, kOwnTag);   // what a lane without an op looks at
+  __syncthreads();
+
+  // segment bookkeeping on the scalar unit: bit seg * P stands for segment seg
+  unsigned long long base_bits = 0ull;
+  for (int s = 0; s < cpw; ++s) base_bits |= 1ull << (s * P);
+  const unsigned long long high_bits = base_bits << (P - 1);
+  const unsigned long long seg_lanes = ((1ull << P) - 1ull) << (seg * P & 63);   // (P <= 32)
+  const unsigned seg_lo = (unsigned)seg_lanes, seg_hi = (unsigned)(seg_lanes >> 32);
+  auto any_in_segment = [&](unsigned long long ballot) -> bool {
+    return (((unsigned)ballot & seg_lo) | ((unsigned)(ballot >> 32) & seg_hi)) != 0u;
+  };
+
+  const unsigned row_stride = (unsigned)D * kRowBytes;
+  const unsigned stride2 = (unsigned)stride * 2u;
+
+  // one device of the lane: its op window, and the op under its cursor, decoded.  A device without an op looks at its
+  // own word with an L that keeps it waiting.
+  struct Device {
+    unsigned win, meta;
+    unsigned free_at8;
+    unsigned j4, w_next;    // the word under the cursor << 2, and the word behind it
+    lds_int4 R;             // the op's table row: L, dur | tag, slot, second edge
+    unsigned loaded2;   // bytes of the row that are in the ring (a device without a list asks for none)
+    unsigned pos2;      // byte position of w_next; the device has issued pos2 / 2 - 1 ops
+    unsigned info;      // what the order pass left for this row: kRow* | stop
+    unsigned busy;
+    uint4 pend0, pend1;
+    int n_pend;         // pieces requested and not landed: pend0, then pend1
+  };
+  Device even, odd;
+  auto idle_device = [&](Device& x) {
+    x.R = lds_int4{1, 0, own_at, 0};
+    x.loaded2 = 0x40000000u;
+    x.pos2 = 2u;
+    x.info = 0u;
+    x.n_pend = 0;
+  };
+  auto set_up = [&](Device& x, int k) {
+    // (lanes eight apart share their banks: the halves of their rings are in different orders)
+    x.win = wave_at + (unsigned)k * kWindowBytes + (unsigned)lane * kRingBytes + (((unsigned)lane >> 3) & 1u) * 16u;
+    x.meta = lds0 + (unsigned)(k * P + pair) * kRowBytes;
+    x.free_at8 = 0u; x.j4 = 0u; x.w_next = 0u; x.busy = 0u;
+    x.pend0 = make_uint4(0u, 0u, 0u, 0u); x.pend1 = x.pend0;
+    idle_device(x);
+  };
+  set_up(even, 0);
+  set_up(odd, 1);
+
+  long long cand = 0;
+  const char* row = reinterpret_cast<const char*>(ops);   // of the even device; the odd one's follows it
+  bool running = false, fresh = true, priming = false;
+  bool any_special = true;          // wave-uniform: some segment starts, or has just started, a candidate
+  bool any_stuck = false;           // wave-uniform: the list of some device stops at an op that may not issue
+  unsigned long long idle_lanes = ~0ull;
+  bool first_draw = true;
+  unsigned long long pool_next = 0ull, pool_end = 0ull;
+
+  // fetch the row of the word that comes under the cursor; what follows from the row is worked out when the device's
+  // next step begins, so that the other half's step covers the wait for it
+  auto decode = [&](Device& x, unsigned word) {
+    const unsigned at = __umul24(word >> 11, row_stride) + x.meta;
+    x.j4 = word << 2;
+    x.R = lds_read<lds_int4>(at);
+  };
+  // address of a byte position in the device's ring
+  auto in_ring = [&](const Device& x, unsigned at2) -> unsigned {
+    return __builtin_amdgcn_bitop3_b32(at2, kRingBytes - 1u, x.win, 0x6a);   // (at2 & mask) ^ win
+  };
+  auto store_piece = [&](Device& x) {
+    lds_write<lds_int4>(in_ring(x, x.loaded2), lds_int4{(int)x.pend0.x, (int)x.pend0.y, (int)x.pend0.z, (int)x.pend0.w});
+    x.pend0 = x.pend1;
+    --x.n_pend;
+  };
+  auto request = [&](Device& x, const char* from, unsigned at2) {
+    x.pend0 = *reinterpret_cast<const uint4*>(from + at2);
+    x.n_pend = 1;
+    if (at2 + kPieceBytes < stride2) {
+      x.pend1 = *reinterpret_cast<const uint4*>(from + at2 + kPieceBytes);
+      x.n_pend = 2;
+    }
+  };
+  // land what has been asked for, where there is room for it
+  auto land = [&](Device& x) {
+    if (x.n_pend > 0 && (int)(x.loaded2 - x.pos2) <= (int)kLandAt) {
+      store_piece(x);
+      // the device goes no further than where the order pass says its list stops (an END word does that by itself)
+      if (any_stuck) {
+        const unsigned stop2 = (x.info & kRowStop) * 2u;
+        if (stop2 - x.loaded2 < kPieceBytes) lds_write<uint16_t>(in_ring(x, stop2), (uint16_t)0);
+      }
+      x.loaded2 += kPieceBytes;
+      // a row that fills its stride has no END word: plant one behind it
+      if (x.loaded2 >= stride2) lds_write<uint16_t>(in_ring(x, stride2), (uint16_t)0);
+    }
+  };
+  auto ask = [&](Device& x, const char* from) {
+    if (x.n_pend == 0 && x.loaded2 < stride2) request(x, from, x.loaded2);
+  };
+  // the head of the row has arrived: the device joins in
+  auto join = [&](Device& x) {
+    x.loaded2 = 0u;
+    store_piece(x);
+    x.loaded2 = kPieceBytes;
+    if (x.n_pend > 0) {
+      store_piece(x);
+      x.loaded2 = 2u * kPieceBytes;
+    }
+    const unsigned stop2 = (x.info & kRowStop) * 2u;
+    const unsigned w = stop2 == 0u ? 0u : lds_read<uint16_t>(in_ring(x, 0u));
+    x.w_next = stop2 <= 2u ? 0u : lds_read<uint16_t>(in_ring(x, 2u));
+    if (stop2 <= x.loaded2) lds_write<uint16_t>(in_ring(x, stop2), (uint16_t)0);   // (behind a full row of one or two pieces too)
+    decode(x, w);
+    x.pos2 = 2u;
+  };
+  // one step of one half of the devices; returns the lanes that issued
+  auto step = [&](Device& x) -> unsigned long long {
+    asm volatile("" : "+v"(x.R), "+v"(x.j4));   // (the row stays one value until here: no earlier wait for it)
+    const unsigned at_slot = (x.j4 & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
+    const unsigned ready8 = lds_read<uint32_t>(at_slot) + (unsigned)x.R.x;
+    unsigned long long moved;
+    const unsigned zero = 0u;
+    asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready8), "v"(zero));
+    unsigned long long issue = moved;
+    if (DEG2) {
+      // an op with two inputs waits for its second one first: once that is there the device's free time takes it in
+      // (nothing but the start of this op looks at that time) and the op waits for its first
+      const unsigned long long absorb = moved & __ballot(x.R.w < 0);
+      if (absorb != 0ull) {
+        if (__builtin_amdgcn_inverse_ballot_w64(absorb)) {
+          x.free_at8 = max(x.free_at8, ready8);
+          const lds_int2 first = lds_read<lds_int2>(lds0 + ((unsigned)x.R.w & 0xffffu));
+          x.R.x = first.x;
+          x.R.z = first.y;
+          x.R.w &= 0x7fffffff;
+        }
+        issue &= ~absorb;
+      }
+    }
+    if (__builtin_amdgcn_inverse_ballot_w64(issue)) {
+      const unsigned val = max(x.free_at8, ready8) + (unsigned)x.R.y;
+      x.free_at8 = val & 0xffffff00u;
+      lds_write<uint32_t>(at_slot, val);
+      if (DEG2 && ((unsigned)x.R.w & kRowTwoOut) != 0u) {
+        const unsigned second = lds_read<uint32_t>(lds0 + ((unsigned)x.R.w & 0xffffu) + 8u);
+        lds_write<uint32_t>((x.j4 & (second >> 16)) + slot_base + (second & 0xffffu), val);
+      }
+      decode(x, x.w_next);
+      x.pos2 += 2u;
+      x.w_next = lds_read<uint16_t>(in_ring(x, x.pos2));
+    }
+    return moved;
+  };
+
+  // Every candidate ends after at most 2 D * stride + 2 rounds (each round but its last issues at least one of its at
+  // most D * stride ops, or takes in the second input of one), so the bound below is never reached; it only makes sure the wavefront leaves the loop
+  // whatever happens.
+  const unsigned long long bound = (2ull * (unsigned)D * (unsigned)stride + 16ull) * ((unsigned long long)n_cand + 1ull);
+  const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
+  for (unsigned round = 0; round < max_rounds; round += kRounds) {
+    land(even);
+    land(odd);
+    // ---- the rare part, only when some segment starts or has just started a candidate
+    if (any_special) {
+      // segments restarted at the previous top-up: the heads of their rows have arrived, they join in and ask for
+      // their second pieces like any other, below
+      if (priming) {
+        join(even);
+        if (has_odd) join(odd);
+      }
+      any_stuck = __ballot(running && ((even.info | odd.info) & kRowStuck) != 0u) != 0ull;
+      priming = false;
+      // hand the segments that ask for one (lane 0 of each speaks for it) their next candidate
+      const unsigned long long want = __ballot(fresh && !first_draw && pair == 0 && lane_ok);
+      unsigned long long from_pool = 0ull;
+      if (want != 0ull) {
+        const int n_want = __popcll(want);
+        const int have = (int)(pool_end - pool_next);
+        unsigned long long new_base = 0ull;
+        int amount = 0;
+        if (n_want > have) {
+          amount = max(draw_block, n_want - have);
+          if (lane == 0) new_base = atomicAdd(next_candidate, (unsigned long long)amount);
+          new_base = __shfl(new_base, 0, 64);
+        }
+        const int rank = __popcll(want & ((1ull << lane) - 1ull));   // among the asking segments
+        from_pool = rank < have ? pool_next + (unsigned)rank : new_base + (unsigned)(rank - have);
+        if (n_want > have) {
+          pool_next = new_base + (unsigned)(n_want - have);
+          pool_end = new_base + (unsigned)amount;
+        } else {
+          pool_next += (unsigned)n_want;
+        }
+      }
+      if (fresh) {
+        fresh = false;
+        unsigned long long drawn = ((unsigned long long)blockIdx.x * (blockDim.x >> 6) + wave) * cpw + seg;
+        if (!first_draw) drawn = __shfl(from_pool, lane_ok ? seg * P : 0, 64);
+        first_draw = false;
+        cand = (long long)drawn;
+        running = lane_ok && cand < n_cand;
+        priming = running;
+        even.free_at8 = 0u;
+        odd.free_at8 = 0u;
+        if (running) {
+          const int n4 = T.cand_slots >> 2;
+          for (int i = pair; i < n4; i += P)
+            lds_write<lds_int4>(slot_base + (unsigned)i * 16u, lds_int4{(int)kEmptySlot, (int)kEmptySlot, (int)kEmptySlot, (int)kEmptySlot});
+          lds_write<uint32_t>(own_word, kOwnTag);
+          if (has_odd) lds_write<uint32_t>(own_word + 4u, kOwnTag);
+          if (pair == 0) lds_write<uint32_t>(at_max, 0u);
+          const long long r = cand * D + d0;
+          row = reinterpret_cast<const char*>(ops + (size_t)r * (size_t)stride);
+          request(even, row, 0u);
+          const unsigned long long left = (unsigned long long)out_idle[r];
+          even.info = (unsigned)(left >> 32);
+          even.busy = (unsigned)left;
+          if (has_odd) {
+            request(odd, row + stride2, 0u);
+            const unsigned long long left_odd = (unsigned long long)out_idle[r + 1];
+            odd.info = (unsigned)(left_odd >> 32);
+            odd.busy = (unsigned)left_odd;
+          }
+        }
+      }
+      // segments that are priming do not count as running yet (nothing can move in them)
+      const unsigned long long all_running = __ballot(running);
+      const unsigned long long primers = __ballot(priming);
+      idle_lanes = ~(all_running & ~primers);
+      any_special = primers != 0ull;
+      if (all_running == 0ull) break;   // every segment of the wave is out of work
+    }
+    ask(even, row);
+    ask(odd, row + stride2);
+#pragma unroll
+    for (unsigned sub = 0; sub < kRounds; ++sub) {
+      const unsigned long long moved_even = step(even);
+      const unsigned long long moved_odd = step(odd);
+      // A segment none of whose lanes issued is finished, and stays so: nothing it reads changes any more.  It could
+      // only be restarted at the next top-up anyway, so only the last round in front of it looks.  Cheap scalar
+      // pre-test: does the issue mask, with the lanes of idle segments set, contain an all-zero field of P bits?
+      // (x - lows) & ~x & highs is non-zero iff some field of x is zero.
+      if (sub == kRounds - 1) {
+        const unsigned long long x = moved_even | moved_odd | idle_lanes;
+        if (((x - base_bits) & ~x & high_bits) != 0ull) {
+          const bool ended = running && !priming && !any_in_segment(x);
+          // (a device that a lane does not have counts as one whose list is exhausted)
+          const unsigned even_at = (even.pos2 >> 1) - 1u, odd_at = has_odd ? (odd.pos2 >> 1) - 1u : 0u;
+          const unsigned both = even.info | odd.info;
+          const bool even_stops = even_at == (even.info & kRowStop), odd_stops = odd_at == (odd.info & kRowStop);
+          const bool stuck = any_in_segment(__ballot(!even_stops || !odd_stops || (both & kRowStuck) != 0u));
+          const bool malformed = any_in_segment(__ballot((even_stops && (even.info & kRowMalformed) != 0u) || (odd_stops && (odd.info & kRowMalformed) != 0u)));
+          const bool unfinished = any_in_segment(__ballot((both & kRowIncomplete) != 0u));
+          const bool over = any_in_segment(__ballot((both & kRowOverCap) != 0u));
+          if (ended) {
+            // the latest finish, in a word that was cleared when the segment started
+            atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at8, odd.free_at8));
+            const unsigned ms = lds_read<uint32_t>(at_max) >> 8;
+            const unsigned flags = stuck ? kDeadlock | (malformed ? kIncomplete : 0u)
+                                         : (unfinished ? (unsigned)kIncomplete : (over ? (unsigned)kOverCap : 0u));
+            const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
+            const long long r = cand * D + d0;
+            out_idle[r] = failed ? -1ll : (long long)((int)ms - (int)even.busy);
+            if (failed) out_peak[r] = -1;
+            if (has_odd) {
+              out_idle[r + 1] = failed ? -1ll : (long long)((int)ms - (int)odd.busy);
+              if (failed) out_peak[r + 1] = -1;
+            }
+            if (pair == 0) {
+              out_makespan[cand] = failed ? 0x7fffffffffffffffll : (long long)ms;
+              out_flags[cand] = (unsigned char)flags;
+            }
+            running = false;
+            fresh = true;
+            idle_device(even);
+            idle_device(odd);
+          }
+          // the finished segments stop counting as running at once
+          idle_lanes = ~__ballot(running && !priming);
+          any_special = true;
+        }
+      }
+    }
+  }
+}
+
+template __global__ void time_lists_kernel<false>(ListTables, const uint16_t*, long long, int, long long*, long long*, int*,
+                                                  unsigned char*, unsigned long long*, int);
+template __global__ void time_lists_kernel<true>(ListTables, const uint16_t*, long long, int, long long*, long long*, int*,
+                                                 unsigned char*, unsigned long long*, int);
+
+}  // namespace fpsched
