@@ -124,6 +124,9 @@ struct SlotTables {
 //     3 if the op has a second input or output: byte offset of a second row | kRowTwoOut | sign bit: two inputs.  An op
 //       with two inputs waits for its second one first: words 0 and 2 are then the second input's.
 //   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 unused
+//   Wide form (times beyond 24 bits; a slot is two dwords, the time and the tag): word 0 is the latency, word 1 the
+//   duration, word 3 the tag the op leaves | the tag it expects << 8 | number of 16-byte rows in front of its second row
+//   << 16 | the two flags; word 3 of a second row is the tag expected on the first edge << 8.
 //   Slots of a candidate, in dwords: [0, D) the devices' own words, D + 1
 //   for the makespan, then from list_slots_at(D) on class * m for backward values, (classes + class) * m for forward
 //   values; finish << 8 | producer stage, kEmptySlot at first.
@@ -135,7 +138,7 @@ struct SlotTables {
 struct ListTables {
   int32_t D, m;
   int32_t cands_per_wave;   // candidates of one wavefront of the timing pass: ceil(D / 2) lanes each
-  int32_t cand_slots;       // dwords per candidate, a multiple of 4
+  int32_t cand_slots;       // slots per candidate, a multiple of 4
   int32_t wave_bytes;       // LDS of one wavefront of the timing pass: op windows, then slots
   int32_t n_time_ints;      // timing rows, padded to a multiple of 8
   int32_t off_check;        // order rows, in ints
@@ -149,6 +152,7 @@ struct ListTables {
   const int32_t* ints;      // DEVICE
 };
 constexpr unsigned kRowTwoOut = 1u << 30;
+constexpr unsigned kWideNever = 0xffu << 8;   // wide form: the tag of an empty slot, expected on a device's own word
 constexpr unsigned kOwnTag = 0xfeu;   // (no stage's op looks at a device's own word)
 constexpr int list_slots_at(int D) { return (D + 2 + 3) & ~3; }
 constexpr unsigned kNoState = 15u;

@@ -51,7 +51,7 @@ struct fpsched_problem {
   int32_t* d_slot_ints = nullptr;
   // the two-pass list evaluation: order pass, timing pass
   bool lists_ok = false;
-  bool lists_deg2 = false;
+  bool lists_deg2 = false, lists_wide = false;
   ListTables ltab{};
   int32_t* d_list_ints = nullptr;
   int32_t check_rows_per_wave = 0, check_waves = 0, check_grid = 0, check_vbits = 0;
@@ -243,6 +243,12 @@ CheckKernel check_kernel_of(int vbits) {
   return vbits == 0 ? &check_rows_kernel<0> : (vbits == 1 ? &check_rows_kernel<1> : &check_rows_kernel<2>);
 }
 
+using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int);
+TimeKernel time_kernel_of(bool deg2, bool wide) {
+  if (wide) return deg2 ? &time_lists_kernel<true, true> : &time_lists_kernel<false, true>;
+  return deg2 ? &time_lists_kernel<true, false> : &time_lists_kernel<false, false>;
+}
+
 // What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
 struct StageEdge { int32_t cls, tag, latency; };
 struct StageEdges { std::vector<StageEdge> in[2], out[2]; };
@@ -257,7 +263,9 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
   for (int s = 0; s < S; ++s) unit_scale = std::gcd<int64_t, int64_t>(unit_scale, desc->mem_units[s]);
   unit_scale = std::max<int64_t>(unit_scale, 1);
   const int64_t cand_slots = (list_slots_at(D) + 2ll * n_classes * m + 3) & ~3ll;
-  if (4 * cand_slots > 0xffff || S > 255 || p->max_comm >= (1ll << 16) || bound >= (1ll << 24)) return;
+  const bool wide = p->max_comm >= (1ll << 16) || bound >= (1ll << 24);
+  const int slot_bytes = wide ? 8 : 4;
+  if (slot_bytes * cand_slots > 0xffff || S > 255) return;
   bool deg2 = false;
   for (int s = 0; s < S; ++s) {
     if (desc->mem_units[s] / unit_scale > 0xff) return;
@@ -302,8 +310,9 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
         const size_t row = ((size_t)kind * kMaxChunks + c) * D;
         int32_t* t = &J[(row + (d & 1) * ((D + 1) / 2) + d / 2) * row_ints];   // even devices first
         int32_t* o = &J[(size_t)T.off_check + (row + d) * 2];
-        t[0] = 1;
-        t[2] = 4 * d;
+        t[0] = wide ? 0 : 1;
+        t[2] = slot_bytes * d;
+        if (wide) t[3] = (int32_t)kWideNever;
         o[0] = (int32_t)(kNoState << 8);
         if (c >= p->n_chunks[d] || kind == kEnd || (kind == kW && !p->has_w)) continue;
         const int s = p->local_stage[(size_t)d * kMaxChunks + c];
@@ -317,18 +326,37 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
         const std::vector<StageEdge>& in = dir < 0 ? none : edges[s].in[dir];
         const std::vector<StageEdge>& out_edges = dir < 0 ? none : edges[s].out[dir];
         const bool crosses = !in.empty() || !out_edges.empty();
-        t[1] = (int32_t)(((unsigned)desc->dur[kind * S + s] << 8) | (crosses ? (unsigned)s : kOwnTag));
-        if (!crosses) { t[0] = -(int32_t)kOwnTag; continue; }
+        const unsigned own_tag = crosses ? (unsigned)s : kOwnTag;
+        t[1] = wide ? desc->dur[kind * S + s] : (int32_t)(((unsigned)desc->dur[kind * S + s] << 8) | own_tag);
+        if (wide) t[3] = (int32_t)own_tag;
+        if (!crosses) {
+          if (wide) t[3] |= (int32_t)(kOwnTag << 8);
+          else t[0] = -(int32_t)kOwnTag;
+          continue;
+        }
         const int base = list_slots_at(D) + (dir == 0 ? n_classes * m : 0);
         for (size_t e = 0; e < std::max(in.size(), out_edges.size()); ++e) {
           const int cls = e < in.size() ? in[e].cls : out_edges[e].cls;
-          const int32_t slot = (int32_t)((unsigned)(4 * (base + cls * m)) | (0x1ffcu << 16));
-          const int32_t wait = e < in.size() ? (int32_t)(((unsigned)in[e].latency << 8) - (unsigned)in[e].tag) : -(int32_t)(kEmptySlot & 0xffu);
-          if (e == 0) { t[0] = wait; t[2] = slot; continue; }
+          const int32_t slot = (int32_t)((unsigned)(slot_bytes * (base + cls * m)) | ((unsigned)(0x7ff * slot_bytes) << 16));
+          const unsigned expected = e < in.size() ? (unsigned)in[e].tag : kEmptySlot & 0xffu;
+          const unsigned latency = e < in.size() ? (unsigned)in[e].latency : 0u;
+          const int32_t wait = (int32_t)(wide ? latency : (latency << 8) - expected);
+          if (e == 0) {
+            t[0] = wait;
+            t[2] = slot;
+            if (wide) t[3] |= (int32_t)(expected << 8);
+            continue;
+          }
           int32_t* second = &J[second_at];
           second[0] = t[0]; second[1] = t[2]; second[2] = slot;
-          t[3] = (int32_t)((unsigned)(4 * second_at) | (e < out_edges.size() ? kRowTwoOut : 0u) | (e < in.size() ? 1u << 31 : 0u));
-          if (e < in.size()) { t[0] = wait; t[2] = slot; }
+          if (wide) second[3] = t[3] & 0xff00;
+          const unsigned flags = (e < out_edges.size() ? kRowTwoOut : 0u) | (e < in.size() ? 1u << 31 : 0u);
+          const unsigned at_second = wide ? (unsigned)(second_at / 4) << 16 : (unsigned)(4 * second_at);
+          t[3] = (int32_t)(((unsigned)t[3] & 0xffffu) | at_second | flags);
+          if (e < in.size()) {
+            t[0] = wait; t[2] = slot;
+            if (wide) t[3] = (int32_t)(((unsigned)t[3] & ~0xff00u) | (expected << 8));
+          }
           second_at += 4;
         }
       }
@@ -348,7 +376,7 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
   WorkgroupShape time{0, 1};
   int cpw = 64 / ((D + 1) / 2);
   for (; cpw >= 1; --cpw) {
-    T.wave_bytes = (int32_t)((kTimeWindowBytes + cpw * 4 * cand_slots + 31) & ~31ll);   // (rings are 32-byte aligned)
+    T.wave_bytes = (int32_t)((kTimeWindowBytes + cpw * slot_bytes * cand_slots + 31) & ~31ll);   // (rings are 32-byte aligned)
     time = workgroup_shape(4ll * T.n_time_ints, T.wave_bytes, p->max_lds);
     if (time.waves >= 1) break;
   }
@@ -360,6 +388,7 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
   p->time_waves = time.waves;
   p->time_grid = p->n_cu * time.groups;
   p->lists_deg2 = deg2;
+  p->lists_wide = wide;
   p->lists_ok = true;
 }
 
@@ -735,8 +764,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       ok = hipMalloc(&p->d_list_ints, list_image.size() * sizeof(int32_t)) == hipSuccess &&
            hipMemcpy(p->d_list_ints, list_image.data(), list_image.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
       for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits)),
-                                 reinterpret_cast<const void*>(&time_lists_kernel<false>),
-                                 reinterpret_cast<const void*>(&time_lists_kernel<true>)})
+                                 reinterpret_cast<const void*>(time_kernel_of(p->lists_deg2, p->lists_wide))})
         ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
       p->ltab.ints = p->d_list_ints;
     }
@@ -932,7 +960,7 @@ static int run_list_evaluation(const fpsched_problem* p, const uint16_t* d_ops, 
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(p->lists_deg2 ? time_lists_kernel<true> : time_lists_kernel<false>, dim3((unsigned)time_blocks),
+  hipLaunchKernelGGL(time_kernel_of(p->lists_deg2, p->lists_wide), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
                      out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave));

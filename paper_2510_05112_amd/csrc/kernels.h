@@ -69,7 +69,8 @@ __global__ void eval_slot_kernel(SlotTables T, const uint16_t* ops, long long n_
 // The list evaluation in two passes.  check_rows_kernel: one lane per (candidate, device) row, rows_per_wave of them per
 // wavefront; per row out_info (kRow* | stop, then the busy time in the low half) and out_peak.  dynamic: more blocks of
 // rows than resident wavefronts, taken draw_blocks at a time, the further ones from counter[1]; else it sets *counter for the timing pass.
-// time_lists_kernel: reads out_info from out_idle, writes the results.  DEG2 = some stage has two inputs or outputs.
+// time_lists_kernel: reads out_info from out_idle, writes the results.  DEG2 = some stage has two inputs or outputs;
+// WIDE = times beyond 24 bits.
 constexpr int kCheckMaxThreads = 512;
 constexpr int kCheckWavesPerSimd = 3;
 constexpr int kTimeMaxThreads = 1024;
@@ -78,7 +79,7 @@ template <int VBITS>   // 0, 1, 2: up to 1, 2, 4 stages per device
 __global__ void check_rows_kernel(ListTables T, const uint16_t* ops, long long n_rows, int stride, int rows_per_wave,
                                   long long* out_info, int* out_peak, unsigned long long* counter,
                                   unsigned long long counter_value, int draw_blocks, int dynamic);
-template <bool DEG2>
+template <bool DEG2, bool WIDE>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block);

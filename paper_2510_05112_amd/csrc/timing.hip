@@ -24,6 +24,11 @@
 // slot[dir][class][j] = finish << 8 | producer stage.  A consumer finds its input iff the tag names its upstream
 // stage.  No order of micro-batches is assumed and a producer never has to wait for room.
 //
+// WIDE: finish times of up to 31 bits (durations in microseconds: 16 devices x 64 micro-batches pass 2^24 within a few
+// dozen ops) take two words per slot, the time and the tag, and the tag is compared on its own; otherwise the same.  The
+// host picks it where the bound on all times does not fit 24 bits or a latency not 16; the table kernel that such
+// problems ran on before took 5.2 ms for 8,192 candidates of that size.
+//
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
@@ -63,12 +68,13 @@ constexpr unsigned kWindowBytes = 64u * kRingBytes;   // the rings of one half o
 
 }  // namespace
 
-template <bool DEG2>
+template <bool DEG2, bool WIDE>
 __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block) {
   constexpr unsigned kRowBytes = 16u;
+  constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
@@ -79,12 +85,16 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   const int d0 = 2 * pair;
   const bool has_odd = d0 + 1 < D;
   const unsigned wave_at = lds0 + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)T.wave_bytes;
-  unsigned slot_base = wave_at + 2u * kWindowBytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * 4u;
+  unsigned slot_base = wave_at + 2u * kWindowBytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * kSlotBytes;
   asm volatile("" : "+v"(slot_base));   // one register, not a sum to be re-associated every round
-  const unsigned own_word = slot_base + (unsigned)(lane_ok ? d0 : 0) * 4u;
-  const int own_at = (lane_ok ? d0 : 0) * 4;   // that word as a row's slot field
-  const unsigned at_max = slot_base + ((unsigned)D + 1u) * 4u;
-  lds_write<uint32_t>(own_word, kOwnTag);   // what a lane without an op looks at
+  const unsigned own_word = slot_base + (unsigned)(lane_ok ? d0 : 0) * kSlotBytes;
+  const int own_at = (lane_ok ? d0 : 0) * (int)kSlotBytes;   // that word as a row's slot field
+  const unsigned at_max = slot_base + ((unsigned)D + 1u) * kSlotBytes;
+  auto clear_own = [&](unsigned at) {
+    if (WIDE) lds_write<lds_int2>(at, lds_int2{0, (int)kOwnTag});
+    else lds_write<uint32_t>(at, kOwnTag);
+  };
+  clear_own(own_word);   // what a lane without an op looks at
   __syncthreads();
 
   // segment bookkeeping on the scalar unit: bit seg * P stands for segment seg
@@ -104,8 +114,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   // own word with an L that keeps it waiting.
   struct Device {
     unsigned win, meta;
-    unsigned free_at8;
-    unsigned j4, w_next;    // the word under the cursor << 2, and the word behind it
+    unsigned free_at;       // narrow: << 8
+    unsigned j_slot, w_next;   // the word under the cursor times the bytes of a slot, and the word behind it
     lds_int4 R;             // the op's table row: L, dur | tag, slot, second edge
     unsigned loaded2;   // bytes of the row that are in the ring (a device without a list asks for none)
     unsigned pos2;      // byte position of w_next; the device has issued pos2 / 2 - 1 ops
@@ -116,7 +126,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   };
   Device even, odd;
   auto idle_device = [&](Device& x) {
-    x.R = lds_int4{1, 0, own_at, 0};
+    x.R = WIDE ? lds_int4{0, 0, own_at, (int)kWideNever} : lds_int4{1, 0, own_at, 0};
     x.loaded2 = 0x40000000u;
     x.pos2 = 2u;
     x.info = 0u;
@@ -126,7 +136,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     // (lanes eight apart share their banks: the halves of their rings are in different orders)
     x.win = wave_at + (unsigned)k * kWindowBytes + (unsigned)lane * kRingBytes + (((unsigned)lane >> 3) & 1u) * 16u;
     x.meta = lds0 + (unsigned)(k * P + pair) * kRowBytes;
-    x.free_at8 = 0u; x.j4 = 0u; x.w_next = 0u; x.busy = 0u;
+    x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
     x.pend0 = make_uint4(0u, 0u, 0u, 0u); x.pend1 = x.pend0;
     idle_device(x);
   };
@@ -146,7 +156,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   // next step begins, so that the other half's step covers the wait for it
   auto decode = [&](Device& x, unsigned word) {
     const unsigned at = __umul24(word >> 11, row_stride) + x.meta;
-    x.j4 = word << 2;
+    x.j_slot = word * kSlotBytes;
     x.R = lds_read<lds_int4>(at);
   };
   // address of a byte position in the device's ring
@@ -199,14 +209,26 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     decode(x, w);
     x.pos2 = 2u;
   };
+  // where the second row of an op with a second input or output is
+  auto second_row = [&](int w) -> unsigned {
+    return lds0 + (WIDE ? ((unsigned)w >> 12) & 0xfff0u : (unsigned)w & 0xffffu);
+  };
   // one step of one half of the devices; returns the lanes that issued
   auto step = [&](Device& x) -> unsigned long long {
-    asm volatile("" : "+v"(x.R), "+v"(x.j4));   // (the row stays one value until here: no earlier wait for it)
-    const unsigned at_slot = (x.j4 & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
-    const unsigned ready8 = lds_read<uint32_t>(at_slot) + (unsigned)x.R.x;
+    asm volatile("" : "+v"(x.R), "+v"(x.j_slot));   // (the row stays one value until here: no earlier wait for it)
+    const unsigned at_slot = (x.j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
+    unsigned ready;
     unsigned long long moved;
-    const unsigned zero = 0u;
-    asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready8), "v"(zero));
+    if (WIDE) {
+      // the slot's second word is the tag, the row's last one the expected tag (byte 1) and the op's own (byte 0)
+      const lds_int2 in = lds_read<lds_int2>(at_slot);
+      ready = (unsigned)in.x + (unsigned)x.R.x;
+      asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:DWORD src1_sel:BYTE_1" : "=s"(moved) : "v"(in.y), "v"(x.R.w));
+    } else {
+      ready = lds_read<uint32_t>(at_slot) + (unsigned)x.R.x;
+      const unsigned zero = 0u;
+      asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready), "v"(zero));
+    }
     unsigned long long issue = moved;
     if (DEG2) {
       // an op with two inputs waits for its second one first: once that is there the device's free time takes it in
@@ -214,22 +236,26 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       const unsigned long long absorb = moved & __ballot(x.R.w < 0);
       if (absorb != 0ull) {
         if (__builtin_amdgcn_inverse_ballot_w64(absorb)) {
-          x.free_at8 = max(x.free_at8, ready8);
-          const lds_int2 first = lds_read<lds_int2>(lds0 + ((unsigned)x.R.w & 0xffffu));
+          x.free_at = max(x.free_at, ready);
+          const lds_int4 first = lds_read<lds_int4>(second_row(x.R.w));
           x.R.x = first.x;
           x.R.z = first.y;
-          x.R.w &= 0x7fffffff;
+          x.R.w = WIDE ? (x.R.w & 0x7fff00ff) | first.w : x.R.w & 0x7fffffff;
         }
         issue &= ~absorb;
       }
     }
     if (__builtin_amdgcn_inverse_ballot_w64(issue)) {
-      const unsigned val = max(x.free_at8, ready8) + (unsigned)x.R.y;
-      x.free_at8 = val & 0xffffff00u;
-      lds_write<uint32_t>(at_slot, val);
+      const unsigned val = max(x.free_at, ready) + (unsigned)x.R.y;
+      x.free_at = WIDE ? val : val & 0xffffff00u;
+      auto leave = [&](unsigned at) {
+        if (WIDE) lds_write<lds_int2>(at, lds_int2{(int)val, x.R.w & 0xff});
+        else lds_write<uint32_t>(at, val);
+      };
+      leave(at_slot);
       if (DEG2 && ((unsigned)x.R.w & kRowTwoOut) != 0u) {
-        const unsigned second = lds_read<uint32_t>(lds0 + ((unsigned)x.R.w & 0xffffu) + 8u);
-        lds_write<uint32_t>((x.j4 & (second >> 16)) + slot_base + (second & 0xffffu), val);
+        const unsigned second = lds_read<uint32_t>(second_row(x.R.w) + 8u);
+        leave((x.j_slot & (second >> 16)) + slot_base + (second & 0xffffu));
       }
       decode(x, x.w_next);
       x.pos2 += 2u;
@@ -286,14 +312,14 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         cand = (long long)drawn;
         running = lane_ok && cand < n_cand;
         priming = running;
-        even.free_at8 = 0u;
-        odd.free_at8 = 0u;
+        even.free_at = 0u;
+        odd.free_at = 0u;
         if (running) {
-          const int n4 = T.cand_slots >> 2;
+          const int n4 = T.cand_slots * (int)kSlotBytes / 16, unused = WIDE ? 0 : (int)kEmptySlot;
           for (int i = pair; i < n4; i += P)
-            lds_write<lds_int4>(slot_base + (unsigned)i * 16u, lds_int4{(int)kEmptySlot, (int)kEmptySlot, (int)kEmptySlot, (int)kEmptySlot});
-          lds_write<uint32_t>(own_word, kOwnTag);
-          if (has_odd) lds_write<uint32_t>(own_word + 4u, kOwnTag);
+            lds_write<lds_int4>(slot_base + (unsigned)i * 16u, lds_int4{unused, (int)kEmptySlot, unused, (int)kEmptySlot});
+          clear_own(own_word);
+          if (has_odd) clear_own(own_word + kSlotBytes);
           if (pair == 0) lds_write<uint32_t>(at_max, 0u);
           const long long r = cand * D + d0;
           row = reinterpret_cast<const char*>(ops + (size_t)r * (size_t)stride);
@@ -340,8 +366,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           const bool over = any_in_segment(__ballot((both & kRowOverCap) != 0u));
           if (ended) {
             // the latest finish, in a word that was cleared when the segment started
-            atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at8, odd.free_at8));
-            const unsigned ms = lds_read<uint32_t>(at_max) >> 8;
+            atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at, odd.free_at));
+            const unsigned ms = lds_read<uint32_t>(at_max) >> (WIDE ? 0 : 8);
             const unsigned flags = stuck ? kDeadlock | (malformed ? kIncomplete : 0u)
                                          : (unfinished ? (unsigned)kIncomplete : (over ? (unsigned)kOverCap : 0u));
             const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
@@ -370,9 +396,13 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   }
 }
 
-template __global__ void time_lists_kernel<false>(ListTables, const uint16_t*, long long, int, long long*, long long*, int*,
-                                                  unsigned char*, unsigned long long*, int);
-template __global__ void time_lists_kernel<true>(ListTables, const uint16_t*, long long, int, long long*, long long*, int*,
-                                                 unsigned char*, unsigned long long*, int);
+#define FPSCHED_INSTANTIATE(DEG2, WIDE)                                                                          \
+  template __global__ void time_lists_kernel<DEG2, WIDE>(ListTables, const uint16_t*, long long, int, long long*, \
+                                                         long long*, int*, unsigned char*, unsigned long long*, int);
+FPSCHED_INSTANTIATE(false, false)
+FPSCHED_INSTANTIATE(true, false)
+FPSCHED_INSTANTIATE(false, true)
+FPSCHED_INSTANTIATE(true, true)
+#undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched

@@ -66,3 +66,20 @@ def test_order_pass_draws_blocks():
     words = workloads.generate(spec_of(prob, 2048, 5, 20, recompute=1), threads=8)
     words = np.tile(words, (64, 1, 1))
     check_batch(prob, words[:131072 - 3], 16, "many blocks", threads=16, kernels=("slots",))
+
+
+@pytest.mark.parametrize("D,v,m,scale", [(3, 2, 9, 20000), (14, 1, 12, 9000), (33, 2, 6, 1500)])
+def test_times_beyond_24_bits(D, v, m, scale):
+    prob = chain_problem(D, m, v=v, f=3 * scale, b=5 * scale + 1, w=2 * scale, comm=scale - 1, mem_cap=max(2, D // 2))
+    words = np.tile(workloads.generate(spec_of(prob, 150, D), threads=8), (1 + 20000 // (150 * D), 1, 1))
+    gpu, _ = check_batch(prob, words, 8, f"D={D}")
+    assert gpu["makespan"].min() > 0
+
+
+def test_times_beyond_24_bits_on_a_dag():
+    """Two towers that merge: second inputs and outputs; latencies beyond 16 bits."""
+    spec = workloads.config(5, 500)
+    prob = spec.problem
+    prob.dur = prob.dur * 3001
+    prob.edge_comm = prob.edge_comm * 70001
+    check_batch(prob, workloads.generate(spec, threads=8), 16, "towers", threads=8)
