@@ -906,20 +906,15 @@ int fpsched_problem_active_kernel(const fpsched_problem* p) {
   return p->use_slots && (!p->mb_set || p->mb_slots_ok) ? FPSCHED_KERNEL_SLOTS : FPSCHED_KERNEL_GENERAL;
 }
 
-static int64_t topk_level_sizes(int64_t n, int32_t k, int64_t* first, int64_t* second) {
-  // survivors after level 0 and after level 1 (the two ping-pong buffers)
-  const int64_t t0 = std::max<int64_t>(1, (n + kTile - 1) / kTile);
-  const int64_t n1 = t0 * k;
-  const int64_t t1 = std::max<int64_t>(1, (n1 + kTile - 1) / kTile);
-  *first = n1;
-  *second = t1 * k;
-  return n1 + *second;
-}
-
 size_t fpsched_workspace_bytes(const fpsched_problem* p, int64_t n_cand, int32_t k) {
   if (!p || n_cand < 0) return 0;
-  int64_t a = 0, b = 0;
-  const int64_t keys = k > 0 ? topk_level_sizes(n_cand, std::min(k, 1024), &a, &b) : 0;
+  // survivors of the top-k's first launch (at most k per tile of candidates), and a second buffer in proportion
+  int64_t keys = 0;
+  if (k > 0) {
+    const int64_t per_part = std::min(k, 1024);
+    const int64_t first = std::max<int64_t>(1, (n_cand + kTile - 1) / kTile) * per_part;
+    keys = first + std::max<int64_t>(1, (first + kTile - 1) / kTile) * per_part;
+  }
   return (size_t)(256 + keys * (int64_t)sizeof(Key));
 }
 
@@ -1926,32 +1921,40 @@ int fpsched_generate_slide_evaluate(const fpsched_problem* p, const fpsched_acto
                                hip_stream, true);
 }
 
-// k smallest (key, index) among the entries whose flag byte is 0: tile sort, then a tree of merges
-static int run_topk(const long long* keys, const unsigned char* flags, int64_t n_cand, int32_t k, int64_t* d_idx,
-                    int64_t* d_key, int32_t* d_count, char* key_buffers, hipStream_t st) {
-  int64_t cap_a = 0, cap_b = 0;
-  topk_level_sizes(n_cand, k, &cap_a, &cap_b);
-  Key* buf_a = reinterpret_cast<Key*>(key_buffers);
-  Key* buf_b = buf_a + cap_a;
+// k smallest (key, index) among the entries whose flag byte is 0: parts, then one workgroup over the parts' survivors
+static int run_topk(const long long* keys, const unsigned char* flags, int64_t n_cand, int32_t k, bool wide_values,
+                    int64_t* d_idx, int64_t* d_key, int32_t* d_count, char* key_buffers, hipStream_t st) {
+  Key* survivors = reinterpret_cast<Key*>(key_buffers);
   long long* f_idx = reinterpret_cast<long long*>(d_idx);
   long long* f_ms = reinterpret_cast<long long*>(d_key);
-
-  int64_t n = n_cand;
-  const Key* src = nullptr;  // level 0 reads keys / flags
-  Key* dst = buf_a;
-  for (;;) {
-    const int64_t tiles = std::max<int64_t>(1, (n + kTile - 1) / kTile);
-    const bool last = tiles == 1;
-    hipLaunchKernelGGL(topk_tile_kernel, dim3((unsigned)tiles), dim3(kTopkThreads), 0, st, keys, flags, src,
-                       (long long)n, (int)k, last ? nullptr : dst, last ? f_idx : nullptr, last ? f_ms : nullptr,
-                       last ? d_count : nullptr);
+  // Elements a workgroup sorts at a time: twice k at least, so that a sort makes room for as many as there are threads;
+  // no more than 1024 unless k needs it (a sort of 2048 takes twice as long), no more than there are.
+  auto threads_for = [&](int64_t n) {
+    int64_t room = 128;
+    while (room < 2 * (int64_t)k || (room < n && room < 1024)) room <<= 1;
+    return (unsigned)(room / 2);
+  };
+  // Parts: one while a workgroup needs but a few sorts; else as many as leave the second launch about 2048 survivors, and
+  // never more than the buffers (one per kTile candidates) have room for.  Positions within a part are 32 bits.
+  const int64_t tiles = (n_cand + kTile - 1) / kTile;
+  int64_t parts = 1;
+  if (n_cand > kTile) parts = std::clamp<int64_t>(2048 / k, 8, 64);
+  parts = std::max<int64_t>(std::min(parts, tiles), (n_cand >> 31) + 1);
+  const int64_t n_part = (n_cand + parts - 1) / parts;
+  if (parts > 1) {
+    parts = (n_cand + n_part - 1) / n_part;
+    const unsigned threads = threads_for(n_part);
+    hipLaunchKernelGGL(topk_kernel, dim3((unsigned)parts), dim3(threads), threads * 24u, st, keys, flags, (const Key*)nullptr,
+                       (long long)n_cand, (long long)n_part, (int)k, (int)wide_values, survivors, (long long*)nullptr,
+                       (long long*)nullptr, (int*)nullptr);
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-    if (last) break;
-    n = tiles * k;
-    src = dst;
-    dst = (dst == buf_a) ? buf_b : buf_a;
   }
-  return FPSCHED_OK;
+  const int64_t n_last = parts > 1 ? parts * k : n_cand;
+  const unsigned threads = threads_for(n_last);
+  hipLaunchKernelGGL(topk_kernel, dim3(1), dim3(threads), threads * 24u, st, keys, flags,
+                     parts > 1 ? (const Key*)survivors : (const Key*)nullptr, (long long)n_last, (long long)std::max<int64_t>(n_last, 1),
+                     (int)k, (int)wide_values, (Key*)nullptr, f_idx, f_ms, d_count);
+  return check_hip(hipGetLastError());
 }
 
 int fpsched_topk(const fpsched_problem* p, fpsched_results in, int64_t n_cand, int32_t k,
@@ -1964,7 +1967,7 @@ int fpsched_topk(const fpsched_problem* p, fpsched_results in, int64_t n_cand, i
   if (workspace_bytes < fpsched_workspace_bytes(p, n_cand, k)) return FPSCHED_ENOMEM;
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
-  return run_topk(reinterpret_cast<const long long*>(in.makespan), in.flags, n_cand, k, d_idx, d_makespan, d_count,
+  return run_topk(reinterpret_cast<const long long*>(in.makespan), in.flags, n_cand, k, false, d_idx, d_makespan, d_count,
                   static_cast<char*>(d_workspace) + 256, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -2017,7 +2020,7 @@ int fpsched_rank(const fpsched_problem* p, fpsched_results in, int64_t n_cand, i
                        excluded);
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   }
-  return run_topk(keys, excluded, n_cand, k, d_idx, d_key, d_count, static_cast<char*>(d_workspace) + 256, st);
+  return run_topk(keys, excluded, n_cand, k, mode == 1 || mode == 2, d_idx, d_key, d_count, static_cast<char*>(d_workspace) + 256, st);
 }
 
 // workspace of the sliding pass: [256 bytes: candidate counter][low halves of the start times: 16 bits per op
@@ -2169,7 +2172,7 @@ int fpsched_pareto(const fpsched_problem* p, fpsched_results in, int64_t n_cand,
   int* front_peak = reinterpret_cast<int*>(front_keys + tiles * kTile);
   int* tile_count = front_peak + tiles * kTile;
   if (tiles > 0) {
-    hipLaunchKernelGGL(pareto_tile_kernel, dim3((unsigned)tiles), dim3(kTopkThreads), 0, st,
+    hipLaunchKernelGGL(pareto_tile_kernel, dim3((unsigned)tiles), dim3(kTile / 2), 0, st,
                        reinterpret_cast<const long long*>(in.makespan), in.peak, in.flags, (long long)n_cand,
                        (int)p->D, front_keys, front_peak, tile_count);
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;

@@ -108,9 +108,9 @@ __global__ void generate_kernel(DevTables T, const int32_t* policy, const int32_
                                 long long n_src, long long n_sets, int stride, uint16_t* ops, int32_t* out_steps,
                                 unsigned char* out_status, unsigned long long* next_set, GenResults R);
 
-__global__ void topk_tile_kernel(const long long* in_makespan, const unsigned char* in_flags,
-                                 const Key* in_keys, long long n, int k, Key* out_keys,
-                                 long long* final_idx, long long* final_makespan, int* final_count);
+__global__ void topk_kernel(const long long* in_makespan, const unsigned char* in_flags, const Key* in_keys, long long n,
+                            long long n_part, int k, int wide_values, Key* out_keys, long long* final_idx,
+                            long long* final_makespan, int* final_count);
 
 __global__ void rank_keys_kernel(const long long* makespan, const long long* idle, const int* peak,
                                  const unsigned char* flags, long long n, int D, int mode, int include_over_cap,
@@ -129,7 +129,7 @@ __global__ void wslide_place_kernel(SlotTables T, const uint16_t* ops, long long
                                     unsigned char* out_flags);
 
 // Pareto front: at most kParetoMaxTiles tiles of kTile candidates (one cursor per tile in LDS).
-constexpr int kParetoMergeThreads = 1024;
+constexpr int kParetoMergeThreads = kTile / 2;
 constexpr int kParetoMaxTiles = 8192;
 
 __global__ void pareto_tile_kernel(const long long* makespan, const int* peak, const unsigned char* flags,

@@ -3,85 +3,161 @@
 // schedules whose bubble ratio is lowest; with fixed total work that is the
 // least makespan).
 //
-// Tile sort + tree merge, all in LDS: every workgroup loads one tile of
-// kTile (makespan, index) keys (infeasible candidates become +inf keys), sorts it
-// with a bitonic network and writes its k smallest keys; the next level treats
-// those survivors as its input, until one tile is left.  The result is a pure
-// function of the keys, so it does not depend on workgroup scheduling, and ties
-// on makespan are broken by the candidate index because the index is part of
-// the key.
+// Each workgroup selects the k smallest of its part of the candidates, a second launch of one workgroup the k
+// smallest of what those left (a batch of one part needs one launch).  A workgroup collects candidates in LDS and
+// sorts when the room is used up (block_sort.h); from then on only candidates in front of the k-th of the last sort
+// are collected, of values in random order about k ln(part / first sort) more, so that a part of any length is sorted
+// two or three times.  The index is part of the key, so the result is a pure function of the values and does not
+// depend on workgroup scheduling.
+//
+// What bounds it: the latency of a few dependent steps on one compute unit (load, sort, launch).  The tree of tile
+// sorts with a barrier after each of 66 stages that was here before took 30 us a level, one for 1,024 candidates and
+// three for 65,536 with k = 128; now 8 us for 1,024 and 2 x 12 us for 65,536.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
+#include "block_sort.h"
 #include "kernels.h"
 
 namespace fpsched {
 
 constexpr long long kInf = 0x7fffffffffffffffll;
 
-__device__ __forceinline__ bool key_less(const Key& a, const Key& b) {
-  return a.makespan < b.makespan || (a.makespan == b.makespan && a.idx < b.idx);
-}
+namespace {
 
-// level 0 reads (makespan, flags); later levels read Key arrays.
-// Output: per tile, k keys (ascending).  When `final_out` is set (single tile),
-// the keys are unpacked into idx / makespan / count instead.
-__global__ __launch_bounds__(kTopkThreads) void topk_tile_kernel(
-    const long long* __restrict__ in_makespan, const unsigned char* __restrict__ in_flags,
-    const Key* __restrict__ in_keys, long long n, int k, Key* __restrict__ out_keys,
-    long long* __restrict__ final_idx, long long* __restrict__ final_makespan,
-    int* __restrict__ final_count) {
-  __shared__ Key tile[kTile];
-  const long long base = (long long)blockIdx.x * kTile;
-  for (int i = threadIdx.x; i < kTile; i += kTopkThreads) {
-    const long long g = base + i;
-    Key key{kInf, kInf};
-    if (g < n) {
-      if (in_keys) {
-        key = in_keys[g];
-      } else if (in_flags[g] == 0) {
-        key.makespan = in_makespan[g];
-        key.idx = g;
-      }
-    }
-    tile[i] = key;
-  }
+constexpr unsigned kNoPos = 0xffffffffu;
+
+struct TopkSource {
+  const long long* makespan;   // candidates: keys and flags
+  const unsigned char* flags;
+  const Key* keys;             // or survivors of the first launch
+};
+
+// Collects the k smallest of elements [first, first + n), ascending, in buf[0 .. *count), and more behind them (all
+// threads get the same *count, at most k).  P = NoPos: the key is value << 32 | position; returns false, in all threads,
+// if some value does not fit.  P = unsigned: the value as an unsigned number in the order of the signed ones.
+template <typename P>
+__device__ bool select_smallest(const TopkSource& src, long long first, unsigned n, int k, const SortBuffer<P>& buf,
+                                int* taken, int* misfit, int* count) {
+  constexpr bool kPacked = std::is_same<P, NoPos>::value;
+  const int tid = threadIdx.x, threads = blockDim.x, lane = tid & 63, room = 2 * threads;
+  constexpr int kBatch = 4;   // elements per thread on their way at a time
+  SortElem<P> none{~0ull, P{}};
+  if constexpr (!kPacked) none.pos = kNoPos;
+  SortElem<P> bar = none;     // the k-th of the last sort: only elements in front of it are collected
+  if (tid < 3) taken[tid] = 0;
+  if (tid == 3) *misfit = 0;
   __syncthreads();
-  for (int size = 2; size <= kTile; size <<= 1) {
-    for (int strd = size >> 1; strd > 0; strd >>= 1) {
-      for (int t = threadIdx.x; t < kTile / 2; t += kTopkThreads) {
-        const int lo = ((t / strd) * (strd << 1)) + (t % strd);
-        const int hi = lo + strd;
-        const bool ascending = ((lo & size) == 0);
-        const Key a = tile[lo], b = tile[hi];
-        if (key_less(b, a) == ascending) {
-          tile[lo] = b;
-          tile[hi] = a;
+  int held = 0;               // elements in buf, the same number in all threads
+  bool sorted = false;
+  auto sort = [&]() {
+    int size = 128;
+    while (size < held) size <<= 1;
+    const int ia = (tid >> 6) * 128 + lane, ib = ia + 64;
+    SortElem<P> a = none, b = none;
+    if (ia < held) a = buf.get(ia);
+    if (ib < held) b = buf.get(ib);
+    block_sort<P>(a, b, size, buf);
+    if (ia < k) buf.put(ia, a);
+    if (ib < k) buf.put(ib, b);
+    __syncthreads();
+    if (held >= k) bar = buf.get(k - 1);
+    held = min(held, k);
+    sorted = true;
+  };
+  int turn = 0;               // the counter of this step; those of the next two are 0 or about to be
+  for (unsigned at = 0; at < n; at += kBatch * threads) {
+    SortElem<P> e[kBatch];
+    bool have[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const unsigned pos = at + i * threads + tid;
+      have[i] = pos < n;
+      long long value = 0;
+      if (have[i]) {
+        const long long g = first + pos;
+        if (src.keys) {
+          const Key s = src.keys[g];
+          value = s.makespan;
+          have[i] = s.idx != kInf;
+        } else {
+          value = src.makespan[g];
+          have[i] = src.flags[g] == 0;
         }
       }
-      __syncthreads();
-    }
-  }
-  if (final_idx) {
-    for (int i = threadIdx.x; i < k; i += kTopkThreads) {
-      const Key key = tile[i];
-      const bool real = key.idx != kInf;
-      final_idx[i] = real ? key.idx : -1ll;
-      final_makespan[i] = real ? key.makespan : kInf;
-    }
-    if (threadIdx.x == 0) {
-      // keys are sorted, the real ones come first: binary search the boundary within [0, k]
-      int lo = 0, hi = k;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (tile[mid].idx != kInf) lo = mid + 1; else hi = mid;
+      if constexpr (kPacked) {
+        e[i].key = (unsigned long long)value << 32 | pos;
+        if (have[i] && (unsigned long long)value >= 0xffffffffull) *misfit = 1;
+      } else {
+        e[i].key = (unsigned long long)value ^ (1ull << 63);
+        e[i].pos = pos;
       }
-      *final_count = lo;
     }
-  } else {
-    Key* dst = out_keys + (long long)blockIdx.x * k;
-    for (int i = threadIdx.x; i < k; i += kTopkThreads) dst[i] = tile[i];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      if (at + i * threads >= n) break;
+      const bool take = have[i] && elem_less(e[i], bar);
+      const unsigned long long takers = __ballot(take);
+      int base = 0;
+      if (lane == 0 && takers != 0ull) base = held + atomicAdd(&taken[turn], __popcll(takers));
+      base = __shfl(base, 0);
+      if (take) buf.put(base + __popcll(takers & ((1ull << lane) - 1ull)), e[i]);
+      __syncthreads();
+      const int more = taken[turn];
+      held += more;
+      sorted = sorted && more == 0;
+      // (read by all before the barrier just passed; in use again two barriers on)
+      const int before = turn == 0 ? 2 : turn - 1;
+      if (tid == 0) taken[before] = 0;
+      turn = turn == 2 ? 0 : turn + 1;
+      if (held + threads > room) sort();
+    }
   }
+  if (kPacked && *misfit != 0) return false;
+  if (!sorted && held > 0) sort();
+  *count = held;
+  return true;
+}
+
+}  // namespace
+
+// One workgroup per part of n_part candidates; the last launch has one workgroup (final_* set) and writes the answer,
+// any other the k survivors of each part, padded with keys behind all real ones.  Dynamic LDS: 12 bytes per element
+// of 2 * blockDim.x >= 2 * k.  wide_values: the caller knows that the values do not fit in 32 bits.
+__global__ __launch_bounds__(kTopkThreads) void topk_kernel(
+    const long long* __restrict__ in_makespan, const unsigned char* __restrict__ in_flags, const Key* __restrict__ in_keys,
+    long long n, long long n_part, int k, int wide_values, Key* __restrict__ out_keys, long long* __restrict__ final_idx,
+    long long* __restrict__ final_makespan, int* __restrict__ final_count) {
+  extern __shared__ unsigned long long topk_lds[];
+  __shared__ int taken[3], misfit;
+  const long long first = (long long)blockIdx.x * n_part;
+  const unsigned here = (unsigned)min(n_part, n - first);
+  const TopkSource src{in_makespan, in_flags, in_keys};
+  const SortBuffer<unsigned> wide{topk_lds, reinterpret_cast<unsigned*>(topk_lds + 2 * blockDim.x)};
+  int count;
+  const bool packed = !wide_values && select_smallest<NoPos>(src, first, here, k, SortBuffer<NoPos>{topk_lds, nullptr}, taken, &misfit, &count);
+  if (!packed) {
+    __syncthreads();
+    select_smallest<unsigned>(src, first, here, k, wide, taken, &misfit, &count);
+  }
+  for (int i = threadIdx.x; i < k; i += blockDim.x) {
+    long long value = kInf, idx = kInf;
+    if (i < count) {
+      const unsigned long long key = topk_lds[i];
+      const unsigned pos = packed ? (unsigned)key : wide.pos[i];
+      value = packed ? (long long)(key >> 32) : (long long)(key ^ (1ull << 63));
+      idx = in_keys ? in_keys[first + pos].idx : first + pos;
+    }
+    if (final_idx) {
+      final_idx[i] = i < count ? idx : -1ll;
+      final_makespan[i] = value;
+    } else {
+      out_keys[(long long)blockIdx.x * k + i] = Key{value, idx};
+    }
+  }
+  if (final_idx && threadIdx.x == 0) *final_count = count;
 }
 
 // Ranking keys of evaluated candidates (one thread per candidate): the quantities the tuner can
