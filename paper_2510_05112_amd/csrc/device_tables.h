@@ -35,19 +35,21 @@ struct DevTables {
   int32_t off_local_stage;  // [D][kMaxChunks], -1 = none
   int32_t off_n_chunks;     // [D]
   int32_t off_mem_cap;      // [D]
-  // Timed form of the generator (generate.hip): one row of eight ints per (instruction type F / B / W,
-  // chunk < gen_row_chunks, device), -1 if the DAG has a stage with more than two inputs or outputs:
-  //   0 duration   1 units allocated at the start   2 units freed at the end
-  //   3 byte offset of the first input slot   4 latency of the first input, or -2^30 if there is none
-  //   5, 6 the same for the second input   7 first output slot | second output slot << 16 (degree one:
-  //   the first output slot alone)
+  // Timed form of the generator (generate.hip): one row per (instruction type F / B / W,
+  // chunk < gen_row_chunks, device), then one that changes nothing; -1 if the DAG has a stage with more than two inputs or
+  // outputs.  A row has two halves of four ints, all first halves stand in front of all second halves:
+  //   0 duration   1 byte offset of the first input slot | of the first output slot << 16
+  //   2 latency of the first input, or -2^30 if there is none   3 chunk | 4 for B
+  //   4 units allocated at the start   5 units freed at the end   6, 7 as 1, 2 for the second input and output
   // Slots of one parameter set: one word per (direction, class, micro-batch) as in the slot kernel
   // (backward class k at k m, forward class k at (classes + k) m) holding a plain finish time, then m
   // words that take what items without an out-edge write (and that items without an input read).
   int32_t off_gen_rows;
   int32_t gen_row_chunks;   // 1, 2 or 4
   int32_t gen_slot_words;   // (2 * classes + 1) * m
-  int32_t gen_spill_words;  // sliding form of the timed generator: queue words per lane in LDS (a power of two), set per launch
+  int32_t gen_sets;         // parameter sets per wavefront, at most 64 / D: as many as LDS holds, set per launch
+  int32_t gen_queue_words;  // sliding form of the timed generator: queue words per lane in LDS, set per launch
+  int32_t off_turnaround;   // [S] generator steps from a micro-batch's forward item to its backward item, 2 * (longest path to a sink) + 1
   const int32_t* ints;      // DEVICE
 };
 

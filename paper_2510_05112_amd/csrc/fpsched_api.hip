@@ -517,6 +517,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
   // class of a not yet continued in-edge of its stage, else it opens a new class.
   std::vector<int32_t> edge_cls(E, -1);
   int n_classes = 0;
+  std::vector<int32_t> turnaround(S, 1);
   {
     std::vector<int> indeg(S, 0), order;
     for (int e = 0; e < E; ++e) indeg[desc->edge_dst[e]]++;
@@ -533,8 +534,12 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       }
     }
     if (n_classes == 0) n_classes = 1;
+    for (size_t i = order.size(); i-- > 0;)
+      for (int e = soff[order[i]]; e < soff[order[i] + 1]; ++e)
+        turnaround[order[i]] = std::max(turnaround[order[i]], turnaround[sst[e]] + 2);
   }
   T.n_table_ints = (int32_t)I.size();   // what the table-walking kernels copy to LDS ends here
+  T.off_turnaround = append(turnaround.data(), S);
   // Rows of the timed generator: what an item of (type, chunk) on a device costs, where its inputs'
   // finish times lie and where its own goes (layout: device_tables.h).
   T.off_gen_rows = -1;
@@ -552,19 +557,26 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       scl[soff[a] + sf[a]++] = edge_cls[e];
     }
     const int32_t dump = 4 * 2 * n_classes * m, none = -(1 << 30);   // slot offsets in bytes
-    std::vector<int32_t> rows((size_t)3 * V * D * 8, 0);
+    const size_t n_rows = (size_t)3 * V * D + 1;
+    std::vector<int32_t> rows(n_rows * 8, 0);
+    for (size_t i = 0; i < n_rows; ++i) {
+      int32_t* a = &rows[i * 4];
+      int32_t* b = a + n_rows * 4;
+      a[1] = b[2] = dump | (dump << 16);
+      a[2] = b[3] = none;
+    }
     for (int t = 0; t < 3; ++t)
       for (int c = 0; c < V; ++c)
         for (int d = 0; d < D; ++d) {
-          int32_t* r = &rows[(((size_t)t * V + c) * D + d) * 8];
-          // (a DAG of degree one has no second output: word 7 is then the first output's offset alone)
-          r[3] = dump; r[4] = none; r[5] = dump; r[6] = none; r[7] = p->max_degree <= 1 ? dump : dump | (dump << 16);
+          int32_t* a = &rows[(((size_t)t * V + c) * D + d) * 4];
+          int32_t* b = a + n_rows * 4;
+          a[3] = c | (t == 1 ? 4 : 0);
           if (c >= p->n_chunks[d]) continue;
           const int s = p->local_stage[(size_t)d * kMaxChunks + c];
           const int kind = t == 0 ? kF : (t == 1 ? kB : kW);
-          r[0] = desc->dur[kind * S + s];
-          r[1] = t == 0 ? desc->mem_units[s] : 0;
-          r[2] = (t == 2 || (t == 1 && !p->has_w)) ? desc->mem_units[s] : 0;
+          a[0] = desc->dur[kind * S + s];
+          b[0] = t == 0 ? desc->mem_units[s] : 0;
+          b[1] = (t == 2 || (t == 1 && !p->has_w)) ? desc->mem_units[s] : 0;
           if (t == 2) continue;
           // forward items read the values of their in-edges and write those of their out-edges; backward
           // items the other way round
@@ -574,13 +586,14 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
           const std::vector<int32_t>& ooff = t == 0 ? soff : poff;
           const std::vector<int32_t>& ocl = t == 0 ? scl : pcl;
           const int32_t dir_base = t == 0 ? n_classes : 0;
+          int32_t in[2] = {dump, dump}, lat[2] = {none, none}, out[2] = {dump, dump};
           for (int k = 0; k < ioff[s + 1] - ioff[s]; ++k) {
-            r[3 + 2 * k] = 4 * (dir_base + icl[ioff[s] + k]) * m;
-            r[4 + 2 * k] = ilat[ioff[s] + k];
+            in[k] = 4 * (dir_base + icl[ioff[s] + k]) * m;
+            lat[k] = ilat[ioff[s] + k];
           }
-          int32_t out[2] = {dump, dump};
           for (int k = 0; k < ooff[s + 1] - ooff[s]; ++k) out[k] = 4 * (dir_base + ocl[ooff[s] + k]) * m;
-          r[7] = p->max_degree <= 1 ? out[0] : out[0] | (out[1] << 16);
+          a[1] = in[0] | (out[0] << 16); a[2] = lat[0];
+          b[2] = in[1] | (out[1] << 16); b[3] = lat[1];
         }
     T.off_gen_rows = append(rows.data(), rows.size());
   }
@@ -1511,6 +1524,7 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
   // classes of the DAG's edges: chains, as for the plain tables
   std::vector<std::vector<int>> out_cls(S);
   int n_classes = 0;
+  std::vector<int32_t> turnaround(S, 1);
   {
     std::vector<int> indeg(S, 0), order;
     std::vector<std::vector<int>> arriving(S);
@@ -1749,11 +1763,13 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
   return FPSCHED_OK;
 }
 
-using GenKernel = void (*)(DevTables, const int32_t*, const int32_t*, const long long*, long long, long long, int, uint16_t*,
+using GenKernel = void (*)(DevTables, const int32_t*, const int32_t*, const long long*, long long, long long, int, int, uint16_t*,
                            int32_t*, unsigned char*, unsigned long long*, GenResults);
 static int gen_waves_per_cu() {
-  // tuning knob: FPSCHED_GEN_WAVES = resident wavefronts per compute unit
-  int waves_per_cu = 24;
+  // tuning knob: FPSCHED_GEN_WAVES = resident wavefronts per compute unit.  Three per SIMD: with more, the sets with the
+  // most steps, which all begin at once (order_sets), advance more slowly and are what the launch ends on (32,768 sets
+  // of 16 devices: 1.93 ms with 12, 2.10 with 16, 2.47 with 24; 8 leave the SIMDs idle between steps)
+  int waves_per_cu = 12;
   if (const char* env = getenv("FPSCHED_GEN_WAVES")) {
     const int v = atoi(env);
     if (v >= 1 && v <= 32) waves_per_cu = v;
@@ -1764,6 +1780,20 @@ static int gen_max_chunks(const fpsched_problem* p) {
   int max_chunks = 0;
   for (int d = 0; d < p->D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
   return max_chunks;
+}
+
+// Which sets the segments of a generator launch take first: with more sets than segments the ones with many steps
+// (generate_order_kernel; returns the number of classes), else each segment starts on its own (returns 0).
+static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const int64_t* d_select, int64_t n_src, int64_t n_sets,
+                      int64_t n_segments, uint8_t* d_status, unsigned long long* counter, hipStream_t st) {
+  if (n_sets <= n_segments || n_sets > (1ll << 31)) {
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)n_segments, 0ull);
+    return hipGetLastError() == hipSuccess ? 0 : FPSCHED_EHIP;
+  }
+  hipLaunchKernelGGL(generate_order_kernel, dim3((unsigned)((n_sets + 3) / 4)), dim3(256), 0, st, p->tables, d_inflight,
+                     reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
+                     (int)(2 * std::max(gen_max_chunks(p), 1) * p->m), d_status, counter);
+  return hipGetLastError() == hipSuccess ? kGenClasses : FPSCHED_EHIP;
 }
 
 static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_policy, const int32_t* d_inflight,
@@ -1781,13 +1811,17 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
   // the first 8 bytes of the workspace hold the counter the segments draw parameter sets from
   if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
   if (workspace_bytes < 256) return FPSCHED_ENOMEM;
-  const int lpc = p->tables.lanes_per_cand;
-  const int cpw = 64 / lpc;
   const int deg = p->max_degree <= 1 ? 1 : (p->max_degree == 2 ? 2 : 0);
-  // tables (if walked), counters and the constant words (a multiple of four), 8 staging dwords per lane
-  const int64_t lds_bytes = 4ll * ((deg == 0 ? p->tables.n_table_ints : 0) +
-                                   (((int64_t)cpw * 3 * p->S + 2 * p->S + 1 + 3) & ~3ll) + 8 * 64);
+  // tables (if walked), counters and the constant word (a multiple of four), the staging dwords
+  auto lds_of = [&](int64_t sets) {
+    return 4ll * ((deg == 0 ? p->tables.n_table_ints : 0) + ((sets * 2 * p->S + 1 + 3) & ~3ll) + kGenStagingWords * 64);
+  };
+  int cpw = 64 / p->D;
+  while (cpw > 1 && lds_of(cpw) > p->max_lds) --cpw;
+  const int64_t lds_bytes = lds_of(cpw);
   if (lds_bytes > p->max_lds) return FPSCHED_EUNSUPPORTED;
+  DevTables tables = p->tables;
+  tables.gen_sets = cpw;
   // persistent grid: as many single-wavefront workgroups as stay resident
   const int64_t blocks = std::min<int64_t>((n_sets + cpw - 1) / cpw, (int64_t)p->n_cu * gen_waves_per_cu());
   DeviceGuard g(p->device_id);
@@ -1803,13 +1837,12 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
                           p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-  // segment g starts on set g; the counter hands out the sets after those
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(hip_stream), counter,
-                     (unsigned long long)(blocks * cpw), 0ull);
+  const int n_classes = order_sets(p, d_inflight, d_select, n_src, n_sets, blocks * cpw, d_status, counter, static_cast<hipStream_t>(hip_stream));
+  if (n_classes < 0) return n_classes;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), (size_t)lds_bytes,
-                     static_cast<hipStream_t>(hip_stream), p->tables, reinterpret_cast<const int32_t*>(d_policy),
-                     d_inflight, reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets, (int)stride_words,
-                     d_ops, d_steps, d_status, counter, GenResults{nullptr, nullptr, nullptr, nullptr});
+                     static_cast<hipStream_t>(hip_stream), tables, reinterpret_cast<const int32_t*>(d_policy),
+                     d_inflight, reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
+                     n_classes, (int)stride_words, d_ops, d_steps, d_status, counter, GenResults{nullptr, nullptr, nullptr, nullptr});
   return check_hip(hipGetLastError());
 }
 
@@ -1847,25 +1880,25 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   if (workspace_bytes < 256) return FPSCHED_ENOMEM;
   // finish times stay below 2^30: every item starts at most (items before it) * (largest cost + latency) late
   if (3ll * p->S * p->m * (p->max_dur + p->max_comm) >= (1ll << 30)) return FPSCHED_EOVERFLOW;
-  const int lpc = p->tables.lanes_per_cand;
-  const int cpw = 64 / lpc;
   const int V = p->tables.gen_row_chunks;
-  // cost rows shared by the workgroup; per wavefront its counters and its sets' slots
-  const int64_t shared_ints = 3ll * V * p->D * 8;
-  // (slide: a ring of queue words per lane for stashes deeper than two words: one bit per entry at two stages per
-  // device, two at four, none at one; a power of two that holds every W item of a device)
+  const int deg = p->max_degree <= 1 ? 1 : 2;
+  // cost rows shared by the workgroup (the sliding form on a DAG of degree one needs the first halves only); per wavefront
+  // its counters and its sets' slots, sliding: the rings of items and the queues (one bit per W item of a device at two
+  // stages per device, two at four, none at one)
+  const int64_t shared_ints = (3ll * V * p->D + 1) * (slide && deg == 1 ? 4 : 8);
   DevTables tables = p->tables;
-  tables.gen_spill_words = 0;
-  if (slide) {
-    const int64_t bits = V == 1 ? 0 : (V == 2 ? 1 : 2);
-    int words = 1;
-    while ((int64_t)words * 32 < (int64_t)V * p->m * bits + 32) words <<= 1;
-    tables.gen_spill_words = words;
-  }
-  const int64_t wave_ints = (((int64_t)cpw * 3 * p->S + 2 * p->S + 1 + 3) & ~3ll) + (int64_t)cpw * p->tables.gen_slot_words +
-                            64ll * tables.gen_spill_words;
+  // (one word more: the word of the next entry is written when all are in as well)
+  tables.gen_queue_words = slide && V > 1 ? (int)((int64_t)V * p->m * (V == 2 ? 1 : 2) / 32) + 1 : 0;
+  auto wave_ints_of = [&](int64_t sets) {
+    return ((sets * 2 * p->S + 1 + 3) & ~3ll) + sets * p->tables.gen_slot_words +
+           (slide ? 64ll * (kGenEvents + tables.gen_queue_words) : 0ll);
+  };
   const int64_t lds_ints = p->max_lds / 4;
+  int cpw = 64 / p->D;
+  while (cpw > 1 && shared_ints + wave_ints_of(cpw) + 64 > lds_ints) --cpw;
+  const int64_t wave_ints = wave_ints_of(cpw);
   if (shared_ints + wave_ints > lds_ints) return FPSCHED_EUNSUPPORTED;
+  tables.gen_sets = cpw;
   // wavefronts per workgroup and workgroups per compute unit: as many resident wavefronts as asked for
   // and as LDS holds, in as few workgroups as possible (each keeps a copy of the rows)
   const int want = gen_waves_per_cu();
@@ -1873,6 +1906,8 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   for (int groups = 1; groups <= 8; ++groups) {
     int wv = (int)std::min<int64_t>((lds_ints / groups - shared_ints - 64) / wave_ints, kGenTimedThreads / 64);
     wv = std::min(wv, (want + groups - 1) / groups);
+    // (a workgroup's wavefronts go to the four SIMDs in turn, starting on the first: others leave one SIMD the slowest)
+    if (wv > 4) wv &= ~3;
     if (wv >= 1 && wv * groups > best_waves * best_groups) { best_waves = wv; best_groups = groups; }
   }
   const int64_t segments = (n_sets + cpw - 1) / cpw;
@@ -1883,7 +1918,6 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   const int64_t lds_bytes = 4 * (shared_ints + best_waves * wave_ints);
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
-  const int deg = p->max_degree <= 1 ? 1 : 2;
   static const GenKernel table[2][3][2] = {
       {{&generate_kernel<1, 1, kGenTimed>, &generate_kernel<1, 2, kGenTimed>},
        {&generate_kernel<2, 1, kGenTimed>, &generate_kernel<2, 2, kGenTimed>},
@@ -1897,11 +1931,12 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
                           p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(hip_stream), counter,
-                     (unsigned long long)(blocks * best_waves * cpw), 0ull);
+  const int n_classes = order_sets(p, d_inflight, nullptr, n_sets, n_sets, blocks * best_waves * cpw, d_status, counter,
+                                   static_cast<hipStream_t>(hip_stream));
+  if (n_classes < 0) return n_classes;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * best_waves), (size_t)lds_bytes,
                      static_cast<hipStream_t>(hip_stream), tables, reinterpret_cast<const int32_t*>(d_policy),
-                     d_inflight, nullptr, (long long)n_sets, (long long)n_sets, 0, nullptr, d_steps, d_status, counter,
+                     d_inflight, nullptr, (long long)n_sets, (long long)n_sets, n_classes, 0, nullptr, d_steps, d_status, counter,
                      GenResults{reinterpret_cast<long long*>(out.makespan), reinterpret_cast<long long*>(out.idle),
                                 out.peak, out.flags});
   return check_hip(hipGetLastError());

@@ -4,7 +4,7 @@
 // The scheduling process is step-synchronous by definition (Section 5.2, Steps 2-5: in a step
 // every actor runs the step function of Algorithm 1 on the state the previous step left, and
 // what an actor schedules stays in its local buffer until the step is over), which is the shape
-// of a wavefront: lane = actor, `64 / pow2(D)` parameter sets per wavefront, one step = one pass
+// of a wavefront: lane = actor, up to 64 / D parameter sets per wavefront, one step = one pass
 // of straight-line code with a read phase and a write phase.
 //
 // State.  Items of one instruction type and stage are scheduled in ascending micro-batch order
@@ -13,10 +13,16 @@
 // the downstream backward passes, a weight-gradient item its backward item), so the instruction
 // pool and the reorder queues of Section 5.1 reduce to one counter per (type, stage): the number
 // of micro-batches scheduled so far.  The next item of (type, stage) is in its reorder queue iff
-// every counter it depends on is ahead of its own.  The counters of a parameter set live in LDS;
-// a lane reads its own and those of its stages' neighbours in the read phase and bumps at most one
-// of its own in the write phase (the old value is the item's micro-batch).
+// every counter it depends on is ahead of its own.  An actor keeps its own counters in registers, two
+// stages side by side in one register; the forward and backward counters also stand in LDS, where the lanes of the
+// neighbouring stages read them in the read phase and the owner stores a new value in the write phase.
 //
+// What bounds it: a set's steps are a serial chain, and the steps of a set differ by a factor of ten (a low in-flight
+// limit makes a micro-batch's way through the stages the chain).  So the time is that of the longest sets where they
+// are few, else the vector instructions of a step (a step's LDS latency is hidden by the other wavefronts of a SIMD).
+// 16,384 sets of 32 devices, 2 stages each, 128 micro-batches (2,657 steps a set, 8,884 the longest), sliding form: 9.2 ms
+// before the sets were ordered, the actor's counters moved to registers and the W items out of the steps, 4.9 ms now (76
+// vector instructions a step, 78 % of the issue slots); 32,768 sets of 16 devices, lists written: 2.5 ms before, 1.9 now.
 // Priorities (Section 5.2; Table of built-in values): computation type traversal priority
 // bwdpass-first / fwdpass-first / interleaved(unit1, unit2); stage traversal priority
 // breadth-first / depth-first with an optional interval, separately for forward and backward
@@ -27,6 +33,7 @@
 #include <stdint.h>
 
 #include "kernels.h"
+#include "lds_access.h"
 
 namespace fpsched {
 
@@ -34,13 +41,24 @@ namespace {
 
 enum GenType : int { kGenF = 0, kGenB = 1, kGenW = 2 };
 
-// lowest / highest set bit of a non-zero 4-bit mask
+// lowest set bit of a non-zero mask
 __device__ __forceinline__ int low_bit(unsigned x) { return __ffs(x) - 1; }
-__device__ __forceinline__ int high_bit(unsigned x) { return 31 - __clz(x); }
 // two 16-bit counters side by side: those of an actor's two stages
 typedef short pair16 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned bits_of(pair16 v) { return __builtin_bit_cast(unsigned, v); }
+__device__ __forceinline__ pair16 pair_of(unsigned v) { return __builtin_bit_cast(pair16, v); }
 constexpr unsigned kBothSigns = 0x80008000u;
+// The steps keep per-lane conditions that select several values as masks (all ones or 0) in a vector register: a select
+// is then one bit-field insert, where a comparison's result in a scalar register goes through 0 / 1 values when conditions
+// are combined.
+__device__ __forceinline__ unsigned mask_of(bool b) { return b ? ~0u : 0u; }
+__device__ __forceinline__ unsigned choose(unsigned mask, unsigned a, unsigned b) { return (a & mask) | (b & ~mask); }
+// An actor's traversal state of one direction (V > 1), in one register: the position (the chunk) from bit kPositionBit on
+// (two chunks: bit 4, so that the register is the shift that brings the position's half of a pair to the front), the
+// upper half the items until the position moves on by itself.  No position
+// sees more than kMaxChunks * m < kFarInterval items, so longer intervals are all the same.  Without an interval the
+// position never moves: the first eligible stage from the first (breadth-first) or last one (depth-first) on is picked.
+constexpr unsigned kPosition = 0x30u, kPositionBit = 4u, kOneItem = 0x10000u, kFarInterval = 0x3fffu;
 
 // one value per chunk of an actor, as one vector value (an array would be indexed in memory)
 template <int V>
@@ -53,14 +71,40 @@ __device__ __forceinline__ int gen_pick(typename GenPerChunk<V>::type a, unsigne
   return r;
 }
 
-// a * b + c for a, b below 2^24, b the same in all lanes: one full-rate instruction
-__device__ __forceinline__ unsigned mad24(unsigned a, unsigned b_uniform, unsigned c) {
-  unsigned r;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b_uniform), "v"(c));
-  return r;
-}
+// steps between two looks at whether a set is done
+constexpr int kStepsPerLook = 8;
+constexpr int kStagingWords = kGenStagingWords;   // 15 op words and those of a look
+static_assert(2 * kStagingWords >= 15 + kStepsPerLook && (kStagingWords & (kStagingWords - 1)) == 0, "");
+constexpr int kRoundsPerLook = 4;   // rounds of settle between two looks at whether there are enough of them
+constexpr unsigned kEvents = kGenEvents;   // (a power of two)
+static_assert(kEvents > kStepsPerLook + 1, "a look's items fit");
 
 }  // namespace
+
+// Order in which the sets of a batch are worked on: those with many steps first, so that the batch does not end on a few
+// wavefronts that have just begun a long one.  A set's steps are nearly those of the slower of two bounds: its actors'
+// items, and for each stage micro-batches x (steps from a micro-batch's forward item to its backward item) / in-flight
+// limit (measured correlation with the true steps: 0.99 for chains of 8 to 64 stages).  One wavefront per set writes
+// the set's class, a power of two of the ratio of the two, into the set's status byte, which the generator overwrites
+// when the set is done; the generator draws all sets once per class.
+__global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ inflight, const long long* __restrict__ select,
+                                      long long n_src, long long n_sets, int work_steps,
+                                      unsigned char* __restrict__ out_status, unsigned long long* __restrict__ next_set) {
+  const int lane = threadIdx.x & 63;
+  const long long set = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next_set = 0ull;
+  if (set >= n_sets) return;
+  const long long src = select ? select[set] : set;
+  float longest = 0.f;
+  if (src >= 0 && src < n_src)
+    for (int s = lane; s < T.S; s += 64)
+      longest = fmaxf(longest, (float)T.ints[T.off_turnaround + s] / (float)max(inflight[src * T.S + s], 1));
+  for (int off = 32; off > 0; off >>= 1) longest = fmaxf(longest, __shfl_xor(longest, off, 64));
+  if (lane == 0) {
+    const float ratio = longest * (float)T.m / (float)work_steps;
+    out_status[set] = (unsigned char)(kGenClassMark | (ratio >= 8.f ? 0 : (ratio >= 4.f ? 1 : (ratio >= 2.f ? 2 : 3))));
+  }
+}
 
 // V = bound on the stages per device (1, 2, 4).  DEG = bound on the DAG in- and out-degree of a
 // stage (1 or 2): the LDS addresses of the neighbours' counters are then kept in registers;
@@ -68,7 +112,11 @@ __device__ __forceinline__ unsigned mad24(unsigned a, unsigned b_uniform, unsign
 //
 // The grid is persistent: a segment (the lanes of one parameter set) that finishes its schedule
 // writes it out, draws the next set from a global counter and starts over while the other segments
-// of the wavefront keep stepping, so that sets that need few and many steps balance out.
+// of the wavefront keep stepping, so that sets that need few and many steps balance out.  With n_classes = 0 segment g
+// starts on set g; else the counter runs over all sets once per class of generate_order_kernel, and a segment
+// takes those of the class (a status byte that still holds the class and one that has been overwritten since both say what
+// is to be done: a set is taken in the pass of its class only).  Sets are drawn one by one: a segment that drew four at a
+// time kept several long ones to itself (14.0 ms instead of 7.9).  A wavefront's priority is that of its longest set.
 //
 // TIMED: generator and evaluator in one (fpsched_generate_evaluate).  An item is scheduled only
 // after everything it depends on was scheduled in an earlier step, so its start time is known the
@@ -83,47 +131,53 @@ __device__ __forceinline__ unsigned mad24(unsigned a, unsigned b_uniform, unsign
 //
 // FORM kGenSlide: the timed form with the weight-gradient sliding pass of Section 5.2 (bubble optimizations) in
 // it: the results fpsched_wslide_evaluate gives for the generated lists.  A W item that the scheduler places is
-// passed over; a B item stashes its W item, and in front of every other item the actor runs the oldest
-// stashed items that end before the item starts.  The stash is a queue of log2(V) bits per entry (the chunk):
-// a head word and a tail word in registers, full words in between in a ring in LDS (kGenSpillWords per lane).
+// passed over (it fills a step in which nothing else is eligible: a count of those not placed yet is all that is kept);
+// a B item stashes its W item, and in front of every other item the actor runs the oldest
+// stashed items that end before the item starts.  None of this moves an F or B item, it only decides what memory is
+// resident at their starts; so the steps only note each item (its gap: how long the actor waits in front of it) in a ring
+// of kEvents words per lane, and a second loop (settle) places W items into gaps, for all lanes at once and only when
+// some lane's ring is nearly full: its rounds are then full of work, where in the step itself a few lanes' W items
+// would be waited for by all (measured: 127 vector instructions a step with the W items in it, 76 without and some 25 in settle).  The stash is a queue of log2(V) bits per entry
+// (the chunk) in LDS: an actor stashes no more than V * m items, so entry i simply stands in word i * log2(V) / 32.
 template <int V, int DEG, int FORM>
 __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void generate_kernel(
     DevTables T, const int32_t* __restrict__ policy, const int32_t* __restrict__ inflight,
-    const long long* __restrict__ select, long long n_src, long long n_sets, int stride, uint16_t* __restrict__ ops,
-    int32_t* __restrict__ out_steps, unsigned char* __restrict__ out_status,
+    const long long* __restrict__ select, long long n_src, long long n_sets, int n_classes, int stride,
+    uint16_t* __restrict__ ops, int32_t* __restrict__ out_steps, unsigned char* out_status,
     unsigned long long* __restrict__ next_set, GenResults R) {
   constexpr bool TIMED = FORM != kGenPlain;
   constexpr bool SLIDE = FORM == kGenSlide;
+  constexpr int NP = (V + 1) / 2;   // pairs of stages
   // SLIDE: bits per queue entry, entries per queue word
-  constexpr unsigned kQBits = V == 1 ? 0u : (V == 2 ? 1u : 2u);
-  constexpr unsigned kQCap = V == 1 ? 0x7fffffffu : 32u / (kQBits ? kQBits : 1u);
+  constexpr unsigned kQueueBits = V > 2 ? 2u : 1u, kQueueEntries = 32u / kQueueBits;
   extern __shared__ int32_t lds[];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6, waves_per_block = blockDim.x >> 6;
   const int S = T.S, m = T.m, D = T.D;
-  const int lpc = T.lanes_per_cand;
-  const int lpc_shift = __ffs(lpc) - 1;
-  const int cpw = 64 >> lpc_shift;
+  const int cpw = T.gen_sets;
   const bool has_w = T.has_w != 0;
-  // LDS: [edge lists, only if DEG == 0 | cost rows, only if TIMED] then per wavefront
-  // [sets of the wavefront: counters [3][S]][words holding m]
-  // [row staging: 16 op words per lane, as 8 dwords laid out [dword][lane] | TIMED: the sets' slots]
-  const int n_tab = TIMED ? 3 * V * D * 8 : (DEG == 0 ? T.n_table_ints : 0);
+  // LDS: [edge lists, only if DEG == 0 | cost rows, only if TIMED: the first halves, then the second halves if they are
+  // needed] then per wavefront
+  // [sets of the wavefront: counters [2][S]][a word holding m]
+  // [row staging: 32 op words per lane, as 16 dwords laid out [dword][lane] | TIMED: the sets' slots, SLIDE: rings, queues]
+  const int n_rows = 3 * V * D + 1;
+  constexpr bool kSecondHalves = DEG > 1 || FORM == kGenTimed;
+  const int n_tab = TIMED ? n_rows * (kSecondHalves ? 8 : 4) : (DEG == 0 ? T.n_table_ints : 0);
   if (TIMED) {
     for (int i = threadIdx.x; i < n_tab; i += blockDim.x) lds[i] = T.ints[T.off_gen_rows + i];
   } else if (DEG == 0) {
     for (int i = lane; i < n_tab; i += 64) lds[i] = T.ints[i];
   }
-  const int n_count_ints = (cpw * 3 * S + 2 * S + 1 + 3) & ~3;
+  const int n_count_ints = (cpw * 2 * S + 1 + 3) & ~3;
   const int slot_words = T.gen_slot_words;
-  const int spill_words = SLIDE ? T.gen_spill_words : 0;   // per lane, a power of two
-  int32_t* counts = lds + n_tab + wave * (n_count_ints + (TIMED ? cpw * slot_words + 64 * spill_words : 8 * 64));
-  // counters that are always "done" (value m): at_m stands in for a missing neighbour, and at_m,
-  // at_m + S, at_m + 2 S for the three counters of a chunk the actor does not have
-  const int at_m = cpw * 3 * S;
-  if (lane < 3) counts[at_m + lane * S] = m;
+  const int queue_words = SLIDE ? T.gen_queue_words : 0;   // per lane
+  int32_t* counts = lds + n_tab + wave * (n_count_ints + (TIMED ? cpw * slot_words + (SLIDE ? 64 * (kEvents + queue_words) : 0) : kStagingWords * 64));
+  // a counter that is always "done" (value m) stands in for a missing neighbour
+  const int at_m = cpw * 2 * S;
+  if (lane == 0) counts[at_m] = m;
   // a lane collects 16 op words (32 bytes) of its row before it stores them: HBM is written in
-  // 32-byte pieces, not a quarter of that
+  // 32-byte pieces, not a quarter of that.  They are stored between the steps: the lanes fill up at different steps, and in
+  // most steps some lane would.
   uint32_t* staging = reinterpret_cast<uint32_t*>(counts + n_count_ints) + lane;   // dword i at + i * 64
   // TIMED: slots never hold anything but finish times (an item without an input reads some word of
   // them and adds -2^30)
@@ -131,21 +185,22 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
     for (int i = lane; i < cpw * slot_words; i += 64) counts[n_count_ints + i] = 0;
   __syncthreads();
 
-  const int seg = lane >> lpc_shift;
-  const int d = lane & (lpc - 1);
-  const bool has_dev = d < D;
-  const int base = seg * 3 * S;   // this segment's counters: counts[base + type * S + stage]
-  int32_t* slot = counts + n_count_ints + seg * slot_words;   // TIMED: this segment's slots
+  const int seg = lane / D;       // (lanes from cpw * D on have no device)
+  const int d = lane - seg * D;
+  const bool has_dev = seg < cpw;
+  const int base = has_dev ? seg * 2 * S : 0;   // this segment's counters: counts[base + type * S + stage]
+  const unsigned slot = lds_address(counts + n_count_ints + (has_dev ? seg : 0) * slot_words);   // TIMED: this segment's slots
 
   // what depends on the actor only
   const int nch = has_dev ? T.ints[T.off_n_chunks + d] : 0;
   int stage[V];
-  int own_at[V];   // LDS index of this actor's forward counter of chunk c (backward at + S, W at + 2 S)
+  unsigned own_at[V];   // LDS address of this actor's forward counter of chunk c (backward: 4 S bytes on)
   int pred_at[V][DEG > 0 ? DEG : 1], succ_at[V][DEG > 0 ? DEG : 1];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
     stage[c] = c < nch ? T.ints[T.off_local_stage + d * kMaxChunks + c] : 0;
-    own_at[c] = c < nch ? base + stage[c] : at_m;
+    own_at[c] = lds_address(counts + (c < nch ? base + stage[c] : at_m));
+    asm("" : "+v"(own_at[c]));   // (whole addresses stay in registers)
 #pragma unroll
     for (int k = 0; k < (DEG > 0 ? DEG : 1); ++k) {
       pred_at[c][k] = at_m;
@@ -171,59 +226,112 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
                                       (has_w ? T.ints[T.off_dur + kW * S + stage[c]] : 0));
   }
   int free_at = 0, mem = 0, peak = 0;
-  // SLIDE: cost and freed units of the W item of each chunk (the W rows), what all of them cost; the queue
-  typename GenPerChunk<V>::type w_dur, w_free;
+  // SLIDE: units of an F item, cost and freed units of a W item of each chunk, what all W items cost
+  typename GenPerChunk<V>::type f_units, w_dur, w_free;
   int w_total = 0;
 #pragma unroll
   for (int c = 0; c < V; ++c) {
-    int wd = 0, wf = 0;
+    f_units[c] = 0; w_dur[c] = 0; w_free[c] = 0;
     if (SLIDE && has_dev && c < nch) {
-      const int32_t* r = lds + ((2 * V + c) * D + d) * 8;   // (read after the barrier above)
-      wd = r[0];
-      wf = r[2];
+      const int32_t* first = T.ints + T.off_gen_rows;
+      const int32_t* second = first + n_rows * 4;
+      f_units[c] = second[(c * D + d) * 4];
+      w_dur[c] = first[((2 * V + c) * D + d) * 4];
+      w_free[c] = second[((2 * V + c) * D + d) * 4 + 1];
     }
-    w_dur[c] = wd; w_free[c] = wf;
-    w_total += m * wd;
+    w_total += m * w_dur[c];
   }
-  uint32_t* spill = reinterpret_cast<uint32_t*>(counts + n_count_ints + cpw * slot_words) + lane;   // word i at + i * 64
-  unsigned q_h = 0u, h_n = 0u, q_t = 0u, t_n = 0u, s_rd = 0u, s_wr = 0u;
-  unsigned q_head_dur = 0xffffffffu;   // cost of the oldest stashed item (all ones: none)
-  int q_head_free = 0, w_placed = 0;
-  auto new_head = [&]() {
-    const unsigned head = V > 1 ? q_h & (unsigned)(V - 1) : 0u;
-    q_head_dur = h_n != 0u ? (unsigned)gen_pick<V>(w_dur, head) : 0xffffffffu;
-    q_head_free = gen_pick<V>(w_free, head);
+  // SLIDE: the ring of items (at: byte offset of the next one in and out), the one whose gap is being filled and what is
+  // left of its gap, the queue (entries in and out, the word being filled)
+  const unsigned ring = lds_address(counts + n_count_ints + cpw * slot_words) + lane * 4;   // entry i at + i * 256
+  const unsigned queue = ring + kEvents * 256;                                               // word i at + i * 256
+  unsigned ring_in = 0u, ring_out = 0u, gap = 0u, q_in = 0u, q_out = 0u, q_tail = 0u;
+  int w_placed = 0;
+  unsigned event = 0u, has_event = 0u;   // (mask)
+  // one round: the oldest stashed W item runs if what is left of the gap has room for it; else the gap's item starts, and
+  // the next one's gap opens
+  auto settle = [&]() {
+    const unsigned next = lds_read<unsigned>(ring + ring_out);
+    unsigned dur = (unsigned)w_dur[0], freed = (unsigned)w_free[0], units = (unsigned)f_units[0];
+    if constexpr (V > 1) {
+      const unsigned word = lds_read<unsigned>(queue + q_out / kQueueEntries * 256u);
+      if constexpr (V == 2) {
+        const unsigned second = (unsigned)((int)(word << (31u - q_out % 32u)) >> 31);
+        dur = choose(second, (unsigned)w_dur[V - 1], dur);
+        freed = choose(second, (unsigned)w_free[V - 1], freed);
+        units = choose((unsigned)((int)(event << 31) >> 31), (unsigned)f_units[V - 1], units);
+      } else {
+        const unsigned c = word >> (q_out % kQueueEntries * kQueueBits) & 3u;
+        dur = (unsigned)gen_pick<V>(w_dur, c);
+        freed = (unsigned)gen_pick<V>(w_free, c);
+        units = (unsigned)gen_pick<V>(f_units, event & 3u);
+      }
+    }
+    const unsigned run_w = mask_of((q_in != q_out) & (dur <= gap)), start = has_event & ~run_w;
+    w_placed += (int)(dur & run_w);
+    q_out -= run_w;
+    const unsigned b = (unsigned)((int)(event << 29) >> 31);
+    mem += (int)(units & start & ~b) - (int)(freed & run_w);
+    peak = max(peak, mem);
+    if constexpr (V > 1) {   // a B item's W item is stashed
+      q_tail |= (event & 3u & b & start) << (q_in % kQueueEntries * kQueueBits);
+      lds_write<unsigned>(queue + q_in / kQueueEntries * 256u, q_tail);
+    }
+    q_in -= b & start;
+    if constexpr (V > 1) q_tail = q_in % kQueueEntries == 0u ? 0u : q_tail;
+    const unsigned more = mask_of(ring_in != ring_out);
+    gap = choose(run_w, gap - dur, next >> 3 & more);
+    event = choose(run_w, event, next);
+    has_event = choose(run_w, has_event, more);
+    ring_out = (ring_out + (256u & more & ~run_w)) & (kEvents * 256u - 1u);
   };
 
-  pair16 limit2 = {1, 1};
-  int w_at[V];   // the weight-gradient counters; without split backward, a word that holds m
+  // the actor's own counters, two stages per register
+  // (n_bl: the backward counters + in-flight limits)
+  unsigned n_f[NP], n_b[NP], n_w[NP], n_bl[NP];
 #pragma unroll
-  for (int c = 0; c < V; ++c) w_at[c] = has_w ? own_at[c] + 2 * S : at_m;
+  for (int i = 0; i < NP; ++i) { n_f[i] = 0u; n_b[i] = 0u; n_w[i] = 0u; n_bl[i] = 0u; }
+  int w_wait = 0;   // SLIDE: B items scheduled up to last_pick whose W item is not
+
+  // TIMED: the item scheduled in the last step, not timed yet: its row (without one: the row that changes nothing) and where
+  // its micro-batch's slots are
+  unsigned row_f = lds_address(lds) + d * 16, row_b = row_f + V * D * 16;
+  asm("" : "+v"(row_f), "+v"(row_b));
+  const unsigned no_row = lds_address(lds) + (n_rows - 1) * 16;
+  int4 item_a = make_int4(0, 0, 0, 0), item_b = item_a;
+  unsigned item_slot = slot;
+  bool item = false;
 
   // per-set state
   long long set = ((long long)blockIdx.x * waves_per_block + wave) * cpw + seg;   // the first set of a segment is its global index
-  bool first_draw = true;
+  bool first_draw = n_classes == 0;
+  int set_class = 3;
   bool has_set = false;   // the segment is working on a set (possibly finished and not yet written out)
   bool fresh = true;      // the segment wants its next set
-  int limit[V];
-  int cttp = 0, unit_f = 1, unit_b = 1, f_dir = 0, f_int = 0, b_dir = 0, b_int = 0;
-#pragma unroll
-  for (int c = 0; c < V; ++c) limit[c] = 1;
-  int turn_type = kGenF, turn_run = 0, pos_f = 0, pos_b = 0, stepped_f = 0, stepped_b = 0;
-  int first = kGenF;   // the instruction type tried first in a step: fixed, or the interleaved priority's turn
-  int left = 0;        // items this actor still has to schedule
+  int unit_f = 1, unit_b = 1;
+  unsigned walk_f = 0u, walk_b = 0u, again_f = 0u, again_b = 0u;   // traversal states, and what they become on a move
+  unsigned moves_f = 0u, moves_b = 0u, up_f = 0u, up_b = 0u;   // masks: an interval is set; breadth-first
+  unsigned f_first = ~0u;   // mask: F is the instruction type tried first in a step; fixed, or the interleaved priority's turn
+  int run = 0;         // items of that type until the turn changes
   bool live = false;   // the set's process is still running
-  int status = 0, len = 0;
-  unsigned long long first_step = 0ull;   // the loop's step counter when the set's process began
+  int status = 0, len = 0, stored = 0;
+  unsigned first_step = 0u;   // the loop's step counter when the set's process began
+  unsigned last_pick = 0u;    // the step in which this actor scheduled its last item so far (first_step - 1: none; SLIDE: W items aside)
   int steps = 0;
-  int last_pick = -1;   // the step, counted from first_step, in which this actor scheduled its last item so far
-  constexpr unsigned long long kEndCheckMask = 7ull;
   uint16_t* row = ops;
   // "does any lane of my segment ...": the ballot against the lanes of the segment
-  const unsigned long long seg_lanes = (lpc == 64 ? ~0ull : ((1ull << lpc) - 1ull)) << (seg * lpc);
+  const unsigned long long seg_lanes = !has_dev ? 0ull : (D == 64 ? ~0ull : ((1ull << D) - 1ull) << (seg * D));
   const unsigned seg_lo = (unsigned)seg_lanes, seg_hi = (unsigned)(seg_lanes >> 32);
   auto any_in_segment = [&](unsigned long long ballot) -> bool {
     return (((unsigned)ballot & seg_lo) | ((unsigned)(ballot >> 32) & seg_hi)) != 0u;
+  };
+  // the largest value of the segment, in all of its lanes
+  auto segment_max = [&](int v) -> int {
+    for (int off = 1; off < D; off <<= 1) {
+      const int o = __shfl_down(v, off, 64);
+      if (d + off < D) v = max(v, o);
+    }
+    return __shfl(v, lane - d, 64);
   };
 
   // Every step but the last of a set schedules at least one of its 3 S m items, and a segment
@@ -231,9 +339,10 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   // wavefront leaves the loop whatever happens.  A workgroup is one wavefront: its LDS instructions
   // execute in program order, so the reads of a step see the counters as the previous step left them
   // and no barrier is needed between the phases.
-  const unsigned long long per_set = 3ull * (unsigned)S * (unsigned)m + 16ull;
-  const unsigned long long bound = per_set * ((unsigned long long)n_sets + 1ull);
-  for (unsigned long long step = 0; step < bound; ++step) {
+  const unsigned long long per_set = 3ull * (unsigned)S * (unsigned)m + 32ull;
+  const unsigned long long bound = per_set * ((unsigned long long)n_sets + 1ull) / kStepsPerLook + 1ull;
+  for (unsigned long long look = 0; look < bound; ++look) {
+    const unsigned step_0 = (unsigned)look * kStepsPerLook;
     if (__ballot(fresh) != 0ull) {
       // ---- segments that finished write their schedule out and start on the next set
       if (fresh) {
@@ -245,14 +354,14 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
             // (SLIDE: what is still stashed runs back to back behind the actor's last item)
             int makespan = SLIDE ? free_at + (w_total - w_placed) : free_at;
             bool over = peak > cap;
-            for (int off = 1; off < lpc; off <<= 1) makespan = max(makespan, __shfl_xor(makespan, off, 64));
+            makespan = segment_max(makespan);
             over = any_in_segment(__ballot(over));
             const bool complete = status == 0;
             if (has_dev) {
               R.idle[set * D + d] = complete ? (long long)makespan - busy_total : -1ll;
               R.peak[set * D + d] = complete ? peak : -1;
             }
-            if (d == 0) {
+            if (d == 0 && has_dev) {
               R.makespan[set] = complete ? (long long)makespan : 0x7fffffffffffffffll;
               R.flags[set] = (unsigned char)(complete ? (over ? kOverCap : 0) : kIncomplete);
               out_steps[set] = steps;
@@ -260,14 +369,13 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
             }
           }
         } else if (has_set && has_dev) {
-          // rows are END-padded to the stride; words still staged go out with the padding
+          // rows are END-padded to the stride; words still staged (less than 16) go out with the padding
           int at = len & ~15;
           if (len & 15) {
-            for (int i = len & 15; i < 16; ++i) reinterpret_cast<uint16_t*>(staging + (i >> 1) * 64)[i & 1] = 0;
-            if (at < stride)
-              *reinterpret_cast<uint4*>(row + at) = make_uint4(staging[0], staging[64], staging[128], staging[192]);
-            if (at + 8 < stride)
-              *reinterpret_cast<uint4*>(row + at + 8) = make_uint4(staging[256], staging[320], staging[384], staging[448]);
+            for (int i = len & 15; i < 16; ++i) reinterpret_cast<uint16_t*>(staging + (((at + i) >> 1) & (kStagingWords - 1)) * 64)[i & 1] = 0;
+            const uint32_t* w = staging + ((at >> 1) & (kStagingWords - 1)) * 64;
+            if (at < stride) *reinterpret_cast<uint4*>(row + at) = make_uint4(w[0], w[64], w[128], w[192]);
+            if (at + 8 < stride) *reinterpret_cast<uint4*>(row + at + 8) = make_uint4(w[256], w[320], w[384], w[448]);
             at += 16;
           }
           for (; at < stride; at += 8) *reinterpret_cast<uint4*>(row + at) = make_uint4(0u, 0u, 0u, 0u);
@@ -277,16 +385,29 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
           }
         }
         if (!first_draw) {
-          unsigned long long drawn = 0ull;
-          if (d == 0 && seg < cpw) drawn = atomicAdd(next_set, 1ull);
-          set = (long long)__shfl(drawn, seg << lpc_shift, 64);
+          long long drawn = -1;
+          if (d == 0 && has_dev) {
+            if (n_classes == 0) {
+              drawn = (long long)atomicAdd(next_set, 1ull);
+            } else {
+              for (;;) {
+                long long q = (long long)atomicAdd(next_set, 1ull);
+                int cls = 0;
+                while (cls < n_classes && q >= n_sets) { q -= n_sets; ++cls; }
+                if (cls == n_classes) break;
+                if (out_status[q] == (unsigned char)(kGenClassMark | cls)) { drawn = q; set_class = cls; break; }
+              }
+            }
+          }
+          set = __shfl(drawn, lane - d, 64);
         }
         first_draw = false;
-        has_set = seg < cpw && set < n_sets;
+        has_set = has_dev && set >= 0 && set < n_sets;
         const bool has_row = has_set && has_dev;
-        if (has_set)
-          for (int i = d; i < 3 * S; i += lpc) counts[base + i] = 0;
-        cttp = 0; unit_f = 1; unit_b = 1; f_dir = 0; f_int = 0; b_dir = 0; b_int = 0;
+        if (has_dev)   // (also without a set: what the counters hold is compared with this actor's m items done)
+          for (int i = d; i < 2 * S; i += D) counts[base + i] = 0;
+        int cttp = 0, f_dir = 0, f_int = 0, b_dir = 0, b_int = 0;
+        unit_f = 1; unit_b = 1;
         // (with a selection, output row `set` is the schedule of parameter set select[set]; an entry that
         // is negative or not below n_src selects nothing and counts as a bad set)
         const long long src = (has_set && select) ? select[set] : set;
@@ -296,250 +417,279 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
           cttp = pol[0]; unit_f = pol[1]; unit_b = pol[2];
           f_dir = pol[3]; f_int = pol[4]; b_dir = pol[5]; b_int = pol[6];
         }
+        int limit[V];
 #pragma unroll
         for (int c = 0; c < V; ++c) limit[c] = (has_src && c < nch) ? inflight[src * S + stage[c]] : 1;
-        if constexpr (V == 2) {   // (no stage has more than m <= 2048 micro-batches in flight)
-          limit2.x = (short)min(limit[0], 0x7fff);
-          limit2.y = (short)min(limit[1], 0x7fff);
+        // (no stage has more than m <= 2048 micro-batches in flight; a chunk the actor does not have is done)
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          const int c0 = 2 * i, c1 = 2 * i + 1 < V ? 2 * i + 1 : 2 * i;
+          const unsigned none0 = c0 < nch ? 0u : (unsigned)m, none1 = (2 * i + 1 < V && c1 < nch) ? 0u : (unsigned)m << 16;
+          n_f[i] = none0 | none1;
+          n_b[i] = none0 | none1;
+          n_bl[i] = (unsigned)min(limit[c0], 0x1fff) | (unsigned)min(limit[c1], 0x1fff) << 16;
+          n_bl[i] += n_b[i];
+          n_w[i] = has_w ? none0 | none1 : (unsigned)m * 0x00010001u;
         }
+        w_wait = 0;
         // a parameter set with a value outside its domain generates nothing (status 4)
         bool bad = (has_row && !has_src) || cttp < 0 || cttp > 2 || unit_f < 1 || unit_b < 1 || f_dir < 0 || f_dir > 1 || f_int < 0 ||
                    b_dir < 0 || b_dir > 1 || b_int < 0 || (cttp != 2 && (unit_f != 1 || unit_b != 1));
 #pragma unroll
         for (int c = 0; c < V; ++c) bad = bad || limit[c] < 1;
         const bool set_bad = any_in_segment(__ballot(bad && has_row));
-        turn_type = kGenF; turn_run = 0;
-        first = cttp == 0 ? kGenB : kGenF;
-        pos_f = f_dir == 0 ? 0 : (nch > 0 ? nch - 1 : 0);
-        pos_b = b_dir == 0 ? 0 : (nch > 0 ? nch - 1 : 0);
-        stepped_f = 0; stepped_b = 0;
-        left = (has_row && !set_bad) ? nch * m * (has_w ? 3 : 2) : 0;
-        live = any_in_segment(__ballot(left > 0));
-        first_step = step; steps = 0; last_pick = -1;
-        status = set_bad ? 4 : 0; len = 0;
+        f_first = mask_of(cttp != 0);
+        run = cttp == 2 ? unit_f : 0x7fffffff;
+        const unsigned last_chunk = nch > 0 ? (unsigned)(nch - 1) << kPositionBit : 0u;
+        moves_f = mask_of(f_int > 0); moves_b = mask_of(b_int > 0);
+        up_f = mask_of(f_dir == 0); up_b = mask_of(b_dir == 0);
+        again_f = f_int > 0 ? (min((unsigned)f_int, kFarInterval) - 1u) << 16 : kOneItem;
+        again_b = b_int > 0 ? (min((unsigned)b_int, kFarInterval) - 1u) << 16 : kOneItem;
+        walk_f = again_f + kOneItem + (up_f ? 0u : last_chunk);
+        walk_b = again_b + kOneItem + (up_b ? 0u : last_chunk);
+        const bool any_item = has_row && !set_bad && nch > 0 && m > 0;
+        if (!any_item)   // (nothing is ever eligible)
+          for (int i = 0; i < NP; ++i) { n_f[i] = n_b[i] = n_w[i] = (unsigned)m * 0x00010001u; }
+        live = any_in_segment(__ballot(any_item));
+        first_step = step_0; steps = 0; last_pick = step_0 - 1u;
+        if (TIMED) {
+          item_a = lds_read<int4>(no_row);
+          if (kSecondHalves) item_b = lds_read<int4>(no_row + n_rows * 16);
+          item_slot = slot;
+          item = false;
+        }
+        status = set_bad ? 4 : 0; len = 0; stored = 0;
         free_at = 0; mem = 0; peak = 0;
-        q_h = 0u; h_n = 0u; q_t = 0u; t_n = 0u; s_rd = 0u; s_wr = 0u; q_head_dur = 0xffffffffu; w_placed = 0;
+        ring_in = 0u; ring_out = 0u; has_event = 0u; event = 0u; gap = 0u; q_in = 0u; q_out = 0u; q_tail = 0u; w_placed = 0;
         if (!TIMED) row = ops + (size_t)(has_row ? set * D + d : 0) * (size_t)stride;
         fresh = has_set && !live;   // nothing to schedule (a bad set, no stages): written out next time round
       }
       if (__ballot(has_set) == 0ull) break;   // every segment of the wavefront is out of work
-    }
-    // ---- read phase: the counters of this actor's own (type, stage) and of the neighbouring stages;
-    // then for which stages the next item of each type is eligible (dependencies resolved, and for
-    // forward items the in-flight rule).  A chunk the actor does not have is never eligible.
-    int pick_t, pick_c, p1;
-    bool is_f, is_b, move;
-    int interval, stepped0;
-    if constexpr (V == 2) {
-      // Two stages per actor: their counters side by side in 16-bit halves (no counter exceeds m <= 2048),
-      // every comparison a packed subtraction whose sign bits (bit 15: first stage, bit 31: second) say
-      // "eligible".  A missing stage reads words that hold m and is never eligible.
-      auto both = [&](int at0, int at1) {
-        pair16 v;
-        v.x = *reinterpret_cast<const short*>(&counts[at0]);
-        v.y = *reinterpret_cast<const short*>(&counts[at1]);
-        return v;
-      };
-      const pair16 nf = both(own_at[0], own_at[1]), nb = both(own_at[0] + S, own_at[1] + S);
-      const pair16 nw = both(w_at[0], w_at[1]);
-      pair16 f_ahead = both(pred_at[0][0], pred_at[1][0]), b_ahead = both(succ_at[0][0], succ_at[1][0]);
-      if (DEG > 1) {
-        f_ahead = __builtin_elementwise_min(f_ahead, both(pred_at[0][DEG > 1 ? 1 : 0], pred_at[1][DEG > 1 ? 1 : 0]));
-        b_ahead = __builtin_elementwise_min(b_ahead, both(succ_at[0][DEG > 1 ? 1 : 0], succ_at[1][DEG > 1 ? 1 : 0]));
+      if (n_classes != 0) {
+        const int longest = __ballot(has_set && set_class == 0) ? 3 : (__ballot(has_set && set_class == 1) ? 2 : (__ballot(has_set && set_class == 2) ? 1 : 0));
+        if (longest == 3) __builtin_amdgcn_s_setprio(3);
+        else if (longest == 2) __builtin_amdgcn_s_setprio(2);
+        else if (longest == 1) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
       }
-      const unsigned alive = live ? kBothSigns : 0u;
-      const unsigned el_f = bits_of(nf - f_ahead) & bits_of(nf - nb - limit2) & alive;
-      const unsigned el_b = bits_of(nb - __builtin_elementwise_min(nf, b_ahead)) & alive;
-      const unsigned el_w = bits_of(nw - nb) & alive;
-      // the step function: the first instruction type, in priority order, with an eligible item ...
-      const bool f_first = first == kGenF;
-      const unsigned el_first = f_first ? el_f : el_b, el_second = f_first ? el_b : el_f;
-      int type = el_w ? (int)kGenW : -1;
-      type = el_second ? (first ^ 1) : type;
-      type = el_first ? first : type;
-      pick_t = type;
-      unsigned el = el_second ? el_second : el_w;
-      el = el_first ? el_first : el;
-      is_f = pick_t == kGenF; is_b = pick_t == kGenB;
-      const int dir = is_f ? f_dir : (is_b ? b_dir : 0);
-      interval = is_f ? f_int : (is_b ? b_int : 0);
-      const int p0 = is_f ? pos_f : pos_b;
-      stepped0 = is_f ? stepped_f : stepped_b;
-      // ... then the stage: "the next stage with an eligible item" is the other one if it has one, and the
-      // first eligible stage in either direction is the only one, or the first / the last of both
-      const unsigned p0_bit = 15u | ((unsigned)p0 << 4);
-      move = stepped0 == interval || !((el >> p0_bit) & 1u);
-      p1 = (move && ((el >> (p0_bit ^ 16u)) & 1u)) ? (p0 ^ 1) : p0;
-      const int without_interval = el == kBothSigns ? dir : (int)(el >> 31);
-      pick_c = interval > 0 ? p1 : without_interval;
-    } else {
-    unsigned ok_f = 0u, ok_b = 0u, ok_w = 0u;
+    }
+    bool picked = false;
+    // (two steps per iteration: the new item's row and the old one's change registers)
+#pragma unroll 2
+    for (int turn = 0; turn < kStepsPerLook; ++turn) {
+      const unsigned step = step_0 + (unsigned)turn;
+      // ---- read phase: the neighbouring stages' counters, then for which stages the next item of each type is eligible
+      // (dependencies resolved, and for forward items the in-flight rule): every comparison a packed subtraction whose
+      // sign bits (bit 15: first stage, bit 31: second) say "eligible".  A missing stage never is.
+      pair16 f_ahead[NP], b_ahead[NP];
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-      const int nf = counts[own_at[c]], nb = counts[own_at[c] + S], nw = counts[own_at[c] + 2 * S];
-      int f_ahead = m, b_ahead = nf;
-      if (DEG > 0) {
-        // (no counter exceeds m, and a missing neighbour reads a word that holds m)
-        f_ahead = counts[pred_at[c][0]];
-        b_ahead = min(b_ahead, counts[succ_at[c][0]]);
+      for (int i = 0; i < NP; ++i) {
+        constexpr int kLast = V - 1;
+        const int c0 = 2 * i, c1 = min(2 * i + 1, kLast);
+        if (DEG > 0) {
+          auto both = [&](int at0, int at1) {
+            pair16 v;
+            v.x = *reinterpret_cast<const short*>(&counts[at0]);
+            v.y = *reinterpret_cast<const short*>(&counts[at1]);
+            return v;
+          };
+          f_ahead[i] = both(pred_at[c0][0], pred_at[c1][0]);
+          b_ahead[i] = both(succ_at[c0][0], succ_at[c1][0]);
 #pragma unroll
-        for (int k = 1; k < (DEG > 0 ? DEG : 1); ++k) {
-          f_ahead = min(f_ahead, counts[pred_at[c][k]]);
-          b_ahead = min(b_ahead, counts[succ_at[c][k]]);
+          for (int k = 1; k < DEG; ++k) {
+            f_ahead[i] = __builtin_elementwise_min(f_ahead[i], both(pred_at[c0][k], pred_at[c1][k]));
+            b_ahead[i] = __builtin_elementwise_min(b_ahead[i], both(succ_at[c0][k], succ_at[c1][k]));
+          }
+        } else {
+          int fa[2], ba[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int c = h == 0 ? c0 : c1;
+            fa[h] = m; ba[h] = m;
+            if (c >= nch) continue;
+            const int32_t* pred_off = lds + T.off_pred_off;
+            const int32_t* succ_off = lds + T.off_succ_off;
+            const int s = stage[c];
+            for (int e = pred_off[s]; e < pred_off[s + 1]; ++e) fa[h] = min(fa[h], counts[base + lds[T.off_pred_stage + e]]);
+            for (int e = succ_off[s]; e < succ_off[s + 1]; ++e) ba[h] = min(ba[h], counts[base + S + lds[T.off_succ_stage + e]]);
+          }
+          f_ahead[i].x = (short)fa[0]; f_ahead[i].y = (short)fa[1];
+          b_ahead[i].x = (short)ba[0]; b_ahead[i].y = (short)ba[1];
         }
-      } else if (c < nch) {
-        const int32_t* pred_off = lds + T.off_pred_off;
-        const int32_t* succ_off = lds + T.off_succ_off;
-        const int s = stage[c];
-        for (int e = pred_off[s]; e < pred_off[s + 1]; ++e) f_ahead = min(f_ahead, counts[base + lds[T.off_pred_stage + e]]);
-        for (int e = succ_off[s]; e < succ_off[s + 1]; ++e) b_ahead = min(b_ahead, counts[base + S + lds[T.off_succ_stage + e]]);
       }
-      ok_f |= (unsigned)(f_ahead > nf && nf - nb < limit[c]) << c;
-      ok_b |= (unsigned)(b_ahead > nb) << c;
-      ok_w |= (unsigned)(has_w && nb > nw) << c;
-    }
-    if (!live) { ok_f = 0u; ok_b = 0u; ok_w = 0u; }
-    // ---- the step function, without branches: the first instruction type, in priority order, with an
-    // eligible item; then the stage, in traversal order
-    const unsigned ok_first = first == kGenF ? ok_f : ok_b, ok_second = first == kGenF ? ok_b : ok_f;
-    pick_t = ok_first ? first : (ok_second ? (first ^ 1) : (ok_w ? kGenW : -1));
-    const unsigned ok = ok_first ? ok_first : (ok_second ? ok_second : ok_w);
-    is_f = pick_t == kGenF; is_b = pick_t == kGenB;
-    const int dir = is_f ? f_dir : (is_b ? b_dir : 0);
-    interval = is_f ? f_int : (is_b ? b_int : 0);
-    const int p0 = is_f ? pos_f : pos_b;
-    stepped0 = is_f ? stepped_f : stepped_b;
-    move = stepped0 == interval || !((ok >> p0) & 1u);
-    if (V <= 2) {
-      // at most two stages: "the next stage with an eligible item" is the other one if it has one, and the
-      // first eligible stage in either direction is the only one, or the first / the last of both
-      const unsigned other = (unsigned)p0 ^ 1u;
-      p1 = (move && ((ok >> other) & 1u)) ? (int)other : p0;
-      const int without_interval = ok == 3u ? dir : (int)(ok >> 1);
-      pick_c = interval > 0 ? p1 : without_interval;
-    } else {
-      // the next stage after p0, in the traversal direction and cyclically, that has an eligible item:
-      // lay the mask out twice, shift it so that the stage after p0 is at bit 0, take the lowest bit
-      // (depth-first: the same on the mirrored mask)
-      const unsigned mirrored = __brev(ok) >> (32 - nch);   // (nch = 0: ok is 0 and nothing is picked)
-      const unsigned walk = dir == 0 ? ok : mirrored;
-      const int q0 = dir == 0 ? p0 : nch - 1 - p0;
-      const unsigned twice = walk | (walk << nch);
-      int q1 = q0 + 1 + low_bit(twice >> (q0 + 1));
-      q1 = q1 >= nch ? q1 - nch : q1;
-      const int moved_to = dir == 0 ? q1 : nch - 1 - q1;
-      p1 = move ? moved_to : p0;
-      const int first_c = low_bit(ok), last_c = high_bit(ok);
-      pick_c = interval > 0 ? p1 : (dir == 0 ? first_c : last_c);
-    }
-    }
-    const int stepped1 = (move ? 0 : stepped0) + 1;
-    if (interval > 0 && is_f) { pos_f = p1; stepped_f = stepped1; }
-    if (interval > 0 && is_b) { pos_b = p1; stepped_b = stepped1; }
-    if (pick_t >= 0) {
-      // ---- write phase: the choice becomes visible for the next step; the counter's old value is
-      // the micro-batch of the item
-      int at = own_at[0];
+      // (TIMED: the inputs of the last step's item, all timed by now)
+      int ready = 0, ready2 = 0;
+      if (TIMED) {
+        ready = lds_read<int>(item_slot + (item_a.y & 0xffff));
+        if (DEG > 1) ready2 = lds_read<int>(item_slot + (item_b.z & 0xffff));
+      }
+      unsigned el_f[NP], el_b[NP], el_w[NP];
 #pragma unroll
-      for (int c = 1; c < V; ++c) at = pick_c == c ? own_at[c] : at;
-      const int j = atomicAdd(&counts[mad24((unsigned)pick_t, (unsigned)S, (unsigned)at)], 1);
-      left -= 1;
-      last_pick = (int)(step - first_step);
-      if (TIMED && (!SLIDE || pick_t != kGenW)) {
-        // the item's row: cost, memory, where its inputs' finish times are and where its own goes
-        const int4* r = reinterpret_cast<const int4*>(
-            reinterpret_cast<const char*>(lds) + __umul24((unsigned)(pick_t * V + pick_c), (unsigned)D * 32u) + d * 32);
-        const int4 a = r[0], b = r[1];
-        // (slot offsets in the rows are byte offsets)
-        char* my_slot = reinterpret_cast<char*>(slot) + j * 4;
-        int ready = *reinterpret_cast<const int32_t*>(my_slot + a.w) + b.x;
-        if (DEG > 1) ready = max(ready, *reinterpret_cast<const int32_t*>(my_slot + b.y) + b.z);
+      for (int i = 0; i < NP; ++i) {
+        const pair16 nf = pair_of(n_f[i]), nb = pair_of(n_b[i]);
+        el_f[i] = bits_of(nf - f_ahead[i]) & bits_of(nf - pair_of(n_bl[i])) & kBothSigns;
+        el_b[i] = bits_of(nb - __builtin_elementwise_min(nf, b_ahead[i])) & kBothSigns;
+        el_w[i] = SLIDE ? 0u : bits_of(pair_of(n_w[i]) - nb) & kBothSigns;
+      }
+      // ---- the step function, without branches: the first instruction type, in priority order, with an eligible item
+      unsigned any_f = el_f[0], any_b = el_b[0], any_w = el_w[0];
+      if (V > 2) { any_f |= el_f[NP - 1]; any_b |= el_b[NP - 1]; any_w |= el_w[NP - 1]; }
+      const unsigned any_first = choose(f_first, any_f, any_b), any_other = choose(f_first, any_b, any_f);
+      const unsigned hit = mask_of(any_first != 0u);
+      const unsigned any_fb = any_first != 0u ? any_first : any_other;
+      const unsigned is_f = ~(f_first ^ hit);   // (unless there is no F or B item: then B, or W)
+      const bool is_w = !SLIDE && any_fb == 0u;
+      picked = (SLIDE ? any_fb : any_fb | any_w) != 0u;
+      auto by_type = [&](unsigned f, unsigned b, unsigned w) {
+        const unsigned fb = choose(is_f, f, b);
+        return !SLIDE && is_w ? w : fb;
+      };
+      // ... then the stage
+      unsigned pick = 0u;   // chunk << kPositionBit
+      unsigned walked = 0u;
+      if constexpr (V > 1) {
+        const unsigned walk = by_type(walk_f, walk_b, kOneItem);
+        bool move;
+        if constexpr (V == 2) {
+          // the eligible ones with the position's half in front: it is taken unless it is not eligible or has had its
+          // items and the other one is eligible
+          const unsigned el = !SLIDE && is_w ? el_w[0] : any_fb;
+          const unsigned turned = __builtin_amdgcn_alignbit(el, el, walk);
+          move = (turned == 0x80000000u) | (walk < kOneItem);
+          pick = (walk & 16u) ^ ((move & ((int)turned < 0)) ? 16u : 0u);
+        } else {
+          const unsigned el0 = by_type(el_f[0], el_b[0], el_w[0]), el1 = by_type(el_f[NP - 1], el_b[NP - 1], el_w[NP - 1]);
+          const unsigned ok = (el0 >> 15 & 1u) | (el0 >> 30 & 2u) | (el1 >> 13 & 4u) | (el1 >> 28 & 8u);
+          // the next stage after p0, in the traversal direction and cyclically, that has an eligible item:
+          // lay the mask out twice, shift it so that the stage after p0 is at bit 0, take the lowest bit
+          // (depth-first: the same on the mirrored mask)
+          const bool up = by_type(up_f, up_b, ~0u) != 0u;
+          const int p0 = (int)((walk & kPosition) >> kPositionBit);
+          move = walk < kOneItem || !((ok >> p0) & 1u);
+          const unsigned mirrored = __brev(ok) >> (32 - nch);   // (nch = 0: ok is 0 and nothing is picked)
+          const unsigned line = up ? ok : mirrored;
+          const int q0 = up ? p0 : nch - 1 - p0;
+          const unsigned twice = line | (line << nch);
+          int q1 = q0 + 1 + low_bit(twice >> (q0 + 1));
+          q1 = q1 >= nch ? q1 - nch : q1;
+          const int moved_to = up ? q1 : nch - 1 - q1;
+          pick = (unsigned)(move ? moved_to : p0) << kPositionBit;
+        }
+        asm("" : "+v"(pick));   // (not taken apart again)
+        walked = ((move ? choose(is_f, again_f, again_b) : walk - kOneItem) & ~kPosition) | pick;
+      }
+      // the interleaved priority's turn
+      run += (int)hit;
+      const bool over = run == 0;
+      run = over ? (int)choose(f_first, (unsigned)unit_b, (unsigned)unit_f) : run;
+      f_first ^= mask_of(over);
+      unsigned next_row = no_row, next_slot = slot;
+      if (picked) {
+        // ---- write phase: the choice becomes visible for the next step; the counter's old value is
+        // the micro-batch of the item
+        const unsigned is_b = SLIDE ? ~is_f : ~is_f & mask_of(!is_w), is_f_too = SLIDE ? is_f : is_f & mask_of(!is_w);
+        if constexpr (V > 1) {
+          walk_f = choose(is_f_too & moves_f, walked, walk_f);
+          walk_b = choose(is_b & moves_b, walked, walk_b);
+        }
+        const unsigned half = V > 1 ? pick & 16u : 0u, one = V > 1 ? 1u << half : 1u;
+        unsigned old;
+        unsigned own = own_at[0];
+        if constexpr (V <= 2) {
+          old = by_type(n_f[0], n_b[0], n_w[0]);
+          n_f[0] += one & is_f_too;
+          n_b[0] += one & is_b;
+          n_bl[0] += one & is_b;
+          if (!SLIDE) n_w[0] += is_w ? one : 0u;
+          if (V == 2) own = pick != 0u ? own_at[V - 1] : own;
+        } else {
+          const unsigned hi = mask_of((pick & 32u) != 0u);
+          old = choose(hi, by_type(n_f[NP - 1], n_b[NP - 1], n_w[NP - 1]), by_type(n_f[0], n_b[0], n_w[0]));
+          const unsigned one0 = one & ~hi, one1 = one & hi;
+          n_f[0] += one0 & is_f_too; n_f[NP - 1] += one1 & is_f_too;
+          n_b[0] += one0 & is_b; n_b[NP - 1] += one1 & is_b;
+          n_bl[0] += one0 & is_b; n_bl[NP - 1] += one1 & is_b;
+          if (!SLIDE) { n_w[0] += is_w ? one0 : 0u; n_w[NP - 1] += is_w ? one1 : 0u; }
+#pragma unroll
+          for (int c = 1; c < V; ++c) own = pick == (unsigned)c << kPositionBit ? own_at[c] : own;
+        }
+        const unsigned j = (old >> half) & 0xffffu;
+        if (SLIDE || !is_w) lds_write<unsigned>(own + (is_b & (unsigned)S * 4u), j + 1u);
+        // (SLIDE: a step in which nothing else is eligible takes a W item while there is one)
+        if (SLIDE) w_wait = max(w_wait + (int)(last_pick + 1u - step), 0) + 1 + (int)is_f;
+        last_pick = step;
+        if constexpr (TIMED) {
+          next_row = __umul24(pick, (unsigned)D) + by_type(row_f, row_b, row_b + V * D * 16);
+          next_slot += j * 4u;
+        } else {
+          const unsigned word = (by_type(1u, 2u, 3u) << 13) | (pick >> kPositionBit << 11) | j;
+          reinterpret_cast<uint16_t*>(staging + ((len >> 1) & (kStagingWords - 1)) * 64)[len & 1] = (uint16_t)word;
+          len += 1;
+        }
+      }
+      if constexpr (TIMED) {
+        // the new item's row is on its way while the last step's is timed: cost, where its inputs' finish times
+        // are and where its own goes (byte offsets), memory
+        const int4 a = item_a, b = item_b;
+        item_a = lds_read<int4>(next_row);
+        if (kSecondHalves) item_b = lds_read<int4>(next_row + n_rows * 16);
+        ready += a.z;
+        if (DEG > 1) ready = max(ready, ready2 + b.w);
         const int start = max(free_at, ready);
-        if (SLIDE && q_head_dur <= (unsigned)(start - free_at)) {
-          // the oldest stashed W items that end before this item starts run in front of it
-          do {
-            free_at += (int)q_head_dur;
-            w_placed += (int)q_head_dur;
-            mem -= q_head_free;
-            q_h >>= kQBits;
-            --h_n;
-            if (h_n == 0u) {
-              // the head word is used up: the oldest full word of the ring, else what the tail word holds
-              if (s_rd != s_wr) {
-                q_h = spill[(s_rd & (unsigned)(spill_words - 1)) * 64];
-                ++s_rd;
-                h_n = kQCap;
-              } else {
-                q_h = q_t; h_n = t_n;
-                q_t = 0u; t_n = 0u;
-              }
-            }
-            new_head();
-          } while (q_head_dur <= (unsigned)(start - free_at));
+        if (SLIDE) {
+          // (all W items of an actor together cost less than 2^29)
+          const unsigned wait = min((unsigned)(start - free_at), 0x1fffffffu);
+          lds_write<unsigned>(ring + ring_in, wait << 3 | (unsigned)a.w);
+          ring_in = item ? (ring_in + 256u) & (kEvents * 256u - 1u) : ring_in;
+          item = picked;
         }
         free_at = start + a.x;
-        *reinterpret_cast<int32_t*>(my_slot + (DEG > 1 ? (b.w & 0xffff) : b.w)) = free_at;
-        if (DEG > 1) *reinterpret_cast<int32_t*>(my_slot + ((unsigned)b.w >> 16)) = free_at;
-        mem += a.y;
-        peak = max(peak, mem);
-        if (!SLIDE) mem -= a.z;   // (SLIDE: with split backward only W items free, and they do when they are placed)
-        if (SLIDE && pick_t == kGenB) {
-          // a B item stashes its W item: into the head word while nothing waits behind it, else into the tail
-          // word, which moves to the ring when it is full
-          if (s_rd == s_wr && t_n == 0u && h_n < kQCap) {
-            q_h |= (unsigned)pick_c << (h_n * kQBits);
-            ++h_n;
-            new_head();
-          } else {
-            q_t |= (unsigned)pick_c << (t_n * kQBits);
-            ++t_n;
-            if (t_n == kQCap) {
-              spill[(s_wr & (unsigned)(spill_words - 1)) * 64] = q_t;
-              ++s_wr;
-              q_t = 0u; t_n = 0u;
-            }
-          }
+        lds_write<int>(item_slot + ((unsigned)a.y >> 16), free_at);
+        if (DEG > 1) lds_write<int>(item_slot + ((unsigned)b.z >> 16), free_at);
+        if (!SLIDE) {
+          mem += b.x;
+          peak = max(peak, mem);
+          mem -= b.y;
         }
-      } else if (TIMED) {
-        // (SLIDE: a W item the scheduler placed is passed over)
-      } else {
-        const unsigned word = ((unsigned)(pick_t + 1) << 13) | ((unsigned)pick_c << 11) | (unsigned)j;
-        // sixteen op words are collected in the lane's staging dwords and stored together
-        reinterpret_cast<uint16_t*>(staging + ((len >> 1) & 7) * 64)[len & 1] = (uint16_t)word;
-        if ((len & 15) == 15) {
-          uint4* dst = reinterpret_cast<uint4*>(row + (len - 15));
-          dst[0] = make_uint4(staging[0], staging[64], staging[128], staging[192]);
-          dst[1] = make_uint4(staging[256], staging[320], staging[384], staging[448]);
-        }
-        len += 1;
+        item_slot = next_slot;
       }
-      if (cttp == 2 && pick_t == turn_type) {
-        if (++turn_run >= (is_f ? unit_f : unit_b)) { turn_type = is_f ? kGenB : kGenF; turn_run = 0; first = turn_type; }
-      }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
-    // ---- has the set's process ended?  Looked at every eighth step only: a process that has ended stays ended
-    // (when every item is scheduled nothing is eligible any more; when a step schedules nothing although items
-    // remain, no later step can), so the few steps a segment runs on change nothing, and the number of steps the
-    // process took is one more than the step of its last item.
-    if ((step & kEndCheckMask) == kEndCheckMask) {
-      const bool any_pick = any_in_segment(__ballot(pick_t >= 0));
-      const bool any_left = any_in_segment(__ballot(left > 0));
-      if (live && (!any_pick || !any_left)) {
-        int last = last_pick;
-        for (int off = 1; off < lpc; off <<= 1) last = max(last, __shfl_xor(last, off, 64));
-        status = any_left ? 1 : status;   // items remain and nothing can move
-        steps = last + 1;
-        live = false;
-        fresh = true;
-      }
+    // ---- has the set's process ended?  Looked at every kStepsPerLook steps only: it has if a step schedules nothing (no
+    // later step can then; SLIDE: W items, on which nothing depends, aside), and stays ended, so the few steps a segment
+    // runs on change nothing, and the number of steps the process took is one more than the step of its last item.
+    const bool any_pick = any_in_segment(__ballot(picked));
+    if (!TIMED && len - stored >= 16) {
+      const uint32_t* w = staging + ((stored >> 1) & (kStagingWords - 1)) * 64;
+      uint4* dst = reinterpret_cast<uint4*>(row + stored);
+      dst[0] = make_uint4(w[0], w[64], w[128], w[192]);
+      dst[1] = make_uint4(w[256], w[320], w[384], w[448]);
+      stored += 16;
+    }
+    if (SLIDE) {
+      // (a look adds at most kStepsPerLook items, and one place of the ring stays empty)
+      const bool ended = live && !any_pick;
+      while (__ballot(((ring_in - ring_out) & (kEvents * 256u - 1u)) > (kEvents - 1 - kStepsPerLook) * 256u ||
+                      (ended && (has_event != 0u || ring_in != ring_out))) != 0ull)
+#pragma unroll
+        for (int i = 0; i < kRoundsPerLook; ++i) settle();
+    }
+    if (live && !any_pick) {
+      bool done = true;   // else items remain and nothing can move
+#pragma unroll
+      for (int i = 0; i < NP; ++i) done = done && (SLIDE || !has_w ? n_b[i] : n_w[i]) == (unsigned)m * 0x00010001u;
+      status = any_in_segment(__ballot(!done)) ? 1 : status;
+      // (SLIDE: the W items that are left follow, one a step)
+      steps = segment_max((int)(last_pick - first_step) + (SLIDE ? w_wait : 0)) + 1;
+      live = false;
+      fresh = true;
     }
   }
 }
 
 #define FPSCHED_INSTANTIATE(V, G, FORM)                                                                     \
   template __global__ void generate_kernel<V, G, FORM>(DevTables, const int32_t*, const int32_t*,            \
-                                                        const long long*, long long, long long, int, uint16_t*, int32_t*, \
+                                                        const long long*, long long, long long, int, int, uint16_t*, int32_t*, \
                                                         unsigned char*, unsigned long long*, GenResults);
 FPSCHED_INSTANTIATE(1, 1, false)
 FPSCHED_INSTANTIATE(2, 1, false)

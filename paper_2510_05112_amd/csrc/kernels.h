@@ -99,14 +99,22 @@ struct GenResults {
   int32_t* peak;
   unsigned char* flags;
 };
-constexpr int kGenTimedThreads = 512;
+constexpr int kGenTimedThreads = 1024;
 // FORM: kGenPlain writes the lists; kGenTimed times them instead (above); kGenSlide times them after the
-// weight-gradient sliding pass (T.gen_spill_words dwords of LDS more per lane)
+// weight-gradient sliding pass (kGenEvents + T.gen_queue_words dwords of LDS more per lane)
 constexpr int kGenPlain = 0, kGenTimed = 1, kGenSlide = 2;
+constexpr int kGenEvents = 16;         // kGenSlide: items noted per lane
+constexpr int kGenStagingWords = 16;   // kGenPlain: dwords of op words staged per lane
 template <int V, int DEG, int FORM>
 __global__ void generate_kernel(DevTables T, const int32_t* policy, const int32_t* inflight, const long long* select,
-                                long long n_src, long long n_sets, int stride, uint16_t* ops, int32_t* out_steps,
-                                unsigned char* out_status, unsigned long long* next_set, GenResults R);
+                                long long n_src, long long n_sets, int n_classes, int stride, uint16_t* ops,
+                                int32_t* out_steps, unsigned char* out_status, unsigned long long* next_set,
+                                GenResults R);
+// classes of the sets by their expected steps, in the status bytes (kGenClassMark | class)
+constexpr int kGenClasses = 4, kGenClassMark = 0x80;
+__global__ void generate_order_kernel(DevTables T, const int32_t* inflight, const long long* select, long long n_src,
+                                      long long n_sets, int work_steps, unsigned char* out_status,
+                                      unsigned long long* next_set);
 
 __global__ void topk_kernel(const long long* in_makespan, const unsigned char* in_flags, const Key* in_keys, long long n,
                             long long n_part, int k, int wide_values, Key* out_keys, long long* final_idx,
