@@ -2097,10 +2097,18 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
   if (workspace_bytes < fpsched_wslide_workspace_bytes(p, n_cand, stride_words)) return FPSCHED_ENOMEM;
   const int lpc = p->stab.lanes_per_cand;
+  // wavefronts per workgroup: as many workgroups of a compute unit's LDS as leave it full (rows differ in length, and a
+  // workgroup's LDS is free when its last wavefront is done)
+  const int64_t place_rows_bytes = (int64_t)kNKinds * kMaxChunks * lpc * 8;
+  int place_waves = 1, place_groups = 1;
+  for (int groups = 1; groups <= 8; ++groups) {
+    const int wv = (int)std::min<int64_t>((p->max_lds / groups - place_rows_bytes) / kSlideWaveLdsBytes, kSlideThreads / 64);
+    if (wv >= 1 && wv * groups >= place_waves * place_groups) { place_waves = wv; place_groups = groups; }
+  }
   // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
   const int64_t place_waves_all = (n_cand * lpc + 63) / 64;
   const int place_threads = 64 * (int)std::clamp<int64_t>((place_waves_all + std::max(p->n_cu, 1) - 1) / std::max(p->n_cu, 1),
-                                                          1, kSlideThreads / 64);
+                                                          1, place_waves);
   const int64_t place_blocks = (n_cand * lpc + place_threads - 1) / place_threads;
   if (place_blocks > 0x7fffffffll) return FPSCHED_EINVAL;
   DeviceGuard g(p->device_id);
@@ -2136,7 +2144,7 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   // pass 2: every row places its W items on its own
   hipLaunchKernelGGL(wslide_place_kernel, dim3((unsigned)place_blocks), dim3(place_threads),
-                     (size_t)kNKinds * kMaxChunks * lpc * 16 + (place_threads / 64) * kSlideWaveLdsBytes, st, p->stab, d_ops,
+                     (size_t)place_rows_bytes + (place_threads / 64) * kSlideWaveLdsBytes, st, p->stab, d_ops,
                      (long long)n_cand, (int)stride_words,
                      starts, escapes, escape_cap, stops, timed_flags, d_ops_out, (int)stride_out_words,
                      reinterpret_cast<long long*>(out.makespan), reinterpret_cast<long long*>(out.idle), out.peak,

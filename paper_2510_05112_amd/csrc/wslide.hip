@@ -15,8 +15,8 @@
 //   2. this kernel places the W items: one lane per (candidate, device) row, no interaction
 //      between lanes until the final reduction.  A lane walks its row once.  One step per loop
 //      iteration, the same code for all lanes: the oldest stashed item if it fits in front of the
-//      item at the list cursor (or the list is over), else that item.  The new row leaves in
-//      16-byte pieces collected in registers; memory is accounted along the new order.
+//      item at the list cursor (or the list is over), else that item.  The new row is staged
+//      in LDS and leaves in 32-byte pieces; memory is accounted along the new order.
 // No global load sits on a step's critical path: op words and the low halves of their start times reach a
 // lane through a 32-position LDS window that the whole wavefront tops up every eighth step, sixteen
 // positions (32 bytes of each) at a time, the loads requested at one top-up landing at the next.  (With
@@ -24,8 +24,14 @@
 // among 64 lanes at 64 different positions some lane always needs its next piece.)  The first kernel
 // hands over sixteen bits per op: a start time is rebuilt from the device's free time in front of the op,
 // start = free + ((low - free) mod 2^16), plus 2^16 times the entry of the row's escape list for the few
-// ops that waited longer.  The stash is a ring of B words in LDS; only a stash deeper than the ring is
+// ops that waited longer.  The stash is a ring of two bits per W item in LDS (the chunk; the micro-batch is
+// counted); only a stash of more than kStash items, or one of a list whose B items are out of order, is
 // read back from the device's own row, with the latency exposed.
+//
+// What bounds it: instruction issue (150 vector and 110 scalar instructions a step) and, with 11 wavefronts per compute
+// unit, waits for LDS and loads.  32,768 candidates of 16 devices, 64 micro-batches, 2 chunks: 1.2 ms; 2.6 ms with a stash
+// ring of 16 words, which the lists of every loose in-flight limit overran, rows stored in 16-byte pieces (1.08 GB written
+// instead of 0.50) and six wavefronts to a workgroup.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -39,8 +45,9 @@ constexpr int kWin = 32;      // window: positions per lane (op words and the lo
 constexpr int kPiece = 16;    // positions per load: 32 bytes of op words, 32 bytes of start times
 constexpr int kRefillAt = 16; // a lane asks for its next piece when at most this many positions are unread
 constexpr unsigned kTopUpMask = 7u;   // the window is topped up every eighth step
-constexpr int kFifo = 16;     // stash ring: B words per lane
-static_assert((2 * kWin + kFifo) * 64 * 2 == kSlideWaveLdsBytes, "LDS of one wavefront");
+constexpr int kStash = 128;   // stash ring: entries of two bits per lane
+constexpr int kOut = 32;      // staging ring of the new row: words per lane; stored sixteen (32 bytes) at a time
+static_assert((2 * kWin + kStash / 8 + kOut) * 64 * 2 == kSlideWaveLdsBytes, "LDS of one wavefront");
 
 }  // namespace
 
@@ -55,15 +62,15 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   const int lpc = T.lanes_per_cand;
   const int lpc_shift = __ffs(lpc) - 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // LDS: [the metadata rows, one int4 per (kind * 4 + chunk, device): x = dur << 8, w = units
-  // allocated at the start (byte 0) | units freed at the end (byte 1)][per wavefront: op-word window
-  // [position][lane], start-time window [position][lane], stash ring [entry][lane], all 16-bit]
-  const int n_meta_ints = kNKinds * kMaxChunks * lpc * 4;
-  for (int i = threadIdx.x; i < n_meta_ints; i += blockDim.x) lds[i] = T.ints[i];
-  const int4* meta = reinterpret_cast<const int4*>(lds);
-  uint16_t* word_win = reinterpret_cast<uint16_t*>(lds + n_meta_ints + wave * (kSlideWaveLdsBytes / 4)) + lane;   // entry i at + i * 64
-  uint16_t* low_win = word_win + kWin * 64;
-  uint16_t* fifo = low_win + kWin * 64;
+  // LDS: [of the metadata rows, per (kind * 4 + chunk, device): dur << 8, then units
+  // allocated at the start (byte 0) | units freed at the end (byte 1)][per wavefront: window [position][lane],
+  // op word | low half of its start time << 16; stash ring [entry][lane] and staging ring [dword][lane], 16 bits a word]
+  const int n_meta_ints = kNKinds * kMaxChunks * lpc * 2;
+  for (int i = threadIdx.x; i < n_meta_ints; i += blockDim.x) lds[i] = T.ints[i * 2 + (i & 1)];
+  const int2* meta = reinterpret_cast<const int2*>(lds);
+  uint32_t* window = reinterpret_cast<uint32_t*>(lds + n_meta_ints + wave * (kSlideWaveLdsBytes / 4)) + lane;   // position i at + i * 64
+  uint32_t* ring = window + kWin * 64;                        // dword i (sixteen entries) at + i * 64
+  uint32_t* staging = ring + kStash / 16 * 64;                // dword i at + i * 64
   __syncthreads();
 
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -93,14 +100,11 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   uint4 pend_w0 = make_uint4(0u, 0u, 0u, 0u), pend_w1 = pend_w0, pend_s0 = pend_w0, pend_s1 = pend_w0;
   bool has_pend = false;
   auto land8 = [&](int q, uint4 wv, uint4 sv) {
-    word_win[(q + 0) * 64] = (uint16_t)wv.x; word_win[(q + 1) * 64] = (uint16_t)(wv.x >> 16);
-    word_win[(q + 2) * 64] = (uint16_t)wv.y; word_win[(q + 3) * 64] = (uint16_t)(wv.y >> 16);
-    word_win[(q + 4) * 64] = (uint16_t)wv.z; word_win[(q + 5) * 64] = (uint16_t)(wv.z >> 16);
-    word_win[(q + 6) * 64] = (uint16_t)wv.w; word_win[(q + 7) * 64] = (uint16_t)(wv.w >> 16);
-    low_win[(q + 0) * 64] = (uint16_t)sv.x; low_win[(q + 1) * 64] = (uint16_t)(sv.x >> 16);
-    low_win[(q + 2) * 64] = (uint16_t)sv.y; low_win[(q + 3) * 64] = (uint16_t)(sv.y >> 16);
-    low_win[(q + 4) * 64] = (uint16_t)sv.z; low_win[(q + 5) * 64] = (uint16_t)(sv.z >> 16);
-    low_win[(q + 6) * 64] = (uint16_t)sv.w; low_win[(q + 7) * 64] = (uint16_t)(sv.w >> 16);
+    auto pair = [&](int i, unsigned w, unsigned s) {
+      window[(q + i) * 64] = (w & 0xffffu) | (s << 16);
+      window[(q + i + 1) * 64] = (w >> 16) | (s & 0xffff0000u);
+    };
+    pair(0, wv.x, sv.x); pair(2, wv.y, sv.y); pair(4, wv.z, sv.z); pair(6, wv.w, sv.w);
   };
   // a piece is sixteen positions, or eight at the end of a row whose stride is not a multiple of 16
   auto request = [&](int at) {
@@ -125,10 +129,16 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   unsigned u8 = 0u;               // the device's free time in the list without W items, << 8
   int mem = 0, pk = 0;
   bool overflow = false, done = !active;
-  // stash ring: entries [q_head, q_tail) are B words whose W item is due, oldest first; `overflowed`:
-  // B words from row position refill_pos on found no room and are still to be read back from the row
-  int q_head = 0, q_tail = 0, refill_pos = 0;
-  bool overflowed = false;
+  // Stash: a B item's W item is known by its chunk as long as the B items of each chunk come in ascending order of their
+  // micro-batches (as in every list of the generator): entries [q_head, q_tail) of the ring are those chunks, two bits
+  // each, and the micro-batch is a count.  `from_row`: B words from row position refill_pos on are not in the ring (it is
+  // full, or a micro-batch is out of order); once it is empty they are read back from the row, one by one, until the list
+  // cursor has been caught up with (an out-of-order chunk stays that way).
+  unsigned q_head = 0u, q_tail = 0u, q_word_in = 0u;
+  int refill_pos = 0;
+  bool from_row = false, out_of_order = false;
+  unsigned n_b[2] = {0u, 0u}, n_w[2] = {0u, 0u};   // B items issued, W items placed: chunks 0 and 1, 2 and 3, 16 bits each
+  bool have_head = false;                          // q_word, q_dur8, q_free are those of the oldest stashed item
   unsigned q_word = 0u, q_dur8 = 0u;   // the oldest stashed item as a W word, its cost and what it frees
   int q_free = 0;
   // cost and freed units of the W item of each chunk of this device (rows kW * 4 + chunk of the metadata)
@@ -136,17 +146,24 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   int w_free[kMaxChunks];
 #pragma unroll
   for (int c = 0; c < kMaxChunks; ++c) {
-    const int4 Mw = meta[(kW * kMaxChunks + c) * lpc + d];
+    const int2 Mw = meta[(kW * kMaxChunks + c) * lpc + d];
     w_dur8[c] = (unsigned)Mw.x;
-    w_free[c] = (int)(((unsigned)Mw.w >> 8) & 0xffu);
+    w_free[c] = (int)(((unsigned)Mw.y >> 8) & 0xffu);
   }
-  // the new row leaves in 16-byte pieces: eight words shifted into four registers
-  unsigned acc0 = 0u, acc1 = 0u, acc2 = 0u, acc3 = 0u;
-  auto shift_in = [&](unsigned word) {
-    acc0 = __builtin_amdgcn_alignbit(acc1, acc0, 16);
-    acc1 = __builtin_amdgcn_alignbit(acc2, acc1, 16);
-    acc2 = __builtin_amdgcn_alignbit(acc3, acc2, 16);
-    acc3 = __builtin_amdgcn_alignbit(word, acc3, 16);
+  auto set_head = [&](unsigned c, unsigned j) {
+    q_word = ((unsigned)kW << 13) | c << 11 | j;
+    q_dur8 = c == 0u ? w_dur8[0] : (c == 1u ? w_dur8[1] : (c == 2u ? w_dur8[2] : w_dur8[3]));
+    q_free = c == 0u ? w_free[0] : (c == 1u ? w_free[1] : (c == 2u ? w_free[2] : w_free[3]));
+    have_head = true;
+  };
+  // The new row is staged in LDS and stored sixteen words at a time when the window is topped up, behind the loads: lanes
+  // fill up at different steps, so stores in the steps are issued in nearly every one, in pieces that the memory has to
+  // merge, and a wait for the window's loads waits for them too.
+  int stored = 0;
+  auto put = [&](int at, unsigned word) { reinterpret_cast<uint16_t*>(staging + ((at >> 1) & (kOut / 2 - 1)) * 64)[at & 1] = (uint16_t)word; };
+  auto staged4 = [&](int at) {   // eight words from a multiple of eight on
+    const uint32_t* w = staging + ((at >> 1) & (kOut / 2 - 1)) * 64;
+    return make_uint4(w[0], w[64], w[128], w[192]);
   };
 
   // One step per iteration and lane, the same straight-line code for all: look at the word at the list
@@ -163,20 +180,26 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
         request(loaded);
         has_pend = true;
       }
+      if (out_len - stored >= 16) {
+        *reinterpret_cast<uint4*>(out_row + stored) = staged4(stored);
+        *reinterpret_cast<uint4*>(out_row + stored + 8) = staged4(stored + 8);
+        stored += 16;
+      }
     }
     const unsigned slot0 = (unsigned)(pos & (kWin - 1)) * 64u, slot1 = (unsigned)((pos + 1) & (kWin - 1)) * 64u;
-    const unsigned w0 = word_win[slot0], w1 = word_win[slot1];
-    const unsigned l0 = low_win[slot0], l1 = low_win[slot1];
+    const unsigned e0 = window[slot0], e1 = window[slot1];
+    const unsigned w0 = e0 & 0xffffu;
     // a W word of the input at the cursor is passed over at once when the word behind it is there as well
     // (it is never in the escape list: in the first pass it starts the moment its device is free)
     const bool hop = !done && pos + 1 < min(stop, loaded) && (w0 >> 13) == (unsigned)kW;
     pos += hop ? 1 : 0;
-    const unsigned w = hop ? w1 : w0;
-    const unsigned low8 = (hop ? l1 : l0) << 8;
+    const unsigned e = hop ? e1 : e0;
+    const unsigned w = e & 0xffffu;
+    const unsigned low8 = e >> 16 << 8;
     const bool have = pos < stop;
     const bool in_window = pos < loaded;
     // (any 16-bit value indexes a row of the table: the top five bits of the word)
-    const int4 M = meta[((w >> 11) << lpc_shift) + d];
+    const int2 M = meta[((w >> 11) << lpc_shift) + d];
     // the start time from its low half and the free time in front of the op, plus what the escape
     // list says for an op that waited 2^16 time units or more
     const bool esc_here = (esc >> 8) == (unsigned)pos;
@@ -185,62 +208,63 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
     const bool word_ok = !done && have && in_window;
     const bool item = word_ok && kind != (unsigned)kW;   // where the input put its W items is not used
     const bool skip = word_ok && kind == (unsigned)kW;
-    const bool place = !done && q_head != q_tail && (have ? (item && t8 + q_dur8 <= s8) : at_end);
+    const bool place = !done && have_head && (have ? (item && t8 + q_dur8 <= s8) : at_end);
     const bool issue = item && !place;
     done = done || (!have && !place);
     if (place || issue) {
       const unsigned dur8 = place ? q_dur8 : (unsigned)M.x;
       const unsigned at8 = place ? t8 : s8;
       if (out_len < stride_out) {
-        shift_in(place ? q_word : w);
-        if ((out_len & 7) == 7) *reinterpret_cast<uint4*>(out_row + (out_len - 7)) = make_uint4(acc0, acc1, acc2, acc3);
+        put(out_len, place ? q_word : w);
         ++out_len;
       } else {
         overflow = true;   // the row keeps its first stride_out items; the candidate is reported as failed
       }
-      mem += place ? 0 : (int)((unsigned)M.w & 0xffu);
+      mem += place ? 0 : (int)((unsigned)M.y & 0xffu);
       pk = max(pk, mem);
-      mem -= place ? q_free : (int)(((unsigned)M.w >> 8) & 0xffu);
+      mem -= place ? q_free : (int)(((unsigned)M.y >> 8) & 0xffu);
       t8 = at8 + dur8;
       busy8 += dur8;
       if (issue) u8 = t8;   // an item of the list ends when it would without any W item
     }
-    bool new_head = false;
     if (place) {
-      ++q_head;
-      new_head = true;
-      if (q_head == q_tail && overflowed) {
-        // the ring ran empty while B words wait in the row: read them back, up to the list cursor
-        int at = refill_pos;
-        while (at < pos && q_tail - q_head < kFifo) {
-          const unsigned b_word = row[at];
-          if ((b_word >> 13) == (unsigned)kB) {
-            fifo[(q_tail & (kFifo - 1)) * 64] = (uint16_t)b_word;
-            ++q_tail;
-          }
-          ++at;
-        }
-        refill_pos = at;
-        overflowed = at < pos;
-      }
+      const unsigned c = (q_word >> 11) & 3u, one = 1u << ((c & 1u) * 16u);
+      n_w[0] += c < 2u ? one : 0u;
+      n_w[1] += c < 2u ? 0u : one;
+      have_head = false;
     }
-    if (issue && kind == (unsigned)kB && !overflowed) {
-      // an issued B item stashes its W item (once the ring has overflowed, later ones stay in the row)
-      if (q_tail - q_head < kFifo) {
-        fifo[(q_tail & (kFifo - 1)) * 64] = (uint16_t)w;
-        new_head = q_tail == q_head;
-        ++q_tail;
-      } else {
-        overflowed = true;
+    if (issue && kind == (unsigned)kB) {   // an issued B item stashes its W item
+      const unsigned c = (w >> 11) & 3u, half = (c & 1u) * 16u, one = 1u << half;
+      const unsigned count = ((c < 2u ? n_b[0] : n_b[1]) >> half) & 0xffffu;
+      n_b[0] += c < 2u ? one : 0u;
+      n_b[1] += c < 2u ? 0u : one;
+      out_of_order = out_of_order || count != (w & 0x7ffu);
+      // (full: the next entry's word still holds older entries)
+      if (!from_row && (out_of_order || q_tail - (q_head & ~15u) == (unsigned)kStash)) {
+        from_row = true;
         refill_pos = pos;
       }
+      if (!from_row) {
+        q_word_in = (q_tail & 15u) == 0u ? c : q_word_in | c << ((q_tail & 15u) * 2u);
+        ring[((q_tail >> 4) & (kStash / 16 - 1)) * 64] = q_word_in;
+        ++q_tail;
+      }
     }
-    if (new_head && q_head != q_tail) {
-      const unsigned b_word = fifo[(q_head & (kFifo - 1)) * 64];
-      const unsigned c = (b_word >> 11) & 3u;
-      q_word = (b_word & 0x1fffu) | ((unsigned)kW << 13);
-      q_dur8 = c == 0u ? w_dur8[0] : (c == 1u ? w_dur8[1] : (c == 2u ? w_dur8[2] : w_dur8[3]));
-      q_free = c == 0u ? w_free[0] : (c == 1u ? w_free[1] : (c == 2u ? w_free[2] : w_free[3]));
+    if (!have_head && q_head != q_tail) {
+      const unsigned c = (ring[((q_head >> 4) & (kStash / 16 - 1)) * 64] >> ((q_head & 15u) * 2u)) & 3u;
+      set_head(c, ((c < 2u ? n_w[0] : n_w[1]) >> ((c & 1u) * 16u)) & 0xffffu);
+      ++q_head;
+    } else if (from_row && !have_head) {
+      // the ring is empty and B words wait in the row: the next one, up to the one just issued
+      const int end = pos + (issue ? 1 : 0);
+      while (refill_pos < end) {
+        const unsigned b_word = row[refill_pos++];
+        if ((b_word >> 13) == (unsigned)kB) {
+          set_head((b_word >> 11) & 3u, b_word & 0x7ffu);
+          break;
+        }
+      }
+      from_row = out_of_order || refill_pos < end;
     }
     if (issue || skip) {
       if (esc_here) esc = esc_row[esc_at++];
@@ -249,13 +273,11 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
     if (__ballot(!done) == 0ull) break;
   }
 
-  // ---- the rest of the new row: words still in the registers, then END words up to the stride
+  // ---- the rest of the new row: words still staged, then END words up to the stride
   if (active) {
     int at = out_len;
-    if (at & 7) {
-      for (; at & 7; ++at) shift_in(0u);
-      *reinterpret_cast<uint4*>(out_row + (at - 8)) = make_uint4(acc0, acc1, acc2, acc3);
-    }
+    for (; at & 7; ++at) put(at, 0u);
+    for (int i = stored; i < at; i += 8) *reinterpret_cast<uint4*>(out_row + i) = staged4(i);
     for (; at < stride_out; at += 8) *reinterpret_cast<uint4*>(out_row + at) = make_uint4(0u, 0u, 0u, 0u);
   }
   // ---- the evaluation of the new lists
