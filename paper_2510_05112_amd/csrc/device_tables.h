@@ -80,9 +80,6 @@ constexpr unsigned kMetaHasProd = 1u << 30;
 constexpr unsigned kMetaHasCons = 1u << 31;
 constexpr unsigned kEmptySlot = 0x000000ffu;  // finish 0, tag 0xff = no stage
 
-// dwords of one device's row of costs per micro-batch (one or two bytes each): enough for m values, and odd
-constexpr unsigned slot_mb_row_dwords(int m, int value_bytes) { return (((unsigned)m * (unsigned)value_bytes + 3u) >> 2) | 1u; }
-
 struct SlotTables {
   int32_t D, m;
   int32_t lanes_per_cand;   // power of two >= D
@@ -97,10 +94,6 @@ struct SlotTables {
   int32_t off_dev;          // in ints
   int32_t dev_ints;         // 2 + 4V
   int32_t off_expect;       // in ints
-  int32_t off_mb;           // in ints; costs per micro-batch inside the shared part (0 = none): values of
-                            // mb_value_bytes (1 or 2) bytes, [block][chunk < V][lanes_per_cand][row of
-                            // slot_mb_row_dwords(m, bytes) dwords], padded to a multiple of 512 ints
-  int32_t mb_value_bytes;
   int32_t link_words;       // link mode: dwords per lane behind its state words, one per device this device
                             // sends to, one for values that stay on the device and, last, one that takes
                             // what ops without an out-edge write (0 = plain model);
@@ -111,12 +104,11 @@ struct SlotTables {
                             // then the number of ring dwords per lane behind its state words
   int32_t off_w;            // in ints; sliding form: per device [lanes_per_cand][2 * kMaxChunks + 1]: cost << 8 of the
                             // W item of each chunk, the units it frees, then (cost << 8 of all W items of the device)
-  uint32_t mb_kind_map;     // four bits per kind: which block of the table at off_mb holds the kind's costs
-                            // (kinds with the same costs share a block)
   const int32_t* ints;      // DEVICE
 };
 
-// Tables of the two-pass list evaluation (rows.hip, timing.hip).  `ints` = [timing rows][order rows][dev]:
+// Tables of the two-pass list evaluation (rows.hip, timing.hip).  `ints` = [timing rows][link rows][cost table][order rows]
+// [dev], link rows and cost table in their forms only:
 //   timing rows [kNKinds * 4][D, the even devices first] x 4 ints, addressed by the top five bits of the op word and
 //   the device:
 //     0 (latency of the first input << 8) - tag expected on it (kEmptySlot's tag if the op starts a class, kOwnTag if
@@ -125,13 +117,19 @@ struct SlotTables {
 //     2 byte offset of its slot for micro-batch 0 | mask of the bits of (word << 2) that are added to it << 16
 //     3 if the op has a second input or output: byte offset of a second row | kRowTwoOut | sign bit: two inputs.  An op
 //       with two inputs waits for its second one first: words 0 and 2 are then the second input's.
-//   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 unused
+//   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 the
+//     second output's link row in the links form
 //   Wide form (times beyond 24 bits; a slot is two dwords, the time and the tag): word 0 is the latency, word 1 the
 //   duration, word 3 the tag the op leaves | the tag it expects << 8 | number of 16-byte rows in front of its second row
 //   << 16 | the two flags; word 3 of a second row is the tag expected on the first edge << 8.
 //   Slots of a candidate, in dwords: [0, D) the devices' own words, D + 1
 //   for the makespan, then from list_slots_at(D) on class * m for backward values, (classes + class) * m for forward
 //   values; finish << 8 | producer stage, kEmptySlot at first.
+//   link rows: byte offset of the word of the link that the first output goes over | latency << 16; an op that sends nothing
+//     to another device has the last word.
+//   cost table: per kind (kinds with the same costs share) and stage a row of mb_bytes per micro-batch, an odd number of
+//     dwords long; word 1 of a timing row then has the byte offset of that row instead of the duration, and the order
+//     rows' durations are 0.
 //   order rows [kNKinds * 4][D] x 2 ints:
 //     0 next state | required state << 8 | units allocated << 16 | units freed << 24   1 dur
 //     Rows of words that may not appear on the device require kNoState.
@@ -143,6 +141,9 @@ struct ListTables {
   int32_t cand_slots;       // slots per candidate, a multiple of 4
   int32_t wave_bytes;       // LDS of one wavefront of the timing pass: op windows, then slots
   int32_t n_time_ints;      // timing rows, padded to a multiple of 8
+  int32_t off_links;        // links form: link rows, one int per timing row in the same order, in ints
+  int32_t link_words;       // links form: words per lane and half (one behind the links for ops that send nothing)
+  int32_t mb_bytes;         // costs per micro-batch: bytes of a value, 1 or 2
   int32_t off_check;        // order rows, in ints
   int32_t n_check_ints;
   int32_t check_shared_bytes;   // order rows and dev rows in LDS, a multiple of 16

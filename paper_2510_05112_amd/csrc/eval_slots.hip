@@ -103,10 +103,9 @@ __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long 
 // (cost << 8, zero for rows the device does not have) in device memory instead of the metadata row;
 // it is requested when the word is decoded and first needed one round later.  That wait also
 // covers the op-window load in flight, so the form is about twice as slow as the plain kernel.
-// MODE kSlotPerMicrobatchLds: the same costs as values of one or two bytes in the shared part of LDS
-// (T.off_mb), read like the metadata row; the host picks it when the table fits.
+// The table of a batch usually fits LDS, and the timing pass (timing.hip) takes it; this form is left for those that do not.
 //
-// MODE kSlotLinks: the link-occupancy variant of the cost model.  Every device a lane's device sends
+// MODES kSlotTimesLinks, kSlotSlideLinks: those two under the link-occupancy variant of the cost model.  Every device a lane's device sends
 // to has a word behind the lane's state words: the time until which that link is busy.  An op with an
 // outgoing edge to another device writes into its output slot not its finish time but the time its
 // value leaves, max(finish, link busy until), and keeps the link busy for the edge's latency from then;
@@ -152,8 +151,7 @@ __global__ __launch_bounds__(kSlotMaxThreads) void eval_slot_kernel(
     uint32_t* __restrict__ out_escape, int escape_cap) {
   constexpr bool TIMES = MODE == kSlotTimes || MODE == kSlotTimesLinks;
   constexpr bool MBDUR = MODE == kSlotPerMicrobatch;
-  constexpr bool MBLDS = MODE == kSlotPerMicrobatchLds || MODE == kSlotPerMicrobatchLdsLinks;
-  constexpr bool LINKS = MODE == kSlotLinks || MODE == kSlotTimesLinks || MODE == kSlotPerMicrobatchLdsLinks || MODE == kSlotSlideLinks;
+  constexpr bool LINKS = MODE == kSlotTimesLinks || MODE == kSlotSlideLinks;
   constexpr bool COPY = MODE == kSlotCopy;
   constexpr bool SYNC = MODE == kSlotSync;
   constexpr bool SLIDE = MODE == kSlotSlide || MODE == kSlotSlideLinks;
@@ -338,16 +336,6 @@ __global__ __launch_bounds__(kSlotMaxThreads) void eval_slot_kernel(
   int dur_mb8 = 0;                   // MBDUR: cost << 8 of the current word
   const unsigned mb_lane = (unsigned)d * (unsigned)m;   // this device's part of a row of mb_rows
   const unsigned mb_row_ints = (unsigned)lpc * (unsigned)m;
-  // MBLDS: [block of the kind][chunk][device][micro-batch] costs of one or two bytes (kind 0 maps to block 0).
-  // A device's row is an odd number of dwords long, so that the lanes of a candidate, which mostly ask
-  // for the same micro-batch, fall into different banks.
-  unsigned dur_mb16 = 0;
-  const bool mb_wide = T.mb_value_bytes == 2;   // else one byte per value
-  const unsigned mb_dev_bytes = slot_mb_row_dwords(m, T.mb_value_bytes) * 4u;
-  const unsigned mb_chunk_bytes = (unsigned)lpc * mb_dev_bytes, mb_kind_bytes = mb_chunk_bytes * (unsigned)V;
-  unsigned mb_lds_lane = lds0 + (unsigned)T.off_mb * 4u + (unsigned)d * mb_dev_bytes;
-  const unsigned mb_kind_map = T.mb_kind_map;
-  if (MBLDS) asm volatile("" : "+v"(mb_lds_lane));
   // LINKS: the current op's first out-edge (latency << 13 | link word offset), the address of its link
   // word and that word's value; the second out-edge is looked at when the op issues
   const unsigned link_base = stt_off + (unsigned)T.state_words * 256u;
@@ -380,12 +368,6 @@ __global__ __launch_bounds__(kSlotMaxThreads) void eval_slot_kernel(
     unsigned chunk_at = __umul24(c, chunk_bytes) + stt_off;
     asm("" : "+v"(chunk_at));
     at_state = (jw << 8) + chunk_at;
-    if (MBLDS) {
-      const unsigned block = __builtin_amdgcn_ubfe(mb_kind_map, c5 & 0x1cu, 3);   // nibble `kind` of the map
-      const unsigned at_row = __umul24(block, mb_kind_bytes) + mb_lds_lane + __umul24(c, mb_chunk_bytes);
-      if (mb_wide) dur_mb16 = lds_read<uint16_t>(at_row + (jc << 1));
-      else dur_mb16 = lds_read<uint8_t>(at_row + jc);
-    }
     if (W_NOOP) at_state = (word >> 13) == (unsigned)kW ? lds0 + zero_off : at_state;
     if (SLIDE) cur_push = c;
     unsigned j_first = jc;
@@ -590,7 +572,7 @@ __global__ __launch_bounds__(kSlotMaxThreads) void eval_slot_kernel(
     // ---- decide.  An exhausted lane sits on a word of kind 0, whose metadata row is invalid; invalid
     // rows require state 15, which no activation is ever in.  Lanes without a device (and idle
     // segments) never initialise their LDS words, so they are masked off explicitly.
-    const unsigned dur8 = MBDUR ? (unsigned)dur_mb8 : (MBLDS ? dur_mb16 << 8 : (unsigned)M.x), lat_tag = (unsigned)M.y, mx_ = (unsigned)M.z, my_ = (unsigned)M.w;
+    const unsigned dur8 = MBDUR ? (unsigned)dur_mb8 : (unsigned)M.x, lat_tag = (unsigned)M.y, mx_ = (unsigned)M.z, my_ = (unsigned)M.w;
     // Everything that can forbid the issue is OR-ed into the low byte of one word: wrong activation
     // state; input slot not tagged with the upstream stage (only if the op has an input: the top
     // byte of the last metadata dword is 0xff then, else 0).  A live lane has dead == 0, any other
@@ -866,10 +848,7 @@ __global__ __launch_bounds__(kSlotMaxThreads) void eval_slot_kernel(
 #define FPSCHED_INSTANTIATE(V, G, O)               \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotTimes)    \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotPerMicrobatch) \
-  FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotPerMicrobatchLds) \
-  FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotLinks)            \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotTimesLinks)       \
-  FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotPerMicrobatchLdsLinks) \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotCopy) \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotSync) \
   FPSCHED_INSTANTIATE_MODE(V, G, O, kSlotSlide) \

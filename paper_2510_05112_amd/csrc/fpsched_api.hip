@@ -16,6 +16,15 @@
 
 using namespace fpsched;
 
+// The list evaluation's tables and launch shape under link occupancy, costs per micro-batch, or both
+struct ListVariant {
+  bool ok = false;
+  ListTables tab{};
+  int32_t* d_image = nullptr;
+  size_t capacity = 0;             // ints
+  int32_t waves = 0, grid = 0;     // of the timing pass: wavefronts per workgroup, resident workgroups
+};
+
 struct fpsched_problem {
   int32_t D = 0, S = 0, m = 0, has_w = 0;
   int device_id = -1;
@@ -56,6 +65,8 @@ struct fpsched_problem {
   int32_t* d_list_ints = nullptr;
   int32_t check_rows_per_wave = 0, check_waves = 0, check_grid = 0, check_vbits = 0;
   int32_t time_waves = 0, time_grid = 0;   // wavefronts per workgroup, resident workgroups
+  std::vector<int32_t> list_image;         // host copy of d_list_ints
+  ListVariant lists_links, lists_mb, lists_both;
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
   int64_t max_comm = 0;
   bool mb_set = false;
@@ -65,18 +76,9 @@ struct fpsched_problem {
   // link occupancy (fpsched_problem_set_link_occupancy): a table image with longer dev rows
   int64_t max_dur = 0;
   bool links_on = false;
-  SlotTables stab_links{};
-  int32_t* d_links_image = nullptr;
-  // both variants together: the cost-table image with the link form's device rows
-  std::vector<int32_t> mb_image_host;   // host copy of the image behind stab_mb
-  std::vector<int32_t> link_rows;       // [lanes per candidate][4V] out-edge entries of the link form
-  int32_t link_words = 0;
+  SlotTables stab_links{};         // of the sliding pass's forms
+  std::vector<int32_t> mb_raw;          // host copy of the cost table that is set, [kinds][S][m]
   int64_t mb_max_dur = 0;               // largest value of the cost table that is set
-  bool combo_ok = false;
-  SlotTables stab_combo{};
-  int32_t* d_combo_image = nullptr;
-  size_t combo_image_ints = 0;
-  int32_t combo_waves = 0, combo_grid = 0, combo_lds_bytes = 0;
   std::vector<int32_t> times_ints;      // host copy of the timing pass's table image
   bool links_slide_ok = false;          // the sliding pass has a link form (its LDS fits)
   SlotTables stab_times_links{};
@@ -99,12 +101,6 @@ struct fpsched_problem {
   int32_t* d_sync_ints = nullptr;
   size_t sync_ints_capacity = 0;
   int32_t sync_lds_bytes = 0;
-  // ... or, when the values fit sixteen bits and the table fits LDS, inside a second table image
-  bool mb_in_lds = false;
-  SlotTables stab_mb{};
-  int32_t* d_mb_image = nullptr;
-  size_t mb_image_ints = 0;
-  int32_t mb_waves = 0, mb_grid = 0, mb_lds_bytes = 0;
 };
 
 namespace {
@@ -244,14 +240,30 @@ CheckKernel check_kernel_of(int vbits) {
 }
 
 using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int);
-TimeKernel time_kernel_of(bool deg2, bool wide) {
-  if (wide) return deg2 ? &time_lists_kernel<true, true> : &time_lists_kernel<false, true>;
-  return deg2 ? &time_lists_kernel<true, false> : &time_lists_kernel<false, false>;
+template <bool LINKS, bool MB>
+TimeKernel narrow_time_kernel_of(bool deg2) {
+  return deg2 ? &time_lists_kernel<true, false, LINKS, MB> : &time_lists_kernel<false, false, LINKS, MB>;
+}
+TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, bool mb = false) {
+  if (wide) return deg2 ? &time_lists_kernel<true, true, false, false> : &time_lists_kernel<false, true, false, false>;
+  if (links) return mb ? narrow_time_kernel_of<true, true>(deg2) : narrow_time_kernel_of<true, false>(deg2);
+  return mb ? narrow_time_kernel_of<false, true>(deg2) : narrow_time_kernel_of<false, false>(deg2);
 }
 
 // What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
 struct StageEdge { int32_t cls, tag, latency; };
 struct StageEdges { std::vector<StageEdge> in[2], out[2]; };
+
+// timing pass: as many candidates per wavefront as its lanes and LDS hold (waves 0: it does not fit)
+WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
+  for (int cpw = 64 / ((T->D + 1) / 2); cpw >= 1; --cpw) {
+    T->cands_per_wave = cpw;   // (rings are 32-byte aligned)
+    T->wave_bytes = (int32_t)((kTimeWindowBytes + 512ll * T->link_words + (int64_t)cpw * slot_bytes * T->cand_slots + 31) & ~31ll);
+    const WorkgroupShape shape = workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds);
+    if (shape.waves >= 1) return shape;
+  }
+  return WorkgroupShape{0, 1};
+}
 
 // Table image of the two-pass list evaluation (layout: device_tables.h) and the launch shapes of its kernels.
 // Leaves lists_ok false if the problem does not fit: more than two inputs or outputs of a stage, times, latencies,
@@ -372,16 +384,8 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
     check = workgroup_shape(T.check_shared_bytes, T.check_wave_bytes, p->max_lds, kCheckMaxThreads / 64, kCheckWavesPerSimd, true);
     if (check.waves >= 1) break;
   }
-  // timing pass: as many candidates per wavefront as its lanes and LDS hold
-  WorkgroupShape time{0, 1};
-  int cpw = 64 / ((D + 1) / 2);
-  for (; cpw >= 1; --cpw) {
-    T.wave_bytes = (int32_t)((kTimeWindowBytes + cpw * slot_bytes * cand_slots + 31) & ~31ll);   // (rings are 32-byte aligned)
-    time = workgroup_shape(4ll * T.n_time_ints, T.wave_bytes, p->max_lds);
-    if (time.waves >= 1) break;
-  }
+  const WorkgroupShape time = timing_shape(&T, slot_bytes, p->max_lds);
   if (check.waves < 1 || time.waves < 1) return;
-  T.cands_per_wave = cpw;
   p->check_rows_per_wave = rows;
   p->check_waves = check.waves;
   p->check_grid = p->n_cu * check.groups;
@@ -390,6 +394,129 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
   p->lists_deg2 = deg2;
   p->lists_wide = wide;
   p->lists_ok = true;
+}
+
+// The tables with link rows (links) and a table of costs per micro-batch (mb: [kinds][S][m]) between the timing rows and
+// the order rows.  FPSCHED_EUNSUPPORTED if they do not fit.
+int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVariant* v) {
+  v->ok = false;
+  if (!p->lists_ok || p->lists_wide) return FPSCHED_EUNSUPPORTED;
+  const ListTables& B = p->ltab;
+  const int D = p->D, S = p->S, m = p->m, n_rows = kNKinds * kMaxChunks * D;
+  const std::vector<int32_t>& I = p->host_ints;
+  const DevTables& G = p->tables;
+  ListTables T = B;
+  std::vector<int32_t> J(p->list_image.begin(), p->list_image.begin() + B.n_time_ints);
+  auto row_at = [&](int kind, int c, int d) { return (kind * kMaxChunks + c) * D + (d & 1) * ((D + 1) / 2) + d / 2; };
+  if (links) {
+    // links of a device: the devices its stages send to (activations to successor stages, gradients to predecessor
+    // stages), numbered in the order they are met; one more for what sends nothing or stays on the device
+    std::vector<std::vector<int>> sends_to(D);
+    struct Sent { int d, link; int32_t latency; };
+    auto out_edge = [&](int s, int dir, int k, Sent* e) {
+      const int off = dir == 0 ? G.off_succ_off : G.off_pred_off, at = I[off + s] + k;
+      if (at >= I[off + s + 1]) return false;
+      const int from = p->stage_device[s], to = p->stage_device[I[(dir == 0 ? G.off_succ_stage : G.off_pred_stage) + at]];
+      if (from == to) return false;
+      std::vector<int>& known = sends_to[from];
+      size_t link = 0;
+      while (link < known.size() && known[link] != to) ++link;
+      if (link == known.size()) known.push_back(to);
+      *e = Sent{from, (int)link, I[(dir == 0 ? G.off_succ_comm : G.off_pred_comm) + at]};
+      return true;
+    };
+    Sent e;
+    for (int s = 0; s < S; ++s)
+      for (int dir = 0; dir < 2; ++dir)
+        for (int k = 0; k < 2; ++k) (void)out_edge(s, dir, k, &e);
+    size_t most = 0;
+    for (const std::vector<int>& known : sends_to) most = std::max(most, known.size());
+    T.link_words = (int32_t)most + 1;
+    if (256 * T.link_words > 0xffff) return FPSCHED_EUNSUPPORTED;
+    const int32_t nowhere = 256 * (T.link_words - 1);
+    T.off_links = (int32_t)J.size();
+    J.resize(J.size() + n_rows, nowhere);
+    for (int kind : {(int)kF, (int)kFD, (int)kB})
+      for (int d = 0; d < D; ++d)
+        for (int c = 0; c < p->n_chunks[d]; ++c) {
+          const int s = p->local_stage[(size_t)d * kMaxChunks + c], dir = kind == kB ? 1 : 0, row = row_at(kind, c, d);
+          auto packed = [&](int k) {
+            return out_edge(s, dir, k, &e) ? (int32_t)((uint32_t)e.latency << 16 | (uint32_t)(256 * e.link)) : nowhere;
+          };
+          J[T.off_links + row] = packed(0);
+          const uint32_t second = (uint32_t)J[4 * row + 3];
+          if (second & kRowTwoOut) J[(second & 0xffffu) / 4 + 3] = packed(1);
+        }
+  }
+  if (mb) {
+    // kinds whose costs are the same (a forward item whether its activation is kept or dropped, a recomputation, ...)
+    // share a block; values of two bytes, or one if all fit
+    int32_t most = 0;
+    for (size_t i = (size_t)S * m; i < (size_t)kNKinds * S * m; ++i) most = std::max(most, mb[i]);
+    if (most >= 65536) return FPSCHED_EUNSUPPORTED;
+    T.mb_bytes = most < 256 ? 1 : 2;
+    std::vector<int> blocks;
+    std::vector<unsigned char> costs;
+    // (a stage's row is an odd number of dwords long: the lanes of a candidate mostly ask for the same micro-batch)
+    const size_t row_bytes = ((((size_t)m * T.mb_bytes + 3) / 4) | 1) * 4, block_bytes = S * row_bytes, first = 4 * J.size();
+    for (int kind = 1; kind < kNKinds; ++kind) {
+      const int32_t* of_kind = mb + (size_t)kind * S * m;
+      size_t b = 0;
+      while (b < blocks.size() && !std::equal(of_kind, of_kind + (size_t)S * m, mb + (size_t)blocks[b] * S * m)) ++b;
+      if (b == blocks.size()) {
+        blocks.push_back(kind);
+        costs.resize(blocks.size() * block_bytes, 0);
+        for (int s = 0; s < S; ++s)
+          for (int j = 0; j < m; ++j)
+            for (int k = 0; k < T.mb_bytes; ++k)
+              costs[b * block_bytes + s * row_bytes + (size_t)j * T.mb_bytes + k] = (unsigned char)((uint32_t)of_kind[s * m + j] >> (8 * k));
+      }
+      for (int d = 0; d < D; ++d)
+        for (int c = 0; c < p->n_chunks[d]; ++c) {
+          const int s = p->local_stage[(size_t)d * kMaxChunks + c];
+          int32_t& word = J[4 * row_at(kind, c, d) + 1];
+          const size_t at = first + b * block_bytes + s * row_bytes;
+          if (at >= 1u << 24) return FPSCHED_EUNSUPPORTED;
+          if (J[4 * row_at(kind, c, d)] != 1) word = (int32_t)((uint32_t)at << 8 | ((uint32_t)word & 0xffu));
+        }
+    }
+    J.resize(J.size() + costs.size() / 4);
+    memcpy(reinterpret_cast<char*>(J.data()) + first, costs.data(), costs.size());
+  }
+  J.resize((J.size() + 7) & ~(size_t)7, 0);
+  T.n_time_ints = (int32_t)J.size();
+  J.insert(J.end(), p->list_image.begin() + B.off_check, p->list_image.end());
+  T.off_check = T.n_time_ints;
+  T.off_dev = T.off_check + (B.off_dev - B.off_check);
+  if (mb)   // (the busy time is the timing pass's)
+    for (int i = 0; i < T.n_check_ints / 2; ++i) J[(size_t)T.off_check + 2 * i + 1] = 0;
+  const WorkgroupShape shape = timing_shape(&T, 4, p->max_lds);
+  if (shape.waves < 1) return FPSCHED_EUNSUPPORTED;
+  // (costs from device memory, kSlotPerMicrobatch, are better than so few wavefronts)
+  if (mb && !links && shape.waves * shape.groups < 6) return FPSCHED_EUNSUPPORTED;
+  DeviceGuard g(p->device_id);
+  if (!g.ok || hipDeviceSynchronize() != hipSuccess) return FPSCHED_EHIP;   // an earlier image may be in use
+  if (J.size() > v->capacity) {
+    if (v->d_image) (void)hipFree(v->d_image);
+    v->d_image = nullptr;
+    v->capacity = 0;
+    if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
+    v->capacity = J.size();
+  }
+  if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
+      hipFuncSetAttribute(reinterpret_cast<const void*>(time_kernel_of(p->lists_deg2, false, links, mb != nullptr)),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
+    return FPSCHED_EHIP;
+  T.ints = v->d_image;
+  v->tab = T;
+  v->waves = shape.waves;
+  v->grid = p->n_cu * shape.groups;
+  v->ok = true;
+  if (getenv("FPSCHED_VERBOSE"))
+    fprintf(stderr, "[fpsched] list evaluation%s%s: %d x %d wavefronts per compute unit (plain: %d x %d), %d candidates each\n",
+            links ? ", links" : "", mb ? ", costs per micro-batch" : "", shape.groups, shape.waves,
+            p->time_grid / std::max(p->n_cu, 1), p->time_waves, T.cands_per_wave);
+  return FPSCHED_OK;
 }
 
 }  // namespace
@@ -734,10 +861,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       ST.off_meta2 = n_meta;
       ST.off_dev = n_shared;
       ST.dev_ints = dev_ints;
-      ST.off_mb = 0;
       ST.link_words = 0;
-      ST.mb_kind_map = 0;
-      ST.mb_value_bytes = 2;
       const SlotGeometry geo = slot_geometry(ST.n_shared_ints, lpc, ST.state_words, ST.slots_per_cand, max_lds);
       const int scpw = geo.cands_per_wave, best_waves = geo.waves, best_groups = geo.groups;
       const int64_t wave_ints = geo.wave_ints;
@@ -780,6 +904,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
                                  reinterpret_cast<const void*>(time_kernel_of(p->lists_deg2, p->lists_wide))})
         ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
       p->ltab.ints = p->d_list_ints;
+      p->list_image = list_image;
     }
     if (ok && p->slots_ok) {
       ok = hipMalloc(&p->d_slot_ints, p->slot_ints.size() * sizeof(int32_t)) == hipSuccess &&
@@ -881,11 +1006,10 @@ void fpsched_problem_destroy(fpsched_problem* p) {
     if (p->d_times_ints) (void)hipFree(p->d_times_ints);
     if (p->d_mb_raw) (void)hipFree(p->d_mb_raw);
     if (p->d_mb_rows) (void)hipFree(p->d_mb_rows);
-    if (p->d_mb_image) (void)hipFree(p->d_mb_image);
-    if (p->d_links_image) (void)hipFree(p->d_links_image);
+    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both})
+      if (v->d_image) (void)hipFree(v->d_image);
     if (p->d_times_links_image) (void)hipFree(p->d_times_links_image);
     if (p->d_slide_links_image) (void)hipFree(p->d_slide_links_image);
-    if (p->d_combo_image) (void)hipFree(p->d_combo_image);
     if (p->d_sync_ints) (void)hipFree(p->d_sync_ints);
   }
   delete p;
@@ -940,16 +1064,17 @@ static int draws_at_a_time(const fpsched_problem* p, int32_t stride_words, int c
 }
 
 // the two-pass list evaluation: the order pass over all rows, then the timing pass on a persistent grid
-static int run_list_evaluation(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_cand, int32_t stride_words,
+// (variant: its tables and launch shape under link occupancy or costs per micro-batch; null: the plain model)
+static int run_list_evaluation(const fpsched_problem* p, const ListVariant* variant, const uint16_t* d_ops, int64_t n_cand, int32_t stride_words,
                                const fpsched_results& out, unsigned long long* counter, hipStream_t st) {
-  const ListTables& T = p->ltab;
+  const ListTables& T = variant ? variant->tab : p->ltab;
   const int64_t n_rows = n_cand * p->D, rpw = p->check_rows_per_wave;
   // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
   const int64_t row_waves = (n_rows + rpw - 1) / rpw;
   const int cw = (int)std::clamp<int64_t>((row_waves + p->check_grid - 1) / p->check_grid, 1, p->check_waves);
   const int64_t check_blocks = std::min<int64_t>((row_waves + cw - 1) / cw, p->check_grid);
-  const int64_t cpw = T.cands_per_wave, grid = p->time_grid;
-  const int tw = (int)std::clamp<int64_t>((n_cand + cpw * grid - 1) / (cpw * grid), 1, p->time_waves);
+  const int64_t cpw = T.cands_per_wave, grid = variant ? variant->grid : p->time_grid, max_waves = variant ? variant->waves : p->time_waves;
+  const int tw = (int)std::clamp<int64_t>((n_cand + cpw * grid - 1) / (cpw * grid), 1, max_waves);
   const int64_t time_blocks = std::min<int64_t>((n_cand + cpw * tw - 1) / (cpw * tw), grid);
   long long* idle = reinterpret_cast<long long*>(out.idle);
   // segment g starts on candidate g, wavefront w of the order pass on block w of rows; the counters hand out those behind
@@ -968,7 +1093,7 @@ static int run_list_evaluation(const fpsched_problem* p, const uint16_t* d_ops, 
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(time_kernel_of(p->lists_deg2, p->lists_wide), dim3((unsigned)time_blocks),
+  hipLaunchKernelGGL(time_kernel_of(p->lists_deg2, p->lists_wide, T.link_words > 0, T.mb_bytes > 0), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
                      out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave));
@@ -1004,18 +1129,17 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-    if (!copy_on_slots && !sync_on_slots && !p->mb_set && !p->links_on)
-      return run_list_evaluation(p, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
-    // costs per micro-batch: their own table image and workgroup shape when the table sits in LDS
-    const bool mb_lds = p->mb_set && p->mb_in_lds;
-    const bool combo = p->links_on && p->mb_set;   // both variants: the setters made sure the tables exist
-    if (combo && !p->combo_ok) return FPSCHED_EUNSUPPORTED;
-    const bool links = p->links_on && !combo;
-    const SlotTables& tab = sync_on_slots ? p->stab_sync : copy_on_slots ? p->stab_copy : combo ? p->stab_combo : links ? p->stab_links : (mb_lds ? p->stab_mb : p->stab);
-    const int waves = sync_on_slots ? p->sync_slot_waves : copy_on_slots ? p->copy_waves : combo ? p->combo_waves : links ? p->links_waves : (mb_lds ? p->mb_waves : p->slot_waves);
-    const int grid = sync_on_slots ? p->sync_slot_grid : copy_on_slots ? p->copy_grid : combo ? p->combo_grid : links ? p->links_grid : (mb_lds ? p->mb_grid : p->slot_grid);
-    const size_t lds_bytes = (size_t)(sync_on_slots ? p->sync_slot_lds_bytes : copy_on_slots ? p->copy_lds_bytes : combo ? p->combo_lds_bytes : links ? p->links_lds_bytes
-                                      : (mb_lds ? p->mb_lds_bytes : p->slot_lds_bytes));
+    if (!copy_on_slots && !sync_on_slots) {
+      const ListVariant* variant = p->links_on ? (p->mb_set ? &p->lists_both : &p->lists_links) : (p->mb_set ? &p->lists_mb : nullptr);
+      if (!variant || variant->ok)
+        return run_list_evaluation(p, variant, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
+      if (p->links_on) return FPSCHED_EUNSUPPORTED;   // (the setters made sure that it is there)
+    }
+    // copy engine, synchronisation stages; costs per micro-batch whose table does not fit LDS
+    const SlotTables& tab = sync_on_slots ? p->stab_sync : copy_on_slots ? p->stab_copy : p->stab;
+    const int waves = sync_on_slots ? p->sync_slot_waves : copy_on_slots ? p->copy_waves : p->slot_waves;
+    const int grid = sync_on_slots ? p->sync_slot_grid : copy_on_slots ? p->copy_grid : p->slot_grid;
+    const size_t lds_bytes = (size_t)(sync_on_slots ? p->sync_slot_lds_bytes : copy_on_slots ? p->copy_lds_bytes : p->slot_lds_bytes);
     const SlotLaunch L = slot_launch(tab, waves, grid, lds_bytes, n_cand);
     const int per_block = tab.cands_per_wave * L.waves;
     const int64_t blocks = L.blocks;
@@ -1030,16 +1154,13 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     const bool one_class = tab.n_classes == 1;
     const SlotKernel kernel = sync_on_slots ? slot_kernel_of<kSlotSync>(p->slot_v, p->sync_deg2, one_class)
                               : copy_on_slots ? slot_kernel_of<kSlotCopy>(p->slot_v, p->slot_deg2, one_class)
-                              : combo ? slot_kernel_of<kSlotPerMicrobatchLdsLinks>(p->slot_v, p->slot_deg2, one_class)
-                              : links ? slot_kernel_of<kSlotLinks>(p->slot_v, p->slot_deg2, one_class)
-                              : (mb_lds ? slot_kernel_of<kSlotPerMicrobatchLds>(p->slot_v, p->slot_deg2, one_class)
-                                        : slot_kernel_of<kSlotPerMicrobatch>(p->slot_v, p->slot_deg2, one_class));
+                              : slot_kernel_of<kSlotPerMicrobatch>(p->slot_v, p->slot_deg2, one_class);
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * L.waves), L.lds_bytes,
                        static_cast<hipStream_t>(hip_stream), tab, d_ops,
                        (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan),
                        reinterpret_cast<long long*>(out.idle), out.peak, out.flags, counter, draw_block,
                        (uint32_t*)nullptr, (int32_t*)nullptr,
-                       (const int32_t*)(p->mb_set && !mb_lds && !combo ? p->d_mb_rows : nullptr), (uint32_t*)nullptr, 0);
+                       (const int32_t*)(p->mb_set ? p->d_mb_rows : nullptr), (uint32_t*)nullptr, 0);
     return check_hip(hipGetLastError());
   }
   const int cpw = p->tables.cands_per_wave;
@@ -1051,59 +1172,6 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
                      reinterpret_cast<long long*>(out.idle), out.peak, out.flags,
                      (const int32_t*)(p->mb_set ? p->d_mb_raw : nullptr));
   return check_hip(hipGetLastError());
-}
-
-// Costs per micro-batch and link occupancy together: the image behind stab_mb with the link form's longer
-// device rows.  Needs both built (the cost table in LDS).  FPSCHED_EUNSUPPORTED if it does not fit.
-static int build_combined_tables(fpsched_problem* p) {
-  p->combo_ok = false;
-  if (!p->mb_in_lds || p->mb_image_host.empty() || p->link_rows.empty()) return FPSCHED_EUNSUPPORTED;
-  const SlotTables& MT = p->stab_mb;
-  const int V = p->slot_v, lpc = MT.lanes_per_cand;
-  const int dev_ints = MT.dev_ints + 4 * V;
-  const int slots_per_cand = (2 * MT.n_classes * p->m + 7) & ~7;   // no dump region in the link form
-  SlotGeometry geo = slot_geometry(MT.n_shared_ints, lpc, MT.state_words + p->link_words, slots_per_cand, p->max_lds,
-                                   MT.cands_per_wave);
-  if (geo.waves * geo.groups < 4 || geo.cands_per_wave != MT.cands_per_wave) return FPSCHED_EUNSUPPORTED;
-  const std::vector<int32_t>& B = p->mb_image_host;
-  std::vector<int32_t> J((size_t)MT.n_shared_ints + (size_t)lpc * dev_ints + (size_t)lpc * MT.state_words, 0);
-  std::copy(B.begin(), B.begin() + MT.n_shared_ints, J.begin());
-  for (int d = 0; d < lpc; ++d) {
-    int32_t* row = &J[(size_t)MT.n_shared_ints + (size_t)d * dev_ints];
-    std::copy(B.begin() + MT.off_dev + (size_t)d * MT.dev_ints, B.begin() + MT.off_dev + (size_t)(d + 1) * MT.dev_ints, row);
-    std::copy(p->link_rows.begin() + (size_t)d * 4 * V, p->link_rows.begin() + (size_t)(d + 1) * 4 * V, row + MT.dev_ints);
-  }
-  std::copy(B.begin() + MT.off_expect, B.end(), J.begin() + MT.n_shared_ints + (size_t)lpc * dev_ints);
-  DeviceGuard g(p->device_id);
-  if (!g.ok) return FPSCHED_EHIP;
-  if (hipDeviceSynchronize() != hipSuccess) return FPSCHED_EHIP;   // an earlier image may be in use
-  if (J.size() > p->combo_image_ints) {
-    if (p->d_combo_image) (void)hipFree(p->d_combo_image);
-    p->d_combo_image = nullptr;
-    p->combo_image_ints = 0;
-    if (hipMalloc(&p->d_combo_image, J.size() * sizeof(int32_t)) != hipSuccess) { p->d_combo_image = nullptr; return FPSCHED_ENOMEM; }
-    p->combo_image_ints = J.size();
-  }
-  const int32_t lds_bytes = (int32_t)(4ll * (MT.n_shared_ints + (int64_t)geo.waves * geo.wave_ints));
-  if (hipMemcpy(p->d_combo_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(slot_kernel_of<kSlotPerMicrobatchLdsLinks>(p->slot_v, p->slot_deg2, MT.n_classes == 1)),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
-    return FPSCHED_EHIP;
-  p->stab_combo = MT;
-  p->stab_combo.ints = p->d_combo_image;
-  p->stab_combo.link_words = p->link_words;
-  p->stab_combo.slots_per_cand = slots_per_cand;
-  p->stab_combo.dev_ints = dev_ints;
-  p->stab_combo.off_expect = MT.n_shared_ints + lpc * dev_ints;
-  p->stab_combo.cands_per_wave = geo.cands_per_wave;
-  p->stab_combo.wave_ints = geo.wave_ints;
-  p->combo_waves = geo.waves;
-  p->combo_grid = p->n_cu * geo.groups;
-  p->combo_lds_bytes = lds_bytes;
-  p->combo_ok = true;
-  if (getenv("FPSCHED_VERBOSE"))
-    fprintf(stderr, "[fpsched] costs per micro-batch + link occupancy: %d x %d wavefronts per compute unit\n", geo.groups, geo.waves);
-  return FPSCHED_OK;
 }
 
 int fpsched_problem_set_microbatch_costs(fpsched_problem* p, const int32_t* dur_mb) {
@@ -1158,84 +1226,18 @@ int fpsched_problem_set_microbatch_costs(fpsched_problem* p, const int32_t* dur_
       hipFuncSetAttribute(reinterpret_cast<const void*>(slot_kernel_of<kSlotPerMicrobatch>(p->slot_v, p->slot_deg2, p->stab.n_classes == 1)),
                           hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
-  // Costs of one or two bytes in LDS next to the metadata, if that leaves room for at least six wavefronts
-  // per compute unit: [block][chunk < V][lanes per candidate][row of m values], padded to 2 KB.  Kinds
-  // whose costs are the same (a forward pass whether its activation is kept or dropped, a
-  // recomputation, ...) share a block.
-  bool in_lds = false;
-  if (p->slots_ok && fits_slots && max_dur < 65536 && !getenv("FPSCHED_MB_GLOBAL")) {
-    const SlotTables& ST = p->stab;
-    const int V = p->slot_v;
-    int block_of[kNKinds] = {0}, n_blocks = 0, kind_of_block[kNKinds] = {0};
-    for (int kind = 1; kind < kNKinds; ++kind) {
-      int found = -1;
-      for (int b = 0; b < n_blocks && found < 0; ++b)
-        if (std::equal(dur_mb + (size_t)kind * S * m, dur_mb + (size_t)(kind + 1) * S * m, dur_mb + (size_t)kind_of_block[b] * S * m)) found = b;
-      if (found < 0) { found = n_blocks; kind_of_block[n_blocks++] = kind; }
-      block_of[kind] = found;
+  p->mb_raw.assign(dur_mb, dur_mb + n_raw);
+  p->lists_mb.ok = p->lists_both.ok = false;
+  if (p->slots_ok && fits_slots) {
+    if (!getenv("FPSCHED_MB_GLOBAL")) {
+      const int rc = build_list_variant(p, false, dur_mb, &p->lists_mb);
+      if (rc != FPSCHED_OK && rc != FPSCHED_EUNSUPPORTED) return rc;
     }
-    uint32_t kind_map = 0;
-    for (int kind = 1; kind < kNKinds; ++kind) kind_map |= (uint32_t)block_of[kind] << (4 * kind);
-    const int value_bytes = max_dur < 256 ? 1 : 2;
-    const int64_t row_dwords = slot_mb_row_dwords(m, value_bytes);   // of one device
-    const int64_t table_ints = ((int64_t)n_blocks * V * lpc * row_dwords + 511) & ~511ll;
-    const int64_t shared = ST.n_shared_ints + table_ints;
-    const SlotGeometry geo = slot_geometry(shared, lpc, ST.state_words, ST.slots_per_cand, p->max_lds, ST.cands_per_wave);
-    if (geo.waves * geo.groups >= 6 && geo.cands_per_wave == ST.cands_per_wave) {
-      std::vector<int32_t> J((size_t)shared + (p->slot_ints.size() - ST.n_shared_ints), 0);
-      std::copy(p->slot_ints.begin(), p->slot_ints.begin() + ST.n_shared_ints, J.begin());
-      std::copy(p->slot_ints.begin() + ST.n_shared_ints, p->slot_ints.end(), J.begin() + shared);
-      unsigned char* t8 = reinterpret_cast<unsigned char*>(J.data() + ST.n_shared_ints);
-      for (int b = 0; b < n_blocks; ++b)
-        for (int c = 0; c < V; ++c)
-          for (int d = 0; d < D; ++d) {
-            if (c >= p->n_chunks[d]) continue;
-            const int s = p->local_stage[(size_t)d * kMaxChunks + c];
-            unsigned char* row = t8 + (((size_t)b * V + c) * lpc + d) * row_dwords * 4;
-            for (int j = 0; j < m; ++j) {
-              const uint32_t value = (uint32_t)dur_mb[((size_t)kind_of_block[b] * S + s) * m + j];
-              if (value_bytes == 1) row[j] = (unsigned char)value;
-              else { row[2 * j] = (unsigned char)value; row[2 * j + 1] = (unsigned char)(value >> 8); }
-            }
-          }
-      if (J.size() > p->mb_image_ints) {   // tables with more distinct kinds need a larger image
-        if (p->d_mb_image) (void)hipFree(p->d_mb_image);
-        p->d_mb_image = nullptr;
-        p->mb_image_ints = 0;
-        if (hipMalloc(&p->d_mb_image, J.size() * sizeof(int32_t)) != hipSuccess) { p->d_mb_image = nullptr; return FPSCHED_ENOMEM; }
-        p->mb_image_ints = J.size();
-      }
-      if (hipMemcpy(p->d_mb_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) return FPSCHED_EHIP;
-      p->mb_image_host = J;
-      p->stab_mb = ST;
-      p->stab_mb.ints = p->d_mb_image;
-      p->stab_mb.off_mb = ST.n_shared_ints;
-      p->stab_mb.mb_kind_map = kind_map;
-      p->stab_mb.mb_value_bytes = value_bytes;
-      p->stab_mb.n_shared_ints = (int32_t)shared;
-      p->stab_mb.off_dev = ST.off_dev + (int32_t)table_ints;
-      p->stab_mb.off_expect = ST.off_expect + (int32_t)table_ints;
-      p->stab_mb.cands_per_wave = geo.cands_per_wave;
-      p->stab_mb.wave_ints = geo.wave_ints;
-      p->mb_waves = geo.waves;
-      p->mb_grid = p->n_cu * geo.groups;
-      p->mb_lds_bytes = (int32_t)(4ll * (shared + (int64_t)geo.waves * geo.wave_ints));
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(slot_kernel_of<kSlotPerMicrobatchLds>(p->slot_v, p->slot_deg2, ST.n_classes == 1)),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
-        return FPSCHED_EHIP;
-      in_lds = true;
+    if (p->links_on) {   // both variants: only with the table in LDS; else the handle stays on the links alone
+      const int rc = build_list_variant(p, true, dur_mb, &p->lists_both);
+      if (rc != FPSCHED_OK) return rc;
     }
   }
-  p->mb_in_lds = in_lds;
-  if (p->links_on) {   // both variants: only with the table in LDS; else the handle stays on the links alone
-    const int rc = build_combined_tables(p);
-    if (rc != FPSCHED_OK) return rc;
-  }
-  if (getenv("FPSCHED_VERBOSE"))
-    fprintf(stderr, "[fpsched] costs per micro-batch: %s; slot kernel %d x %d wavefronts per compute unit (plain: %d x %d), LDS limit %d bytes\n",
-            !(p->slots_ok && fits_slots) ? "general kernel" : (in_lds ? "slot kernel, table in LDS" : "slot kernel, table in device memory"),
-            in_lds ? p->mb_grid / std::max(p->n_cu, 1) : p->slot_grid / std::max(p->n_cu, 1), in_lds ? p->mb_waves : p->slot_waves,
-            p->slot_grid / std::max(p->n_cu, 1), p->slot_waves, p->max_lds);
   p->mb_set = true;
   p->mb_slots_ok = p->slots_ok && fits_slots;
   p->mb_max_dur = max_dur;
@@ -1258,14 +1260,18 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
     return FPSCHED_OK;
   }
   if (!p->slots_ok || bound >= (1ll << 24)) return FPSCHED_EUNSUPPORTED;
-  if (p->d_links_image) {   // built by an earlier call
-    if (p->mb_set) {        // both variants: the cost table's image with this form's device rows
-      const int rc = build_combined_tables(p);
-      if (rc != FPSCHED_OK) return rc;
-    }
+  if (p->mb_set) {   // both variants
+    const int rc = build_list_variant(p, true, p->mb_raw.data(), &p->lists_both);
+    if (rc != FPSCHED_OK) return rc;
+  }
+  if (p->lists_links.ok) {   // built by an earlier call
     p->links_on = true;
     return FPSCHED_OK;
   }
+  const int rc = build_list_variant(p, true, nullptr, &p->lists_links);
+  if (rc != FPSCHED_OK) return rc;
+  p->links_on = true;
+  // ---- the sliding pass under the link model, if it fits
   // links of a device: the devices its stages send to (activations to successor stages, gradients to
   // predecessor stages), numbered in the order they are met
   const std::vector<int32_t>& I = p->host_ints;
@@ -1298,7 +1304,7 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
   // out-edge write
   int link_words = 2;
   for (int d = 0; d < D; ++d) link_words = std::max(link_words, (int)sends_to[d].size() + 2);
-  if (link_words * 256 > 0xffff) return FPSCHED_EUNSUPPORTED;
+  if (link_words * 256 > 0xffff) return FPSCHED_OK;
   const uint32_t spare = (uint32_t)(link_words - 2) * 256u;
   // (this form of the kernel needs no dump region behind the slots: ops without an out-edge write the
   // lane's last link word)
@@ -1306,7 +1312,7 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
   // (as many candidates per wavefront as the plain tables: the per-lane constants are shared)
   SlotGeometry geo = slot_geometry(ST.n_shared_ints, lpc, ST.state_words + link_words, slots_per_cand, p->max_lds,
                                    ST.cands_per_wave);
-  if (geo.waves < 1 || geo.cands_per_wave != ST.cands_per_wave) return FPSCHED_EUNSUPPORTED;
+  if (geo.waves < 1 || geo.cands_per_wave != ST.cands_per_wave) return FPSCHED_OK;
   // never more wavefronts than the plain kernel runs with: where this form would fit more (batches of
   // short candidates), more segments only lengthen the ragged end of a batch
   const int plain_groups = std::max(p->slot_grid / std::max(p->n_cu, 1), 1);
@@ -1315,8 +1321,7 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
     geo.waves = p->slot_waves;
     geo.groups = plain_groups;
   }
-  // a table image (the plain one, or the timing pass's) with longer dev rows:
-  // [.. 2 + 4V ints as before ..][4V out-edges]
+  // the timing pass's table image with longer dev rows: [.. 2 + 4V ints as before ..][4V out-edges]
   const int dev_ints = ST.dev_ints + 4 * V;
   auto with_links = [&](const std::vector<int32_t>& base) {
   std::vector<int32_t> J((size_t)ST.n_shared_ints + (size_t)lpc * dev_ints + (size_t)lpc * ST.state_words, 0);
@@ -1342,21 +1347,10 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
   std::copy(base.begin() + ST.off_expect, base.end(), J.begin() + ST.n_shared_ints + (size_t)lpc * dev_ints);
   return J;
   };
-  const std::vector<int32_t> J = with_links(p->slot_ints);
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
-  int32_t* image = nullptr;
-  if (hipMalloc(&image, J.size() * sizeof(int32_t)) != hipSuccess) return FPSCHED_ENOMEM;
-  const SlotKernel kernel = slot_kernel_of<kSlotLinks>(p->slot_v, p->slot_deg2, ST.n_classes == 1);
   const int32_t lds_bytes = (int32_t)(4ll * (ST.n_shared_ints + (int64_t)geo.waves * geo.wave_ints));
-  if (hipMemcpy(image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess) {
-    (void)hipFree(image);
-    return FPSCHED_EHIP;
-  }
-  p->d_links_image = image;
   p->stab_links = ST;
-  p->stab_links.ints = image;
   p->stab_links.link_words = link_words;
   p->stab_links.slots_per_cand = slots_per_cand;
   p->stab_links.dev_ints = dev_ints;
@@ -1366,11 +1360,6 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
   p->links_waves = geo.waves;
   p->links_grid = p->n_cu * geo.groups;
   p->links_lds_bytes = lds_bytes;
-  p->link_words = link_words;
-  p->link_rows.assign((size_t)lpc * 4 * V, 0);
-  for (int d = 0; d < lpc; ++d)
-    std::copy(J.begin() + ST.n_shared_ints + (size_t)d * dev_ints + ST.dev_ints,
-              J.begin() + ST.n_shared_ints + (size_t)(d + 1) * dev_ints, p->link_rows.begin() + (size_t)d * 4 * V);
   // the sliding pass's timing kernel under the link model: the timing image, widened the same way; it
   // needs 16 bytes of LDS more
   if (p->slide_ok && !p->times_ints.empty() && (int64_t)lds_bytes + 16 <= p->max_lds / geo.groups) {
@@ -1408,14 +1397,6 @@ int fpsched_problem_set_link_occupancy(fpsched_problem* p, int32_t on) {
       if (timg) (void)hipFree(timg);
     }
   }
-  if (p->mb_set) {   // both variants (the link tables stay built whatever comes of it)
-    const int rc = build_combined_tables(p);
-    if (rc != FPSCHED_OK) return rc;
-  }
-  p->links_on = true;
-  if (getenv("FPSCHED_VERBOSE"))
-    fprintf(stderr, "[fpsched] link occupancy: %d link words per lane, %d x %d wavefronts per compute unit (plain: %d x %d)\n",
-            link_words, geo.groups, geo.waves, p->slot_grid / std::max(p->n_cu, 1), p->slot_waves);
   return FPSCHED_OK;
 }
 
@@ -1649,7 +1630,7 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
   ST.off_dev = n_shared;
   ST.dev_ints = dev_ints;
   ST.off_expect = n_shared + lpc * dev_ints;
-  ST.off_mb = 0; ST.link_words = 0; ST.mb_kind_map = 0; ST.copy_depth = 0;
+  ST.link_words = 0; ST.copy_depth = 0;
   const SlotGeometry geo = slot_geometry(n_shared, lpc, state_words, slot_stride, p->max_lds);
   if (geo.waves < 1) return;
   ST.cands_per_wave = geo.cands_per_wave;

@@ -41,12 +41,9 @@ constexpr int kSlotMaxThreads = 64 * kSlotMaxWaves;
 // [n_cand][D] (words issued per device) and out_flags (DEADLOCK / INCOMPLETE only) instead of makespan, idle and peak;
 // needs 16 bytes of LDS more.
 // MODE kSlotPerMicrobatch: durations from mb_rows [32][lanes per candidate][m] (cost << 8 per metadata
-// row, device and micro-batch) instead of the metadata rows.  MODE kSlotPerMicrobatchLds: from the
-// sixteen-bit table at T.off_mb, which travels to LDS with the metadata.
-// MODE kSlotLinks: every ordered pair of devices is a link that carries one value at a time; a
-// producer holds its value back until its link is free (T.link_words, the longer dev rows).
-// MODE kSlotTimesLinks: the timing pass of the sliding under the link model (both of the above).
-// MODE kSlotPerMicrobatchLdsLinks: costs per micro-batch from LDS and link occupancy together.
+// row, device and micro-batch) instead of the metadata rows.
+// MODE kSlotTimesLinks: the timing pass of the sliding under the link model: every ordered pair of devices is a link that
+// carries one value at a time; a producer holds its value back until its link is free (T.link_words, the longer dev rows).
 // MODE kSlotCopy: offload and reload items run on a copy engine beside the computation (T.copy_depth transfers
 // at most in the engine; T.link_words = 32 dwords per lane behind its state words: the finish times and keys of
 // the last eight transfers, and a ring of eight pending memory events).
@@ -55,9 +52,8 @@ constexpr int kSlotMaxThreads = 64 * kSlotMaxWaves;
 // per chunk the micro-batches per item | items << 16.
 // MODE kSlotSlide: the weight-gradient sliding pass without its lists: the results of the lists the two-pass form
 // would write, in one kernel (tables as for kSlotTimes plus the W items' costs at T.off_w; 16 bytes of LDS more).
-constexpr int kSlotTimes = 1, kSlotPerMicrobatch = 2, kSlotPerMicrobatchLds = 3, kSlotLinks = 4,
-              kSlotTimesLinks = 5, kSlotPerMicrobatchLdsLinks = 6, kSlotCopy = 7, kSlotSync = 8, kSlotSlide = 9,
-              kSlotSlideLinks = 10;   // kSlotSlide under the link model
+constexpr int kSlotTimes = 1, kSlotPerMicrobatch = 2, kSlotTimesLinks = 3, kSlotCopy = 4, kSlotSync = 5, kSlotSlide = 6,
+              kSlotSlideLinks = 7;   // kSlotSlide under the link model
 constexpr int kSlotCopyWords = 32;
 template <int V, bool DEG2, bool ONE_CLASS, int MODE>
 __global__ void eval_slot_kernel(SlotTables T, const uint16_t* ops, long long n_cand, int stride,
@@ -79,7 +75,7 @@ template <int VBITS>   // 0, 1, 2: up to 1, 2, 4 stages per device
 __global__ void check_rows_kernel(ListTables T, const uint16_t* ops, long long n_rows, int stride, int rows_per_wave,
                                   long long* out_info, int* out_peak, unsigned long long* counter,
                                   unsigned long long counter_value, int draw_blocks, int dynamic);
-template <bool DEG2, bool WIDE>
+template <bool DEG2, bool WIDE, bool LINKS, bool MB>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block);

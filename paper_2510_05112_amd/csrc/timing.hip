@@ -29,6 +29,18 @@
 // host picks it where the bound on all times does not fit 24 bits or a latency not 16; the table kernel that such
 // problems ran on before took 5.2 ms for 8,192 candidates of that size.
 //
+// LINKS, the link-occupancy variant of the cost model: a link between two devices carries one value at a time.  An op
+// with an output to another device leaves in its slot not its finish time but the time its value leaves, max(finish, link
+// busy until), and keeps the link busy for the edge's latency from then; the consumer adds the latency as before.  The
+// lane keeps that time of each link its devices send over in a word of LDS, and the op's row has a word more: the link
+// and the latency.  An op without such an output has a link of its own of latency 0, which only ever holds earlier
+// finish times of the device.  The word is read together with the slot, since only the lane itself writes it.
+//
+// MB, costs per micro-batch: the row has, instead of the cost, where the costs of its (kind, stage) begin in a table in
+// LDS; the cost is read together with the slot as well.  The busy time is then summed up here.  Both forms, 20,011
+// candidates of 11 devices, 45 micro-batches, 3 chunks: 0.64 + 0.06 ms; 2.01 ms as forms of the slot kernel with all
+// devices in every round and 16 lanes to a candidate.
+//
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
@@ -68,11 +80,12 @@ constexpr unsigned kWindowBytes = 64u * kRingBytes;   // the rings of one half o
 
 }  // namespace
 
-template <bool DEG2, bool WIDE>
+template <bool DEG2, bool WIDE, bool LINKS, bool MB>
 __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block) {
+  static_assert(!WIDE || !(LINKS || MB), "these forms have times of 24 bits");
   constexpr unsigned kRowBytes = 16u;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
   extern __shared__ int32_t lds[];
@@ -85,7 +98,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   const int d0 = 2 * pair;
   const bool has_odd = d0 + 1 < D;
   const unsigned wave_at = lds0 + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)T.wave_bytes;
-  unsigned slot_base = wave_at + 2u * kWindowBytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * kSlotBytes;
+  const unsigned links_bytes = LINKS ? (unsigned)T.link_words * 512u : 0u;   // of the wavefront: [half][link][lane]
+  unsigned slot_base = wave_at + 2u * kWindowBytes + links_bytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * kSlotBytes;
   asm volatile("" : "+v"(slot_base));   // one register, not a sum to be re-associated every round
   const unsigned own_word = slot_base + (unsigned)(lane_ok ? d0 : 0) * kSlotBytes;
   const int own_at = (lane_ok ? d0 : 0) * (int)kSlotBytes;   // that word as a row's slot field
@@ -121,12 +135,15 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned pos2;      // byte position of w_next; the device has issued pos2 / 2 - 1 ops
     unsigned info;      // what the order pass left for this row: kRow* | stop
     unsigned busy;
+    unsigned link_rows, links;   // LINKS: where its devices' link rows are, the lane's link words
+    unsigned link;               // the op's link row: byte offset of the link word, latency << 16
     uint4 pend0, pend1;
     int n_pend;         // pieces requested and not landed: pend0, then pend1
   };
   Device even, odd;
   auto idle_device = [&](Device& x) {
     x.R = WIDE ? lds_int4{0, 0, own_at, (int)kWideNever} : lds_int4{1, 0, own_at, 0};
+    x.link = 0u;
     x.loaded2 = 0x40000000u;
     x.pos2 = 2u;
     x.info = 0u;
@@ -136,6 +153,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     // (lanes eight apart share their banks: the halves of their rings are in different orders)
     x.win = wave_at + (unsigned)k * kWindowBytes + (unsigned)lane * kRingBytes + (((unsigned)lane >> 3) & 1u) * 16u;
     x.meta = lds0 + (unsigned)(k * P + pair) * kRowBytes;
+    x.link_rows = LINKS ? lds0 + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
+    x.links = LINKS ? wave_at + 2u * kWindowBytes + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
     x.pend0 = make_uint4(0u, 0u, 0u, 0u); x.pend1 = x.pend0;
     idle_device(x);
@@ -158,6 +177,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     const unsigned at = __umul24(word >> 11, row_stride) + x.meta;
     x.j_slot = word * kSlotBytes;
     x.R = lds_read<lds_int4>(at);
+    if (LINKS) x.link = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.link_rows);
   };
   // address of a byte position in the device's ring
   auto in_ring = [&](const Device& x, unsigned at2) -> unsigned {
@@ -217,8 +237,16 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   auto step = [&](Device& x) -> unsigned long long {
     asm volatile("" : "+v"(x.R), "+v"(x.j_slot));   // (the row stays one value until here: no earlier wait for it)
     const unsigned at_slot = (x.j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
-    unsigned ready;
+    unsigned ready, cost_tag = (unsigned)x.R.y, link_free = 0u;
     unsigned long long moved;
+    unsigned cost = 0u;
+    if (MB) {
+      // (a row without a cost table reads some word of LDS and does not issue)
+      const unsigned at = lds0 + (cost_tag >> 8) + (((x.j_slot >> 2) & 0x7ffu) << (T.mb_bytes - 1));
+      cost = T.mb_bytes == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
+      cost_tag = cost << 8 | (cost_tag & 0xffu);
+    }
+    if (LINKS) link_free = lds_read<unsigned>(x.links + (x.link & 0xffffu));
     if (WIDE) {
       // the slot's second word is the tag, the row's last one the expected tag (byte 1) and the op's own (byte 0)
       const lds_int2 in = lds_read<lds_int2>(at_slot);
@@ -246,8 +274,15 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       }
     }
     if (__builtin_amdgcn_inverse_ballot_w64(issue)) {
-      const unsigned val = max(x.free_at, ready) + (unsigned)x.R.y;
+      unsigned val = max(x.free_at, ready) + cost_tag;
       x.free_at = WIDE ? val : val & 0xffffff00u;
+      if (MB) x.busy += cost;
+      if (LINKS) {
+        // (the tag stays in the low byte, which the link words do not have)
+        const unsigned leaves = max(val, link_free | (cost_tag & 0xffu));
+        lds_write<unsigned>(x.links + (x.link & 0xffffu), (leaves & 0xffffff00u) + (x.link >> 16 << 8));
+        val = leaves;
+      }
       auto leave = [&](unsigned at) {
         if (WIDE) lds_write<lds_int2>(at, lds_int2{(int)val, x.R.w & 0xff});
         else lds_write<uint32_t>(at, val);
@@ -255,6 +290,11 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       leave(at_slot);
       if (DEG2 && ((unsigned)x.R.w & kRowTwoOut) != 0u) {
         const unsigned second = lds_read<uint32_t>(second_row(x.R.w) + 8u);
+        if (LINKS) {
+          const unsigned link = lds_read<unsigned>(second_row(x.R.w) + 12u);
+          val = max(x.free_at, lds_read<unsigned>(x.links + (link & 0xffffu))) | (cost_tag & 0xffu);
+          lds_write<unsigned>(x.links + (link & 0xffffu), (val & 0xffffff00u) + (link >> 16 << 8));
+        }
         leave((x.j_slot & (second >> 16)) + slot_base + (second & 0xffffu));
       }
       decode(x, x.w_next);
@@ -321,6 +361,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           clear_own(own_word);
           if (has_odd) clear_own(own_word + kSlotBytes);
           if (pair == 0) lds_write<uint32_t>(at_max, 0u);
+          if (LINKS)
+            for (unsigned i = 0; i < links_bytes / 2u; i += 256u) { lds_write<unsigned>(even.links + i, 0u); lds_write<unsigned>(odd.links + i, 0u); }
           const long long r = cand * D + d0;
           row = reinterpret_cast<const char*>(ops + (size_t)r * (size_t)stride);
           request(even, row, 0u);
@@ -396,13 +438,19 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   }
 }
 
-#define FPSCHED_INSTANTIATE(DEG2, WIDE)                                                                          \
-  template __global__ void time_lists_kernel<DEG2, WIDE>(ListTables, const uint16_t*, long long, int, long long*, \
-                                                         long long*, int*, unsigned char*, unsigned long long*, int);
-FPSCHED_INSTANTIATE(false, false)
-FPSCHED_INSTANTIATE(true, false)
-FPSCHED_INSTANTIATE(false, true)
-FPSCHED_INSTANTIATE(true, true)
+#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB)                                                                     \
+  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB>(ListTables, const uint16_t*, long long, int, long long*, \
+                                                                    long long*, int*, unsigned char*, unsigned long long*, int);
+FPSCHED_INSTANTIATE(false, false, false, false)
+FPSCHED_INSTANTIATE(true, false, false, false)
+FPSCHED_INSTANTIATE(false, true, false, false)
+FPSCHED_INSTANTIATE(true, true, false, false)
+FPSCHED_INSTANTIATE(false, false, true, false)
+FPSCHED_INSTANTIATE(true, false, true, false)
+FPSCHED_INSTANTIATE(false, false, false, true)
+FPSCHED_INSTANTIATE(true, false, false, true)
+FPSCHED_INSTANTIATE(false, false, true, true)
+FPSCHED_INSTANTIATE(true, false, true, true)
 #undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched
