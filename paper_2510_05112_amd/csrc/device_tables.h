@@ -107,8 +107,8 @@ struct SlotTables {
   const int32_t* ints;      // DEVICE
 };
 
-// Tables of the two-pass list evaluation (rows.hip, timing.hip).  `ints` = [timing rows][link rows][cost table][order rows]
-// [dev], link rows and cost table in their forms only:
+// Tables of the two-pass list evaluation (rows.hip, timing.hip).  `ints` = [timing rows][link or group rows]
+// [cost table][order rows][dev], those in the middle in their forms only:
 //   timing rows [kNKinds * 4][D, the even devices first] x 4 ints, addressed by the top five bits of the op word and
 //   the device:
 //     0 (latency of the first input << 8) - tag expected on it (kEmptySlot's tag if the op starts a class, kOwnTag if
@@ -123,16 +123,18 @@ struct SlotTables {
 //   duration, word 3 the tag the op leaves | the tag it expects << 8 | number of 16-byte rows in front of its second row
 //   << 16 | the two flags; word 3 of a second row is the tag expected on the first edge << 8.
 //   Slots of a candidate, in dwords: [0, D) the devices' own words, D + 1
-//   for the makespan, then from list_slots_at(D) on class * m for backward values, (classes + class) * m for forward
-//   values; finish << 8 | producer stage, kEmptySlot at first.
+//   for the makespan, then from list_slots_at(D) on class * m for backward values, (backward classes + class) * m for
+//   forward values; finish << 8 | producer stage, kEmptySlot at first.
 //   link rows: byte offset of the word of the link that the first output goes over | latency << 16; an op that sends nothing
 //     to another device has the last word.
 //   cost table: per kind (kinds with the same costs share) and stage a row of mb_bytes per micro-batch, an odd number of
 //     dwords long; word 1 of a timing row then has the byte offset of that row instead of the duration, and the order
 //     rows' durations are 0.
+//   group rows: micro-batches per item of the op's stage | of them, those whose input it waits for (1 without an input) << 16
 //   order rows [kNKinds * 4][D] x 2 ints:
 //     0 next state | required state << 8 | units allocated << 16 | units freed << 24   1 dur
-//     Rows of words that may not appear on the device require kNoState.
+//     Rows of words that may not appear on the device require kNoState; word 1 of the rows of kind 0 has the items of the
+//     chunk's stage.
 //   dev [D] x 2: chunks on the device, memory cap / unit_scale
 // Memory units are divided by their greatest common divisor (unit_scale) and must then fit a byte.
 struct ListTables {
@@ -144,6 +146,7 @@ struct ListTables {
   int32_t off_links;        // links form: link rows, one int per timing row in the same order, in ints
   int32_t link_words;       // links form: words per lane and half (one behind the links for ops that send nothing)
   int32_t mb_bytes;         // costs per micro-batch: bytes of a value, 1 or 2
+  int32_t off_sync;         // synchronisation form: group rows, one int per timing row in the same order, in ints (0: none)
   int32_t off_check;        // order rows, in ints
   int32_t n_check_ints;
   int32_t check_shared_bytes;   // order rows and dev rows in LDS, a multiple of 16

@@ -18,7 +18,7 @@ using namespace fpsched;
 
 // The list evaluation's tables and launch shape under link occupancy, costs per micro-batch, or both
 struct ListVariant {
-  bool ok = false;
+  bool ok = false, deg2 = false;
   ListTables tab{};
   int32_t* d_image = nullptr;
   size_t capacity = 0;             // ints
@@ -66,7 +66,7 @@ struct fpsched_problem {
   int32_t check_rows_per_wave = 0, check_waves = 0, check_grid = 0, check_vbits = 0;
   int32_t time_waves = 0, time_grid = 0;   // wavefronts per workgroup, resident workgroups
   std::vector<int32_t> list_image;         // host copy of d_list_ints
-  ListVariant lists_links, lists_mb, lists_both;
+  ListVariant lists_links, lists_mb, lists_both, lists_sync;
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
   int64_t max_comm = 0;
   bool mb_set = false;
@@ -242,10 +242,11 @@ CheckKernel check_kernel_of(int vbits) {
 using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int);
 template <bool LINKS, bool MB>
 TimeKernel narrow_time_kernel_of(bool deg2) {
-  return deg2 ? &time_lists_kernel<true, false, LINKS, MB> : &time_lists_kernel<false, false, LINKS, MB>;
+  return deg2 ? &time_lists_kernel<true, false, LINKS, MB, false> : &time_lists_kernel<false, false, LINKS, MB, false>;
 }
-TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, bool mb = false) {
-  if (wide) return deg2 ? &time_lists_kernel<true, true, false, false> : &time_lists_kernel<false, true, false, false>;
+TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, bool mb = false, bool sync = false) {
+  if (sync) return deg2 ? &time_lists_kernel<true, false, false, false, true> : &time_lists_kernel<false, false, false, false, true>;
+  if (wide) return deg2 ? &time_lists_kernel<true, true, false, false, false> : &time_lists_kernel<false, true, false, false, false>;
   if (links) return mb ? narrow_time_kernel_of<true, true>(deg2) : narrow_time_kernel_of<true, false>(deg2);
   return mb ? narrow_time_kernel_of<false, true>(deg2) : narrow_time_kernel_of<false, false>(deg2);
 }
@@ -265,41 +266,55 @@ WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
   return WorkgroupShape{0, 1};
 }
 
-// Table image of the two-pass list evaluation (layout: device_tables.h) and the launch shapes of its kernels.
-// Leaves lists_ok false if the problem does not fit: more than two inputs or outputs of a stage, times, latencies,
-// stages or slots beyond the widths of their fields, or no room in LDS.
-void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, const std::vector<StageEdges>& edges,
-                       int n_classes, int64_t bound, std::vector<int32_t>* image) {
+// Edge slots of an op: an input and the output that continues its class share one, an output (or input) of a class of its
+// own has one.
+struct EdgeSlot { int32_t cls; const StageEdge* in; bool out; };
+std::vector<EdgeSlot> edge_slots(const StageEdges& e, int dir) {
+  std::vector<EdgeSlot> slots;
+  for (const StageEdge& in : e.in[dir]) slots.push_back(EdgeSlot{in.cls, &in, false});
+  for (const StageEdge& out : e.out[dir]) {
+    size_t i = 0;
+    while (i < slots.size() && slots[i].cls != out.cls) ++i;
+    if (i == slots.size()) slots.push_back(EdgeSlot{out.cls, nullptr, true});
+    else slots[i].out = true;
+  }
+  // (the output of the first slot goes with the op's first row)
+  if (slots.size() > 1 && !slots[0].out && slots[1].out) std::swap(slots[0], slots[1]);
+  return slots;
+}
+
+// Table image of the two-pass list evaluation (layout: device_tables.h): rows and sizes, not yet the launch shapes.
+// n_forward, n_backward: slot classes of either direction.  items: per stage (m, or fewer where an item is a group of micro-batches).  Returns false if the problem does not fit:
+// more than two edge slots of a stage in one direction, or times, latencies,
+// stages or slots beyond the widths of their fields.
+bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& edges, int n_forward, int n_backward, bool wide,
+                     const std::vector<int32_t>& items, ListTables* tables, bool* deg2, std::vector<int32_t>* image) {
   const int D = p->D, S = p->S, m = p->m;
+  const int32_t* dur = &p->host_ints[p->tables.off_dur];
+  const int32_t* mem_units = &p->host_ints[p->tables.off_mem_units];
+  const int32_t* mem_cap = &p->host_ints[p->tables.off_mem_cap];
   int64_t unit_scale = 0;
-  for (int s = 0; s < S; ++s) unit_scale = std::gcd<int64_t, int64_t>(unit_scale, desc->mem_units[s]);
+  for (int s = 0; s < S; ++s) unit_scale = std::gcd<int64_t, int64_t>(unit_scale, mem_units[s]);
   unit_scale = std::max<int64_t>(unit_scale, 1);
-  const int64_t cand_slots = (list_slots_at(D) + 2ll * n_classes * m + 3) & ~3ll;
-  const bool wide = p->max_comm >= (1ll << 16) || bound >= (1ll << 24);
+  const int64_t cand_slots = (list_slots_at(D) + (int64_t)(n_forward + n_backward) * m + 3) & ~3ll;
   const int slot_bytes = wide ? 8 : 4;
-  if (slot_bytes * cand_slots > 0xffff || S > 255) return;
-  bool deg2 = false;
+  if (slot_bytes * cand_slots > 0xffff || S > 255) return false;
+  *deg2 = false;
+  int n_second = 0;   // (F, FD and B rows of a stage may each have a second row)
   for (int s = 0; s < S; ++s) {
-    if (desc->mem_units[s] / unit_scale > 0xff) return;
+    if (mem_units[s] / unit_scale > 0xff) return false;
     for (int dir = 0; dir < 2; ++dir) {
-      // (an output edge continues the class of the input edge of the same number: see the slot classes)
-      for (size_t e = 0; e < std::min(edges[s].in[dir].size(), edges[s].out[dir].size()); ++e)
-        if (edges[s].in[dir][e].cls != edges[s].out[dir][e].cls) return;
-      const size_t n = std::max(edges[s].in[dir].size(), edges[s].out[dir].size());
-      if (n > 2) return;
-      deg2 = deg2 || n > 1;
+      const size_t n = edge_slots(edges[s], dir).size();
+      if (n > 2) return false;
+      if (n > 1) { *deg2 = true; n_second += dir == 0 ? 2 : 1; }
     }
   }
   const int row_ints = 4;
-  ListTables& T = p->ltab;
+  ListTables& T = *tables;
+  T = ListTables{};
   T.D = D; T.m = m;
-  // (F, FD and B rows of a stage may each have a second row)
-  int n_second = 0;
-  for (int s = 0; s < S; ++s)
-    for (int dir = 0; dir < 2; ++dir)
-      if (std::max(edges[s].in[dir].size(), edges[s].out[dir].size()) > 1) n_second += dir == 0 ? 2 : 1;
   T.n_time_ints = (kNKinds * kMaxChunks * D * row_ints + n_second * 4 + 7) & ~7;
-  if (4ll * T.n_time_ints > 0xffff) return;
+  if (4ll * T.n_time_ints > 0xffff) return false;
   int second_at = kNKinds * kMaxChunks * D * row_ints;
   T.off_check = T.n_time_ints;
   T.n_check_ints = kNKinds * kMaxChunks * D * 2;
@@ -308,9 +323,6 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
   T.cand_slots = (int32_t)cand_slots;
   T.terminal = p->has_w ? kDone : kBDone;
   T.unit_scale = (int32_t)unit_scale;
-  int max_chunks = 1;
-  for (int d = 0; d < D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
-  p->check_vbits = max_chunks <= 1 ? 0 : (max_chunks <= 2 ? 1 : 2);
   T.state_bytes = ((((m + 1) * (1 << p->check_vbits) + 3) / 4) | 1) * 4;
   std::vector<int32_t>& J = *image;
   J.assign((size_t)T.off_dev + 2 * D, 0);
@@ -326,32 +338,31 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
         t[2] = slot_bytes * d;
         if (wide) t[3] = (int32_t)kWideNever;
         o[0] = (int32_t)(kNoState << 8);
+        if (kind == kEnd && c < p->n_chunks[d]) o[1] = items[p->local_stage[(size_t)d * kMaxChunks + c]];
         if (c >= p->n_chunks[d] || kind == kEnd || (kind == kW && !p->has_w)) continue;
         const int s = p->local_stage[(size_t)d * kMaxChunks + c];
-        const unsigned units = (unsigned)(desc->mem_units[s] / unit_scale);
+        const unsigned units = (unsigned)(mem_units[s] / unit_scale);
         const bool allocs = kind == kF || kind == kFD || kind == kR || kind == kL;
         const bool frees = kind == kFD || kind == kO || kind == (p->has_w ? kW : kB);
         o[0] = (int32_t)((unsigned)next_of[kind] | ((unsigned)need_of[kind] << 8) | ((allocs ? units : 0u) << 16) | ((frees ? units : 0u) << 24));
-        o[1] = desc->dur[kind * S + s];
+        o[1] = dur[kind * S + s];
         const int dir = kind == kF || kind == kFD ? 0 : (kind == kB ? 1 : -1);
-        const std::vector<StageEdge> none;
-        const std::vector<StageEdge>& in = dir < 0 ? none : edges[s].in[dir];
-        const std::vector<StageEdge>& out_edges = dir < 0 ? none : edges[s].out[dir];
-        const bool crosses = !in.empty() || !out_edges.empty();
+        const std::vector<EdgeSlot> slots = dir < 0 ? std::vector<EdgeSlot>() : edge_slots(edges[s], dir);
+        const bool crosses = !slots.empty();
         const unsigned own_tag = crosses ? (unsigned)s : kOwnTag;
-        t[1] = wide ? desc->dur[kind * S + s] : (int32_t)(((unsigned)desc->dur[kind * S + s] << 8) | own_tag);
+        t[1] = wide ? dur[kind * S + s] : (int32_t)(((unsigned)dur[kind * S + s] << 8) | own_tag);
         if (wide) t[3] = (int32_t)own_tag;
         if (!crosses) {
           if (wide) t[3] |= (int32_t)(kOwnTag << 8);
           else t[0] = -(int32_t)kOwnTag;
           continue;
         }
-        const int base = list_slots_at(D) + (dir == 0 ? n_classes * m : 0);
-        for (size_t e = 0; e < std::max(in.size(), out_edges.size()); ++e) {
-          const int cls = e < in.size() ? in[e].cls : out_edges[e].cls;
-          const int32_t slot = (int32_t)((unsigned)(slot_bytes * (base + cls * m)) | ((unsigned)(0x7ff * slot_bytes) << 16));
-          const unsigned expected = e < in.size() ? (unsigned)in[e].tag : kEmptySlot & 0xffu;
-          const unsigned latency = e < in.size() ? (unsigned)in[e].latency : 0u;
+        const int base = list_slots_at(D) + (dir == 0 ? n_backward * m : 0);
+        for (size_t e = 0; e < slots.size(); ++e) {
+          const StageEdge* in = slots[e].in;
+          const int32_t slot = (int32_t)((unsigned)(slot_bytes * (base + slots[e].cls * m)) | ((unsigned)(0x7ff * slot_bytes) << 16));
+          const unsigned expected = in ? (unsigned)in->tag : kEmptySlot & 0xffu;
+          const unsigned latency = in ? (unsigned)in->latency : 0u;
           const int32_t wait = (int32_t)(wide ? latency : (latency << 8) - expected);
           if (e == 0) {
             t[0] = wait;
@@ -362,10 +373,10 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
           int32_t* second = &J[second_at];
           second[0] = t[0]; second[1] = t[2]; second[2] = slot;
           if (wide) second[3] = t[3] & 0xff00;
-          const unsigned flags = (e < out_edges.size() ? kRowTwoOut : 0u) | (e < in.size() ? 1u << 31 : 0u);
+          const unsigned flags = (slots[e].out ? kRowTwoOut : 0u) | (in ? 1u << 31 : 0u);
           const unsigned at_second = wide ? (unsigned)(second_at / 4) << 16 : (unsigned)(4 * second_at);
           t[3] = (int32_t)(((unsigned)t[3] & 0xffffu) | at_second | flags);
-          if (e < in.size()) {
+          if (in) {
             t[0] = wait; t[2] = slot;
             if (wide) t[3] = (int32_t)(((unsigned)t[3] & ~0xff00u) | (expected << 8));
           }
@@ -374,8 +385,22 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
       }
   for (int d = 0; d < D; ++d) {
     J[(size_t)T.off_dev + 2 * d] = p->n_chunks[d];
-    J[(size_t)T.off_dev + 2 * d + 1] = (int32_t)(desc->mem_cap[d] / unit_scale);   // peak > cap  <=>  peak / scale > floor(cap / scale)
+    J[(size_t)T.off_dev + 2 * d + 1] = (int32_t)(mem_cap[d] / unit_scale);   // peak > cap  <=>  peak / scale > floor(cap / scale)
   }
+  return true;
+}
+
+// The plain model's image and the launch shapes; leaves lists_ok false if the problem does not fit.
+void build_list_tables(fpsched_problem* p, const std::vector<StageEdges>& edges, int n_classes, int64_t bound,
+                       std::vector<int32_t>* image) {
+  const bool wide = p->max_comm >= (1ll << 16) || bound >= (1ll << 24);
+  const int slot_bytes = wide ? 8 : 4;
+  int max_chunks = 1;
+  for (int d = 0; d < p->D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
+  p->check_vbits = max_chunks <= 1 ? 0 : (max_chunks <= 2 ? 1 : 2);
+  ListTables& T = p->ltab;
+  bool deg2 = false;
+  if (!fill_list_image(p, edges, n_classes, n_classes, wide, std::vector<int32_t>(p->S, p->m), &T, &deg2, image)) return;
   // order pass: as many rows per wavefront as the states leave room for
   WorkgroupShape check{0, 1};
   int rows = 64;
@@ -394,6 +419,37 @@ void build_list_tables(fpsched_problem* p, const fpsched_problem_desc* desc, con
   p->lists_deg2 = deg2;
   p->lists_wide = wide;
   p->lists_ok = true;
+}
+
+// The launch shape of a variant's tables and its image on the device.  FPSCHED_EUNSUPPORTED if fewer than min_waves
+// wavefronts fit a compute unit.
+int install_list_variant(fpsched_problem* p, ListTables T, const std::vector<int32_t>& J, bool deg2, int min_waves, ListVariant* v) {
+  const WorkgroupShape shape = timing_shape(&T, 4, p->max_lds);
+  if (shape.waves < 1 || shape.waves * shape.groups < min_waves) return FPSCHED_EUNSUPPORTED;
+  DeviceGuard g(p->device_id);
+  if (!g.ok || hipDeviceSynchronize() != hipSuccess) return FPSCHED_EHIP;   // an earlier image may be in use
+  if (J.size() > v->capacity) {
+    if (v->d_image) (void)hipFree(v->d_image);
+    v->d_image = nullptr;
+    v->capacity = 0;
+    if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
+    v->capacity = J.size();
+  }
+  const TimeKernel kernel = time_kernel_of(deg2, false, T.link_words > 0, T.mb_bytes > 0, T.off_sync > 0);
+  if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
+    return FPSCHED_EHIP;
+  T.ints = v->d_image;
+  v->tab = T;
+  v->deg2 = deg2;
+  v->waves = shape.waves;
+  v->grid = p->n_cu * shape.groups;
+  v->ok = true;
+  if (getenv("FPSCHED_VERBOSE"))
+    fprintf(stderr, "[fpsched] list evaluation%s%s%s: %d x %d wavefronts per compute unit (plain: %d x %d), %d candidates each\n",
+            T.link_words > 0 ? ", links" : "", T.mb_bytes > 0 ? ", costs per micro-batch" : "", T.off_sync > 0 ? ", synchronisation" : "",
+            shape.groups, shape.waves, p->time_grid / std::max(p->n_cu, 1), p->time_waves, T.cands_per_wave);
+  return FPSCHED_OK;
 }
 
 // The tables with link rows (links) and a table of costs per micro-batch (mb: [kinds][S][m]) between the timing rows and
@@ -489,34 +545,9 @@ int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVa
   T.off_check = T.n_time_ints;
   T.off_dev = T.off_check + (B.off_dev - B.off_check);
   if (mb)   // (the busy time is the timing pass's)
-    for (int i = 0; i < T.n_check_ints / 2; ++i) J[(size_t)T.off_check + 2 * i + 1] = 0;
-  const WorkgroupShape shape = timing_shape(&T, 4, p->max_lds);
-  if (shape.waves < 1) return FPSCHED_EUNSUPPORTED;
+    for (int i = kMaxChunks * D; i < T.n_check_ints / 2; ++i) J[(size_t)T.off_check + 2 * i + 1] = 0;
   // (costs from device memory, kSlotPerMicrobatch, are better than so few wavefronts)
-  if (mb && !links && shape.waves * shape.groups < 6) return FPSCHED_EUNSUPPORTED;
-  DeviceGuard g(p->device_id);
-  if (!g.ok || hipDeviceSynchronize() != hipSuccess) return FPSCHED_EHIP;   // an earlier image may be in use
-  if (J.size() > v->capacity) {
-    if (v->d_image) (void)hipFree(v->d_image);
-    v->d_image = nullptr;
-    v->capacity = 0;
-    if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
-    v->capacity = J.size();
-  }
-  if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(time_kernel_of(p->lists_deg2, false, links, mb != nullptr)),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
-    return FPSCHED_EHIP;
-  T.ints = v->d_image;
-  v->tab = T;
-  v->waves = shape.waves;
-  v->grid = p->n_cu * shape.groups;
-  v->ok = true;
-  if (getenv("FPSCHED_VERBOSE"))
-    fprintf(stderr, "[fpsched] list evaluation%s%s: %d x %d wavefronts per compute unit (plain: %d x %d), %d candidates each\n",
-            links ? ", links" : "", mb ? ", costs per micro-batch" : "", shape.groups, shape.waves,
-            p->time_grid / std::max(p->n_cu, 1), p->time_waves, T.cands_per_wave);
-  return FPSCHED_OK;
+  return install_list_variant(p, T, J, p->lists_deg2, mb && !links ? 6 : 1, v);
 }
 
 }  // namespace
@@ -888,7 +919,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
         se[a].in[1].push_back({edge_cls[e], b, lat});
         se[b].out[1].push_back({edge_cls[e], a, lat});
       }
-      build_list_tables(p, desc, se, n_classes, (int64_t)D * max_stride_words * (max_dur + max_comm), &list_image);
+      build_list_tables(p, se, n_classes, (int64_t)D * max_stride_words * (max_dur + max_comm), &list_image);
     }
     if (!p->general_ok && !p->lists_ok) { delete p; return FPSCHED_EUNSUPPORTED; }
     p->use_slots = p->lists_ok;
@@ -1006,7 +1037,7 @@ void fpsched_problem_destroy(fpsched_problem* p) {
     if (p->d_times_ints) (void)hipFree(p->d_times_ints);
     if (p->d_mb_raw) (void)hipFree(p->d_mb_raw);
     if (p->d_mb_rows) (void)hipFree(p->d_mb_rows);
-    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both})
+    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync})
       if (v->d_image) (void)hipFree(v->d_image);
     if (p->d_times_links_image) (void)hipFree(p->d_times_links_image);
     if (p->d_slide_links_image) (void)hipFree(p->d_slide_links_image);
@@ -1093,7 +1124,7 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(time_kernel_of(p->lists_deg2, p->lists_wide, T.link_words > 0, T.mb_bytes > 0), dim3((unsigned)time_blocks),
+  hipLaunchKernelGGL(time_kernel_of(variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant, T.link_words > 0, T.mb_bytes > 0, T.off_sync > 0), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
                      out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave));
@@ -1129,6 +1160,8 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
+    if (sync_on_slots && p->lists_sync.ok)
+      return run_list_evaluation(p, &p->lists_sync, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (!copy_on_slots && !sync_on_slots) {
       const ListVariant* variant = p->links_on ? (p->mb_set ? &p->lists_both : &p->lists_links) : (p->mb_set ? &p->lists_mb : nullptr);
       if (!variant || variant->ok)
@@ -1489,11 +1522,13 @@ static int install_table_model(fpsched_problem* p, const std::vector<int32_t>& g
 // The slot kernel's form of the synchronisation model (mode kSlotSync): possible when every dependency pair runs
 // forward-to-forward or backward-to-backward, no stage has more than two inputs or outputs in either direction
 // (pairs included), and the neighbours of a stage with more than one micro-batch per item all have one.  The
-// table image has the plain layout; a pair is an edge of a slot class of its own that exists in one direction.
+// table image has the plain layout; a pair is an edge of a slot class of its own that exists in one direction.  The
+// two-pass evaluation takes those settings in which an op's edges need no more than two slots (p->lists_sync).
 // Leaves p->sync_slots_ok false when the setting does not fit.
 static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t>& grp, const std::vector<int32_t>& items,
                                    int32_t n_pairs, const fpsched_dependency* pairs, int64_t max_lat) {
   p->sync_slots_ok = false;
+  p->lists_sync.ok = false;
   if (!p->slots_ok) return;   // (units, stage count and word format were checked for the plain tables)
   const int D = p->D, S = p->S, m = p->m;
   const std::vector<int32_t>& I = p->host_ints;
@@ -1505,7 +1540,6 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
   // classes of the DAG's edges: chains, as for the plain tables
   std::vector<std::vector<int>> out_cls(S);
   int n_classes = 0;
-  std::vector<int32_t> turnaround(S, 1);
   {
     std::vector<int> indeg(S, 0), order;
     std::vector<std::vector<int>> arriving(S);
@@ -1547,6 +1581,51 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
     if (most > 1) deg2 = true;
     if (grp[s] > 1)
       for (int t : partners[s]) if (grp[t] != 1) return;
+  }
+  if (p->lists_ok && !p->lists_wide) {
+    // the two-pass evaluation's form, where no stage has more than two edge slots in a direction
+    // (classes numbered per direction: a pair has slots in one only)
+    std::vector<StageEdges> edges(S);
+    std::vector<int> number[2];
+    int n_of[2] = {0, 0};
+    for (int dir = 0; dir < 2; ++dir) {
+      number[dir].assign(n_classes, -1);
+      auto numbered = [&](int cls) {
+        if (number[dir][cls] < 0) number[dir][cls] = n_of[dir]++;
+        return number[dir][cls];
+      };
+      for (int s = 0; s < S; ++s) {
+        for (const In& in : dir == 0 ? fwd_in[s] : bwd_in[s]) edges[s].in[dir].push_back(StageEdge{numbered(in.cls), in.from, in.lat});
+        for (int cls : dir == 0 ? fwd_out[s] : bwd_out[s]) edges[s].out[dir].push_back(StageEdge{numbered(cls), 0, 0});
+      }
+    }
+    ListTables LT;
+    bool two = false;
+    std::vector<int32_t> image;
+    if (fill_list_image(p, edges, n_of[0], n_of[1], false, items, &LT, &two, &image)) {
+      // group rows behind the timing rows
+      std::vector<int32_t> rows((kNKinds * kMaxChunks * D + 7) & ~7, 0x10001);
+      for (int kind : {(int)kF, (int)kFD, (int)kB})
+        for (int d = 0; d < D; ++d)
+          for (int c = 0; c < p->n_chunks[d]; ++c) {
+            const int s = p->local_stage[(size_t)d * kMaxChunks + c], dir = kind == kB ? 1 : 0;
+            if (edges[s].in[dir].empty() && edges[s].out[dir].empty()) continue;   // (no slots: the device's own word)
+            rows[(kind * kMaxChunks + c) * D + (d & 1) * ((D + 1) / 2) + d / 2] =
+                grp[s] | (edges[s].in[dir].empty() ? 1 : grp[s]) << 16;
+          }
+      LT.check_wave_bytes = p->ltab.check_wave_bytes;   // (the order pass is launched as for the plain model)
+      const int32_t old_ints = LT.n_time_ints;
+      LT.off_sync = old_ints;
+      LT.n_time_ints += (int32_t)rows.size();
+      LT.off_check += (int32_t)rows.size();
+      LT.off_dev += (int32_t)rows.size();
+      image.insert(image.begin() + old_ints, rows.begin(), rows.end());
+      if (install_list_variant(p, LT, image, two, 1, &p->lists_sync) == FPSCHED_OK) {
+        p->sync_slots_ok = true;
+        return;
+      }
+      (void)hipGetLastError();
+    }
   }
   const int V = p->slot_v, lpc = T.lanes_per_cand;
   const int slot_stride = ((2 * n_classes + 1) * m + 7) & ~7;

@@ -75,7 +75,7 @@ template <int VBITS>   // 0, 1, 2: up to 1, 2, 4 stages per device
 __global__ void check_rows_kernel(ListTables T, const uint16_t* ops, long long n_rows, int stride, int rows_per_wave,
                                   long long* out_info, int* out_peak, unsigned long long* counter,
                                   unsigned long long counter_value, int draw_blocks, int dynamic);
-template <bool DEG2, bool WIDE, bool LINKS, bool MB>
+template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block);

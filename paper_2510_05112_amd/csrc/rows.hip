@@ -30,7 +30,7 @@ typedef unsigned short u16_pair __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned bits_of(u16_pair v) { return __builtin_bit_cast(unsigned, v); }
 __device__ __forceinline__ u16_pair pair_of(unsigned v) { return __builtin_bit_cast(u16_pair, v); }
 
-constexpr unsigned kPadState = 14u;   // state of the byte behind a chunk's last micro-batch: no op requires it
+constexpr unsigned kPadState = 14u;   // state of the bytes behind a chunk's last item: no op requires it
 
 }  // namespace
 
@@ -91,9 +91,14 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   for (int i = lane * 16; i < T.check_wave_bytes; i += 1024) lds_write<lds_int4>(wave_states + i, lds_int4{0, 0, 0, 0});
   const lds_int2 dev = lds_read<lds_int2>(dev_table + (unsigned)d * 8u);
   const int n_chunks = dev.x, cap = dev.y;
-  if (active)
-    for (int c = 0; c < n_chunks; ++c) lds_write<uint8_t>(state + c * (m + 1) + m, (uint8_t)kPadState);
   const unsigned meta = lds0 + (unsigned)d * 8u;
+  // (the items of a chunk's stage stand in its row of kind 0: m, or fewer where an item is a group of micro-batches)
+  auto items_of = [&](unsigned c) -> int { return lds_read<int>(c * row_bytes + meta + 4u); };
+  auto pad = [&](unsigned value) {
+    for (int c = 0; c < n_chunks; ++c)
+      for (int i = items_of((unsigned)c); i <= m; ++i) lds_write<uint8_t>(state + c * (m + 1) + i, (uint8_t)value);
+  };
+  if (active) pad(kPadState);
   int mem = 0, pk = 0;
   unsigned busy = 0u;
   bool alive = active;
@@ -183,7 +188,7 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
       }
       // (an END word ends the list whatever its low bits are)
       if ((stop_word >> 13) != 0u)
-        status = kRowStuck | ((((stop_row >> 8) & 0xffu) == kNoState || (int)(stop_word & 0x7ffu) >= m) ? kRowMalformed : 0u);
+        status = kRowStuck | ((((stop_row >> 8) & 0xffu) == kNoState || (int)(stop_word & 0x7ffu) >= items_of((stop_word >> 11) & 3u)) ? kRowMalformed : 0u);
       stop = at + first_bad;
       alive = false;
     }
@@ -220,8 +225,8 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   if (draw) left = draw_blocks;
   if (block < n_blocks) take(block);
   if (was_active) {
-  // every activation consumed?  (the byte behind each chunk is set to the final state first)
-  for (int c = 0; c < n_chunks; ++c) lds_write<uint8_t>(state + c * (m + 1) + m, (uint8_t)T.terminal);
+  // every activation consumed?  (the bytes behind each chunk's items are set to the final state first)
+  pad((unsigned)T.terminal);
   const unsigned want = (unsigned)T.terminal * 0x01010101u;
   const int n_bytes = n_chunks * (m + 1);
   unsigned differ = 0u;

@@ -41,6 +41,12 @@
 // candidates of 11 devices, 45 micro-batches, 3 chunks: 0.64 + 0.06 ms; 2.01 ms as forms of the slot kernel with all
 // devices in every round and 16 lanes to a candidate.
 //
+// SYNC, stages whose items stand for groups of micro-batches (a synchronisation every n micro-batches, Section 4.2 / 7.2
+// of the paper) and dependency pairs between items of one direction.  An item of a stage with group n waits for the n
+// values of its micro-batches, one slot after the other, taken in like a second input, and leaves its own in the n slots.
+// A pair is an edge of its own slot class in one direction only.  (The host only picks this form when the neighbours of
+// such a stage have one item per micro-batch.)
+//
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
@@ -80,12 +86,13 @@ constexpr unsigned kWindowBytes = 64u * kRingBytes;   // the rings of one half o
 
 }  // namespace
 
-template <bool DEG2, bool WIDE, bool LINKS, bool MB>
+template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC>
 __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block) {
-  static_assert(!WIDE || !(LINKS || MB), "these forms have times of 24 bits");
+  static_assert(!WIDE || !(LINKS || MB || SYNC), "these forms have times of 24 bits");
+  static_assert(!SYNC || !(LINKS || MB), "");
   constexpr unsigned kRowBytes = 16u;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
   extern __shared__ int32_t lds[];
@@ -136,6 +143,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned info;      // what the order pass left for this row: kRow* | stop
     unsigned busy;
     unsigned link_rows, links;   // LINKS: where its devices' link rows are, the lane's link words
+    unsigned sync_rows;          // SYNC: where its devices' group rows are
+    unsigned group, taken;       // SYNC: micro-batches of the item | values it waits for << 16; those taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
     uint4 pend0, pend1;
     int n_pend;         // pieces requested and not landed: pend0, then pend1
@@ -144,6 +153,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   auto idle_device = [&](Device& x) {
     x.R = WIDE ? lds_int4{0, 0, own_at, (int)kWideNever} : lds_int4{1, 0, own_at, 0};
     x.link = 0u;
+    x.group = 0x10001u; x.taken = 0u;
     x.loaded2 = 0x40000000u;
     x.pos2 = 2u;
     x.info = 0u;
@@ -154,6 +164,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     x.win = wave_at + (unsigned)k * kWindowBytes + (unsigned)lane * kRingBytes + (((unsigned)lane >> 3) & 1u) * 16u;
     x.meta = lds0 + (unsigned)(k * P + pair) * kRowBytes;
     x.link_rows = LINKS ? lds0 + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
+    x.sync_rows = SYNC ? lds0 + (unsigned)T.off_sync * 4u + (unsigned)(k * P + pair) * 4u : 0u;
     x.links = LINKS ? wave_at + 2u * kWindowBytes + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
     x.pend0 = make_uint4(0u, 0u, 0u, 0u); x.pend1 = x.pend0;
@@ -177,6 +188,10 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     const unsigned at = __umul24(word >> 11, row_stride) + x.meta;
     x.j_slot = word * kSlotBytes;
     x.R = lds_read<lds_int4>(at);
+    if (SYNC) {
+      x.group = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.sync_rows);
+      x.taken = 0u;
+    }
     if (LINKS) x.link = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.link_rows);
   };
   // address of a byte position in the device's ring
@@ -236,7 +251,15 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   // one step of one half of the devices; returns the lanes that issued
   auto step = [&](Device& x) -> unsigned long long {
     asm volatile("" : "+v"(x.R), "+v"(x.j_slot));   // (the row stays one value until here: no earlier wait for it)
-    const unsigned at_slot = (x.j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
+    unsigned j_slot = x.j_slot, n_slots = 1u;
+    bool more = false;   // the item waits for further values of this input
+    if (SYNC) {
+      const unsigned first_j = __umul24((x.j_slot >> 2) & 0x7ffu, x.group & 0xffffu);
+      n_slots = min(x.group & 0xffffu, (unsigned)T.m - first_j);
+      more = x.taken + 1u < min(x.group >> 16, n_slots);
+      j_slot = (first_j + x.taken) << 2;
+    }
+    const unsigned at_slot = (j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
     unsigned ready, cost_tag = (unsigned)x.R.y, link_free = 0u;
     unsigned long long moved;
     unsigned cost = 0u;
@@ -246,6 +269,9 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       cost = T.mb_bytes == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
       cost_tag = cost << 8 | (cost_tag & 0xffu);
     }
+    // (the second row comes with the slot: read where it is needed, some lane of a wavefront waits for it in most steps)
+    lds_int4 second_r{0, 0, 0, 0};
+    if (DEG2) second_r = lds_read<lds_int4>(second_row(x.R.w));
     if (LINKS) link_free = lds_read<unsigned>(x.links + (x.link & 0xffffu));
     if (WIDE) {
       // the slot's second word is the tag, the row's last one the expected tag (byte 1) and the op's own (byte 0)
@@ -258,17 +284,27 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready), "v"(zero));
     }
     unsigned long long issue = moved;
+    if (SYNC) {
+      const unsigned long long take = moved & __ballot(more);
+      if (take != 0ull) {
+        if (__builtin_amdgcn_inverse_ballot_w64(take)) {
+          x.free_at = max(x.free_at, ready & 0xffffff00u);
+          ++x.taken;
+        }
+        issue &= ~take;
+      }
+    }
     if (DEG2) {
       // an op with two inputs waits for its second one first: once that is there the device's free time takes it in
       // (nothing but the start of this op looks at that time) and the op waits for its first
-      const unsigned long long absorb = moved & __ballot(x.R.w < 0);
+      const unsigned long long absorb = issue & __ballot(x.R.w < 0);
       if (absorb != 0ull) {
         if (__builtin_amdgcn_inverse_ballot_w64(absorb)) {
           x.free_at = max(x.free_at, ready);
-          const lds_int4 first = lds_read<lds_int4>(second_row(x.R.w));
-          x.R.x = first.x;
-          x.R.z = first.y;
-          x.R.w = WIDE ? (x.R.w & 0x7fff00ff) | first.w : x.R.w & 0x7fffffff;
+          x.R.x = second_r.x;
+          x.R.z = second_r.y;
+          x.taken = 0u;
+          x.R.w = WIDE ? (x.R.w & 0x7fff00ff) | second_r.w : x.R.w & 0x7fffffff;
         }
         issue &= ~absorb;
       }
@@ -287,15 +323,24 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         if (WIDE) lds_write<lds_int2>(at, lds_int2{(int)val, x.R.w & 0xff});
         else lds_write<uint32_t>(at, val);
       };
-      leave(at_slot);
+      if (SYNC && n_slots > 1u) {
+        // an item of a group is the value of each of its micro-batches
+        const unsigned first_at = at_slot - (x.taken << 2);
+        for (unsigned k = 0; k < n_slots; ++k) leave(first_at + (k << 2));
+      } else {
+        leave(at_slot);
+      }
       if (DEG2 && ((unsigned)x.R.w & kRowTwoOut) != 0u) {
-        const unsigned second = lds_read<uint32_t>(second_row(x.R.w) + 8u);
+        const unsigned second = (unsigned)second_r.z;
         if (LINKS) {
-          const unsigned link = lds_read<unsigned>(second_row(x.R.w) + 12u);
+          const unsigned link = (unsigned)second_r.w;
           val = max(x.free_at, lds_read<unsigned>(x.links + (link & 0xffffu))) | (cost_tag & 0xffu);
           lds_write<unsigned>(x.links + (link & 0xffffu), (val & 0xffffff00u) + (link >> 16 << 8));
         }
-        leave((x.j_slot & (second >> 16)) + slot_base + (second & 0xffffu));
+        const unsigned second_at = ((j_slot - (SYNC ? x.taken << 2 : 0u)) & (second >> 16)) + slot_base + (second & 0xffffu);
+        leave(second_at);
+        if (SYNC)
+          for (unsigned k = 1; k < n_slots; ++k) leave(second_at + (k << 2));
       }
       decode(x, x.w_next);
       x.pos2 += 2u;
@@ -307,7 +352,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   // Every candidate ends after at most 2 D * stride + 2 rounds (each round but its last issues at least one of its at
   // most D * stride ops, or takes in the second input of one), so the bound below is never reached; it only makes sure the wavefront leaves the loop
   // whatever happens.
-  const unsigned long long bound = (2ull * (unsigned)D * (unsigned)stride + 16ull) * ((unsigned long long)n_cand + 1ull);
+  // (SYNC: an op takes in at most 2 m values)
+  const unsigned long long bound = (2ull * (unsigned)D * (unsigned)stride * (SYNC ? (unsigned long long)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
     land(even);
@@ -438,19 +484,21 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   }
 }
 
-#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB)                                                                     \
-  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB>(ListTables, const uint16_t*, long long, int, long long*, \
+#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC)                                                                     \
+  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC>(ListTables, const uint16_t*, long long, int, long long*, \
                                                                     long long*, int*, unsigned char*, unsigned long long*, int);
-FPSCHED_INSTANTIATE(false, false, false, false)
-FPSCHED_INSTANTIATE(true, false, false, false)
-FPSCHED_INSTANTIATE(false, true, false, false)
-FPSCHED_INSTANTIATE(true, true, false, false)
-FPSCHED_INSTANTIATE(false, false, true, false)
-FPSCHED_INSTANTIATE(true, false, true, false)
-FPSCHED_INSTANTIATE(false, false, false, true)
-FPSCHED_INSTANTIATE(true, false, false, true)
-FPSCHED_INSTANTIATE(false, false, true, true)
-FPSCHED_INSTANTIATE(true, false, true, true)
+FPSCHED_INSTANTIATE(false, false, false, false, false)
+FPSCHED_INSTANTIATE(true, false, false, false, false)
+FPSCHED_INSTANTIATE(false, true, false, false, false)
+FPSCHED_INSTANTIATE(true, true, false, false, false)
+FPSCHED_INSTANTIATE(false, false, true, false, false)
+FPSCHED_INSTANTIATE(true, false, true, false, false)
+FPSCHED_INSTANTIATE(false, false, false, true, false)
+FPSCHED_INSTANTIATE(true, false, false, true, false)
+FPSCHED_INSTANTIATE(false, false, true, true, false)
+FPSCHED_INSTANTIATE(true, false, true, true, false)
+FPSCHED_INSTANTIATE(false, false, false, false, true)
+FPSCHED_INSTANTIATE(true, false, false, false, true)
 #undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched
