@@ -1843,13 +1843,11 @@ static int gen_max_chunks(const fpsched_problem* p) {
 }
 
 // Which sets the segments of a generator launch take first: with more sets than segments the ones with many steps
-// (generate_order_kernel; returns the number of classes), else each segment starts on its own (returns 0).
+// (generate_order_kernel; returns the number of classes), else each segment has its own (returns 0).
 static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const int64_t* d_select, int64_t n_src, int64_t n_sets,
                       int64_t n_segments, uint8_t* d_status, unsigned long long* counter, hipStream_t st) {
-  if (n_sets <= n_segments || n_sets > (1ll << 31)) {
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)n_segments, 0ull);
-    return hipGetLastError() == hipSuccess ? 0 : FPSCHED_EHIP;
-  }
+  if (n_sets <= n_segments) return 0;
+  if (n_sets >= (1ll << 33)) return FPSCHED_EINVAL;   // (more workgroups than a launch has)
   hipLaunchKernelGGL(generate_order_kernel, dim3((unsigned)((n_sets + 3) / 4)), dim3(256), 0, st, p->tables, d_inflight,
                      reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
                      (int)(2 * std::max(gen_max_chunks(p), 1) * p->m), d_status, counter);

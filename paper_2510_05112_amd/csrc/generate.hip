@@ -112,9 +112,9 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 //
 // The grid is persistent: a segment (the lanes of one parameter set) that finishes its schedule
 // writes it out, draws the next set from a global counter and starts over while the other segments
-// of the wavefront keep stepping, so that sets that need few and many steps balance out.  With n_classes = 0 segment g
-// starts on set g; else the counter runs over all sets once per class of generate_order_kernel, and a segment
-// takes those of the class (a status byte that still holds the class and one that has been overwritten since both say what
+// of the wavefront keep stepping, so that sets that need few and many steps balance out.  With n_classes = 0 (no
+// more sets than segments) segment g has set g; else the counter runs over all sets once per class of
+// generate_order_kernel, and a segment takes those of the class (a status byte that still holds the class and one that has been overwritten since both say what
 // is to be done: a set is taken in the pass of its class only).  Sets are drawn one by one: a segment that drew four at a
 // time kept several long ones to itself (14.0 ms instead of 7.9).  A wavefront's priority is that of its longest set.
 //
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
           long long drawn = -1;
           if (d == 0 && has_dev) {
             if (n_classes == 0) {
-              drawn = (long long)atomicAdd(next_set, 1ull);
+              drawn = n_sets;   // (no more sets than segments: each has had its own)
             } else {
               for (;;) {
                 long long q = (long long)atomicAdd(next_set, 1ull);

@@ -90,19 +90,33 @@ def grid(problem, circular: bool, inflight_options=None, forward_first: bool = F
     for all actors, times every in-flight option.  inflight_options: list of int32 [S] arrays
     (default: no limit, and the 1F1B-like limit ceil((p - d) / v) per stage).
     Returns (labels, policy int32 [n][D][8], inflight int32 [n][S])."""
+    D = int(problem.n_devices)
+    if inflight_options is None:
+        inflight_options = _default_inflight(problem)
+    types = schedule_types(D, circular, forward_first)
+    pol, inf = _grid_arrays(types, D, inflight_options)
+    return _grid_labels(types, len(inflight_options)), pol, inf
+
+
+def _default_inflight(problem):
     D, S = int(problem.n_devices), int(problem.n_stages)
     dev = np.asarray(problem.stage_device, np.int64)
-    if inflight_options is None:
-        v = max(1, int(np.bincount(dev, minlength=D).max()))
-        inflight_options = [np.full(S, NO_LIMIT, np.int32), (-(-(D - dev) // v)).astype(np.int32)]
-    types = schedule_types(D, circular, forward_first)
-    labels, pol, inf = [], [], []
-    for t in types:
-        for i, limit in enumerate(inflight_options):
-            labels.append(f"{t.label()} inflight#{i}")
-            pol.append([t.policy_row()] * D)
-            inf.append(np.asarray(limit, np.int32))
-    return labels, np.asarray(pol, np.int32), np.stack(inf).astype(np.int32)
+    v = max(1, int(np.bincount(dev, minlength=D).max()))
+    return [np.full(S, NO_LIMIT, np.int32), (-(-(D - dev) // v)).astype(np.int32)]
+
+
+def _grid_labels(types, n_limits):
+    return [f"{t.label()} inflight#{i}" for t in types for i in range(n_limits)]
+
+
+def _grid_arrays(types, n_devices, inflight_options):
+    """policy int32 [n][D][8] and inflight int32 [n][S] of the schedule types times the in-flight options."""
+    limits = np.asarray([np.asarray(x, np.int32) for x in inflight_options], np.int32)
+    rows = np.asarray([t.policy_row() for t in types], np.int32)
+    n = len(types) * len(limits)
+    pol = np.empty((n, n_devices, 8), np.int32)
+    pol[:] = np.repeat(rows, len(limits), axis=0)[:, None, :]
+    return pol, np.tile(limits, (len(types), 1))
 
 
 def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, forward_first: bool = False,
@@ -119,11 +133,19 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
     (uint16 [D][stride]; the slid list for entries with ``slid`` set)."""
     import torch
 
-    labels, pol, inf = grid(problem, circular, inflight_options, forward_first)
-    n = len(labels)
+    from .binding import FpschedError
+
+    if inflight_options is None:
+        inflight_options = _default_inflight(problem)
+    types = schedule_types(int(problem.n_devices), circular, forward_first)
+    pol, inf = _grid_arrays(types, int(problem.n_devices), inflight_options)
+    n = len(pol)
     stride = stride_for(problem)
+    # (one copy to the device, one back: each costs a grid of this size about as much as a kernel)
+    d_all = torch.from_numpy(np.concatenate([pol.ravel(), inf.ravel()])).cuda()
+    d_pol, d_inf = d_all[:pol.size].view(pol.shape), d_all[pol.size:].view(inf.shape)
     if fused:
-        d_pol, d_inf = torch.from_numpy(pol).cuda(), torch.from_numpy(inf).cuda()
+        labels = _grid_labels(types, len(inflight_options))
         res, _ = handle.generate_evaluate(d_pol, d_inf)
         if slide and problem.has_w:
             slid, _ = handle.generate_evaluate(d_pol, d_inf, slide=True)
@@ -139,18 +161,41 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
             ops = np.where((idx >= n)[:, None, None], handle.wslide(rows, stride)["ops"].cpu().numpy().view(np.uint16), ops)
         return [dict(label=labels[int(i) % n] + (" +slide" if i >= n else ""), makespan=int(t), index=int(i) % n,
                      slid=bool(i >= n), ops=ops[r]) for r, (i, t) in enumerate(zip(idx, ms))]
-    out = handle.generate(torch.from_numpy(pol).cuda(), torch.from_numpy(inf).cuda(), stride)
-    res = handle.evaluate(out["ops"])
-    if slide and problem.has_w:
-        # only the results of the slid lists are ranked: the one-kernel form, which writes no list
-        slid = handle.wslide_evaluate(out["ops"])
-        res = {name: torch.cat([res[name], slid[name]]) for name in ("makespan", "idle", "peak", "flags")}
-    top = handle.topk(res, min(k, 1024))
-    torch.cuda.synchronize()
-    cnt = int(top["count"].item())
-    idx, ms = top["idx"].cpu().numpy()[:cnt], top["makespan"].cpu().numpy()[:cnt]
+    slide = slide and bool(problem.has_w)
+    res = handle.alloc_results(2 * n if slide else n)
+    halves = [{name: t[lo:lo + n] for name, t in res.items()} for lo in ((0, n) if slide else (0,))]
+    try:
+        # Nothing but the results is asked for: the kernels that time the schedules while they generate them, the plain
+        # form and the sliding one side by side (a grid fills a small part of the GPU, and each takes as long as its
+        # longest schedule has steps)
+        if stride > handle.max_stride:
+            raise FpschedError(-1, "fpsched_evaluate")
+        main = torch.cuda.current_stream(handle.device)
+        if slide:
+            side = torch.cuda.Stream(handle.device)
+            side.wait_stream(main)
+            # (what the side stream works with is kept until it is done)
+            side_workspace = handle.alloc_workspace(n, 0)
+            side_out = handle.generate_evaluate(d_pol, d_inf, results=halves[1], workspace=side_workspace, stream=side, slide=True)
+        handle.generate_evaluate(d_pol, d_inf, results=halves[0])
+        if slide:
+            main.wait_stream(side)
+    except FpschedError:
+        # (a cost model or a problem those kernels do not take: through lists in memory)
+        torch.cuda.synchronize()
+        ops = handle.generate(d_pol, d_inf, stride)["ops"]
+        handle.evaluate(ops, halves[0])
+        if slide:
+            # only the results of the slid lists are ranked: the one-kernel form, which writes no list
+            handle.wslide_evaluate(ops, halves[1])
+    k = min(k, 1024)
+    best = torch.empty(2 * k + 1, dtype=torch.int64, device=res["makespan"].device)
+    handle.topk(res, k, out=dict(idx=best[:k], makespan=best[k:2 * k], count=best[2 * k:].view(torch.int32)))
+    labels = _grid_labels(types, len(inflight_options))   # (while the GPU works)
+    best = best.cpu().numpy()
+    cnt = int(best[2 * k:].view(np.int32)[0])
     return [dict(label=labels[int(i) % n] + (" +slide" if i >= n else ""), makespan=int(t), index=int(i) % n,
-                 slid=bool(i >= n)) for i, t in zip(idx, ms)]
+                 slid=bool(i >= n)) for i, t in zip(best[:cnt], best[k:k + cnt])]
 
 
 # ---- shared stages: the weight-gradient synchronisation of the bidirectional placement ----------------
