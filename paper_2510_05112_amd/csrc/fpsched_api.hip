@@ -970,7 +970,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
                         hipMemcpy(p->d_times_ints, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess &&
                         hipFuncSetAttribute(reinterpret_cast<const void*>(slot_kernel_of<kSlotTimes>(p->slot_v, p->slot_deg2, p->stab.n_classes == 1)),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess &&
-                        hipFuncSetAttribute(reinterpret_cast<const void*>(&wslide_place_kernel),
+                        hipFuncSetAttribute(reinterpret_cast<const void*>(p->slot_v > 2 ? &wslide_place_kernel<true> : &wslide_place_kernel<false>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
         if (up) {
           p->stab_times.ints = p->d_times_ints;
@@ -2201,7 +2201,7 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
                      draw_block, starts, stops, (const int32_t*)nullptr, escapes, escape_cap);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   // pass 2: every row places its W items on its own
-  hipLaunchKernelGGL(wslide_place_kernel, dim3((unsigned)place_blocks), dim3(place_threads),
+  hipLaunchKernelGGL(p->slot_v > 2 ? wslide_place_kernel<true> : wslide_place_kernel<false>, dim3((unsigned)place_blocks), dim3(place_threads),
                      (size_t)place_rows_bytes + (place_threads / 64) * kSlideWaveLdsBytes, st, p->stab, d_ops,
                      (long long)n_cand, (int)stride_words,
                      starts, escapes, escape_cap, stops, timed_flags, d_ops_out, (int)stride_out_words,

@@ -125,6 +125,7 @@ __global__ void rank_keys_kernel(const long long* makespan, const long long* idl
 constexpr int kSlideThreads = 1024;
 // dynamic LDS of a workgroup: the metadata rows, then 10 KB per wavefront (windows and stash ring)
 constexpr int kSlideWaveLdsBytes = 14336;
+template <bool FOUR>
 __global__ void wslide_place_kernel(SlotTables T, const uint16_t* ops, long long n_cand, int stride,
                                     const uint32_t* start_low, const uint32_t* escapes, int escape_cap,
                                     const int32_t* stop_pos,

@@ -28,10 +28,11 @@
 // counted); only a stash of more than kStash items, or one of a list whose B items are out of order, is
 // read back from the device's own row, with the latency exposed.
 //
-// What bounds it: instruction issue (150 vector and 110 scalar instructions a step) and, with 11 wavefronts per compute
-// unit, waits for LDS and loads.  32,768 candidates of 16 devices, 64 micro-batches, 2 chunks: 1.2 ms; 2.6 ms with a stash
+// What bounds it: instruction issue and, with 11 wavefronts per compute unit, waits for LDS and loads.  32,768 candidates
+// of 16 devices, 64 micro-batches, 2 chunks: 1.0 ms; 2.6 ms with a stash
 // ring of 16 words, which the lists of every loose in-flight limit overran, rows stored in 16-byte pieces (1.08 GB written
-// instead of 0.50) and six wavefronts to a workgroup.
+// instead of 0.50) and six wavefronts to a workgroup; 1.2 ms with branches and scalar conditions in the step (150 vector and
+// 110 scalar instructions).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -44,13 +45,18 @@ namespace {
 constexpr int kWin = 32;      // window: positions per lane (op words and the low halves of their start times)
 constexpr int kPiece = 16;    // positions per load: 32 bytes of op words, 32 bytes of start times
 constexpr int kRefillAt = 16; // a lane asks for its next piece when at most this many positions are unread
-constexpr unsigned kTopUpMask = 7u;   // the window is topped up every eighth step
 constexpr int kStash = 128;   // stash ring: entries of two bits per lane
 constexpr int kOut = 32;      // staging ring of the new row: words per lane; stored sixteen (32 bytes) at a time
+constexpr int kSteps = 8;     // between two top-ups
+// per-lane conditions that select several values, as masks in vector registers: a select is then one bit-field insert
+__device__ __forceinline__ unsigned mask_of(bool b) { return b ? ~0u : 0u; }
+__device__ __forceinline__ unsigned choose(unsigned mask, unsigned a, unsigned b) { return (a & mask) | (b & ~mask); }
 static_assert((2 * kWin + kStash / 8 + kOut) * 64 * 2 == kSlideWaveLdsBytes, "LDS of one wavefront");
 
 }  // namespace
 
+// FOUR: some device has more than two stages
+template <bool FOUR>
 __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
     SlotTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride,
     const uint32_t* __restrict__ start_low, const uint32_t* __restrict__ escapes, int escape_cap,
@@ -128,7 +134,7 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   unsigned t8 = 0u, busy8 = 0u;   // device free time and busy time, << 8
   unsigned u8 = 0u;               // the device's free time in the list without W items, << 8
   int mem = 0, pk = 0;
-  bool overflow = false, done = !active;
+  bool done = !active;
   // Stash: a B item's W item is known by its chunk as long as the B items of each chunk come in ascending order of their
   // micro-batches (as in every list of the generator): entries [q_head, q_tail) of the ring are those chunks, two bits
   // each, and the micro-batch is a count.  `from_row`: B words from row position refill_pos on are not in the ring (it is
@@ -138,7 +144,7 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   int refill_pos = 0;
   bool from_row = false, out_of_order = false;
   unsigned n_b[2] = {0u, 0u}, n_w[2] = {0u, 0u};   // B items issued, W items placed: chunks 0 and 1, 2 and 3, 16 bits each
-  bool have_head = false;                          // q_word, q_dur8, q_free are those of the oldest stashed item
+  bool have_head = false;      // q_word, q_dur8, q_free are those of the oldest stashed item
   unsigned q_word = 0u, q_dur8 = 0u;   // the oldest stashed item as a W word, its cost and what it frees
   int q_free = 0;
   // cost and freed units of the W item of each chunk of this device (rows kW * 4 + chunk of the metadata)
@@ -150,11 +156,33 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
     w_dur8[c] = (unsigned)Mw.x;
     w_free[c] = (int)(((unsigned)Mw.y >> 8) & 0xffu);
   }
-  auto set_head = [&](unsigned c, unsigned j) {
-    q_word = ((unsigned)kW << 13) | c << 11 | j;
-    q_dur8 = c == 0u ? w_dur8[0] : (c == 1u ? w_dur8[1] : (c == 2u ? w_dur8[2] : w_dur8[3]));
-    q_free = c == 0u ? w_free[0] : (c == 1u ? w_free[1] : (c == 2u ? w_free[2] : w_free[3]));
-    have_head = true;
+  // the oldest stashed item of the lanes in `mask` becomes chunk c, micro-batch j
+  auto set_head = [&](unsigned mask, unsigned c, unsigned j) {
+    const unsigned odd = 0u - (c & 1u);
+    unsigned dur = choose(odd, w_dur8[1], w_dur8[0]), freed = choose(odd, (unsigned)w_free[1], (unsigned)w_free[0]);
+    if (FOUR) {
+      const unsigned upper = 0u - (c >> 1);
+      dur = choose(upper, choose(odd, w_dur8[3], w_dur8[2]), dur);
+      freed = choose(upper, choose(odd, (unsigned)w_free[3], (unsigned)w_free[2]), freed);
+    }
+    q_word = choose(mask, ((unsigned)kW << 13) | c << 11 | j, q_word);
+    q_dur8 = choose(mask, dur, q_dur8);
+    q_free = (int)choose(mask, freed, (unsigned)q_free);
+  };
+  // a counter of chunk c, and its increment
+  auto count_of = [&](const unsigned (&n)[2], unsigned c) -> unsigned {
+    const unsigned word = FOUR ? choose(0u - (c >> 1), n[1], n[0]) : n[0];
+    return (word >> ((c & 1u) << 4)) & 0xffffu;
+  };
+  auto add_one = [&](unsigned (&n)[2], unsigned c, unsigned mask) {
+    const unsigned one = (1u << ((c & 1u) << 4)) & mask;
+    if (FOUR) {
+      const unsigned upper = 0u - (c >> 1);
+      n[0] += one & ~upper;
+      n[1] += one & upper;
+    } else {
+      n[0] += one;
+    }
   };
   // The new row is staged in LDS and stored sixteen words at a time when the window is topped up, behind the loads: lanes
   // fill up at different steps, so stores in the steps are issued in nearly every one, in pieces that the memory has to
@@ -170,112 +198,103 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   // cursor (in the window unless the lane has outrun it: then it waits for the next top-up); the oldest
   // stashed item runs if it ends by the start of that item (or the list is over); else the item issues, or
   // a W word of the input is passed over.
-  for (unsigned step = 0;; ++step) {
-    if ((step & kTopUpMask) == 0u) {
-      if (has_pend) {
-        land();
-        has_pend = false;
-      }
-      if (!done && loaded - pos <= kRefillAt && loaded < stride) {
-        request(loaded);
-        has_pend = true;
-      }
-      if (out_len - stored >= 16) {
-        *reinterpret_cast<uint4*>(out_row + stored) = staged4(stored);
-        *reinterpret_cast<uint4*>(out_row + stored + 8) = staged4(stored + 8);
-        stored += 16;
-      }
-    }
-    const unsigned slot0 = (unsigned)(pos & (kWin - 1)) * 64u, slot1 = (unsigned)((pos + 1) & (kWin - 1)) * 64u;
-    const unsigned e0 = window[slot0], e1 = window[slot1];
-    const unsigned w0 = e0 & 0xffffu;
-    // a W word of the input at the cursor is passed over at once when the word behind it is there as well
-    // (it is never in the escape list: in the first pass it starts the moment its device is free)
-    const bool hop = !done && pos + 1 < min(stop, loaded) && (w0 >> 13) == (unsigned)kW;
-    pos += hop ? 1 : 0;
-    const unsigned e = hop ? e1 : e0;
-    const unsigned w = e & 0xffffu;
-    const unsigned low8 = e >> 16 << 8;
-    const bool have = pos < stop;
-    const bool in_window = pos < loaded;
-    // (any 16-bit value indexes a row of the table: the top five bits of the word)
-    const int2 M = meta[((w >> 11) << lpc_shift) + d];
-    // the start time from its low half and the free time in front of the op, plus what the escape
-    // list says for an op that waited 2^16 time units or more
-    const bool esc_here = (esc >> 8) == (unsigned)pos;
-    const unsigned s8 = u8 + ((low8 - u8) & 0x00ffff00u) + (esc_here ? esc << 24 : 0u);
-    const unsigned kind = w >> 13;
-    const bool word_ok = !done && have && in_window;
-    const bool item = word_ok && kind != (unsigned)kW;   // where the input put its W items is not used
-    const bool skip = word_ok && kind == (unsigned)kW;
-    const bool place = !done && have_head && (have ? (item && t8 + q_dur8 <= s8) : at_end);
-    const bool issue = item && !place;
-    done = done || (!have && !place);
-    if (place || issue) {
-      const unsigned dur8 = place ? q_dur8 : (unsigned)M.x;
-      const unsigned at8 = place ? t8 : s8;
-      if (out_len < stride_out) {
-        put(out_len, place ? q_word : w);
-        ++out_len;
-      } else {
-        overflow = true;   // the row keeps its first stride_out items; the candidate is reported as failed
-      }
-      mem += place ? 0 : (int)((unsigned)M.y & 0xffu);
-      pk = max(pk, mem);
-      mem -= place ? q_free : (int)(((unsigned)M.y >> 8) & 0xffu);
-      t8 = at8 + dur8;
-      busy8 += dur8;
-      if (issue) u8 = t8;   // an item of the list ends when it would without any W item
-    }
-    if (place) {
-      const unsigned c = (q_word >> 11) & 3u, one = 1u << ((c & 1u) * 16u);
-      n_w[0] += c < 2u ? one : 0u;
-      n_w[1] += c < 2u ? 0u : one;
-      have_head = false;
-    }
-    if (issue && kind == (unsigned)kB) {   // an issued B item stashes its W item
-      const unsigned c = (w >> 11) & 3u, half = (c & 1u) * 16u, one = 1u << half;
-      const unsigned count = ((c < 2u ? n_b[0] : n_b[1]) >> half) & 0xffffu;
-      n_b[0] += c < 2u ? one : 0u;
-      n_b[1] += c < 2u ? 0u : one;
-      out_of_order = out_of_order || count != (w & 0x7ffu);
-      // (full: the next entry's word still holds older entries)
-      if (!from_row && (out_of_order || q_tail - (q_head & ~15u) == (unsigned)kStash)) {
-        from_row = true;
-        refill_pos = pos;
-      }
-      if (!from_row) {
-        q_word_in = (q_tail & 15u) == 0u ? c : q_word_in | c << ((q_tail & 15u) * 2u);
-        ring[((q_tail >> 4) & (kStash / 16 - 1)) * 64] = q_word_in;
-        ++q_tail;
-      }
-    }
-    if (!have_head && q_head != q_tail) {
-      const unsigned c = (ring[((q_head >> 4) & (kStash / 16 - 1)) * 64] >> ((q_head & 15u) * 2u)) & 3u;
-      set_head(c, ((c < 2u ? n_w[0] : n_w[1]) >> ((c & 1u) * 16u)) & 0xffffu);
-      ++q_head;
-    } else if (from_row && !have_head) {
-      // the ring is empty and B words wait in the row: the next one, up to the one just issued
-      const int end = pos + (issue ? 1 : 0);
-      while (refill_pos < end) {
-        const unsigned b_word = row[refill_pos++];
-        if ((b_word >> 13) == (unsigned)kB) {
-          set_head((b_word >> 11) & 3u, b_word & 0x7ffu);
-          break;
-        }
-      }
-      from_row = out_of_order || refill_pos < end;
-    }
-    if (issue || skip) {
-      if (esc_here) esc = esc_row[esc_at++];
-      ++pos;
+  for (;;) {
+    if (has_pend) {
+      land();
+      has_pend = false;
     }
     if (__ballot(!done) == 0ull) break;
+    if (!done && loaded - pos <= kRefillAt && loaded < stride) {
+      request(loaded);
+      has_pend = true;
+    }
+    if (out_len - stored >= 16) {
+      // (the row keeps its first stride_out items; the candidate is reported as failed if there are more)
+      if (stored + 8 <= stride_out) *reinterpret_cast<uint4*>(out_row + stored) = staged4(stored);
+      if (stored + 16 <= stride_out) *reinterpret_cast<uint4*>(out_row + stored + 8) = staged4(stored + 8);
+      stored += 16;
+    }
+    const int limit = min(stop, loaded);   // positions in front of it are in the window
+#pragma unroll 2
+    for (int step = 0; step < kSteps; ++step) {
+      const unsigned e0 = window[(unsigned)(pos & (kWin - 1)) * 64u], e1 = window[(unsigned)((pos + 1) & (kWin - 1)) * 64u];
+      const unsigned head_word = ring[((q_head >> 4) & (kStash / 16 - 1)) * 64];
+      // a W word of the input at the cursor is passed over at once when the word behind it is there as well
+      // (it is never in the escape list: in the first pass it starts the moment its device is free)
+      const bool hop = (pos + 1 < limit) & ((e0 & 0xe000u) == ((unsigned)kW << 13));
+      pos += hop ? 1 : 0;
+      const unsigned e = hop ? e1 : e0, w = e & 0xffffu;
+      // (any 16-bit value indexes a row of the table: the top five bits of the word)
+      const int2 M = meta[((w >> 11) << lpc_shift) + d];
+      const bool have = pos < limit, over = pos >= stop;
+      const bool is_w = (w >> 13) == (unsigned)kW;   // where the input put its W items is not used
+      // the start time from its low half and the free time in front of the op, plus what the escape
+      // list says for an op that waited 2^16 time units or more
+      unsigned s8 = u8 + (((e >> 16 << 8) - u8) & 0x00ffff00u);
+      const bool esc_here = (esc >> 8) == (unsigned)pos;
+      s8 += esc_here ? esc << 24 : 0u;
+      const bool item = have & !is_w;
+      const bool place = have_head & ((item & (t8 + q_dur8 <= s8)) | (over & at_end & !done));
+      const bool issue = item & !place;
+      done = done | (over & !place);
+      const unsigned placing = mask_of(place), issuing = mask_of(issue), acting = placing | issuing;
+      put(out_len, choose(placing, q_word, w));   // (a word of a lane that does neither is overwritten by its next one)
+      out_len -= (int)acting;
+      const unsigned dur8 = choose(placing, q_dur8, (unsigned)M.x) & acting;
+      t8 = choose(issuing, s8, t8) + dur8;
+      busy8 += dur8;
+      u8 = choose(issuing, t8, u8);   // an item of the list ends when it would without any W item
+      mem += (int)((unsigned)M.y & 0xffu & issuing);
+      pk = max(pk, mem);
+      mem -= (int)(choose(placing, (unsigned)q_free, ((unsigned)M.y >> 8) & 0xffu) & acting);
+      add_one(n_w, (q_word >> 11) & 3u, placing);
+      have_head = have_head & !place;
+      // an issued B item stashes its W item
+      const bool is_b = issue & ((w >> 13) == (unsigned)kB);
+      const unsigned c = (w >> 11) & (FOUR ? 3u : 1u);
+      bool push = false;
+      if (is_b) {
+        out_of_order = out_of_order | (count_of(n_b, c) != (w & 0x7ffu));
+        add_one(n_b, c, ~0u);
+        // (full: the next entry's word still holds older entries)
+        const bool leave = out_of_order | (q_tail - (q_head & ~15u) == (unsigned)kStash);
+        refill_pos = leave & !from_row ? pos : refill_pos;
+        from_row = from_row | leave;
+        push = !from_row;
+        if (push) {
+          q_word_in = ((q_tail & 15u) == 0u ? 0u : q_word_in) | c << ((q_tail & 15u) * 2u);
+          ring[((q_tail >> 4) & (kStash / 16 - 1)) * 64] = q_word_in;
+        }
+      }
+      const bool waiting = q_head != q_tail;   // (of those in front of this step's)
+      q_tail += push ? 1u : 0u;
+      const bool take = !have_head & (waiting | push);
+      const unsigned head = waiting ? (head_word >> ((q_head & 15u) * 2u)) & (FOUR ? 3u : 1u) : c;
+      set_head(mask_of(take), head, count_of(n_w, head));
+      q_head += take ? 1u : 0u;
+      have_head = have_head | take;
+      if (__ballot(from_row & !have_head) != 0ull && from_row && !have_head) {
+        // the ring is empty and B words wait in the row: the next one, up to the one just issued
+        const int end = pos + (issue ? 1 : 0);
+        while (refill_pos < end) {
+          const unsigned b_word = row[refill_pos++];
+          if ((b_word >> 13) == (unsigned)kB) {
+            set_head(~0u, (b_word >> 11) & 3u, b_word & 0x7ffu);
+            have_head = true;
+            break;
+          }
+        }
+        from_row = out_of_order || refill_pos < end;
+      }
+      const bool advance = have & !place;
+      if (__ballot(esc_here & advance) != 0ull && esc_here && advance) esc = esc_row[esc_at++];
+      pos += advance ? 1 : 0;
+    }
   }
 
   // ---- the rest of the new row: words still staged, then END words up to the stride
   if (active) {
-    int at = out_len;
+    int at = min(out_len, stride_out);
     for (; at & 7; ++at) put(at, 0u);
     for (int i = stored; i < at; i += 8) *reinterpret_cast<uint4*>(out_row + i) = staged4(i);
     for (; at < stride_out; at += 8) *reinterpret_cast<uint4*>(out_row + at) = make_uint4(0u, 0u, 0u, 0u);
@@ -284,7 +303,7 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   const int seg_base = (threadIdx.x & 63) & ~(lpc - 1);
   const unsigned long long seg_mask = (lpc == 64 ? ~0ull : ((1ull << lpc) - 1ull)) << seg_base;
   const int cap = active ? T.ints[T.off_dev + d * T.dev_ints + 1] : 0;
-  const unsigned long long full = __ballot(active && overflow) & seg_mask;
+  const unsigned long long full = __ballot(active && out_len > stride_out) & seg_mask;
   const unsigned long long over = __ballot(active && pk > cap) & seg_mask;
   int ms = active ? (int)(t8 >> 8) : 0;
   for (int off = 1; off < lpc; off <<= 1) ms = max(ms, __shfl_xor(ms, off, 64));
@@ -301,5 +320,10 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
     }
   }
 }
+
+template __global__ void wslide_place_kernel<false>(SlotTables, const uint16_t*, long long, int, const uint32_t*, const uint32_t*, int, const int32_t*,
+                                                    const unsigned char*, uint16_t*, int, long long*, long long*, int*, unsigned char*);
+template __global__ void wslide_place_kernel<true>(SlotTables, const uint16_t*, long long, int, const uint32_t*, const uint32_t*, int, const int32_t*,
+                                                   const unsigned char*, uint16_t*, int, long long*, long long*, int*, unsigned char*);
 
 }  // namespace fpsched
