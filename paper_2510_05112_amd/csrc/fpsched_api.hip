@@ -2014,40 +2014,53 @@ int fpsched_generate_slide_evaluate(const fpsched_problem* p, const fpsched_acto
                                hip_stream, true);
 }
 
-// k smallest (key, index) among the entries whose flag byte is 0: parts, then one workgroup over the parts' survivors
+// The order in which a top-k workgroup walks its batches of elements: every `step`-th of them, about 0.62 of all, so that
+// the first few are spread over the part wherever they stop.
+static unsigned batch_step(unsigned batches) {
+  unsigned step = std::max(1u, batches * 5u / 8u);
+  while (std::gcd(step, batches) != 1u) ++step;
+  return step;   // (at most batches - 1, or 1: no common divisor)
+}
+
+// k smallest (key, index) among the entries whose flag byte is 0: parts, then parts of the parts' survivors, at last one
+// workgroup.  key_buffers: as fpsched_workspace_bytes lays them out.
 static int run_topk(const long long* keys, const unsigned char* flags, int64_t n_cand, int32_t k, bool wide_values,
                     int64_t* d_idx, int64_t* d_key, int32_t* d_count, char* key_buffers, hipStream_t st) {
-  Key* survivors = reinterpret_cast<Key*>(key_buffers);
   long long* f_idx = reinterpret_cast<long long*>(d_idx);
   long long* f_ms = reinterpret_cast<long long*>(d_key);
+  Key* buffer[2] = {reinterpret_cast<Key*>(key_buffers), nullptr};
+  buffer[1] = buffer[0] + std::max<int64_t>(1, (n_cand + kTile - 1) / kTile) * k;
   // Elements a workgroup sorts at a time: twice k at least, so that a sort makes room for as many as there are threads;
   // no more than 1024 unless k needs it (a sort of 2048 takes twice as long), no more than there are.
-  auto threads_for = [&](int64_t n) {
+  auto room_for = [&](int64_t n) {
     int64_t room = 128;
     while (room < 2 * (int64_t)k || (room < n && room < 1024)) room <<= 1;
-    return (unsigned)(room / 2);
+    return room;
   };
-  // Parts: one while a workgroup needs but a few sorts; else as many as leave the second launch about 2048 survivors, and
-  // never more than the buffers (one per kTile candidates) have room for.  Positions within a part are 32 bits.
-  const int64_t tiles = (n_cand + kTile - 1) / kTile;
-  int64_t parts = 1;
-  if (n_cand > kTile) parts = std::clamp<int64_t>(2048 / k, 8, 64);
-  parts = std::max<int64_t>(std::min(parts, tiles), (n_cand >> 31) + 1);
-  const int64_t n_part = (n_cand + parts - 1) / parts;
-  if (parts > 1) {
-    parts = (n_cand + n_part - 1) / n_part;
-    const unsigned threads = threads_for(n_part);
-    hipLaunchKernelGGL(topk_kernel, dim3((unsigned)parts), dim3(threads), threads * 24u, st, keys, flags, (const Key*)nullptr,
-                       (long long)n_cand, (long long)n_part, (int)k, (int)wide_values, survivors, (long long*)nullptr,
-                       (long long*)nullptr, (int*)nullptr);
+  const Key* in = nullptr;
+  int64_t n = n_cand;
+  for (int level = 0;; ++level) {
+    // Parts: one while a workgroup needs but a few sorts; else as many as leave the next launch about 2048 survivors, but
+    // enough that none is longer than kTopkPartRooms sorts' worth (more launches instead of longer ones: each level has
+    // at most 1/16 of the elements of the one before).  At most one part per kTile elements: a level's survivors then fit
+    // their buffer, k per kTile elements.
+    const int64_t most = kTopkPartRooms * room_for(n), tiles = (n + kTile - 1) / kTile;
+    int64_t parts = 1;
+    if (level == 0 ? n > kTile : n > most) parts = std::max(std::min(std::clamp<int64_t>(2048 / k, 8, 64), tiles), (n + most - 1) / most);
+    const int64_t n_part = std::max<int64_t>((n + parts - 1) / parts, 1);
+    parts = std::max<int64_t>((n + n_part - 1) / n_part, 1);
+    if (parts > 0x7fffffffll) return FPSCHED_EINVAL;
+    const unsigned threads = (unsigned)(room_for(n_part) / 2), batches = (unsigned)((n_part + threads - 1) / threads);
+    const bool last = parts == 1;
+    Key* out = buffer[level & 1];
+    hipLaunchKernelGGL(topk_kernel, dim3((unsigned)parts), dim3(threads), threads * 24u, st, keys, flags, in, (long long)n,
+                       (long long)n_part, batches, batch_step(batches), (int)k, (int)wide_values, last ? (Key*)nullptr : out,
+                       last ? f_idx : (long long*)nullptr, last ? f_ms : (long long*)nullptr, last ? d_count : (int*)nullptr);
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
+    if (last) return FPSCHED_OK;
+    in = out;
+    n = parts * k;
   }
-  const int64_t n_last = parts > 1 ? parts * k : n_cand;
-  const unsigned threads = threads_for(n_last);
-  hipLaunchKernelGGL(topk_kernel, dim3(1), dim3(threads), threads * 24u, st, keys, flags,
-                     parts > 1 ? (const Key*)survivors : (const Key*)nullptr, (long long)n_last, (long long)std::max<int64_t>(n_last, 1),
-                     (int)k, (int)wide_values, (Key*)nullptr, f_idx, f_ms, d_count);
-  return check_hip(hipGetLastError());
 }
 
 int fpsched_topk(const fpsched_problem* p, fpsched_results in, int64_t n_cand, int32_t k,

@@ -13,6 +13,7 @@ struct Key {
 };
 constexpr int kTile = 2048;
 constexpr int kTopkThreads = 1024;
+constexpr int kTopkPartRooms = 16;   // most elements of a part of the top-k, in what its workgroup sorts at a time
 
 // dur_mb: nullptr, or costs per micro-batch [kinds][S][m] in device memory that replace the table's.
 __global__ void eval_general_kernel(DevTables T, const uint16_t* ops, long long n_cand, int stride,
@@ -113,7 +114,7 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* inflight, cons
                                       unsigned long long* next_set);
 
 __global__ void topk_kernel(const long long* in_makespan, const unsigned char* in_flags, const Key* in_keys, long long n,
-                            long long n_part, int k, int wide_values, Key* out_keys, long long* final_idx,
+                            long long n_part, unsigned batches, unsigned step, int k, int wide_values, Key* out_keys, long long* final_idx,
                             long long* final_makespan, int* final_count);
 
 __global__ void rank_keys_kernel(const long long* makespan, const long long* idle, const int* peak,

@@ -3,16 +3,22 @@
 // schedules whose bubble ratio is lowest; with fixed total work that is the
 // least makespan).
 //
-// Each workgroup selects the k smallest of its part of the candidates, a second launch of one workgroup the k
-// smallest of what those left (a batch of one part needs one launch).  A workgroup collects candidates in LDS and
-// sorts when the room is used up (block_sort.h); from then on only candidates in front of the k-th of the last sort
-// are collected, of values in random order about k ln(part / first sort) more, so that a part of any length is sorted
-// two or three times.  The index is part of the key, so the result is a pure function of the values and does not
+// Each workgroup selects the k smallest of its part of the candidates, further launches the k smallest of what those left,
+// the last one with one workgroup (a batch of one part needs one launch).  A workgroup collects candidates in LDS and sorts
+// when the room is used up (block_sort.h); from then on only candidates in front of the k-th of the last sort
+// are collected, of values in random order about k ln(part / first sort) more, so that a part is sorted
+// a few times.  The index is part of the key, so the result is a pure function of the values and does not
 // depend on workgroup scheduling.
 //
-// What bounds it: the latency of a few dependent steps on one compute unit (load, sort, launch).  The tree of tile
-// sorts with a barrier after each of 66 stages that was here before took 30 us a level, one for 1,024 candidates and
-// three for 65,536 with k = 128; now 8 us for 1,024 and 2 x 12 us for 65,536.
+// The time must not depend on the order of the values: a search that appends better and better candidates hands in falling
+// ones, of which every element displaces the ones before it.  So a part is not walked from front to back but in strides of
+// about 0.62 of its length (batch_step), which meets the best of a rising or falling sequence within a few
+// batches, and a part has at most kTopkPartRooms times the elements that are sorted at a time, which bounds the sorts for
+// any order.  Walked from the front, in at most 64 parts however large the batch, 1,048,576 values took 116 us (random
+// order) and 702 us (falling) at k = 128, 1.2 ms (either) at k = 1024; now 68 and 75 us, 166 and 94 us.
+//
+// What bounds it: the latency of a few dependent steps on one compute unit (load, sort, launch): 20 us for 4,096
+// candidates, 25 for 262,144 at k = 1, 56 at k = 128, 140 for 16,777,216 at k = 128.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -36,11 +42,12 @@ struct TopkSource {
 };
 
 // Collects the k smallest of elements [first, first + n), ascending, in buf[0 .. *count), and more behind them (all
-// threads get the same *count, at most k).  P = NoPos: the key is value << 32 | position; returns false, in all threads,
-// if some value does not fit.  P = unsigned: the value as an unsigned number in the order of the signed ones.
+// threads get the same *count, at most k).  The elements are walked in `batches` >= n / threads batches of one per
+// thread, `step` batches on at a time (step and batches have no common divisor).  P = NoPos: the key is
+// value << 32 | position; returns false, in all threads, if some value does not fit.  P = unsigned: the value as an unsigned number in the order of the signed ones.
 template <typename P>
-__device__ bool select_smallest(const TopkSource& src, long long first, unsigned n, int k, const SortBuffer<P>& buf,
-                                int* taken, int* misfit, int* count) {
+__device__ bool select_smallest(const TopkSource& src, long long first, unsigned n, unsigned batches, unsigned step, int k,
+                                const SortBuffer<P>& buf, int* taken, int* misfit, int* count) {
   constexpr bool kPacked = std::is_same<P, NoPos>::value;
   const int tid = threadIdx.x, threads = blockDim.x, lane = tid & 63, room = 2 * threads;
   constexpr int kBatch = 4;   // elements per thread on their way at a time
@@ -67,14 +74,17 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
     held = min(held, k);
     sorted = true;
   };
-  int turn = 0;               // the counter of this step; those of the next two are 0 or about to be
-  for (unsigned at = 0; at < n; at += kBatch * threads) {
+  int turn = 0;               // the counter of this try; those of the next two are 0 or about to be
+  unsigned batch = 0;
+  for (unsigned done = 0; done < batches; done += kBatch) {
     SortElem<P> e[kBatch];
     bool have[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      const unsigned pos = at + i * threads + tid;
-      have[i] = pos < n;
+      const unsigned pos = batch * threads + tid;
+      have[i] = done + i < batches && pos < n;
+      batch += step;
+      batch = batch >= batches ? batch - batches : batch;
       long long value = 0;
       if (have[i]) {
         const long long g = first + pos;
@@ -97,24 +107,31 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
     }
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      if (at + i * threads >= n) break;
-      const bool take = have[i] && elem_less(e[i], bar);
-      const unsigned long long takers = __ballot(take);
-      int base = 0;
-      if (lane == 0 && takers != 0ull) base = held + atomicAdd(&taken[turn], __popcll(takers));
-      base = __shfl(base, 0);
-      if (take) buf.put(base + __popcll(takers & ((1ull << lane) - 1ull)), e[i]);
-      __syncthreads();
-      const int more = taken[turn];
-      held += more;
-      sorted = sorted && more == 0;
-      // (read by all before the barrier just passed; in use again two barriers on)
-      const int before = turn == 0 ? 2 : turn - 1;
-      if (tid == 0) taken[before] = 0;
-      turn = turn == 2 ? 0 : turn + 1;
-      if (held + threads > room) sort();
+      if (done + i >= batches) break;
+      for (;;) {
+        const bool take = have[i] && elem_less(e[i], bar);
+        const unsigned long long takers = __ballot(take);
+        int base = 0;
+        if (lane == 0 && takers != 0ull) base = atomicAdd(&taken[turn], __popcll(takers));
+        base = __shfl(base, 0) + held;
+        __syncthreads();
+        const int more = taken[turn];
+        // (read by all before the next barrier; in use again two barriers on)
+        const int before = turn == 0 ? 2 : turn - 1;
+        if (tid == 0) taken[before] = 0;
+        turn = turn == 2 ? 0 : turn + 1;
+        if (held + more <= room) {
+          if (take) buf.put(base + __popcll(takers & ((1ull << lane) - 1ull)), e[i]);
+          held += more;
+          sorted = sorted && more == 0;
+          break;
+        }
+        // no room for what the batch adds: sort, which leaves k <= threads, and look at the batch against the new bar
+        sort();
+      }
     }
   }
+  __syncthreads();
   if (kPacked && *misfit != 0) return false;
   if (!sorted && held > 0) sort();
   *count = held;
@@ -124,11 +141,11 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
 }  // namespace
 
 // One workgroup per part of n_part candidates; the last launch has one workgroup (final_* set) and writes the answer,
-// any other the k survivors of each part, padded with keys behind all real ones.  Dynamic LDS: 12 bytes per element
-// of 2 * blockDim.x >= 2 * k.  wide_values: the caller knows that the values do not fit in 32 bits.
+// any other the k survivors of each part, padded with keys behind all real ones.  batches, step: how a part is walked
+// (select_smallest).  Dynamic LDS: 12 bytes per element of 2 * blockDim.x >= 2 * k.  wide_values: the caller knows that the values do not fit in 32 bits.
 __global__ __launch_bounds__(kTopkThreads) void topk_kernel(
     const long long* __restrict__ in_makespan, const unsigned char* __restrict__ in_flags, const Key* __restrict__ in_keys,
-    long long n, long long n_part, int k, int wide_values, Key* __restrict__ out_keys, long long* __restrict__ final_idx,
+    long long n, long long n_part, unsigned batches, unsigned step, int k, int wide_values, Key* __restrict__ out_keys, long long* __restrict__ final_idx,
     long long* __restrict__ final_makespan, int* __restrict__ final_count) {
   extern __shared__ unsigned long long topk_lds[];
   __shared__ int taken[3], misfit;
@@ -137,10 +154,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(
   const TopkSource src{in_makespan, in_flags, in_keys};
   const SortBuffer<unsigned> wide{topk_lds, reinterpret_cast<unsigned*>(topk_lds + 2 * blockDim.x)};
   int count;
-  const bool packed = !wide_values && select_smallest<NoPos>(src, first, here, k, SortBuffer<NoPos>{topk_lds, nullptr}, taken, &misfit, &count);
+  const bool packed = !wide_values && select_smallest<NoPos>(src, first, here, batches, step, k, SortBuffer<NoPos>{topk_lds, nullptr}, taken, &misfit, &count);
   if (!packed) {
     __syncthreads();
-    select_smallest<unsigned>(src, first, here, k, wide, taken, &misfit, &count);
+    select_smallest<unsigned>(src, first, here, batches, step, k, wide, taken, &misfit, &count);
   }
   for (int i = threadIdx.x; i < k; i += blockDim.x) {
     long long value = kInf, idx = kInf;
