@@ -1842,15 +1842,31 @@ static int gen_max_chunks(const fpsched_problem* p) {
   return max_chunks;
 }
 
-// Which sets the segments of a generator launch take first: with more sets than segments the ones with many steps
-// (generate_order_kernel; returns the number of classes), else each segment has its own (returns 0).
+// How the segments of a generator launch come by their sets.  No more sets than segments: each has its own (returns 0).
+// Else a counter hands out those behind the segments' first ones (returns 1), or, for long sets, all of them class by class,
+// the ones with many steps first (generate_order_kernel; returns the number of classes).  The classes keep a batch from
+// ending on a few sets that were begun late; they cost four draws per set from one counter, some 1e8 a second, where the plain
+// order costs at most one per set.  So they pay where a set's steps, about items per actor x (1 + stages per actor) / 2 at
+// about 1 us each, last as long as the draws of one set per segment, and where a segment has two sets or more
+// (results only: 1.25 or more, if the steps last half as long again).
+// Measured over 2 to 32 devices, 16 to 128 micro-batches, 1 to 4 stages per device, classes and plain order: 36,864 sets of
+// 32 x 64 x 2: 3.92 and 4.66 ms (lists), 16,588 of 32 x 128 x 2, sliding: 5.03 and 6.40 ms, 15,974 of 16 x 128 x 2 (1.3 per
+// segment), sliding: 2.86 and 3.11 ms.  On the other side of the line 55,296 sets of 20 x 30 x 2: 2.57 and 1.86 ms,
+// 65,536 of 8 x 8 x 1: 0.97 and 0.30 ms, 15,974 of 16 x 64 x 2: 1.60 and 1.30 ms (lists), 1.89 and 1.64 ms (sliding).  At the
+// line 33,177 of 16 x 64 x 2: 1.92 and 1.96 ms.
 static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const int64_t* d_select, int64_t n_src, int64_t n_sets,
-                      int64_t n_segments, uint8_t* d_status, unsigned long long* counter, hipStream_t st) {
+                      int64_t n_segments, bool lists, uint8_t* d_status, unsigned long long* counter, hipStream_t st) {
   if (n_sets <= n_segments) return 0;
+  const int64_t chunks = std::max(gen_max_chunks(p), 1), steps = 15 * (p->has_w ? 3 : 2) * chunks * p->m * (1 + chunks);
+  const bool by_class = steps >= n_segments && (n_sets >= 2 * n_segments || (!lists && 2 * steps >= 3 * n_segments && 4 * n_sets >= 5 * n_segments));
+  if (!by_class) {
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)n_segments, 0ull);
+    return hipGetLastError() == hipSuccess ? 1 : FPSCHED_EHIP;
+  }
   if (n_sets >= (1ll << 33)) return FPSCHED_EINVAL;   // (more workgroups than a launch has)
   hipLaunchKernelGGL(generate_order_kernel, dim3((unsigned)((n_sets + 3) / 4)), dim3(256), 0, st, p->tables, d_inflight,
                      reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
-                     (int)(2 * std::max(gen_max_chunks(p), 1) * p->m), d_status, counter);
+                     (int)(2 * chunks * p->m), d_status, counter);
   return hipGetLastError() == hipSuccess ? kGenClasses : FPSCHED_EHIP;
 }
 
@@ -1895,7 +1911,7 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
                           p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-  const int n_classes = order_sets(p, d_inflight, d_select, n_src, n_sets, blocks * cpw, d_status, counter, static_cast<hipStream_t>(hip_stream));
+  const int n_classes = order_sets(p, d_inflight, d_select, n_src, n_sets, blocks * cpw, true, d_status, counter, static_cast<hipStream_t>(hip_stream));
   if (n_classes < 0) return n_classes;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), (size_t)lds_bytes,
                      static_cast<hipStream_t>(hip_stream), tables, reinterpret_cast<const int32_t*>(d_policy),
@@ -1989,7 +2005,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
                           p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-  const int n_classes = order_sets(p, d_inflight, nullptr, n_sets, n_sets, blocks * best_waves * cpw, d_status, counter,
+  const int n_classes = order_sets(p, d_inflight, nullptr, n_sets, n_sets, blocks * best_waves * cpw, false, d_status, counter,
                                    static_cast<hipStream_t>(hip_stream));
   if (n_classes < 0) return n_classes;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * best_waves), (size_t)lds_bytes,

@@ -112,11 +112,14 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 //
 // The grid is persistent: a segment (the lanes of one parameter set) that finishes its schedule
 // writes it out, draws the next set from a global counter and starts over while the other segments
-// of the wavefront keep stepping, so that sets that need few and many steps balance out.  With n_classes = 0 (no
-// more sets than segments) segment g has set g; else the counter runs over all sets once per class of
-// generate_order_kernel, and a segment takes those of the class (a status byte that still holds the class and one that has been overwritten since both say what
-// is to be done: a set is taken in the pass of its class only).  Sets are drawn one by one: a segment that drew four at a
-// time kept several long ones to itself (14.0 ms instead of 7.9).  A wavefront's priority is that of its longest set.
+// of the wavefront keep stepping, so that sets that need few and many steps balance out.  Segment g begins with set g and,
+// with n_classes = 0 (no more sets than segments), has no other; with n_classes = 1 the counter hands out those behind the
+// first ones, all that a wavefront asks for with one atomic.  With more classes the counter runs over all sets
+// once per class of generate_order_kernel from the beginning on, and a segment takes those of the class (a status byte that
+// still holds the class and one that has been overwritten since both say what is to be done: a set is taken in the pass of
+// its class only).  These are drawn one by one: a segment that drew four at a time kept several long ones to itself (14.0 ms
+// instead of 7.9), and so did a wavefront that claimed as many numbers as were likely to hold what it asked for (8.6 instead of
+// 5.3 ms).  A wavefront's priority is that of its longest set.  (fpsched_api.hip, order_sets, says which of the two when.)
 //
 // TIMED: generator and evaluator in one (fpsched_generate_evaluate).  An item is scheduled only
 // after everything it depends on was scheduled in an earlier step, so its start time is known the
@@ -304,7 +307,8 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
 
   // per-set state
   long long set = ((long long)blockIdx.x * waves_per_block + wave) * cpw + seg;   // the first set of a segment is its global index
-  bool first_draw = n_classes == 0;
+  bool first_draw = n_classes <= 1;
+  bool sets_left = n_classes != 0;   // (wave-uniform)
   int set_class = 3;
   bool has_set = false;   // the segment is working on a set (possibly finished and not yet written out)
   bool fresh = true;      // the segment wants its next set
@@ -344,6 +348,29 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   for (unsigned long long look = 0; look < bound; ++look) {
     const unsigned step_0 = (unsigned)look * kStepsPerLook;
     if (__ballot(fresh) != 0ull) {
+      // ---- the next sets of the segments that ask for one (lane 0 of each speaks for it)
+      long long drawn = -1;
+      const bool asks = sets_left && fresh && !first_draw && d == 0 && has_dev;
+      const unsigned long long asking = __ballot(asks);
+      if (asking != 0ull) {
+        if (n_classes == 1) {
+          // (one atomic for all of the wavefront's)
+          unsigned long long first = 0ull;
+          if (lane == 0) first = atomicAdd(next_set, (unsigned long long)__popcll(asking));
+          drawn = (long long)__shfl(first, 0) + __popcll(asking & ((1ull << lane) - 1ull));
+        } else if (asks) {
+          for (;;) {
+            long long q = (long long)atomicAdd(next_set, 1ull);
+            int cls = 0;
+            while (cls < n_classes && q >= n_sets) { q -= n_sets; ++cls; }
+            drawn = n_sets;
+            if (cls == n_classes) break;
+            if (out_status[q] == (unsigned char)(kGenClassMark | cls)) { drawn = q; set_class = cls; break; }
+          }
+        }
+        // (once a draw has come away empty the wavefront's other segments need not go for one)
+        sets_left = __ballot(asks && drawn >= n_sets) == 0ull;
+      }
       // ---- segments that finished write their schedule out and start on the next set
       if (fresh) {
         fresh = false;
@@ -384,23 +411,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
             out_status[set] = (unsigned char)status;
           }
         }
-        if (!first_draw) {
-          long long drawn = -1;
-          if (d == 0 && has_dev) {
-            if (n_classes == 0) {
-              drawn = n_sets;   // (no more sets than segments: each has had its own)
-            } else {
-              for (;;) {
-                long long q = (long long)atomicAdd(next_set, 1ull);
-                int cls = 0;
-                while (cls < n_classes && q >= n_sets) { q -= n_sets; ++cls; }
-                if (cls == n_classes) break;
-                if (out_status[q] == (unsigned char)(kGenClassMark | cls)) { drawn = q; set_class = cls; break; }
-              }
-            }
-          }
-          set = __shfl(drawn, lane - d, 64);
-        }
+        if (!first_draw) set = __shfl(drawn, lane - d, 64);
         first_draw = false;
         has_set = has_dev && set >= 0 && set < n_sets;
         const bool has_row = has_set && has_dev;
@@ -465,7 +476,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
         fresh = has_set && !live;   // nothing to schedule (a bad set, no stages): written out next time round
       }
       if (__ballot(has_set) == 0ull) break;   // every segment of the wavefront is out of work
-      if (n_classes != 0) {
+      if (n_classes > 1) {
         const int longest = __ballot(has_set && set_class == 0) ? 3 : (__ballot(has_set && set_class == 1) ? 2 : (__ballot(has_set && set_class == 2) ? 1 : 0));
         if (longest == 3) __builtin_amdgcn_s_setprio(3);
         else if (longest == 2) __builtin_amdgcn_s_setprio(2);

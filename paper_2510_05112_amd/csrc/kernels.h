@@ -85,8 +85,9 @@ __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n
 __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2 = 0);
 
 // V as above; DEG = bound on the in- and out-degree of a stage (1, 2, or 0 = any).  One wavefront per
-// workgroup, 64 / lanes_per_cand parameter sets per wavefront at a time; next_set: a counter in
-// device memory, preset to the number of segments in the grid, from which segments draw their sets.
+// workgroup, T.gen_sets <= 64 / D parameter sets per wavefront at a time; next_set: a counter in device memory from
+// which segments draw their sets.  n_classes = 0: not looked at, no more sets than segments; 1: preset to the number of
+// segments in the grid; kGenClasses: set to 0 by generate_order_kernel, which has left each set's class in out_status.
 // select: null, or which of the n_src parameter sets each output row takes (outside 0 .. n_src - 1: none).
 // TIMED (DEG 1 or 2 only): the schedules are timed as they are generated and only the results R are
 // written (ops and select unused); workgroups of up to kGenTimedThreads threads.
