@@ -13,6 +13,8 @@ FLAG_DEADLOCK = 1
 FLAG_INCOMPLETE = 2
 FLAG_OVER_CAP = 4
 NKINDS = 8
+ERR_OVERFLOW = -4      # the problem's time bound does not fit
+ERR_UNSUPPORTED = -6   # no kernel takes this problem, cost model or setting
 
 
 class FpschedError(RuntimeError):

@@ -133,7 +133,7 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
     (uint16 [D][stride]; the slid list for entries with ``slid`` set)."""
     import torch
 
-    from .binding import FpschedError
+    from .binding import ERR_OVERFLOW, ERR_UNSUPPORTED, FpschedError
 
     if inflight_options is None:
         inflight_options = _default_inflight(problem)
@@ -164,25 +164,29 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
     slide = slide and bool(problem.has_w)
     res = handle.alloc_results(2 * n if slide else n)
     halves = [{name: t[lo:lo + n] for name, t in res.items()} for lo in ((0, n) if slide else (0,))]
-    try:
-        # Nothing but the results is asked for: the kernels that time the schedules while they generate them, the plain
-        # form and the sliding one side by side (a grid fills a small part of the GPU, and each takes as long as its
-        # longest schedule has steps)
-        if stride > handle.max_stride:
-            raise FpschedError(-1, "fpsched_evaluate")
+    # Nothing but the results is asked for: the kernels that time the schedules while they generate them, the plain
+    # form and the sliding one side by side (a grid fills a small part of the GPU, and each takes as long as its
+    # longest schedule has steps)
+    timed = stride <= handle.max_stride   # (else the list evaluation below refuses the stride)
+    if timed:
         main = torch.cuda.current_stream(handle.device)
-        if slide:
-            side = torch.cuda.Stream(handle.device)
-            side.wait_stream(main)
-            # (what the side stream works with is kept until it is done)
-            side_workspace = handle.alloc_workspace(n, 0)
-            side_out = handle.generate_evaluate(d_pol, d_inf, results=halves[1], workspace=side_workspace, stream=side, slide=True)
-        handle.generate_evaluate(d_pol, d_inf, results=halves[0])
-        if slide:
-            main.wait_stream(side)
-    except FpschedError:
-        # (a cost model or a problem those kernels do not take: through lists in memory)
-        torch.cuda.synchronize()
+        side = torch.cuda.Stream(handle.device) if slide else None
+        try:
+            if slide:
+                side.wait_stream(main)
+                side_workspace = handle.alloc_workspace(n, 0)
+                side_out = handle.generate_evaluate(d_pol, d_inf, results=halves[1], workspace=side_workspace, stream=side, slide=True)
+            handle.generate_evaluate(d_pol, d_inf, results=halves[0])
+        except FpschedError as e:
+            # (a cost model or a problem those kernels do not take: through lists in memory)
+            if e.code not in (ERR_UNSUPPORTED, ERR_OVERFLOW):
+                raise
+            timed = False
+        finally:
+            # whatever comes next, the memory the side stream works with among it, comes after the side stream's work
+            if slide:
+                main.wait_stream(side)
+    if not timed:
         ops = handle.generate(d_pol, d_inf, stride)["ops"]
         handle.evaluate(ops, halves[0])
         if slide:
