@@ -397,8 +397,9 @@ int fpsched_encode(const fpsched_problem *p, const int32_t *kind_stage_mb /* HOS
 int64_t fpsched_validate(const fpsched_problem *p, const uint16_t *h_ops, int64_t n_cand,
                          int32_t stride_words);
 
-/* Introspection (HOST): which kernel variant the handle selected and how many
- * candidates one wavefront carries. */
+/* Introspection (HOST), of the selected evaluation kernel under the plain cost model: lanes of a
+ * wavefront per candidate, candidates per wavefront (their product is at most 64) and bytes of LDS
+ * per wavefront, its share of the tables included. */
 int fpsched_problem_info(const fpsched_problem *p, int32_t *lanes_per_candidate,
                          int32_t *candidates_per_wave, int32_t *lds_bytes_per_wave);
 

@@ -1050,7 +1050,7 @@ int fpsched_problem_info(const fpsched_problem* p, int32_t* lanes_per_candidate,
                          int32_t* candidates_per_wave, int32_t* lds_bytes_per_wave) {
   if (!p) return FPSCHED_EINVAL;
   const bool slots = p->use_slots;
-  if (lanes_per_candidate) *lanes_per_candidate = p->tables.lanes_per_cand;
+  if (lanes_per_candidate) *lanes_per_candidate = slots ? (p->D + 1) / 2 : p->tables.lanes_per_cand;
   if (candidates_per_wave) *candidates_per_wave = slots ? p->ltab.cands_per_wave : p->tables.cands_per_wave;
   if (lds_bytes_per_wave) *lds_bytes_per_wave = slots ? 4 * p->ltab.n_time_ints / std::max(p->time_waves, 1) + p->ltab.wave_bytes : p->lds_bytes;
   return FPSCHED_OK;
