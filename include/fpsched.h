@@ -35,7 +35,9 @@
  *   FPSCHED_GEN_WAVES=n   (fpsched_generate) n resident wavefronts per compute unit, default 24;
  *   FPSCHED_MB_GLOBAL=1   (fpsched_problem_set_microbatch_costs) keep the cost table in device
  *                         memory even where it would fit LDS;
- *   FPSCHED_VERBOSE=1     the two cost-model setters print the kernel form and shape they chose.
+ *   FPSCHED_SYNC_SLOTS=1  (fpsched_problem_set_sync) the one-kernel form of the model even where the
+ *                         two-pass form takes the setting;
+ *   FPSCHED_VERBOSE=1     the cost-model setters print the kernel form and shape they chose.
  */
 #ifndef FPSCHED_H
 #define FPSCHED_H

@@ -1582,7 +1582,7 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
     if (grp[s] > 1)
       for (int t : partners[s]) if (grp[t] != 1) return;
   }
-  if (p->lists_ok && !p->lists_wide) {
+  if (p->lists_ok && !p->lists_wide && !getenv("FPSCHED_SYNC_SLOTS")) {
     // the two-pass evaluation's form, where no stage has more than two edge slots in a direction
     // (classes numbered per direction: a pair has slots in one only)
     std::vector<StageEdges> edges(S);
@@ -1736,6 +1736,8 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
   p->sync_slot_grid = p->n_cu * geo.groups;
   p->sync_slot_lds_bytes = (int32_t)(4ll * (n_shared + (int64_t)geo.waves * geo.wave_ints));
   p->sync_slots_ok = true;
+  if (getenv("FPSCHED_VERBOSE"))
+    fprintf(stderr, "[fpsched] slot kernel, synchronisation: %d x %d wavefronts per compute unit, %d candidates each\n", geo.groups, geo.waves, geo.cands_per_wave);
 }
 
 int fpsched_problem_set_sync(fpsched_problem* p, const int32_t* group, int32_t n_pairs,
