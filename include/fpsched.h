@@ -246,7 +246,8 @@ typedef struct {
 } fpsched_results;
 
 /* Bytes of DEVICE workspace fpsched_evaluate / fpsched_topk need for this batch (>= 256;
- * k may be 0 when only fpsched_evaluate is called).  The workspace must be 16-byte aligned;
+ * k may be 0 when only fpsched_evaluate is called; the general kernel looks at no workspace, and runs
+ * where a problem with times of 2^24 or more or latencies of 2^16 or more comes without one).  The workspace must be 16-byte aligned;
  * the library keeps no other device scratch.  Two calls may share a workspace only if they
  * run one after the other on the same stream. */
 size_t fpsched_workspace_bytes(const fpsched_problem *p, int64_t n_cand, int32_t k);

@@ -1155,7 +1155,10 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     return check_hip(hipGetLastError());
   }
   if (p->links_on && !p->use_slots) return FPSCHED_EUNSUPPORTED;   // the general kernel has no link form
-  if (copy_on_slots || sync_on_slots || (p->use_slots && (!p->mb_set || p->mb_slots_ok))) {
+  // (times or latencies beyond the 24-bit forms: the general kernel, which needs no workspace, takes calls without one)
+  const bool usable_workspace = d_workspace && (reinterpret_cast<uintptr_t>(d_workspace) & 15) == 0 && workspace_bytes >= 256;
+  const bool without_workspace = !usable_workspace && !p->slots_ok && p->general_ok;
+  if (copy_on_slots || sync_on_slots || (p->use_slots && (!p->mb_set || p->mb_slots_ok) && !without_workspace)) {
     // the first 8 bytes of the workspace hold the counter the segments draw candidates from
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
