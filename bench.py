@@ -25,86 +25,70 @@ HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 # int32 vector peak: 256 CUs x 4 SIMDs x 16 lanes, one operation per lane and clock at 2.4 GHz
 # (= the published 157.3 TFLOP/s fp32 vector figure / 4: an FMA counts two, packed issue two more)
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-# Counted figures of ONE launch of each kernel on the default workload, from the rocprofv3 summaries under
-# profiles/ (HBM traffic: FETCH_SIZE / WRITE_SIZE scaled by a copy kernel of known size; vector wavefront
-# instructions: SQ_INSTS_VALU).  They belong to the kernel as it was when the profile was taken:
-# profile_kernel_ms is that run's launch duration, and a live launch that differs from it by more than
-# 10 % means the kernel has changed since -- the counted figures are then left out (null) instead of being
-# carried over.  valu_per_wave_round: vector instructions of one round of the whole wavefront (from the
-# kernel's instruction listing), which turns the instruction count into wavefront-rounds.
-MEASURED = {("cfg4", 65536): {"traffic_bytes": 4.514e9, "valu_wave_instructions": 2.088e9,
-                              "valu_per_wave_round": 33.7, "profile_kernel_ms": 4.884,
-                              "profile": "profiles/eval_slot_kernel_cfg4_counters.md"}}
-# with costs per micro-batch (--mb-costs)
-MEASURED_MB = {("cfg4", 65536): {"traffic_bytes": None, "valu_wave_instructions": 2.694e9,
-                                 "valu_per_wave_round": None, "profile_kernel_ms": 7.32,
-                                 "profile": "profiles/eval_slot_kernel_cfg4_microbatch_costs.md"}}
-# with link occupancy (--links)
-MEASURED_LINKS = {("cfg4", 65536): {"traffic_bytes": None, "valu_wave_instructions": 2.890e9,
-                                    "valu_per_wave_round": None, "profile_kernel_ms": 6.16,
-                                    "profile": "profiles/eval_slot_kernel_cfg4_link_occupancy.md"}}
-# both cost-model variants together (--links --mb-costs)
-MEASURED_BOTH = {("cfg4", 65536): {"traffic_bytes": 3.765e9, "valu_wave_instructions": 3.520e9,
-                                   "valu_per_wave_round": None, "profile_kernel_ms": 8.554,
-                                   "profile": "profiles/eval_slot_kernel_cfg4_links_and_microbatch_costs.md"}}
-# the evaluation with synchronisation stages (--mode sync)
-# the sliding pass without its lists (--mode wslide --no-lists): one launch of the evaluation kernel's sliding mode
-MEASURED_WSLIDE_EVAL = {("cfg4", 65536): {"traffic_bytes": 4.64e9, "valu_wave_instructions": 5.813e9,
-                                          "valu_per_wave_round": None, "profile_kernel_ms": 10.83,
-                                          "profile": "profiles/wslide_kernel_cfg4.md"}}
-MEASURED_SYNC = {("sync4", 65536): {"traffic_bytes": None, "valu_wave_instructions": 5.62e8,
-                                   "valu_per_wave_round": None, "profile_kernel_ms": 1.293,
-                                   "profile": "profiles/eval_sync_kernel.md"}}
-MEASURED_SYNC_TABLE = {("sync4", 65536): {"traffic_bytes": None, "valu_wave_instructions": 1.068e9,
-                                         "valu_per_wave_round": None, "profile_kernel_ms": 7.12,
-                                         "profile": "profiles/eval_sync_kernel.md"}}
-# one generator launch (--mode generate): WRITE_SIZE x 1024 plus the parameter sets read
-MEASURED_GENERATE = {("cfg4", 65536): {"traffic_bytes": 4.83e9, "valu_wave_instructions": 7.945e9,
-                                       "valu_per_wave_round": None, "profile_kernel_ms": 14.67,
-                                       "profile": "profiles/generate_kernel_cfg4.md"}}
-# generator and evaluator in one kernel (--mode search --fused)
-MEASURED_FUSED = {("cfg4", 65536): {"traffic_bytes": None, "valu_wave_instructions": 7.821e9,
-                                    "valu_per_wave_round": None, "profile_kernel_ms": 14.46,
-                                    "profile": "profiles/generate_kernel_cfg4.md"}}
-# the sliding pass (--mode wslide), both of its kernels
-MEASURED_WSLIDE = {("cfg4", 65536): {"traffic_bytes": 4.06e10, "valu_wave_instructions": 5.89e9,
-                                     "valu_per_wave_round": None, "profile_kernel_ms": 18.34,
-                                     "profile": "profiles/wslide_kernel_cfg4.md"}}
+# Counted figures of ONE pass of each path on the default workload (all of its kernels), from the rocprofv3 summaries
+# under profiles/ (HBM traffic: FETCH_SIZE / WRITE_SIZE scaled by a copy kernel of known size; vector wavefront
+# instructions: SQ_INSTS_VALU).  They belong to the kernels as they were when the profile was taken:
+# profile_kernel_ms is that run's duration, and a live one that differs from it by more than
+# 10 % means the kernels have changed since -- the counted figures are then left out (null) instead of being
+# carried over.
 
 
-def rooflines(alg_bytes, kernel_ms, kernel_name, counted, units=None):
+def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
+    return dict(traffic_bytes=traffic_bytes, valu_wave_instructions=valu_wave_instructions,
+                profile_kernel_ms=profile_kernel_ms, profile=f"profiles/{profile}")
+
+
+# the list evaluation (order pass and timing pass): plain, with costs per micro-batch (--mb-costs), with link occupancy
+# (--links), with both
+MEASURED = {("cfg4", 65536): counted(1.664e10, 1.111e9, 3.151, "list_evaluation.md")}
+MEASURED_MB = {("cfg4", 65536): counted(None, 1.426e9, 4.010, "list_evaluation.md")}
+MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.426e9, 3.715, "list_evaluation.md")}
+MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.782e9, 4.916, "list_evaluation.md")}
+# the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
+MEASURED_SYNC = {("sync4", 65536): counted(None, 3.176e8, 1.150, "list_evaluation.md")}
+MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}
+# the copy engine (--config 5 --copy-engine 4)
+MEASURED_COPY = {("cfg5", 131072): counted(None, 1.850e9, 5.106, "eval_sync_kernel.md")}
+# the sliding pass (--mode wslide), both of its kernels, and without its lists (--no-lists): one kernel
+MEASURED_WSLIDE = {("cfg4", 65536): counted(3.38e10, 6.281e9, 16.01, "wslide_kernel_cfg4.md")}
+MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.813e9, 10.74, "wslide_kernel_cfg4.md")}
+# the generator (--mode generate; traffic: WRITE_SIZE x 1024 plus the parameter sets read), generator and evaluator in one
+# kernel (--mode search --fused), the same with the sliding pass in it (--slide)
+MEASURED_GENERATE = {("cfg4", 65536): counted(5.40e9, 7.390e9, 11.77, "generate_kernel_cfg4.md")}
+MEASURED_FUSED = {("cfg4", 65536): counted(None, 7.649e9, 11.00, "generate_kernel_cfg4.md")}
+MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 9.320e9, 13.82, "generate_kernel_cfg4.md")}
+
+
+def rooflines(alg_bytes, kernel_ms, kernel_name, figures, units=None):
     """The roofline object of the JSON line and its sibling.  `roofline` is the HBM view the metric names:
     algorithmic bytes of one launch / the launch duration measured in this run, against 8 TB/s; `traffic`
     is the counted HBM bytes of a launch, or null.  `issue` is the vector-ALU view of the same launch
-    (executed wavefront instructions x 64 lanes against the int32 issue peak), with the share of lane-rounds
-    that evaluated an op where the profile allows to state it; None when no count applies to this run."""
+    (executed wavefront instructions x 64 lanes against the int32 issue peak); None when no count applies to
+    this run."""
     achieved = alg_bytes / (kernel_ms * 1e-3) / 1e9
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": kernel_name,
                 "algorithmic_bytes_per_launch": alg_bytes, "kernel_ms": kernel_ms}
-    if not counted:
+    if not figures:
         roofline["note"] = "no rocprofv3 count was taken for this workload"
         return roofline, None
-    drift = kernel_ms / counted["profile_kernel_ms"] - 1.0
+    drift = kernel_ms / figures["profile_kernel_ms"] - 1.0
     if abs(drift) > 0.10:
-        roofline["note"] = (f"the launch took {kernel_ms:.3f} ms, the profiled kernel {counted['profile_kernel_ms']:.3f} ms "
-                            f"({counted['profile']}): the counted figures belong to another version of the "
+        roofline["note"] = (f"the launch took {kernel_ms:.3f} ms, the profiled kernel {figures['profile_kernel_ms']:.3f} ms "
+                            f"({figures['profile']}): the counted figures belong to another version of the "
                             "kernel and are left out")
         return roofline, None
-    roofline["traffic"] = counted["traffic_bytes"]
-    roofline["traffic_source"] = counted["profile"]
-    tops = counted["valu_wave_instructions"] * 64 / (kernel_ms * 1e-3) / 1e12
+    roofline["traffic"] = figures["traffic_bytes"]
+    roofline["traffic_source"] = figures["profile"]
+    tops = figures["valu_wave_instructions"] * 64 / (kernel_ms * 1e-3) / 1e12
     issue = {"bound": "alu", "achieved": tops, "peak": ALU_PEAK_TOPS,
              "unit": "TOP/s (int32 vector lane slots, waiting and masked lanes included)",
              "frac": tops / ALU_PEAK_TOPS,
-             "vector_wave_instructions_per_launch": counted["valu_wave_instructions"],
-             "source": f"rocprofv3 SQ_INSTS_VALU of one launch on this workload ({counted['profile']}); "
+             "vector_wave_instructions_per_launch": figures["valu_wave_instructions"],
+             "source": f"rocprofv3 SQ_INSTS_VALU of one launch on this workload ({figures['profile']}); "
                        "occupancy of the issue slots, not useful throughput"}
-    if units and counted.get("valu_per_wave_round"):
-        wave_rounds = counted["valu_wave_instructions"] / counted["valu_per_wave_round"]
-        issue["useful_lane_fraction"] = units / (64.0 * wave_rounds)
-        issue["useful_frac_of_peak"] = issue["frac"] * issue["useful_lane_fraction"]
-        issue["vector_wave_instructions_per_unit"] = counted["valu_wave_instructions"] / units
+    if units:
+        issue["vector_wave_instructions_per_unit"] = figures["valu_wave_instructions"] / units
     return roofline, issue
 
 
@@ -201,10 +185,10 @@ def bench_generate(args, spec, threads) -> int:
         # written in full, END padding included: the evaluator reads them as they are), steps and status
         alg_bytes = pol.nbytes + inf.nbytes + words.nbytes + 5 * n
     gen_roofline, gen_issue = rooflines(alg_bytes, gen_ms,
-                                        "fpsched generator kernel, timed form (generate_kernel<.., true>)" if fused
+                                        "fpsched generator kernel, timed form (generate_kernel)" if fused
                                         else "fpsched generator kernel (generate_kernel)",
-                                        None if fused and slide else
-                                        (MEASURED_FUSED if fused else MEASURED_GENERATE).get((f"cfg{spec.index}", n)),
+                                        (MEASURED_FUSED_SLIDE if fused and slide else MEASURED_FUSED if fused
+                                         else MEASURED_GENERATE).get((f"cfg{spec.index}", n)),
                                         units=n_ops)
     json_res = {
         "metric": "schedules generated, evaluated and ranked/sec" if search else "schedules generated/sec",
@@ -454,7 +438,7 @@ def bench_sync(args, threads) -> int:
     alg_bytes = 2 * n_ops + C * (8 + 8 * D + 4 * D + 1)
     on_slots = handle.active_kernel() == "slots"
     roofline, issue = rooflines(alg_bytes, eval_ms,
-                                "fpsched evaluation kernel (eval_slot_kernel, synchronisation mode)" if on_slots
+                                "fpsched evaluation, two passes (check_rows_kernel + time_lists_kernel, synchronisation form)" if on_slots
                                 else "fpsched evaluation kernel for synchronisation stages, table form (eval_sync_kernel)",
                                 (MEASURED_SYNC if on_slots else MEASURED_SYNC_TABLE).get(("sync4", C)), units=n_ops)
     flags = res["flags"].cpu().numpy()
@@ -533,7 +517,7 @@ def main() -> int:
                     help="evaluate mode: offload and reload items run on a copy engine that holds at most DEPTH "
                          "transfers (1..7) instead of the compute timeline; meant for --config 5")
     ap.add_argument("--table-kernel", action="store_true",
-                    help="evaluate and sync modes: the table form of the evaluation kernel instead of the slot kernel")
+                    help="evaluate and sync modes: the table form of the evaluation kernel instead of the forms with mail slots")
     ap.add_argument("--copy-probe", action="store_true",
                     help="also run one plain elementwise copy of the op batch (a kernel of known HBM "
                          "traffic, used to calibrate rocprofv3's FETCH_SIZE / WRITE_SIZE counters)")
@@ -611,7 +595,7 @@ def main() -> int:
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    # K timed steps; HIP events on the launch stream bracket the evaluation kernel of each step
+    # K timed steps; HIP events on the launch stream bracket the evaluation kernels of each step
     ev = [[torch.cuda.Event(enable_timing=True) for _ in range(3)] for _ in range(args.steps)]
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -631,12 +615,13 @@ def main() -> int:
     # algorithmic bytes of one evaluation launch: 2 B per op word actually needed, plus the
     # per-candidate outputs (makespan 8 + idle 8D + peak 4D + flags 1)
     alg_bytes = 2 * n_ops + C * (8 + 8 * D + 4 * D + 1)
-    counted = ({} if args.copy_engine or args.table_kernel else MEASURED_BOTH if args.links and args.mb_costs else MEASURED_LINKS if args.links
-               else MEASURED_MB if args.mb_costs else MEASURED)
+    figures = ({} if args.table_kernel else MEASURED_COPY if args.copy_engine else MEASURED_BOTH if args.links and args.mb_costs
+               else MEASURED_LINKS if args.links else MEASURED_MB if args.mb_costs else MEASURED)
     roofline, issue = rooflines(alg_bytes, eval_ms,
                                 "fpsched evaluation kernel, table form" + (" (eval_sync_kernel, copy-engine form)" if args.copy_engine else " (eval_general_kernel)")
-                                if args.table_kernel else "fpsched evaluation kernel (eval_slot_kernel" + (", copy-engine mode)" if args.copy_engine else ")"),
-                                counted.get((f"cfg{spec.index}", C)), units=n_ops)
+                                if args.table_kernel else "fpsched evaluation kernel (eval_slot_kernel, copy-engine mode)" if args.copy_engine
+                                else "fpsched evaluation, two passes (check_rows_kernel + time_lists_kernel)",
+                                figures.get((f"cfg{spec.index}", C)), units=n_ops)
     flags = res["flags"].cpu().numpy()
     makespan = res["makespan"].cpu().numpy()
     out = {

@@ -22,17 +22,17 @@
  *
  * Ownership and threads.  The caller owns every buffer it passes, the workspaces
  * included; the library owns only the opaque handle and the few KB of tables it
- * uploads when the handle is created (it allocates nothing afterwards, except for the tables
- * of fpsched_problem_set_microbatch_costs and fpsched_problem_set_link_occupancy).  A handle is
- * immutable after creation except for fpsched_problem_select_kernel and those two calls: calls on
+ * uploads when the handle is created (it allocates nothing afterwards, except for the tables of the
+ * four fpsched_problem_set_* calls).  A handle is immutable after creation except for
+ * fpsched_problem_select_kernel and those calls: calls on
  * distinct handles, and calls on one handle that use distinct workspaces and
  * output buffers, may run from different host threads and on different streams.
  * Device calls only enqueue kernels on the given stream and return.
  *
  * Environment variables, read when the call they belong to runs; none changes a result:
- *   FPSCHED_SLOT_WAVES=n  (fpsched_problem_create, the two cost-model setters) at most n wavefronts
- *                         per workgroup of the main evaluation kernel, one workgroup per compute unit;
- *   FPSCHED_GEN_WAVES=n   (fpsched_generate) n resident wavefronts per compute unit, default 24;
+ *   FPSCHED_SLOT_WAVES=n  (fpsched_problem_create, the cost-model setters) at most n wavefronts per
+ *                         workgroup of the evaluation kernels with mail slots, one workgroup per compute unit;
+ *   FPSCHED_GEN_WAVES=n   (the fpsched_generate* calls) n resident wavefronts per compute unit, default 12;
  *   FPSCHED_MB_GLOBAL=1   (fpsched_problem_set_microbatch_costs) keep the cost table in device
  *                         memory even where it would fit LDS;
  *   FPSCHED_SYNC_SLOTS=1  (fpsched_problem_set_sync) the one-kernel form of the model even where the
@@ -155,7 +155,8 @@ int fpsched_problem_set_microbatch_costs(fpsched_problem *p, const int32_t *dur_
  * link for edge_comm and arrives at its end; the values of a device leave in the order its items
  * run (two values of one item: in the order of the edge list).  A consumer is ready when all its
  * inputs have arrived; everything else is unchanged, and with latencies of zero the two models
- * coincide.  on == 0 switches back.  Only the slot kernel has this form: FPSCHED_EUNSUPPORTED if
+ * coincide.  on == 0 switches back.  Only the evaluation with mail slots (FPSCHED_KERNEL_SLOTS, there
+ * the two-pass form) has this model: FPSCHED_EUNSUPPORTED if
  * the problem does not fit it (more than two inputs or outputs per stage, or
  * D * max_stride * (max dur + 2 * max comm) >= 2^24), and from fpsched_evaluate while the general
  * kernel is selected.  Together with costs per micro-batch (either call may come first; the two are
@@ -188,11 +189,13 @@ int fpsched_problem_set_link_occupancy(fpsched_problem *p, int32_t on);
  *     kind (FPSCHED_F also constrains FD).  Pairs that close a cycle make candidates deadlock, which
  *     their flags report.
  * From then on fpsched_evaluate (and fpsched_evaluate_topk_static) time the candidates under this
- * model -- with the slot kernel when every pair runs forward-to-forward or backward-to-backward, no
- * stage has more than two inputs or outputs in a direction (pairs included) and the neighbours of a
- * stage with group > 1 all have group 1, else with a kernel that keeps whole finish-time tables in LDS
- * (fpsched_problem_active_kernel says which; the slot kernel needs the workspace as in the plain
- * model); fpsched_encode and fpsched_validate check micro-batch fields against the item counts.
+ * model -- with mail slots (FPSCHED_KERNEL_SLOTS) when every pair runs forward-to-forward or
+ * backward-to-backward, no stage has more than two inputs or outputs in a direction (pairs included) and
+ * the neighbours of a stage with group > 1 all have group 1: in two passes as in the plain model where an
+ * item's inputs and outputs together need at most two slots (an output that continues an input's chain of
+ * edges shares its slot, a pair has one of its own), else in one kernel.  All other settings run on a
+ * kernel that keeps whole finish-time tables in LDS (fpsched_problem_active_kernel says which; the forms
+ * with mail slots need the workspace as in the plain model); fpsched_encode and fpsched_validate check micro-batch fields against the item counts.
  * (NULL, 0, NULL) switches back.
  * Copied; synchronous (waits for the device's queued work); allocates one table of device memory
  * (FPSCHED_ENOMEM), freed by fpsched_problem_destroy.  FPSCHED_EINVAL for a group < 1, a stage or
@@ -231,8 +234,9 @@ int fpsched_problem_set_sync(fpsched_problem *p, const int32_t *group, int32_t n
  * the tables do not fit LDS or while costs per micro-batch, link occupancy or fpsched_problem_set_sync
  * are in force (and those setters, fpsched_wslide answer FPSCHED_EUNSUPPORTED while this is): the
  * handle keeps what it had.  Synchronous; allocates one table of device memory at most; works on a
- * host-only handle (validation only).  Both evaluation kernels have a form of this model: the slot
- * kernel's runs when the problem fits it (fpsched_problem_select_kernel chooses as for the plain
+ * host-only handle (validation only).  FPSCHED_KERNEL_SLOTS and _GENERAL both have a form of this
+ * model, the former one kernel (no order pass in front) for problems whose times stay below 2^24 and
+ * latencies below 2^16; it runs where it fits (fpsched_problem_select_kernel chooses as for the plain
  * model), and then fpsched_evaluate needs its workspace as in the plain model. */
 #define FPSCHED_MAX_COPY_DEPTH 7
 int fpsched_problem_set_copy_engine(fpsched_problem *p, int32_t depth);
@@ -243,7 +247,8 @@ typedef struct {
   int64_t *idle;     /* [C][D]  makespan - busy time of the device (head/tail included)   */
   int32_t *peak;     /* [C][D]  peak resident activation units                            */
   uint8_t *flags;    /* [C]     FPSCHED_FLAG_* bits                                       */
-} fpsched_results;
+} fpsched_results;   /* (valid once the call's work is done: idle and peak also carry values
+                         from the first evaluation pass to the second) */
 
 /* Bytes of DEVICE workspace fpsched_evaluate / fpsched_topk need for this batch (>= 256;
  * k may be 0 when only fpsched_evaluate is called; the general kernel looks at no workspace, and runs
@@ -335,8 +340,8 @@ int fpsched_rank(const fpsched_problem *p, fpsched_results in, int64_t n_cand, i
  * moves an item of the list), and the candidate is reported as DEADLOCK | INCOMPLETE with
  * the sentinels.  Rows of candidates that fail otherwise hold the items that did issue.
  * The makespan may grow: an item that moves up can open idle time that the stashed items do
- * not fit into; evaluate both lists and rank.  Needs the slot tables (at most two inputs and
- * outputs per stage, see fpsched_problem_info), else FPSCHED_EUNSUPPORTED.  Cost model: the
+ * not fit into; evaluate both lists and rank.  FPSCHED_EUNSUPPORTED if a stage has more than two
+ * inputs or outputs or D * max_stride * (max dur + max comm) >= 2^24 or a latency is 2^16 or more.  Cost model: the
  * handle's latencies as pure latencies or, after fpsched_problem_set_link_occupancy, as links
  * that carry one value at a time; FPSCHED_EUNSUPPORTED while costs per micro-batch are set.
  * Workspace: fpsched_wslide_workspace_bytes (DEVICE, 16-byte aligned; it holds sixteen bits
@@ -356,8 +361,8 @@ int fpsched_wslide(const fpsched_problem *p, const uint16_t *d_ops, int64_t n_ca
  * stashed W items in front of every item they end before.  Same arguments, alignment and
  * errors as fpsched_evaluate; workspace: fpsched_workspace_bytes(p, n_cand, 0) (DEVICE, 16-byte
  * aligned).  Cost model: as for fpsched_wslide (pure latencies, or links that carry one value
- * at a time).  FPSCHED_EINVAL without split backward; FPSCHED_EUNSUPPORTED without the slot
- * tables or while costs per micro-batch, synchronisation stages or the copy engine are set.
+ * at a time).  FPSCHED_EINVAL without split backward; FPSCHED_EUNSUPPORTED for the problems
+ * fpsched_wslide does not take or while costs per micro-batch, synchronisation stages or the copy engine are set.
  * Asynchronous on hip_stream. */
 int fpsched_wslide_evaluate(const fpsched_problem *p, const uint16_t *d_ops, int64_t n_cand,
                             int32_t stride_words, fpsched_results out, void *d_workspace,
@@ -406,19 +411,23 @@ int64_t fpsched_validate(const fpsched_problem *p, const uint16_t *h_ops, int64_
 int fpsched_problem_info(const fpsched_problem *p, int32_t *lanes_per_candidate,
                          int32_t *candidates_per_wave, int32_t *lds_bytes_per_wave);
 
-/* Two evaluation kernels compute the same results.  SLOTS (default whenever its LDS
- * footprint fits): per-micro-batch mail slots, a few KB of LDS per candidate.  GENERAL:
- * whole finish-time tables in LDS, one wavefront per workgroup; kept for problems whose
- * state words do not fit the slot kernel and as a cross-check.  EUNSUPPORTED if the
- * requested kernel does not fit this problem. */
+/* Two ways of evaluating compute the same results.  SLOTS (default wherever the problem fits): an
+ * order pass over every device's list (legality, memory, busy time), then a timing pass with one mail
+ * slot per chain of edges, direction and micro-batch, a few KB of LDS per candidate; times up to 2^31
+ * (slots of two words where 24 bits are not enough).  GENERAL: one kernel with whole finish-time tables
+ * in LDS, one wavefront per workgroup; for problems with more than two inputs or outputs per stage,
+ * more than 255 stages, activations of more than 255 units of memory each (after division by their
+ * greatest common divisor) or more slots than LDS holds, and as a cross-check.  EUNSUPPORTED if the
+ * requested one does not fit this problem. */
 #define FPSCHED_KERNEL_AUTO 0
 #define FPSCHED_KERNEL_GENERAL 1
 #define FPSCHED_KERNEL_SLOTS 2
 int fpsched_problem_select_kernel(fpsched_problem *p, int which);
 /* Which of the two fpsched_evaluate would launch under the handle's present cost model and selection:
- * FPSCHED_KERNEL_SLOTS or FPSCHED_KERNEL_GENERAL (the table form: eval_general_kernel, or eval_sync_kernel
- * under the synchronisation or copy-engine model when the setting does not fit the slot kernel); a negative
- * code for a null or host-only handle. */
+ * FPSCHED_KERNEL_SLOTS (the two passes, or eval_slot_kernel: the copy engine, synchronisation settings the
+ * two passes do not take, costs per micro-batch whose table does not fit LDS) or FPSCHED_KERNEL_GENERAL
+ * (the table form: eval_general_kernel, or eval_sync_kernel under the synchronisation or copy-engine model
+ * when the setting does not fit mail slots); a negative code for a null or host-only handle. */
 int fpsched_problem_active_kernel(const fpsched_problem *p);
 
 /* ---- schedule generator: the actor-aware schedule of Section 5 -------------------------
@@ -467,8 +476,9 @@ typedef struct {
  * in full (END-padded); stride_words a multiple of 8 and >= (most stages on one device)
  * x m x (3 if has_w else 2).  d_steps: DEVICE out int32 [n_sets], scheduling steps taken
  * (the unit-time length of the schedule, bubbles included); d_status: DEVICE out uint8
- * [n_sets], 0 or FPSCHED_GEN_*.  d_workspace: DEVICE, 16-byte aligned, >= 256 bytes (a work
- * counter; the same rules as for fpsched_evaluate).  Asynchronous on hip_stream.
+ * [n_sets], 0 or FPSCHED_GEN_* once the call's work is done (until then the library keeps other
+ * values there, so concurrent calls need arrays of their own).  d_workspace: DEVICE, 16-byte aligned,
+ * >= 256 bytes (a work counter; the same rules as for fpsched_evaluate).  Asynchronous on hip_stream.
  * EUNSUPPORTED if the problem's tables do not fit LDS. */
 int fpsched_generate(const fpsched_problem *p, const fpsched_actor_policy *d_policy,
                      const int32_t *d_inflight, int64_t n_sets, int32_t stride_words,

@@ -1110,9 +1110,13 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   long long* idle = reinterpret_cast<long long*>(out.idle);
   // segment g starts on candidate g, wavefront w of the order pass on block w of rows; the counters hand out those behind
   const unsigned long long first_drawn = (unsigned long long)(time_blocks * cpw * tw);
-  // (about four draws per wavefront even out the last blocks; with as many as there are blocks the counter's address is
-  // what the pass waits for, 1001 instead of 870 us for 262,144 candidates of 16 rows.  A few blocks per wavefront are
-  // shared out equally.)
+  // (About four draws per wavefront even out the last blocks; with as many as there are blocks the counter's address is
+  // what the pass waits for.  Up to eight blocks per wavefront are shared out equally.  Equal shares against draws of one
+  // block, whole evaluation, 32 shapes of 2 to 40 devices with 2 to 31 blocks per wavefront: rows of up to 100 words 59
+  // and 107 us (65,536 candidates of 4 x 8 x 1), 216 and 343 us (262,144 of 3 x 20 x 1); rows of 192 to 1,000 words 322
+  // and 388 us (65,536 of 8 x 32 x 2) at best and 3 % worse at worst; 12 % worse on 24 x 100 x 4, whose rows of 1,200 words
+  // leave room for four wavefronts.  Two, four, eight or sixteen draws beyond eight blocks: within 3 % of each other on
+  // rows of 192 words and more.)
   const int64_t check_waves = check_blocks * cw, per_wave = (row_waves + check_waves - 1) / check_waves;
   const int draw_blocks = (int)(per_wave <= 8 ? per_wave : per_wave / 4);
   const bool dynamic = row_waves > check_waves * draw_blocks;
@@ -1832,8 +1836,11 @@ using GenKernel = void (*)(DevTables, const int32_t*, const int32_t*, const long
                            int32_t*, unsigned char*, unsigned long long*, GenResults);
 static int gen_waves_per_cu() {
   // tuning knob: FPSCHED_GEN_WAVES = resident wavefronts per compute unit.  Three per SIMD: with more, the sets with the
-  // most steps, which all begin at once (order_sets), advance more slowly and are what the launch ends on (32,768 sets
-  // of 16 devices: 1.93 ms with 12, 2.10 with 16, 2.47 with 24; 8 leave the SIMDs idle between steps)
+  // most steps advance more slowly and are what the launch ends on, with fewer the SIMDs are idle between steps (lists,
+  // 33,177 sets of 16 x 64 x 2: 2.00 ms with 8, 1.92 with 12, 2.10 with 16, 2.19 with 24; results only: 2.07, 2.05, 2.16,
+  // 2.43).  8, 12, 16, 20 and 24 measured on 13 problems of 2 to 32 devices: results only, 12 are within 4 % of the best
+  // (11 % on 32 x 128 x 2 without the sliding pass, where 8 are); lists, within 5 % up to 16 devices and 2 stages, but 8
+  // are 8 to 21 % faster for 24 devices or more and for four stages (16,276 sets of 32 x 128 x 2: 4.16 and 5.24 ms).
   int waves_per_cu = 12;
   if (const char* env = getenv("FPSCHED_GEN_WAVES")) {
     const int v = atoi(env);

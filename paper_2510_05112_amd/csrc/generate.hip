@@ -21,8 +21,9 @@
 // limit makes a micro-batch's way through the stages the chain).  So the time is that of the longest sets where they
 // are few, else the vector instructions of a step (a step's LDS latency is hidden by the other wavefronts of a SIMD).
 // 16,384 sets of 32 devices, 2 stages each, 128 micro-batches (2,657 steps a set, 8,884 the longest), sliding form: 9.2 ms
-// before the sets were ordered, the actor's counters moved to registers and the W items out of the steps, 4.9 ms now (76
-// vector instructions a step, 78 % of the issue slots); 32,768 sets of 16 devices, lists written: 2.5 ms before, 1.9 now.
+// before the sets were ordered, the actor's counters moved to registers and the W items out of the steps, 5.0 ms now (87 %
+// of the issue slots); 65,536 sets: 22.1 and 13.8 ms (135 and 106 vector instructions a step, no free issue slot now,
+// profiles/generate_kernel_cfg4.md); 32,768 sets of 16 devices, lists written: 2.5 ms before, 1.9 now.
 // Priorities (Section 5.2; Table of built-in values): computation type traversal priority
 // bwdpass-first / fwdpass-first / interleaved(unit1, unit2); stage traversal priority
 // breadth-first / depth-first with an optional interval, separately for forward and backward
@@ -140,7 +141,7 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 // resident at their starts; so the steps only note each item (its gap: how long the actor waits in front of it) in a ring
 // of kEvents words per lane, and a second loop (settle) places W items into gaps, for all lanes at once and only when
 // some lane's ring is nearly full: its rounds are then full of work, where in the step itself a few lanes' W items
-// would be waited for by all (measured: 127 vector instructions a step with the W items in it, 76 without and some 25 in settle).  The stash is a queue of log2(V) bits per entry
+// would be waited for by all.  The stash is a queue of log2(V) bits per entry
 // (the chunk) in LDS: an actor stashes no more than V * m items, so entry i simply stands in word i * log2(V) / 32.
 template <int V, int DEG, int FORM>
 __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void generate_kernel(

@@ -125,7 +125,7 @@ __global__ void rank_keys_kernel(const long long* makespan, const long long* idl
 // Second kernel of the weight-gradient sliding: one lane per (candidate, device) row places the W
 // items into the idle time in front of the ops timed by eval_slot_kernel<..., kSlotTimes>.
 constexpr int kSlideThreads = 1024;
-// dynamic LDS of a workgroup: the metadata rows, then 10 KB per wavefront (windows and stash ring)
+// dynamic LDS of a workgroup: the metadata rows, then 14 KB per wavefront (windows, stash ring, staged rows)
 constexpr int kSlideWaveLdsBytes = 14336;
 template <bool FOUR>
 __global__ void wslide_place_kernel(SlotTables T, const uint16_t* ops, long long n_cand, int stride,

@@ -50,23 +50,23 @@
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
-// What bounds it: LDS and vector issue, about equally (counters of one launch over 65,536 candidates of 32 devices, 128
-// micro-batches, two chunks: LDS busy 85 % of the time, vector units 73 %).  Everything that does not need the order
+// What bounds it: LDS, vector issue and the fetching of op words (counters of one launch over 65,536 candidates of 32
+// devices, 128 micro-batches, two chunks, profiles/list_evaluation.md: LDS busy 86 % of the time, vector units 67 %, 12.8 GB
+// fetched at 6.2 TB/s for a batch of 3.76 GB).  Everything that does not need the order
 // between devices is the order pass's, which also says where each list stops, so that no word in front of that needs
 // a check.  A step is five vector instructions to decide (the slot's address from the row; an addition that gives the
 // ready time with a low byte that is zero iff the slot carries the expected tag; one byte compare) and nine to issue and
 // to decode the next word; in LDS the slot read (random addresses: half of it bank conflicts), the row, the next word
 // and the slot written.  The row is fetched when the device issues and first looked at in its next step, so the other
 // half's step covers the wait.  That batch took 4.88 ms when one kernel with all devices in every round did the order
-// pass's work as well; now 1.07 ms (rows.hip) + 2.06 ms.
+// pass's work as well; now 1.10 ms (rows.hip) + 2.05 ms.
 //
 // Op words reach a device through a ring of sixteen words in LDS that is topped up every eighth round, eight words at a
 // time, where at most seven are unread.  A device that issues one op per round so never runs dry (it reads the word two
 // behind the one it issues; after every top-up eight or more are unread), and sixteen places hold the words unread, at
 // most fifteen, and the END word that is planted behind a full row.  Words are requested 32 bytes at a time, as soon as
-// the registers they arrive in are free: with the rows of a compute unit's candidates in flight the lines do not stay in
-// the L2 cache from one request to the next, and requests of 16 bytes fetched every line six times (24 GB for a 3.8 GB
-// batch).  (Rings of 32 words leave room for 11 instead of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth
+// the registers they arrive in are free: with the rows of a compute unit's candidates in flight the 128-byte lines mostly
+// do not stay in the L2 cache from one request to the next.  (Rings of 32 words leave room for 11 instead of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth
 // round: 2.19 ms.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
