@@ -15,10 +15,10 @@
 // about 0.62 of its length (batch_step), which meets the best of a rising or falling sequence within a few
 // batches, and a part has at most kTopkPartRooms times the elements that are sorted at a time, which bounds the sorts for
 // any order.  Walked from the front, in at most 64 parts however large the batch, 1,048,576 values took 116 us (random
-// order) and 702 us (falling) at k = 128, 1.2 ms (either) at k = 1024; now 68 and 75 us, 166 and 94 us.
+// order) and 702 us (falling) at k = 128, 1.2 ms (either) at k = 1024; now 68 and 72 us, 172 and 89 us.
 //
 // What bounds it: the latency of a few dependent steps on one compute unit (load, sort, launch): 20 us for 4,096
-// candidates, 25 for 262,144 at k = 1, 56 at k = 128, 140 for 16,777,216 at k = 128.
+// candidates, 24 for 262,144 at k = 1, 55 at k = 128, 136 for 16,777,216 at k = 128.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -75,16 +75,17 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
     sorted = true;
   };
   int turn = 0;               // the counter of this try; those of the next two are 0 or about to be
-  unsigned batch = 0;
+  const unsigned stride = step * threads, wrap = batches * threads;
+  unsigned at = 0;            // the batch's first element
   for (unsigned done = 0; done < batches; done += kBatch) {
     SortElem<P> e[kBatch];
     bool have[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      const unsigned pos = batch * threads + tid;
-      have[i] = done + i < batches && pos < n;
-      batch += step;
-      batch = batch >= batches ? batch - batches : batch;
+      const unsigned pos = at + tid;
+      have[i] = pos < (done + i < batches ? n : 0u);
+      at += stride;
+      at = at >= wrap ? at - wrap : at;
       long long value = 0;
       if (have[i]) {
         const long long g = first + pos;
@@ -105,33 +106,41 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
         e[i].pos = pos;
       }
     }
+    // the elements of a batch in front of the bar: a place for each in lane 0's `base`, and, a barrier later, their number
+    int base = 0;
+    bool take = false;
+    unsigned long long takers = 0ull;
+    auto count = [&](int i) {
+      take = have[i] && elem_less(e[i], bar);
+      takers = __ballot(take);
+      base = 0;
+      if (lane == 0 && takers != 0ull) base = held + atomicAdd(&taken[turn], __popcll(takers));
+    };
+    auto total = [&]() -> int {
+      __syncthreads();
+      const int more = taken[turn];
+      // (read by all before the next barrier; in use again two barriers on)
+      const int before = turn == 0 ? 2 : turn - 1;
+      if (tid == 0) taken[before] = 0;
+      turn = turn == 2 ? 0 : turn + 1;
+      return more;
+    };
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       if (done + i >= batches) break;
-      for (;;) {
-        const bool take = have[i] && elem_less(e[i], bar);
-        const unsigned long long takers = __ballot(take);
-        int base = 0;
-        if (lane == 0 && takers != 0ull) base = atomicAdd(&taken[turn], __popcll(takers));
-        base = __shfl(base, 0) + held;
-        __syncthreads();
-        const int more = taken[turn];
-        // (read by all before the next barrier; in use again two barriers on)
-        const int before = turn == 0 ? 2 : turn - 1;
-        if (tid == 0) taken[before] = 0;
-        turn = turn == 2 ? 0 : turn + 1;
-        if (held + more <= room) {
-          if (take) buf.put(base + __popcll(takers & ((1ull << lane) - 1ull)), e[i]);
-          held += more;
-          sorted = sorted && more == 0;
-          break;
-        }
-        // no room for what the batch adds: sort, which leaves k <= threads, and look at the batch against the new bar
-        sort();
+      // where there may not be room for what the batch adds: sort, which leaves k <= threads, if there is not
+      if (held + threads > room) {
+        count(i);
+        if (held + total() > room) sort();
       }
+      count(i);
+      base = __shfl(base, 0);
+      if (take) buf.put(base + __popcll(takers & ((1ull << lane) - 1ull)), e[i]);
+      const int more = total();
+      held += more;
+      sorted = sorted && more == 0;
     }
   }
-  __syncthreads();
   if (kPacked && *misfit != 0) return false;
   if (!sorted && held > 0) sort();
   *count = held;
