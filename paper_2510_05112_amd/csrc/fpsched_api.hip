@@ -1900,7 +1900,7 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
   const int deg = p->max_degree <= 1 ? 1 : (p->max_degree == 2 ? 2 : 0);
   // tables (if walked), counters and the constant word (a multiple of four), the staging dwords
   auto lds_of = [&](int64_t sets) {
-    return 4ll * ((deg == 0 ? p->tables.n_table_ints : 0) + ((sets * 2 * p->S + 1 + 3) & ~3ll) + kGenStagingWords * 64);
+    return 4ll * ((deg == 0 ? p->tables.n_table_ints : 0) + ((sets * 2 * p->S + 2 + 3) & ~3ll) + kGenStagingWords * 64);
   };
   int cpw = 64 / p->D;
   while (cpw > 1 && lds_of(cpw) > p->max_lds) --cpw;
@@ -1976,7 +1976,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   // (one word more: the word of the next entry is written when all are in as well)
   tables.gen_queue_words = slide && V > 1 ? (int)((int64_t)V * p->m * (V == 2 ? 1 : 2) / 32) + 1 : 0;
   auto wave_ints_of = [&](int64_t sets) {
-    return ((sets * 2 * p->S + 1 + 3) & ~3ll) + sets * p->tables.gen_slot_words +
+    return ((sets * 2 * p->S + 2 + 3) & ~3ll) + sets * p->tables.gen_slot_words +
            (slide ? 64ll * (kGenEvents + tables.gen_queue_words) : 0ll);
   };
   const int64_t lds_ints = p->max_lds / 4;

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   const bool has_w = T.has_w != 0;
   // LDS: [edge lists, only if DEG == 0 | cost rows, only if TIMED: the first halves, then the second halves if they are
   // needed] then per wavefront
-  // [sets of the wavefront: counters [2][S]][a word holding m]
+  // [sets of the wavefront: counters [2][S]][a word holding m][a word: may there be sets left to draw]
   // [row staging: 32 op words per lane, as 16 dwords laid out [dword][lane] | TIMED: the sets' slots, SLIDE: rings, queues]
   const int n_rows = 3 * V * D + 1;
   constexpr bool kSecondHalves = DEG > 1 || FORM == kGenTimed;
@@ -172,13 +172,13 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   } else if (DEG == 0) {
     for (int i = lane; i < n_tab; i += 64) lds[i] = T.ints[i];
   }
-  const int n_count_ints = (cpw * 2 * S + 1 + 3) & ~3;
+  const int n_count_ints = (cpw * 2 * S + 2 + 3) & ~3;
   const int slot_words = T.gen_slot_words;
   const int queue_words = SLIDE ? T.gen_queue_words : 0;   // per lane
   int32_t* counts = lds + n_tab + wave * (n_count_ints + (TIMED ? cpw * slot_words + (SLIDE ? 64 * (kEvents + queue_words) : 0) : kStagingWords * 64));
   // a counter that is always "done" (value m) stands in for a missing neighbour
   const int at_m = cpw * 2 * S;
-  if (lane == 0) counts[at_m] = m;
+  if (lane == 0) { counts[at_m] = m; counts[at_m + 1] = 1; }
   // a lane collects 16 op words (32 bytes) of its row before it stores them: HBM is written in
   // 32-byte pieces, not a quarter of that.  They are stored between the steps: the lanes fill up at different steps, and in
   // most steps some lane would.
@@ -309,7 +309,6 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   // per-set state
   long long set = ((long long)blockIdx.x * waves_per_block + wave) * cpw + seg;   // the first set of a segment is its global index
   bool first_draw = n_classes <= 1;
-  bool sets_left = n_classes != 0;   // (wave-uniform)
   int set_class = 3;
   bool has_set = false;   // the segment is working on a set (possibly finished and not yet written out)
   bool fresh = true;      // the segment wants its next set
@@ -349,29 +348,6 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   for (unsigned long long look = 0; look < bound; ++look) {
     const unsigned step_0 = (unsigned)look * kStepsPerLook;
     if (__ballot(fresh) != 0ull) {
-      // ---- the next sets of the segments that ask for one (lane 0 of each speaks for it)
-      long long drawn = -1;
-      const bool asks = sets_left && fresh && !first_draw && d == 0 && has_dev;
-      const unsigned long long asking = __ballot(asks);
-      if (asking != 0ull) {
-        if (n_classes == 1) {
-          // (one atomic for all of the wavefront's)
-          unsigned long long first = 0ull;
-          if (lane == 0) first = atomicAdd(next_set, (unsigned long long)__popcll(asking));
-          drawn = (long long)__shfl(first, 0) + __popcll(asking & ((1ull << lane) - 1ull));
-        } else if (asks) {
-          for (;;) {
-            long long q = (long long)atomicAdd(next_set, 1ull);
-            int cls = 0;
-            while (cls < n_classes && q >= n_sets) { q -= n_sets; ++cls; }
-            drawn = n_sets;
-            if (cls == n_classes) break;
-            if (out_status[q] == (unsigned char)(kGenClassMark | cls)) { drawn = q; set_class = cls; break; }
-          }
-        }
-        // (once a draw has come away empty the wavefront's other segments need not go for one)
-        sets_left = __ballot(asks && drawn >= n_sets) == 0ull;
-      }
       // ---- segments that finished write their schedule out and start on the next set
       if (fresh) {
         fresh = false;
@@ -412,7 +388,30 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
             out_status[set] = (unsigned char)status;
           }
         }
-        if (!first_draw) set = __shfl(drawn, lane - d, 64);
+        if (!first_draw) {
+          long long drawn = -1;
+          const bool asks = d == 0 && has_dev;
+          const unsigned long long asking = __ballot(asks);
+          if (n_classes == 1) {
+            // (one atomic for all of the wavefront's, which once it has come away empty does not ask again)
+            const int leader = __ffsll((long long)asking) - 1;
+            unsigned long long first = (unsigned long long)n_sets;
+            if (lane == leader && counts[at_m + 1] != 0) {
+              first = atomicAdd(next_set, (unsigned long long)__popcll(asking));
+              if (first >= (unsigned long long)n_sets) counts[at_m + 1] = 0;
+            }
+            drawn = (long long)__shfl(first, leader) + __popcll(asking & ((1ull << lane) - 1ull));
+          } else if (n_classes > 1 && asks) {
+            for (;;) {
+              long long q = (long long)atomicAdd(next_set, 1ull);
+              int cls = 0;
+              while (cls < n_classes && q >= n_sets) { q -= n_sets; ++cls; }
+              if (cls == n_classes) break;
+              if (out_status[q] == (unsigned char)(kGenClassMark | cls)) { drawn = q; set_class = cls; break; }
+            }
+          }
+          set = __shfl(drawn, lane - d, 64);
+        }
         first_draw = false;
         has_set = has_dev && set >= 0 && set < n_sets;
         const bool has_row = has_set && has_dev;
