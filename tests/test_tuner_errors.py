@@ -1,5 +1,7 @@
 """``tuner.tune`` goes through lists where the kernels that time schedules while they generate them do not take the
 problem or the cost model, and only there."""
+import gc
+
 import pytest
 
 from paper_2510_05112_amd import tuner
@@ -11,6 +13,13 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(scope="module")
 def problem():
     return chain(4, 2, 10, "circular")
+
+
+@pytest.fixture(autouse=True)
+def collect():
+    """The caught errors' frames hold device tensors in reference cycles: gone before another test counts allocations."""
+    yield
+    gc.collect()
 
 
 class Refusing:
