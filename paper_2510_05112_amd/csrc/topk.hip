@@ -129,7 +129,7 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
     for (int i = 0; i < kBatch; ++i) {
       if (done + i >= batches) break;
       // where there may not be room for what the batch adds: sort, which leaves k <= threads, if there is not
-      if (held + threads > room) {
+      if (__builtin_expect(held + threads > room, 0)) {
         count(i);
         if (held + total() > room) sort();
       }

@@ -1,5 +1,6 @@
-"""The generator where a batch has more sets than the launch has segments (sets are then taken class by class) on device
-counts that leave lanes of a wavefront over, and the sliding form where stashes and item rings wrap."""
+"""The generator where a batch has more sets than the launch has segments (here in plain order; by class:
+test_gpu_generate_draws.py) on device counts that leave lanes of a wavefront over, and the sliding form where stashes and
+item rings wrap."""
 import numpy as np
 import pytest
 
