@@ -117,6 +117,7 @@ struct SlotTables {
 //     2 byte offset of its slot for micro-batch 0 | mask of the bits of (word << 2) that are added to it << 16
 //     3 if the op has a second input or output: byte offset of a second row | kRowTwoOut | sign bit: two inputs.  An op
 //       with two inputs waits for its second one first: words 0 and 2 are then the second input's.
+//     (problems none of whose ops has a second input or output: 2 the mask, 3 the offset)
 //   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 the
 //     second output's link row in the links form
 //   Wide form (times beyond 24 bits; a slot is two dwords, the time and the tag): word 0 is the latency, word 1 the
@@ -141,7 +142,7 @@ struct ListTables {
   int32_t D, m;
   int32_t cands_per_wave;   // candidates of one wavefront of the timing pass: ceil(D / 2) lanes each
   int32_t cand_slots;       // slots per candidate, a multiple of 4
-  int32_t wave_bytes;       // LDS of one wavefront of the timing pass: op windows, then slots
+  int32_t wave_bytes;       // LDS of one wavefront of the timing pass: op windows, link words, slots
   int32_t n_time_ints;      // timing rows, padded to a multiple of 8
   int32_t off_links;        // links form: link rows, one int per timing row in the same order, in ints
   int32_t link_words;       // links form: words per lane and half (one behind the links for ops that send nothing)

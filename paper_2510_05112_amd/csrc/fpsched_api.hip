@@ -383,6 +383,13 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
           second_at += 4;
         }
       }
+  // (without second rows the last word of a row is free: the slot's mask and offset in a word each)
+  if (!*deg2 && !wide)
+    for (int i = 0; i < kNKinds * kMaxChunks * D; ++i) {
+      int32_t* t = &J[(size_t)i * row_ints];
+      t[3] = t[2] & 0xffff;
+      t[2] = (int32_t)((uint32_t)t[2] >> 16);
+    }
   for (int d = 0; d < D; ++d) {
     J[(size_t)T.off_dev + 2 * d] = p->n_chunks[d];
     J[(size_t)T.off_dev + 2 * d + 1] = (int32_t)(mem_cap[d] / unit_scale);   // peak > cap  <=>  peak / scale > floor(cap / scale)

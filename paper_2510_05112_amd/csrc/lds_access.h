@@ -9,7 +9,8 @@ namespace fpsched {
 #define FPSCHED_LDS __attribute__((address_space(3)))
 template <class T>
 __device__ __forceinline__ T lds_read(unsigned a) {
-  return *reinterpret_cast<const FPSCHED_LDS T*>(a);
+  typedef T access __attribute__((may_alias));   // (rings and states are written in dwords and read in halves or bytes)
+  return *reinterpret_cast<const FPSCHED_LDS access*>(a);
 }
 typedef int lds_int4 __attribute__((ext_vector_type(4)));
 typedef int lds_int3 __attribute__((ext_vector_type(3)));
@@ -26,7 +27,8 @@ __device__ __forceinline__ int2 lds_read<int2>(unsigned a) {
 }
 template <class T>
 __device__ __forceinline__ void lds_write(unsigned a, T v) {
-  *reinterpret_cast<FPSCHED_LDS T*>(a) = v;
+  typedef T access __attribute__((may_alias));
+  *reinterpret_cast<FPSCHED_LDS access*>(a) = v;
 }
 __device__ __forceinline__ unsigned lds_address(const void* p) {
   return (unsigned)(size_t)(const FPSCHED_LDS char*)p;

@@ -50,24 +50,27 @@
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
-// What bounds it: LDS, vector issue and the fetching of op words (counters of one launch over 65,536 candidates of 32
-// devices, 128 micro-batches, two chunks, profiles/list_evaluation.md: LDS busy 86 % of the time, vector units 67 %, 12.8 GB
-// fetched at 6.2 TB/s for a batch of 3.76 GB).  Everything that does not need the order
+// What bounds it: LDS and vector issue (busy 85 and 81 % of the time; one launch over 65,536 candidates of
+// 32 devices, 128 micro-batches, two chunks, profiles/list_evaluation.md).  Everything that does not need the order
 // between devices is the order pass's, which also says where each list stops, so that no word in front of that needs
-// a check.  A step is five vector instructions to decide (the slot's address from the row; an addition that gives the
+// a check.  A step is four vector instructions to decide (the slot's address from the row; an addition that gives the
 // ready time with a low byte that is zero iff the slot carries the expected tag; one byte compare) and nine to issue and
 // to decode the next word; in LDS the slot read (random addresses: half of it bank conflicts), the row, the next word
 // and the slot written.  The row is fetched when the device issues and first looked at in its next step, so the other
 // half's step covers the wait.  That batch took 4.88 ms when one kernel with all devices in every round did the order
-// pass's work as well; now 1.10 ms (rows.hip) + 2.05 ms.
+// pass's work as well; then 1.10 ms (rows.hip) + 2.05 ms; the pass takes 1.68 ms since the step of the plain form is
+// without branches (FPSCHED_STEP below: half of the gain), the rings are read without bank conflicts and requests are
+// twice as large.
 //
 // Op words reach a device through a ring of sixteen words in LDS that is topped up every eighth round, eight words at a
 // time, where at most seven are unread.  A device that issues one op per round so never runs dry (it reads the word two
 // behind the one it issues; after every top-up eight or more are unread), and sixteen places hold the words unread, at
-// most fifteen, and the END word that is planted behind a full row.  Words are requested 32 bytes at a time, as soon as
-// the registers they arrive in are free: with the rows of a compute unit's candidates in flight the 128-byte lines mostly
-// do not stay in the L2 cache from one request to the next.  (Rings of 32 words leave room for 11 instead of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth
-// round: 2.19 ms.)
+// most fifteen, and the END word that is planted behind a full row.  The ring of a lane is a column of dwords in a bank of
+// its own: read in lanes' own 32 bytes, some eight lanes shared their banks (6.6 clocks a read instead of 2.2).  Words are
+// requested 64 bytes (other forms: 32) at a time, as soon as the registers they arrive in are free: with the rows of a
+// compute unit's candidates in flight the 128-byte lines mostly do not stay in the L2 cache from one request to the next
+// (12.8 GB fetched for that batch of 3.76 GB with 32 bytes, 6.9 with 64).  (Rings of 32 words leave room for 11 instead
+// of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth round: 2.19 ms.  Loads that bypass L2: 2.8 ms.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -79,12 +82,58 @@ namespace fpsched {
 namespace {
 
 constexpr unsigned kRounds = 8;          // rounds (a step of either half) between two top-ups
-constexpr unsigned kRingBytes = 32u;     // ring of sixteen words
-constexpr unsigned kPieceBytes = 16u;    // what is landed at a time; a request is two of them
-constexpr unsigned kLandAt = 16u;        // land where at most seven words are unread: loaded - cursor <= 16 bytes
-constexpr unsigned kWindowBytes = 64u * kRingBytes;   // the rings of one half of a wavefront's devices
+constexpr unsigned kWindowBytes = 64u * 32u;   // the rings (sixteen words) of one half of a wavefront's devices, [dword][lane]
+// Positions in a list and in its ring: the dword from bit 8 on (256 bytes are a dword of all lanes), the half of the dword
+// in bit 1; what stands in the bits between is not looked at.
+constexpr unsigned kPosMask = 0x702u;    // of a position: its place in the ring
+constexpr unsigned kPosBetween = 0xfcu;
+constexpr unsigned kPiece = 4u << 8;     // what is landed at a time: eight words, 16 bytes
+constexpr unsigned kNoList = 0x40000000u;
+__device__ __forceinline__ unsigned position_of(unsigned word) { return word >> 1 << 8 | (word & 1u) << 1; }
+__device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1 | (pos >> 1 & 1u); }
 
 }  // namespace
+
+// One step of one half of the devices in the plain form (X, Y: this half and the other one; RX, RY, RW: registers of the
+// words of this half's row, OZ, OW: of the last two of the other's).  As written by the compiler a step has a branch around
+// what the issuing lanes do, and waits in front of its decision for all that the step before it has requested; here
+//   - the decision becomes the execution mask itself, and nothing branches;
+//   - the slots that this half writes are the only thing the other half's read of its slots has to follow, so that read is
+//     made before this half's issued ops give way to the next ones, and their rows and words are on their way while the
+//     other half decides.
+// In flight at the beginning, oldest first: this half's slot, the other half's row and the word behind it.
+#define FPSCHED_STEP(X, Y, X_ROW, Y_ROW, RX, RY, RW, READ_AHEAD)                                                          \
+  asm volatile(                                                                                                          \
+      "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
+      "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
+      "v_cmpx_eq_u32_sdwa %[moved], %[in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                                   \
+      "v_max_u32 %[t], %[free], %[in]\n\t"                                                                              \
+      "v_add_u32 %[t], %[t], v" RY "\n\t"                                                                               \
+      "ds_write_b32 %[at], %[t]\n\t"                                                                                    \
+      "v_and_b32 %[free], 0xffffff00, %[t]\n\t"                                                                         \
+      "s_mov_b64 exec, -1\n\t" READ_AHEAD                                                                               \
+      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
+      "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
+      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
+      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
+      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
+      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
+      "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
+      "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
+      "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
+      "s_mov_b64 exec, -1"                                                                                               \
+      : [in] "+v"(X##_in), [at] "+v"(X##_at), [free] "+v"(X.free_at), [next] "+v"(X.w_next), [j] "+v"(X.j_slot),         \
+        [pos] "+v"(X.pos), [t] "=&v"(scratch), [moved] "=&s"(moved_##X), [row] "+{" X_ROW "}"(X.R),                      \
+        [other_row] "+{" Y_ROW "}"(Y.R), [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot),     \
+        [other_next] "+v"(Y.w_next)                                                                                      \
+      : [zero] "v"(0u), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),           \
+        [slots] "v"(slot_base)                                                                                           \
+      : "memory")
+#define FPSCHED_READ_AHEAD(OZ, OW)                                                                                       \
+  "s_waitcnt lgkmcnt(1)\n\t"                                                                                            \
+  "v_and_b32 %[other_at], %[other_j], v" OZ "\n\t"                                                                      \
+  "v_add3_u32 %[other_at], %[other_at], v" OW ", %[slots]\n\t"                                                          \
+  "ds_read_b32 %[other_in], %[other_at]\n\t"
 
 template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC>
 __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
@@ -94,19 +143,24 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   static_assert(!WIDE || !(LINKS || MB || SYNC), "these forms have times of 24 bits");
   static_assert(!SYNC || !(LINKS || MB), "");
   constexpr unsigned kRowBytes = 16u;
+  constexpr bool PLAIN = !DEG2 && !WIDE && !LINKS && !MB && !SYNC;
+  constexpr bool SPLIT = !DEG2 && !WIDE;   // rows with the slot's mask and offset in a word each
+  // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
+  constexpr int kPieces = PLAIN ? 4 : 2;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
-  for (int i = tid; i < T.n_time_ints; i += blockDim.x) lds[i] = T.ints[i];
-  const unsigned lds0 = lds_address(lds);
+  // LDS: [op windows of all wavefronts][tables][per wavefront: link words, slots]
+  const unsigned lds0 = lds_address(lds), tables = lds0 + (blockDim.x >> 6) * (unsigned)kTimeWindowBytes;
+  for (int i = tid; i < T.n_time_ints; i += blockDim.x) lds_write<int>(tables + (unsigned)i * 4u, T.ints[i]);
   const int seg = lane / P, pair = lane - seg * P;
   const bool lane_ok = seg < cpw;
   const int d0 = 2 * pair;
   const bool has_odd = d0 + 1 < D;
-  const unsigned wave_at = lds0 + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)T.wave_bytes;
+  const unsigned wave_at = tables + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)(T.wave_bytes - kTimeWindowBytes);
   const unsigned links_bytes = LINKS ? (unsigned)T.link_words * 512u : 0u;   // of the wavefront: [half][link][lane]
-  unsigned slot_base = wave_at + 2u * kWindowBytes + links_bytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * kSlotBytes;
+  unsigned slot_base = wave_at + links_bytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * kSlotBytes;
   asm volatile("" : "+v"(slot_base));   // one register, not a sum to be re-associated every round
   const unsigned own_word = slot_base + (unsigned)(lane_ok ? d0 : 0) * kSlotBytes;
   const int own_at = (lane_ok ? d0 : 0) * (int)kSlotBytes;   // that word as a row's slot field
@@ -129,7 +183,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   };
 
   const unsigned row_stride = (unsigned)D * kRowBytes;
-  const unsigned stride2 = (unsigned)stride * 2u;
+  const unsigned stride2 = (unsigned)stride * 2u, stride_pos = position_of((unsigned)stride);
 
   // one device of the lane: its op window, and the op under its cursor, decoded.  A device without an op looks at its
   // own word with an L that keeps it waiting.
@@ -138,36 +192,35 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned free_at;       // narrow: << 8
     unsigned j_slot, w_next;   // the word under the cursor times the bytes of a slot, and the word behind it
     lds_int4 R;             // the op's table row: L, dur | tag, slot, second edge
-    unsigned loaded2;   // bytes of the row that are in the ring (a device without a list asks for none)
-    unsigned pos2;      // byte position of w_next; the device has issued pos2 / 2 - 1 ops
+    unsigned loaded;    // position up to which the row has been in the ring (kNoList: no list, or all of it)
+    unsigned asked;     // ... up to which it has been requested
+    unsigned pos;       // position of w_next; the device has issued one op less than words in front of it
     unsigned info;      // what the order pass left for this row: kRow* | stop
     unsigned busy;
     unsigned link_rows, links;   // LINKS: where its devices' link rows are, the lane's link words
     unsigned sync_rows;          // SYNC: where its devices' group rows are
     unsigned group, taken;       // SYNC: micro-batches of the item | values it waits for << 16; those taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
-    uint4 pend0, pend1;
-    int n_pend;         // pieces requested and not landed: pend0, then pend1
+    uint4 pend[kPieces];   // what has been requested and is not in the ring, in order
   };
   Device even, odd;
   auto idle_device = [&](Device& x) {
-    x.R = WIDE ? lds_int4{0, 0, own_at, (int)kWideNever} : lds_int4{1, 0, own_at, 0};
+    x.R = WIDE ? lds_int4{0, 0, own_at, (int)kWideNever} : (SPLIT ? lds_int4{1, 0, 0, own_at} : lds_int4{1, 0, own_at, 0});
     x.link = 0u;
     x.group = 0x10001u; x.taken = 0u;
-    x.loaded2 = 0x40000000u;
-    x.pos2 = 2u;
+    x.loaded = kNoList;
+    x.asked = 0u;
+    x.pos = position_of(1u);
     x.info = 0u;
-    x.n_pend = 0;
   };
   auto set_up = [&](Device& x, int k) {
-    // (lanes eight apart share their banks: the halves of their rings are in different orders)
-    x.win = wave_at + (unsigned)k * kWindowBytes + (unsigned)lane * kRingBytes + (((unsigned)lane >> 3) & 1u) * 16u;
-    x.meta = lds0 + (unsigned)(k * P + pair) * kRowBytes;
-    x.link_rows = LINKS ? lds0 + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
-    x.sync_rows = SYNC ? lds0 + (unsigned)T.off_sync * 4u + (unsigned)(k * P + pair) * 4u : 0u;
-    x.links = LINKS ? wave_at + 2u * kWindowBytes + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
+    x.win = lds0 + (unsigned)wave * (unsigned)kTimeWindowBytes + (unsigned)k * kWindowBytes + (unsigned)lane * 4u;
+    x.meta = tables + (unsigned)(k * P + pair) * kRowBytes;
+    x.link_rows = LINKS ? tables + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
+    x.sync_rows = SYNC ? tables + (unsigned)T.off_sync * 4u + (unsigned)(k * P + pair) * 4u : 0u;
+    x.links = LINKS ? wave_at + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
-    x.pend0 = make_uint4(0u, 0u, 0u, 0u); x.pend1 = x.pend0;
+    for (int i = 0; i < kPieces; ++i) x.pend[i] = make_uint4(0u, 0u, 0u, 0u);
     idle_device(x);
   };
   set_up(even, 0);
@@ -194,61 +247,74 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     }
     if (LINKS) x.link = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.link_rows);
   };
-  // address of a byte position in the device's ring
-  auto in_ring = [&](const Device& x, unsigned at2) -> unsigned {
-    return __builtin_amdgcn_bitop3_b32(at2, kRingBytes - 1u, x.win, 0x6a);   // (at2 & mask) ^ win
+  // address of a position in the device's ring (the windows of a wavefront begin at a multiple of their size)
+  auto in_ring = [&](const Device& x, unsigned pos) -> unsigned {
+    return __builtin_amdgcn_bitop3_b32(pos, kPosMask, x.win, 0x6a);   // (pos & mask) ^ win
   };
   auto store_piece = [&](Device& x) {
-    lds_write<lds_int4>(in_ring(x, x.loaded2), lds_int4{(int)x.pend0.x, (int)x.pend0.y, (int)x.pend0.z, (int)x.pend0.w});
-    x.pend0 = x.pend1;
-    --x.n_pend;
+    const unsigned at = in_ring(x, x.loaded);
+    lds_write<uint32_t>(at, x.pend[0].x);
+    lds_write<uint32_t>(at + 256u, x.pend[0].y);
+    lds_write<uint32_t>(at + 512u, x.pend[0].z);
+    lds_write<uint32_t>(at + 768u, x.pend[0].w);
+#pragma unroll
+    for (int i = 1; i < kPieces; ++i) x.pend[i - 1] = x.pend[i];
   };
-  auto request = [&](Device& x, const char* from, unsigned at2) {
-    x.pend0 = *reinterpret_cast<const uint4*>(from + at2);
-    x.n_pend = 1;
-    if (at2 + kPieceBytes < stride2) {
-      x.pend1 = *reinterpret_cast<const uint4*>(from + at2 + kPieceBytes);
-      x.n_pend = 2;
+  auto request = [&](Device& x, const char* from, unsigned pos) {
+    const unsigned at2 = pos >> 6;   // (a piece begins with a dword)
+    const uint4* piece = reinterpret_cast<const uint4*>(from + at2);
+    x.asked = pos + (unsigned)kPieces * kPiece;
+    if ((stride2 & (16u * kPieces - 1u)) == 0u) {
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) x.pend[i] = piece[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i)
+        if (at2 + 16u * (unsigned)i < stride2) x.pend[i] = piece[i];
     }
   };
-  // land what has been asked for, where there is room for it
+  // land what has been asked for, where at most seven words are unread
   auto land = [&](Device& x) {
-    if (x.n_pend > 0 && (int)(x.loaded2 - x.pos2) <= (int)kLandAt) {
+    if ((int)(x.loaded - x.pos) <= (int)kPiece && x.loaded != x.asked) {
       store_piece(x);
       // the device goes no further than where the order pass says its list stops (an END word does that by itself)
       if (any_stuck) {
-        const unsigned stop2 = (x.info & kRowStop) * 2u;
-        if (stop2 - x.loaded2 < kPieceBytes) lds_write<uint16_t>(in_ring(x, stop2), (uint16_t)0);
+        const unsigned stop = position_of(x.info & kRowStop);
+        if (stop - x.loaded < kPiece) lds_write<uint16_t>(in_ring(x, stop), (uint16_t)0);
       }
-      x.loaded2 += kPieceBytes;
+      x.loaded += kPiece;
       // a row that fills its stride has no END word: plant one behind it
-      if (x.loaded2 >= stride2) lds_write<uint16_t>(in_ring(x, stride2), (uint16_t)0);
+      if (x.loaded >= stride_pos) {
+        lds_write<uint16_t>(in_ring(x, stride_pos), (uint16_t)0);
+        x.loaded = kNoList;
+      }
     }
   };
   auto ask = [&](Device& x, const char* from) {
-    if (x.n_pend == 0 && x.loaded2 < stride2) request(x, from, x.loaded2);
+    if (x.loaded == x.asked) request(x, from, x.loaded);
   };
   // the head of the row has arrived: the device joins in
   auto join = [&](Device& x) {
-    x.loaded2 = 0u;
+    x.loaded = 0u;
     store_piece(x);
-    x.loaded2 = kPieceBytes;
-    if (x.n_pend > 0) {
+    x.loaded = kPiece;
+    if (stride_pos > kPiece) {
       store_piece(x);
-      x.loaded2 = 2u * kPieceBytes;
+      x.loaded = 2u * kPiece;
     }
-    const unsigned stop2 = (x.info & kRowStop) * 2u;
-    const unsigned w = stop2 == 0u ? 0u : lds_read<uint16_t>(in_ring(x, 0u));
-    x.w_next = stop2 <= 2u ? 0u : lds_read<uint16_t>(in_ring(x, 2u));
-    if (stop2 <= x.loaded2) lds_write<uint16_t>(in_ring(x, stop2), (uint16_t)0);   // (behind a full row of one or two pieces too)
+    const unsigned stop = x.info & kRowStop, stop_pos = position_of(stop);
+    const unsigned w = stop == 0u ? 0u : lds_read<uint16_t>(in_ring(x, 0u));
+    x.w_next = stop <= 1u ? 0u : lds_read<uint16_t>(in_ring(x, position_of(1u)));
+    if (stop_pos <= x.loaded) lds_write<uint16_t>(in_ring(x, stop_pos), (uint16_t)0);   // (behind a full row of one or two pieces too)
+    if (x.loaded >= stride_pos) x.loaded = kNoList;
     decode(x, w);
-    x.pos2 = 2u;
+    x.pos = position_of(1u);
   };
   // where the second row of an op with a second input or output is
   auto second_row = [&](int w) -> unsigned {
-    return lds0 + (WIDE ? ((unsigned)w >> 12) & 0xfff0u : (unsigned)w & 0xffffu);
+    return tables + (WIDE ? ((unsigned)w >> 12) & 0xfff0u : (unsigned)w & 0xffffu);
   };
-  // one step of one half of the devices; returns the lanes that issued
+  // one step of one half of the devices in the other forms; returns the lanes that issued
   auto step = [&](Device& x) -> unsigned long long {
     asm volatile("" : "+v"(x.R), "+v"(x.j_slot));   // (the row stays one value until here: no earlier wait for it)
     unsigned j_slot = x.j_slot, n_slots = 1u;
@@ -259,13 +325,14 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       more = x.taken + 1u < min(x.group >> 16, n_slots);
       j_slot = (first_j + x.taken) << 2;
     }
-    const unsigned at_slot = (j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
+    const unsigned at_slot = SPLIT ? (j_slot & (unsigned)x.R.z) + ((unsigned)x.R.w + slot_base)
+                                   : (j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
     unsigned ready, cost_tag = (unsigned)x.R.y, link_free = 0u;
     unsigned long long moved;
     unsigned cost = 0u;
     if (MB) {
       // (a row without a cost table reads some word of LDS and does not issue)
-      const unsigned at = lds0 + (cost_tag >> 8) + (((x.j_slot >> 2) & 0x7ffu) << (T.mb_bytes - 1));
+      const unsigned at = tables + (cost_tag >> 8) + (((x.j_slot >> 2) & 0x7ffu) << (T.mb_bytes - 1));
       cost = T.mb_bytes == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
       cost_tag = cost << 8 | (cost_tag & 0xffu);
     }
@@ -343,8 +410,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           for (unsigned k = 1; k < n_slots; ++k) leave(second_at + (k << 2));
       }
       decode(x, x.w_next);
-      x.pos2 += 2u;
-      x.w_next = lds_read<uint16_t>(in_ring(x, x.pos2));
+      x.pos = (x.pos | kPosBetween) + 2u;
+      x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
     }
     return moved;
   };
@@ -432,10 +499,30 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     }
     ask(even, row);
     ask(odd, row + stride2);
+    unsigned even_in = 0u, odd_in = 0u, even_at = 0u, odd_at = 0u, scratch;
+    if constexpr (PLAIN)
+      asm volatile("s_waitcnt lgkmcnt(0)\n\t"
+                   "v_and_b32 %[at], %[j], v42\n\t"
+                   "v_add3_u32 %[at], %[at], v43, %[slots]\n\t"
+                   "ds_read_b32 %[in], %[at]\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : [in] "=&v"(even_in), [at] "=&v"(even_at), [row] "+{v[40:43]}"(even.R)
+                   : [j] "v"(even.j_slot), [slots] "v"(slot_base) : "memory");
 #pragma unroll
     for (unsigned sub = 0; sub < kRounds; ++sub) {
-      const unsigned long long moved_even = step(even);
-      const unsigned long long moved_odd = step(odd);
+      unsigned long long moved_even, moved_odd;
+      if constexpr (PLAIN) {
+        FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("46", "47"));
+        if (sub + 1 < kRounds) {
+          FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("42", "43"));
+        } else {
+          FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "");
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
+        }
+      } else {
+        moved_even = step(even);
+        moved_odd = step(odd);
+      }
       // A segment none of whose lanes issued is finished, and stays so: nothing it reads changes any more.  It could
       // only be restarted at the next top-up anyway, so only the last round in front of it looks.  Cheap scalar
       // pre-test: does the issue mask, with the lanes of idle segments set, contain an all-zero field of P bits?
@@ -445,9 +532,9 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         if (((x - base_bits) & ~x & high_bits) != 0ull) {
           const bool ended = running && !priming && !any_in_segment(x);
           // (a device that a lane does not have counts as one whose list is exhausted)
-          const unsigned even_at = (even.pos2 >> 1) - 1u, odd_at = has_odd ? (odd.pos2 >> 1) - 1u : 0u;
+          const unsigned even_issued = word_at(even.pos) - 1u, odd_issued = has_odd ? word_at(odd.pos) - 1u : 0u;
           const unsigned both = even.info | odd.info;
-          const bool even_stops = even_at == (even.info & kRowStop), odd_stops = odd_at == (odd.info & kRowStop);
+          const bool even_stops = even_issued == (even.info & kRowStop), odd_stops = odd_issued == (odd.info & kRowStop);
           const bool stuck = any_in_segment(__ballot(!even_stops || !odd_stops || (both & kRowStuck) != 0u));
           const bool malformed = any_in_segment(__ballot((even_stops && (even.info & kRowMalformed) != 0u) || (odd_stops && (odd.info & kRowMalformed) != 0u)));
           const bool unfinished = any_in_segment(__ballot((both & kRowIncomplete) != 0u));
