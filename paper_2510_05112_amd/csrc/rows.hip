@@ -14,10 +14,13 @@
 // list stops (its END word, or an op that is not legal) is gone over again for those lanes: the states behind the
 // stop are put back, the sums taken up to it.
 //
-// What bounds it: per 64 words fourteen vector instructions and twelve clocks of LDS, and the op words once from HBM; none
+// What bounds it: per 64 words twelve vector instructions and twelve clocks of LDS, and the op words once from HBM; none
 // of the three is at its limit (65,536 candidates of 32 devices, 128 micro-batches, two chunks, profiles/list_evaluation.md:
-// vector units 59 % busy, LDS 54 %, 3.8 GB at 3.4 TB/s in 1.10 ms), what is left are waits with eight wavefronts per compute
-// unit.  A lane reads its row 64 bytes at a time.
+// vector units 54 % busy, LDS 58 %, 3.8 GB at 3.4 TB/s in 1.11 ms), what is left are waits with eight wavefronts per compute
+// unit.  A lane reads its row 64 bytes at a time.  (Fourteen vector instructions, the places of the states worked out word
+// by word: 1.15 ms in the same run.  States without bank conflicts, a dword of all rows side by side: LDS 32 % busy, one
+// instruction more, 1.14 ms.  128 bytes at a time: 5 % less on long batches of 16 devices, none on 32, 2 to 3 % more on
+// short rows.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -116,8 +119,7 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   };
   auto pair_word = [](const uint4& q, int k) -> unsigned { return k < 2 ? q.x : (k < 4 ? q.y : (k < 6 ? q.z : q.w)); };
   auto word_of = [&](const uint4& q, int k) -> unsigned { return (k & 1) ? pair_word(q, k) >> 16 : pair_word(q, k) & 0xffffu; };
-  const unsigned m1 = (unsigned)m + 1u;
-  const unsigned state1 = state + m1;
+  const u16_pair per_chunk = {(unsigned short)(m + 1), (unsigned short)(m + 1)};
   const u16_pair limit = {(unsigned short)m, (unsigned short)m};
   auto row_of = [&](const uint4& q, int k) -> unsigned { return __umul24(word_of(q, k) >> 11, row_bytes) + meta; };
   auto fetch = [&](Group& G, const uint4& q) {
@@ -131,21 +133,29 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   };
   // where the state of a word's activation is: a micro-batch out of range looks at the byte behind its chunk, a chunk that
   // the device does not have at some chunk's bytes -- the op is found out either way and its write taken back
-  auto state_of = [&](const uint4& q, int k) -> unsigned {
-    const unsigned two = bits_of(__builtin_elementwise_min(pair_of(pair_word(q, k) & 0x07ff07ffu), limit));
-    unsigned at_chunk = state;
-    if (VBITS == 1) {   // (all ones where the chunk bit is set)
-      const unsigned second = (unsigned)((int)(pair_word(q, k) << ((k & 1) ? 4 : 20)) >> 31);
-      at_chunk = (second & state1) | (~second & state);
+  auto states_of = [&](unsigned pair) -> unsigned {   // (of both words of a pair, 16 bits each, from this row's first on)
+    unsigned at = bits_of(__builtin_elementwise_min(pair_of(pair & 0x07ff07ffu), limit));
+    if (VBITS > 0) {
+      // (written out: the compiler makes comparisons and selects of it)
+      unsigned chunk;
+      asm("v_pk_lshrrev_b16 %0, 11, %1 op_sel_hi:[0,1]" : "=v"(chunk) : "v"(pair));
+      chunk &= VBITS == 1 ? 0x00010001u : 0x00030003u;
+      asm("v_pk_mad_u16 %0, %1, %2, %0" : "+v"(at) : "v"(chunk), "v"(bits_of(per_chunk)));
     }
-    if (VBITS == 2) at_chunk = __umul24((word_of(q, k) >> 11) & 3u, m1) + state;
-    asm("" : "+v"(at_chunk));   // (one addition with a half-word operand remains)
-    return at_chunk + ((k & 1) ? two >> 16 : two & 0xffffu);
+    return at;
+  };
+  auto state_of = [&](unsigned two, int k) -> unsigned {
+    unsigned at;
+    if (k & 1) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1" : "=v"(at) : "v"(state), "v"(two));
+    else asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_0" : "=v"(at) : "v"(state), "v"(two));
+    return at;
   };
   auto exchange = [&](Group& G) {
+    unsigned two = 0u;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const unsigned at = state_of(G.q, k);
+      if ((k & 1) == 0) two = states_of(pair_word(G.q, k));
+      const unsigned at = state_of(two, k);
       G.old[k] = lds_read<uint8_t>(at);
       lds_write<uint8_t>(at, (uint8_t)G.x[k]);
     }
@@ -173,7 +183,7 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
 #pragma unroll
       for (int k = 7; k >= 0; --k)
         if (k >= first_bad) {
-          lds_write<uint8_t>(state_of(G.q, k), (uint8_t)G.old[k]);
+          lds_write<uint8_t>(state_of(states_of(pair_word(G.q, k)), k), (uint8_t)G.old[k]);
           busy -= lds_read<uint32_t>(row_of(G.q, k) + 4u);
         }
 #pragma unroll
