@@ -163,6 +163,7 @@ constexpr unsigned kWideNever = 0xffu << 8;   // wide form: the tag of an empty 
 constexpr unsigned kOwnTag = 0xfeu;   // (no stage's op looks at a device's own word)
 constexpr int list_slots_at(int D) { return (D + 2 + 3) & ~3; }
 constexpr unsigned kNoState = 15u;
+constexpr unsigned kPadState = 14u;   // order pass: state of the bytes behind a chunk's last item
 // the upper half of what the order pass leaves per row: the position at which the list stops (its END word, the end
 // of the row, or the first op that may not issue there), and
 constexpr unsigned kRowStop = 0x0fffffffu;

@@ -67,6 +67,7 @@ struct fpsched_problem {
   int32_t time_waves = 0, time_grid = 0;   // wavefronts per workgroup, resident workgroups
   std::vector<int32_t> list_image;         // host copy of d_list_ints
   ListVariant lists_links, lists_mb, lists_both, lists_sync;
+  ListVariant lists_times;                 // the lists without their W items, first pass of the sliding pass
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
   int64_t max_comm = 0;
   bool mb_set = false;
@@ -235,18 +236,21 @@ int next_pow2(int x) {
 }
 
 using CheckKernel = void (*)(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+template <bool NO_W>
 CheckKernel check_kernel_of(int vbits) {
-  return vbits == 0 ? &check_rows_kernel<0> : (vbits == 1 ? &check_rows_kernel<1> : &check_rows_kernel<2>);
+  return vbits == 0 ? &check_rows_kernel<0, NO_W> : (vbits == 1 ? &check_rows_kernel<1, NO_W> : &check_rows_kernel<2, NO_W>);
 }
+CheckKernel check_kernel_of(int vbits, bool no_w = false) { return no_w ? check_kernel_of<true>(vbits) : check_kernel_of<false>(vbits); }
 
-using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int);
+using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
 template <bool LINKS, bool MB>
 TimeKernel narrow_time_kernel_of(bool deg2) {
-  return deg2 ? &time_lists_kernel<true, false, LINKS, MB, false> : &time_lists_kernel<false, false, LINKS, MB, false>;
+  return deg2 ? &time_lists_kernel<true, false, LINKS, MB, false, false> : &time_lists_kernel<false, false, LINKS, MB, false, false>;
 }
+TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, false, false, true>; }
 TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, bool mb = false, bool sync = false) {
-  if (sync) return deg2 ? &time_lists_kernel<true, false, false, false, true> : &time_lists_kernel<false, false, false, false, true>;
-  if (wide) return deg2 ? &time_lists_kernel<true, true, false, false, false> : &time_lists_kernel<false, true, false, false, false>;
+  if (sync) return deg2 ? &time_lists_kernel<true, false, false, false, true, false> : &time_lists_kernel<false, false, false, false, true, false>;
+  if (wide) return deg2 ? &time_lists_kernel<true, true, false, false, false, false> : &time_lists_kernel<false, true, false, false, false, false>;
   if (links) return mb ? narrow_time_kernel_of<true, true>(deg2) : narrow_time_kernel_of<true, false>(deg2);
   return mb ? narrow_time_kernel_of<false, true>(deg2) : narrow_time_kernel_of<false, false>(deg2);
 }
@@ -555,6 +559,35 @@ int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVa
     for (int i = kMaxChunks * D; i < T.n_check_ints / 2; ++i) J[(size_t)T.off_check + 2 * i + 1] = 0;
   // (costs from device memory, kSlotPerMicrobatch, are better than so few wavefronts)
   return install_list_variant(p, T, J, p->lists_deg2, mb && !links ? 6 : 1, v);
+}
+
+// The tables of the lists without their W items: a W word is a no-op, an activation is consumed by its B item.
+int build_times_variant(fpsched_problem* p) {
+  ListVariant* v = &p->lists_times;
+  ListTables T = p->ltab;
+  std::vector<int32_t> J = p->list_image;
+  const int D = p->D;
+  for (int c = 0; c < kMaxChunks; ++c)
+    for (int d = 0; d < D; ++d) {
+      if (c >= p->n_chunks[d]) continue;
+      const size_t row = ((size_t)kW * kMaxChunks + c) * D;
+      J[(row + (d & 1) * ((D + 1) / 2) + d / 2) * 4 + 1] = (int32_t)kOwnTag;   // no cost
+      int32_t* o = &J[(size_t)T.off_check + (row + d) * 2];
+      o[0] = (int32_t)(kPadState | kPadState << 8);
+      o[1] = 0;
+    }
+  T.terminal = kBDone;
+  if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
+  v->capacity = J.size();
+  if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) return FPSCHED_EHIP;
+  for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, true)), reinterpret_cast<const void*>(times_kernel())})
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess) return FPSCHED_EHIP;
+  T.ints = v->d_image;
+  v->tab = T;
+  v->waves = p->time_waves;
+  v->grid = p->time_grid;
+  v->ok = true;
+  return FPSCHED_OK;
 }
 
 }  // namespace
@@ -982,6 +1015,9 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
         if (up) {
           p->stab_times.ints = p->d_times_ints;
           p->slide_ok = true;
+          // ... or, on the plain model, the two passes of the list evaluation do, with the same change to their tables
+          // (without them the slot kernel stays in use)
+          if (p->lists_ok && !p->lists_deg2 && !p->lists_wide) (void)build_times_variant(p);
           // the one-kernel form: the same image, and behind it per device the cost << 8 of the W item of each
           // chunk, the units it frees, and the cost << 8 of all W items of the device
           std::vector<int32_t> JS = J;
@@ -1044,7 +1080,7 @@ void fpsched_problem_destroy(fpsched_problem* p) {
     if (p->d_times_ints) (void)hipFree(p->d_times_ints);
     if (p->d_mb_raw) (void)hipFree(p->d_mb_raw);
     if (p->d_mb_rows) (void)hipFree(p->d_mb_rows);
-    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync})
+    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync, &p->lists_times})
       if (v->d_image) (void)hipFree(v->d_image);
     if (p->d_times_links_image) (void)hipFree(p->d_times_links_image);
     if (p->d_slide_links_image) (void)hipFree(p->d_slide_links_image);
@@ -1102,9 +1138,11 @@ static int draws_at_a_time(const fpsched_problem* p, int32_t stride_words, int c
 }
 
 // the two-pass list evaluation: the order pass over all rows, then the timing pass on a persistent grid
-// (variant: its tables and launch shape under link occupancy or costs per micro-batch; null: the plain model)
+// (variant: its tables and launch shape under link occupancy or costs per micro-batch; null: the plain model; starts: what
+// the first pass of the sliding pass leaves, with its variant)
 static int run_list_evaluation(const fpsched_problem* p, const ListVariant* variant, const uint16_t* d_ops, int64_t n_cand, int32_t stride_words,
-                               const fpsched_results& out, unsigned long long* counter, hipStream_t st) {
+                               const fpsched_results& out, unsigned long long* counter, hipStream_t st,
+                               const StartTimes* starts = nullptr) {
   const ListTables& T = variant ? variant->tab : p->ltab;
   const int64_t n_rows = n_cand * p->D, rpw = p->check_rows_per_wave;
   // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
@@ -1131,14 +1169,14 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, first_drawn, (unsigned long long)(check_waves * draw_blocks));
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   }
-  hipLaunchKernelGGL(check_kernel_of(p->check_vbits), dim3((unsigned)check_blocks), dim3(64 * cw),
+  hipLaunchKernelGGL(check_kernel_of(p->check_vbits, starts != nullptr), dim3((unsigned)check_blocks), dim3(64 * cw),
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(time_kernel_of(variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant, T.link_words > 0, T.mb_bytes > 0, T.off_sync > 0), dim3((unsigned)time_blocks),
+  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant, T.link_words > 0, T.mb_bytes > 0, T.off_sync > 0), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
-                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave));
+                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), starts ? *starts : StartTimes{});
   return check_hip(hipGetLastError());
 }
 
@@ -2231,23 +2269,30 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   // (under the link model: that model's tables and workgroup shape; W items send nothing, so the second
   // pass is the same)
   const bool links = p->links_on;
-  const SlotTables& times_tab = links ? p->stab_times_links : p->stab_times;
-  const int waves = links ? p->links_waves : p->slot_waves;
-  const int grid = links ? p->links_grid : p->slot_grid;
-  const size_t times_lds = (size_t)(links ? p->links_lds_bytes : p->slot_lds_bytes) + 16;
-  const SlotLaunch L = slot_launch(times_tab, waves, grid, times_lds, n_cand);
-  const int per_block = times_tab.cands_per_wave * L.waves;
-  const int64_t blocks = L.blocks;
-  const int64_t row_words = (int64_t)p->D * stride_words;
-  const int draw_block = (int)std::clamp<int64_t>((12288 + row_words - 1) / row_words, 1, times_tab.cands_per_wave);
-  const bool one_class = p->stab.n_classes == 1;
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)(blocks * per_block), 0ull);
-  hipLaunchKernelGGL(links ? slot_kernel_of<kSlotTimesLinks>(p->slot_v, p->slot_deg2, one_class)
-                           : slot_kernel_of<kSlotTimes>(p->slot_v, p->slot_deg2, one_class),
-                     dim3((unsigned)blocks), dim3(64 * L.waves), L.lds_bytes, st, times_tab, d_ops, (long long)n_cand,
-                     (int)stride_words, (long long*)nullptr, (long long*)nullptr, (int*)nullptr, timed_flags, counter,
-                     draw_block, starts, stops, (const int32_t*)nullptr, escapes, escape_cap);
-  if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
+  if (!links && p->lists_times.ok) {
+    const fpsched_results timed{out.makespan, out.idle, out.peak, timed_flags};   // (what the order pass leaves stands in the results until pass 2)
+    const StartTimes left{starts, escapes, stops, escape_cap, lpc};
+    const int rc = run_list_evaluation(p, &p->lists_times, d_ops, n_cand, stride_words, timed, counter, st, &left);
+    if (rc != FPSCHED_OK) return rc;
+  } else {
+    const SlotTables& times_tab = links ? p->stab_times_links : p->stab_times;
+    const int waves = links ? p->links_waves : p->slot_waves;
+    const int grid = links ? p->links_grid : p->slot_grid;
+    const size_t times_lds = (size_t)(links ? p->links_lds_bytes : p->slot_lds_bytes) + 16;
+    const SlotLaunch L = slot_launch(times_tab, waves, grid, times_lds, n_cand);
+    const int per_block = times_tab.cands_per_wave * L.waves;
+    const int64_t blocks = L.blocks;
+    const int64_t row_words = (int64_t)p->D * stride_words;
+    const int draw_block = (int)std::clamp<int64_t>((12288 + row_words - 1) / row_words, 1, times_tab.cands_per_wave);
+    const bool one_class = p->stab.n_classes == 1;
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)(blocks * per_block), 0ull);
+    hipLaunchKernelGGL(links ? slot_kernel_of<kSlotTimesLinks>(p->slot_v, p->slot_deg2, one_class)
+                             : slot_kernel_of<kSlotTimes>(p->slot_v, p->slot_deg2, one_class),
+                       dim3((unsigned)blocks), dim3(64 * L.waves), L.lds_bytes, st, times_tab, d_ops, (long long)n_cand,
+                       (int)stride_words, (long long*)nullptr, (long long*)nullptr, (int*)nullptr, timed_flags, counter,
+                       draw_block, starts, stops, (const int32_t*)nullptr, escapes, escape_cap);
+    if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
+  }
   // pass 2: every row places its W items on its own
   hipLaunchKernelGGL(p->slot_v > 2 ? wslide_place_kernel<true> : wslide_place_kernel<false>, dim3((unsigned)place_blocks), dim3(place_threads),
                      (size_t)place_rows_bytes + (place_threads / 64) * kSlideWaveLdsBytes, st, p->stab, d_ops,

@@ -72,14 +72,25 @@ constexpr int kCheckMaxThreads = 512;
 constexpr int kCheckWavesPerSimd = 3;
 constexpr int kTimeMaxThreads = 1024;
 constexpr int kTimeWindowBytes = 2 * 64 * 32;   // op windows of a wavefront of the timing pass
-template <int VBITS>   // 0, 1, 2: up to 1, 2, 4 stages per device
+// VBITS 0, 1, 2: up to 1, 2, 4 stages per device.  NO_W: W items are no-ops that only have to be in range (tables: their
+// rows ask for kPadState and leave it).
+template <int VBITS, bool NO_W>
 __global__ void check_rows_kernel(ListTables T, const uint16_t* ops, long long n_rows, int stride, int rows_per_wave,
                                   long long* out_info, int* out_peak, unsigned long long* counter,
                                   unsigned long long counter_value, int draw_blocks, int dynamic);
-template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC>
+// TIMES: the first pass of the weight-gradient sliding (wslide.hip) on the plain model: what eval_slot_kernel<.., kSlotTimes>
+// leaves, for lists the NO_W order pass has walked (out_flags and `starts`; makespan, idle and peak are not written).
+struct StartTimes {
+  uint32_t* low;        // [n_cand][stride / 8][lanes][8 x 16 bits]
+  uint32_t* escapes;    // [n_cand][D][escape_cap]
+  int32_t* stops;       // [n_cand][D]
+  int32_t escape_cap, lanes;
+};
+template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC, bool TIMES>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
-                                  unsigned char* out_flags, unsigned long long* next_candidate, int draw_block);
+                                  unsigned char* out_flags, unsigned long long* next_candidate, int draw_block,
+                                  StartTimes starts);
 
 // counter[0] = value, counter[1] = value2
 __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2 = 0);

@@ -35,12 +35,10 @@ typedef unsigned short u16_pair __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned bits_of(u16_pair v) { return __builtin_bit_cast(unsigned, v); }
 __device__ __forceinline__ u16_pair pair_of(unsigned v) { return __builtin_bit_cast(u16_pair, v); }
 
-constexpr unsigned kPadState = 14u;   // state of the bytes behind a chunk's last item: no op requires it
-
 }  // namespace
 
 // VBITS: bits of the chunk field that select a chunk's states (0, 1, 2: up to 1, 2, 4 stages per device)
-template <int VBITS>
+template <int VBITS, bool NO_W>
 __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_eu(kCheckWavesPerSimd, kCheckWavesPerSimd))) void check_rows_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_rows, int stride, int rows_per_wave,
     long long* __restrict__ out_info, int* __restrict__ out_peak, unsigned long long* __restrict__ counter,
@@ -135,6 +133,14 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   // the device does not have at some chunk's bytes -- the op is found out either way and its write taken back
   auto states_of = [&](unsigned pair) -> unsigned {   // (of both words of a pair, 16 bits each, from this row's first on)
     unsigned at = bits_of(__builtin_elementwise_min(pair_of(pair & 0x07ff07ffu), limit));
+    if (NO_W) {
+      // a W item in range looks at the byte behind its chunk's items, whose state it asks for and leaves; one out of range
+      // at item 0, which never has that state
+      const u16_pair one = {1, 1}, zero = {0, 0};
+      const unsigned other = bits_of(zero - __builtin_elementwise_min(pair_of((pair & 0xe000e000u) ^ 0x60006000u), one));
+      const unsigned no_op = bits_of(__builtin_elementwise_min(limit - pair_of(at), one) * limit);
+      at = (at & other) | (no_op & ~other);
+    }
     if (VBITS > 0) {
       // (written out: the compiler makes comparisons and selects of it)
       unsigned chunk;
@@ -256,8 +262,14 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   }
 }
 
-template __global__ void check_rows_kernel<0>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
-template __global__ void check_rows_kernel<1>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
-template __global__ void check_rows_kernel<2>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+#define FPSCHED_INSTANTIATE(VBITS, NO_W) \
+  template __global__ void check_rows_kernel<VBITS, NO_W>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+FPSCHED_INSTANTIATE(0, false)
+FPSCHED_INSTANTIATE(1, false)
+FPSCHED_INSTANTIATE(2, false)
+FPSCHED_INSTANTIATE(0, true)
+FPSCHED_INSTANTIATE(1, true)
+FPSCHED_INSTANTIATE(2, true)
+#undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched

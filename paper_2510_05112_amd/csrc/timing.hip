@@ -47,6 +47,13 @@
 // A pair is an edge of its own slot class in one direction only.  (The host only picks this form when the neighbours of
 // such a stage have one item per micro-batch.)
 //
+// TIMES, the first pass of the weight-gradient sliding (wslide.hip) on problems of the plain form: the lists without their W
+// items (a W word is an op of the device's own without a cost), of which it leaves the low sixteen bits of each op's start
+// time, the ops that waited 2^16 time units or more, and where the lists stop.  A start time takes the place of the op's
+// word in the ring and leaves eight at a time when the next piece lands there, so that a step has four vector instructions
+// more and no store.  32,768 candidates of 16 devices, 64 micro-batches, 2 chunks: 0.15 ms (order pass) + 0.59 ms; 1.46 ms
+// as a form of the slot kernel, with all devices in every round.
+//
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
@@ -129,21 +136,66 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
       : [zero] "v"(0u), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),           \
         [slots] "v"(slot_base)                                                                                           \
       : "memory")
-#define FPSCHED_READ_AHEAD(OZ, OW)                                                                                       \
-  "s_waitcnt lgkmcnt(1)\n\t"                                                                                            \
+#define FPSCHED_READ_AHEAD(WRITES, OZ, OW)                                                                               \
+  "s_waitcnt lgkmcnt(" WRITES ")\n\t"                                                                                   \
   "v_and_b32 %[other_at], %[other_j], v" OZ "\n\t"                                                                      \
   "v_add3_u32 %[other_at], %[other_at], v" OW ", %[slots]\n\t"                                                          \
   "ds_read_b32 %[other_in], %[other_at]\n\t"
 
-template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC>
+// The same in two halves, between which the few ops are looked after that waited 2^16 time units or more (LATE), for the
+// form that leaves start times: an op's start goes where its own word was in the ring (OWN: that place; AT_NEXT: the place
+// of the word behind it, read already).
+#define FPSCHED_START(X, RX, RY)                                                                                         \
+  asm volatile(                                                                                                          \
+      "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
+      "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
+      "v_cmpx_eq_u32_sdwa %[moved], %[in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                                   \
+      "v_max_u32 %[t], %[free], %[in]\n\t"                                                                              \
+      "v_lshrrev_b32 %[start], 8, %[t]\n\t"                                                                             \
+      "v_sub_u32 %[wait], %[t], %[free]\n\t"                                                                            \
+      "v_add_u32 %[t], %[t], v" RY "\n\t"                                                                               \
+      "ds_write_b32 %[at], %[t]\n\t"                                                                                    \
+      "ds_write_b16 %[own], %[start]\n\t"                                                                               \
+      "v_and_b32 %[free], 0xffffff00, %[t]\n\t"                                                                         \
+      "v_cmp_lt_u32 %[late], %[most], %[wait]\n\t"                                                                      \
+      "s_mov_b64 exec, -1"                                                                                               \
+      : [in] "+v"(X##_in), [free] "+v"(X.free_at), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited),  \
+        [moved] "=&s"(moved_##X), [late] "=&s"(late)                                                                     \
+      : [at] "v"(X##_at), [own] "v"(X.own_place), [zero] "v"(0u), [most] "s"(0xffffffu), [row] "{" FPSCHED_ROW_OF_##X "}"(X.R) \
+      : "memory")
+#define FPSCHED_ADVANCE(X, Y, RX, RW, READ_AHEAD)                                                                        \
+  asm volatile(                                                                                                          \
+      READ_AHEAD                                                                                                         \
+      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
+      "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
+      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
+      "v_mov_b32 %[own], %[at_next]\n\t"                                                                                \
+      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
+      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
+      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
+      "v_bitop3_b32 %[at_next], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                               \
+      "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
+      "ds_read_u16 %[next], %[at_next]\n\t"                                                                             \
+      "s_mov_b64 exec, -1"                                                                                               \
+      : [next] "+v"(X.w_next), [j] "+v"(X.j_slot), [pos] "+v"(X.pos), [t] "=&v"(scratch), [own] "+v"(X.own_place),       \
+        [at_next] "+v"(X.next_place), [row] "+{" FPSCHED_ROW_OF_##X "}"(X.R), [other_row] "+{" FPSCHED_ROW_OF_##Y "}"(Y.R), \
+        [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot), [other_next] "+v"(Y.w_next)          \
+      : [moved] "s"(moved_##X), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),   \
+        [slots] "v"(slot_base)                                                                                           \
+      : "memory")
+#define FPSCHED_ROW_OF_even "v[40:43]"
+#define FPSCHED_ROW_OF_odd "v[44:47]"
+
+template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC, bool TIMES>
 __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
-    unsigned long long* __restrict__ next_candidate, int draw_block) {
+    unsigned long long* __restrict__ next_candidate, int draw_block, StartTimes starts) {
   static_assert(!WIDE || !(LINKS || MB || SYNC), "these forms have times of 24 bits");
   static_assert(!SYNC || !(LINKS || MB), "");
+  static_assert(!TIMES || !(DEG2 || WIDE || LINKS || MB || SYNC), "");
   constexpr unsigned kRowBytes = 16u;
-  constexpr bool PLAIN = !DEG2 && !WIDE && !LINKS && !MB && !SYNC;
+  constexpr bool PLAIN = !DEG2 && !WIDE && !LINKS && !MB && !SYNC;   // (TIMES too)
   constexpr bool SPLIT = !DEG2 && !WIDE;   // rows with the slot's mask and offset in a word each
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
   constexpr int kPieces = PLAIN ? 4 : 2;
@@ -201,6 +253,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned sync_rows;          // SYNC: where its devices' group rows are
     unsigned group, taken;       // SYNC: micro-batches of the item | values it waits for << 16; those taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
+    unsigned own_place, next_place;   // TIMES: places in the ring of the words under and behind the cursor
+    int n_late;                       // TIMES: entries of the row's escape list
     uint4 pend[kPieces];   // what has been requested and is not in the ring, in order
   };
   Device even, odd;
@@ -220,6 +274,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     x.sync_rows = SYNC ? tables + (unsigned)T.off_sync * 4u + (unsigned)(k * P + pair) * 4u : 0u;
     x.links = LINKS ? wave_at + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
+    x.own_place = x.win; x.next_place = x.win; x.n_late = 0;
     for (int i = 0; i < kPieces; ++i) x.pend[i] = make_uint4(0u, 0u, 0u, 0u);
     idle_device(x);
   };
@@ -227,6 +282,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   set_up(odd, 1);
 
   long long cand = 0;
+  uint32_t* start_row = starts.low;   // TIMES: of the even device
   const char* row = reinterpret_cast<const char*>(ops);   // of the even device; the odd one's follows it
   bool running = false, fresh = true, priming = false;
   bool any_special = true;          // wave-uniform: some segment starts, or has just started, a candidate
@@ -273,9 +329,33 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         if (at2 + 16u * (unsigned)i < stride2) x.pend[i] = piece[i];
     }
   };
+  // TIMES: the start times of the eight ops from a position on, whose words' places in the ring they have taken
+  auto leave_starts = [&](const Device& x, unsigned pos, int odd_device) {
+    const unsigned at = in_ring(x, pos);
+    const uint4 eight = make_uint4(lds_read<uint32_t>(at), lds_read<uint32_t>(at + 256u), lds_read<uint32_t>(at + 512u), lds_read<uint32_t>(at + 768u));
+    *reinterpret_cast<uint4*>(start_row + (size_t)(pos >> 10) * (unsigned)starts.lanes * 4u + odd_device * 4) = eight;
+  };
   // land what has been asked for, where at most seven words are unread
-  auto land = [&](Device& x) {
-    if ((int)(x.loaded - x.pos) <= (int)kPiece && x.loaded != x.asked) {
+  // (TIMES: where all ops whose places are taken have issued, which is at most six unread: the word behind the cursor may
+  // have been read too early and is read again.  Behind a full row comes a piece of nothing but the END word.)
+  auto land = [&](Device& x, int odd_device) {
+    if constexpr (TIMES) {
+      if ((int)(x.loaded - (x.pos & ~kPosBetween)) <= (int)kPiece - 2 && (x.loaded != x.asked || x.loaded == stride_pos)) {
+        if (x.loaded >= 2u * kPiece) leave_starts(x, x.loaded - 2u * kPiece, odd_device);
+        if (x.loaded < stride_pos) {
+          store_piece(x);
+          if (any_stuck) {
+            const unsigned stop = position_of(x.info & kRowStop);
+            if (stop - x.loaded < kPiece) lds_write<uint16_t>(in_ring(x, stop), (uint16_t)0);
+          }
+          x.loaded += kPiece;
+        } else {
+          lds_write<uint16_t>(in_ring(x, stride_pos), (uint16_t)0);
+          x.loaded = kNoList;
+        }
+        x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
+      }
+    } else if ((int)(x.loaded - x.pos) <= (int)kPiece && x.loaded != x.asked) {
       store_piece(x);
       // the device goes no further than where the order pass says its list stops (an END word does that by itself)
       if (any_stuck) {
@@ -291,7 +371,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     }
   };
   auto ask = [&](Device& x, const char* from) {
-    if (x.loaded == x.asked) request(x, from, x.loaded);
+    if (x.loaded == x.asked && (!TIMES || x.loaded < stride_pos)) request(x, from, x.loaded);
   };
   // the head of the row has arrived: the device joins in
   auto join = [&](Device& x) {
@@ -305,8 +385,13 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     const unsigned stop = x.info & kRowStop, stop_pos = position_of(stop);
     const unsigned w = stop == 0u ? 0u : lds_read<uint16_t>(in_ring(x, 0u));
     x.w_next = stop <= 1u ? 0u : lds_read<uint16_t>(in_ring(x, position_of(1u)));
-    if (stop_pos <= x.loaded) lds_write<uint16_t>(in_ring(x, stop_pos), (uint16_t)0);   // (behind a full row of one or two pieces too)
-    if (x.loaded >= stride_pos) x.loaded = kNoList;
+    if (TIMES ? stop_pos < x.loaded : stop_pos <= x.loaded) lds_write<uint16_t>(in_ring(x, stop_pos), (uint16_t)0);   // (behind a full row of one or two pieces too)
+    if (!TIMES && x.loaded >= stride_pos) x.loaded = kNoList;
+    if (TIMES) {
+      x.own_place = in_ring(x, 0u);
+      x.next_place = in_ring(x, position_of(1u));
+      x.n_late = 0;
+    }
     decode(x, w);
     x.pos = position_of(1u);
   };
@@ -423,8 +508,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   const unsigned long long bound = (2ull * (unsigned)D * (unsigned)stride * (SYNC ? (unsigned long long)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
-    land(even);
-    land(odd);
+    land(even, 0);
+    land(odd, 1);
     // ---- the rare part, only when some segment starts or has just started a candidate
     if (any_special) {
       // segments restarted at the previous top-up: the heads of their rows have arrived, they join in and ask for
@@ -478,6 +563,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
             for (unsigned i = 0; i < links_bytes / 2u; i += 256u) { lds_write<unsigned>(even.links + i, 0u); lds_write<unsigned>(odd.links + i, 0u); }
           const long long r = cand * D + d0;
           row = reinterpret_cast<const char*>(ops + (size_t)r * (size_t)stride);
+          if (TIMES) start_row = starts.low + (size_t)cand * ((size_t)stride >> 1) * (unsigned)starts.lanes + (unsigned)d0 * 4u;
           request(even, row, 0u);
           const unsigned long long left = (unsigned long long)out_idle[r];
           even.info = (unsigned)(left >> 32);
@@ -512,13 +598,34 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     for (unsigned sub = 0; sub < kRounds; ++sub) {
       unsigned long long moved_even, moved_odd;
       if constexpr (PLAIN) {
-        FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("46", "47"));
-        if (sub + 1 < kRounds) {
-          FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("42", "43"));
+        if constexpr (TIMES) {
+          unsigned start_time, waited;
+          unsigned long long late;
+          // an op that waited 2^16 time units or more cannot be rebuilt from the low half of its start time
+          auto escape = [&](Device& x, int odd_device) {
+            if (late != 0ull && __builtin_amdgcn_inverse_ballot_w64(late) && x.n_late < starts.escape_cap - 1)
+              starts.escapes[((size_t)cand * D + d0 + odd_device) * (size_t)starts.escape_cap + x.n_late++] = (word_at(x.pos) - 1u) << 8 | waited >> 24;
+          };
+          FPSCHED_START(even, "40", "41");
+          escape(even, 0);
+          FPSCHED_ADVANCE(even, odd, "40", "43", FPSCHED_READ_AHEAD("2", "46", "47"));
+          FPSCHED_START(odd, "44", "45");
+          escape(odd, 1);
+          if (sub + 1 < kRounds) {
+            FPSCHED_ADVANCE(odd, even, "44", "47", FPSCHED_READ_AHEAD("2", "42", "43"));
+          } else {
+            FPSCHED_ADVANCE(odd, even, "44", "47", "");
+          }
         } else {
-          FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "");
-          asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
+          FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"));
+          if (sub + 1 < kRounds) {
+            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"));
+          } else {
+            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "");
+          }
         }
+        if (sub + 1 == kRounds)
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
       } else {
         moved_even = step(even);
         moved_odd = step(odd);
@@ -540,22 +647,37 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           const bool unfinished = any_in_segment(__ballot((both & kRowIncomplete) != 0u));
           const bool over = any_in_segment(__ballot((both & kRowOverCap) != 0u));
           if (ended) {
-            // the latest finish, in a word that was cleared when the segment started
-            atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at, odd.free_at));
-            const unsigned ms = lds_read<uint32_t>(at_max) >> (WIDE ? 0 : 8);
             const unsigned flags = stuck ? kDeadlock | (malformed ? kIncomplete : 0u)
                                          : (unfinished ? (unsigned)kIncomplete : (over ? (unsigned)kOverCap : 0u));
-            const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
-            const long long r = cand * D + d0;
-            out_idle[r] = failed ? -1ll : (long long)((int)ms - (int)even.busy);
-            if (failed) out_peak[r] = -1;
-            if (has_odd) {
-              out_idle[r + 1] = failed ? -1ll : (long long)((int)ms - (int)odd.busy);
-              if (failed) out_peak[r + 1] = -1;
-            }
-            if (pair == 0) {
-              out_makespan[cand] = failed ? 0x7fffffffffffffffll : (long long)ms;
-              out_flags[cand] = (unsigned char)flags;
+            if constexpr (TIMES) {
+              // the start times still in the rings, the ends of the escape lists, and where the lists stopped
+              auto leave = [&](const Device& x, int odd_device, unsigned issued) {
+                const unsigned landed = x.loaded == kNoList ? stride_pos + kPiece : x.loaded;
+                for (unsigned back = 2u * kPiece; back > 0u; back -= kPiece)
+                  if (landed >= back && (landed - back) >> 7 < issued) leave_starts(x, landed - back, odd_device);
+                const size_t r = (size_t)cand * D + d0 + odd_device;
+                starts.escapes[r * (size_t)starts.escape_cap + x.n_late] = 0xffffffffu;
+                starts.stops[r] = (int)issued;
+              };
+              leave(even, 0, even_issued);
+              if (has_odd) leave(odd, 1, odd_issued);
+              if (pair == 0) out_flags[cand] = (unsigned char)(flags & (kDeadlock | kIncomplete));
+            } else {
+              // the latest finish, in a word that was cleared when the segment started
+              atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at, odd.free_at));
+              const unsigned ms = lds_read<uint32_t>(at_max) >> (WIDE ? 0 : 8);
+              const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
+              const long long r = cand * D + d0;
+              out_idle[r] = failed ? -1ll : (long long)((int)ms - (int)even.busy);
+              if (failed) out_peak[r] = -1;
+              if (has_odd) {
+                out_idle[r + 1] = failed ? -1ll : (long long)((int)ms - (int)odd.busy);
+                if (failed) out_peak[r + 1] = -1;
+              }
+              if (pair == 0) {
+                out_makespan[cand] = failed ? 0x7fffffffffffffffll : (long long)ms;
+                out_flags[cand] = (unsigned char)flags;
+              }
             }
             running = false;
             fresh = true;
@@ -571,21 +693,22 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   }
 }
 
-#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC)                                                                     \
-  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC>(ListTables, const uint16_t*, long long, int, long long*, \
-                                                                    long long*, int*, unsigned char*, unsigned long long*, int);
-FPSCHED_INSTANTIATE(false, false, false, false, false)
-FPSCHED_INSTANTIATE(true, false, false, false, false)
-FPSCHED_INSTANTIATE(false, true, false, false, false)
-FPSCHED_INSTANTIATE(true, true, false, false, false)
-FPSCHED_INSTANTIATE(false, false, true, false, false)
-FPSCHED_INSTANTIATE(true, false, true, false, false)
-FPSCHED_INSTANTIATE(false, false, false, true, false)
-FPSCHED_INSTANTIATE(true, false, false, true, false)
-FPSCHED_INSTANTIATE(false, false, true, true, false)
-FPSCHED_INSTANTIATE(true, false, true, true, false)
-FPSCHED_INSTANTIATE(false, false, false, false, true)
-FPSCHED_INSTANTIATE(true, false, false, false, true)
+#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES)                                                              \
+  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES>(ListTables, const uint16_t*, long long, int, long long*, \
+                                                                    long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
+FPSCHED_INSTANTIATE(false, false, false, false, false, false)
+FPSCHED_INSTANTIATE(true, false, false, false, false, false)
+FPSCHED_INSTANTIATE(false, true, false, false, false, false)
+FPSCHED_INSTANTIATE(true, true, false, false, false, false)
+FPSCHED_INSTANTIATE(false, false, true, false, false, false)
+FPSCHED_INSTANTIATE(true, false, true, false, false, false)
+FPSCHED_INSTANTIATE(false, false, false, true, false, false)
+FPSCHED_INSTANTIATE(true, false, false, true, false, false)
+FPSCHED_INSTANTIATE(false, false, true, true, false, false)
+FPSCHED_INSTANTIATE(true, false, true, true, false, false)
+FPSCHED_INSTANTIATE(false, false, false, false, true, false)
+FPSCHED_INSTANTIATE(true, false, false, false, true, false)
+FPSCHED_INSTANTIATE(false, false, false, false, false, true)
 #undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched
