@@ -115,9 +115,11 @@ struct SlotTables {
 //       it has no cross-stage edge); 1: the op never issues
 //     1 dur << 8 | tag it leaves: its stage, or kOwnTag
 //     2 byte offset of its slot for micro-batch 0 | mask of the bits of (word << 2) that are added to it << 16
-//     3 if the op has a second input or output: byte offset of a second row | kRowTwoOut | sign bit: two inputs.  An op
+//     3 if the op has a second input or output (not in the plain form): byte offset of a second row | kRowTwoOut | sign bit: two inputs.  An op
 //       with two inputs waits for its second one first: words 0 and 2 are then the second input's.
-//     (problems none of whose ops has a second input or output: 2 the mask, 3 the offset)
+//     Narrow forms without second rows beside the row: 2 the mask | 16-byte rows in front of the row that follows << 18
+//     (0: none), 3 the offset.  The plain form keeps second edges in rows that follow: [takes in the second input: no cost,
+//     leaves an empty slot] [the op] [leaves the second output: expects an empty slot, no cost].  In the other forms:
 //   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 the
 //     second output's link row in the links form
 //   Wide form (times beyond 24 bits; a slot is two dwords, the time and the tag): word 0 is the latency, word 1 the

@@ -65,7 +65,9 @@ struct fpsched_problem {
   int32_t* d_list_ints = nullptr;
   int32_t check_rows_per_wave = 0, check_waves = 0, check_grid = 0, check_vbits = 0;
   int32_t time_waves = 0, time_grid = 0;   // wavefronts per workgroup, resident workgroups
-  std::vector<int32_t> list_image;         // host copy of d_list_ints
+  // what the variants' tables are made from: as ltab and its image, second edges as the variants read them
+  ListTables variants_tab{};
+  std::vector<int32_t> variants_image;
   ListVariant lists_links, lists_mb, lists_both, lists_sync;
   ListVariant lists_times;                 // the lists without their W items, first pass of the sliding pass
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
@@ -291,8 +293,9 @@ std::vector<EdgeSlot> edge_slots(const StageEdges& e, int dir) {
 // n_forward, n_backward: slot classes of either direction.  items: per stage (m, or fewer where an item is a group of micro-batches).  Returns false if the problem does not fit:
 // more than two edge slots of a stage in one direction, or times, latencies,
 // stages or slots beyond the widths of their fields.
+// follow: second edges are rows of their own that follow the op's (the plain narrow form; device_tables.h).
 bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& edges, int n_forward, int n_backward, bool wide,
-                     const std::vector<int32_t>& items, ListTables* tables, bool* deg2, std::vector<int32_t>* image) {
+                     bool follow, const std::vector<int32_t>& items, ListTables* tables, bool* deg2, std::vector<int32_t>* image) {
   const int D = p->D, S = p->S, m = p->m;
   const int32_t* dur = &p->host_ints[p->tables.off_dur];
   const int32_t* mem_units = &p->host_ints[p->tables.off_mem_units];
@@ -310,7 +313,7 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
     for (int dir = 0; dir < 2; ++dir) {
       const size_t n = edge_slots(edges[s], dir).size();
       if (n > 2) return false;
-      if (n > 1) { *deg2 = true; n_second += dir == 0 ? 2 : 1; }
+      if (n > 1) { *deg2 = true; n_second += (dir == 0 ? 2 : 1) * (follow ? 2 : 1); }
     }
   }
   const int row_ints = 4;
@@ -375,6 +378,25 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
             continue;
           }
           int32_t* second = &J[second_at];
+          if (follow) {
+            // (SPLIT below: the row's number stands above the mask of 16 bits and two of the word that it is applied to)
+            auto in_front_of = [&](int32_t* row, int32_t at) { row[3] = at / 4; };
+            int32_t* main = t;
+            if (in) {
+              for (int i = 0; i < 4; ++i) second[i] = t[i];
+              main = second;
+              t[0] = wait; t[1] = (int32_t)(kEmptySlot & 0xffu); t[2] = slot;
+              in_front_of(t, second_at);
+              second_at += 4;
+            }
+            if (slots[e].out) {
+              int32_t* last = &J[second_at];
+              last[0] = -(int32_t)(kEmptySlot & 0xffu); last[1] = (int32_t)own_tag; last[2] = slot;
+              in_front_of(main, second_at);
+              second_at += 4;
+            }
+            continue;
+          }
           second[0] = t[0]; second[1] = t[2]; second[2] = slot;
           if (wide) second[3] = t[3] & 0xff00;
           const unsigned flags = (slots[e].out ? kRowTwoOut : 0u) | (in ? 1u << 31 : 0u);
@@ -387,12 +409,13 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
           second_at += 4;
         }
       }
-  // (without second rows the last word of a row is free: the slot's mask and offset in a word each)
-  if (!*deg2 && !wide)
-    for (int i = 0; i < kNKinds * kMaxChunks * D; ++i) {
+  // (without second rows beside them: the slot's mask and offset in a word each, above the mask the row that follows)
+  if ((!*deg2 || follow) && !wide)
+    for (int i = 0; i < second_at / row_ints; ++i) {
       int32_t* t = &J[(size_t)i * row_ints];
+      const uint32_t behind = (uint32_t)t[3];
       t[3] = t[2] & 0xffff;
-      t[2] = (int32_t)((uint32_t)t[2] >> 16);
+      t[2] = (int32_t)((uint32_t)t[2] >> 16 | behind << 18);
     }
   for (int d = 0; d < D; ++d) {
     J[(size_t)T.off_dev + 2 * d] = p->n_chunks[d];
@@ -411,7 +434,11 @@ void build_list_tables(fpsched_problem* p, const std::vector<StageEdges>& edges,
   p->check_vbits = max_chunks <= 1 ? 0 : (max_chunks <= 2 ? 1 : 2);
   ListTables& T = p->ltab;
   bool deg2 = false;
-  if (!fill_list_image(p, edges, n_classes, n_classes, wide, std::vector<int32_t>(p->S, p->m), &T, &deg2, image)) return;
+  const std::vector<int32_t> items(p->S, p->m);
+  if (!fill_list_image(p, edges, n_classes, n_classes, wide, false, items, &T, &deg2, image)) return;
+  p->variants_tab = T;
+  p->variants_image = *image;
+  if (deg2 && !wide && !fill_list_image(p, edges, n_classes, n_classes, wide, true, items, &T, &deg2, image)) return;
   // order pass: as many rows per wavefront as the states leave room for
   WorkgroupShape check{0, 1};
   int rows = 64;
@@ -422,6 +449,7 @@ void build_list_tables(fpsched_problem* p, const std::vector<StageEdges>& edges,
   }
   const WorkgroupShape time = timing_shape(&T, slot_bytes, p->max_lds);
   if (check.waves < 1 || time.waves < 1) return;
+  p->variants_tab.check_wave_bytes = T.check_wave_bytes;
   p->check_rows_per_wave = rows;
   p->check_waves = check.waves;
   p->check_grid = p->n_cu * check.groups;
@@ -468,12 +496,12 @@ int install_list_variant(fpsched_problem* p, ListTables T, const std::vector<int
 int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVariant* v) {
   v->ok = false;
   if (!p->lists_ok || p->lists_wide) return FPSCHED_EUNSUPPORTED;
-  const ListTables& B = p->ltab;
+  const ListTables& B = p->variants_tab;
   const int D = p->D, S = p->S, m = p->m, n_rows = kNKinds * kMaxChunks * D;
   const std::vector<int32_t>& I = p->host_ints;
   const DevTables& G = p->tables;
   ListTables T = B;
-  std::vector<int32_t> J(p->list_image.begin(), p->list_image.begin() + B.n_time_ints);
+  std::vector<int32_t> J(p->variants_image.begin(), p->variants_image.begin() + B.n_time_ints);
   auto row_at = [&](int kind, int c, int d) { return (kind * kMaxChunks + c) * D + (d & 1) * ((D + 1) / 2) + d / 2; };
   if (links) {
     // links of a device: the devices its stages send to (activations to successor stages, gradients to predecessor
@@ -552,7 +580,7 @@ int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVa
   }
   J.resize((J.size() + 7) & ~(size_t)7, 0);
   T.n_time_ints = (int32_t)J.size();
-  J.insert(J.end(), p->list_image.begin() + B.off_check, p->list_image.end());
+  J.insert(J.end(), p->variants_image.begin() + B.off_check, p->variants_image.end());
   T.off_check = T.n_time_ints;
   T.off_dev = T.off_check + (B.off_dev - B.off_check);
   if (mb)   // (the busy time is the timing pass's)
@@ -565,7 +593,7 @@ int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVa
 int build_times_variant(fpsched_problem* p) {
   ListVariant* v = &p->lists_times;
   ListTables T = p->ltab;
-  std::vector<int32_t> J = p->list_image;
+  std::vector<int32_t> J = p->variants_image;   // (no second edges: the plain model's too)
   const int D = p->D;
   for (int c = 0; c < kMaxChunks; ++c)
     for (int d = 0; d < D; ++d) {
@@ -975,7 +1003,6 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
                                  reinterpret_cast<const void*>(time_kernel_of(p->lists_deg2, p->lists_wide))})
         ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
       p->ltab.ints = p->d_list_ints;
-      p->list_image = list_image;
     }
     if (ok && p->slots_ok) {
       ok = hipMalloc(&p->d_slot_ints, p->slot_ints.size() * sizeof(int32_t)) == hipSuccess &&
@@ -1654,7 +1681,7 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
     ListTables LT;
     bool two = false;
     std::vector<int32_t> image;
-    if (fill_list_image(p, edges, n_of[0], n_of[1], false, items, &LT, &two, &image)) {
+    if (fill_list_image(p, edges, n_of[0], n_of[1], false, false, items, &LT, &two, &image)) {
       // group rows behind the timing rows
       std::vector<int32_t> rows((kNKinds * kMaxChunks * D + 7) & ~7, 0x10001);
       for (int kind : {(int)kF, (int)kFD, (int)kB})

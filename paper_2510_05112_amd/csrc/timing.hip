@@ -24,6 +24,12 @@
 // slot[dir][class][j] = finish << 8 | producer stage.  A consumer finds its input iff the tag names its upstream
 // stage.  No order of micro-batches is assumed and a producer never has to wait for room.
 //
+// Second inputs and outputs (DEG2), plain form: an op is up to three rows that follow each other, each of them a step like
+// any other op's: the first takes in the second input (no cost; it leaves the slot it has read empty), the second is the op,
+// the third leaves the second output (no cost).  So a step has one comparison more, and nothing that only few ops need: with
+// a second row beside the first, read by every lane in every step, 131,072 candidates of 16 devices (two towers), 64
+// micro-batches, offload took 0.88 ms instead of 0.77.  The other forms still have that.
+//
 // WIDE: finish times of up to 31 bits (durations in microseconds: 16 devices x 64 micro-batches pass 2^24 within a few
 // dozen ops) take two words per slot, the time and the tag, and the tag is compared on its own; otherwise the same.  The
 // host picks it where the bound on all times does not fit 24 bits or a latency not 16; the table kernel that such
@@ -109,7 +115,8 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
 //     made before this half's issued ops give way to the next ones, and their rows and words are on their way while the
 //     other half decides.
 // In flight at the beginning, oldest first: this half's slot, the other half's row and the word behind it.
-#define FPSCHED_STEP(X, Y, X_ROW, Y_ROW, RX, RY, RW, READ_AHEAD)                                                          \
+// (FOLLOW: for rows that another row follows in the place of the next word's, in the form with second edges)
+#define FPSCHED_STEP(X, Y, X_ROW, Y_ROW, RX, RY, RW, READ_AHEAD, FOLLOW, NOT_FOLLOWED)                                     \
   asm volatile(                                                                                                          \
       "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
       "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
@@ -121,10 +128,10 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
       "s_mov_b64 exec, -1\n\t" READ_AHEAD                                                                               \
       "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
       "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
-      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
+      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t" FOLLOW                                                         \
+      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t" NOT_FOLLOWED                                                            \
       "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
       "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
-      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
       "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
       "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
       "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
@@ -134,8 +141,18 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
         [other_row] "+{" Y_ROW "}"(Y.R), [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot),     \
         [other_next] "+v"(Y.w_next)                                                                                      \
       : [zero] "v"(0u), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),           \
-        [slots] "v"(slot_base)                                                                                           \
-      : "memory")
+        [slots] "v"(slot_base), [tables] "s"(tables)                                                                     \
+      : "memory", "vcc", "scc")
+// lanes whose row (its mask: RZ) has another one behind it fetch that and stay at their word
+#define FPSCHED_FOLLOW(RZ)                                                                                               \
+  "v_cmp_lt_u32 vcc, 0x3ffff, v" RZ "\n\t"                                                                              \
+  "s_cbranch_vccz .Lfollow%=\n\t"                                                                                       \
+  "s_mov_b64 exec, vcc\n\t"                                                                                             \
+  "v_lshrrev_b32 %[t], 14, v" RZ "\n\t"                                                                                 \
+  "v_add_u32 %[t], %[tables], %[t]\n\t"                                                                                 \
+  "s_mov_b64 exec, %[moved]\n\t"                                                                                        \
+  ".Lfollow%=:\n\t"
+#define FPSCHED_NOT_FOLLOWED "s_andn2_b64 exec, exec, vcc\n\t"
 #define FPSCHED_READ_AHEAD(WRITES, OZ, OW)                                                                               \
   "s_waitcnt lgkmcnt(" WRITES ")\n\t"                                                                                   \
   "v_and_b32 %[other_at], %[other_j], v" OZ "\n\t"                                                                      \
@@ -195,8 +212,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   static_assert(!SYNC || !(LINKS || MB), "");
   static_assert(!TIMES || !(DEG2 || WIDE || LINKS || MB || SYNC), "");
   constexpr unsigned kRowBytes = 16u;
-  constexpr bool PLAIN = !DEG2 && !WIDE && !LINKS && !MB && !SYNC;   // (TIMES too)
-  constexpr bool SPLIT = !DEG2 && !WIDE;   // rows with the slot's mask and offset in a word each
+  constexpr bool PLAIN = !WIDE && !LINKS && !MB && !SYNC;   // (TIMES too)
+  constexpr bool SPLIT = !WIDE && (!DEG2 || PLAIN);   // rows with the slot's mask and offset in a word each
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
   constexpr int kPieces = PLAIN ? 4 : 2;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
@@ -501,11 +518,11 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     return moved;
   };
 
-  // Every candidate ends after at most 2 D * stride + 2 rounds (each round but its last issues at least one of its at
-  // most D * stride ops, or takes in the second input of one), so the bound below is never reached; it only makes sure the wavefront leaves the loop
-  // whatever happens.
+  // Every candidate ends after at most 3 D * stride + 2 rounds (each round but its last issues at least one of its at
+  // most D * stride ops, takes in the second input of one or leaves the second output), so the bound below is never reached;
+  // it only makes sure the wavefront leaves the loop whatever happens.
   // (SYNC: an op takes in at most 2 m values)
-  const unsigned long long bound = (2ull * (unsigned)D * (unsigned)stride * (SYNC ? (unsigned long long)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
+  const unsigned long long bound = (3ull * (unsigned)D * (unsigned)stride * (SYNC ? (unsigned long long)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
     land(even, 0);
@@ -616,12 +633,19 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           } else {
             FPSCHED_ADVANCE(odd, even, "44", "47", "");
           }
-        } else {
-          FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"));
+        } else if constexpr (DEG2) {
+          FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"), FPSCHED_FOLLOW("42"), FPSCHED_NOT_FOLLOWED);
           if (sub + 1 < kRounds) {
-            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"));
+            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"), FPSCHED_FOLLOW("46"), FPSCHED_NOT_FOLLOWED);
           } else {
-            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "");
+            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "", FPSCHED_FOLLOW("46"), FPSCHED_NOT_FOLLOWED);
+          }
+        } else {
+          FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"), "", "");
+          if (sub + 1 < kRounds) {
+            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"), "", "");
+          } else {
+            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "", "", "");
           }
         }
         if (sub + 1 == kRounds)
