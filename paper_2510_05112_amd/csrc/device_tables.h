@@ -36,7 +36,7 @@ struct DevTables {
   int32_t off_n_chunks;     // [D]
   int32_t off_mem_cap;      // [D]
   // Timed form of the generator (generate.hip): one row per (instruction type F / B / W,
-  // chunk < gen_row_chunks, device), then one that changes nothing; -1 if the DAG has a stage with more than two inputs or
+  // chunk < gen_row_chunks, device); -1 if the DAG has a stage with more than two inputs or
   // outputs.  A row has two halves of four ints, all first halves stand in front of all second halves:
   //   0 duration   1 byte offset of the first input slot | of the first output slot << 16
   //   2 latency of the first input, or -2^30 if there is none   3 chunk | 4 for B

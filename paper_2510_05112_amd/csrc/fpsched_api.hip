@@ -783,7 +783,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       scl[soff[a] + sf[a]++] = edge_cls[e];
     }
     const int32_t dump = 4 * 2 * n_classes * m, none = -(1 << 30);   // slot offsets in bytes
-    const size_t n_rows = (size_t)3 * V * D + 1;
+    const size_t n_rows = (size_t)3 * V * D;
     std::vector<int32_t> rows(n_rows * 8, 0);
     for (size_t i = 0; i < n_rows; ++i) {
       int32_t* a = &rows[i * 4];
@@ -2043,7 +2043,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   // cost rows shared by the workgroup (the sliding form on a DAG of degree one needs the first halves only); per wavefront
   // its counters and its sets' slots, sliding: the rings of items and the queues (one bit per W item of a device at two
   // stages per device, two at four, none at one)
-  const int64_t shared_ints = (3ll * V * p->D + 1) * (slide && deg == 1 ? 4 : 8);
+  const int64_t shared_ints = 3ll * V * p->D * (slide && deg == 1 ? 4 : 8);
   DevTables tables = p->tables;
   // (one word more: the word of the next entry is written when all are in as well)
   tables.gen_queue_words = slide && V > 1 ? (int)((int64_t)V * p->m * (V == 2 ? 1 : 2) / 32) + 1 : 0;

@@ -20,10 +20,13 @@
 // What bounds it: a set's steps are a serial chain, and the steps of a set differ by a factor of ten (a low in-flight
 // limit makes a micro-batch's way through the stages the chain).  So the time is that of the longest sets where they
 // are few, else the vector instructions of a step (a step's LDS latency is hidden by the other wavefronts of a SIMD).
-// 16,384 sets of 32 devices, 2 stages each, 128 micro-batches (2,657 steps a set, 8,884 the longest), sliding form: 9.2 ms
-// before the sets were ordered, the actor's counters moved to registers and the W items out of the steps, 5.0 ms now (87 %
-// of the issue slots); 65,536 sets: 22.1 and 13.8 ms (135 and 106 vector instructions a step, no free issue slot now,
-// profiles/generate_kernel_cfg4.md); 32,768 sets of 16 devices, lists written: 2.5 ms before, 1.9 now.
+// A step of the form with the sliding pass takes 57 vector instructions at two stages per actor, and the placing of W items
+// behind it some 20 more; conditions are combined and state is changed by sets of lanes in scalar registers, and an item is
+// timed in the step behind its own, before which nothing waits for LDS that the next step does not wait for as well.
+// 16,384 sets of 32 devices, 2 stages each, 128 micro-batches (2,657 steps a set, 8,884 the longest): sliding form 4.84 ms
+// with 73 instructions, conditions as masks in vector registers, 4.22 now; results only 5.49 and 4.66, lists 5.04 and
+// 3.96; 4,096 sets of 16 devices, 64 micro-batches (the longest sets' chain): 0.77 and 0.75, 0.74 and 0.67, 0.66 and 0.54 ms;
+// 65,536 of 8 devices, 32 micro-batches: 0.90 and 0.81, 0.77 and 0.72, 0.78 and 0.70 ms.
 // Priorities (Section 5.2; Table of built-in values): computation type traversal priority
 // bwdpass-first / fwdpass-first / interleaved(unit1, unit2); stage traversal priority
 // breadth-first / depth-first with an optional interval, separately for forward and backward
@@ -49,14 +52,19 @@ typedef short pair16 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned bits_of(pair16 v) { return __builtin_bit_cast(unsigned, v); }
 __device__ __forceinline__ pair16 pair_of(unsigned v) { return __builtin_bit_cast(pair16, v); }
 constexpr unsigned kBothSigns = 0x80008000u;
-// The steps keep per-lane conditions that select several values as masks (all ones or 0) in a vector register: a select
+// settle keeps per-lane conditions that select several values as masks (all ones or 0) in a vector register: a select
 // is then one bit-field insert, where a comparison's result in a scalar register goes through 0 / 1 values when conditions
 // are combined.
 __device__ __forceinline__ unsigned mask_of(bool b) { return b ? ~0u : 0u; }
 __device__ __forceinline__ unsigned choose(unsigned mask, unsigned a, unsigned b) { return (a & mask) | (b & ~mask); }
+// The steps' conditions are sets of lanes in scalar registers, combined there, beside the vector instructions.
+typedef unsigned long long Lanes;
+__device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ballot_w64(l); }
+template <class A>
+__device__ __forceinline__ A of(Lanes l, A a, A b) { return in(l) ? a : b; }
 // An actor's traversal state of one direction (V > 1), in one register: the position (the chunk) from bit kPositionBit on
 // (two chunks: bit 4, so that the register is the shift that brings the position's half of a pair to the front), the
-// upper half the items until the position moves on by itself.  No position
+// upper half the items until the position moves on by itself, less one (negative: it does).  No position
 // sees more than kMaxChunks * m < kFarInterval items, so longer intervals are all the same.  Without an interval the
 // position never moves: the first eligible stage from the first (breadth-first) or last one (depth-first) on is picked.
 constexpr unsigned kPosition = 0x30u, kPositionBit = 4u, kOneItem = 0x10000u, kFarInterval = 0x3fffu;
@@ -160,22 +168,23 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   const int S = T.S, m = T.m, D = T.D;
   const int cpw = T.gen_sets;
   const bool has_w = T.has_w != 0;
-  // LDS: [edge lists, only if DEG == 0 | cost rows, only if TIMED: the first halves, then the second halves if they are
+  // LDS: [SLIDE: rings of all wavefronts][edge lists, only if DEG == 0 | cost rows, only if TIMED: the first halves, then the second halves if they are
   // needed] then per wavefront
   // [sets of the wavefront: counters [2][S]][a word holding m][a word: may there be sets left to draw]
-  // [row staging: 32 op words per lane, as 16 dwords laid out [dword][lane] | TIMED: the sets' slots, SLIDE: rings, queues]
-  const int n_rows = 3 * V * D + 1;
+  // [row staging: 32 op words per lane, as 16 dwords laid out [dword][lane] | TIMED: the sets' slots, SLIDE: queues]
+  int32_t* tab = lds + (SLIDE ? waves_per_block * (int)kEvents * 64 : 0);
+  const int n_rows = 3 * V * D;
   constexpr bool kSecondHalves = DEG > 1 || FORM == kGenTimed;
   const int n_tab = TIMED ? n_rows * (kSecondHalves ? 8 : 4) : (DEG == 0 ? T.n_table_ints : 0);
   if (TIMED) {
-    for (int i = threadIdx.x; i < n_tab; i += blockDim.x) lds[i] = T.ints[T.off_gen_rows + i];
+    for (int i = threadIdx.x; i < n_tab; i += blockDim.x) tab[i] = T.ints[T.off_gen_rows + i];
   } else if (DEG == 0) {
     for (int i = lane; i < n_tab; i += 64) lds[i] = T.ints[i];
   }
   const int n_count_ints = (cpw * 2 * S + 2 + 3) & ~3;
   const int slot_words = T.gen_slot_words;
   const int queue_words = SLIDE ? T.gen_queue_words : 0;   // per lane
-  int32_t* counts = lds + n_tab + wave * (n_count_ints + (TIMED ? cpw * slot_words + (SLIDE ? 64 * (kEvents + queue_words) : 0) : kStagingWords * 64));
+  int32_t* counts = tab + n_tab + wave * (n_count_ints + (TIMED ? cpw * slot_words + (SLIDE ? 64 * queue_words : 0) : kStagingWords * 64));
   // a counter that is always "done" (value m) stands in for a missing neighbour
   const int at_m = cpw * 2 * S;
   if (lane == 0) { counts[at_m] = m; counts[at_m + 1] = 1; }
@@ -245,17 +254,18 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
     }
     w_total += m * w_dur[c];
   }
-  // SLIDE: the ring of items (at: byte offset of the next one in and out), the one whose gap is being filled and what is
+  // SLIDE: the ring of items (LDS address of the next one in and out), the one whose gap is being filled and what is
   // left of its gap, the queue (entries in and out, the word being filled)
-  const unsigned ring = lds_address(counts + n_count_ints + cpw * slot_words) + lane * 4;   // entry i at + i * 256
-  const unsigned queue = ring + kEvents * 256;                                               // word i at + i * 256
-  unsigned ring_in = 0u, ring_out = 0u, gap = 0u, q_in = 0u, q_out = 0u, q_tail = 0u;
+  const unsigned ring = lds_address(lds) + wave * kEvents * 256 + lane * 4;   // entry i at + i * 256; a multiple of its size + lane * 4
+  const unsigned queue = lds_address(counts + n_count_ints + cpw * slot_words) + lane * 4;   // word i at + i * 256
+  auto on_ring = [&](unsigned at) -> unsigned { return (at & (kEvents - 1u) * 256u) | ring; };
+  unsigned ring_in = ring, ring_out = ring, gap = 0u, q_in = 0u, q_out = 0u, q_tail = 0u;
   int w_placed = 0;
   unsigned event = 0u, has_event = 0u;   // (mask)
   // one round: the oldest stashed W item runs if what is left of the gap has room for it; else the gap's item starts, and
   // the next one's gap opens
   auto settle = [&]() {
-    const unsigned next = lds_read<unsigned>(ring + ring_out);
+    const unsigned next = lds_read<unsigned>(ring_out);
     unsigned dur = (unsigned)w_dur[0], freed = (unsigned)w_free[0], units = (unsigned)f_units[0];
     if constexpr (V > 1) {
       const unsigned word = lds_read<unsigned>(queue + q_out / kQueueEntries * 256u);
@@ -287,7 +297,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
     gap = choose(run_w, gap - dur, next >> 3 & more);
     event = choose(run_w, event, next);
     has_event = choose(run_w, has_event, more);
-    ring_out = (ring_out + (256u & more & ~run_w)) & (kEvents * 256u - 1u);
+    ring_out = on_ring(ring_out + (256u & more & ~run_w));
   };
 
   // the actor's own counters, two stages per register
@@ -295,16 +305,17 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   unsigned n_f[NP], n_b[NP], n_w[NP], n_bl[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) { n_f[i] = 0u; n_b[i] = 0u; n_w[i] = 0u; n_bl[i] = 0u; }
-  int w_wait = 0;   // SLIDE: B items scheduled up to last_pick whose W item is not
 
-  // TIMED: the item scheduled in the last step, not timed yet: its row (without one: the row that changes nothing) and where
-  // its micro-batch's slots are
-  unsigned row_f = lds_address(lds) + d * 16, row_b = row_f + V * D * 16;
+  // TIMED: the items scheduled in the last step, not timed yet: the lanes that have one, its row and where its
+  // micro-batch's slots are (of every other step in registers of their own: a lane without an item keeps an older one's)
+  unsigned row_f = lds_address(tab) + d * 16, row_b = row_f + V * D * 16;
   asm("" : "+v"(row_f), "+v"(row_b));
-  const unsigned no_row = lds_address(lds) + (n_rows - 1) * 16;
-  int4 item_a = make_int4(0, 0, 0, 0), item_b = item_a;
-  unsigned item_slot = slot;
-  bool item = false;
+  struct Item { int4 a, b; unsigned slot; };
+  Item items_of[2] = {{make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0), slot}, {make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0), slot}};
+  Lanes items = 0;
+  // where the actor's counters are: of chunk 0, and how much further that of the last chunk is (V == 2)
+  const unsigned own_f = own_at[0], own_b = own_at[0] + 4u * (unsigned)S;
+  const int own_step = (int)(own_at[V - 1] - own_at[0]);
 
   // per-set state
   long long set = ((long long)blockIdx.x * waves_per_block + wave) * cpw + seg;   // the first set of a segment is its global index
@@ -312,15 +323,18 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   int set_class = 3;
   bool has_set = false;   // the segment is working on a set (possibly finished and not yet written out)
   bool fresh = true;      // the segment wants its next set
-  int unit_f = 1, unit_b = 1;
   unsigned walk_f = 0u, walk_b = 0u, again_f = 0u, again_b = 0u;   // traversal states, and what they become on a move
-  unsigned moves_f = 0u, moves_b = 0u, up_f = 0u, up_b = 0u;   // masks: an interval is set; breadth-first
-  unsigned f_first = ~0u;   // mask: F is the instruction type tried first in a step; fixed, or the interleaved priority's turn
-  int run = 0;         // items of that type until the turn changes
+  bool moves_f = false, moves_b = false, up_f = true, up_b = true;   // an interval is set; breadth-first
+  Lanes moving_f = 0, moving_b = 0, upward_f = 0, upward_b = 0;      // (of all lanes)
+  // The instruction type tried first in a step: F where it is not negative, else B; fixed, or the interleaved priority's
+  // turn: an item of the type whose turn it is counts down from unit_f - 1 to -unit_b and then begins anew
+  int turn_at = 0, turn_end = 0, turn_begin = 0;
   bool live = false;   // the set's process is still running
   int status = 0, len = 0, stored = 0;
   unsigned first_step = 0u;   // the loop's step counter when the set's process began
-  unsigned last_pick = 0u;    // the step in which this actor scheduled its last item so far (first_step - 1: none; SLIDE: W items aside)
+  // the step behind the one in which this actor scheduled its last item so far (first_step: none).  SLIDE: the step behind
+  // the last W item if those up to here filled the steps from then on in which nothing else is eligible
+  unsigned next_step = 0u;
   int steps = 0;
   uint16_t* row = ops;
   // "does any lane of my segment ...": the ballot against the lanes of the segment
@@ -417,8 +431,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
         const bool has_row = has_set && has_dev;
         if (has_dev)   // (also without a set: what the counters hold is compared with this actor's m items done)
           for (int i = d; i < 2 * S; i += D) counts[base + i] = 0;
-        int cttp = 0, f_dir = 0, f_int = 0, b_dir = 0, b_int = 0;
-        unit_f = 1; unit_b = 1;
+        int cttp = 0, unit_f = 1, unit_b = 1, f_dir = 0, f_int = 0, b_dir = 0, b_int = 0;
         // (with a selection, output row `set` is the schedule of parameter set select[set]; an entry that
         // is negative or not below n_src selects nothing and counts as a bad set)
         const long long src = (has_set && select) ? select[set] : set;
@@ -442,39 +455,36 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
           n_bl[i] += n_b[i];
           n_w[i] = has_w ? none0 | none1 : (unsigned)m * 0x00010001u;
         }
-        w_wait = 0;
         // a parameter set with a value outside its domain generates nothing (status 4)
         bool bad = (has_row && !has_src) || cttp < 0 || cttp > 2 || unit_f < 1 || unit_b < 1 || f_dir < 0 || f_dir > 1 || f_int < 0 ||
                    b_dir < 0 || b_dir > 1 || b_int < 0 || (cttp != 2 && (unit_f != 1 || unit_b != 1));
 #pragma unroll
         for (int c = 0; c < V; ++c) bad = bad || limit[c] < 1;
         const bool set_bad = any_in_segment(__ballot(bad && has_row));
-        f_first = mask_of(cttp != 0);
-        run = cttp == 2 ? unit_f : 0x7fffffff;
+        turn_begin = unit_f - 1;
+        turn_end = cttp == 2 ? -unit_b : (int)0x80000000;
+        turn_at = cttp == 2 ? turn_begin : (cttp != 0 ? 0x7fffffff : -1);
         const unsigned last_chunk = nch > 0 ? (unsigned)(nch - 1) << kPositionBit : 0u;
-        moves_f = mask_of(f_int > 0); moves_b = mask_of(b_int > 0);
-        up_f = mask_of(f_dir == 0); up_b = mask_of(b_dir == 0);
-        again_f = f_int > 0 ? (min((unsigned)f_int, kFarInterval) - 1u) << 16 : kOneItem;
-        again_b = b_int > 0 ? (min((unsigned)b_int, kFarInterval) - 1u) << 16 : kOneItem;
+        moves_f = f_int > 0; moves_b = b_int > 0;
+        up_f = f_dir == 0; up_b = b_dir == 0;
+        again_f = f_int > 0 ? (min((unsigned)f_int, kFarInterval) - 2u) << 16 : 0u;
+        again_b = b_int > 0 ? (min((unsigned)b_int, kFarInterval) - 2u) << 16 : 0u;
         walk_f = again_f + kOneItem + (up_f ? 0u : last_chunk);
         walk_b = again_b + kOneItem + (up_b ? 0u : last_chunk);
         const bool any_item = has_row && !set_bad && nch > 0 && m > 0;
         if (!any_item)   // (nothing is ever eligible)
           for (int i = 0; i < NP; ++i) { n_f[i] = n_b[i] = n_w[i] = (unsigned)m * 0x00010001u; }
         live = any_in_segment(__ballot(any_item));
-        first_step = step_0; steps = 0; last_pick = step_0 - 1u;
-        if (TIMED) {
-          item_a = lds_read<int4>(no_row);
-          if (kSecondHalves) item_b = lds_read<int4>(no_row + n_rows * 16);
-          item_slot = slot;
-          item = false;
-        }
+        first_step = step_0; steps = 0; next_step = step_0;
         status = set_bad ? 4 : 0; len = 0; stored = 0;
         free_at = 0; mem = 0; peak = 0;
-        ring_in = 0u; ring_out = 0u; has_event = 0u; event = 0u; gap = 0u; q_in = 0u; q_out = 0u; q_tail = 0u; w_placed = 0;
+        ring_in = ring; ring_out = ring; has_event = 0u; event = 0u; gap = 0u; q_in = 0u; q_out = 0u; q_tail = 0u; w_placed = 0;
         if (!TIMED) row = ops + (size_t)(has_row ? set * D + d : 0) * (size_t)stride;
         fresh = has_set && !live;   // nothing to schedule (a bad set, no stages): written out next time round
       }
+      moving_f = __ballot(moves_f);
+      moving_b = __ballot(moves_b);
+      if (V > 2) { upward_f = __ballot(up_f); upward_b = __ballot(up_b); }
       if (__ballot(has_set) == 0ull) break;   // every segment of the wavefront is out of work
       if (n_classes > 1) {
         const int longest = __ballot(has_set && set_class == 0) ? 3 : (__ballot(has_set && set_class == 1) ? 2 : (__ballot(has_set && set_class == 2) ? 1 : 0));
@@ -484,11 +494,8 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
         else __builtin_amdgcn_s_setprio(0);
       }
     }
-    bool picked = false;
-    // (two steps per iteration: the new item's row and the old one's change registers)
-#pragma unroll 2
-    for (int turn = 0; turn < kStepsPerLook; ++turn) {
-      const unsigned step = step_0 + (unsigned)turn;
+    Lanes picked = 0;
+    auto take_step = [&](const unsigned step, Item& now, const Item& last) {
       // ---- read phase: the neighbouring stages' counters, then for which stages the next item of each type is eligible
       // (dependencies resolved, and for forward items the in-flight rule): every comparison a packed subtraction whose
       // sign bits (bit 15: first stage, bit 31: second) say "eligible".  A missing stage never is.
@@ -528,11 +535,11 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
           b_ahead[i].x = (short)ba[0]; b_ahead[i].y = (short)ba[1];
         }
       }
-      // (TIMED: the inputs of the last step's item, all timed by now)
+      // (TIMED: the inputs of the last step's items, all timed by now; a lane without one reads some slot)
       int ready = 0, ready2 = 0;
       if (TIMED) {
-        ready = lds_read<int>(item_slot + (item_a.y & 0xffff));
-        if (DEG > 1) ready2 = lds_read<int>(item_slot + (item_b.z & 0xffff));
+        ready = lds_read<int>(last.slot + (last.a.y & 0xffff));
+        if (DEG > 1) ready2 = lds_read<int>(last.slot + (last.b.z & 0xffff));
       }
       unsigned el_f[NP], el_b[NP], el_w[NP];
 #pragma unroll
@@ -542,134 +549,160 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
         el_b[i] = bits_of(nb - __builtin_elementwise_min(nf, b_ahead[i])) & kBothSigns;
         el_w[i] = SLIDE ? 0u : bits_of(pair_of(n_w[i]) - nb) & kBothSigns;
       }
-      // ---- the step function, without branches: the first instruction type, in priority order, with an eligible item
+      // ---- the step function: the first instruction type, in priority order, with an eligible item
       unsigned any_f = el_f[0], any_b = el_b[0], any_w = el_w[0];
       if (V > 2) { any_f |= el_f[NP - 1]; any_b |= el_b[NP - 1]; any_w |= el_w[NP - 1]; }
-      const unsigned any_first = choose(f_first, any_f, any_b), any_other = choose(f_first, any_b, any_f);
-      const unsigned hit = mask_of(any_first != 0u);
-      const unsigned any_fb = any_first != 0u ? any_first : any_other;
-      const unsigned is_f = ~(f_first ^ hit);   // (unless there is no F or B item: then B, or W)
-      const bool is_w = !SLIDE && any_fb == 0u;
-      picked = (SLIDE ? any_fb : any_fb | any_w) != 0u;
+      const Lanes b_first = __ballot(turn_at < 0);
+      const unsigned any_first = of(b_first, any_b, any_f), any_other = of(b_first, any_f, any_b);
+      const Lanes hit = __ballot(any_first != 0u), is_f = hit ^ b_first;
+      const unsigned any_fb = of(hit, any_first, any_other);
+      const Lanes some_fb = __ballot(any_fb != 0u), is_w = SLIDE ? 0ull : ~some_fb;
+      picked = SLIDE ? some_fb : __ballot((any_fb | any_w) != 0u);
+      const Lanes picked_f = some_fb & is_f, picked_b = some_fb & ~is_f;
+      // the interleaved priority's turn
+      turn_at -= of(hit, 1, 0);
+      turn_at = turn_at < turn_end ? turn_begin : turn_at;
       auto by_type = [&](unsigned f, unsigned b, unsigned w) {
-        const unsigned fb = choose(is_f, f, b);
-        return !SLIDE && is_w ? w : fb;
+        const unsigned fb = of(is_f, f, b);
+        return SLIDE ? fb : of(is_w, w, fb);
       };
-      // ... then the stage
+      const Lanes timed = items;
+      if (TIMED) items = picked;
+      // ... then the stage.  (From here on all lanes do what those with an item need; where that changes the actor's state
+      // it is done for those only.  A branch around it would make the items' timing wait for what stands behind it.)
       unsigned pick = 0u;   // chunk << kPositionBit
-      unsigned walked = 0u;
       if constexpr (V > 1) {
         const unsigned walk = by_type(walk_f, walk_b, kOneItem);
-        bool move;
+        Lanes move;
         if constexpr (V == 2) {
-          // the eligible ones with the position's half in front: it is taken unless it is not eligible or has had its
-          // items and the other one is eligible
-          const unsigned el = !SLIDE && is_w ? el_w[0] : any_fb;
+          // the eligible ones with the position's half in the low half: it is taken unless it is not eligible or has had
+          // its items and the other one is eligible
+          const unsigned el = SLIDE ? any_fb : of(is_w, any_w, any_fb);
           const unsigned turned = __builtin_amdgcn_alignbit(el, el, walk);
-          move = (turned == 0x80000000u) | (walk < kOneItem);
-          pick = (walk & 16u) ^ ((move & ((int)turned < 0)) ? 16u : 0u);
+          const unsigned other = turned & (walk | ~(turned << 16));   // (its sign)
+          pick = (walk ^ (other >> 27)) & 16u;
+          move = __ballot((int)(walk | other) < 0);
         } else {
           const unsigned el0 = by_type(el_f[0], el_b[0], el_w[0]), el1 = by_type(el_f[NP - 1], el_b[NP - 1], el_w[NP - 1]);
           const unsigned ok = (el0 >> 15 & 1u) | (el0 >> 30 & 2u) | (el1 >> 13 & 4u) | (el1 >> 28 & 8u);
           // the next stage after p0, in the traversal direction and cyclically, that has an eligible item:
           // lay the mask out twice, shift it so that the stage after p0 is at bit 0, take the lowest bit
           // (depth-first: the same on the mirrored mask)
-          const bool up = by_type(up_f, up_b, ~0u) != 0u;
+          const Lanes up = (is_f & upward_f) | (~is_f & upward_b) | is_w;
           const int p0 = (int)((walk & kPosition) >> kPositionBit);
-          move = walk < kOneItem || !((ok >> p0) & 1u);
-          const unsigned mirrored = __brev(ok) >> (32 - nch);   // (nch = 0: ok is 0 and nothing is picked)
-          const unsigned line = up ? ok : mirrored;
-          const int q0 = up ? p0 : nch - 1 - p0;
+          move = __ballot((int)walk < 0) | __ballot(((ok >> p0) & 1u) == 0u);
+          const unsigned mirrored = __brev(ok) >> (32 - nch);   // (without an item ok is 0 and the chunk some number)
+          const unsigned line = of(up, ok, mirrored);
+          const int q0 = of(up, p0, nch - 1 - p0);
           const unsigned twice = line | (line << nch);
           int q1 = q0 + 1 + low_bit(twice >> (q0 + 1));
           q1 = q1 >= nch ? q1 - nch : q1;
-          const int moved_to = up ? q1 : nch - 1 - q1;
-          pick = (unsigned)(move ? moved_to : p0) << kPositionBit;
+          const int moved_to = of(up, q1, nch - 1 - q1);
+          pick = ((unsigned)of(move, moved_to, p0) & 3u) << kPositionBit;
         }
         asm("" : "+v"(pick));   // (not taken apart again)
-        walked = ((move ? choose(is_f, again_f, again_b) : walk - kOneItem) & ~kPosition) | pick;
+        const unsigned left = of(move, of(is_f, again_f, again_b), walk - kOneItem);
+        const unsigned walked = (left & ~kPosition) | pick;
+        walk_f = of(moving_f & picked_f, walked, walk_f);
+        walk_b = of(moving_b & picked_b, walked, walk_b);
       }
-      // the interleaved priority's turn
-      run += (int)hit;
-      const bool over = run == 0;
-      run = over ? (int)choose(f_first, (unsigned)unit_b, (unsigned)unit_f) : run;
-      f_first ^= mask_of(over);
-      unsigned next_row = no_row, next_slot = slot;
-      if (picked) {
-        // ---- write phase: the choice becomes visible for the next step; the counter's old value is
-        // the micro-batch of the item
-        const unsigned is_b = SLIDE ? ~is_f : ~is_f & mask_of(!is_w), is_f_too = SLIDE ? is_f : is_f & mask_of(!is_w);
-        if constexpr (V > 1) {
-          walk_f = choose(is_f_too & moves_f, walked, walk_f);
-          walk_b = choose(is_b & moves_b, walked, walk_b);
-        }
-        const unsigned half = V > 1 ? pick & 16u : 0u, one = V > 1 ? 1u << half : 1u;
-        unsigned old;
-        unsigned own = own_at[0];
-        if constexpr (V <= 2) {
-          old = by_type(n_f[0], n_b[0], n_w[0]);
-          n_f[0] += one & is_f_too;
-          n_b[0] += one & is_b;
-          n_bl[0] += one & is_b;
-          if (!SLIDE) n_w[0] += is_w ? one : 0u;
-          if (V == 2) own = pick != 0u ? own_at[V - 1] : own;
-        } else {
-          const unsigned hi = mask_of((pick & 32u) != 0u);
-          old = choose(hi, by_type(n_f[NP - 1], n_b[NP - 1], n_w[NP - 1]), by_type(n_f[0], n_b[0], n_w[0]));
-          const unsigned one0 = one & ~hi, one1 = one & hi;
-          n_f[0] += one0 & is_f_too; n_f[NP - 1] += one1 & is_f_too;
-          n_b[0] += one0 & is_b; n_b[NP - 1] += one1 & is_b;
-          n_bl[0] += one0 & is_b; n_bl[NP - 1] += one1 & is_b;
-          if (!SLIDE) { n_w[0] += is_w ? one0 : 0u; n_w[NP - 1] += is_w ? one1 : 0u; }
+      // ---- write phase: the choice becomes visible for the next step; the counter's old value is the micro-batch of the
+      // item.  Counts go up with the lanes of each type in turn, one instruction each.  (next_step: SLIDE, a step in which
+      // nothing else is eligible takes a W item while there is one.)
+      const unsigned half = V > 2 ? pick & 16u : pick, one = V > 1 ? 1u << (half & 31u) : 1u;
+      unsigned old, own = of(is_f, own_f, own_b);
+      unsigned hi = 0u;
+      if constexpr (V <= 2) {
+        old = by_type(n_f[0], n_b[0], n_w[0]);
+        // (the second chunk's counter: the upper half of `one` is 1)
+        if constexpr (V == 2) asm("v_mad_i32_i16 %0, %1, %2, %0 op_sel:[1,0,0,0]" : "+v"(own) : "v"(one), "v"(own_step));
+      } else {
+        hi = mask_of((pick & 32u) != 0u);
+        old = choose(hi, by_type(n_f[NP - 1], n_b[NP - 1], n_w[NP - 1]), by_type(n_f[0], n_b[0], n_w[0]));
+        unsigned first = own_at[0];
 #pragma unroll
-          for (int c = 1; c < V; ++c) own = pick == (unsigned)c << kPositionBit ? own_at[c] : own;
+        for (int c = 1; c < V; ++c) first = pick == (unsigned)c << kPositionBit ? own_at[c] : first;
+        own += first - own_at[0];
+      }
+      const unsigned j = V > 1 ? __builtin_amdgcn_ubfe(old, half, 16u) : old & 0xffffu, behind = j + 1u;
+      auto count = [&](unsigned& f, unsigned& b, unsigned& bl, unsigned& w, unsigned by) {
+        asm volatile("s_mov_b64 exec, %[is_b]\n\t"
+                     "v_add_u32 %[b], %[b], %[by]\n\t"
+                     "v_add_u32 %[bl], %[bl], %[by]\n\t"
+                     "s_mov_b64 exec, %[is_f]\n\t"
+                     "v_add_u32 %[f], %[f], %[by]\n\t"
+                     "s_mov_b64 exec, -1"
+                     : [b] "+v"(b), [bl] "+v"(bl), [f] "+v"(f) : [by] "v"(by), [is_b] "s"(picked_b), [is_f] "s"(picked_f));
+        if constexpr (!SLIDE) w += of(picked & is_w, by, 0u);
+      };
+      if constexpr (V <= 2) {
+        count(n_f[0], n_b[0], n_bl[0], n_w[0], one);
+      } else {
+        count(n_f[0], n_b[0], n_bl[0], n_w[0], one & ~hi);
+        count(n_f[NP - 1], n_b[NP - 1], n_bl[NP - 1], n_w[NP - 1], one & hi);
+      }
+      const Lanes counted = SLIDE ? picked : some_fb;
+      asm volatile("s_mov_b64 exec, %[counted]\n\t"
+                   "ds_write_b32 %[own], %[behind]\n\t"
+                   "s_mov_b64 exec, -1"
+                   : : [own] "v"(own), [behind] "v"(behind), [counted] "s"(counted) : "memory");
+      if constexpr (SLIDE) {
+        asm volatile("s_mov_b64 exec, %[all]\n\t"
+                     "v_lshl_add_u32 %[slot], %[j], 2, %[slots]\n\t"
+                     "v_max_u32 %[next], %[step], %[next]\n\t"
+                     "v_add_u32 %[next], 1, %[next]\n\t"
+                     "s_mov_b64 exec, %[is_b]\n\t"
+                     "v_add_u32 %[next], 1, %[next]\n\t"
+                     "s_mov_b64 exec, -1"
+                     : [next] "+v"(next_step), [slot] "+v"(now.slot)
+                     : [j] "v"(j), [slots] "v"(slot), [step] "s"(step), [all] "s"(picked), [is_b] "s"(picked_b));
+      } else {
+        next_step = of(picked, step + 1u, next_step);
+        if (TIMED) now.slot = of(picked, slot + j * 4u, now.slot);
+      }
+      if constexpr (TIMED) {
+        // the new item's row is on its way while the last step's is timed: cost, where its inputs' finish times
+        // are and where its own goes (byte offsets), memory
+        const unsigned next_row = __umul24(pick, (unsigned)D) + by_type(row_f, row_b, row_b + V * D * 16);
+        now.a = lds_read<int4>(next_row);
+        if (kSecondHalves) now.b = lds_read<int4>(next_row + n_rows * 16);
+        if (in(timed)) {
+          const int4 a = last.a, b = last.b;
+          ready += a.z;
+          if (DEG > 1) ready = max(ready, ready2 + b.w);
+          const int start = max(free_at, ready);
+          if (SLIDE) {
+            // (all W items of an actor together cost less than 2^29)
+            const unsigned wait = min((unsigned)(start - free_at), 0x1fffffffu);
+            lds_write<unsigned>(ring_in, wait << 3 | (unsigned)a.w);
+            ring_in = on_ring(ring_in + 256u);
+          }
+          free_at = start + a.x;
+          lds_write<int>(last.slot + ((unsigned)a.y >> 16), free_at);
+          if (DEG > 1) lds_write<int>(last.slot + ((unsigned)b.z >> 16), free_at);
+          if (!SLIDE) {
+            mem += b.x;
+            peak = max(peak, mem);
+            mem -= b.y;
+          }
         }
-        const unsigned j = (old >> half) & 0xffffu;
-        if (SLIDE || !is_w) lds_write<unsigned>(own + (is_b & (unsigned)S * 4u), j + 1u);
-        // (SLIDE: a step in which nothing else is eligible takes a W item while there is one)
-        if (SLIDE) w_wait = max(w_wait + (int)(last_pick + 1u - step), 0) + 1 + (int)is_f;
-        last_pick = step;
-        if constexpr (TIMED) {
-          next_row = __umul24(pick, (unsigned)D) + by_type(row_f, row_b, row_b + V * D * 16);
-          next_slot += j * 4u;
-        } else {
+      } else {
+        if (in(picked)) {
           const unsigned word = (by_type(1u, 2u, 3u) << 13) | (pick >> kPositionBit << 11) | j;
           reinterpret_cast<uint16_t*>(staging + ((len >> 1) & (kStagingWords - 1)) * 64)[len & 1] = (uint16_t)word;
           len += 1;
         }
       }
-      if constexpr (TIMED) {
-        // the new item's row is on its way while the last step's is timed: cost, where its inputs' finish times
-        // are and where its own goes (byte offsets), memory
-        const int4 a = item_a, b = item_b;
-        item_a = lds_read<int4>(next_row);
-        if (kSecondHalves) item_b = lds_read<int4>(next_row + n_rows * 16);
-        ready += a.z;
-        if (DEG > 1) ready = max(ready, ready2 + b.w);
-        const int start = max(free_at, ready);
-        if (SLIDE) {
-          // (all W items of an actor together cost less than 2^29)
-          const unsigned wait = min((unsigned)(start - free_at), 0x1fffffffu);
-          lds_write<unsigned>(ring + ring_in, wait << 3 | (unsigned)a.w);
-          ring_in = item ? (ring_in + 256u) & (kEvents * 256u - 1u) : ring_in;
-          item = picked;
-        }
-        free_at = start + a.x;
-        lds_write<int>(item_slot + ((unsigned)a.y >> 16), free_at);
-        if (DEG > 1) lds_write<int>(item_slot + ((unsigned)b.z >> 16), free_at);
-        if (!SLIDE) {
-          mem += b.x;
-          peak = max(peak, mem);
-          mem -= b.y;
-        }
-        item_slot = next_slot;
-      }
       __builtin_amdgcn_wave_barrier();
+    };
+    for (unsigned turn = 0; turn < kStepsPerLook; turn += 2) {
+      take_step(step_0 + turn, items_of[0], items_of[1]);
+      take_step(step_0 + turn + 1u, items_of[1], items_of[0]);
     }
     // ---- has the set's process ended?  Looked at every kStepsPerLook steps only: it has if a step schedules nothing (no
     // later step can then; SLIDE: W items, on which nothing depends, aside), and stays ended, so the few steps a segment
     // runs on change nothing, and the number of steps the process took is one more than the step of its last item.
-    const bool any_pick = any_in_segment(__ballot(picked));
+    const bool any_pick = any_in_segment(picked);
     if (!TIMED && len - stored >= 16) {
       const uint32_t* w = staging + ((stored >> 1) & (kStagingWords - 1)) * 64;
       uint4* dst = reinterpret_cast<uint4*>(row + stored);
@@ -691,7 +724,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
       for (int i = 0; i < NP; ++i) done = done && (SLIDE || !has_w ? n_b[i] : n_w[i]) == (unsigned)m * 0x00010001u;
       status = any_in_segment(__ballot(!done)) ? 1 : status;
       // (SLIDE: the W items that are left follow, one a step)
-      steps = segment_max((int)(last_pick - first_step) + (SLIDE ? w_wait : 0)) + 1;
+      steps = segment_max((int)(next_step - first_step));
       live = false;
       fresh = true;
     }
