@@ -48,6 +48,7 @@ struct DevTables {
   int32_t gen_row_chunks;   // 1, 2 or 4
   int32_t gen_slot_words;   // (2 * classes + 1) * m
   int32_t gen_sets;         // parameter sets per wavefront, at most 64 / D: as many as LDS holds, set per launch
+  int32_t gen_events;       // sliding form of the timed generator: items noted per lane, a power of two, set per launch
   int32_t gen_queue_words;  // sliding form of the timed generator: queue words per lane in LDS, set per launch
   int32_t off_turnaround;   // [S] generator steps from a micro-batch's forward item to its backward item, 2 * (longest path to a sink) + 1
   const int32_t* ints;      // DEVICE

@@ -2045,11 +2045,19 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   // stages per device, two at four, none at one)
   const int64_t shared_ints = 3ll * V * p->D * (slide && deg == 1 ? 4 : 8);
   DevTables tables = p->tables;
+  // A larger ring of items evens out lanes whose items come in bursts; but a set that ends has its ring emptied while the
+  // other sets of its wavefront wait.  So it pays where a set has many items per actor and a wavefront few sets.  Items
+  // per actor / sets per wavefront, rings of 16 and 32: 4 (65,536 sets of 4 x 16 x 2) 183 and 280 us, 16 (of 8 x 32 x 2) 800 and
+  // 820, 16 (of 4 x 128 x 1) 533 and 621, 32 (of 16 x 64 x 1) 916 and 933, 48 (30,000 of 12 x 40 x 3) 2439 and 2385, 60
+  // (16,384 of 6 x 100 x 3) 2360 and 2169, 64 (32,768 of 16 x 64 x 2) 1985 and 1960, 80 (16,384 of 10 x 120 x 2) 2167 and
+  // 1425, 256 (of 32 x 128 x 2) 4138 and 3970.  (64: 4735 on the last, whose wavefronts then do not all find room.)
+  const int sets_per_wave = 64 / p->D, items_per_actor = 2 * gen_max_chunks(p) * p->m;
+  tables.gen_events = items_per_actor >= 40 * sets_per_wave ? kGenMoreEvents : kGenFewEvents;
   // (one word more: the word of the next entry is written when all are in as well)
   tables.gen_queue_words = slide && V > 1 ? (int)((int64_t)V * p->m * (V == 2 ? 1 : 2) / 32) + 1 : 0;
   auto wave_ints_of = [&](int64_t sets) {
     return ((sets * 2 * p->S + 2 + 3) & ~3ll) + sets * p->tables.gen_slot_words +
-           (slide ? 64ll * (kGenEvents + tables.gen_queue_words) : 0ll);
+           (slide ? 64ll * (tables.gen_events + tables.gen_queue_words) : 0ll);
   };
   const int64_t lds_ints = p->max_lds / 4;
   int cpw = 64 / p->D;

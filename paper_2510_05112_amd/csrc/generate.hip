@@ -85,8 +85,7 @@ constexpr int kStepsPerLook = 8;
 constexpr int kStagingWords = kGenStagingWords;   // 15 op words and those of a look
 static_assert(2 * kStagingWords >= 15 + kStepsPerLook && (kStagingWords & (kStagingWords - 1)) == 0, "");
 constexpr int kRoundsPerLook = 4;   // rounds of settle between two looks at whether there are enough of them
-constexpr unsigned kEvents = kGenEvents;   // (a power of two)
-static_assert(kEvents > kStepsPerLook + 1, "a look's items fit");
+static_assert(kGenFewEvents > kStepsPerLook + 1, "a look's items fit");
 
 }  // namespace
 
@@ -147,7 +146,7 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 // a B item stashes its W item, and in front of every other item the actor runs the oldest
 // stashed items that end before the item starts.  None of this moves an F or B item, it only decides what memory is
 // resident at their starts; so the steps only note each item (its gap: how long the actor waits in front of it) in a ring
-// of kEvents words per lane, and a second loop (settle) places W items into gaps, for all lanes at once and only when
+// of T.gen_events words per lane, and a second loop (settle) places W items into gaps, for all lanes at once and only when
 // some lane's ring is nearly full: its rounds are then full of work, where in the step itself a few lanes' W items
 // would be waited for by all.  The stash is a queue of log2(V) bits per entry
 // (the chunk) in LDS: an actor stashes no more than V * m items, so entry i simply stands in word i * log2(V) / 32.
@@ -172,7 +171,8 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   // needed] then per wavefront
   // [sets of the wavefront: counters [2][S]][a word holding m][a word: may there be sets left to draw]
   // [row staging: 32 op words per lane, as 16 dwords laid out [dword][lane] | TIMED: the sets' slots, SLIDE: queues]
-  int32_t* tab = lds + (SLIDE ? waves_per_block * (int)kEvents * 64 : 0);
+  const unsigned ring_bytes = SLIDE ? (unsigned)T.gen_events * 256u : 0u;   // of a wavefront
+  int32_t* tab = lds + waves_per_block * (int)(ring_bytes / 4u);
   const int n_rows = 3 * V * D;
   constexpr bool kSecondHalves = DEG > 1 || FORM == kGenTimed;
   const int n_tab = TIMED ? n_rows * (kSecondHalves ? 8 : 4) : (DEG == 0 ? T.n_table_ints : 0);
@@ -256,9 +256,9 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   }
   // SLIDE: the ring of items (LDS address of the next one in and out), the one whose gap is being filled and what is
   // left of its gap, the queue (entries in and out, the word being filled)
-  const unsigned ring = lds_address(lds) + wave * kEvents * 256 + lane * 4;   // entry i at + i * 256; a multiple of its size + lane * 4
+  const unsigned ring = lds_address(lds) + wave * ring_bytes + lane * 4;   // entry i at + i * 256; a multiple of its size + lane * 4
   const unsigned queue = lds_address(counts + n_count_ints + cpw * slot_words) + lane * 4;   // word i at + i * 256
-  auto on_ring = [&](unsigned at) -> unsigned { return (at & (kEvents - 1u) * 256u) | ring; };
+  auto on_ring = [&](unsigned at) -> unsigned { return (at & (ring_bytes - 256u)) | ring; };
   unsigned ring_in = ring, ring_out = ring, gap = 0u, q_in = 0u, q_out = 0u, q_tail = 0u;
   int w_placed = 0;
   unsigned event = 0u, has_event = 0u;   // (mask)
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
     if (SLIDE) {
       // (a look adds at most kStepsPerLook items, and one place of the ring stays empty)
       const bool ended = live && !any_pick;
-      while (__ballot(((ring_in - ring_out) & (kEvents * 256u - 1u)) > (kEvents - 1 - kStepsPerLook) * 256u ||
+      while (__ballot(((ring_in - ring_out) & (ring_bytes - 1u)) > ring_bytes - (1 + kStepsPerLook) * 256u ||
                       (ended && (has_event != 0u || ring_in != ring_out))) != 0ull)
 #pragma unroll
         for (int i = 0; i < kRoundsPerLook; ++i) settle();

@@ -110,9 +110,9 @@ struct GenResults {
 };
 constexpr int kGenTimedThreads = 1024;
 // FORM: kGenPlain writes the lists; kGenTimed times them instead (above); kGenSlide times them after the
-// weight-gradient sliding pass (kGenEvents + T.gen_queue_words dwords of LDS more per lane)
+// weight-gradient sliding pass (T.gen_events + T.gen_queue_words dwords of LDS more per lane)
 constexpr int kGenPlain = 0, kGenTimed = 1, kGenSlide = 2;
-constexpr int kGenEvents = 16;         // kGenSlide: items noted per lane
+constexpr int kGenFewEvents = 16, kGenMoreEvents = 32;   // kGenSlide: items noted per lane (T.gen_events)
 constexpr int kGenStagingWords = 16;   // kGenPlain: dwords of op words staged per lane
 template <int V, int DEG, int FORM>
 __global__ void generate_kernel(DevTables T, const int32_t* policy, const int32_t* inflight, const long long* select,
