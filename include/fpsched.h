@@ -32,7 +32,7 @@
  * Environment variables, read when the call they belong to runs; none changes a result:
  *   FPSCHED_SLOT_WAVES=n  (fpsched_problem_create, the cost-model setters) at most n wavefronts per
  *                         workgroup of the evaluation kernels with mail slots, one workgroup per compute unit;
- *   FPSCHED_GEN_WAVES=n   (the fpsched_generate* calls) n resident wavefronts per compute unit, default 12;
+ *   FPSCHED_GEN_WAVES=n   (the fpsched_generate* calls) n resident wavefronts per compute unit, default 8 to 16;
  *   FPSCHED_MB_GLOBAL=1   (fpsched_problem_set_microbatch_costs) keep the cost table in device
  *                         memory even where it would fit LDS;
  *   FPSCHED_SYNC_SLOTS=1  (fpsched_problem_set_sync) the one-kernel form of the model even where the

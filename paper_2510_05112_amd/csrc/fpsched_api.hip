@@ -1906,24 +1906,16 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
 
 using GenKernel = void (*)(DevTables, const int32_t*, const int32_t*, const long long*, long long, long long, int, int, uint16_t*,
                            int32_t*, unsigned char*, unsigned long long*, GenResults);
-static int gen_waves_per_cu() {
-  // tuning knob: FPSCHED_GEN_WAVES = resident wavefronts per compute unit.  Three per SIMD: with more, the sets with the
-  // most steps advance more slowly and are what the launch ends on, with fewer the SIMDs are idle between steps (lists,
-  // 33,177 sets of 16 x 64 x 2: 2.00 ms with 8, 1.92 with 12, 2.10 with 16, 2.19 with 24; results only: 2.07, 2.05, 2.16,
-  // 2.43).  8, 12, 16, 20 and 24 measured on 13 problems of 2 to 32 devices: results only, 12 are within 4 % of the best
-  // (11 % on 32 x 128 x 2 without the sliding pass, where 8 are); lists, within 5 % up to 16 devices and 2 stages, but 8
-  // are 8 to 21 % faster for 24 devices or more and for four stages (16,276 sets of 32 x 128 x 2: 4.16 and 5.24 ms).
-  int waves_per_cu = 12;
-  if (const char* env = getenv("FPSCHED_GEN_WAVES")) {
-    const int v = atoi(env);
-    if (v >= 1 && v <= 32) waves_per_cu = v;
-  }
-  return waves_per_cu;
-}
 static int gen_max_chunks(const fpsched_problem* p) {
   int max_chunks = 0;
   for (int d = 0; d < p->D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
   return max_chunks;
+}
+
+// about how many draws from one counter a set's steps last as long as (about 1 us and 100 draws each; order_sets)
+static int64_t gen_steps(const fpsched_problem* p) {
+  const int64_t chunks = std::max(gen_max_chunks(p), 1);
+  return 15 * (p->has_w ? 3 : 2) * chunks * p->m * (1 + chunks);
 }
 
 // How the segments of a generator launch come by their sets.  No more sets than segments: each has its own (returns 0).
@@ -1941,7 +1933,7 @@ static int gen_max_chunks(const fpsched_problem* p) {
 static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const int64_t* d_select, int64_t n_src, int64_t n_sets,
                       int64_t n_segments, bool lists, uint8_t* d_status, unsigned long long* counter, hipStream_t st) {
   if (n_sets <= n_segments) return 0;
-  const int64_t chunks = std::max(gen_max_chunks(p), 1), steps = 15 * (p->has_w ? 3 : 2) * chunks * p->m * (1 + chunks);
+  const int64_t steps = gen_steps(p);
   const bool by_class = steps >= n_segments && (n_sets >= 2 * n_segments || (!lists && 2 * steps >= 3 * n_segments && 4 * n_sets >= 5 * n_segments));
   if (!by_class) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, (unsigned long long)n_segments, 0ull);
@@ -1950,8 +1942,44 @@ static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const
   if (n_sets >= (1ll << 33)) return FPSCHED_EINVAL;   // (more workgroups than a launch has)
   hipLaunchKernelGGL(generate_order_kernel, dim3((unsigned)((n_sets + 3) / 4)), dim3(256), 0, st, p->tables, d_inflight,
                      reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
-                     (int)(2 * chunks * p->m), d_status, counter);
+                     2 * std::max(gen_max_chunks(p), 1) * p->m, d_status, counter);
   return hipGetLastError() == hipSuccess ? kGenClasses : FPSCHED_EHIP;
+}
+
+// Launch shape of the generator: workgroups of one wavefront per SIMD, as many per compute unit as asked for and as LDS
+// holds.  (In larger ones the sets with most steps, which are drawn first, go to all wavefronts of a few compute units; those
+// of one wavefront come to the SIMDs unevenly.  16,384 sets of 32 x 128 x 2, eight wavefronts per compute unit as one
+// workgroup, two, eight: results only 4.57, 3.40 and 3.52 ms, lists 4.36, 2.94 and 3.21.)
+//
+// Wavefronts per compute unit: with more of them the sets with most steps advance more slowly and are what the launch ends
+// on, with fewer the SIMDs are idle between steps.  Short sets are drawn in plain order: 16 (65,536 sets of 4 x 16 x 2, sliding,
+// with 8, 12 and 16: 313, 280 and 179 us; of 8 x 32 x 2: 892, 823 and 802).  Else eight where the batch has few sets per
+// segment, measured by how much longer the longest sets are, which goes with the devices and with the stages, and twelve
+// beyond (results only, eight and twelve: 16,384 of 32 x 128 x 2, 4 sets per segment of eight wavefronts, 3.41 and 3.64 ms;
+// 32,768 of them, 8 per segment, 6.53 and 5.21; of 32 x 64 x 2, 4 and 6 per segment, 1.92 and 1.99, 2.82 and 2.37; of
+// 20 x 100 x 2, 2.7 and 5.3 per segment, 1.78 and 2.00, 3.27 and 2.79; 16,384 of 24 x 80 x 2, 4 per segment, 2.08 and 1.91;
+// 30,000 of 12 x 40 x 3, 2.9 per segment, 2.11 and 2.21; 32,768 of 16 x 64 x 2, 4 per segment, 1.84 and 1.65).
+struct GenShape { int waves; int64_t blocks, lds_bytes; };
+static GenShape gen_shape(const fpsched_problem* p, int64_t n_sets, int64_t sets_per_wave, int64_t shared_ints, int64_t wave_ints) {
+  const int64_t lds_ints = p->max_lds / 4, segments_of_8 = 8ll * p->n_cu * sets_per_wave;
+  int want = 16;
+  if (2 * gen_steps(p) >= 3 * segments_of_8) want = (double)n_sets < segments_of_8 * std::max(p->D / 6.4, p->S / 12.0) ? 8 : 12;
+  // tuning knob: FPSCHED_GEN_WAVES = resident wavefronts per compute unit
+  if (const char* env = getenv("FPSCHED_GEN_WAVES")) {
+    const int v = atoi(env);
+    if (v >= 1 && v <= 32) want = v;
+  }
+  int best_waves = 1, best_groups = 1;
+  for (int groups = 1; groups <= 8; ++groups) {
+    int wv = (int)std::min<int64_t>((lds_ints / groups - shared_ints - 64) / wave_ints, kGenThreads / 64);
+    wv = std::min(wv, want / groups);
+    if (wv >= 1 && wv * groups > best_waves * best_groups) { best_waves = wv; best_groups = groups; }
+  }
+  // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
+  const int64_t wavefronts = (n_sets + sets_per_wave - 1) / sets_per_wave;
+  best_waves = (int)std::clamp<int64_t>((wavefronts + p->n_cu - 1) / p->n_cu, 1, best_waves);
+  return GenShape{best_waves, std::min<int64_t>((wavefronts + best_waves - 1) / best_waves, (int64_t)p->n_cu * best_groups),
+                  4 * (shared_ints + best_waves * wave_ints)};
 }
 
 static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_policy, const int32_t* d_inflight,
@@ -1971,17 +1999,15 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
   if (workspace_bytes < 256) return FPSCHED_ENOMEM;
   const int deg = p->max_degree <= 1 ? 1 : (p->max_degree == 2 ? 2 : 0);
   // tables (if walked), counters and the constant word (a multiple of four), the staging dwords
-  auto lds_of = [&](int64_t sets) {
-    return 4ll * ((deg == 0 ? p->tables.n_table_ints : 0) + ((sets * 2 * p->S + 2 + 3) & ~3ll) + kGenStagingWords * 64);
-  };
+  const int64_t shared_ints = deg == 0 ? p->tables.n_table_ints : 0, lds_ints = p->max_lds / 4;
+  auto wave_ints_of = [&](int64_t sets) { return ((sets * 2 * p->S + 2 + 3) & ~3ll) + kGenStagingWords * 64; };
   int cpw = 64 / p->D;
-  while (cpw > 1 && lds_of(cpw) > p->max_lds) --cpw;
-  const int64_t lds_bytes = lds_of(cpw);
-  if (lds_bytes > p->max_lds) return FPSCHED_EUNSUPPORTED;
+  while (cpw > 1 && shared_ints + wave_ints_of(cpw) > lds_ints) --cpw;
+  const int64_t wave_ints = wave_ints_of(cpw);
+  if (shared_ints + wave_ints > lds_ints) return FPSCHED_EUNSUPPORTED;
   DevTables tables = p->tables;
   tables.gen_sets = cpw;
-  // persistent grid: as many single-wavefront workgroups as stay resident
-  const int64_t blocks = std::min<int64_t>((n_sets + cpw - 1) / cpw, (int64_t)p->n_cu * gen_waves_per_cu());
+  const GenShape shape = gen_shape(p, n_sets, cpw, shared_ints, wave_ints);
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
   const int V = max_chunks <= 1 ? 1 : (max_chunks <= 2 ? 2 : 4);
@@ -1990,14 +2016,14 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
       {&generate_kernel<2, 0, kGenPlain>, &generate_kernel<2, 1, kGenPlain>, &generate_kernel<2, 2, kGenPlain>},
       {&generate_kernel<4, 0, kGenPlain>, &generate_kernel<4, 1, kGenPlain>, &generate_kernel<4, 2, kGenPlain>}};
   const GenKernel kernel = table[V == 1 ? 0 : (V == 2 ? 1 : 2)][deg];
-  if (lds_bytes > 64 * 1024 &&
+  if (shape.lds_bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                           p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-  const int n_classes = order_sets(p, d_inflight, d_select, n_src, n_sets, blocks * cpw, true, d_status, counter, static_cast<hipStream_t>(hip_stream));
+  const int n_classes = order_sets(p, d_inflight, d_select, n_src, n_sets, shape.blocks * shape.waves * cpw, true, d_status, counter, static_cast<hipStream_t>(hip_stream));
   if (n_classes < 0) return n_classes;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), (size_t)lds_bytes,
+  hipLaunchKernelGGL(kernel, dim3((unsigned)shape.blocks), dim3(64 * shape.waves), (size_t)shape.lds_bytes,
                      static_cast<hipStream_t>(hip_stream), tables, reinterpret_cast<const int32_t*>(d_policy),
                      d_inflight, reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
                      n_classes, (int)stride_words, d_ops, d_steps, d_status, counter, GenResults{nullptr, nullptr, nullptr, nullptr});
@@ -2065,23 +2091,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   const int64_t wave_ints = wave_ints_of(cpw);
   if (shared_ints + wave_ints > lds_ints) return FPSCHED_EUNSUPPORTED;
   tables.gen_sets = cpw;
-  // wavefronts per workgroup and workgroups per compute unit: as many resident wavefronts as asked for
-  // and as LDS holds, in as few workgroups as possible (each keeps a copy of the rows)
-  const int want = gen_waves_per_cu();
-  int best_waves = 1, best_groups = 1;
-  for (int groups = 1; groups <= 8; ++groups) {
-    int wv = (int)std::min<int64_t>((lds_ints / groups - shared_ints - 64) / wave_ints, kGenTimedThreads / 64);
-    wv = std::min(wv, (want + groups - 1) / groups);
-    // (a workgroup's wavefronts go to the four SIMDs in turn, starting on the first: others leave one SIMD the slowest)
-    if (wv > 4) wv &= ~3;
-    if (wv >= 1 && wv * groups > best_waves * best_groups) { best_waves = wv; best_groups = groups; }
-  }
-  const int64_t segments = (n_sets + cpw - 1) / cpw;
-  // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
-  const int64_t grid = (int64_t)p->n_cu * best_groups;
-  best_waves = (int)std::clamp<int64_t>((segments + grid - 1) / grid, 1, best_waves);
-  const int64_t blocks = std::min<int64_t>((segments + best_waves - 1) / best_waves, grid);
-  const int64_t lds_bytes = 4 * (shared_ints + best_waves * wave_ints);
+  const GenShape shape = gen_shape(p, n_sets, cpw, shared_ints, wave_ints);
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
   static const GenKernel table[2][3][2] = {
@@ -2092,15 +2102,15 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
        {&generate_kernel<2, 1, kGenSlide>, &generate_kernel<2, 2, kGenSlide>},
        {&generate_kernel<4, 1, kGenSlide>, &generate_kernel<4, 2, kGenSlide>}}};
   const GenKernel kernel = table[slide ? 1 : 0][V == 1 ? 0 : (V == 2 ? 1 : 2)][deg - 1];
-  if (lds_bytes > 64 * 1024 &&
+  if (shape.lds_bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                           p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
   unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-  const int n_classes = order_sets(p, d_inflight, nullptr, n_sets, n_sets, blocks * best_waves * cpw, false, d_status, counter,
+  const int n_classes = order_sets(p, d_inflight, nullptr, n_sets, n_sets, shape.blocks * shape.waves * cpw, false, d_status, counter,
                                    static_cast<hipStream_t>(hip_stream));
   if (n_classes < 0) return n_classes;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * best_waves), (size_t)lds_bytes,
+  hipLaunchKernelGGL(kernel, dim3((unsigned)shape.blocks), dim3(64 * shape.waves), (size_t)shape.lds_bytes,
                      static_cast<hipStream_t>(hip_stream), tables, reinterpret_cast<const int32_t*>(d_policy),
                      d_inflight, nullptr, (long long)n_sets, (long long)n_sets, n_classes, 0, nullptr, d_steps, d_status, counter,
                      GenResults{reinterpret_cast<long long*>(out.makespan), reinterpret_cast<long long*>(out.idle),

@@ -24,9 +24,10 @@
 // behind it some 20 more; conditions are combined and state is changed by sets of lanes in scalar registers, and an item is
 // timed in the step behind its own, before which nothing waits for LDS that the next step does not wait for as well.
 // 16,384 sets of 32 devices, 2 stages each, 128 micro-batches (2,657 steps a set, 8,884 the longest): sliding form 4.84 ms
-// with 73 instructions, conditions as masks in vector registers, 4.22 now; results only 5.49 and 4.66, lists 5.04 and
-// 3.96; 4,096 sets of 16 devices, 64 micro-batches (the longest sets' chain): 0.77 and 0.75, 0.74 and 0.67, 0.66 and 0.54 ms;
-// 65,536 of 8 devices, 32 micro-batches: 0.90 and 0.81, 0.77 and 0.72, 0.78 and 0.70 ms.
+// with 73 instructions, conditions as masks in vector registers, and 12 wavefronts per compute unit in one workgroup, 4.22
+// with 57 instructions, 3.97 with larger rings, 3.89 now (fpsched_api.hip, gen_shape); results only 5.49, 4.66, then 3.42,
+// lists 5.04, 3.96, then 2.94; 4,096 sets of 16 devices, 64 micro-batches (the longest sets' chain): 0.77 and 0.75, 0.74 and
+// 0.67, 0.66 and 0.54 ms; 65,536 of 8 devices, 32 micro-batches: 0.90 and 0.81, 0.77 and 0.72, 0.78 and 0.67 ms.
 // Priorities (Section 5.2; Table of built-in values): computation type traversal priority
 // bwdpass-first / fwdpass-first / interleaved(unit1, unit2); stage traversal priority
 // breadth-first / depth-first with an optional interval, separately for forward and backward
@@ -151,7 +152,7 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 // would be waited for by all.  The stash is a queue of log2(V) bits per entry
 // (the chunk) in LDS: an actor stashes no more than V * m items, so entry i simply stands in word i * log2(V) / 32.
 template <int V, int DEG, int FORM>
-__global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void generate_kernel(
+__global__ __launch_bounds__(kGenThreads) void generate_kernel(
     DevTables T, const int32_t* __restrict__ policy, const int32_t* __restrict__ inflight,
     const long long* __restrict__ select, long long n_src, long long n_sets, int n_classes, int stride,
     uint16_t* __restrict__ ops, int32_t* __restrict__ out_steps, unsigned char* out_status,
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
   if (TIMED) {
     for (int i = threadIdx.x; i < n_tab; i += blockDim.x) tab[i] = T.ints[T.off_gen_rows + i];
   } else if (DEG == 0) {
-    for (int i = lane; i < n_tab; i += 64) lds[i] = T.ints[i];
+    for (int i = threadIdx.x; i < n_tab; i += blockDim.x) lds[i] = T.ints[i];
   }
   const int n_count_ints = (cpw * 2 * S + 2 + 3) & ~3;
   const int slot_words = T.gen_slot_words;
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(FORM != kGenPlain ? kGenTimedThreads : 64) void gen
 
   // Every step but the last of a set schedules at least one of its 3 S m items, and a segment
   // cannot draw more than all sets: the bound below is never reached, it only makes sure that the
-  // wavefront leaves the loop whatever happens.  A workgroup is one wavefront: its LDS instructions
+  // wavefront leaves the loop whatever happens.  A wavefront's counters are its own: its LDS instructions
   // execute in program order, so the reads of a step see the counters as the previous step left them
   // and no barrier is needed between the phases.
   const unsigned long long per_set = 3ull * (unsigned)S * (unsigned)m + 32ull;

@@ -95,20 +95,20 @@ __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n
 // counter[0] = value, counter[1] = value2
 __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2 = 0);
 
-// V as above; DEG = bound on the in- and out-degree of a stage (1, 2, or 0 = any).  One wavefront per
-// workgroup, T.gen_sets <= 64 / D parameter sets per wavefront at a time; next_set: a counter in device memory from
+// V as above; DEG = bound on the in- and out-degree of a stage (1, 2, or 0 = any).  Wavefronts that work
+// apart, T.gen_sets <= 64 / D parameter sets at a time each; next_set: a counter in device memory from
 // which segments draw their sets.  n_classes = 0: not looked at, no more sets than segments; 1: preset to the number of
 // segments in the grid; kGenClasses: set to 0 by generate_order_kernel, which has left each set's class in out_status.
 // select: null, or which of the n_src parameter sets each output row takes (outside 0 .. n_src - 1: none).
 // TIMED (DEG 1 or 2 only): the schedules are timed as they are generated and only the results R are
-// written (ops and select unused); workgroups of up to kGenTimedThreads threads.
+// written (ops and select unused).
 struct GenResults {
   long long* makespan;
   long long* idle;
   int32_t* peak;
   unsigned char* flags;
 };
-constexpr int kGenTimedThreads = 1024;
+constexpr int kGenThreads = 256;   // of a workgroup: a wavefront per SIMD
 // FORM: kGenPlain writes the lists; kGenTimed times them instead (above); kGenSlide times them after the
 // weight-gradient sliding pass (T.gen_events + T.gen_queue_words dwords of LDS more per lane)
 constexpr int kGenPlain = 0, kGenTimed = 1, kGenSlide = 2;
