@@ -125,7 +125,8 @@ struct SlotTables {
 //     second output's link row in the links form
 //   Wide form (times beyond 24 bits; a slot is two dwords, the time and the tag): word 0 is the latency, word 1 the
 //   duration, word 3 the tag the op leaves | the tag it expects << 8 | number of 16-byte rows in front of its second row
-//   << 16 | the two flags; word 3 of a second row is the tag expected on the first edge << 8.
+//   << 16 | the two flags (problems without second edges: word 2 the mask, word 3 the two tags | the slot's offset << 16);
+//   word 3 of a second row is the tag expected on the first edge << 8.
 //   Slots of a candidate, in dwords: [0, D) the devices' own words, D + 1
 //   for the makespan, then from list_slots_at(D) on class * m for backward values, (backward classes + class) * m for
 //   forward values; finish << 8 | producer stage, kEmptySlot at first.

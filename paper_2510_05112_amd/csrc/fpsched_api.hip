@@ -245,17 +245,18 @@ CheckKernel check_kernel_of(int vbits) {
 CheckKernel check_kernel_of(int vbits, bool no_w = false) { return no_w ? check_kernel_of<true>(vbits) : check_kernel_of<false>(vbits); }
 
 using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
-template <bool LINKS, bool MB>
-TimeKernel narrow_time_kernel_of(bool deg2) {
-  return deg2 ? &time_lists_kernel<true, false, LINKS, MB, false, false> : &time_lists_kernel<false, false, LINKS, MB, false, false>;
+template <bool DEG2>
+TimeKernel time_kernel_of(bool wide, bool links, int mb_bytes, bool sync) {
+  if (sync) return &time_lists_kernel<DEG2, false, false, 0, true, false>;
+  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false>;
+  if (mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false> : &time_lists_kernel<DEG2, false, false, 1, false, false>;
+  if (mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false> : &time_lists_kernel<DEG2, false, false, 2, false, false>;
+  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false> : &time_lists_kernel<DEG2, false, false, 0, false, false>;
 }
-TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, false, false, true>; }
-TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, bool mb = false, bool sync = false) {
-  if (sync) return deg2 ? &time_lists_kernel<true, false, false, false, true, false> : &time_lists_kernel<false, false, false, false, true, false>;
-  if (wide) return deg2 ? &time_lists_kernel<true, true, false, false, false, false> : &time_lists_kernel<false, true, false, false, false, false>;
-  if (links) return mb ? narrow_time_kernel_of<true, true>(deg2) : narrow_time_kernel_of<true, false>(deg2);
-  return mb ? narrow_time_kernel_of<false, true>(deg2) : narrow_time_kernel_of<false, false>(deg2);
+TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, int mb_bytes = 0, bool sync = false) {
+  return deg2 ? time_kernel_of<true>(wide, links, mb_bytes, sync) : time_kernel_of<false>(wide, links, mb_bytes, sync);
 }
+TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true>; }
 
 // What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
 struct StageEdge { int32_t cls, tag, latency; };
@@ -417,6 +418,13 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
       t[3] = t[2] & 0xffff;
       t[2] = (int32_t)((uint32_t)t[2] >> 16 | behind << 18);
     }
+  // (wide: the mask, and the offset above the two tags)
+  if (!*deg2 && wide)
+    for (int i = 0; i < kNKinds * kMaxChunks * D; ++i) {
+      int32_t* t = &J[(size_t)i * row_ints];
+      t[3] = (int32_t)(((uint32_t)t[3] & 0xffffu) | (uint32_t)t[2] << 16);
+      t[2] = (int32_t)((uint32_t)t[2] >> 16);
+    }
   for (int d = 0; d < D; ++d) {
     J[(size_t)T.off_dev + 2 * d] = p->n_chunks[d];
     J[(size_t)T.off_dev + 2 * d + 1] = (int32_t)(mem_cap[d] / unit_scale);   // peak > cap  <=>  peak / scale > floor(cap / scale)
@@ -474,7 +482,7 @@ int install_list_variant(fpsched_problem* p, ListTables T, const std::vector<int
     if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
     v->capacity = J.size();
   }
-  const TimeKernel kernel = time_kernel_of(deg2, false, T.link_words > 0, T.mb_bytes > 0, T.off_sync > 0);
+  const TimeKernel kernel = time_kernel_of(deg2, false, T.link_words > 0, T.mb_bytes, T.off_sync > 0);
   if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
@@ -1200,7 +1208,7 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant, T.link_words > 0, T.mb_bytes > 0, T.off_sync > 0), dim3((unsigned)time_blocks),
+  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant, T.link_words > 0, T.mb_bytes, T.off_sync > 0), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
                      out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), starts ? *starts : StartTimes{});

@@ -44,8 +44,11 @@
 //
 // MB, costs per micro-batch: the row has, instead of the cost, where the costs of its (kind, stage) begin in a table in
 // LDS; the cost is read together with the slot as well.  The busy time is then summed up here.  Both forms, 20,011
-// candidates of 11 devices, 45 micro-batches, 3 chunks: 0.64 + 0.06 ms; 2.01 ms as forms of the slot kernel with all
-// devices in every round and 16 lanes to a candidate.
+// candidates of 11 devices, 45 micro-batches, 3 chunks: 2.01 ms as forms of the slot kernel with all devices in every round and
+// 16 lanes to a candidate; 0.64 + 0.06 ms here with the step as the compiler makes it, 0.55 + 0.06 without branches, and
+// what the link and the cost take read ahead with the slot (FPSCHED_COST_STEP).  Such a batch has one candidate per segment:
+// the time is its longest chain's, a step's instructions and waits one after the other.  So has one in microseconds: 8,192
+// candidates of 16 devices, 64 micro-batches, 2 chunks 0.21 and 0.17 ms (FPSCHED_WIDE_STEP).
 //
 // SYNC, stages whose items stand for groups of micro-batches (a synchronisation every n micro-batches, Section 4.2 / 7.2
 // of the paper) and dependency pairs between items of one direction.  An item of a stage with group n waits for the n
@@ -80,7 +83,7 @@
 // behind the one it issues; after every top-up eight or more are unread), and sixteen places hold the words unread, at
 // most fifteen, and the END word that is planted behind a full row.  The ring of a lane is a column of dwords in a bank of
 // its own: read in lanes' own 32 bytes, some eight lanes shared their banks (6.6 clocks a read instead of 2.2).  Words are
-// requested 64 bytes (other forms: 32) at a time, as soon as the registers they arrive in are free: with the rows of a
+// requested 64 bytes (forms with the compiler's step: 32) at a time, as soon as the registers they arrive in are free: with the rows of a
 // compute unit's candidates in flight the 128-byte lines mostly do not stay in the L2 cache from one request to the next
 // (12.8 GB fetched for that batch of 3.76 GB with 32 bytes, 6.9 with 64).  (Rings of 32 words leave room for 11 instead
 // of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth round: 2.19 ms.  Loads that bypass L2: 2.8 ms.)
@@ -200,10 +203,97 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
       : [moved] "s"(moved_##X), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),   \
         [slots] "v"(slot_base)                                                                                           \
       : "memory")
+// The same for the forms with link occupancy and costs per micro-batch.  COST: how the op's cost and tag are added to its
+// start; SEND: when the value leaves over the link, and until when that keeps the link busy; AHEAD: with the slot, the other
+// half's link words and costs are read; LINK_ROW: the next op's link row is fetched in front of its row.
+#define FPSCHED_COST_STEP(X, Y, X_ROW, Y_ROW, RX, RW, COST, SEND, WAIT, AHEAD, LINK_ROW)                                 \
+  asm volatile(                                                                                                          \
+      "s_waitcnt lgkmcnt(" WAIT ")\n\t"                                                                                 \
+      "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
+      "v_cmpx_eq_u32_sdwa %[moved], %[in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                                   \
+      "v_max_u32 %[t], %[free], %[in]\n\t" COST                                                                         \
+      "v_and_b32 %[free], 0xffffff00, %[t]\n\t" SEND                                                                    \
+      "ds_write_b32 %[at], %[t]\n\t"                                                                                    \
+      "s_mov_b64 exec, -1\n\t" AHEAD                                                                                    \
+      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
+      "v_lshrrev_b32 %[t], 11, %[next]\n\t" LINK_ROW                                                                    \
+      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
+      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
+      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
+      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
+      "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
+      "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
+      "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
+      "s_mov_b64 exec, -1"                                                                                               \
+      : [in] "+v"(X##_in), [at] "+v"(X##_at), [free] "+v"(X.free_at), [next] "+v"(X.w_next), [j] "+v"(X.j_slot),         \
+        [pos] "+v"(X.pos), [t] "=&v"(scratch), [u] "=&v"(scratch2), [moved] "=&s"(moved_##X), [row] "+{" X_ROW "}"(X.R), \
+        [other_row] "+{" Y_ROW "}"(Y.R), [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot),     \
+        [other_next] "+v"(Y.w_next), [link] "+v"(X.link), [other_link] "+v"(Y.link), [link_at] "+v"(X##_link_at),        \
+        [other_link_at] "+v"(Y##_link_at), [sent] "+v"(X##_sent), [other_sent] "+v"(Y##_sent), [cost] "+v"(X##_cost),    \
+        [other_cost] "+v"(Y##_cost), [busy] "+v"(X.busy)                                                                 \
+      : [zero] "v"(0u), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),           \
+        [slots] "v"(slot_base), [byte] "s"(0xffu), [link_stride] "s"(row_stride / 4u), [link_rows] "v"(X.link_rows),     \
+        [other_links] "v"(Y.links)                                                                                       \
+      : "memory")
+#define FPSCHED_COST_PLAIN(RY) "v_add_u32 %[t], %[t], v" RY "\n\t"
+#define FPSCHED_COST_TABLE(RY)                                                                                           \
+  "v_add_u32 %[busy], %[busy], %[cost]\n\t"                                                                             \
+  "v_lshl_add_u32 %[t], %[cost], 8, %[t]\n\t"                                                                           \
+  "v_add_u32_sdwa %[t], %[t], v" RY " dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+#define FPSCHED_SEND_LINK(RY)                                                                                            \
+  "v_and_or_b32 %[u], v" RY ", %[byte], %[sent]\n\t"                                                                    \
+  "v_max_u32 %[t], %[t], %[u]\n\t"                                                                                      \
+  "v_lshrrev_b32 %[sent], 16, %[link]\n\t"                                                                              \
+  "v_and_b32 %[u], 0xffffff00, %[t]\n\t"                                                                                \
+  "v_lshl_add_u32 %[u], %[sent], 8, %[u]\n\t"                                                                           \
+  "ds_write_b32 %[link_at], %[u]\n\t"
+#define FPSCHED_AHEAD_LINK                                                                                               \
+  "v_add_u32_sdwa %[other_link_at], %[other_links], %[other_link] dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_0\n\t"     \
+  "ds_read_b32 %[other_sent], %[other_link_at]\n\t"
+#define FPSCHED_AHEAD_COST(OY, SHIFT, READ)                                                                              \
+  "v_lshrrev_b32 %[other_cost], 8, v" OY "\n\t"                                                                         \
+  "v_bfe_u32 %[t], %[other_j], 2, 11\n\t"                                                                               \
+  "v_lshl_add_u32 %[other_cost], %[t], " SHIFT ", %[other_cost]\n\t" READ " %[other_cost], %[other_cost]\n\t"
+#define FPSCHED_LINK_ROW                                                                                                 \
+  "v_mad_u32_u24 %[u], %[t], %[link_stride], %[link_rows]\n\t"                                                          \
+  "ds_read_b32 %[link], %[u]\n\t"
+
+// ... and for times of two words (rows: latency; cost; mask; own tag, expected tag, slot's offset; the slot's words: IN, TAG).
+#define FPSCHED_WIDE_STEP(X, Y, X_ROW, Y_ROW, X_SLOT, Y_SLOT, RX, RY, RW, IN, TAG, AHEAD)                                 \
+  asm volatile(                                                                                                          \
+      "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
+      "v_cmpx_eq_u32_sdwa %[moved], v" TAG ", v" RW " src0_sel:BYTE_0 src1_sel:BYTE_1\n\t"                               \
+      "v_add_u32 v" IN ", v" IN ", v" RX "\n\t"                                                                         \
+      "v_max_u32 %[free], %[free], v" IN "\n\t"                                                                         \
+      "v_add_u32 %[free], %[free], v" RY "\n\t"                                                                         \
+      "ds_write2_b32 %[at], %[free], v" RW " offset1:1\n\t"                                                             \
+      "s_mov_b64 exec, -1\n\t" AHEAD                                                                                    \
+      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
+      "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
+      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
+      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
+      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
+      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
+      "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
+      "v_lshlrev_b32 %[j], 3, %[next]\n\t"                                                                              \
+      "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
+      "s_mov_b64 exec, -1"                                                                                               \
+      : [slot] "+{" X_SLOT "}"(X##_both), [other_slot] "+{" Y_SLOT "}"(Y##_both), [at] "+v"(X##_at),                     \
+        [free] "+v"(X.free_at), [next] "+v"(X.w_next), [j] "+v"(X.j_slot), [pos] "+v"(X.pos), [t] "=&v"(scratch),        \
+        [moved] "=&s"(moved_##X), [row] "+{" X_ROW "}"(X.R), [other_row] "+{" Y_ROW "}"(Y.R), [other_at] "+v"(Y##_at),   \
+        [other_j] "+v"(Y.j_slot), [other_next] "+v"(Y.w_next)                                                            \
+      : [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask), [slots] "v"(slot_base)    \
+      : "memory")
+#define FPSCHED_WIDE_AHEAD(OZ, OW, SLOT)                                                                                 \
+  "s_waitcnt lgkmcnt(1)\n\t"                                                                                            \
+  "v_and_b32 %[other_at], %[other_j], v" OZ "\n\t"                                                                      \
+  "v_add_u32_sdwa %[other_at], %[other_at], v" OW " dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"                   \
+  "v_add_u32 %[other_at], %[other_at], %[slots]\n\t"                                                                    \
+  "ds_read_b64 " SLOT ", %[other_at]\n\t"
 #define FPSCHED_ROW_OF_even "v[40:43]"
 #define FPSCHED_ROW_OF_odd "v[44:47]"
 
-template <bool DEG2, bool WIDE, bool LINKS, bool MB, bool SYNC, bool TIMES>
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES>
 __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
@@ -213,16 +303,19 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   static_assert(!TIMES || !(DEG2 || WIDE || LINKS || MB || SYNC), "");
   constexpr unsigned kRowBytes = 16u;
   constexpr bool PLAIN = !WIDE && !LINKS && !MB && !SYNC;   // (TIMES too)
+  constexpr bool STRAIGHT = PLAIN || (!DEG2 && !SYNC);   // the step without branches
   constexpr bool SPLIT = !WIDE && (!DEG2 || PLAIN);   // rows with the slot's mask and offset in a word each
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
-  constexpr int kPieces = PLAIN ? 4 : 2;
+  constexpr int kPieces = STRAIGHT ? 4 : 2;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
   // LDS: [op windows of all wavefronts][tables][per wavefront: link words, slots]
   const unsigned lds0 = lds_address(lds), tables = lds0 + (blockDim.x >> 6) * (unsigned)kTimeWindowBytes;
-  for (int i = tid; i < T.n_time_ints; i += blockDim.x) lds_write<int>(tables + (unsigned)i * 4u, T.ints[i]);
+  // (MB: where the costs begin, in the rows' second words, becomes an LDS address)
+  for (int i = tid; i < T.n_time_ints; i += blockDim.x)
+    lds_write<int>(tables + (unsigned)i * 4u, T.ints[i] + (MB != 0 && (i & 3) == 1 && i < kNKinds * kMaxChunks * 4 * T.D ? (int)(tables << 8) : 0));
   const int seg = lane / P, pair = lane - seg * P;
   const bool lane_ok = seg < cpw;
   const int d0 = 2 * pair;
@@ -276,7 +369,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   };
   Device even, odd;
   auto idle_device = [&](Device& x) {
-    x.R = WIDE ? lds_int4{0, 0, own_at, (int)kWideNever} : (SPLIT ? lds_int4{1, 0, 0, own_at} : lds_int4{1, 0, own_at, 0});
+    x.R = WIDE ? (STRAIGHT ? lds_int4{0, 0, 0, own_at << 16 | (int)kWideNever} : lds_int4{0, 0, own_at, (int)kWideNever}) : (SPLIT ? lds_int4{1, 0, 0, own_at} : lds_int4{1, 0, own_at, 0});
     x.link = 0u;
     x.group = 0x10001u; x.taken = 0u;
     x.loaded = kNoList;
@@ -434,8 +527,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned cost = 0u;
     if (MB) {
       // (a row without a cost table reads some word of LDS and does not issue)
-      const unsigned at = tables + (cost_tag >> 8) + (((x.j_slot >> 2) & 0x7ffu) << (T.mb_bytes - 1));
-      cost = T.mb_bytes == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
+      const unsigned at = (cost_tag >> 8) + (((x.j_slot >> 2) & 0x7ffu) << (MB - 1));
+      cost = MB == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
       cost_tag = cost << 8 | (cost_tag & 0xffu);
     }
     // (the second row comes with the slot: read where it is needed, some lane of a wavefront waits for it in most steps)
@@ -602,8 +695,10 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     }
     ask(even, row);
     ask(odd, row + stride2);
-    unsigned even_in = 0u, odd_in = 0u, even_at = 0u, odd_at = 0u, scratch;
-    if constexpr (PLAIN)
+    unsigned even_in = 0u, odd_in = 0u, even_at = 0u, odd_at = 0u, scratch, scratch2;
+    unsigned even_link_at = 0u, odd_link_at = 0u, even_sent = 0u, odd_sent = 0u, even_cost = 0u, odd_cost = 0u;
+    lds_int2 even_both{0, 0}, odd_both{0, 0};
+    if constexpr (STRAIGHT && !WIDE)
       asm volatile("s_waitcnt lgkmcnt(0)\n\t"
                    "v_and_b32 %[at], %[j], v42\n\t"
                    "v_add3_u32 %[at], %[at], v43, %[slots]\n\t"
@@ -611,6 +706,24 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
                    "s_waitcnt lgkmcnt(0)"
                    : [in] "=&v"(even_in), [at] "=&v"(even_at), [row] "+{v[40:43]}"(even.R)
                    : [j] "v"(even.j_slot), [slots] "v"(slot_base) : "memory");
+    if constexpr (STRAIGHT && WIDE)
+      asm volatile("s_waitcnt lgkmcnt(0)\n\t"
+                   "v_and_b32 %[at], %[j], v42\n\t"
+                   "v_add_u32_sdwa %[at], %[at], v43 dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"
+                   "v_add_u32 %[at], %[at], %[slots]\n\t"
+                   "ds_read_b64 v[48:49], %[at]\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : [slot] "=&{v[48:49]}"(even_both), [at] "=&v"(even_at), [row] "+{v[40:43]}"(even.R)
+                   : [j] "v"(even.j_slot), [slots] "v"(slot_base) : "memory");
+    if constexpr (STRAIGHT && LINKS) {
+      even_link_at = even.links + (even.link & 0xffffu);
+      even_sent = lds_read<unsigned>(even_link_at);
+    }
+    if constexpr (STRAIGHT && MB != 0) {
+      const unsigned at = ((unsigned)even.R.y >> 8) + (((even.j_slot >> 2) & 0x7ffu) << (MB - 1));
+      even_cost = MB == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
+    }
+    if constexpr (STRAIGHT && (LINKS || MB != 0)) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(even_sent), "+v"(even_cost));
 #pragma unroll
     for (unsigned sub = 0; sub < kRounds; ++sub) {
       unsigned long long moved_even, moved_odd;
@@ -650,6 +763,52 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         }
         if (sub + 1 == kRounds)
           asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
+      } else if constexpr (STRAIGHT) {
+        if constexpr (WIDE) {
+          FPSCHED_WIDE_STEP(even, odd, "v[40:43]", "v[44:47]", "v[48:49]", "v[50:51]", "40", "41", "43", "48", "49", FPSCHED_WIDE_AHEAD("46", "47", "v[50:51]"));
+          if (sub + 1 < kRounds) {
+            FPSCHED_WIDE_STEP(odd, even, "v[44:47]", "v[40:43]", "v[50:51]", "v[48:49]", "44", "45", "47", "50", "51", FPSCHED_WIDE_AHEAD("42", "43", "v[48:49]"));
+          } else {
+            FPSCHED_WIDE_STEP(odd, even, "v[44:47]", "v[40:43]", "v[50:51]", "v[48:49]", "44", "45", "47", "50", "51", "");
+          }
+        } else if constexpr (LINKS && MB == 0) {
+          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_PLAIN("41"), FPSCHED_SEND_LINK("41"), "3", FPSCHED_READ_AHEAD("2", "46", "47") FPSCHED_AHEAD_LINK, FPSCHED_LINK_ROW);
+          if (sub + 1 < kRounds) {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_PLAIN("45"), FPSCHED_SEND_LINK("45"), "3", FPSCHED_READ_AHEAD("2", "42", "43") FPSCHED_AHEAD_LINK, FPSCHED_LINK_ROW);
+          } else {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_PLAIN("45"), FPSCHED_SEND_LINK("45"), "3", "", FPSCHED_LINK_ROW);
+          }
+        } else if constexpr (LINKS && MB == 1) {
+          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), FPSCHED_SEND_LINK("41"), "3", FPSCHED_READ_AHEAD("2", "46", "47") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("45", "0", "ds_read_u8"), FPSCHED_LINK_ROW);
+          if (sub + 1 < kRounds) {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", FPSCHED_READ_AHEAD("2", "42", "43") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("41", "0", "ds_read_u8"), FPSCHED_LINK_ROW);
+          } else {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", "", FPSCHED_LINK_ROW);
+          }
+        } else if constexpr (LINKS) {
+          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), FPSCHED_SEND_LINK("41"), "3", FPSCHED_READ_AHEAD("2", "46", "47") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("45", "1", "ds_read_u16"), FPSCHED_LINK_ROW);
+          if (sub + 1 < kRounds) {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", FPSCHED_READ_AHEAD("2", "42", "43") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("41", "1", "ds_read_u16"), FPSCHED_LINK_ROW);
+          } else {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", "", FPSCHED_LINK_ROW);
+          }
+        } else if constexpr (MB == 1) {
+          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), "", "2", FPSCHED_READ_AHEAD("1", "46", "47") FPSCHED_AHEAD_COST("45", "0", "ds_read_u8"), "");
+          if (sub + 1 < kRounds) {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", FPSCHED_READ_AHEAD("1", "42", "43") FPSCHED_AHEAD_COST("41", "0", "ds_read_u8"), "");
+          } else {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", "", "");
+          }
+        } else {
+          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), "", "2", FPSCHED_READ_AHEAD("1", "46", "47") FPSCHED_AHEAD_COST("45", "1", "ds_read_u16"), "");
+          if (sub + 1 < kRounds) {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", FPSCHED_READ_AHEAD("1", "42", "43") FPSCHED_AHEAD_COST("41", "1", "ds_read_u16"), "");
+          } else {
+            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", "", "");
+          }
+        }
+        if (sub + 1 == kRounds)
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next), "+v"(even.link), "+v"(odd.link) : : "memory");
       } else {
         moved_even = step(even);
         moved_odd = step(odd);
@@ -720,19 +879,19 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
 #define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES)                                                              \
   template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES>(ListTables, const uint16_t*, long long, int, long long*, \
                                                                     long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
-FPSCHED_INSTANTIATE(false, false, false, false, false, false)
-FPSCHED_INSTANTIATE(true, false, false, false, false, false)
-FPSCHED_INSTANTIATE(false, true, false, false, false, false)
-FPSCHED_INSTANTIATE(true, true, false, false, false, false)
-FPSCHED_INSTANTIATE(false, false, true, false, false, false)
-FPSCHED_INSTANTIATE(true, false, true, false, false, false)
-FPSCHED_INSTANTIATE(false, false, false, true, false, false)
-FPSCHED_INSTANTIATE(true, false, false, true, false, false)
-FPSCHED_INSTANTIATE(false, false, true, true, false, false)
-FPSCHED_INSTANTIATE(true, false, true, true, false, false)
-FPSCHED_INSTANTIATE(false, false, false, false, true, false)
-FPSCHED_INSTANTIATE(true, false, false, false, true, false)
-FPSCHED_INSTANTIATE(false, false, false, false, false, true)
+#define FPSCHED_INSTANTIATE_MODELS(DEG2)                     \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false)   \
+  FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 0, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 1, false, false)   \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 2, false, false)   \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 1, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 0, true, false)
+FPSCHED_INSTANTIATE_MODELS(false)
+FPSCHED_INSTANTIATE_MODELS(true)
+FPSCHED_INSTANTIATE(false, false, false, 0, false, true)
+#undef FPSCHED_INSTANTIATE_MODELS
 #undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched
