@@ -135,7 +135,10 @@ struct SlotTables {
 //   cost table: per kind (kinds with the same costs share) and stage a row of mb_bytes per micro-batch, an odd number of
 //     dwords long; word 1 of a timing row then has the byte offset of that row instead of the duration, and the order
 //     rows' durations are 0.
-//   group rows: micro-batches per item of the op's stage | of them, those whose input it waits for (1 without an input) << 16
+//   items of groups (synchronisation form): the timing row never issues, its word 1 is kGroupRow and it names, as a row that
+//     follows, two group rows, of the first edge and of the second: 0 as in a timing row (without an input: 0), 1 (first)
+//     dur << 8 | stage, 2 (first) micro-batches per item | kGroupIn if it has an input | kGroupOut if an output, 3 byte offset
+//     of the slots
 //   order rows [kNKinds * 4][D] x 2 ints:
 //     0 next state | required state << 8 | units allocated << 16 | units freed << 24   1 dur
 //     Rows of words that may not appear on the device require kNoState; word 1 of the rows of kind 0 has the items of the
@@ -151,7 +154,7 @@ struct ListTables {
   int32_t off_links;        // links form: link rows, one int per timing row in the same order, in ints
   int32_t link_words;       // links form: words per lane and half (one behind the links for ops that send nothing)
   int32_t mb_bytes;         // costs per micro-batch: bytes of a value, 1 or 2
-  int32_t off_sync;         // synchronisation form: group rows, one int per timing row in the same order, in ints (0: none)
+  int32_t off_sync;         // synchronisation form: group rows, in ints (0: another form)
   int32_t off_check;        // order rows, in ints
   int32_t n_check_ints;
   int32_t check_shared_bytes;   // order rows and dev rows in LDS, a multiple of 16
@@ -163,6 +166,8 @@ struct ListTables {
   const int32_t* ints;      // DEVICE
 };
 constexpr unsigned kRowTwoOut = 1u << 30;
+constexpr int kGroupRow = -1;
+constexpr unsigned kGroupIn = 1u << 16, kGroupOut = 1u << 17;
 constexpr unsigned kWideNever = 0xffu << 8;   // wide form: the tag of an empty slot, expected on a device's own word
 constexpr unsigned kOwnTag = 0xfeu;   // (no stage's op looks at a device's own word)
 constexpr int list_slots_at(int D) { return (D + 2 + 3) & ~3; }

@@ -247,7 +247,7 @@ CheckKernel check_kernel_of(int vbits, bool no_w = false) { return no_w ? check_
 using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
 template <bool DEG2>
 TimeKernel time_kernel_of(bool wide, bool links, int mb_bytes, bool sync) {
-  if (sync) return &time_lists_kernel<DEG2, false, false, 0, true, false>;
+  if (sync) return &time_lists_kernel<true, false, false, 0, true, false>;
   if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false>;
   if (mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false> : &time_lists_kernel<DEG2, false, false, 1, false, false>;
   if (mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false> : &time_lists_kernel<DEG2, false, false, 2, false, false>;
@@ -1689,19 +1689,31 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
     ListTables LT;
     bool two = false;
     std::vector<int32_t> image;
-    if (fill_list_image(p, edges, n_of[0], n_of[1], false, false, items, &LT, &two, &image)) {
-      // group rows behind the timing rows
-      std::vector<int32_t> rows((kNKinds * kMaxChunks * D + 7) & ~7, 0x10001);
+    if (fill_list_image(p, edges, n_of[0], n_of[1], false, true, items, &LT, &two, &image)) {
+      // items of groups: rows that never issue and name two rows behind the timing rows (device_tables.h)
+      std::vector<int32_t> rows;
+      const int32_t old_ints = LT.n_time_ints;
       for (int kind : {(int)kF, (int)kFD, (int)kB})
         for (int d = 0; d < D; ++d)
           for (int c = 0; c < p->n_chunks[d]; ++c) {
             const int s = p->local_stage[(size_t)d * kMaxChunks + c], dir = kind == kB ? 1 : 0;
-            if (edges[s].in[dir].empty() && edges[s].out[dir].empty()) continue;   // (no slots: the device's own word)
-            rows[(kind * kMaxChunks + c) * D + (d & 1) * ((D + 1) / 2) + d / 2] =
-                grp[s] | (edges[s].in[dir].empty() ? 1 : grp[s]) << 16;
+            const std::vector<EdgeSlot> slots = edge_slots(edges[s], dir);
+            if (grp[s] <= 1 || slots.empty()) continue;   // (no slots: the device's own word)
+            int32_t* t = &image[((kind * kMaxChunks + c) * D + (d & 1) * ((D + 1) / 2) + d / 2) * 4];
+            int32_t of_group[8] = {0, (int32_t)((uint32_t)p->host_ints[p->tables.off_dur + kind * S + s] << 8 | (uint32_t)s), grp[s], 0, 0, 0, 0, 0};
+            for (size_t e = 0; e < slots.size(); ++e) {
+              const StageEdge* in = slots[e].in;
+              of_group[4 * e] = in ? (int32_t)(((uint32_t)in->latency << 8) - (uint32_t)in->tag) : 0;
+              of_group[4 * e + 2] |= (in ? (int32_t)kGroupIn : 0) | (slots[e].out ? (int32_t)kGroupOut : 0);
+              of_group[4 * e + 3] = 4 * (list_slots_at(D) + (dir == 0 ? n_of[1] * m : 0) + slots[e].cls * m);
+            }
+            t[0] = 1; t[1] = (int32_t)kGroupRow;
+            t[2] = (int32_t)((uint32_t)((old_ints + (int)rows.size()) / 4) << 18);
+            t[3] = 4 * d;
+            rows.insert(rows.end(), of_group, of_group + 8);
           }
+      rows.resize((rows.size() + 7) & ~(size_t)7, 0);
       LT.check_wave_bytes = p->ltab.check_wave_bytes;   // (the order pass is launched as for the plain model)
-      const int32_t old_ints = LT.n_time_ints;
       LT.off_sync = old_ints;
       LT.n_time_ints += (int32_t)rows.size();
       LT.off_check += (int32_t)rows.size();

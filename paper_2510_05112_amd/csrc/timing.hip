@@ -52,9 +52,11 @@
 //
 // SYNC, stages whose items stand for groups of micro-batches (a synchronisation every n micro-batches, Section 4.2 / 7.2
 // of the paper) and dependency pairs between items of one direction.  An item of a stage with group n waits for the n
-// values of its micro-batches, one slot after the other, taken in like a second input, and leaves its own in the n slots.
+// values of its micro-batches and leaves its own in the n slots.  Its row never issues; every fourth round the devices at such
+// an item take in up to four values each and run it with the last one (groups), so that the steps are those of the plain form.
 // A pair is an edge of its own slot class in one direction only.  (The host only picks this form when the neighbours of
-// such a stage have one item per micro-batch.)
+// such a stage have one item per micro-batch.)  65,536 candidates of 12 devices, 64 micro-batches, groups of four: 1.03 ms
+// with one value a step in a step with branches, 0.76 now; groups looked after every second round 0.81, every eighth 0.84.
 //
 // TIMES, the first pass of the weight-gradient sliding (wslide.hip) on problems of the plain form: the lists without their W
 // items (a W word is an op of the device's own without a cost), of which it leaves the low sixteen bits of each op's start
@@ -299,11 +301,11 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block, StartTimes starts) {
   static_assert(!WIDE || !(LINKS || MB || SYNC), "these forms have times of 24 bits");
-  static_assert(!SYNC || !(LINKS || MB), "");
+  static_assert(!SYNC || (DEG2 && !LINKS && !MB), "rows that follow others");
   static_assert(!TIMES || !(DEG2 || WIDE || LINKS || MB || SYNC), "");
   constexpr unsigned kRowBytes = 16u;
-  constexpr bool PLAIN = !WIDE && !LINKS && !MB && !SYNC;   // (TIMES too)
-  constexpr bool STRAIGHT = PLAIN || (!DEG2 && !SYNC);   // the step without branches
+  constexpr bool PLAIN = !WIDE && !LINKS && !MB;   // (TIMES and SYNC too)
+  constexpr bool STRAIGHT = PLAIN || !DEG2;   // the step without branches
   constexpr bool SPLIT = !WIDE && (!DEG2 || PLAIN);   // rows with the slot's mask and offset in a word each
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
   constexpr int kPieces = STRAIGHT ? 4 : 2;
@@ -360,8 +362,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned info;      // what the order pass left for this row: kRow* | stop
     unsigned busy;
     unsigned link_rows, links;   // LINKS: where its devices' link rows are, the lane's link words
-    unsigned sync_rows;          // SYNC: where its devices' group rows are
-    unsigned group, taken;       // SYNC: micro-batches of the item | values it waits for << 16; those taken in
+    unsigned taken;              // SYNC: values of its group's item taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
     unsigned own_place, next_place;   // TIMES: places in the ring of the words under and behind the cursor
     int n_late;                       // TIMES: entries of the row's escape list
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   auto idle_device = [&](Device& x) {
     x.R = WIDE ? (STRAIGHT ? lds_int4{0, 0, 0, own_at << 16 | (int)kWideNever} : lds_int4{0, 0, own_at, (int)kWideNever}) : (SPLIT ? lds_int4{1, 0, 0, own_at} : lds_int4{1, 0, own_at, 0});
     x.link = 0u;
-    x.group = 0x10001u; x.taken = 0u;
+    x.taken = 0u;
     x.loaded = kNoList;
     x.asked = 0u;
     x.pos = position_of(1u);
@@ -381,7 +382,6 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     x.win = lds0 + (unsigned)wave * (unsigned)kTimeWindowBytes + (unsigned)k * kWindowBytes + (unsigned)lane * 4u;
     x.meta = tables + (unsigned)(k * P + pair) * kRowBytes;
     x.link_rows = LINKS ? tables + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
-    x.sync_rows = SYNC ? tables + (unsigned)T.off_sync * 4u + (unsigned)(k * P + pair) * 4u : 0u;
     x.links = LINKS ? wave_at + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
     x.own_place = x.win; x.next_place = x.win; x.n_late = 0;
@@ -407,10 +407,6 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     const unsigned at = __umul24(word >> 11, row_stride) + x.meta;
     x.j_slot = word * kSlotBytes;
     x.R = lds_read<lds_int4>(at);
-    if (SYNC) {
-      x.group = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.sync_rows);
-      x.taken = 0u;
-    }
     if (LINKS) x.link = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.link_rows);
   };
   // address of a position in the device's ring (the windows of a wavefront begin at a multiple of their size)
@@ -512,14 +508,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   // one step of one half of the devices in the other forms; returns the lanes that issued
   auto step = [&](Device& x) -> unsigned long long {
     asm volatile("" : "+v"(x.R), "+v"(x.j_slot));   // (the row stays one value until here: no earlier wait for it)
-    unsigned j_slot = x.j_slot, n_slots = 1u;
-    bool more = false;   // the item waits for further values of this input
-    if (SYNC) {
-      const unsigned first_j = __umul24((x.j_slot >> 2) & 0x7ffu, x.group & 0xffffu);
-      n_slots = min(x.group & 0xffffu, (unsigned)T.m - first_j);
-      more = x.taken + 1u < min(x.group >> 16, n_slots);
-      j_slot = (first_j + x.taken) << 2;
-    }
+    const unsigned j_slot = x.j_slot;
     const unsigned at_slot = SPLIT ? (j_slot & (unsigned)x.R.z) + ((unsigned)x.R.w + slot_base)
                                    : (j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
     unsigned ready, cost_tag = (unsigned)x.R.y, link_free = 0u;
@@ -546,16 +535,6 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
       asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready), "v"(zero));
     }
     unsigned long long issue = moved;
-    if (SYNC) {
-      const unsigned long long take = moved & __ballot(more);
-      if (take != 0ull) {
-        if (__builtin_amdgcn_inverse_ballot_w64(take)) {
-          x.free_at = max(x.free_at, ready & 0xffffff00u);
-          ++x.taken;
-        }
-        issue &= ~take;
-      }
-    }
     if (DEG2) {
       // an op with two inputs waits for its second one first: once that is there the device's free time takes it in
       // (nothing but the start of this op looks at that time) and the op waits for its first
@@ -565,7 +544,6 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           x.free_at = max(x.free_at, ready);
           x.R.x = second_r.x;
           x.R.z = second_r.y;
-          x.taken = 0u;
           x.R.w = WIDE ? (x.R.w & 0x7fff00ff) | second_r.w : x.R.w & 0x7fffffff;
         }
         issue &= ~absorb;
@@ -585,13 +563,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         if (WIDE) lds_write<lds_int2>(at, lds_int2{(int)val, x.R.w & 0xff});
         else lds_write<uint32_t>(at, val);
       };
-      if (SYNC && n_slots > 1u) {
-        // an item of a group is the value of each of its micro-batches
-        const unsigned first_at = at_slot - (x.taken << 2);
-        for (unsigned k = 0; k < n_slots; ++k) leave(first_at + (k << 2));
-      } else {
-        leave(at_slot);
-      }
+      leave(at_slot);
       if (DEG2 && ((unsigned)x.R.w & kRowTwoOut) != 0u) {
         const unsigned second = (unsigned)second_r.z;
         if (LINKS) {
@@ -599,10 +571,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           val = max(x.free_at, lds_read<unsigned>(x.links + (link & 0xffffu))) | (cost_tag & 0xffu);
           lds_write<unsigned>(x.links + (link & 0xffffu), (val & 0xffffff00u) + (link >> 16 << 8));
         }
-        const unsigned second_at = ((j_slot - (SYNC ? x.taken << 2 : 0u)) & (second >> 16)) + slot_base + (second & 0xffffu);
-        leave(second_at);
-        if (SYNC)
-          for (unsigned k = 1; k < n_slots; ++k) leave(second_at + (k << 2));
+        leave((j_slot & (second >> 16)) + slot_base + (second & 0xffffu));
       }
       decode(x, x.w_next);
       x.pos = (x.pos | kPosBetween) + 2u;
@@ -610,12 +579,61 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     }
     return moved;
   };
+  // SYNC, every fourth round: the devices at an item of a group of micro-batches (their rows never issue and name another
+  // one, then one of the second edge) take in what has arrived of the values it waits for, up to four at a time; with the last one the
+  // item runs, and leaves its value in the slots of its micro-batches.  Returns the lanes that took in a value or issued.
+  // (stepped: the lanes that have issued in this round, which do not again: the ring has words for one op a round)
+  auto groups = [&](Device& x, unsigned long long stepped) -> unsigned long long {
+    const unsigned long long at_group = __ballot(x.R.y == kGroupRow) & ~stepped;
+    if (at_group == 0ull) return 0ull;
+    unsigned long long moved = 0ull;
+    if (__builtin_amdgcn_inverse_ballot_w64(at_group)) {
+      const unsigned at = tables + ((unsigned)x.R.z >> 14);
+      const lds_int4 first = lds_read<lds_int4>(at), second = lds_read<lds_int4>(at + 16u);
+      const unsigned n = (unsigned)first.z & 0xffffu;
+      const unsigned first_j = __umul24((x.j_slot >> 2) & 0x7ffu, n), n_slots = min(n, (unsigned)T.m - first_j);
+      const unsigned first_at = slot_base + (unsigned)first.w + (first_j << 2), second_at = slot_base + (unsigned)second.w + (first_j << 2);
+      const unsigned of_first = ((unsigned)first.z & kGroupIn) != 0u ? n_slots : 0u, of_second = ((unsigned)second.z & kGroupIn) != 0u ? n_slots : 0u;
+      // (up to four values of one edge at a time)
+      const bool at_first = x.taken < of_first;
+      const unsigned done = at_first ? x.taken : x.taken - of_first, left = (at_first ? of_first : of_second) - done;
+      const unsigned from = (at_first ? first_at : second_at) + (done << 2), wait = (unsigned)(at_first ? first.x : second.x);
+      unsigned value[4];
+#pragma unroll
+      for (unsigned k = 0; k < 4; ++k) value[k] = lds_read<unsigned>(from + (k < left ? k << 2 : 0u));
+      bool there = true;
+      unsigned got = 0u;
+#pragma unroll
+      for (unsigned k = 0; k < 4; ++k) {
+        const unsigned ready = value[k] + wait;
+        there = there && k < left && (ready & 0xffu) == 0u;
+        x.free_at = there ? max(x.free_at, ready) : x.free_at;
+        got += there ? 1u : 0u;
+      }
+      x.taken += got;
+      const bool issue = x.taken == of_first + of_second;
+      moved = __ballot(issue || got != 0u);
+      if (issue) {
+        const unsigned val = x.free_at + (unsigned)first.y;
+        x.free_at = val & 0xffffff00u;
+        for (unsigned k = 0; k < n_slots; ++k) {
+          lds_write<unsigned>(first_at + (k << 2), val);
+          if (((unsigned)second.z & kGroupOut) != 0u) lds_write<unsigned>(second_at + (k << 2), val);
+        }
+        x.taken = 0u;
+        decode(x, x.w_next);
+        x.pos = (x.pos | kPosBetween) + 2u;
+        x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
+      }
+    }
+    return __shfl(moved, __ffsll((long long)at_group) - 1);
+  };
 
   // Every candidate ends after at most 3 D * stride + 2 rounds (each round but its last issues at least one of its at
   // most D * stride ops, takes in the second input of one or leaves the second output), so the bound below is never reached;
   // it only makes sure the wavefront leaves the loop whatever happens.
-  // (SYNC: an op takes in at most 2 m values)
-  const unsigned long long bound = (3ull * (unsigned)D * (unsigned)stride * (SYNC ? (unsigned long long)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
+  // (SYNC: an op takes in at most 2 m values, in every fourth round)
+  const unsigned long long bound = (3ull * (unsigned)D * (unsigned)stride * (SYNC ? 4ull * (unsigned)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
     land(even, 0);
@@ -698,7 +716,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned even_in = 0u, odd_in = 0u, even_at = 0u, odd_at = 0u, scratch, scratch2;
     unsigned even_link_at = 0u, odd_link_at = 0u, even_sent = 0u, odd_sent = 0u, even_cost = 0u, odd_cost = 0u;
     lds_int2 even_both{0, 0}, odd_both{0, 0};
-    if constexpr (STRAIGHT && !WIDE)
+    auto read_ahead = [&]() {
       asm volatile("s_waitcnt lgkmcnt(0)\n\t"
                    "v_and_b32 %[at], %[j], v42\n\t"
                    "v_add3_u32 %[at], %[at], v43, %[slots]\n\t"
@@ -706,6 +724,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
                    "s_waitcnt lgkmcnt(0)"
                    : [in] "=&v"(even_in), [at] "=&v"(even_at), [row] "+{v[40:43]}"(even.R)
                    : [j] "v"(even.j_slot), [slots] "v"(slot_base) : "memory");
+    };
+    if constexpr (STRAIGHT && !WIDE) read_ahead();
     if constexpr (STRAIGHT && WIDE)
       asm volatile("s_waitcnt lgkmcnt(0)\n\t"
                    "v_and_b32 %[at], %[j], v42\n\t"
@@ -748,10 +768,18 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           }
         } else if constexpr (DEG2) {
           FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"), FPSCHED_FOLLOW("42"), FPSCHED_NOT_FOLLOWED);
-          if (sub + 1 < kRounds) {
+          if (sub + 1 < kRounds && !(SYNC && (sub & 3u) == 3u)) {
             FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"), FPSCHED_FOLLOW("46"), FPSCHED_NOT_FOLLOWED);
           } else {
             FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "", FPSCHED_FOLLOW("46"), FPSCHED_NOT_FOLLOWED);
+          }
+          if constexpr (SYNC) {
+            if ((sub & 3u) == 3u) {
+              asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
+              moved_even |= groups(even, moved_even);
+              moved_odd |= groups(odd, moved_odd);
+              if (sub + 1 < kRounds) read_ahead();
+            }
           }
         } else {
           FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"), "", "");
@@ -886,10 +914,10 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   FPSCHED_INSTANTIATE(DEG2, false, false, 1, false, false)   \
   FPSCHED_INSTANTIATE(DEG2, false, false, 2, false, false)   \
   FPSCHED_INSTANTIATE(DEG2, false, true, 1, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 0, true, false)
+  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false)
 FPSCHED_INSTANTIATE_MODELS(false)
 FPSCHED_INSTANTIATE_MODELS(true)
+FPSCHED_INSTANTIATE(true, false, false, 0, true, false)
 FPSCHED_INSTANTIATE(false, false, false, 0, false, true)
 #undef FPSCHED_INSTANTIATE_MODELS
 #undef FPSCHED_INSTANTIATE

@@ -93,3 +93,20 @@ def test_a_stage_with_three_edge_slots_gets_the_one_kernel_form(m, grouped, monk
     out, chosen = evaluate(prob, words, group, pairs, capfd)
     assert chosen == ONE_KERNEL and (ref["flags"] == 0).any()
     assert_same(out, ref, f"m {m}")
+
+
+@pytest.mark.parametrize("every", [2, 3, 4, 5, 9, 64])
+@pytest.mark.parametrize("m", [8, 33, 64])
+def test_groups_of_all_sizes_and_remainders(every, m, capfd, monkeypatch):
+    """Groups below, at and above the values taken in at a time, with whole and partial last groups, and a device whose list
+    has one such item behind the other; more candidates than a launch has segments."""
+    import dataclasses
+    monkeypatch.setenv("FPSCHED_VERBOSE", "1")
+    spec = workloads.sync_config(300, every)
+    prob = dataclasses.replace(spec.problem, n_microbatches=m)
+    longest = 3 * m + 3 * (-(-m // every))
+    spec = dataclasses.replace(spec, problem=prob, group=np.minimum(spec.group, m), stride=-(-longest // 8) * 8, swap_per_mille=60)
+    words = np.tile(workloads.generate_sync(spec, threads=4), (60 if (every, m) == (4, 64) else 1, 1, 1))
+    out, form = evaluate(prob, words, spec.group, spec.pairs, capfd)
+    assert form == TWO_PASS
+    assert_same(out, oracle.evaluate_sync(prob, words, spec.group, spec.pairs, threads=8), f"{every} of {m}")
