@@ -37,6 +37,7 @@
  *                         memory even where it would fit LDS;
  *   FPSCHED_SYNC_SLOTS=1  (fpsched_problem_set_sync) the one-kernel form of the model even where the
  *                         two-pass form takes the setting;
+ *   FPSCHED_COPY_SLOTS=1  (fpsched_problem_set_copy_engine) the one-kernel form of the model likewise;
  *   FPSCHED_VERBOSE=1     the cost-model setters print the kernel form and shape they chose.
  */
 #ifndef FPSCHED_H

@@ -123,6 +123,8 @@ struct SlotTables {
 //     leaves an empty slot] [the op] [leaves the second output: expects an empty slot, no cost].  In the other forms:
 //   second rows x 4 ints: 0 and 1 words 0 and 2 of the first edge, 2 the slot of the second output (as word 2), 3 the
 //     second output's link row in the links form
+//   Copy-engine form: rows that follow others as in the plain form; the upper half of word 3 has the units the op allocates |
+//     those it frees << 8.
 //   Wide form (times beyond 24 bits; a slot is two dwords, the time and the tag): word 0 is the latency, word 1 the
 //   duration, word 3 the tag the op leaves | the tag it expects << 8 | number of 16-byte rows in front of its second row
 //   << 16 | the two flags (problems without second edges: word 2 the mask, word 3 the two tags | the slot's offset << 16);
@@ -153,6 +155,7 @@ struct ListTables {
   int32_t n_time_ints;      // timing rows, padded to a multiple of 8
   int32_t off_links;        // links form: link rows, one int per timing row in the same order, in ints
   int32_t link_words;       // links form: words per lane and half (one behind the links for ops that send nothing)
+  int32_t copy_depth;       // copy-engine form: transfers the engine holds at most, else 0
   int32_t mb_bytes;         // costs per micro-batch: bytes of a value, 1 or 2
   int32_t off_sync;         // synchronisation form: group rows, in ints (0: another form)
   int32_t off_check;        // order rows, in ints

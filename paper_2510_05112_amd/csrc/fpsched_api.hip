@@ -65,10 +65,11 @@ struct fpsched_problem {
   int32_t* d_list_ints = nullptr;
   int32_t check_rows_per_wave = 0, check_waves = 0, check_grid = 0, check_vbits = 0;
   int32_t time_waves = 0, time_grid = 0;   // wavefronts per workgroup, resident workgroups
+  std::vector<int32_t> list_image;         // host copy of d_list_ints
   // what the variants' tables are made from: as ltab and its image, second edges as the variants read them
   ListTables variants_tab{};
   std::vector<int32_t> variants_image;
-  ListVariant lists_links, lists_mb, lists_both, lists_sync;
+  ListVariant lists_links, lists_mb, lists_both, lists_sync, lists_copy;
   ListVariant lists_times;                 // the lists without their W items, first pass of the sliding pass
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
   int64_t max_comm = 0;
@@ -246,17 +247,20 @@ CheckKernel check_kernel_of(int vbits, bool no_w = false) { return no_w ? check_
 
 using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
 template <bool DEG2>
-TimeKernel time_kernel_of(bool wide, bool links, int mb_bytes, bool sync) {
-  if (sync) return &time_lists_kernel<true, false, false, 0, true, false>;
-  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false>;
-  if (mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false> : &time_lists_kernel<DEG2, false, false, 1, false, false>;
-  if (mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false> : &time_lists_kernel<DEG2, false, false, 2, false, false>;
-  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false> : &time_lists_kernel<DEG2, false, false, 0, false, false>;
+TimeKernel time_kernel_of(const ListTables& T, bool wide) {
+  const bool links = T.link_words > 0;
+  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false, false>;
+  if (T.mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false, false> : &time_lists_kernel<DEG2, false, false, 1, false, false, false>;
+  if (T.mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false, false> : &time_lists_kernel<DEG2, false, false, 2, false, false, false>;
+  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false, false> : &time_lists_kernel<DEG2, false, false, 0, false, false, false>;
 }
-TimeKernel time_kernel_of(bool deg2, bool wide, bool links = false, int mb_bytes = 0, bool sync = false) {
-  return deg2 ? time_kernel_of<true>(wide, links, mb_bytes, sync) : time_kernel_of<false>(wide, links, mb_bytes, sync);
+// the form that reads these tables
+TimeKernel time_kernel_of(const ListTables& T, bool deg2, bool wide) {
+  if (T.off_sync > 0) return &time_lists_kernel<true, false, false, 0, true, false, false>;
+  if (T.copy_depth > 0) return &time_lists_kernel<true, false, false, 0, false, false, true>;
+  return deg2 ? time_kernel_of<true>(T, wide) : time_kernel_of<false>(T, wide);
 }
-TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true>; }
+TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true, false>; }
 
 // What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
 struct StageEdge { int32_t cls, tag, latency; };
@@ -267,7 +271,8 @@ WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
   for (int cpw = 64 / ((T->D + 1) / 2); cpw >= 1; --cpw) {
     T->cands_per_wave = cpw;   // (rings are 32-byte aligned)
     T->wave_bytes = (int32_t)((kTimeWindowBytes + 512ll * T->link_words + (int64_t)cpw * slot_bytes * T->cand_slots + 31) & ~31ll);
-    const WorkgroupShape shape = workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds);
+    const WorkgroupShape shape = T->copy_depth > 0 ? workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds, kTimeCopyMaxThreads / 64, kTimeCopyWavesPerSimd)
+                                                   : workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds);
     if (shape.waves >= 1) return shape;
   }
   return WorkgroupShape{0, 1};
@@ -482,7 +487,7 @@ int install_list_variant(fpsched_problem* p, ListTables T, const std::vector<int
     if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
     v->capacity = J.size();
   }
-  const TimeKernel kernel = time_kernel_of(deg2, false, T.link_words > 0, T.mb_bytes, T.off_sync > 0);
+  const TimeKernel kernel = time_kernel_of(T, deg2, false);
   if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess)
     return FPSCHED_EHIP;
@@ -494,7 +499,7 @@ int install_list_variant(fpsched_problem* p, ListTables T, const std::vector<int
   v->ok = true;
   if (getenv("FPSCHED_VERBOSE"))
     fprintf(stderr, "[fpsched] list evaluation%s%s%s: %d x %d wavefronts per compute unit (plain: %d x %d), %d candidates each\n",
-            T.link_words > 0 ? ", links" : "", T.mb_bytes > 0 ? ", costs per micro-batch" : "", T.off_sync > 0 ? ", synchronisation" : "",
+            T.copy_depth > 0 ? ", copy engine" : T.link_words > 0 ? ", links" : "", T.mb_bytes > 0 ? ", costs per micro-batch" : "", T.off_sync > 0 ? ", synchronisation" : "",
             shape.groups, shape.waves, p->time_grid / std::max(p->n_cu, 1), p->time_waves, T.cands_per_wave);
   return FPSCHED_OK;
 }
@@ -595,6 +600,28 @@ int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVa
     for (int i = kMaxChunks * D; i < T.n_check_ints / 2; ++i) J[(size_t)T.off_check + 2 * i + 1] = 0;
   // (costs from device memory, kSlotPerMicrobatch, are better than so few wavefronts)
   return install_list_variant(p, T, J, p->lists_deg2, mb && !links ? 6 : 1, v);
+}
+
+// The tables of the copy-engine form: the plain ones, with the units in the rows of the ops themselves; transfers are no
+// busy time.
+int build_copy_variant(fpsched_problem* p, int depth) {
+  p->lists_copy.ok = false;
+  if (!p->lists_ok || p->lists_wide || depth >= kCopyTransfers) return FPSCHED_EUNSUPPORTED;
+  ListTables T = p->ltab;
+  std::vector<int32_t> J = p->list_image;
+  const int D = p->D;
+  T.copy_depth = depth;
+  for (int kind = 1; kind < kNKinds; ++kind)
+    for (int c = 0; c < kMaxChunks; ++c)
+      for (int d = 0; d < D; ++d) {
+        const size_t row = ((size_t)kind * kMaxChunks + c) * D;
+        int32_t* o = &J[(size_t)T.off_check + (row + d) * 2];
+        int32_t* t = &J[(row + (d & 1) * ((D + 1) / 2) + d / 2) * 4];
+        if (t[1] == (int32_t)(kEmptySlot & 0xffu)) t = &J[(size_t)((uint32_t)t[2] >> 18) * 4];   // (takes in the second input; the op follows)
+        t[3] |= (int32_t)((uint32_t)o[0] & 0xffff0000u);
+        if (kind == kO || kind == kL) o[1] = 0;
+      }
+  return install_list_variant(p, T, J, true, 1, &p->lists_copy);
 }
 
 // The tables of the lists without their W items: a W word is a no-op, an activation is consumed by its B item.
@@ -1008,9 +1035,10 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
       ok = hipMalloc(&p->d_list_ints, list_image.size() * sizeof(int32_t)) == hipSuccess &&
            hipMemcpy(p->d_list_ints, list_image.data(), list_image.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
       for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits)),
-                                 reinterpret_cast<const void*>(time_kernel_of(p->lists_deg2, p->lists_wide))})
+                                 reinterpret_cast<const void*>(time_kernel_of(p->ltab, p->lists_deg2, p->lists_wide))})
         ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
       p->ltab.ints = p->d_list_ints;
+      p->list_image = list_image;
     }
     if (ok && p->slots_ok) {
       ok = hipMalloc(&p->d_slot_ints, p->slot_ints.size() * sizeof(int32_t)) == hipSuccess &&
@@ -1115,7 +1143,7 @@ void fpsched_problem_destroy(fpsched_problem* p) {
     if (p->d_times_ints) (void)hipFree(p->d_times_ints);
     if (p->d_mb_raw) (void)hipFree(p->d_mb_raw);
     if (p->d_mb_rows) (void)hipFree(p->d_mb_rows);
-    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync, &p->lists_times})
+    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync, &p->lists_copy, &p->lists_times})
       if (v->d_image) (void)hipFree(v->d_image);
     if (p->d_times_links_image) (void)hipFree(p->d_times_links_image);
     if (p->d_slide_links_image) (void)hipFree(p->d_slide_links_image);
@@ -1208,7 +1236,7 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant, T.link_words > 0, T.mb_bytes, T.off_sync > 0), dim3((unsigned)time_blocks),
+  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(T, variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
                      out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), starts ? *starts : StartTimes{});
@@ -1247,6 +1275,11 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
+    // (a batch of a few candidates per compute unit is one launch's latency: two towers on 16 devices, depth 3, the slot kernel
+    // and the two passes: 256 candidates of 8 micro-batches 61 and 74 us, 4,000 of 20 149 and 148, 12,000 of 60 735 and 410,
+    // 20,011 of 45 740 and 557, 65,536 of 64 2,800 and 2,477)
+    if (copy_on_slots && p->lists_copy.ok && n_cand >= 8ll * p->n_cu)
+      return run_list_evaluation(p, &p->lists_copy, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (sync_on_slots && p->lists_sync.ok)
       return run_list_evaluation(p, &p->lists_sync, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (!copy_on_slots && !sync_on_slots) {
@@ -1901,6 +1934,10 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
     // the slot kernel has a form of this model too: the plain tables, 32 more dwords of LDS per lane for
     // the rings of the copy timeline
     p->copy_slots_ok = false;
+    // the two-pass evaluation takes it where times fit 24 bits and few transfers are in the engine at a time
+    p->lists_copy.ok = false;
+    const int list_rc = p->slots_ok && !getenv("FPSCHED_COPY_SLOTS") ? build_copy_variant(p, depth) : FPSCHED_EUNSUPPORTED;
+    if (list_rc != FPSCHED_OK && list_rc != FPSCHED_EUNSUPPORTED) return list_rc;
     if (p->slots_ok) {
       const SlotTables& PT = p->stab;
       const SlotGeometry geo = slot_geometry(PT.n_shared_ints, PT.lanes_per_cand, PT.state_words + kSlotCopyWords,

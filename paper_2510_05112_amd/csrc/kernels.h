@@ -67,10 +67,13 @@ __global__ void eval_slot_kernel(SlotTables T, const uint16_t* ops, long long n_
 // wavefront; per row out_info (kRow* | stop, then the busy time in the low half) and out_peak.  dynamic: more blocks of
 // rows than resident wavefronts, taken draw_blocks at a time, the further ones from counter[1]; else it sets *counter for the timing pass.
 // time_lists_kernel: reads out_info from out_idle, writes the results.  DEG2 = some stage has two inputs or outputs;
-// WIDE = times beyond 24 bits; MB: bytes of a value of the cost table (0: none).
+// WIDE = times beyond 24 bits; MB: bytes of a value of the cost table (0: none);
+// COPY: copy engine (T.copy_depth < kCopyTransfers).
 constexpr int kCheckMaxThreads = 512;
 constexpr int kCheckWavesPerSimd = 3;
 constexpr int kTimeMaxThreads = 1024;
+constexpr int kTimeCopyMaxThreads = 512, kTimeCopyWavesPerSimd = 3;   // copy-engine form (up to 168 registers)
+constexpr int kCopyTransfers = 4;   // ... transfers and events that a lane keeps
 constexpr int kTimeWindowBytes = 2 * 64 * 32;   // op windows of a wavefront of the timing pass
 // VBITS 0, 1, 2: up to 1, 2, 4 stages per device.  NO_W: W items are no-ops that only have to be in range (tables: their
 // rows ask for kPadState and leave it).
@@ -86,7 +89,7 @@ struct StartTimes {
   int32_t* stops;       // [n_cand][D]
   int32_t escape_cap, lanes;
 };
-template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES>
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, bool COPY>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block,

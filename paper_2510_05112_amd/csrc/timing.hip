@@ -58,6 +58,17 @@
 // such a stage have one item per micro-batch.)  65,536 candidates of 12 devices, 64 micro-batches, groups of four: 1.03 ms
 // with one value a step in a step with branches, 0.76 now; groups looked after every second round 0.81, every eighth 0.84.
 //
+// COPY, the copy-engine model (the paper names CPU offloading without saying how an offload is timed): offload and reload
+// items run on a copy timeline of the device.  The walk hands such an item over when it reaches it and goes on at once, unless
+// copy_depth transfers are unfinished (then it waits for the oldest of them); a transfer starts at max(hand-over, finish of the
+// transfer before it).  A backward item waits for the reload of its activation.  Memory is a sum over events in time order: a
+// reload allocates at its start, an offload releases at its end, compute events come first at equal times; so the peak is
+// found here and not in the order pass.  Transfers are no busy time; the makespan covers both timelines.  The last transfers
+// and the events to come stand in registers, shifted along: in LDS every lane's loop over them was a wait for all lanes.
+// 20,011 candidates of 16 devices (two towers), 45 micro-batches, depth 3: 0.72 ms as a form of the slot kernel, all devices
+// in every round; 1.43 ms here with rings in LDS, 0.49 (and 0.05 for the order pass) with registers.  (With eight transfers,
+// for depths up to 7, as long as there or up to a fifth longer.)
+//
 // TIMES, the first pass of the weight-gradient sliding (wslide.hip) on problems of the plain form: the lists without their W
 // items (a W word is an op of the device's own without a cost), of which it leaves the low sixteen bits of each op's start
 // time, the ops that waited 2^16 time units or more, and where the lists stop.  A start time takes the place of the op's
@@ -295,18 +306,19 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
 #define FPSCHED_ROW_OF_even "v[40:43]"
 #define FPSCHED_ROW_OF_odd "v[44:47]"
 
-template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES>
-__global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, bool COPY>
+__global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : 4))) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block, StartTimes starts) {
-  static_assert(!WIDE || !(LINKS || MB || SYNC), "these forms have times of 24 bits");
+  static_assert(!WIDE || !(LINKS || MB || SYNC || COPY), "these forms have times of 24 bits");
+  static_assert(!COPY || (DEG2 && !LINKS && !MB && !SYNC && !TIMES), "rows that follow others");
   static_assert(!SYNC || (DEG2 && !LINKS && !MB), "rows that follow others");
   static_assert(!TIMES || !(DEG2 || WIDE || LINKS || MB || SYNC), "");
   constexpr unsigned kRowBytes = 16u;
-  constexpr bool PLAIN = !WIDE && !LINKS && !MB;   // (TIMES and SYNC too)
+  constexpr bool PLAIN = !WIDE && !LINKS && !MB && !COPY;   // (TIMES and SYNC too)
   constexpr bool STRAIGHT = PLAIN || !DEG2;   // the step without branches
-  constexpr bool SPLIT = !WIDE && (!DEG2 || PLAIN);   // rows with the slot's mask and offset in a word each
+  constexpr bool SPLIT = !WIDE && (!DEG2 || PLAIN || COPY);   // rows with the slot's mask and offset in a word each
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
   constexpr int kPieces = STRAIGHT ? 4 : 2;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
@@ -349,6 +361,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   const unsigned row_stride = (unsigned)D * kRowBytes;
   const unsigned stride2 = (unsigned)stride * 2u, stride_pos = position_of((unsigned)stride);
 
+  constexpr int kTransfers = COPY ? kCopyTransfers : 1;
   // one device of the lane: its op window, and the op under its cursor, decoded.  A device without an op looks at its
   // own word with an L that keeps it waiting.
   struct Device {
@@ -362,6 +375,11 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     unsigned info;      // what the order pass left for this row: kRow* | stop
     unsigned busy;
     unsigned link_rows, links;   // LINKS: where its devices' link rows are, the lane's link words
+    // COPY: the copy timeline, the last COPY transfers: finish << 8 and key (a reload's word without its kind, else all ones),
+    // newest first (0: none); the memory events that the walk has not passed, oldest first, time << 8 | units (all ones: none),
+    // with a bit each for those that allocate
+    unsigned copy_end[kTransfers], copy_key[kTransfers], event[kTransfers], event_adds, n_events;
+    int mem, pk, cap;
     unsigned taken;              // SYNC: values of its group's item taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
     unsigned own_place, next_place;   // TIMES: places in the ring of the words under and behind the cursor
@@ -378,12 +396,19 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     x.pos = position_of(1u);
     x.info = 0u;
   };
+  auto no_transfers = [&](Device& x) {
+#pragma unroll
+    for (int i = 0; i < kTransfers; ++i) { x.copy_end[i] = 0u; x.copy_key[i] = ~0u; x.event[i] = ~0u; }
+    x.event_adds = 0u; x.n_events = 0u; x.mem = 0; x.pk = 0;
+  };
   auto set_up = [&](Device& x, int k) {
     x.win = lds0 + (unsigned)wave * (unsigned)kTimeWindowBytes + (unsigned)k * kWindowBytes + (unsigned)lane * 4u;
     x.meta = tables + (unsigned)(k * P + pair) * kRowBytes;
     x.link_rows = LINKS ? tables + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
     x.links = LINKS ? wave_at + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
+    x.cap = COPY && (k == 0 || has_odd) && lane_ok ? T.ints[T.off_dev + 2 * (d0 + k) + 1] : 0x7fffffff;
+    no_transfers(x);
     x.own_place = x.win; x.next_place = x.win; x.n_late = 0;
     for (int i = 0; i < kPieces; ++i) x.pend[i] = make_uint4(0u, 0u, 0u, 0u);
     idle_device(x);
@@ -579,6 +604,75 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
     }
     return moved;
   };
+  // COPY: the memory events in front of a time are summed up, and `units` that come in at an earlier time among them
+  auto pass_events = [&](Device& x, unsigned until, unsigned from, int units) {
+    while (x.event[0] < until) {
+      const int now = x.event[0] >= from ? units : 0, change = (int)(x.event[0] & 0xffu);
+      units -= now;
+      x.mem += now;
+      x.pk = max(x.pk, x.mem);
+      x.mem += (x.event_adds & 1u) != 0u ? change : -change;
+      x.pk = max(x.pk, x.mem);
+#pragma unroll
+      for (int i = 0; i + 1 < kTransfers; ++i) x.event[i] = x.event[i + 1];
+      x.event[kTransfers - 1] = ~0u;
+      x.event_adds >>= 1;
+      --x.n_events;
+    }
+    x.mem += units;
+    x.pk = max(x.pk, x.mem);
+  };
+  auto copy_step = [&](Device& x) -> unsigned long long {
+    const unsigned offset = (unsigned)x.R.w;
+    const unsigned at_slot = (x.j_slot & (unsigned)x.R.z) + ((offset & 0xffffu) + slot_base);
+    const unsigned ready = lds_read<uint32_t>(at_slot) + (unsigned)x.R.x;
+    unsigned long long moved;
+    const unsigned zero = 0u;
+    asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready), "v"(zero));
+    if (__builtin_amdgcn_inverse_ballot_w64(moved)) {
+      const unsigned kind = x.j_slot >> 15, key = x.j_slot >> 2 & 0x1fffu;
+      const unsigned dur = (unsigned)x.R.y & 0xffffff00u, allocated = offset >> 16 & 0xffu, freed = offset >> 24;
+      const bool transfer = kind - (unsigned)kO < 2u, reload = kind == (unsigned)kL;
+      // a B item waits for the reload of its activation, which may still run if it is among the last transfers (one further
+      // back than copy_depth has finished before the device got here, so a match there changes nothing); a transfer is handed
+      // over when the engine is done with the one copy_depth transfers back
+      unsigned start = max(x.free_at, ready);
+      const unsigned reloaded = kind == (unsigned)kB ? key : 0x10000u;
+#pragma unroll
+      for (int i = 0; i < kTransfers; ++i) {
+        const bool waits = transfer ? T.copy_depth == i + 1 : x.copy_key[i] == reloaded;
+        start = max(start, waits ? x.copy_end[i] : 0u);
+      }
+      const unsigned val = start + (unsigned)x.R.y;
+      x.free_at = transfer ? start : val & 0xffffff00u;
+      if (!transfer) lds_write<uint32_t>(at_slot, val);
+      pass_events(x, x.free_at, start, transfer ? 0 : (int)allocated);
+      if (transfer) {
+        // a reload allocates when it starts, an offload releases when it ends
+        const unsigned begin = max(start, x.copy_end[0]), end = begin + dur;
+        const unsigned event = reload ? begin | allocated : end | freed;
+#pragma unroll
+        for (int i = kTransfers - 1; i > 0; --i) { x.copy_end[i] = x.copy_end[i - 1]; x.copy_key[i] = x.copy_key[i - 1]; }
+        x.copy_end[0] = end;
+        x.copy_key[0] = reload ? key : ~0u;
+#pragma unroll
+        for (int i = 0; i < kTransfers; ++i) x.event[i] = x.n_events == (unsigned)i ? event : x.event[i];
+        x.event_adds |= (reload ? 1u : 0u) << x.n_events;
+        ++x.n_events;
+      } else {
+        x.mem -= (int)freed;
+      }
+      const unsigned behind = (unsigned)x.R.z >> 14 & ~15u;
+      if (behind != 0u) {
+        x.R = lds_read<lds_int4>(tables + behind);
+      } else {
+        decode(x, x.w_next);
+        x.pos = (x.pos | kPosBetween) + 2u;
+        x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
+      }
+    }
+    return moved;
+  };
   // SYNC, every fourth round: the devices at an item of a group of micro-batches (their rows never issue and name another
   // one, then one of the second edge) take in what has arrived of the values it waits for, up to four at a time; with the last one the
   // item runs, and leaves its value in the slots of its micro-batches.  Returns the lanes that took in a value or issued.
@@ -687,6 +781,7 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           clear_own(own_word);
           if (has_odd) clear_own(own_word + kSlotBytes);
           if (pair == 0) lds_write<uint32_t>(at_max, 0u);
+          if (COPY) { no_transfers(even); no_transfers(odd); }
           if (LINKS)
             for (unsigned i = 0; i < links_bytes / 2u; i += 256u) { lds_write<unsigned>(even.links + i, 0u); lds_write<unsigned>(odd.links + i, 0u); }
           const long long r = cand * D + d0;
@@ -838,8 +933,8 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
         if (sub + 1 == kRounds)
           asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next), "+v"(even.link), "+v"(odd.link) : : "memory");
       } else {
-        moved_even = step(even);
-        moved_odd = step(odd);
+        moved_even = COPY ? copy_step(even) : step(even);
+        moved_odd = COPY ? copy_step(odd) : step(odd);
       }
       // A segment none of whose lanes issued is finished, and stays so: nothing it reads changes any more.  It could
       // only be restarted at the next top-up anyway, so only the last round in front of it looks.  Cheap scalar
@@ -856,7 +951,14 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
           const bool stuck = any_in_segment(__ballot(!even_stops || !odd_stops || (both & kRowStuck) != 0u));
           const bool malformed = any_in_segment(__ballot((even_stops && (even.info & kRowMalformed) != 0u) || (odd_stops && (odd.info & kRowMalformed) != 0u)));
           const bool unfinished = any_in_segment(__ballot((both & kRowIncomplete) != 0u));
-          const bool over = any_in_segment(__ballot((both & kRowOverCap) != 0u));
+          if (COPY && ended) {
+            // what the engine still had to do; the makespan covers both timelines
+            pass_events(even, ~0u, ~0u, 0);
+            pass_events(odd, ~0u, ~0u, 0);
+            even.free_at = max(even.free_at, even.copy_end[0]);
+            odd.free_at = max(odd.free_at, odd.copy_end[0]);
+          }
+          const bool over = any_in_segment(__ballot(COPY ? even.pk > even.cap || odd.pk > odd.cap : (both & kRowOverCap) != 0u));
           if (ended) {
             const unsigned flags = stuck ? kDeadlock | (malformed ? kIncomplete : 0u)
                                          : (unfinished ? (unsigned)kIncomplete : (over ? (unsigned)kOverCap : 0u));
@@ -880,10 +982,10 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
               const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
               const long long r = cand * D + d0;
               out_idle[r] = failed ? -1ll : (long long)((int)ms - (int)even.busy);
-              if (failed) out_peak[r] = -1;
+              if (COPY || failed) out_peak[r] = failed ? -1 : even.pk * T.unit_scale;
               if (has_odd) {
                 out_idle[r + 1] = failed ? -1ll : (long long)((int)ms - (int)odd.busy);
-                if (failed) out_peak[r + 1] = -1;
+                if (COPY || failed) out_peak[r + 1] = failed ? -1 : odd.pk * T.unit_scale;
               }
               if (pair == 0) {
                 out_makespan[cand] = failed ? 0x7fffffffffffffffll : (long long)ms;
@@ -904,21 +1006,22 @@ __global__ __launch_bounds__(kTimeMaxThreads) void time_lists_kernel(
   }
 }
 
-#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES)                                                              \
-  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES>(ListTables, const uint16_t*, long long, int, long long*, \
+#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY)                                                        \
+  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY>(ListTables, const uint16_t*, long long, int, long long*, \
                                                                     long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
-#define FPSCHED_INSTANTIATE_MODELS(DEG2)                     \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false)   \
-  FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 0, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 1, false, false)   \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 2, false, false)   \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 1, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false)
+#define FPSCHED_INSTANTIATE_MODELS(DEG2)                            \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false, false)   \
+  FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 0, false, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 1, false, false, false)   \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 2, false, false, false)   \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 1, false, false, false)    \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false, false)
 FPSCHED_INSTANTIATE_MODELS(false)
 FPSCHED_INSTANTIATE_MODELS(true)
-FPSCHED_INSTANTIATE(true, false, false, 0, true, false)
-FPSCHED_INSTANTIATE(false, false, false, 0, false, true)
+FPSCHED_INSTANTIATE(true, false, false, 0, true, false, false)
+FPSCHED_INSTANTIATE(false, false, false, 0, false, true, false)
+FPSCHED_INSTANTIATE(true, false, false, 0, false, false, true)
 #undef FPSCHED_INSTANTIATE_MODELS
 #undef FPSCHED_INSTANTIATE
 

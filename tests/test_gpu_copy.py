@@ -121,3 +121,45 @@ def test_configuration_five_reduced_batch_and_switching():
         free.set_copy_engine(2)
     assert e.value.code == -1
     free.close()
+
+
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+def test_two_pass_and_one_kernel_forms(depth, monkeypatch, capfd):
+    """Both forms at the depths that the two passes take and the first one beyond, short and long transfers, batches on either
+    side of the line between the forms and one of more candidates than a launch has segments."""
+    monkeypatch.setenv("FPSCHED_VERBOSE", "1")
+    rng = np.random.default_rng(depth)
+    for i, prob in enumerate(transfer_problems()):
+        lists = []
+        for t in range(24):
+            base = random_valid_lists(prob, rng, 0.3 * (t % 2), 0.3 + 0.3 * ((t // 2) % 2))
+            lists += [base, perturb(base, rng, 1 + t % 3)]
+        words = np.tile(batch_from_lists(lists), (1000 if i == 1 and depth == 3 else 50, 1, 1))
+        ref = oracle.evaluate_copy(prob, words, depth=depth, threads=8)
+        capfd.readouterr()
+        out, _ = gpu_copy(prob, words, depth)
+        assert ("list evaluation, copy engine" in capfd.readouterr().err) == (depth < 4)
+        assert_same(out, ref, f"problem {i} two passes")
+        few = {name: a[:40] for name, a in ref.items()}
+        assert_same(gpu_copy(prob, words[:40], depth)[0], few, f"problem {i} small batch")
+        monkeypatch.setenv("FPSCHED_COPY_SLOTS", "1")
+        capfd.readouterr()
+        out, _ = gpu_copy(prob, words, depth)
+        assert "list evaluation, copy engine" not in capfd.readouterr().err
+        assert_same(out, ref, f"problem {i} one kernel")
+        monkeypatch.delenv("FPSCHED_COPY_SLOTS")
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_two_passes_on_random_problems(seed):
+    from test_gpu_fuzz import random_problem
+    rng = np.random.default_rng(7000 + seed)
+    for i in range(6):
+        prob = random_problem(rng)
+        lists = []
+        for t in range(24):
+            base = random_valid_lists(prob, rng, 0.3 * (t % 2), 0.2 + 0.3 * ((t // 2) % 2))
+            lists += [base, perturb(base, rng, 1 + t % 3)]
+        words = np.tile(batch_from_lists(lists), (50, 1, 1))
+        depth = int(rng.integers(1, 4))
+        assert_same(gpu_copy(prob, words, depth)[0], oracle.evaluate_copy(prob, words, depth=depth, threads=8), f"{seed} {i} depth {depth}")
