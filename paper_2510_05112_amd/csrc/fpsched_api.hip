@@ -1073,6 +1073,8 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
                         hipMemcpy(p->d_times_ints, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess &&
                         hipFuncSetAttribute(reinterpret_cast<const void*>(slot_kernel_of<kSlotTimes>(p->slot_v, p->slot_deg2, p->stab.n_classes == 1)),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess &&
+                        hipFuncSetAttribute(reinterpret_cast<const void*>(&wslide_place_rows_kernel),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess &&
                         hipFuncSetAttribute(reinterpret_cast<const void*>(p->slot_v > 2 ? &wslide_place_kernel<true> : &wslide_place_kernel<false>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
         if (up) {
@@ -2395,7 +2397,20 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
                        draw_block, starts, stops, (const int32_t*)nullptr, escapes, escape_cap);
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   }
-  // pass 2: every row places its W items on its own
+  // pass 2: every row places its W items on its own; a wavefront per row where they are few (both passes, a lane and a
+  // wavefront per row: 4,096 rows of 32 x 128 x 2 2333 and 1535 us, 16,384 2372 and 1778, 65,536 2494 and 3085; of
+  // 16 x 64 x 2 2,048 rows 617 and 452 us, 8,192 611 and 514, 16,384 623 and 636; of 8 x 32 x 2 16,384 255 and 236, 32,768
+  // 269 and 316; of 4 x 200 x 4 512 3092 and 1348, 32,768 4249 and 3972)
+  const int stash = (int)std::min<int64_t>((int64_t)gen_max_chunks(p) * p->m, stride_words);
+  const int64_t rows_shared = place_rows_bytes + 4ll * 4 * kMaxDevices, rows_wave = slide_rows_wave_bytes(stride_out_words, stash);
+  const int64_t rows_waves = std::min<int64_t>({(p->max_lds - rows_shared) / rows_wave, kSlideThreads / 64, p->D});
+  if (n_cand * p->D <= 16384 && rows_waves >= std::min(p->D, 4)) {
+    hipLaunchKernelGGL(wslide_place_rows_kernel, dim3((unsigned)n_cand), dim3(64 * (unsigned)rows_waves),
+                       (size_t)(rows_shared + rows_waves * rows_wave), st, p->stab, d_ops, (int)stride_words, starts, escapes,
+                       escape_cap, stops, timed_flags, d_ops_out, (int)stride_out_words, stash,
+                       reinterpret_cast<long long*>(out.makespan), reinterpret_cast<long long*>(out.idle), out.peak, out.flags);
+    return check_hip(hipGetLastError());
+  }
   hipLaunchKernelGGL(p->slot_v > 2 ? wslide_place_kernel<true> : wslide_place_kernel<false>, dim3((unsigned)place_blocks), dim3(place_threads),
                      (size_t)place_rows_bytes + (place_threads / 64) * kSlideWaveLdsBytes, st, p->stab, d_ops,
                      (long long)n_cand, (int)stride_words,

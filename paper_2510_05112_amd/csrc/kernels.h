@@ -149,6 +149,17 @@ __global__ void wslide_place_kernel(SlotTables T, const uint16_t* ops, long long
                                     long long* out_makespan, long long* out_idle, int* out_peak,
                                     unsigned char* out_flags);
 
+// ... and for few candidates: one wavefront per row, a workgroup per candidate; dynamic LDS: the metadata rows, 4 ints per
+// device, slide_rows_wave_bytes per wavefront.  stash: bound on the B items of a row that are issued.
+__host__ __device__ constexpr int64_t slide_rows_wave_bytes(int64_t stride_out, int64_t stash) {
+  return 2 * stride_out + ((10 * stash + 8 + 15) & ~15ll);
+}
+__global__ void wslide_place_rows_kernel(SlotTables T, const uint16_t* ops, int stride, const uint32_t* start_low,
+                                         const uint32_t* escapes, int escape_cap, const int32_t* stop_pos,
+                                         const unsigned char* timed_flags, uint16_t* ops_out, int stride_out, int stash,
+                                         long long* out_makespan, long long* out_idle, int* out_peak,
+                                         unsigned char* out_flags);
+
 // Pareto front: at most kParetoMaxTiles tiles of kTile candidates (one cursor per tile in LDS).
 constexpr int kParetoMergeThreads = kTile / 2;
 constexpr int kParetoMaxTiles = 8192;
