@@ -2018,7 +2018,7 @@ static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const
 // 32,768 of them, 8 per segment, 6.53 and 5.21; of 32 x 64 x 2, 4 and 6 per segment, 1.92 and 1.99, 2.82 and 2.37; of
 // 20 x 100 x 2, 2.7 and 5.3 per segment, 1.78 and 2.00, 3.27 and 2.79; 16,384 of 24 x 80 x 2, 4 per segment, 2.08 and 1.91;
 // 30,000 of 12 x 40 x 3, 2.9 per segment, 2.11 and 2.21; 32,768 of 16 x 64 x 2, 4 per segment, 1.84 and 1.65).
-struct GenShape { int waves; int64_t blocks, lds_bytes; };
+struct GenShape { int waves, resident; int64_t blocks, lds_bytes; };   // resident: wavefronts that a compute unit has room for
 static GenShape gen_shape(const fpsched_problem* p, int64_t n_sets, int64_t sets_per_wave, int64_t shared_ints, int64_t wave_ints) {
   const int64_t lds_ints = p->max_lds / 4, segments_of_8 = 8ll * p->n_cu * sets_per_wave;
   int want = 16;
@@ -2036,8 +2036,9 @@ static GenShape gen_shape(const fpsched_problem* p, int64_t n_sets, int64_t sets
   }
   // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
   const int64_t wavefronts = (n_sets + sets_per_wave - 1) / sets_per_wave;
+  const int resident = best_waves * best_groups;
   best_waves = (int)std::clamp<int64_t>((wavefronts + p->n_cu - 1) / p->n_cu, 1, best_waves);
-  return GenShape{best_waves, std::min<int64_t>((wavefronts + best_waves - 1) / best_waves, (int64_t)p->n_cu * best_groups),
+  return GenShape{best_waves, resident, std::min<int64_t>((wavefronts + best_waves - 1) / best_waves, (int64_t)p->n_cu * best_groups),
                   4 * (shared_ints + best_waves * wave_ints)};
 }
 
@@ -2130,14 +2131,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   // stages per device, two at four, none at one)
   const int64_t shared_ints = 3ll * V * p->D * (slide && deg == 1 ? 4 : 8);
   DevTables tables = p->tables;
-  // A larger ring of items evens out lanes whose items come in bursts; but a set that ends has its ring emptied while the
-  // other sets of its wavefront wait.  So it pays where a set has many items per actor and a wavefront few sets.  Items
-  // per actor / sets per wavefront, rings of 16 and 32: 4 (65,536 sets of 4 x 16 x 2) 183 and 280 us, 16 (of 8 x 32 x 2) 800 and
-  // 820, 16 (of 4 x 128 x 1) 533 and 621, 32 (of 16 x 64 x 1) 916 and 933, 48 (30,000 of 12 x 40 x 3) 2439 and 2385, 60
-  // (16,384 of 6 x 100 x 3) 2360 and 2169, 64 (32,768 of 16 x 64 x 2) 1985 and 1960, 80 (16,384 of 10 x 120 x 2) 2167 and
-  // 1425, 256 (of 32 x 128 x 2) 4138 and 3970.  (64: 4735 on the last, whose wavefronts then do not all find room.)
-  const int sets_per_wave = 64 / p->D, items_per_actor = 2 * gen_max_chunks(p) * p->m;
-  tables.gen_events = items_per_actor >= 40 * sets_per_wave ? kGenMoreEvents : kGenFewEvents;
+  tables.gen_events = kGenFewEvents;
   // (one word more: the word of the next entry is written when all are in as well)
   tables.gen_queue_words = slide && V > 1 ? (int)((int64_t)V * p->m * (V == 2 ? 1 : 2) / 32) + 1 : 0;
   auto wave_ints_of = [&](int64_t sets) {
@@ -2147,10 +2141,24 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   const int64_t lds_ints = p->max_lds / 4;
   int cpw = 64 / p->D;
   while (cpw > 1 && shared_ints + wave_ints_of(cpw) + 64 > lds_ints) --cpw;
-  const int64_t wave_ints = wave_ints_of(cpw);
-  if (shared_ints + wave_ints > lds_ints) return FPSCHED_EUNSUPPORTED;
+  if (shared_ints + wave_ints_of(cpw) > lds_ints) return FPSCHED_EUNSUPPORTED;
   tables.gen_sets = cpw;
-  const GenShape shape = gen_shape(p, n_sets, cpw, shared_ints, wave_ints);
+  GenShape shape = gen_shape(p, n_sets, cpw, shared_ints, wave_ints_of(cpw));
+  // A larger ring of items evens out lanes whose items come in bursts; but a set that ends has its ring emptied while the
+  // other sets of its wavefront wait.  So it pays where a set has many items per actor and a wavefront few sets.  Items
+  // per actor / sets per wavefront, rings of 16 and 32: 4 (65,536 sets of 4 x 16 x 2) 183 and 280 us, 16 (of 8 x 32 x 2) 800 and
+  // 820, 16 (of 4 x 128 x 1) 533 and 621, 32 (of 16 x 64 x 1) 916 and 933, 48 (30,000 of 12 x 40 x 3) 2439 and 2385, 60
+  // (16,384 of 6 x 100 x 3) 2360 and 2169, 64 (32,768 of 16 x 64 x 2) 1985 and 1960, 80 (16,384 of 10 x 120 x 2) 2167 and
+  // 1425, 256 (of 32 x 128 x 2) 4138 and 3970.  (64: 4735 on the last, whose wavefronts then do not all find room.)  And it
+  // must not cost wavefronts: 65,536 of 32 x 128 x 2 14,353 us with 8 per compute unit and rings of 32, 11,607 with 12
+  // and 16; 32,768 of 20 x 100 x 2 3419 and 3200.
+  if (slide && 2 * gen_max_chunks(p) * p->m >= 40 * (64 / p->D)) {
+    tables.gen_events = kGenMoreEvents;
+    const int64_t more_ints = wave_ints_of(cpw);
+    const GenShape other = gen_shape(p, n_sets, cpw, shared_ints, more_ints);
+    if (shared_ints + more_ints + 64 <= lds_ints && other.resident >= shape.resident) shape = other;
+    else tables.gen_events = kGenFewEvents;
+  }
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
   static const GenKernel table[2][3][2] = {
