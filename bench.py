@@ -40,12 +40,12 @@ def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
 
 # the list evaluation (order pass and timing pass): plain, with costs per micro-batch (--mb-costs), with link occupancy
 # (--links), with both
-MEASURED = {("cfg4", 65536): counted(1.664e10, 1.111e9, 3.151, "list_evaluation.md")}
+MEASURED = {("cfg4", 65536): counted(1.069e10, 1.062e9, 2.808, "list_evaluation.md")}
 MEASURED_MB = {("cfg4", 65536): counted(None, 1.426e9, 4.010, "list_evaluation.md")}
 MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.426e9, 3.715, "list_evaluation.md")}
 MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.782e9, 4.916, "list_evaluation.md")}
 # the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
-MEASURED_SYNC = {("sync4", 65536): counted(None, 3.176e8, 1.150, "list_evaluation.md")}
+MEASURED_SYNC = {("sync4", 65536): counted(None, 2.389e8, 0.918, "list_evaluation.md")}
 MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}
 # the copy engine (--config 5 --copy-engine 4)
 MEASURED_COPY = {("cfg5", 131072): counted(None, 1.850e9, 5.106, "eval_sync_kernel.md")}
@@ -54,9 +54,9 @@ MEASURED_WSLIDE = {("cfg4", 65536): counted(3.38e10, 6.281e9, 16.01, "wslide_ker
 MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.813e9, 10.74, "wslide_kernel_cfg4.md")}
 # the generator (--mode generate; traffic: WRITE_SIZE x 1024 plus the parameter sets read), generator and evaluator in one
 # kernel (--mode search --fused), the same with the sliding pass in it (--slide)
-MEASURED_GENERATE = {("cfg4", 65536): counted(5.40e9, 7.390e9, 11.77, "generate_kernel_cfg4.md")}
-MEASURED_FUSED = {("cfg4", 65536): counted(None, 7.649e9, 11.00, "generate_kernel_cfg4.md")}
-MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 9.320e9, 13.82, "generate_kernel_cfg4.md")}
+MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.762e9, 9.21, "generate_kernel_cfg4.md")}
+MEASURED_FUSED = {("cfg4", 65536): counted(None, 6.020e9, 10.14, "generate_kernel_cfg4.md")}
+MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 7.325e9, 11.65, "generate_kernel_cfg4.md")}
 
 
 def rooflines(alg_bytes, kernel_ms, kernel_name, figures, units=None):
