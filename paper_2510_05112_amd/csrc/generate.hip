@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
                      "s_mov_b64 exec, %[is_f]\n\t"
                      "v_add_u32 %[f], %[f], %[by]\n\t"
                      "s_mov_b64 exec, -1"
-                     : [b] "+v"(b), [bl] "+v"(bl), [f] "+v"(f) : [by] "v"(by), [is_b] "s"(picked_b), [is_f] "s"(picked_f));
+                     : [b] "+&v"(b), [bl] "+&v"(bl), [f] "+&v"(f) : [by] "v"(by), [is_b] "s"(picked_b), [is_f] "s"(picked_f));
         if constexpr (!SLIDE) w += of(picked & is_w, by, 0u);
       };
       if constexpr (V <= 2) {
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
                      "s_mov_b64 exec, %[is_b]\n\t"
                      "v_add_u32 %[next], 1, %[next]\n\t"
                      "s_mov_b64 exec, -1"
-                     : [next] "+v"(next_step), [slot] "+v"(now.slot)
+                     : [next] "+&v"(next_step), [slot] "+&v"(now.slot)
                      : [j] "v"(j), [slots] "v"(slot), [step] "s"(step), [all] "s"(picked), [is_b] "s"(picked_b));
       } else {
         next_step = of(picked, step + 1u, next_step);

@@ -123,188 +123,237 @@ __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1
 
 }  // namespace
 
-// One step of one half of the devices in the plain form (X, Y: this half and the other one; RX, RY, RW: registers of the
-// words of this half's row, OZ, OW: of the last two of the other's).  As written by the compiler a step has a branch around
-// what the issuing lanes do, and waits in front of its decision for all that the step before it has requested; here
+// The rounds between two looks at the lists, in one statement: what a step requests is waited for in the next one or the
+// one behind it, by count, and nothing may come between that does not know it (a copy of such a register, say).  As written
+// by the compiler a step has a branch around what the issuing lanes do, and waits in front of its decision for all that the
+// step before it has requested; here
 //   - the decision becomes the execution mask itself, and nothing branches;
-//   - the slots that this half writes are the only thing the other half's read of its slots has to follow, so that read is
+//   - the slots that a half writes are the only thing the other half's read of its slots has to follow, so that read is
 //     made before this half's issued ops give way to the next ones, and their rows and words are on their way while the
 //     other half decides.
-// In flight at the beginning, oldest first: this half's slot, the other half's row and the word behind it.
-// (FOLLOW: for rows that another row follows in the place of the next word's, in the form with second edges)
-#define FPSCHED_STEP(X, Y, X_ROW, Y_ROW, RX, RY, RW, READ_AHEAD, FOLLOW, NOT_FOLLOWED)                                     \
-  asm volatile(                                                                                                          \
-      "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
-      "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
-      "v_cmpx_eq_u32_sdwa %[moved], %[in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                                   \
-      "v_max_u32 %[t], %[free], %[in]\n\t"                                                                              \
-      "v_add_u32 %[t], %[t], v" RY "\n\t"                                                                               \
-      "ds_write_b32 %[at], %[t]\n\t"                                                                                    \
-      "v_and_b32 %[free], 0xffffff00, %[t]\n\t"                                                                         \
-      "s_mov_b64 exec, -1\n\t" READ_AHEAD                                                                               \
-      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
-      "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
-      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t" FOLLOW                                                         \
-      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t" NOT_FOLLOWED                                                            \
-      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
-      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
-      "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
-      "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
-      "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
-      "s_mov_b64 exec, -1"                                                                                               \
-      : [in] "+v"(X##_in), [at] "+v"(X##_at), [free] "+v"(X.free_at), [next] "+v"(X.w_next), [j] "+v"(X.j_slot),         \
-        [pos] "+v"(X.pos), [t] "=&v"(scratch), [moved] "=&s"(moved_##X), [row] "+{" X_ROW "}"(X.R),                      \
-        [other_row] "+{" Y_ROW "}"(Y.R), [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot),     \
-        [other_next] "+v"(Y.w_next)                                                                                      \
-      : [zero] "v"(0u), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),           \
-        [slots] "v"(slot_base), [tables] "s"(tables)                                                                     \
-      : "memory", "vcc", "scc")
-// lanes whose row (its mask: RZ) has another one behind it fetch that and stay at their word
-#define FPSCHED_FOLLOW(RZ)                                                                                               \
-  "v_cmp_lt_u32 vcc, 0x3ffff, v" RZ "\n\t"                                                                              \
-  "s_cbranch_vccz .Lfollow%=\n\t"                                                                                       \
+// In flight at the beginning of a step, oldest first: its half's slot, the other half's row and the word behind it; at the
+// end of the statement nothing.
+// S, O: this half and the other one, `even` or `odd`.  Registers of their rows' four words, and of the two of a wide slot:
+#define FPSCHED_even_X "v40"
+#define FPSCHED_even_Y "v41"
+#define FPSCHED_even_Z "v42"
+#define FPSCHED_even_W "v43"
+#define FPSCHED_even_ROW "v[40:43]"
+#define FPSCHED_even_IN "v48"
+#define FPSCHED_even_TAG "v49"
+#define FPSCHED_even_SLOT "v[48:49]"
+#define FPSCHED_odd_X "v44"
+#define FPSCHED_odd_Y "v45"
+#define FPSCHED_odd_Z "v46"
+#define FPSCHED_odd_W "v47"
+#define FPSCHED_odd_ROW "v[44:47]"
+#define FPSCHED_odd_IN "v50"
+#define FPSCHED_odd_TAG "v51"
+#define FPSCHED_odd_SLOT "v[50:51]"
+
+// STEP(S, what is read ahead), AHEAD(O): of a form
+#define FPSCHED_FIRST_LOOK(AHEAD) "s_waitcnt lgkmcnt(0)\n\t" AHEAD(even) "s_waitcnt lgkmcnt(0)\n\t"
+#define FPSCHED_ROUND(STEP, AHEAD) STEP(even, AHEAD(odd)) STEP(odd, AHEAD(even))
+#define FPSCHED_FOUR_ROUNDS(STEP, AHEAD)                                                                                 \
+  FPSCHED_FIRST_LOOK(AHEAD) FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD)              \
+  STEP(even, AHEAD(odd)) STEP(odd, "") "s_waitcnt lgkmcnt(0)"
+#define FPSCHED_EIGHT_ROUNDS(STEP, AHEAD)                                                                                \
+  FPSCHED_FIRST_LOOK(AHEAD) FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD)              \
+  FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD) FPSCHED_ROUND(STEP, AHEAD)             \
+  STEP(even, AHEAD(odd)) STEP(odd, "") "s_waitcnt lgkmcnt(0)"
+// Operands of all forms.  (Every output is written while inputs are still to be read.)
+#define FPSCHED_STATE(S)                                                                                                 \
+  [S##_free] "+&v"(S.free_at), [S##_next] "+&v"(S.w_next), [S##_j] "+&v"(S.j_slot), [S##_pos] "+&v"(S.pos),               \
+  [S##_row] "+&{" FPSCHED_##S##_ROW "}"(S.R), [S##_at] "=&v"(at_##S), [S##_moved] "=&s"(moved_##S)
+#define FPSCHED_PLACES(S) [S##_rows] "v"(S.meta), [S##_ring] "v"(S.win)
+#define FPSCHED_SHARED [stride] "s"(row_stride), [mask] "s"(kPosMask), [slots] "v"(slot_base)
+
+// ... the plain form.  (FOLLOW: for rows that another row follows in the place of the next word's, in the form with second
+// edges)
+#define FPSCHED_STEP(S, AHEAD, FOLLOW, NOT_FOLLOWED)                                                                     \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                            \
+  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                       \
+  "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
+  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t"                                                                    \
+  "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"                                                                       \
+  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                 \
+  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"                                                                      \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                          \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t" FOLLOW                                                      \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t" NOT_FOLLOWED                                                           \
+  FPSCHED_NEXT_WORD(S)
+#define FPSCHED_NEXT_WORD(S)                                                                                             \
+  "v_or_b32 %[" #S "_pos], 0xfc, %[" #S "_pos]\n\t"                                                                     \
+  "v_add_u32 %[" #S "_pos], 2, %[" #S "_pos]\n\t"                                                                       \
+  "v_bitop3_b32 %[t], %[" #S "_pos], %[mask], %[" #S "_ring] bitop3:0x6a\n\t"                                           \
+  "v_lshlrev_b32 %[" #S "_j], 2, %[" #S "_next]\n\t"                                                                    \
+  "ds_read_u16 %[" #S "_next], %[t]\n\t"                                                                                \
+  "s_mov_b64 exec, -1\n\t"
+// the other half's slot, whose row is there when as many requests as this half's have been made since are still out
+#define FPSCHED_AHEAD_SLOT(O, OWN)                                                                                       \
+  "s_waitcnt lgkmcnt(" OWN ")\n\t"                                                                                      \
+  "v_and_b32 %[" #O "_at], %[" #O "_j], " FPSCHED_##O##_Z "\n\t"                                                        \
+  "v_add3_u32 %[" #O "_at], %[" #O "_at], " FPSCHED_##O##_W ", %[slots]\n\t"                                            \
+  "ds_read_b32 %[" #O "_in], %[" #O "_at]\n\t"
+#define FPSCHED_PLAIN_STEP(S, AHEAD) FPSCHED_STEP(S, AHEAD, "", "")
+#define FPSCHED_PLAIN_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "1")
+// lanes whose row (its mask) has another one behind it fetch that and stay at their word
+#define FPSCHED_FOLLOW(S)                                                                                                \
+  "v_cmp_lt_u32 vcc, 0x3ffff, " FPSCHED_##S##_Z "\n\t"                                                                  \
+  "s_cbranch_vccz 1f\n\t"                                                                                               \
   "s_mov_b64 exec, vcc\n\t"                                                                                             \
-  "v_lshrrev_b32 %[t], 14, v" RZ "\n\t"                                                                                 \
+  "v_lshrrev_b32 %[t], 14, " FPSCHED_##S##_Z "\n\t"                                                                     \
   "v_add_u32 %[t], %[tables], %[t]\n\t"                                                                                 \
-  "s_mov_b64 exec, %[moved]\n\t"                                                                                        \
-  ".Lfollow%=:\n\t"
-#define FPSCHED_NOT_FOLLOWED "s_andn2_b64 exec, exec, vcc\n\t"
-#define FPSCHED_READ_AHEAD(WRITES, OZ, OW)                                                                               \
-  "s_waitcnt lgkmcnt(" WRITES ")\n\t"                                                                                   \
-  "v_and_b32 %[other_at], %[other_j], v" OZ "\n\t"                                                                      \
-  "v_add3_u32 %[other_at], %[other_at], v" OW ", %[slots]\n\t"                                                          \
-  "ds_read_b32 %[other_in], %[other_at]\n\t"
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
+  "1:\n\t"
+#define FPSCHED_FOLLOW_STEP(S, AHEAD) FPSCHED_STEP(S, AHEAD, FPSCHED_FOLLOW(S), "s_andn2_b64 exec, exec, vcc\n\t")
+#define FPSCHED_ROUNDS(TEXT)                                                                                             \
+  asm volatile(TEXT                                                                                                      \
+               : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd), [t] "=&v"(scratch) \
+               : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [tables] "s"(tables)        \
+               : "memory", "vcc", "scc")
 
-// The same in two halves, between which the few ops are looked after that waited 2^16 time units or more (LATE), for the
-// form that leaves start times: an op's start goes where its own word was in the ring (OWN: that place; AT_NEXT: the place
-// of the word behind it, read already).
-#define FPSCHED_START(X, RX, RY)                                                                                         \
-  asm volatile(                                                                                                          \
-      "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
-      "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
-      "v_cmpx_eq_u32_sdwa %[moved], %[in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                                   \
-      "v_max_u32 %[t], %[free], %[in]\n\t"                                                                              \
-      "v_lshrrev_b32 %[start], 8, %[t]\n\t"                                                                             \
-      "v_sub_u32 %[wait], %[t], %[free]\n\t"                                                                            \
-      "v_add_u32 %[t], %[t], v" RY "\n\t"                                                                               \
-      "ds_write_b32 %[at], %[t]\n\t"                                                                                    \
-      "ds_write_b16 %[own], %[start]\n\t"                                                                               \
-      "v_and_b32 %[free], 0xffffff00, %[t]\n\t"                                                                         \
-      "v_cmp_lt_u32 %[late], %[most], %[wait]\n\t"                                                                      \
-      "s_mov_b64 exec, -1"                                                                                               \
-      : [in] "+v"(X##_in), [free] "+v"(X.free_at), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited),  \
-        [moved] "=&s"(moved_##X), [late] "=&s"(late)                                                                     \
-      : [at] "v"(X##_at), [own] "v"(X.own_place), [zero] "v"(0u), [most] "s"(0xffffffu), [row] "{" FPSCHED_ROW_OF_##X "}"(X.R) \
-      : "memory")
-#define FPSCHED_ADVANCE(X, Y, RX, RW, READ_AHEAD)                                                                        \
-  asm volatile(                                                                                                          \
-      READ_AHEAD                                                                                                         \
-      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
-      "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
-      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
-      "v_mov_b32 %[own], %[at_next]\n\t"                                                                                \
-      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
-      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
-      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
-      "v_bitop3_b32 %[at_next], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                               \
-      "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
-      "ds_read_u16 %[next], %[at_next]\n\t"                                                                             \
-      "s_mov_b64 exec, -1"                                                                                               \
-      : [next] "+v"(X.w_next), [j] "+v"(X.j_slot), [pos] "+v"(X.pos), [t] "=&v"(scratch), [own] "+v"(X.own_place),       \
-        [at_next] "+v"(X.next_place), [row] "+{" FPSCHED_ROW_OF_##X "}"(X.R), [other_row] "+{" FPSCHED_ROW_OF_##Y "}"(Y.R), \
-        [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot), [other_next] "+v"(Y.w_next)          \
-      : [moved] "s"(moved_##X), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),   \
-        [slots] "v"(slot_base)                                                                                           \
-      : "memory")
-// The same for the forms with link occupancy and costs per micro-batch.  COST: how the op's cost and tag are added to its
-// start; SEND: when the value leaves over the link, and until when that keeps the link busy; AHEAD: with the slot, the other
-// half's link words and costs are read; LINK_ROW: the next op's link row is fetched in front of its row.
-#define FPSCHED_COST_STEP(X, Y, X_ROW, Y_ROW, RX, RW, COST, SEND, WAIT, AHEAD, LINK_ROW)                                 \
-  asm volatile(                                                                                                          \
-      "s_waitcnt lgkmcnt(" WAIT ")\n\t"                                                                                 \
-      "v_add_u32 %[in], %[in], v" RX "\n\t"                                                                             \
-      "v_cmpx_eq_u32_sdwa %[moved], %[in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                                   \
-      "v_max_u32 %[t], %[free], %[in]\n\t" COST                                                                         \
-      "v_and_b32 %[free], 0xffffff00, %[t]\n\t" SEND                                                                    \
-      "ds_write_b32 %[at], %[t]\n\t"                                                                                    \
-      "s_mov_b64 exec, -1\n\t" AHEAD                                                                                    \
-      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
-      "v_lshrrev_b32 %[t], 11, %[next]\n\t" LINK_ROW                                                                    \
-      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
-      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
-      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
-      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
-      "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
-      "v_lshlrev_b32 %[j], 2, %[next]\n\t"                                                                              \
-      "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
-      "s_mov_b64 exec, -1"                                                                                               \
-      : [in] "+v"(X##_in), [at] "+v"(X##_at), [free] "+v"(X.free_at), [next] "+v"(X.w_next), [j] "+v"(X.j_slot),         \
-        [pos] "+v"(X.pos), [t] "=&v"(scratch), [u] "=&v"(scratch2), [moved] "=&s"(moved_##X), [row] "+{" X_ROW "}"(X.R), \
-        [other_row] "+{" Y_ROW "}"(Y.R), [other_in] "+v"(Y##_in), [other_at] "+v"(Y##_at), [other_j] "+v"(Y.j_slot),     \
-        [other_next] "+v"(Y.w_next), [link] "+v"(X.link), [other_link] "+v"(Y.link), [link_at] "+v"(X##_link_at),        \
-        [other_link_at] "+v"(Y##_link_at), [sent] "+v"(X##_sent), [other_sent] "+v"(Y##_sent), [cost] "+v"(X##_cost),    \
-        [other_cost] "+v"(Y##_cost), [busy] "+v"(X.busy)                                                                 \
-      : [zero] "v"(0u), [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask),           \
-        [slots] "v"(slot_base), [byte] "s"(0xffu), [link_stride] "s"(row_stride / 4u), [link_rows] "v"(X.link_rows),     \
-        [other_links] "v"(Y.links)                                                                                       \
-      : "memory")
-#define FPSCHED_COST_PLAIN(RY) "v_add_u32 %[t], %[t], v" RY "\n\t"
-#define FPSCHED_COST_TABLE(RY)                                                                                           \
-  "v_add_u32 %[busy], %[busy], %[cost]\n\t"                                                                             \
-  "v_lshl_add_u32 %[t], %[cost], 8, %[t]\n\t"                                                                           \
-  "v_add_u32_sdwa %[t], %[t], v" RY " dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_0\n\t"
-#define FPSCHED_SEND_LINK(RY)                                                                                            \
-  "v_and_or_b32 %[u], v" RY ", %[byte], %[sent]\n\t"                                                                    \
+// ... the form that leaves start times: an op's start goes where its own word was in the ring (own: that place; at_next: the
+// place of the word behind it, read already).  The few ops that waited 2^16 time units or more cannot be rebuilt from the low
+// half of their start times and go to the row's escape list, while that has room: position << 8 | wait >> 16.
+#define FPSCHED_TIMES_STEP(S, AHEAD)                                                                                     \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                            \
+  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                       \
+  "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
+  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t"                                                                    \
+  "v_lshrrev_b32 %[start], 8, %[t]\n\t"                                                                                 \
+  "v_sub_u32 %[wait], %[t], %[" #S "_free]\n\t"                                                                         \
+  "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"                                                                       \
+  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                 \
+  "ds_write_b16 %[" #S "_own], %[start]\n\t"                                                                            \
+  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"                                                                      \
+  "v_cmp_lt_u32 vcc, %[most], %[wait]\n\t"                                                                              \
+  "s_mov_b64 exec, vcc\n\t"                                                                                             \
+  "s_cbranch_execz 1f\n\t"                                                                                              \
+  "v_cmp_lt_i32 vcc, 0, %[" #S "_room]\n\t"                                                                             \
+  "s_mov_b64 exec, vcc\n\t"                                                                                             \
+  "v_lshrrev_b32 %[t], 8, %[" #S "_pos]\n\t"                                                                            \
+  "v_bfe_u32 %[start], %[" #S "_pos], 1, 1\n\t"                                                                         \
+  "v_lshl_or_b32 %[t], %[t], 1, %[start]\n\t"                                                                           \
+  "v_add_u32 %[t], -1, %[t]\n\t"                                                                                        \
+  "v_lshrrev_b32 %[wait], 24, %[wait]\n\t"                                                                              \
+  "v_lshl_or_b32 %[t], %[t], 8, %[wait]\n\t"                                                                            \
+  "global_store_dword %[" #S "_escape], %[t], off\n\t"                                                                  \
+  "v_lshl_add_u64 %[" #S "_escape], %[" #S "_escape], 0, 4\n\t"                                                         \
+  "v_add_u32 %[" #S "_room], -1, %[" #S "_room]\n\t"                                                                    \
+  "1:\n\t"                                                                                                              \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                          \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                             \
+  "v_mov_b32 %[" #S "_own], %[" #S "_at_next]\n\t"                                                                      \
+  "v_or_b32 %[" #S "_pos], 0xfc, %[" #S "_pos]\n\t"                                                                     \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                        \
+  "v_add_u32 %[" #S "_pos], 2, %[" #S "_pos]\n\t"                                                                       \
+  "v_bitop3_b32 %[" #S "_at_next], %[" #S "_pos], %[mask], %[" #S "_ring] bitop3:0x6a\n\t"                              \
+  "v_lshlrev_b32 %[" #S "_j], 2, %[" #S "_next]\n\t"                                                                    \
+  "ds_read_u16 %[" #S "_next], %[" #S "_at_next]\n\t"                                                                   \
+  "s_mov_b64 exec, -1\n\t"
+#define FPSCHED_TIMES_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2")
+#define FPSCHED_LEFT(S)                                                                                                  \
+  [S##_own] "+&v"(S.own_place), [S##_at_next] "+&v"(S.next_place), [S##_escape] "+&v"(S.escape), [S##_room] "+&v"(S.escape_room)
+#define FPSCHED_TIMES_ROUNDS(TEXT)                                                                                       \
+  asm volatile(TEXT                                                                                                      \
+               : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
+                 FPSCHED_LEFT(even), FPSCHED_LEFT(odd), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited) \
+               : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [most] "s"(0xffffffu)       \
+               : "memory", "vcc", "scc")
+
+// ... the forms with link occupancy and costs per micro-batch.  COST: how the op's cost and tag are added to its start; SEND:
+// when the value leaves over the link, and until when that keeps the link busy; LINK_ROW: the next op's link row is fetched in
+// front of its row.  With the slot, the other half's link word and cost are read ahead.
+#define FPSCHED_COST_STEP(S, AHEAD, COST, SEND, REQUESTED, LINK_ROW)                                                     \
+  "s_waitcnt lgkmcnt(" REQUESTED ")\n\t"                                                                                \
+  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                       \
+  "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
+  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t" COST                                                               \
+  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t" SEND                                                                 \
+  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                 \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t" LINK_ROW                                                                 \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                             \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                        \
+  FPSCHED_NEXT_WORD(S)
+#define FPSCHED_COST_PLAIN(S) "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"
+#define FPSCHED_COST_TABLE(S)                                                                                            \
+  "v_add_u32 %[" #S "_busy], %[" #S "_busy], %[" #S "_cost]\n\t"                                                        \
+  "v_lshl_add_u32 %[t], %[" #S "_cost], 8, %[t]\n\t"                                                                    \
+  "v_add_u32_sdwa %[t], %[t], " FPSCHED_##S##_Y " dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+#define FPSCHED_SEND_LINK(S)                                                                                             \
+  "v_and_or_b32 %[u], " FPSCHED_##S##_Y ", %[byte], %[" #S "_sent]\n\t"                                                 \
   "v_max_u32 %[t], %[t], %[u]\n\t"                                                                                      \
-  "v_lshrrev_b32 %[sent], 16, %[link]\n\t"                                                                              \
+  "v_lshrrev_b32 %[" #S "_sent], 16, %[" #S "_link]\n\t"                                                                \
   "v_and_b32 %[u], 0xffffff00, %[t]\n\t"                                                                                \
-  "v_lshl_add_u32 %[u], %[sent], 8, %[u]\n\t"                                                                           \
-  "ds_write_b32 %[link_at], %[u]\n\t"
-#define FPSCHED_AHEAD_LINK                                                                                               \
-  "v_add_u32_sdwa %[other_link_at], %[other_links], %[other_link] dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_0\n\t"     \
-  "ds_read_b32 %[other_sent], %[other_link_at]\n\t"
-#define FPSCHED_AHEAD_COST(OY, SHIFT, READ)                                                                              \
-  "v_lshrrev_b32 %[other_cost], 8, v" OY "\n\t"                                                                         \
-  "v_bfe_u32 %[t], %[other_j], 2, 11\n\t"                                                                               \
-  "v_lshl_add_u32 %[other_cost], %[t], " SHIFT ", %[other_cost]\n\t" READ " %[other_cost], %[other_cost]\n\t"
-#define FPSCHED_LINK_ROW                                                                                                 \
-  "v_mad_u32_u24 %[u], %[t], %[link_stride], %[link_rows]\n\t"                                                          \
-  "ds_read_b32 %[link], %[u]\n\t"
+  "v_lshl_add_u32 %[u], %[" #S "_sent], 8, %[u]\n\t"                                                                    \
+  "ds_write_b32 %[" #S "_link_at], %[u]\n\t"
+#define FPSCHED_LINK_ROW(S)                                                                                              \
+  "v_mad_u32_u24 %[u], %[t], %[link_stride], %[" #S "_link_rows]\n\t"                                                   \
+  "ds_read_b32 %[" #S "_link], %[u]\n\t"
+#define FPSCHED_AHEAD_LINK(O)                                                                                            \
+  "v_add_u32_sdwa %[" #O "_link_at], %[" #O "_links], %[" #O "_link] dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_0\n\t"  \
+  "ds_read_b32 %[" #O "_sent], %[" #O "_link_at]\n\t"
+#define FPSCHED_AHEAD_COST(O, SHIFT, READ)                                                                               \
+  "v_lshrrev_b32 %[" #O "_cost], 8, " FPSCHED_##O##_Y "\n\t"                                                            \
+  "v_bfe_u32 %[t], %[" #O "_j], 2, 11\n\t"                                                                              \
+  "v_lshl_add_u32 %[" #O "_cost], %[t], " SHIFT ", %[" #O "_cost]\n\t" READ " %[" #O "_cost], %[" #O "_cost]\n\t"
+#define FPSCHED_LINKS_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_PLAIN(S), FPSCHED_SEND_LINK(S), "3", FPSCHED_LINK_ROW(S))
+#define FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_LINK(O)
+#define FPSCHED_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), "", "2", "")
+#define FPSCHED_MB1_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "1") FPSCHED_AHEAD_COST(O, "0", "ds_read_u8")
+#define FPSCHED_MB2_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "1") FPSCHED_AHEAD_COST(O, "1", "ds_read_u16")
+#define FPSCHED_LINKS_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_SEND_LINK(S), "3", FPSCHED_LINK_ROW(S))
+#define FPSCHED_LINKS_MB1_AHEAD(O) FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_COST(O, "0", "ds_read_u8")
+#define FPSCHED_LINKS_MB2_AHEAD(O) FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_COST(O, "1", "ds_read_u16")
+#define FPSCHED_COST_STATE(S)                                                                                            \
+  [S##_link] "+&v"(S.link), [S##_busy] "+&v"(S.busy), [S##_link_at] "=&v"(link_at_##S), [S##_sent] "=&v"(sent_##S),       \
+  [S##_cost] "=&v"(cost_##S)
+#define FPSCHED_COST_ROUNDS(TEXT)                                                                                        \
+  asm volatile(TEXT                                                                                                      \
+               : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
+                 FPSCHED_COST_STATE(even), FPSCHED_COST_STATE(odd), [t] "=&v"(scratch), [u] "=&v"(scratch2)             \
+               : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [byte] "s"(0xffu),          \
+                 [link_stride] "s"(row_stride / 4u), [even_link_rows] "v"(even.link_rows), [odd_link_rows] "v"(odd.link_rows), \
+                 [even_links] "v"(even.links), [odd_links] "v"(odd.links)                                               \
+               : "memory", "scc")
 
-// ... and for times of two words (rows: latency; cost; mask; own tag, expected tag, slot's offset; the slot's words: IN, TAG).
-#define FPSCHED_WIDE_STEP(X, Y, X_ROW, Y_ROW, X_SLOT, Y_SLOT, RX, RY, RW, IN, TAG, AHEAD)                                 \
-  asm volatile(                                                                                                          \
-      "s_waitcnt lgkmcnt(2)\n\t"                                                                                        \
-      "v_cmpx_eq_u32_sdwa %[moved], v" TAG ", v" RW " src0_sel:BYTE_0 src1_sel:BYTE_1\n\t"                               \
-      "v_add_u32 v" IN ", v" IN ", v" RX "\n\t"                                                                         \
-      "v_max_u32 %[free], %[free], v" IN "\n\t"                                                                         \
-      "v_add_u32 %[free], %[free], v" RY "\n\t"                                                                         \
-      "ds_write2_b32 %[at], %[free], v" RW " offset1:1\n\t"                                                             \
-      "s_mov_b64 exec, -1\n\t" AHEAD                                                                                    \
-      "s_mov_b64 exec, %[moved]\n\t"                                                                                    \
-      "v_lshrrev_b32 %[t], 11, %[next]\n\t"                                                                             \
-      "v_mad_u32_u24 %[t], %[t], %[stride], %[rows]\n\t"                                                                \
-      "v_or_b32 %[pos], 0xfc, %[pos]\n\t"                                                                               \
-      "ds_read_b128 v[" RX ":" RW "], %[t]\n\t"                                                                         \
-      "v_add_u32 %[pos], 2, %[pos]\n\t"                                                                                 \
-      "v_bitop3_b32 %[t], %[pos], %[mask], %[ring] bitop3:0x6a\n\t"                                                     \
-      "v_lshlrev_b32 %[j], 3, %[next]\n\t"                                                                              \
-      "ds_read_u16 %[next], %[t]\n\t"                                                                                   \
-      "s_mov_b64 exec, -1"                                                                                               \
-      : [slot] "+{" X_SLOT "}"(X##_both), [other_slot] "+{" Y_SLOT "}"(Y##_both), [at] "+v"(X##_at),                     \
-        [free] "+v"(X.free_at), [next] "+v"(X.w_next), [j] "+v"(X.j_slot), [pos] "+v"(X.pos), [t] "=&v"(scratch),        \
-        [moved] "=&s"(moved_##X), [row] "+{" X_ROW "}"(X.R), [other_row] "+{" Y_ROW "}"(Y.R), [other_at] "+v"(Y##_at),   \
-        [other_j] "+v"(Y.j_slot), [other_next] "+v"(Y.w_next)                                                            \
-      : [stride] "s"(row_stride), [rows] "v"(X.meta), [ring] "v"(X.win), [mask] "s"(kPosMask), [slots] "v"(slot_base)    \
-      : "memory")
-#define FPSCHED_WIDE_AHEAD(OZ, OW, SLOT)                                                                                 \
+// ... and the form with times of two words (rows: latency; cost; mask; own tag, expected tag, slot's offset).
+#define FPSCHED_WIDE_STEP(S, AHEAD)                                                                                      \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                            \
+  "v_cmpx_eq_u32_sdwa %[" #S "_moved], " FPSCHED_##S##_TAG ", " FPSCHED_##S##_W " src0_sel:BYTE_0 src1_sel:BYTE_1\n\t"   \
+  "v_add_u32 " FPSCHED_##S##_IN ", " FPSCHED_##S##_IN ", " FPSCHED_##S##_X "\n\t"                                       \
+  "v_max_u32 %[" #S "_free], %[" #S "_free], " FPSCHED_##S##_IN "\n\t"                                                  \
+  "v_add_u32 %[" #S "_free], %[" #S "_free], " FPSCHED_##S##_Y "\n\t"                                                   \
+  "ds_write2_b32 %[" #S "_at], %[" #S "_free], " FPSCHED_##S##_W " offset1:1\n\t"                                       \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                          \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                             \
+  "v_or_b32 %[" #S "_pos], 0xfc, %[" #S "_pos]\n\t"                                                                     \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                        \
+  "v_add_u32 %[" #S "_pos], 2, %[" #S "_pos]\n\t"                                                                       \
+  "v_bitop3_b32 %[t], %[" #S "_pos], %[mask], %[" #S "_ring] bitop3:0x6a\n\t"                                           \
+  "v_lshlrev_b32 %[" #S "_j], 3, %[" #S "_next]\n\t"                                                                    \
+  "ds_read_u16 %[" #S "_next], %[t]\n\t"                                                                                \
+  "s_mov_b64 exec, -1\n\t"
+#define FPSCHED_WIDE_AHEAD(O)                                                                                            \
   "s_waitcnt lgkmcnt(1)\n\t"                                                                                            \
-  "v_and_b32 %[other_at], %[other_j], v" OZ "\n\t"                                                                      \
-  "v_add_u32_sdwa %[other_at], %[other_at], v" OW " dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"                   \
-  "v_add_u32 %[other_at], %[other_at], %[slots]\n\t"                                                                    \
-  "ds_read_b64 " SLOT ", %[other_at]\n\t"
-#define FPSCHED_ROW_OF_even "v[40:43]"
-#define FPSCHED_ROW_OF_odd "v[44:47]"
+  "v_and_b32 %[" #O "_at], %[" #O "_j], " FPSCHED_##O##_Z "\n\t"                                                        \
+  "v_add_u32_sdwa %[" #O "_at], %[" #O "_at], " FPSCHED_##O##_W " dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"     \
+  "v_add_u32 %[" #O "_at], %[" #O "_at], %[slots]\n\t"                                                                  \
+  "ds_read_b64 " FPSCHED_##O##_SLOT ", %[" #O "_at]\n\t"
+#define FPSCHED_WIDE_ROUNDS(TEXT)                                                                                        \
+  asm volatile(TEXT                                                                                                      \
+               : FPSCHED_STATE(even), FPSCHED_STATE(odd), [t] "=&v"(scratch)                                            \
+               : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED                                              \
+               : "memory", "scc", "v48", "v49", "v50", "v51")
 
 template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, bool COPY>
 __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : 4))) void time_lists_kernel(
@@ -383,7 +432,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     unsigned taken;              // SYNC: values of its group's item taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
     unsigned own_place, next_place;   // TIMES: places in the ring of the words under and behind the cursor
-    int n_late;                       // TIMES: entries of the row's escape list
+    uint32_t* escape;                 // TIMES: next entry of the row's escape list
+    int escape_room;                  // TIMES: ... and how many it has room for, one for its end aside
     uint4 pend[kPieces];   // what has been requested and is not in the ring, in order
   };
   Device even, odd;
@@ -409,7 +459,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
     x.cap = COPY && (k == 0 || has_odd) && lane_ok ? T.ints[T.off_dev + 2 * (d0 + k) + 1] : 0x7fffffff;
     no_transfers(x);
-    x.own_place = x.win; x.next_place = x.win; x.n_late = 0;
+    x.own_place = x.win; x.next_place = x.win; x.escape = starts.escapes; x.escape_room = 0;
     for (int i = 0; i < kPieces; ++i) x.pend[i] = make_uint4(0u, 0u, 0u, 0u);
     idle_device(x);
   };
@@ -505,7 +555,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     if (x.loaded == x.asked && (!TIMES || x.loaded < stride_pos)) request(x, from, x.loaded);
   };
   // the head of the row has arrived: the device joins in
-  auto join = [&](Device& x) {
+  auto join = [&](Device& x, int odd_device) {
     x.loaded = 0u;
     store_piece(x);
     x.loaded = kPiece;
@@ -521,7 +571,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     if (TIMES) {
       x.own_place = in_ring(x, 0u);
       x.next_place = in_ring(x, position_of(1u));
-      x.n_late = 0;
+      x.escape = starts.escapes + ((size_t)cand * D + d0 + odd_device) * (size_t)starts.escape_cap;
+      x.escape_room = starts.escape_cap - 1;
     }
     decode(x, w);
     x.pos = position_of(1u);
@@ -737,8 +788,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       // segments restarted at the previous top-up: the heads of their rows have arrived, they join in and ask for
       // their second pieces like any other, below
       if (priming) {
-        join(even);
-        if (has_odd) join(odd);
+        join(even, 0);
+        if (has_odd) join(odd, 1);
       }
       any_stuck = __ballot(running && ((even.info | odd.info) & kRowStuck) != 0u) != 0ull;
       priming = false;
@@ -808,200 +859,106 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     }
     ask(even, row);
     ask(odd, row + stride2);
-    unsigned even_in = 0u, odd_in = 0u, even_at = 0u, odd_at = 0u, scratch, scratch2;
-    unsigned even_link_at = 0u, odd_link_at = 0u, even_sent = 0u, odd_sent = 0u, even_cost = 0u, odd_cost = 0u;
-    lds_int2 even_both{0, 0}, odd_both{0, 0};
-    auto read_ahead = [&]() {
-      asm volatile("s_waitcnt lgkmcnt(0)\n\t"
-                   "v_and_b32 %[at], %[j], v42\n\t"
-                   "v_add3_u32 %[at], %[at], v43, %[slots]\n\t"
-                   "ds_read_b32 %[in], %[at]\n\t"
-                   "s_waitcnt lgkmcnt(0)"
-                   : [in] "=&v"(even_in), [at] "=&v"(even_at), [row] "+{v[40:43]}"(even.R)
-                   : [j] "v"(even.j_slot), [slots] "v"(slot_base) : "memory");
-    };
-    if constexpr (STRAIGHT && !WIDE) read_ahead();
-    if constexpr (STRAIGHT && WIDE)
-      asm volatile("s_waitcnt lgkmcnt(0)\n\t"
-                   "v_and_b32 %[at], %[j], v42\n\t"
-                   "v_add_u32_sdwa %[at], %[at], v43 dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"
-                   "v_add_u32 %[at], %[at], %[slots]\n\t"
-                   "ds_read_b64 v[48:49], %[at]\n\t"
-                   "s_waitcnt lgkmcnt(0)"
-                   : [slot] "=&{v[48:49]}"(even_both), [at] "=&v"(even_at), [row] "+{v[40:43]}"(even.R)
-                   : [j] "v"(even.j_slot), [slots] "v"(slot_base) : "memory");
-    if constexpr (STRAIGHT && LINKS) {
-      even_link_at = even.links + (even.link & 0xffffu);
-      even_sent = lds_read<unsigned>(even_link_at);
-    }
-    if constexpr (STRAIGHT && MB != 0) {
-      const unsigned at = ((unsigned)even.R.y >> 8) + (((even.j_slot >> 2) & 0x7ffu) << (MB - 1));
-      even_cost = MB == 1 ? lds_read<uint8_t>(at) : lds_read<uint16_t>(at);
-    }
-    if constexpr (STRAIGHT && (LINKS || MB != 0)) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(even_sent), "+v"(even_cost));
+    unsigned long long moved_even = 0ull, moved_odd = 0ull;
+    if constexpr (STRAIGHT) {
+      [[maybe_unused]] unsigned in_even, in_odd, at_even, at_odd, scratch, scratch2, start_time, waited;
+      [[maybe_unused]] unsigned link_at_even, link_at_odd, sent_even, sent_odd, cost_even, cost_odd;
+      if constexpr (SYNC) {
 #pragma unroll
-    for (unsigned sub = 0; sub < kRounds; ++sub) {
-      unsigned long long moved_even, moved_odd;
-      if constexpr (PLAIN) {
-        if constexpr (TIMES) {
-          unsigned start_time, waited;
-          unsigned long long late;
-          // an op that waited 2^16 time units or more cannot be rebuilt from the low half of its start time
-          auto escape = [&](Device& x, int odd_device) {
-            if (late != 0ull && __builtin_amdgcn_inverse_ballot_w64(late) && x.n_late < starts.escape_cap - 1)
-              starts.escapes[((size_t)cand * D + d0 + odd_device) * (size_t)starts.escape_cap + x.n_late++] = (word_at(x.pos) - 1u) << 8 | waited >> 24;
-          };
-          FPSCHED_START(even, "40", "41");
-          escape(even, 0);
-          FPSCHED_ADVANCE(even, odd, "40", "43", FPSCHED_READ_AHEAD("2", "46", "47"));
-          FPSCHED_START(odd, "44", "45");
-          escape(odd, 1);
-          if (sub + 1 < kRounds) {
-            FPSCHED_ADVANCE(odd, even, "44", "47", FPSCHED_READ_AHEAD("2", "42", "43"));
-          } else {
-            FPSCHED_ADVANCE(odd, even, "44", "47", "");
-          }
-        } else if constexpr (DEG2) {
-          FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"), FPSCHED_FOLLOW("42"), FPSCHED_NOT_FOLLOWED);
-          if (sub + 1 < kRounds && !(SYNC && (sub & 3u) == 3u)) {
-            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"), FPSCHED_FOLLOW("46"), FPSCHED_NOT_FOLLOWED);
-          } else {
-            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "", FPSCHED_FOLLOW("46"), FPSCHED_NOT_FOLLOWED);
-          }
-          if constexpr (SYNC) {
-            if ((sub & 3u) == 3u) {
-              asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
-              moved_even |= groups(even, moved_even);
-              moved_odd |= groups(odd, moved_odd);
-              if (sub + 1 < kRounds) read_ahead();
-            }
-          }
-        } else {
-          FPSCHED_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "41", "43", FPSCHED_READ_AHEAD("1", "46", "47"), "", "");
-          if (sub + 1 < kRounds) {
-            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", FPSCHED_READ_AHEAD("1", "42", "43"), "", "");
-          } else {
-            FPSCHED_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "45", "47", "", "", "");
-          }
+        for (unsigned sub = 0; sub < kRounds; sub += 4u) {
+          FPSCHED_ROUNDS(FPSCHED_FOUR_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
+          moved_even |= groups(even, moved_even);
+          moved_odd |= groups(odd, moved_odd);
         }
-        if (sub + 1 == kRounds)
-          asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next) : : "memory");
-      } else if constexpr (STRAIGHT) {
-        if constexpr (WIDE) {
-          FPSCHED_WIDE_STEP(even, odd, "v[40:43]", "v[44:47]", "v[48:49]", "v[50:51]", "40", "41", "43", "48", "49", FPSCHED_WIDE_AHEAD("46", "47", "v[50:51]"));
-          if (sub + 1 < kRounds) {
-            FPSCHED_WIDE_STEP(odd, even, "v[44:47]", "v[40:43]", "v[50:51]", "v[48:49]", "44", "45", "47", "50", "51", FPSCHED_WIDE_AHEAD("42", "43", "v[48:49]"));
-          } else {
-            FPSCHED_WIDE_STEP(odd, even, "v[44:47]", "v[40:43]", "v[50:51]", "v[48:49]", "44", "45", "47", "50", "51", "");
-          }
-        } else if constexpr (LINKS && MB == 0) {
-          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_PLAIN("41"), FPSCHED_SEND_LINK("41"), "3", FPSCHED_READ_AHEAD("2", "46", "47") FPSCHED_AHEAD_LINK, FPSCHED_LINK_ROW);
-          if (sub + 1 < kRounds) {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_PLAIN("45"), FPSCHED_SEND_LINK("45"), "3", FPSCHED_READ_AHEAD("2", "42", "43") FPSCHED_AHEAD_LINK, FPSCHED_LINK_ROW);
-          } else {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_PLAIN("45"), FPSCHED_SEND_LINK("45"), "3", "", FPSCHED_LINK_ROW);
-          }
-        } else if constexpr (LINKS && MB == 1) {
-          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), FPSCHED_SEND_LINK("41"), "3", FPSCHED_READ_AHEAD("2", "46", "47") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("45", "0", "ds_read_u8"), FPSCHED_LINK_ROW);
-          if (sub + 1 < kRounds) {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", FPSCHED_READ_AHEAD("2", "42", "43") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("41", "0", "ds_read_u8"), FPSCHED_LINK_ROW);
-          } else {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", "", FPSCHED_LINK_ROW);
-          }
-        } else if constexpr (LINKS) {
-          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), FPSCHED_SEND_LINK("41"), "3", FPSCHED_READ_AHEAD("2", "46", "47") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("45", "1", "ds_read_u16"), FPSCHED_LINK_ROW);
-          if (sub + 1 < kRounds) {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", FPSCHED_READ_AHEAD("2", "42", "43") FPSCHED_AHEAD_LINK FPSCHED_AHEAD_COST("41", "1", "ds_read_u16"), FPSCHED_LINK_ROW);
-          } else {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), FPSCHED_SEND_LINK("45"), "3", "", FPSCHED_LINK_ROW);
-          }
-        } else if constexpr (MB == 1) {
-          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), "", "2", FPSCHED_READ_AHEAD("1", "46", "47") FPSCHED_AHEAD_COST("45", "0", "ds_read_u8"), "");
-          if (sub + 1 < kRounds) {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", FPSCHED_READ_AHEAD("1", "42", "43") FPSCHED_AHEAD_COST("41", "0", "ds_read_u8"), "");
-          } else {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", "", "");
-          }
-        } else {
-          FPSCHED_COST_STEP(even, odd, "v[40:43]", "v[44:47]", "40", "43", FPSCHED_COST_TABLE("41"), "", "2", FPSCHED_READ_AHEAD("1", "46", "47") FPSCHED_AHEAD_COST("45", "1", "ds_read_u16"), "");
-          if (sub + 1 < kRounds) {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", FPSCHED_READ_AHEAD("1", "42", "43") FPSCHED_AHEAD_COST("41", "1", "ds_read_u16"), "");
-          } else {
-            FPSCHED_COST_STEP(odd, even, "v[44:47]", "v[40:43]", "44", "47", FPSCHED_COST_TABLE("45"), "", "2", "", "");
-          }
-        }
-        if (sub + 1 == kRounds)
-          asm volatile("s_waitcnt lgkmcnt(0)" : "+{v[40:43]}"(even.R), "+{v[44:47]}"(odd.R), "+v"(even.w_next), "+v"(odd.w_next), "+v"(even.link), "+v"(odd.link) : : "memory");
+      } else if constexpr (TIMES) {
+        FPSCHED_TIMES_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_TIMES_STEP, FPSCHED_TIMES_AHEAD));
+      } else if constexpr (WIDE) {
+        FPSCHED_WIDE_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_WIDE_STEP, FPSCHED_WIDE_AHEAD));
+      } else if constexpr (LINKS && MB == 0) {
+        FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_LINKS_STEP, FPSCHED_LINKS_AHEAD));
+      } else if constexpr (LINKS && MB == 1) {
+        FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_LINKS_MB_STEP, FPSCHED_LINKS_MB1_AHEAD));
+      } else if constexpr (LINKS) {
+        FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_LINKS_MB_STEP, FPSCHED_LINKS_MB2_AHEAD));
+      } else if constexpr (MB == 1) {
+        FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_MB_STEP, FPSCHED_MB1_AHEAD));
+      } else if constexpr (MB == 2) {
+        FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_MB_STEP, FPSCHED_MB2_AHEAD));
+      } else if constexpr (DEG2) {
+        FPSCHED_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
       } else {
+        FPSCHED_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_PLAIN_STEP, FPSCHED_PLAIN_AHEAD));
+      }
+    } else {
+#pragma unroll
+      for (unsigned sub = 0; sub < kRounds; ++sub) {
         moved_even = COPY ? copy_step(even) : step(even);
         moved_odd = COPY ? copy_step(odd) : step(odd);
       }
-      // A segment none of whose lanes issued is finished, and stays so: nothing it reads changes any more.  It could
-      // only be restarted at the next top-up anyway, so only the last round in front of it looks.  Cheap scalar
-      // pre-test: does the issue mask, with the lanes of idle segments set, contain an all-zero field of P bits?
-      // (x - lows) & ~x & highs is non-zero iff some field of x is zero.
-      if (sub == kRounds - 1) {
-        const unsigned long long x = moved_even | moved_odd | idle_lanes;
-        if (((x - base_bits) & ~x & high_bits) != 0ull) {
-          const bool ended = running && !priming && !any_in_segment(x);
-          // (a device that a lane does not have counts as one whose list is exhausted)
-          const unsigned even_issued = word_at(even.pos) - 1u, odd_issued = has_odd ? word_at(odd.pos) - 1u : 0u;
-          const unsigned both = even.info | odd.info;
-          const bool even_stops = even_issued == (even.info & kRowStop), odd_stops = odd_issued == (odd.info & kRowStop);
-          const bool stuck = any_in_segment(__ballot(!even_stops || !odd_stops || (both & kRowStuck) != 0u));
-          const bool malformed = any_in_segment(__ballot((even_stops && (even.info & kRowMalformed) != 0u) || (odd_stops && (odd.info & kRowMalformed) != 0u)));
-          const bool unfinished = any_in_segment(__ballot((both & kRowIncomplete) != 0u));
-          if (COPY && ended) {
-            // what the engine still had to do; the makespan covers both timelines
-            pass_events(even, ~0u, ~0u, 0);
-            pass_events(odd, ~0u, ~0u, 0);
-            even.free_at = max(even.free_at, even.copy_end[0]);
-            odd.free_at = max(odd.free_at, odd.copy_end[0]);
-          }
-          const bool over = any_in_segment(__ballot(COPY ? even.pk > even.cap || odd.pk > odd.cap : (both & kRowOverCap) != 0u));
-          if (ended) {
-            const unsigned flags = stuck ? kDeadlock | (malformed ? kIncomplete : 0u)
-                                         : (unfinished ? (unsigned)kIncomplete : (over ? (unsigned)kOverCap : 0u));
-            if constexpr (TIMES) {
-              // the start times still in the rings, the ends of the escape lists, and where the lists stopped
-              auto leave = [&](const Device& x, int odd_device, unsigned issued) {
-                const unsigned landed = x.loaded == kNoList ? stride_pos + kPiece : x.loaded;
-                for (unsigned back = 2u * kPiece; back > 0u; back -= kPiece)
-                  if (landed >= back && (landed - back) >> 7 < issued) leave_starts(x, landed - back, odd_device);
-                const size_t r = (size_t)cand * D + d0 + odd_device;
-                starts.escapes[r * (size_t)starts.escape_cap + x.n_late] = 0xffffffffu;
-                starts.stops[r] = (int)issued;
-              };
-              leave(even, 0, even_issued);
-              if (has_odd) leave(odd, 1, odd_issued);
-              if (pair == 0) out_flags[cand] = (unsigned char)(flags & (kDeadlock | kIncomplete));
-            } else {
-              // the latest finish, in a word that was cleared when the segment started
-              atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at, odd.free_at));
-              const unsigned ms = lds_read<uint32_t>(at_max) >> (WIDE ? 0 : 8);
-              const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
-              const long long r = cand * D + d0;
-              out_idle[r] = failed ? -1ll : (long long)((int)ms - (int)even.busy);
-              if (COPY || failed) out_peak[r] = failed ? -1 : even.pk * T.unit_scale;
-              if (has_odd) {
-                out_idle[r + 1] = failed ? -1ll : (long long)((int)ms - (int)odd.busy);
-                if (COPY || failed) out_peak[r + 1] = failed ? -1 : odd.pk * T.unit_scale;
-              }
-              if (pair == 0) {
-                out_makespan[cand] = failed ? 0x7fffffffffffffffll : (long long)ms;
-                out_flags[cand] = (unsigned char)flags;
-              }
-            }
-            running = false;
-            fresh = true;
-            idle_device(even);
-            idle_device(odd);
-          }
-          // the finished segments stop counting as running at once
-          idle_lanes = ~__ballot(running && !priming);
-          any_special = true;
-        }
+    }
+    // A segment none of whose lanes issued is finished, and stays so: nothing it reads changes any more.  It could
+    // only be restarted at the next top-up anyway, so only the last round in front of it looks.  Cheap scalar
+    // pre-test: does the issue mask, with the lanes of idle segments set, contain an all-zero field of P bits?
+    // (x - lows) & ~x & highs is non-zero iff some field of x is zero.
+    const unsigned long long x = moved_even | moved_odd | idle_lanes;
+    if (((x - base_bits) & ~x & high_bits) != 0ull) {
+      const bool ended = running && !priming && !any_in_segment(x);
+      // (a device that a lane does not have counts as one whose list is exhausted)
+      const unsigned even_issued = word_at(even.pos) - 1u, odd_issued = has_odd ? word_at(odd.pos) - 1u : 0u;
+      const unsigned both = even.info | odd.info;
+      const bool even_stops = even_issued == (even.info & kRowStop), odd_stops = odd_issued == (odd.info & kRowStop);
+      const bool stuck = any_in_segment(__ballot(!even_stops || !odd_stops || (both & kRowStuck) != 0u));
+      const bool malformed = any_in_segment(__ballot((even_stops && (even.info & kRowMalformed) != 0u) || (odd_stops && (odd.info & kRowMalformed) != 0u)));
+      const bool unfinished = any_in_segment(__ballot((both & kRowIncomplete) != 0u));
+      if (COPY && ended) {
+        // what the engine still had to do; the makespan covers both timelines
+        pass_events(even, ~0u, ~0u, 0);
+        pass_events(odd, ~0u, ~0u, 0);
+        even.free_at = max(even.free_at, even.copy_end[0]);
+        odd.free_at = max(odd.free_at, odd.copy_end[0]);
       }
+      const bool over = any_in_segment(__ballot(COPY ? even.pk > even.cap || odd.pk > odd.cap : (both & kRowOverCap) != 0u));
+      if (ended) {
+        const unsigned flags = stuck ? kDeadlock | (malformed ? kIncomplete : 0u)
+                                     : (unfinished ? (unsigned)kIncomplete : (over ? (unsigned)kOverCap : 0u));
+        if constexpr (TIMES) {
+          // the start times still in the rings, the ends of the escape lists, and where the lists stopped
+          auto leave = [&](const Device& x, int odd_device, unsigned issued) {
+            const unsigned landed = x.loaded == kNoList ? stride_pos + kPiece : x.loaded;
+            for (unsigned back = 2u * kPiece; back > 0u; back -= kPiece)
+              if (landed >= back && (landed - back) >> 7 < issued) leave_starts(x, landed - back, odd_device);
+            const size_t r = (size_t)cand * D + d0 + odd_device;
+            *x.escape = 0xffffffffu;
+            starts.stops[r] = (int)issued;
+          };
+          leave(even, 0, even_issued);
+          if (has_odd) leave(odd, 1, odd_issued);
+          if (pair == 0) out_flags[cand] = (unsigned char)(flags & (kDeadlock | kIncomplete));
+        } else {
+          // the latest finish, in a word that was cleared when the segment started
+          atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at, odd.free_at));
+          const unsigned ms = lds_read<uint32_t>(at_max) >> (WIDE ? 0 : 8);
+          const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
+          const long long r = cand * D + d0;
+          out_idle[r] = failed ? -1ll : (long long)((int)ms - (int)even.busy);
+          if (COPY || failed) out_peak[r] = failed ? -1 : even.pk * T.unit_scale;
+          if (has_odd) {
+            out_idle[r + 1] = failed ? -1ll : (long long)((int)ms - (int)odd.busy);
+            if (COPY || failed) out_peak[r + 1] = failed ? -1 : odd.pk * T.unit_scale;
+          }
+          if (pair == 0) {
+            out_makespan[cand] = failed ? 0x7fffffffffffffffll : (long long)ms;
+            out_flags[cand] = (unsigned char)flags;
+          }
+        }
+        running = false;
+        fresh = true;
+        idle_device(even);
+        idle_device(odd);
+      }
+      // the finished segments stop counting as running at once
+      idle_lanes = ~__ballot(running && !priming);
+      any_special = true;
     }
   }
 }
