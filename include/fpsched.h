@@ -37,7 +37,6 @@
  *                         memory even where it would fit LDS;
  *   FPSCHED_SYNC_SLOTS=1  (fpsched_problem_set_sync) the one-kernel form of the model even where the
  *                         two-pass form takes the setting;
- *   FPSCHED_COPY_SLOTS=1  (fpsched_problem_set_copy_engine) the one-kernel form of the model likewise;
  *   FPSCHED_VERBOSE=1     the cost-model setters print the kernel form and shape they chose.
  */
 #ifndef FPSCHED_H
@@ -236,8 +235,9 @@ int fpsched_problem_set_sync(fpsched_problem *p, const int32_t *group, int32_t n
  * are in force (and those setters, fpsched_wslide answer FPSCHED_EUNSUPPORTED while this is): the
  * handle keeps what it had.  Synchronous; allocates one table of device memory at most; works on a
  * host-only handle (validation only).  FPSCHED_KERNEL_SLOTS and _GENERAL both have a form of this
- * model, the former one kernel (no order pass in front) for problems whose times stay below 2^24 and
- * latencies below 2^16; it runs where it fits (fpsched_problem_select_kernel chooses as for the plain
+ * model, the former for problems whose times stay below 2^24 and latencies below 2^16: the two passes of the
+ * plain model up to a depth of 3, or one kernel (deeper engines, and batches that it finishes sooner); it runs
+ * where it fits (fpsched_problem_select_kernel chooses as for the plain
  * model), and then fpsched_evaluate needs its workspace as in the plain model. */
 #define FPSCHED_MAX_COPY_DEPTH 7
 int fpsched_problem_set_copy_engine(fpsched_problem *p, int32_t depth);
@@ -425,8 +425,8 @@ int fpsched_problem_info(const fpsched_problem *p, int32_t *lanes_per_candidate,
 #define FPSCHED_KERNEL_SLOTS 2
 int fpsched_problem_select_kernel(fpsched_problem *p, int which);
 /* Which of the two fpsched_evaluate would launch under the handle's present cost model and selection:
- * FPSCHED_KERNEL_SLOTS (the two passes, or eval_slot_kernel: the copy engine, synchronisation settings the
- * two passes do not take, costs per micro-batch whose table does not fit LDS) or FPSCHED_KERNEL_GENERAL
+ * FPSCHED_KERNEL_SLOTS (the two passes, or eval_slot_kernel: the copy engine where the two passes do not take it or
+ * take longer, synchronisation settings the two passes do not take, costs per micro-batch whose table does not fit LDS) or FPSCHED_KERNEL_GENERAL
  * (the table form: eval_general_kernel, or eval_sync_kernel under the synchronisation or copy-engine model
  * when the setting does not fit mail slots); a negative code for a null or host-only handle. */
 int fpsched_problem_active_kernel(const fpsched_problem *p);

@@ -1245,6 +1245,32 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   return check_hip(hipGetLastError());
 }
 
+static int max_chunks_of(const fpsched_problem* p) {
+  int max_chunks = 0;
+  for (int d = 0; d < p->D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
+  return max_chunks;
+}
+
+// Copy engine: the two passes or the one kernel.  The two passes have the cheaper steps, on half the lanes, and an order pass
+// and a launch more; the one kernel has its candidates side by side in wavefronts until the chip is full (`resident`), and
+// takes another turn for the rest.  Measured over 2 to 64 devices, 6 to 150 micro-batches, 1 to 4 stages per device, depths
+// 1 to 3, 64 to 131,072 candidates, one kernel / two passes:
+//   more than one turn: 1.0 to 2.4 times; but 0.72 to 1.2 beyond four turns on rows below some 96 items (65,536 of 32 x 8 x 1:
+//   0.72, of 32 x 24 x 1: 0.89, of 16 x 16 x 1: 0.95; of 32 x 32 x 2: 1.24, two towers on 16 devices, 64 micro-batches: 1.16);
+//   one turn, two or more stages per device: 1.0 to 1.3 (256 of 32 x 128 x 2: 1982 and 1630 us, 2,048 of 8 x 32 x 2: 590 and
+//   500, of 16 x 4 x 2: 83 and 75); but 0.94 to 0.99 on 3 x 6 x 2, and 0.9 to 1.0 on two devices, which are a lane per candidate in
+//   the one and two in the other (2,048 of 2 x 8 x 4: 0.92);
+//   one turn, one stage per device: on rows of 96 items and more 0.9 to 1.15 up to half a chip (2,048 of the towers with 45
+//   micro-batches 281 and 247 us, of 16 x 48 x 1: 1.06, of 24 x 48 x 1: 0.93), 0.9 to 1.03 beyond (4,096 of 24 x 48 x 1: 0.89, 8,192
+//   of 16 x 48 x 1: 0.91); on shorter rows 0.98 to 1.08 up to half a chip on four to eight devices (256 of 4 x 16 x 1: 115 and 111
+//   us), 0.85 to 1.06 on more (4,096 of the towers with 8 micro-batches 57 and 67 us); 0.93 to 1.02 on two devices (2 x 60 x 1).
+static bool copy_takes_two_passes(const fpsched_problem* p, int64_t n_cand) {
+  const int64_t resident = (int64_t)p->copy_grid * p->copy_waves * p->stab_copy.cands_per_wave;
+  const bool long_rows = (int64_t)max_chunks_of(p) * p->m * (p->has_w ? 3 : 2) >= 96;
+  if (n_cand > resident) return long_rows || n_cand <= 4 * resident;
+  return max_chunks_of(p) > 1 ? p->D > (long_rows ? 2 : 3) : p->D > 3 && (long_rows || p->D <= 8) && 2 * n_cand <= resident;
+}
+
 int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_cand,
                      int32_t stride_words, fpsched_results out, void* d_workspace,
                      size_t workspace_bytes, void* hip_stream) {
@@ -1277,10 +1303,7 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-    // (a batch of a few candidates per compute unit is one launch's latency: two towers on 16 devices, depth 3, the slot kernel
-    // and the two passes: 256 candidates of 8 micro-batches 61 and 74 us, 4,000 of 20 149 and 148, 12,000 of 60 735 and 410,
-    // 20,011 of 45 740 and 557, 65,536 of 64 2,800 and 2,477)
-    if (copy_on_slots && p->lists_copy.ok && n_cand >= 8ll * p->n_cu)
+    if (copy_on_slots && p->lists_copy.ok && copy_takes_two_passes(p, n_cand))
       return run_list_evaluation(p, &p->lists_copy, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (sync_on_slots && p->lists_sync.ok)
       return run_list_evaluation(p, &p->lists_sync, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
@@ -1938,7 +1961,7 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
     p->copy_slots_ok = false;
     // the two-pass evaluation takes it where times fit 24 bits and few transfers are in the engine at a time
     p->lists_copy.ok = false;
-    const int list_rc = p->slots_ok && !getenv("FPSCHED_COPY_SLOTS") ? build_copy_variant(p, depth) : FPSCHED_EUNSUPPORTED;
+    const int list_rc = p->slots_ok ? build_copy_variant(p, depth) : FPSCHED_EUNSUPPORTED;
     if (list_rc != FPSCHED_OK && list_rc != FPSCHED_EUNSUPPORTED) return list_rc;
     if (p->slots_ok) {
       const SlotTables& PT = p->stab;
@@ -1956,6 +1979,8 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
         p->copy_grid = p->n_cu * geo.groups;
         p->copy_lds_bytes = (int32_t)(4ll * (PT.n_shared_ints + (int64_t)geo.waves * geo.wave_ints));
         p->copy_slots_ok = true;
+        if (getenv("FPSCHED_VERBOSE"))
+          fprintf(stderr, "[fpsched] slot kernel, copy engine: %d x %d wavefronts per compute unit, %d candidates each\n", geo.groups, geo.waves, geo.cands_per_wave);
       }
     }
   }
@@ -1965,15 +1990,10 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
 
 using GenKernel = void (*)(DevTables, const int32_t*, const int32_t*, const long long*, long long, long long, int, int, uint16_t*,
                            int32_t*, unsigned char*, unsigned long long*, GenResults);
-static int gen_max_chunks(const fpsched_problem* p) {
-  int max_chunks = 0;
-  for (int d = 0; d < p->D; ++d) max_chunks = std::max(max_chunks, p->n_chunks[d]);
-  return max_chunks;
-}
 
 // about how many draws from one counter a set's steps last as long as (about 1 us and 100 draws each; order_sets)
 static int64_t gen_steps(const fpsched_problem* p) {
-  const int64_t chunks = std::max(gen_max_chunks(p), 1);
+  const int64_t chunks = std::max(max_chunks_of(p), 1);
   return 15 * (p->has_w ? 3 : 2) * chunks * p->m * (1 + chunks);
 }
 
@@ -2001,7 +2021,7 @@ static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const
   if (n_sets >= (1ll << 33)) return FPSCHED_EINVAL;   // (more workgroups than a launch has)
   hipLaunchKernelGGL(generate_order_kernel, dim3((unsigned)((n_sets + 3) / 4)), dim3(256), 0, st, p->tables, d_inflight,
                      reinterpret_cast<const long long*>(d_select), (long long)n_src, (long long)n_sets,
-                     2 * std::max(gen_max_chunks(p), 1) * p->m, d_status, counter);
+                     2 * std::max(max_chunks_of(p), 1) * p->m, d_status, counter);
   return hipGetLastError() == hipSuccess ? kGenClasses : FPSCHED_EHIP;
 }
 
@@ -2050,7 +2070,7 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
   if (n_sets == 0) return FPSCHED_OK;
   if (!d_policy || !d_inflight || !d_ops || !d_steps || !d_status) return FPSCHED_EINVAL;
   if (p->sync_on) return FPSCHED_EUNSUPPORTED;   // the generator schedules one item per micro-batch
-  const int max_chunks = gen_max_chunks(p);
+  const int max_chunks = max_chunks_of(p);
   const int64_t longest = (int64_t)max_chunks * p->m * (p->has_w ? 3 : 2);
   if (stride_words < 8 || (stride_words & 7) || stride_words < longest) return FPSCHED_EINVAL;
   if (reinterpret_cast<uintptr_t>(d_ops) & 15) return FPSCHED_EINVAL;
@@ -2152,7 +2172,7 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   // 1425, 256 (of 32 x 128 x 2) 4138 and 3970.  (64: 4735 on the last, whose wavefronts then do not all find room.)  And it
   // must not cost wavefronts: 65,536 of 32 x 128 x 2 14,353 us with 8 per compute unit and rings of 32, 11,607 with 12
   // and 16; 32,768 of 20 x 100 x 2 3419 and 3200.
-  if (slide && 2 * gen_max_chunks(p) * p->m >= 40 * (64 / p->D)) {
+  if (slide && 2 * max_chunks_of(p) * p->m >= 40 * (64 / p->D)) {
     tables.gen_events = kGenMoreEvents;
     const int64_t more_ints = wave_ints_of(cpw);
     const GenShape other = gen_shape(p, n_sets, cpw, shared_ints, more_ints);
@@ -2409,7 +2429,7 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   // wavefront per row: 4,096 rows of 32 x 128 x 2 2333 and 1535 us, 16,384 2372 and 1778, 65,536 2494 and 3085; of
   // 16 x 64 x 2 2,048 rows 617 and 452 us, 8,192 611 and 514, 16,384 623 and 636; of 8 x 32 x 2 16,384 255 and 236, 32,768
   // 269 and 316; of 4 x 200 x 4 512 3092 and 1348, 32,768 4249 and 3972)
-  const int stash = (int)std::min<int64_t>((int64_t)gen_max_chunks(p) * p->m, stride_words);
+  const int stash = (int)std::min<int64_t>((int64_t)max_chunks_of(p) * p->m, stride_words);
   const int64_t rows_shared = place_rows_bytes + 4ll * 4 * kMaxDevices, rows_wave = slide_rows_wave_bytes(stride_out_words, stash);
   const int64_t rows_waves = std::min<int64_t>({(p->max_lds - rows_shared) / rows_wave, kSlideThreads / 64, p->D});
   if (n_cand * p->D <= 16384 && rows_waves >= std::min(p->D, 4)) {
