@@ -2425,14 +2425,17 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
                        draw_block, starts, stops, (const int32_t*)nullptr, escapes, escape_cap);
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   }
-  // pass 2: every row places its W items on its own; a wavefront per row where they are few (both passes, a lane and a
-  // wavefront per row: 4,096 rows of 32 x 128 x 2 2333 and 1535 us, 16,384 2372 and 1778, 65,536 2494 and 3085; of
-  // 16 x 64 x 2 2,048 rows 617 and 452 us, 8,192 611 and 514, 16,384 623 and 636; of 8 x 32 x 2 16,384 255 and 236, 32,768
-  // 269 and 316; of 4 x 200 x 4 512 3092 and 1348, 32,768 4249 and 3972)
+  // pass 2: every row places its W items on its own, by a lane, whose steps wait for each other, or by a wavefront, of which
+  // a compute unit has few: so where rows are few, and the more so the longer they are.  Both passes, a lane / a wavefront per
+  // row, at 12,288 and 16,384 rows, 26 shapes: below 128 items 0.95 (20 x 10 x 1) to 1.05 and 0.88 to 0.98, four devices aside
+  // (4 x 16 x 1: 1.23 and 1.12, at 24,576 0.99); of 180 to 384 items 1.07 (30 x 60 x 1) to 1.74 and 0.98 (16 x 64 x 2, 615 and
+  // 628 us) to 1.65, at 24,576 0.85 to 1.04 (2 x 60 x 1 aside: 1.56); of 450 items and more 1.2 to 1.87 and 1.13 to 1.75, at 24,576 1.02 (20 x 50 x 3) to 1.51, at 32,768 0.89 to 1.34
+  // (32 x 128 x 2: 2352 and 2179 us; 4 x 200 x 4: 4139 and 3960).
   const int stash = (int)std::min<int64_t>((int64_t)max_chunks_of(p) * p->m, stride_words);
   const int64_t rows_shared = place_rows_bytes + 4ll * 4 * kMaxDevices, rows_wave = slide_rows_wave_bytes(stride_out_words, stash);
   const int64_t rows_waves = std::min<int64_t>({(p->max_lds - rows_shared) / rows_wave, kSlideThreads / 64, p->D});
-  if (n_cand * p->D <= 16384 && rows_waves >= std::min(p->D, 4)) {
+  const int64_t items = 3ll * max_chunks_of(p) * p->m, few_rows = items >= 448 ? 24576 : items >= 128 || p->D <= 4 ? 16384 : 12288;
+  if (n_cand * p->D <= few_rows && rows_waves >= std::min(p->D, 4)) {
     hipLaunchKernelGGL(wslide_place_rows_kernel, dim3((unsigned)n_cand), dim3(64 * (unsigned)rows_waves),
                        (size_t)(rows_shared + rows_waves * rows_wave), st, p->stab, d_ops, (int)stride_words, starts, escapes,
                        escape_cap, stops, timed_flags, d_ops_out, (int)stride_out_words, stash,

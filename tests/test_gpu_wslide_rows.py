@@ -1,5 +1,5 @@
-"""The second kernel of the sliding pass in its two forms, a wavefront per row for few rows and a lane per row for many, on the
-same lists: long and short rows, chunks out of order, waits of 2^16 time units and more, lists that stop early, rows of the new
+"""The second kernel of the sliding pass in its two forms, a wavefront per row for few rows and a lane per row for many (beyond
+12,288 rows, or 16,384 or 24,576 where they are longer), on the same lists: long and short rows, chunks out of order, waits of 2^16 time units and more, lists that stop early, rows of the new
 lists that are too short."""
 import numpy as np
 import pytest
@@ -28,7 +28,7 @@ def lists_of(prob, rng, n):
 
 def check(prob, words, what):
     n, D, stride = words.shape
-    many = -(-16400 // (n * D))
+    many = -(-24600 // (n * D))
     h = fp.Problem(prob, stride + 8, device=0)
     for stride_out in (stride + 8, max(8, stride // 2 // 8 * 8)):
         ref = oracle.wslide(prob, words, stride_out, threads=8)
