@@ -2032,17 +2032,24 @@ static int order_sets(const fpsched_problem* p, const int32_t* d_inflight, const
 //
 // Wavefronts per compute unit: with more of them the sets with most steps advance more slowly and are what the launch ends
 // on, with fewer the SIMDs are idle between steps.  Short sets are drawn in plain order: 16 (65,536 sets of 4 x 16 x 2, sliding,
-// with 8, 12 and 16: 313, 280 and 179 us; of 8 x 32 x 2: 892, 823 and 802).  Else eight where the batch has few sets per
-// segment, measured by how much longer the longest sets are, which goes with the devices and with the stages, and twelve
-// beyond (results only, eight and twelve: 16,384 of 32 x 128 x 2, 4 sets per segment of eight wavefronts, 3.41 and 3.64 ms;
-// 32,768 of them, 8 per segment, 6.53 and 5.21; of 32 x 64 x 2, 4 and 6 per segment, 1.92 and 1.99, 2.82 and 2.37; of
-// 20 x 100 x 2, 2.7 and 5.3 per segment, 1.78 and 2.00, 3.27 and 2.79; 16,384 of 24 x 80 x 2, 4 per segment, 2.08 and 1.91;
-// 30,000 of 12 x 40 x 3, 2.9 per segment, 2.11 and 2.21; 32,768 of 16 x 64 x 2, 4 per segment, 1.84 and 1.65).
+// with 8, 12 and 16: 313, 280 and 179 us; of 8 x 32 x 2: 892, 823 and 802; but of 16 x 128 x 1 16,384 sets 899, 737 and 844).
+// Else eight while the sets with most steps take longer than all steps shared out over the segments, that is up to about
+// 1.3 times as many sets per segment as the longest set has steps of the mean one's, and twelve beyond.  The longest set's
+// steps over the mean's are about 1 + D / 8 with one stage per device, 1 + D / 13 with two, 1 + D / 10 with more (sets as the
+// tuner's grid and `policy_sets` have them; 32 x 128 x 1 5.05, 16 x 128 x 1 3.2, 8 x 128 x 1 2.1; 32 x 128 x 2 3.34, 16 x 64 x 2 2.27,
+// 4 x 128 x 2 1.47; 32 x 48 x 3 3.7, 24 x 48 x 4 3.3, 6 x 100 x 3 1.64).  Sets per segment of eight where twelve become as good:
+// 32 x 128 x 2 4.3, 24 x 80 x 2 3.5, 16 x 64 x 2 2.7, 10 x 120 x 2 2.3, 32 x 48 x 3 5.1, 24 x 48 x 4 4.6, 28 x 100 x 1 6.  Over 20 shapes
+// with 1 to 8 sets per segment, three forms each, this is 1.2 % off the best of 8, 12 and 16 on average (20 % at worst: 49,152
+// sets of 5 x 128 x 4, lists; factors of 1.2 to 1.4 are as good); always eight 7 %, always twelve 5 %, always sixteen 9 %.
 struct GenShape { int waves, resident; int64_t blocks, lds_bytes; };   // resident: wavefronts that a compute unit has room for
 static GenShape gen_shape(const fpsched_problem* p, int64_t n_sets, int64_t sets_per_wave, int64_t shared_ints, int64_t wave_ints) {
   const int64_t lds_ints = p->max_lds / 4, segments_of_8 = 8ll * p->n_cu * sets_per_wave;
   int want = 16;
-  if (2 * gen_steps(p) >= 3 * segments_of_8) want = (double)n_sets < segments_of_8 * std::max(p->D / 6.4, p->S / 12.0) ? 8 : 12;
+  if (2 * gen_steps(p) >= 3 * segments_of_8) {
+    const int chunks = max_chunks_of(p);
+    const double longest = 1.0 + p->D / (chunks <= 1 ? 8.0 : chunks == 2 ? 13.0 : 10.0);
+    want = (double)n_sets < 1.3 * longest * (double)segments_of_8 ? 8 : 12;
+  }
   // tuning knob: FPSCHED_GEN_WAVES = resident wavefronts per compute unit
   if (const char* env = getenv("FPSCHED_GEN_WAVES")) {
     const int v = atoi(env);
