@@ -265,6 +265,8 @@ size_t fpsched_workspace_bytes(const fpsched_problem *p, int64_t n_cand, int32_t
  * stages, backward items for the backward items of the successor stages, each
  * device runs its list in order;  start = max(device free, inputs' finish +
  * cross-device latency),  finish = start + dur[kind][stage].
+ * Rows of more than 2^23 - 32 words are beyond the two passes and go to the other kernels
+ * (FPSCHED_EUNSUPPORTED if none of them fits the problem).
  * Asynchronous: work is enqueued on hip_stream (a hipStream_t, NULL = default
  * stream) and the call returns.  n_cand == 0 is a no-op. */
 int fpsched_evaluate(const fpsched_problem *p, const uint16_t *d_ops, int64_t n_cand,

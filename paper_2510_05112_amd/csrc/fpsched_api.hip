@@ -1282,8 +1282,11 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
   if (reinterpret_cast<uintptr_t>(d_ops) & 15) return FPSCHED_EINVAL;
   DeviceGuard g(p->device_id);
   if (!g.ok) return FPSCHED_EHIP;
+  // Rows too long for the timing pass's positions: the other kernels.  (Link occupancy needs D * stride * (the largest cost + two
+  // latencies) below 2^24: such rows have a single device, or no costs and latencies at all, and the plain model's results.)
+  const bool two_passes = stride_words <= kTimeMaxStride;
   const bool copy_on_slots = p->copy_depth > 0 && p->use_slots && p->copy_slots_ok;
-  const bool sync_on_slots = p->sync_on && p->use_slots && p->sync_slots_ok;
+  const bool sync_on_slots = p->sync_on && p->use_slots && p->sync_slots_ok && (two_passes || !p->lists_sync.ok);
   if ((p->sync_on || p->copy_depth > 0) && !copy_on_slots && !sync_on_slots) {
     const int cpw = p->sync_tab.cands_per_wave;
     const int64_t blocks = (n_cand + cpw - 1) / cpw;
@@ -1298,12 +1301,14 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
   // (times or latencies beyond the 24-bit forms: the general kernel, which needs no workspace, takes calls without one)
   const bool usable_workspace = d_workspace && (reinterpret_cast<uintptr_t>(d_workspace) & 15) == 0 && workspace_bytes >= 256;
   const bool without_workspace = !usable_workspace && !p->slots_ok && p->general_ok;
-  if (copy_on_slots || sync_on_slots || (p->use_slots && (!p->mb_set || p->mb_slots_ok) && !without_workspace)) {
+  const bool rows_fit = two_passes || copy_on_slots || sync_on_slots || (p->mb_set && !p->links_on && !p->lists_mb.ok);
+  if (!rows_fit && !p->general_ok) return FPSCHED_EUNSUPPORTED;
+  if (copy_on_slots || sync_on_slots || (p->use_slots && (!p->mb_set || p->mb_slots_ok) && !without_workspace && rows_fit)) {
     // the first 8 bytes of the workspace hold the counter the segments draw candidates from
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-    if (copy_on_slots && p->lists_copy.ok && copy_takes_two_passes(p, n_cand))
+    if (copy_on_slots && two_passes && p->lists_copy.ok && copy_takes_two_passes(p, n_cand))
       return run_list_evaluation(p, &p->lists_copy, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (sync_on_slots && p->lists_sync.ok)
       return run_list_evaluation(p, &p->lists_sync, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
@@ -2408,7 +2413,7 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   // (under the link model: that model's tables and workgroup shape; W items send nothing, so the second
   // pass is the same)
   const bool links = p->links_on;
-  if (!links && p->lists_times.ok) {
+  if (!links && p->lists_times.ok && stride_words <= kTimeMaxStride) {
     const fpsched_results timed{out.makespan, out.idle, out.peak, timed_flags};   // (what the order pass leaves stands in the results until pass 2)
     const StartTimes left{starts, escapes, stops, escape_cap, lpc};
     const int rc = run_list_evaluation(p, &p->lists_times, d_ops, n_cand, stride_words, timed, counter, st, &left);

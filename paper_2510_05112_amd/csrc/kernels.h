@@ -74,6 +74,7 @@ constexpr int kCheckWavesPerSimd = 3;
 constexpr int kTimeMaxThreads = 1024;
 constexpr int kTimeCopyMaxThreads = 512, kTimeCopyWavesPerSimd = 3;   // copy-engine form (up to 168 registers)
 constexpr int kCopyTransfers = 4;   // ... transfers and events that a lane keeps
+constexpr int kTimeMaxStride = (1 << 23) - 32;   // longest rows that the timing pass has positions for
 constexpr int kTimeWindowBytes = 2 * 64 * 32;   // op windows of a wavefront of the timing pass
 // VBITS 0, 1, 2: up to 1, 2, 4 stages per device.  NO_W: W items are no-ops that only have to be in range (tables: their
 // rows ask for kPadState and leave it).

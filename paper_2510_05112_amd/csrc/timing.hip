@@ -118,6 +118,8 @@ constexpr unsigned kPosMask = 0x702u;    // of a position: its place in the ring
 constexpr unsigned kPosBetween = 0xfcu;
 constexpr unsigned kPiece = 4u << 8;     // what is landed at a time: eight words, 16 bytes
 constexpr unsigned kNoList = 0x40000000u;
+// (a request reaches up to three pieces beyond the row, and no position may be kNoList)
+static_assert(((unsigned)kTimeMaxStride >> 1 << 8) + 3u * kPiece < kNoList, "");
 __device__ __forceinline__ unsigned position_of(unsigned word) { return word >> 1 << 8 | (word & 1u) << 1; }
 __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1 | (pos >> 1 & 1u); }
 

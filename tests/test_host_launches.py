@@ -1,0 +1,102 @@
+"""Which kernels a call launches, without a GPU: every test runs in a process of its own in which a stand-in for the HIP runtime
+(hip_stub.c) comes before the real one, so that launches are only noted."""
+import ctypes
+import os
+import re
+import shutil
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+import paper_2510_05112_amd as fp
+from workloads.problem import F, L, O, chain_problem
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+HEADERS = "/opt/rocm/include"
+pytestmark = pytest.mark.skipif(not (shutil.which("gcc") and os.path.isdir(os.path.join(HEADERS, "hip"))), reason="no compiler, no HIP headers")
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-I" + HEADERS, "-o", path, os.path.join(HERE, "hip_stub.c")], check=True)
+    return path
+
+
+def run(stub, what):
+    """Runs the function `what` of this file in a new process, with the stand-in."""
+    code = f"import sys; sys.path[:0] = [{HERE!r}, {os.path.dirname(HERE)!r}]; import test_host_launches as t; t.{what}(t.Device({stub!r}))"
+    done = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert done.returncode == 0, done.stdout
+
+
+class Device:
+    """In the new process: the stand-in, and calls with pointers that nothing looks at."""
+
+    def __init__(self, stub):
+        self.stub = ctypes.CDLL(stub, mode=ctypes.RTLD_GLOBAL)
+        self.stub.stub_launched.restype = ctypes.c_char_p
+        self.lib = fp.load_library()
+        self.results = fp.binding._Results(4096, 4096, 4096, 4096)
+
+    def launched(self, rc=0, what=0):
+        assert rc == what, rc
+        names = [self.stub.stub_launched(i).decode() for i in range(self.stub.stub_launches())]
+        self.stub.stub_reset()
+        return [re.search(r"\d([a-z_]+_kernel)", n).group(1) for n in names]
+
+    def evaluate(self, h, stride, n=1, what=0):
+        return self.launched(self.lib.fpsched_evaluate(h._h, 4096, n, stride, self.results, 4096, 1 << 20, None), what)
+
+    def wslide(self, h, stride):
+        size = self.lib.fpsched_wslide_workspace_bytes(h._h, 1, stride)
+        return self.launched(self.lib.fpsched_wslide(h._h, 4096, 1, stride, 4096, 64, self.results, 4096, size, None))
+
+
+LONGEST = (1 << 23) - 32   # rows that the timing pass has positions for
+TWO_PASSES = ["check_rows_kernel", "time_lists_kernel"]
+
+
+def long_rows(dev):
+    # times beyond 24 bits: positions of a row of 2^25 words would wrap
+    h = fp.Problem(chain_problem(2, 8, v=2, f=2, b=4, w=1, comm=1), 1 << 25, device=0)
+    for stride in (64, LONGEST):
+        assert dev.evaluate(h, stride) == TWO_PASSES
+    for stride in (LONGEST + 8, 1 << 23, 1 << 25):
+        assert dev.evaluate(h, stride) == ["eval_general_kernel"]
+    h.close()
+    # every form with times of 24 bits (a single device, costs of one)
+    prob = chain_problem(1, 16, v=2, f=1, b=1, w=1)
+    prob.dur[O], prob.dur[L] = 1, 1
+    ones = np.ones((8, prob.n_stages, prob.n_microbatches), np.int32)
+    forms = {"plain": (lambda h: None, "eval_general_kernel"),
+             "costs": (lambda h: h.set_microbatch_costs(ones), "eval_general_kernel"),
+             "links": (lambda h: h.set_link_occupancy(True), "eval_general_kernel"),
+             "both": (lambda h: (h.set_microbatch_costs(ones), h.set_link_occupancy(True)), "eval_general_kernel"),
+             "groups": (lambda h: h.set_sync([2, 1]), "eval_sync_kernel"),
+             "pairs": (lambda h: h.set_sync(None, [(F, 1, F, 0, 0)]), "eval_sync_kernel"),
+             "copy": (lambda h: h.set_copy_engine(3), "eval_slot_kernel")}
+    n = 1 << 20   # (more than the one kernel of the copy engine has side by side)
+    for name, (set_model, beyond) in forms.items():
+        h = fp.Problem(prob, 1 << 23, device=0)
+        set_model(h)
+        got = dev.evaluate(h, LONGEST, n)
+        assert got[-2:] == TWO_PASSES, (name, got)
+        got = dev.evaluate(h, LONGEST + 8, n)
+        assert got[-1] == beyond, (name, got)
+        h.close()
+    h = fp.Problem(prob, 1 << 23, device=0)
+    assert dev.wslide(h, LONGEST)[:2] == TWO_PASSES
+    assert "eval_slot_kernel" in dev.wslide(h, LONGEST + 8)
+    h.close()
+    # whole finish-time tables that do not fit LDS: refused
+    h = fp.Problem(chain_problem(4, 1500, v=4, f=0, b=0), 1 << 25, device=0)
+    assert dev.evaluate(h, LONGEST) == TWO_PASSES
+    assert dev.evaluate(h, LONGEST + 8, what=-6) == []
+    h.close()
+
+
+def test_rows_beyond_the_positions_of_the_timing_pass(stub):
+    run(stub, "long_rows")
