@@ -1082,7 +1082,7 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
           p->slide_ok = true;
           // ... or, on the plain model, the two passes of the list evaluation do, with the same change to their tables
           // (without them the slot kernel stays in use)
-          if (p->lists_ok && !p->lists_deg2 && !p->lists_wide) (void)build_times_variant(p);
+          if (p->lists_ok && !p->lists_deg2 && !p->lists_wide && build_times_variant(p) != FPSCHED_OK) (void)hipGetLastError();
           // the one-kernel form: the same image, and behind it per device the cost << 8 of the W item of each
           // chunk, the units it frees, and the cost << 8 of all W items of the device
           std::vector<int32_t> JS = J;
@@ -1964,10 +1964,10 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
     // the slot kernel has a form of this model too: the plain tables, 32 more dwords of LDS per lane for
     // the rings of the copy timeline
     p->copy_slots_ok = false;
-    // the two-pass evaluation takes it where times fit 24 bits and few transfers are in the engine at a time
+    // the two-pass evaluation takes it where times fit 24 bits and few transfers are in the engine at a time (without its
+    // tables the slot kernel stays in use)
     p->lists_copy.ok = false;
-    const int list_rc = p->slots_ok ? build_copy_variant(p, depth) : FPSCHED_EUNSUPPORTED;
-    if (list_rc != FPSCHED_OK && list_rc != FPSCHED_EUNSUPPORTED) return list_rc;
+    if (p->slots_ok && build_copy_variant(p, depth) != FPSCHED_OK) (void)hipGetLastError();
     if (p->slots_ok) {
       const SlotTables& PT = p->stab;
       const SlotGeometry geo = slot_geometry(PT.n_shared_ints, PT.lanes_per_cand, PT.state_words + kSlotCopyWords,

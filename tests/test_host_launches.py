@@ -100,3 +100,48 @@ def long_rows(dev):
 
 def test_rows_beyond_the_positions_of_the_timing_pass(stub):
     run(stub, "long_rows")
+
+
+def no_memory_for_copy_tables(dev):
+    prob = chain_problem(8, 16, v=2, f=3, b=4, w=2, comm=1)
+    prob.dur[O], prob.dur[L] = 2, 2
+    h = fp.Problem(prob, 128, device=0)
+    h.set_copy_engine(4)   # (deeper than the two passes go)
+    dev.stub.stub_fail_malloc(1)
+    h.set_copy_engine(3)
+    assert dev.stub.stub_fail_malloc(0) == 0
+    assert dev.evaluate(h, 128, 1 << 16) == ["reset_counter_kernel", "eval_slot_kernel"]
+    h.set_copy_engine(3)
+    assert dev.evaluate(h, 128, 1 << 16)[-2:] == TWO_PASSES
+    h.close()
+
+
+def no_memory_for_some_table(dev):
+    prob = chain_problem(4, 8, v=2, f=3, b=4, w=2, comm=1)
+    nth, first = 0, set()
+    while True:
+        nth += 1
+        dev.stub.stub_fail_malloc(nth)
+        try:
+            h = fp.Problem(prob, 64, device=0)
+        except fp.FpschedError as e:
+            assert e.code in (-2, -3)
+            dev.stub.hipGetLastError()
+            continue
+        left = dev.stub.stub_fail_malloc(0)
+        assert dev.evaluate(h, 64) == TWO_PASSES   # (and no error of the handle's making is reported)
+        size = dev.lib.fpsched_wslide_workspace_bytes(h._h, 1, 64)
+        rc = dev.lib.fpsched_wslide(h._h, 4096, 1, 64, 4096, 64, dev.results, 4096, size, None)
+        if rc == 0:
+            first.add(dev.launched()[0])
+        else:
+            assert dev.launched(rc, -6) == []
+        h.close()
+        if left > 0:
+            break
+    assert first == {"check_rows_kernel", "reset_counter_kernel"}   # (the two passes, and the slot kernel without their tables)
+
+
+@pytest.mark.parametrize("what", ["no_memory_for_copy_tables", "no_memory_for_some_table"])
+def test_no_memory_for_a_faster_form(what, stub):
+    run(stub, what)
