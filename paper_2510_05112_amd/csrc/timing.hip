@@ -583,12 +583,12 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   auto second_row = [&](int w) -> unsigned {
     return tables + (WIDE ? ((unsigned)w >> 12) & 0xfff0u : (unsigned)w & 0xffffu);
   };
-  // one step of one half of the devices in the other forms; returns the lanes that issued
+  // one step of one half of the devices with second edges in the wide form and under link occupancy or costs per
+  // micro-batch; returns the lanes that issued
   auto step = [&](Device& x) -> unsigned long long {
     asm volatile("" : "+v"(x.R), "+v"(x.j_slot));   // (the row stays one value until here: no earlier wait for it)
     const unsigned j_slot = x.j_slot;
-    const unsigned at_slot = SPLIT ? (j_slot & (unsigned)x.R.z) + ((unsigned)x.R.w + slot_base)
-                                   : (j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
+    const unsigned at_slot = (j_slot & ((unsigned)x.R.z >> 16)) + (slot_base + ((unsigned)x.R.z & 0xffffu));
     unsigned ready, cost_tag = (unsigned)x.R.y, link_free = 0u;
     unsigned long long moved;
     unsigned cost = 0u;
@@ -599,8 +599,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       cost_tag = cost << 8 | (cost_tag & 0xffu);
     }
     // (the second row comes with the slot: read where it is needed, some lane of a wavefront waits for it in most steps)
-    lds_int4 second_r{0, 0, 0, 0};
-    if (DEG2) second_r = lds_read<lds_int4>(second_row(x.R.w));
+    const lds_int4 second_r = lds_read<lds_int4>(second_row(x.R.w));
     if (LINKS) link_free = lds_read<unsigned>(x.links + (x.link & 0xffffu));
     if (WIDE) {
       // the slot's second word is the tag, the row's last one the expected tag (byte 1) and the op's own (byte 0)
@@ -612,20 +611,18 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       const unsigned zero = 0u;
       asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready), "v"(zero));
     }
+    // an op with two inputs waits for its second one first: once that is there the device's free time takes it in
+    // (nothing but the start of this op looks at that time) and the op waits for its first
     unsigned long long issue = moved;
-    if (DEG2) {
-      // an op with two inputs waits for its second one first: once that is there the device's free time takes it in
-      // (nothing but the start of this op looks at that time) and the op waits for its first
-      const unsigned long long absorb = issue & __ballot(x.R.w < 0);
-      if (absorb != 0ull) {
-        if (__builtin_amdgcn_inverse_ballot_w64(absorb)) {
-          x.free_at = max(x.free_at, ready);
-          x.R.x = second_r.x;
-          x.R.z = second_r.y;
-          x.R.w = WIDE ? (x.R.w & 0x7fff00ff) | second_r.w : x.R.w & 0x7fffffff;
-        }
-        issue &= ~absorb;
+    const unsigned long long absorb = issue & __ballot(x.R.w < 0);
+    if (absorb != 0ull) {
+      if (__builtin_amdgcn_inverse_ballot_w64(absorb)) {
+        x.free_at = max(x.free_at, ready);
+        x.R.x = second_r.x;
+        x.R.z = second_r.y;
+        x.R.w = WIDE ? (x.R.w & 0x7fff00ff) | second_r.w : x.R.w & 0x7fffffff;
       }
+      issue &= ~absorb;
     }
     if (__builtin_amdgcn_inverse_ballot_w64(issue)) {
       unsigned val = max(x.free_at, ready) + cost_tag;
@@ -642,7 +639,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
         else lds_write<uint32_t>(at, val);
       };
       leave(at_slot);
-      if (DEG2 && ((unsigned)x.R.w & kRowTwoOut) != 0u) {
+      if (((unsigned)x.R.w & kRowTwoOut) != 0u) {
         const unsigned second = (unsigned)second_r.z;
         if (LINKS) {
           const unsigned link = (unsigned)second_r.w;
