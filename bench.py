@@ -40,23 +40,24 @@ def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
 
 # the list evaluation (order pass and timing pass): plain, with costs per micro-batch (--mb-costs), with link occupancy
 # (--links), with both
-MEASURED = {("cfg4", 65536): counted(1.069e10, 1.062e9, 2.808, "list_evaluation.md")}
-MEASURED_MB = {("cfg4", 65536): counted(None, 1.426e9, 4.010, "list_evaluation.md")}
-MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.426e9, 3.715, "list_evaluation.md")}
-MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.782e9, 4.916, "list_evaluation.md")}
+MEASURED = {("cfg4", 65536): counted(1.069e10, 1.055e9, 2.807, "list_evaluation.md")}
+MEASURED_MB = {("cfg4", 65536): counted(None, 1.276e9, 3.437, "list_evaluation.md")}
+MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.736, "list_evaluation.md")}
+MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.589e9, 4.466, "list_evaluation.md")}
 # the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
-MEASURED_SYNC = {("sync4", 65536): counted(None, 2.389e8, 0.918, "list_evaluation.md")}
+MEASURED_SYNC = {("sync4", 65536): counted(None, 2.380e8, 0.916, "list_evaluation.md")}
 MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}
-# the copy engine (--config 5 --copy-engine 4)
-MEASURED_COPY = {("cfg5", 131072): counted(None, 1.850e9, 5.106, "eval_sync_kernel.md")}
-# the sliding pass (--mode wslide), both of its kernels, and without its lists (--no-lists): one kernel
-MEASURED_WSLIDE = {("cfg4", 65536): counted(3.38e10, 6.281e9, 16.01, "wslide_kernel_cfg4.md")}
-MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.813e9, 10.74, "wslide_kernel_cfg4.md")}
+# the copy engine (--config 5 --copy-engine 4: the slot kernel; up to a depth of 3: two passes)
+MEASURED_COPY = {("cfg5", 131072): counted(None, 1.850e9, 5.120, "eval_sync_kernel.md")}
+MEASURED_COPY_LISTS = {("cfg5", 131072): counted(None, 1.523e9, 4.438, "list_evaluation.md")}
+# the sliding pass (--mode wslide), all of its kernels, and without its lists (--no-lists): one kernel
+MEASURED_WSLIDE = {("cfg4", 65536): counted(3.79e10, 4.990e9, 13.18, "wslide_kernel_cfg4.md")}
+MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.814e9, 10.77, "wslide_kernel_cfg4.md")}
 # the generator (--mode generate; traffic: WRITE_SIZE x 1024 plus the parameter sets read), generator and evaluator in one
 # kernel (--mode search --fused), the same with the sliding pass in it (--slide)
-MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.762e9, 9.21, "generate_kernel_cfg4.md")}
+MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.763e9, 9.23, "generate_kernel_cfg4.md")}
 MEASURED_FUSED = {("cfg4", 65536): counted(None, 6.020e9, 10.14, "generate_kernel_cfg4.md")}
-MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 7.325e9, 11.65, "generate_kernel_cfg4.md")}
+MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 7.327e9, 11.66, "generate_kernel_cfg4.md")}
 
 
 def rooflines(alg_bytes, kernel_ms, kernel_name, figures, units=None):
@@ -329,7 +330,8 @@ def bench_wslide(args, spec, threads) -> int:
     ws_roofline, ws_issue = rooflines(
         alg_bytes, kernel_ms,
         "fpsched sliding pass without lists: eval_slot_kernel in its sliding mode" if no_lists
-        else "fpsched sliding pass: eval_slot_kernel in its timing mode + wslide_place_kernel",
+        else "fpsched sliding pass: eval_slot_kernel in its timing mode + wslide_place_kernel" if args.links or spec.index == 5   # (second edges)
+        else "fpsched sliding pass: check_rows_kernel + time_lists_kernel, start times left + wslide_place_kernel",
         None if args.links else (MEASURED_WSLIDE_EVAL if no_lists else MEASURED_WSLIDE).get((f"cfg{spec.index}", C)))
     fl0, fl1 = before["flags"].cpu().numpy(), out["flags"].cpu().numpy()
     ms0, ms1 = before["makespan"].cpu().numpy(), out["makespan"].cpu().numpy()
@@ -615,11 +617,12 @@ def main() -> int:
     # algorithmic bytes of one evaluation launch: 2 B per op word actually needed, plus the
     # per-candidate outputs (makespan 8 + idle 8D + peak 4D + flags 1)
     alg_bytes = 2 * n_ops + C * (8 + 8 * D + 4 * D + 1)
-    figures = ({} if args.table_kernel else MEASURED_COPY if args.copy_engine else MEASURED_BOTH if args.links and args.mb_costs
+    copy_on_lists = 0 < args.copy_engine <= 3   # (batches of a configuration's size)
+    figures = ({} if args.table_kernel else (MEASURED_COPY_LISTS if copy_on_lists else MEASURED_COPY) if args.copy_engine else MEASURED_BOTH if args.links and args.mb_costs
                else MEASURED_LINKS if args.links else MEASURED_MB if args.mb_costs else MEASURED)
     roofline, issue = rooflines(alg_bytes, eval_ms,
                                 "fpsched evaluation kernel, table form" + (" (eval_sync_kernel, copy-engine form)" if args.copy_engine else " (eval_general_kernel)")
-                                if args.table_kernel else "fpsched evaluation kernel (eval_slot_kernel, copy-engine mode)" if args.copy_engine
+                                if args.table_kernel else "fpsched evaluation kernel (eval_slot_kernel, copy-engine mode)" if args.copy_engine and not copy_on_lists
                                 else "fpsched evaluation, two passes (check_rows_kernel + time_lists_kernel)",
                                 figures.get((f"cfg{spec.index}", C)), units=n_ops)
     flags = res["flags"].cpu().numpy()

@@ -233,7 +233,7 @@ int fpsched_problem_set_sync(fpsched_problem *p, const int32_t *group, int32_t n
  * range or some stage has dur[O] < 1 or dur[L] < 1 (a transfer takes time); FPSCHED_EUNSUPPORTED if
  * the tables do not fit LDS or while costs per micro-batch, link occupancy or fpsched_problem_set_sync
  * are in force (and those setters, fpsched_wslide answer FPSCHED_EUNSUPPORTED while this is): the
- * handle keeps what it had.  Synchronous; allocates one table of device memory at most; works on a
+ * handle keeps what it had.  Synchronous; allocates two tables of device memory at most; works on a
  * host-only handle (validation only).  FPSCHED_KERNEL_SLOTS and _GENERAL both have a form of this
  * model, the former for problems whose times stay below 2^24 and latencies below 2^16: the two passes of the
  * plain model up to a depth of 3, or one kernel (deeper engines, and batches that it finishes sooner); it runs

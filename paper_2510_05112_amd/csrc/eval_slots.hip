@@ -87,7 +87,7 @@ __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long 
 }
 
 // MODE kSlotTimes (TIMES below) is the first pass of the weight-gradient sliding (wslide.hip) where the timing pass
-// (timing.hip) does not take the problem, which is where some stage has two inputs or outputs: the tables then
+// (timing.hip) does not take the problem (some stage has two inputs or outputs, rows too long for its positions): the tables then
 // describe the lists without their W items (a W word is a no-op that always issues at once), and
 // instead of makespan, idle and peak the kernel writes, per op word, the low sixteen bits of the time
 // the op started (eight positions of a device are 16 bytes, and the 16-byte pieces of a candidate's

@@ -138,7 +138,7 @@ __global__ void rank_keys_kernel(const long long* makespan, const long long* idl
                                  long long* key_out, unsigned char* excluded_out);
 
 // Second kernel of the weight-gradient sliding: one lane per (candidate, device) row places the W
-// items into the idle time in front of the ops timed by eval_slot_kernel<..., kSlotTimes>.
+// items into the idle time in front of the ops timed by the pass in front of it.
 constexpr int kSlideThreads = 1024;
 // dynamic LDS of a workgroup: the metadata rows, then 14 KB per wavefront (windows, stash ring, staged rows)
 constexpr int kSlideWaveLdsBytes = 14336;

@@ -66,7 +66,7 @@
 // found here and not in the order pass.  Transfers are no busy time; the makespan covers both timelines.  The last transfers
 // and the events to come stand in registers, shifted along: in LDS every lane's loop over them was a wait for all lanes.
 // 20,011 candidates of 16 devices (two towers), 45 micro-batches, depth 3: 0.72 ms as a form of the slot kernel, all devices
-// in every round; 1.43 ms here with rings in LDS, 0.49 (and 0.05 for the order pass) with registers.  (With eight transfers,
+// in every round; 1.43 ms here with rings in LDS, 0.50 (and 0.05 for the order pass) with registers.  (With eight transfers,
 // for depths up to 7, as long as there or up to a fifth longer.)
 //
 // TIMES, the first pass of the weight-gradient sliding (wslide.hip) on problems of the plain form: the lists without their W
@@ -79,7 +79,7 @@
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
 // of each cross-stage input + latency if the input ran on another device); finish = start + dur[kind][stage].
 //
-// What bounds it: LDS and vector issue (busy 85 and 81 % of the time; one launch over 65,536 candidates of
+// What bounds it: LDS and vector issue (busy 85 and 80 % of the time; one launch over 65,536 candidates of
 // 32 devices, 128 micro-batches, two chunks, profiles/list_evaluation.md).  Everything that does not need the order
 // between devices is the order pass's, which also says where each list stops, so that no word in front of that needs
 // a check.  A step is four vector instructions to decide (the slot's address from the row; an addition that gives the
@@ -87,7 +87,7 @@
 // to decode the next word; in LDS the slot read (random addresses: half of it bank conflicts), the row, the next word
 // and the slot written.  The row is fetched when the device issues and first looked at in its next step, so the other
 // half's step covers the wait.  That batch took 4.88 ms when one kernel with all devices in every round did the order
-// pass's work as well; then 1.10 ms (rows.hip) + 2.05 ms; the pass takes 1.68 ms since the step of the plain form is
+// pass's work as well; then 1.10 ms (rows.hip) + 2.05 ms; the pass takes 1.72 ms since the step of the plain form is
 // without branches (FPSCHED_STEP below: half of the gain), the rings are read without bank conflicts and requests are
 // twice as large.
 //
