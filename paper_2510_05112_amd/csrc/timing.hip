@@ -780,6 +780,9 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   const unsigned long long bound = (3ull * (unsigned)D * (unsigned)stride * (SYNC ? 4ull * (unsigned)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
+    // (vmcnt(0): the requests of the last top-up.  Waited for behind the first start times that leave, they would take these
+    // stores with them, which have only just been issued.)
+    if constexpr (TIMES) __builtin_amdgcn_s_waitcnt(0x0f70);
     land(even, 0);
     land(odd, 1);
     // ---- the rare part, only when some segment starts or has just started a candidate
