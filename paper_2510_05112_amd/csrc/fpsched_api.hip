@@ -239,11 +239,14 @@ int next_pow2(int x) {
 }
 
 using CheckKernel = void (*)(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
-template <bool NO_W>
+template <bool NO_W, bool SHARED>
 CheckKernel check_kernel_of(int vbits) {
-  return vbits == 0 ? &check_rows_kernel<0, NO_W> : (vbits == 1 ? &check_rows_kernel<1, NO_W> : &check_rows_kernel<2, NO_W>);
+  return vbits == 0 ? &check_rows_kernel<0, NO_W, SHARED> : (vbits == 1 ? &check_rows_kernel<1, NO_W, SHARED> : &check_rows_kernel<2, NO_W, SHARED>);
 }
-CheckKernel check_kernel_of(int vbits, bool no_w = false) { return no_w ? check_kernel_of<true>(vbits) : check_kernel_of<false>(vbits); }
+CheckKernel check_kernel_of(int vbits, bool no_w, bool shared) {
+  return no_w ? (shared ? check_kernel_of<true, true>(vbits) : check_kernel_of<true, false>(vbits))
+              : (shared ? check_kernel_of<false, true>(vbits) : check_kernel_of<false, false>(vbits));
+}
 
 using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
 template <bool DEG2>
@@ -643,7 +646,8 @@ int build_times_variant(fpsched_problem* p) {
   if (hipMalloc(&v->d_image, J.size() * sizeof(int32_t)) != hipSuccess) { v->d_image = nullptr; return FPSCHED_ENOMEM; }
   v->capacity = J.size();
   if (hipMemcpy(v->d_image, J.data(), J.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) return FPSCHED_EHIP;
-  for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, true)), reinterpret_cast<const void*>(times_kernel())})
+  for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, true, false)),
+                             reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, true, true)), reinterpret_cast<const void*>(times_kernel())})
     if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) != hipSuccess) return FPSCHED_EHIP;
   T.ints = v->d_image;
   v->tab = T;
@@ -1034,7 +1038,8 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
     if (ok && p->lists_ok) {
       ok = hipMalloc(&p->d_list_ints, list_image.size() * sizeof(int32_t)) == hipSuccess &&
            hipMemcpy(p->d_list_ints, list_image.data(), list_image.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
-      for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits)),
+      for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, false, false)),
+                                 reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, false, true)),
                                  reinterpret_cast<const void*>(time_kernel_of(p->ltab, p->lists_deg2, p->lists_wide))})
         ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
       p->ltab.ints = p->d_list_ints;
@@ -1230,11 +1235,13 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   const int64_t check_waves = check_blocks * cw, per_wave = (row_waves + check_waves - 1) / check_waves;
   const int draw_blocks = (int)(per_wave <= 8 ? per_wave : per_wave / 4);
   const bool dynamic = row_waves > check_waves * draw_blocks;
+  // (How the rows are read, see there)
+  const bool shared = (row_waves + draw_blocks - 1) / draw_blocks > 8 * (int64_t)p->n_cu && check_waves > 8 * (int64_t)p->n_cu && stride_words >= 64;
   if (dynamic) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter, first_drawn, (unsigned long long)(check_waves * draw_blocks));
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   }
-  hipLaunchKernelGGL(check_kernel_of(p->check_vbits, starts != nullptr), dim3((unsigned)check_blocks), dim3(64 * cw),
+  hipLaunchKernelGGL(check_kernel_of(p->check_vbits, starts != nullptr, shared), dim3((unsigned)check_blocks), dim3(64 * cw),
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;

@@ -77,8 +77,8 @@ constexpr int kCopyTransfers = 4;   // ... transfers and events that a lane keep
 constexpr int kTimeMaxStride = (1 << 23) - 32;   // longest rows that the timing pass has positions for
 constexpr int kTimeWindowBytes = 2 * 64 * 32;   // op windows of a wavefront of the timing pass
 // VBITS 0, 1, 2: up to 1, 2, 4 stages per device.  NO_W: W items are no-ops that only have to be in range (tables: their
-// rows ask for kPadState and leave it).
-template <int VBITS, bool NO_W>
+// rows ask for kPadState and leave it).  SHARED: four lanes read each other's rows.
+template <int VBITS, bool NO_W, bool SHARED>
 __global__ void check_rows_kernel(ListTables T, const uint16_t* ops, long long n_rows, int stride, int rows_per_wave,
                                   long long* out_info, int* out_peak, unsigned long long* counter,
                                   unsigned long long counter_value, int draw_blocks, int dynamic);

@@ -17,10 +17,18 @@
 // What bounds it: per 64 words twelve vector instructions and twelve clocks of LDS, and the op words once from HBM; none
 // of the three is at its limit (65,536 candidates of 32 devices, 128 micro-batches, two chunks, profiles/list_evaluation.md:
 // vector units 54 % busy, LDS 57 %, 3.8 GB at 3.5 TB/s in 1.09 ms), what is left are waits with eight wavefronts per compute
-// unit.  A lane reads its row 64 bytes at a time.  (Fourteen vector instructions, the places of the states worked out word
+// unit.  A row is read 64 bytes at a time.  (Fourteen vector instructions, the places of the states worked out word
 // by word: 1.15 ms in the same run.  States without bank conflicts, a dword of all rows side by side: LDS 32 % busy, one
 // instruction more, 1.14 ms.  128 bytes at a time: 5 % less on long batches of 16 devices, none on 32, 2 to 3 % more on
 // short rows.)
+//
+// SHARED: a load in which every lane reads a row of its own asks for 64 lines, one after the other, and the three behind it
+// for the same lines while they are on their way.  With twelve wavefronts per compute unit that is what the pass waits for
+// (262,144 candidates of 16 devices, 64 micro-batches, two chunks: address units busy half the time, 0.97 ms).  Four lanes that read
+// 64 bytes of each other's rows in turn ask for a quarter as many (0.77 ms); handing the words round takes 32 vector instructions
+// per 64 bytes of 64 rows, which is more than is gained with eight wavefronts per compute unit or fewer (the batch of 32 devices
+// above: 1.09 and 1.16 ms) and on rows of one or two requests (262,144 candidates of 4 devices, rows of 16 words, whole evaluation: 165 and
+// 169 us; rows of 64 to 96 words the same either way, of 150 words 565 and 518 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,16 +43,46 @@ typedef unsigned short u16_pair __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned bits_of(u16_pair v) { return __builtin_bit_cast(unsigned, v); }
 __device__ __forceinline__ u16_pair pair_of(unsigned v) { return __builtin_bit_cast(u16_pair, v); }
 
+typedef unsigned uint4_of_row __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ long long of_first_lane(long long v) {
+  return (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)v));
+}
+// Of two registers, lanes that differ in bit BIT (0 or 1) of their number trade: the one with 0 there gets the other's `a` as
+// its second value, that one its `b` as its first.
+template <int BIT>
+__device__ __forceinline__ void exchange_lanes(const uint4& a, const uint4& b, uint4& first, uint4& second) {
+  constexpr unsigned long long kLower = BIT == 0 ? 0x5555555555555555ull : 0x3333333333333333ull;
+#define FPSCHED_TRADE(PERM)                                                              \
+  asm("s_nop 1\n\t"                                                                      \
+      "s_mov_b64 vcc, %16\n\t"                                                           \
+      "v_cndmask_b32_dpp %0, %12, %8, vcc " PERM "\n\t"                                 \
+      "v_cndmask_b32_dpp %1, %13, %9, vcc " PERM "\n\t"                                 \
+      "v_cndmask_b32_dpp %2, %14, %10, vcc " PERM "\n\t"                                \
+      "v_cndmask_b32_dpp %3, %15, %11, vcc " PERM "\n\t"                                \
+      "s_not_b64 vcc, vcc\n\t"                                                           \
+      "v_cndmask_b32_dpp %4, %8, %12, vcc " PERM "\n\t"                                 \
+      "v_cndmask_b32_dpp %5, %9, %13, vcc " PERM "\n\t"                                 \
+      "v_cndmask_b32_dpp %6, %10, %14, vcc " PERM "\n\t"                                \
+      "v_cndmask_b32_dpp %7, %11, %15, vcc " PERM                                        \
+      : "=&v"(first.x), "=&v"(first.y), "=&v"(first.z), "=&v"(first.w), "=&v"(second.x), "=&v"(second.y), "=&v"(second.z), \
+        "=&v"(second.w)                                                                  \
+      : "v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(b.x), "v"(b.y), "v"(b.z), "v"(b.w), "s"(kLower) \
+      : "vcc", "scc")
+  if constexpr (BIT == 0) FPSCHED_TRADE("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
+  else FPSCHED_TRADE("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
+#undef FPSCHED_TRADE
+}
+
 }  // namespace
 
 // VBITS: bits of the chunk field that select a chunk's states (0, 1, 2: up to 1, 2, 4 stages per device)
-template <int VBITS, bool NO_W>
+template <int VBITS, bool NO_W, bool SHARED>
 __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_eu(kCheckWavesPerSimd, kCheckWavesPerSimd))) void check_rows_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_rows, int stride, int rows_per_wave,
     long long* __restrict__ out_info, int* __restrict__ out_peak, unsigned long long* __restrict__ counter,
     unsigned long long counter_value, int draw_blocks, int dynamic) {
   extern __shared__ int32_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // where the timing pass draws its candidates from (dynamic: set, with the counter of this pass behind it, by a kernel
   // in front of this one)
   if (!dynamic && blockIdx.x == 0 && tid == 0) *counter = counter_value;
@@ -61,25 +99,56 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   const long long n_blocks = (n_rows + rows_per_wave - 1) / rows_per_wave;
   const unsigned row_bytes = (unsigned)T.D * 8u;
   const unsigned dev_table = lds0 + (unsigned)T.n_check_ints * 4u;
-  // the row that this lane walks, the next one, and the words of either that are on their way or in registers: 64 bytes
-  // of the row at a time, the next ones requested when their walk begins
+  // The row that this lane walks, and the words of it or of the next one that are on their way or in registers: 64 bytes of
+  // each row at a time, requested when the walk of those in front of them begins.  SHARED: by the row's four neighbouring
+  // lanes, sixteen bytes each, row after row; what has arrived is then handed round among them.
   long long r = 0;
   int d = 0;
   bool active = false;
-  const uint16_t* row = ops;
   constexpr int kGroups = 4;
-  uint4 first[kGroups], second[kGroups];
+  const unsigned quarter = lane & 3, row_bytes2 = (unsigned)stride * 2u;
+  const unsigned lane_at = (unsigned)(lane & ~3) * row_bytes2 + quarter * 16u;
+  const uint16_t* row = ops;
+  int rows_here = 0;   // SHARED: of the block, less those in front of these four lanes'
+  uint4 first[kGroups], second[kGroups], asked[SHARED ? kGroups : 1];
   auto request = [&](uint4 (&piece)[kGroups], int at) {
+    if constexpr (SHARED) {
+      typedef const __attribute__((address_space(1))) char global_bytes;
+      typedef const __attribute__((address_space(1))) uint4_of_row global_piece;
+      global_bytes* const block_at = (global_bytes*)of_first_lane((long long)row);   // (one address of the wavefront)
+      const bool in_row = at + 8 * (int)quarter < stride;
+      const unsigned from = lane_at + (unsigned)at * 2u;
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g)
-      if (at + 8 * g < stride) piece[g] = *reinterpret_cast<const uint4*>(row + at + 8 * g);
+      for (int i = 0; i < kGroups; ++i) {
+        global_bytes* row_at = block_at + (size_t)i * row_bytes2;
+        asm("" : "+s"(row_at));   // (and a lane's offset)
+        if (in_row && i < rows_here) {
+          const uint4_of_row v = *(global_piece*)(row_at + from);
+          asked[i] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int g = 0; g < kGroups; ++g)
+        if (at + 8 * g < stride) piece[g] = *reinterpret_cast<const uint4*>(row + at + 8 * g);
+    }
+  };
+  auto arrive = [&](uint4 (&piece)[kGroups]) {
+    if constexpr (SHARED) {
+      uint4 half[kGroups];
+      exchange_lanes<0>(asked[0], asked[1], half[0], half[1]);
+      exchange_lanes<0>(asked[2], asked[3], half[2], half[3]);
+      exchange_lanes<1>(half[0], half[2], piece[0], piece[2]);
+      exchange_lanes<1>(half[1], half[3], piece[1], piece[3]);
+    }
   };
   auto take = [&](long long block) {
     r = block * rows_per_wave + lane;
     active = lane < rows_per_wave && r < n_rows;
     r = active ? r : 0;
     d = n_rows >> 31 ? (int)(r % T.D) : (int)((unsigned)r % (unsigned)T.D);
-    row = ops + (size_t)r * (size_t)stride;
+    row = ops + (size_t)(SHARED ? block * rows_per_wave : r) * (size_t)stride;
+    rows_here = (int)min((long long)rows_per_wave, n_rows - block * rows_per_wave) - (lane & ~3);
     request(first, 0);
   };
   // (drawn several at a time: atomics on one address complete at some 8e7 per second)
@@ -219,6 +288,7 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
     for (int g = 0; g < kGroups; ++g) {
       Group& now = (g & 1) ? B : A;
       Group& then = (g & 1) ? A : B;
+      if (g + 1 == kGroups) arrive(next);
       // (behind the end of the row this fetches rows of whatever words the registers hold, which nobody looks at)
       fetch(then, g + 1 < kGroups ? piece[g + 1] : next[0]);
       __builtin_amdgcn_sched_barrier(0);
@@ -228,6 +298,7 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  arrive(first);
   fetch(A, first[0]);
   if (alive) exchange(A);
   for (int at = 0;; at += 16 * kGroups) {
@@ -239,7 +310,7 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   // (a list that fills its row stops at the row's end: stop is the stride)
   const long long r_done = r;
   const bool was_active = active;
-  block = draw ? __shfl(drawn, 0) : block + 1;
+  block = draw ? of_first_lane(drawn) : block + 1;
   if (draw) left = draw_blocks;
   if (block < n_blocks) take(block);
   if (was_active) {
@@ -262,14 +333,18 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   }
 }
 
-#define FPSCHED_INSTANTIATE(VBITS, NO_W) \
-  template __global__ void check_rows_kernel<VBITS, NO_W>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
-FPSCHED_INSTANTIATE(0, false)
-FPSCHED_INSTANTIATE(1, false)
-FPSCHED_INSTANTIATE(2, false)
-FPSCHED_INSTANTIATE(0, true)
-FPSCHED_INSTANTIATE(1, true)
-FPSCHED_INSTANTIATE(2, true)
+#define FPSCHED_INSTANTIATE(VBITS, NO_W, SHARED) \
+  template __global__ void check_rows_kernel<VBITS, NO_W, SHARED>(ListTables, const uint16_t*, long long, int, int, long long*, int*, unsigned long long*, unsigned long long, int, int);
+#define FPSCHED_INSTANTIATE_LOADS(SHARED) \
+  FPSCHED_INSTANTIATE(0, false, SHARED)   \
+  FPSCHED_INSTANTIATE(1, false, SHARED)   \
+  FPSCHED_INSTANTIATE(2, false, SHARED)   \
+  FPSCHED_INSTANTIATE(0, true, SHARED)    \
+  FPSCHED_INSTANTIATE(1, true, SHARED)    \
+  FPSCHED_INSTANTIATE(2, true, SHARED)
+FPSCHED_INSTANTIATE_LOADS(false)
+FPSCHED_INSTANTIATE_LOADS(true)
+#undef FPSCHED_INSTANTIATE_LOADS
 #undef FPSCHED_INSTANTIATE
 
 }  // namespace fpsched
