@@ -53,7 +53,7 @@ template <int BIT>
 __device__ __forceinline__ void exchange_lanes(const uint4& a, const uint4& b, uint4& first, uint4& second) {
   constexpr unsigned long long kLower = BIT == 0 ? 0x5555555555555555ull : 0x3333333333333333ull;
 #define FPSCHED_TRADE(PERM)                                                              \
-  asm("s_nop 1\n\t"                                                                      \
+  asm volatile("s_nop 1\n\t"                                                             \
       "s_mov_b64 vcc, %16\n\t"                                                           \
       "v_cndmask_b32_dpp %0, %12, %8, vcc " PERM "\n\t"                                 \
       "v_cndmask_b32_dpp %1, %13, %9, vcc " PERM "\n\t"                                 \
