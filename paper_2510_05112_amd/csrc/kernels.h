@@ -7,6 +7,11 @@
 
 namespace fpsched {
 
+// a value that all lanes agree on, in scalar registers
+__device__ __forceinline__ long long of_first_lane(long long v) {
+  return (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)v));
+}
+
 struct Key {
   long long makespan;
   long long idx;

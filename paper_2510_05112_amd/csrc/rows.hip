@@ -44,9 +44,6 @@ __device__ __forceinline__ unsigned bits_of(u16_pair v) { return __builtin_bit_c
 __device__ __forceinline__ u16_pair pair_of(unsigned v) { return __builtin_bit_cast(u16_pair, v); }
 
 typedef unsigned uint4_of_row __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ long long of_first_lane(long long v) {
-  return (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)v));
-}
 // Of two registers, lanes that differ in bit BIT (0 or 1) of their number trade: the one with 0 there gets the other's `a` as
 // its second value, that one its `b` as its first.
 template <int BIT>

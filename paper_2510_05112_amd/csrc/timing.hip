@@ -477,6 +477,10 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   unsigned long long idle_lanes = ~0ull;
   bool first_draw = true;
   unsigned long long pool_next = 0ull, pool_end = 0ull;
+  // The counter may still have candidates to hand out.  (Where there are no more of them than segments nothing is ever drawn, and
+  // a segment that ends changes nothing for the others: a draw that comes back empty costs the wavefront some 4,500 clocks, which
+  // were 8 to 13 % of the pass on such batches.)
+  bool draws = (unsigned long long)gridDim.x * (blockDim.x >> 6) * (unsigned)cpw < (unsigned long long)n_cand;
 
   // fetch the row of the word that comes under the cursor; what follows from the row is worked out when the device's
   // next step begins, so that the other half's step covers the wait for it
@@ -801,20 +805,22 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       if (want != 0ull) {
         const int n_want = __popcll(want);
         const int have = (int)(pool_end - pool_next);
-        unsigned long long new_base = 0ull;
+        const bool drew = n_want > have && draws;
+        unsigned long long new_base = (unsigned long long)n_cand;
         int amount = 0;
-        if (n_want > have) {
+        if (drew) {
           amount = max(draw_block, n_want - have);
           if (lane == 0) new_base = atomicAdd(next_candidate, (unsigned long long)amount);
-          new_base = __shfl(new_base, 0, 64);
+          new_base = (unsigned long long)of_first_lane((long long)new_base);
+          draws = new_base + (unsigned)amount < (unsigned long long)n_cand;
         }
         const int rank = __popcll(want & ((1ull << lane) - 1ull));   // among the asking segments
-        from_pool = rank < have ? pool_next + (unsigned)rank : new_base + (unsigned)(rank - have);
-        if (n_want > have) {
+        from_pool = rank < have ? pool_next + (unsigned)rank : (drew ? new_base + (unsigned)(rank - have) : (unsigned long long)n_cand);
+        if (drew) {
           pool_next = new_base + (unsigned)(n_want - have);
           pool_end = new_base + (unsigned)amount;
         } else {
-          pool_next += (unsigned)n_want;
+          pool_next += (unsigned)min(n_want, have);
         }
       }
       if (fresh) {
@@ -905,6 +911,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     const unsigned long long x = moved_even | moved_odd | idle_lanes;
     if (((x - base_bits) & ~x & high_bits) != 0ull) {
       const bool ended = running && !priming && !any_in_segment(x);
+      const bool more = draws || (pool_next < pool_end && pool_next < (unsigned long long)n_cand);
       // (a device that a lane does not have counts as one whose list is exhausted)
       const unsigned even_issued = word_at(even.pos) - 1u, odd_issued = has_odd ? word_at(odd.pos) - 1u : 0u;
       const unsigned both = even.info | odd.info;
@@ -954,13 +961,15 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
           }
         }
         running = false;
-        fresh = true;
+        fresh = more;
         idle_device(even);
         idle_device(odd);
       }
       // the finished segments stop counting as running at once
-      idle_lanes = ~__ballot(running && !priming);
-      any_special = true;
+      const unsigned long long all_running = __ballot(running);
+      idle_lanes = ~(all_running & ~__ballot(priming));
+      any_special = any_special || more;
+      if (all_running == 0ull && !more) break;
     }
   }
 }
