@@ -361,7 +361,7 @@ template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, bool 
 __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : 4))) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
-    unsigned long long* __restrict__ next_candidate, int draw_block, StartTimes starts) {
+    unsigned long long* __restrict__ next_candidate, int draw_block, float draw_share, StartTimes starts) {
   static_assert(!WIDE || !(LINKS || MB || SYNC || COPY), "these forms have times of 24 bits");
   static_assert(!COPY || (DEG2 && !LINKS && !MB && !SYNC && !TIMES), "rows that follow others");
   static_assert(!SYNC || (DEG2 && !LINKS && !MB), "rows that follow others");
@@ -480,7 +480,12 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   // The counter may still have candidates to hand out.  (Where there are no more of them than segments nothing is ever drawn, and
   // a segment that ends changes nothing for the others: a draw that comes back empty costs the wavefront some 4,500 clocks, which
   // were 8 to 13 % of the pass on such batches.)
-  bool draws = (unsigned long long)gridDim.x * (blockDim.x >> 6) * (unsigned)cpw < (unsigned long long)n_cand;
+  // Drawn at a time: draw_share of this wavefront's share of those that were left at its last draw, up to one a segment, and
+  // draw_block at least.
+  const unsigned n_waves = gridDim.x * (blockDim.x >> 6);
+  unsigned long long handed_out = (unsigned long long)n_waves * (unsigned)cpw;   // as far as this wavefront knows
+  const float share = draw_share / (float)n_waves;
+  bool draws = handed_out < (unsigned long long)n_cand;
 
   // fetch the row of the word that comes under the cursor; what follows from the row is worked out when the device's
   // next step begins, so that the other half's step covers the wait for it
@@ -809,10 +814,11 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
         unsigned long long new_base = (unsigned long long)n_cand;
         int amount = 0;
         if (drew) {
-          amount = max(draw_block, n_want - have);
+          amount = max(max(draw_block, n_want - have), (int)fminf((float)((unsigned long long)n_cand - handed_out) * share, (float)cpw));
           if (lane == 0) new_base = atomicAdd(next_candidate, (unsigned long long)amount);
           new_base = (unsigned long long)of_first_lane((long long)new_base);
-          draws = new_base + (unsigned)amount < (unsigned long long)n_cand;
+          handed_out = new_base + (unsigned)amount;
+          draws = handed_out < (unsigned long long)n_cand;
         }
         const int rank = __popcll(want & ((1ull << lane) - 1ull));   // among the asking segments
         from_pool = rank < have ? pool_next + (unsigned)rank : (drew ? new_base + (unsigned)(rank - have) : (unsigned long long)n_cand);
@@ -976,7 +982,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
 
 #define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY)                                                        \
   template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY>(ListTables, const uint16_t*, long long, int, long long*, \
-                                                                    long long*, int*, unsigned char*, unsigned long long*, int, StartTimes);
+                                                                    long long*, int*, unsigned char*, unsigned long long*, int, float, StartTimes);
 #define FPSCHED_INSTANTIATE_MODELS(DEG2)                            \
   FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false, false)   \
   FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false, false)    \
