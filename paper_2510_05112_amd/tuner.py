@@ -109,14 +109,17 @@ def _grid_labels(types, n_limits):
     return [f"{t.label()} inflight#{i}" for t in types for i in range(n_limits)]
 
 
-def _grid_arrays(types, n_devices, inflight_options):
-    """policy int32 [n][D][8] and inflight int32 [n][S] of the schedule types times the in-flight options."""
+def _grid_arrays(types, n_devices, inflight_options, empty=np.empty):
+    """policy int32 [n][D][8] and inflight int32 [n][S] of the schedule types times the in-flight options, one behind the
+    other in one array of empty(size, int32)."""
     limits = np.asarray([np.asarray(x, np.int32) for x in inflight_options], np.int32)
     rows = np.asarray([t.policy_row() for t in types], np.int32)
-    n = len(types) * len(limits)
-    pol = np.empty((n, n_devices, 8), np.int32)
-    pol[:] = np.repeat(rows, len(limits), axis=0)[:, None, :]
-    return pol, np.tile(limits, (len(types), 1))
+    n, S = len(rows) * len(limits), limits.shape[1]
+    both = empty(n * (n_devices * 8 + S), np.int32)
+    pol, inf = both[:n * n_devices * 8].reshape(n, n_devices, 8), both[n * n_devices * 8:].reshape(n, S)
+    pol.reshape(len(rows), len(limits), n_devices, 8)[:] = rows[:, None, None, :]
+    inf.reshape(len(rows), len(limits), S)[:] = limits
+    return pol, inf
 
 
 def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, forward_first: bool = False,
@@ -138,11 +141,16 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
     if inflight_options is None:
         inflight_options = _default_inflight(problem)
     types = schedule_types(int(problem.n_devices), circular, forward_first)
-    pol, inf = _grid_arrays(types, int(problem.n_devices), inflight_options)
+    pinned = []
+
+    def empty(size, dtype):
+        pinned.append(torch.empty(size, dtype=torch.int32, pin_memory=True))
+        return pinned[0].numpy()
+    pol, inf = _grid_arrays(types, int(problem.n_devices), inflight_options, empty)
     n = len(pol)
     stride = stride_for(problem)
     # (one copy to the device, one back: each costs a grid of this size about as much as a kernel)
-    d_all = torch.from_numpy(np.concatenate([pol.ravel(), inf.ravel()])).cuda()
+    d_all = pinned[0].to(torch.device("cuda", handle.device), non_blocking=True)
     d_pol, d_inf = d_all[:pol.size].view(pol.shape), d_all[pol.size:].view(inf.shape)
     if fused:
         labels = _grid_labels(types, len(inflight_options))
@@ -163,20 +171,21 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
                      slid=bool(i >= n), ops=ops[r]) for r, (i, t) in enumerate(zip(idx, ms))]
     slide = slide and bool(problem.has_w)
     res = handle.alloc_results(2 * n if slide else n)
-    halves = [{name: t[lo:lo + n] for name, t in res.items()} for lo in ((0, n) if slide else (0,))]
+
+    def half(lo):
+        return {name: t[lo:lo + n] for name, t in res.items()}
     # Nothing but the results is asked for: the kernels that time the schedules while they generate them, the plain
     # form and the sliding one side by side (a grid fills a small part of the GPU, and each takes as long as its
-    # longest schedule has steps)
+    # longest schedule has steps; the sliding form, which takes longer, first, and what the other one needs behind its launch)
     timed = stride <= handle.max_stride   # (else the list evaluation below refuses the stride)
-    if timed:
-        main = torch.cuda.current_stream(handle.device)
-        side = torch.cuda.Stream(handle.device) if slide else None
+    if timed and slide:
+        main, side = torch.cuda.current_stream(handle.device), torch.cuda.Stream(handle.device)
+        ready = main.record_event()
         try:
-            if slide:
-                side.wait_stream(main)
-                side_workspace = handle.alloc_workspace(n, 0)
-                side_out = handle.generate_evaluate(d_pol, d_inf, results=halves[1], workspace=side_workspace, stream=side, slide=True)
-            handle.generate_evaluate(d_pol, d_inf, results=halves[0])
+            handle.generate_evaluate(d_pol, d_inf, results=half(n), slide=True)
+            side.wait_event(ready)
+            side_workspace = handle.alloc_workspace(n, 0)
+            side_out = handle.generate_evaluate(d_pol, d_inf, results=half(0), workspace=side_workspace, stream=side)
         except FpschedError as e:
             # (a cost model or a problem those kernels do not take: through lists in memory)
             if e.code not in (ERR_UNSUPPORTED, ERR_OVERFLOW):
@@ -184,14 +193,20 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
             timed = False
         finally:
             # whatever comes next, the memory the side stream works with among it, comes after the side stream's work
-            if slide:
-                main.wait_stream(side)
+            main.wait_stream(side)
+    elif timed:
+        try:
+            handle.generate_evaluate(d_pol, d_inf, results=res)
+        except FpschedError as e:
+            if e.code not in (ERR_UNSUPPORTED, ERR_OVERFLOW):
+                raise
+            timed = False
     if not timed:
         ops = handle.generate(d_pol, d_inf, stride)["ops"]
-        handle.evaluate(ops, halves[0])
+        handle.evaluate(ops, half(0))
         if slide:
             # only the results of the slid lists are ranked: the one-kernel form, which writes no list
-            handle.wslide_evaluate(ops, halves[1])
+            handle.wslide_evaluate(ops, half(n))
     k = min(k, 1024)
     best = torch.empty(2 * k + 1, dtype=torch.int64, device=res["makespan"].device)
     handle.topk(res, k, out=dict(idx=best[:k], makespan=best[k:2 * k], count=best[2 * k:].view(torch.int32)))
