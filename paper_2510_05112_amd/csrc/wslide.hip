@@ -30,7 +30,8 @@
 // read back from the device's own row, with the latency exposed.
 //
 // What bounds it: instruction issue and, with 11 wavefronts per compute unit, waits for LDS and loads.  32,768 candidates
-// of 16 devices, 64 micro-batches, 2 chunks: 1.0 ms; 2.6 ms with a stash
+// of 16 devices, 64 micro-batches, 2 chunks: 0.95 ms; 1.05 when the next entry of the escape list, loaded in a branch that is hardly
+// ever taken, was waited for in every step, with all that was on its way for the windows; 2.6 ms with a stash
 // ring of 16 words, which the lists of every loose in-flight limit overran, rows stored in 16-byte pieces (1.08 GB written
 // instead of 0.50) and six wavefronts to a workgroup; 1.2 ms with branches and scalar conditions in the step (150 vector and
 // 110 scalar instructions).
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
         add_one(n_b, c, ~0u);
         // (full: the next entry's word still holds older entries)
         const bool leave = out_of_order | (q_tail - (q_head & ~15u) == (unsigned)kStash);
-        refill_pos = leave & !from_row ? pos : refill_pos;
+        refill_pos = (leave & !from_row) ? pos : refill_pos;
         from_row = from_row | leave;
         push = !from_row;
         if (push) {
@@ -274,7 +275,7 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
       set_head(mask_of(take), head, count_of(n_w, head));
       q_head += take ? 1u : 0u;
       have_head = have_head | take;
-      if (__ballot(from_row & !have_head) != 0ull && from_row && !have_head) {
+      if (from_row & !have_head) {
         // the ring is empty and B words wait in the row: the next one, up to the one just issued
         const int end = pos + (issue ? 1 : 0);
         while (refill_pos < end) {
@@ -288,7 +289,10 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
         from_row = out_of_order || refill_pos < end;
       }
       const bool advance = have & !place;
-      if (__ballot(esc_here & advance) != 0ull && esc_here && advance) esc = esc_row[esc_at++];
+      if (esc_here & advance) {
+        esc = esc_row[esc_at++];
+        asm volatile("" : "+v"(esc));   // (waited for here, and not in every step together with all that is on its way for the window)
+      }
       pos += advance ? 1 : 0;
     }
   }
