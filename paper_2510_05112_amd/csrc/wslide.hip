@@ -30,11 +30,12 @@
 // read back from the device's own row, with the latency exposed.
 //
 // What bounds it: instruction issue and, with 11 wavefronts per compute unit, waits for LDS and loads.  32,768 candidates
-// of 16 devices, 64 micro-batches, 2 chunks: 0.95 ms; 1.05 when the next entry of the escape list, loaded in a branch that is hardly
-// ever taken, was waited for in every step, with all that was on its way for the windows; 2.6 ms with a stash
+// of 16 devices, 64 micro-batches, 2 chunks: 0.85 ms, some 75 vector instructions a step; 0.95 ms with 100, conditions as masks in vector
+// registers and selects where now the lanes that an instruction is for execute it; 1.05 ms when the next entry of the escape list, loaded in a
+// branch that is hardly ever taken, was waited for in every step, with all that was on its way for the windows; 1.2 ms with
+// branches and scalar conditions in the step (150 vector and 110 scalar instructions); 2.6 ms with a stash
 // ring of 16 words, which the lists of every loose in-flight limit overran, rows stored in 16-byte pieces (1.08 GB written
-// instead of 0.50) and six wavefronts to a workgroup; 1.2 ms with branches and scalar conditions in the step (150 vector and
-// 110 scalar instructions).
+// instead of 0.50) and six wavefronts to a workgroup.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -50,9 +51,10 @@ constexpr int kRefillAt = 16; // a lane asks for its next piece when at most thi
 constexpr int kStash = 128;   // stash ring: entries of two bits per lane
 constexpr int kOut = 32;      // staging ring of the new row: words per lane; stored sixteen (32 bytes) at a time
 constexpr int kSteps = 8;     // between two top-ups
-// per-lane conditions that select several values, as masks in vector registers: a select is then one bit-field insert
-__device__ __forceinline__ unsigned mask_of(bool b) { return b ? ~0u : 0u; }
-__device__ __forceinline__ unsigned choose(unsigned mask, unsigned a, unsigned b) { return (a & mask) | (b & ~mask); }
+// conditions are sets of lanes in scalar registers, combined there
+typedef unsigned long long Lanes;
+__device__ __forceinline__ Lanes lanes(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ballot_w64(l); }
 static_assert((2 * kWin + kStash / 8 + kOut) * 64 * 2 == kSlideWaveLdsBytes, "LDS of one wavefront");
 
 }  // namespace
@@ -96,11 +98,12 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   unsigned end_word = (active && stop < stride) ? row[stop] : 0u;
   // the first op that waited 2^16 time units or more (position << 8 | wait >> 16; all ones: none)
   unsigned esc = active ? esc_row[0] : 0xffffffffu;
+  unsigned esc_pos = esc >> 8;
   int esc_at = 1;
   // have them in registers before the loop: a wait for them inside the loop would also wait for
   // the window loads in flight
   asm volatile("" : "+v"(stop), "+v"(end_word), "+v"(esc));
-  const bool at_end = active && (end_word >> 13) == (unsigned)kEnd;
+  const Lanes at_end = lanes(active && (end_word >> 13) == (unsigned)kEnd);
 
   // window: positions [loaded - kWin, loaded) of the row are in the rings; the whole wavefront tops
   // them up every eighth step, the loads requested at one top-up landing at the next
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   unsigned t8 = 0u, busy8 = 0u;   // device free time and busy time, << 8
   unsigned u8 = 0u;               // the device's free time in the list without W items, << 8
   int mem = 0, pk = 0;
-  bool done = !active;
+  Lanes done = lanes(!active);
   // Stash: a B item's W item is known by its chunk as long as the B items of each chunk come in ascending order of their
   // micro-batches (as in every list of the generator): entries [q_head, q_tail) of the ring are those chunks, two bits
   // each, and the micro-batch is a count.  `from_row`: B words from row position refill_pos on are not in the ring (it is
@@ -144,52 +147,55 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   // cursor has been caught up with (an out-of-order chunk stays that way).
   unsigned q_head = 0u, q_tail = 0u, q_word_in = 0u;
   int refill_pos = 0;
-  bool from_row = false, out_of_order = false;
-  unsigned n_b[2] = {0u, 0u}, n_w[2] = {0u, 0u};   // B items issued, W items placed: chunks 0 and 1, 2 and 3, 16 bits each
-  bool have_head = false;      // q_word, q_dur8, q_free are those of the oldest stashed item
+  Lanes from_row = 0, out_of_order = 0;
+  // next B word expected (without its kind), next W word, of chunks 0 and 1, 2 and 3, 16 bits each
+  unsigned next_b[2] = {1u << 27, 2u << 11 | 3u << 27}, next_w[2] = {next_b[0] | 0x60006000u, next_b[1] | 0x60006000u};
+  static_assert(kW << 13 == 0x6000, "");
+  Lanes have_head = 0;         // q_word, q_dur8, q_free are those of the oldest stashed item
   unsigned q_word = 0u, q_dur8 = 0u;   // the oldest stashed item as a W word, its cost and what it frees
   int q_free = 0;
   // cost and freed units of the W item of each chunk of this device (rows kW * 4 + chunk of the metadata)
-  unsigned w_dur8[kMaxChunks];
-  int w_free[kMaxChunks];
+  // (as one vector value each: arrays would be indexed in memory)
+  typedef int PerChunk __attribute__((ext_vector_type(kMaxChunks)));
+  PerChunk w_dur8, w_free;
 #pragma unroll
   for (int c = 0; c < kMaxChunks; ++c) {
     const int2 Mw = meta[(kW * kMaxChunks + c) * lpc + d];
-    w_dur8[c] = (unsigned)Mw.x;
+    w_dur8[c] = Mw.x;
     w_free[c] = (int)(((unsigned)Mw.y >> 8) & 0xffu);
   }
-  // the oldest stashed item of the lanes in `mask` becomes chunk c, micro-batch j
-  auto set_head = [&](unsigned mask, unsigned c, unsigned j) {
-    const unsigned odd = 0u - (c & 1u);
-    unsigned dur = choose(odd, w_dur8[1], w_dur8[0]), freed = choose(odd, (unsigned)w_free[1], (unsigned)w_free[0]);
-    if (FOUR) {
-      const unsigned upper = 0u - (c >> 1);
-      dur = choose(upper, choose(odd, w_dur8[3], w_dur8[2]), dur);
-      freed = choose(upper, choose(odd, (unsigned)w_free[3], (unsigned)w_free[2]), freed);
-    }
-    q_word = choose(mask, ((unsigned)kW << 13) | c << 11 | j, q_word);
-    q_dur8 = choose(mask, dur, q_dur8);
-    q_free = (int)choose(mask, freed, (unsigned)q_free);
+  auto of_chunk = [&](const PerChunk& v, unsigned c) -> int {
+    const int low = (c & 1u) != 0u ? v[1] : v[0];
+    return FOUR && c > 1u ? ((c & 1u) != 0u ? v[3] : v[2]) : low;
   };
-  // a counter of chunk c, and its increment
-  auto count_of = [&](const unsigned (&n)[2], unsigned c) -> unsigned {
-    const unsigned word = FOUR ? choose(0u - (c >> 1), n[1], n[0]) : n[0];
-    return (word >> ((c & 1u) << 4)) & 0xffffu;
+  // the next word of chunk c, and the one behind it
+  auto next_of = [&](const unsigned (&n)[2], unsigned c) -> unsigned {
+    const unsigned two = FOUR ? (c > 1u ? n[1] : n[0]) : n[0];
+    return __builtin_amdgcn_ubfe(two, (c & 1u) << 4, 16u);
   };
-  auto add_one = [&](unsigned (&n)[2], unsigned c, unsigned mask) {
-    const unsigned one = (1u << ((c & 1u) << 4)) & mask;
+  auto move_on = [&](unsigned (&n)[2], unsigned c) {
+    const unsigned one = 1u << ((c & 1u) << 4);
     if (FOUR) {
-      const unsigned upper = 0u - (c >> 1);
-      n[0] += one & ~upper;
-      n[1] += one & upper;
+      n[0] += c > 1u ? 0u : one;
+      n[1] += c > 1u ? one : 0u;
     } else {
       n[0] += one;
     }
+  };
+  // the oldest stashed item becomes the next one of chunk c, or `word`
+  auto set_head = [&](unsigned c, unsigned word) {
+    q_word = word;
+    move_on(next_w, c);
+    q_dur8 = (unsigned)of_chunk(w_dur8, c);
+    q_free = of_chunk(w_free, c);
   };
   // The new row is staged in LDS and stored sixteen words at a time when the window is topped up, behind the loads: lanes
   // fill up at different steps, so stores in the steps are issued in nearly every one, in pieces that the memory has to
   // merge, and a wait for the window's loads waits for them too.
   int stored = 0;
+  const char* const meta_d = reinterpret_cast<const char*>(meta + d);
+  const unsigned meta_row = (unsigned)lpc * 8u;
+  auto meta_of = [&](unsigned top) -> int2 { return *reinterpret_cast<const int2*>(meta_d + __umul24(top, meta_row)); };
   auto put = [&](int at, unsigned word) { reinterpret_cast<uint16_t*>(staging + ((at >> 1) & (kOut / 2 - 1)) * 64)[at & 1] = (uint16_t)word; };
   auto staged4 = [&](int at) {   // eight words from a multiple of eight on
     const uint32_t* w = staging + ((at >> 1) & (kOut / 2 - 1)) * 64;
@@ -205,8 +211,8 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
       land();
       has_pend = false;
     }
-    if (__ballot(!done) == 0ull) break;
-    if (!done && loaded - pos <= kRefillAt && loaded < stride) {
+    if (~done == 0ull) break;
+    if (!in(done) && loaded - pos <= kRefillAt && loaded < stride) {
       request(loaded);
       has_pend = true;
     }
@@ -220,80 +226,98 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
 #pragma unroll 2
     for (int step = 0; step < kSteps; ++step) {
       const unsigned e0 = window[(unsigned)(pos & (kWin - 1)) * 64u], e1 = window[(unsigned)((pos + 1) & (kWin - 1)) * 64u];
-      const unsigned head_word = ring[((q_head >> 4) & (kStash / 16 - 1)) * 64];
+      const unsigned head_word = ring[__builtin_amdgcn_ubfe(q_head, 4u, 3u) * 64u];
       // a W word of the input at the cursor is passed over at once when the word behind it is there as well
       // (it is never in the escape list: in the first pass it starts the moment its device is free)
-      const bool hop = (pos + 1 < limit) & ((e0 & 0xe000u) == ((unsigned)kW << 13));
+      const bool hop = in(lanes(__builtin_amdgcn_ubfe(e0, 13u, 3u) == (unsigned)kW) & lanes(pos + 1 < limit));
       pos += hop ? 1 : 0;
-      const unsigned e = hop ? e1 : e0, w = e & 0xffffu;
+      const unsigned e = hop ? e1 : e0, kind = __builtin_amdgcn_ubfe(e, 13u, 3u);
       // (any 16-bit value indexes a row of the table: the top five bits of the word)
-      const int2 M = meta[((w >> 11) << lpc_shift) + d];
-      const bool have = pos < limit, over = pos >= stop;
-      const bool is_w = (w >> 13) == (unsigned)kW;   // where the input put its W items is not used
+      const int2 M = meta_of(__builtin_amdgcn_ubfe(e, 11u, 5u));
+      const Lanes have = lanes(pos < limit), over = lanes(pos >= stop);
       // the start time from its low half and the free time in front of the op, plus what the escape
-      // list says for an op that waited 2^16 time units or more
-      unsigned s8 = u8 + (((e >> 16 << 8) - u8) & 0x00ffff00u);
-      const bool esc_here = (esc >> 8) == (unsigned)pos;
-      s8 += esc_here ? esc << 24 : 0u;
-      const bool item = have & !is_w;
-      const bool place = have_head & ((item & (t8 + q_dur8 <= s8)) | (over & at_end & !done));
-      const bool issue = item & !place;
-      done = done | (over & !place);
-      const unsigned placing = mask_of(place), issuing = mask_of(issue), acting = placing | issuing;
-      put(out_len, choose(placing, q_word, w));   // (a word of a lane that does neither is overwritten by its next one)
-      out_len -= (int)acting;
-      const unsigned dur8 = choose(placing, q_dur8, (unsigned)M.x) & acting;
-      t8 = choose(issuing, s8, t8) + dur8;
-      busy8 += dur8;
-      u8 = choose(issuing, t8, u8);   // an item of the list ends when it would without any W item
-      mem += (int)((unsigned)M.y & 0xffu & issuing);
-      pk = max(pk, mem);
-      mem -= (int)(choose(placing, (unsigned)q_free, ((unsigned)M.y >> 8) & 0xffu) & acting);
-      add_one(n_w, (q_word >> 11) & 3u, placing);
-      have_head = have_head & !place;
+      // list says for an op that waited 2^16 time units or more (of the word's bits below it none gets into the time)
+      unsigned s8 = u8 + (((e >> 8) - u8) & 0x00ffff00u);
+      const Lanes esc_here = lanes(esc_pos == (unsigned)pos);
+      if (in(esc_here)) s8 += esc << 24;
+      const Lanes item = have & lanes(kind != (unsigned)kW);   // where the input put its W items is not used
+      const Lanes place = have_head & ((item & lanes(t8 + q_dur8 <= s8)) | (over & at_end & ~done));
+      const Lanes issue = item & ~place;
+      done |= over & ~place;
+      put(out_len, in(place) ? q_word : e);   // (a word of a lane that does neither is overwritten by its next one)
+      // an item of the list ends when it would without any W item; a W item takes its place in front of it
+      asm volatile("s_mov_b64 exec, %[issue]\n\t"
+                   "v_add_u32 %[t], %[start], %[cost]\n\t"
+                   "v_add_u32_sdwa %[mem], %[mem], %[units] dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+                   "v_add_u32 %[busy], %[busy], %[cost]\n\t"
+                   "v_max_i32 %[pk], %[pk], %[mem]\n\t"
+                   "v_mov_b32 %[u], %[t]\n\t"
+                   "v_sub_u32_sdwa %[mem], %[mem], %[units] dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_1\n\t"
+                   "s_mov_b64 exec, %[place]\n\t"
+                   "v_add_u32 %[t], %[t], %[w_cost]\n\t"
+                   "v_add_u32 %[busy], %[busy], %[w_cost]\n\t"
+                   "v_sub_u32 %[mem], %[mem], %[w_units]\n\t"
+                   "s_or_b64 exec, exec, %[issue]\n\t"
+                   "v_add_u32 %[len], 1, %[len]\n\t"
+                   "s_mov_b64 exec, -1"
+                   : [t] "+&v"(t8), [u] "+&v"(u8), [mem] "+&v"(mem), [pk] "+&v"(pk), [busy] "+&v"(busy8), [len] "+&v"(out_len)
+                   : [start] "v"(s8), [cost] "v"(M.x), [units] "v"(M.y), [w_cost] "v"(q_dur8), [w_units] "v"(q_free), [issue] "s"(issue),
+                     [place] "s"(place)
+                   : "scc");
+      have_head &= ~place;
       // an issued B item stashes its W item
-      const bool is_b = issue & ((w >> 13) == (unsigned)kB);
-      const unsigned c = (w >> 11) & (FOUR ? 3u : 1u);
-      bool push = false;
-      if (is_b) {
-        out_of_order = out_of_order | (count_of(n_b, c) != (w & 0x7ffu));
-        add_one(n_b, c, ~0u);
+      const Lanes is_b = issue & lanes(kind == (unsigned)kB);
+      const unsigned c = __builtin_amdgcn_ubfe(e, 11u, FOUR ? 2u : 1u);
+      Lanes push = 0;
+      const Lanes waiting = lanes(q_head != q_tail);   // (of those in front of this step's)
+      if (is_b != 0ull) {
+        out_of_order |= is_b & lanes(next_of(next_b, c) != (e & 0x1fffu));
         // (full: the next entry's word still holds older entries)
-        const bool leave = out_of_order | (q_tail - (q_head & ~15u) == (unsigned)kStash);
-        refill_pos = (leave & !from_row) ? pos : refill_pos;
-        from_row = from_row | leave;
-        push = !from_row;
-        if (push) {
-          q_word_in = ((q_tail & 15u) == 0u ? 0u : q_word_in) | c << ((q_tail & 15u) * 2u);
-          ring[((q_tail >> 4) & (kStash / 16 - 1)) * 64] = q_word_in;
+        const Lanes leave = is_b & (out_of_order | lanes(q_tail - (q_head & ~15u) == (unsigned)kStash));
+        refill_pos = in(leave & ~from_row) ? pos : refill_pos;
+        from_row |= leave;
+        push = is_b & ~from_row;
+        if (in(is_b)) move_on(next_b, c);
+        if (in(push)) {
+          const unsigned at = (q_tail & 15u) * 2u;
+          q_word_in = (at == 0u ? 0u : q_word_in) | c << at;
+          ring[__builtin_amdgcn_ubfe(q_tail, 4u, 3u) * 64u] = q_word_in;
+          q_tail += 1u;
         }
       }
-      const bool waiting = q_head != q_tail;   // (of those in front of this step's)
-      q_tail += push ? 1u : 0u;
-      const bool take = !have_head & (waiting | push);
-      const unsigned head = waiting ? (head_word >> ((q_head & 15u) * 2u)) & (FOUR ? 3u : 1u) : c;
-      set_head(mask_of(take), head, count_of(n_w, head));
-      q_head += take ? 1u : 0u;
-      have_head = have_head | take;
-      if (from_row & !have_head) {
+      const Lanes take = ~have_head & (waiting | push);
+      if (in(take)) {
+        const unsigned stashed = __builtin_amdgcn_ubfe(head_word, (q_head & 15u) * 2u, FOUR ? 2u : 1u), head = in(waiting) ? stashed : c;
+        set_head(head, next_of(next_w, head));
+        q_head += 1u;
+      }
+      have_head |= take;
+      const Lanes refill = from_row & ~have_head;
+      if (refill != 0ull) {
         // the ring is empty and B words wait in the row: the next one, up to the one just issued
-        const int end = pos + (issue ? 1 : 0);
-        while (refill_pos < end) {
-          const unsigned b_word = row[refill_pos++];
-          if ((b_word >> 13) == (unsigned)kB) {
-            set_head(~0u, (b_word >> 11) & 3u, b_word & 0x7ffu);
-            have_head = true;
-            break;
+        bool found = false, more = false;
+        if (in(refill)) {
+          const int end = pos + (in(issue) ? 1 : 0);
+          while (refill_pos < end) {
+            const unsigned b_word = row[refill_pos++];
+            if ((b_word >> 13) == (unsigned)kB) {
+              set_head((b_word >> 11) & 3u, (unsigned)kW << 13 | (b_word & 0x1fffu));
+              found = true;
+              break;
+            }
           }
+          more = refill_pos < end;
         }
-        from_row = out_of_order || refill_pos < end;
+        have_head |= lanes(found);
+        from_row &= ~refill | out_of_order | lanes(more);
       }
-      const bool advance = have & !place;
-      if (esc_here & advance) {
+      const Lanes advance = have & ~place;
+      if (in(esc_here & advance)) {
         esc = esc_row[esc_at++];
         asm volatile("" : "+v"(esc));   // (waited for here, and not in every step together with all that is on its way for the window)
+        esc_pos = esc >> 8;
       }
-      pos += advance ? 1 : 0;
+      pos += in(advance) ? 1 : 0;
     }
   }
 
