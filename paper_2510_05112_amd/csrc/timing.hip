@@ -66,8 +66,8 @@
 // found here and not in the order pass.  Transfers are no busy time; the makespan covers both timelines.  The last transfers
 // and the events to come stand in registers, shifted along: in LDS every lane's loop over them was a wait for all lanes.
 // 20,011 candidates of 16 devices (two towers), 45 micro-batches, depth 3: 0.72 ms as a form of the slot kernel, all devices
-// in every round; 1.43 ms here with rings in LDS, 0.50 (and 0.05 for the order pass) with registers.  (With eight transfers,
-// for depths up to 7, as long as there or up to a fifth longer.)
+// in every round; 1.43 ms here with rings in LDS, 0.50 (and 0.05 for the order pass) with registers, 0.32 with conditions as sets
+// of lanes and state changes on the lanes they are for (110 vector instructions a step as the compiler made them of selects).
 //
 // TIMES, the first pass of the weight-gradient sliding (wslide.hip) on problems of the plain form: the lists without their W
 // items (a W word is an op of the device's own without a cost), of which it leaves the low sixteen bits of each op's start
@@ -122,6 +122,10 @@ constexpr unsigned kNoList = 0x40000000u;
 static_assert(((unsigned)kTimeMaxStride >> 1 << 8) + 3u * kPiece < kNoList, "");
 __device__ __forceinline__ unsigned position_of(unsigned word) { return word >> 1 << 8 | (word & 1u) << 1; }
 __device__ __forceinline__ unsigned word_at(unsigned pos) { return pos >> 8 << 1 | (pos >> 1 & 1u); }
+// COPY: a step's conditions are sets of lanes in scalar registers
+typedef unsigned long long Lanes;
+__device__ __forceinline__ Lanes lanes(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ballot_w64(l); }
 
 }  // namespace
 
@@ -412,7 +416,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   const unsigned row_stride = (unsigned)D * kRowBytes;
   const unsigned stride2 = (unsigned)stride * 2u, stride_pos = position_of((unsigned)stride);
 
-  constexpr int kTransfers = COPY ? kCopyTransfers : 1;
+  // (a transfer more may have its memory event to come than may be unfinished: of equal times the compute event is first)
+  constexpr int kTransfers = COPY ? kCopyTransfers - 1 : 1, kEvents = COPY ? kCopyTransfers : 1;
   // one device of the lane: its op window, and the op under its cursor, decoded.  A device without an op looks at its
   // own word with an L that keeps it waiting.
   struct Device {
@@ -429,7 +434,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     // COPY: the copy timeline, the last COPY transfers: finish << 8 and key (a reload's word without its kind, else all ones),
     // newest first (0: none); the memory events that the walk has not passed, oldest first, time << 8 | units (all ones: none),
     // with a bit each for those that allocate
-    unsigned copy_end[kTransfers], copy_key[kTransfers], event[kTransfers], event_adds, n_events;
+    unsigned copy_end[kTransfers], copy_key[kTransfers], event[kEvents], event_adds, n_events;
     int mem, pk, cap;
     unsigned taken;              // SYNC: values of its group's item taken in
     unsigned link;               // the op's link row: byte offset of the link word, latency << 16
@@ -450,7 +455,9 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   };
   auto no_transfers = [&](Device& x) {
 #pragma unroll
-    for (int i = 0; i < kTransfers; ++i) { x.copy_end[i] = 0u; x.copy_key[i] = ~0u; x.event[i] = ~0u; }
+    for (int i = 0; i < kTransfers; ++i) { x.copy_end[i] = 0u; x.copy_key[i] = ~0u; }
+#pragma unroll
+    for (int i = 0; i < kEvents; ++i) x.event[i] = ~0u;
     x.event_adds = 0u; x.n_events = 0u; x.mem = 0; x.pk = 0;
   };
   auto set_up = [&](Device& x, int k) {
@@ -673,8 +680,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       x.mem += (x.event_adds & 1u) != 0u ? change : -change;
       x.pk = max(x.pk, x.mem);
 #pragma unroll
-      for (int i = 0; i + 1 < kTransfers; ++i) x.event[i] = x.event[i + 1];
-      x.event[kTransfers - 1] = ~0u;
+      for (int i = 0; i + 1 < kEvents; ++i) x.event[i] = x.event[i + 1];
+      x.event[kEvents - 1] = ~0u;
       x.event_adds >>= 1;
       --x.n_events;
     }
@@ -685,51 +692,68 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     const unsigned offset = (unsigned)x.R.w;
     const unsigned at_slot = (x.j_slot & (unsigned)x.R.z) + ((offset & 0xffffu) + slot_base);
     const unsigned ready = lds_read<uint32_t>(at_slot) + (unsigned)x.R.x;
-    unsigned long long moved;
+    Lanes moved;
     const unsigned zero = 0u;
     asm volatile("v_cmp_eq_u32_sdwa %0, %1, %2 src0_sel:BYTE_0 src1_sel:DWORD" : "=s"(moved) : "v"(ready), "v"(zero));
-    if (__builtin_amdgcn_inverse_ballot_w64(moved)) {
-      const unsigned kind = x.j_slot >> 15, key = x.j_slot >> 2 & 0x1fffu;
-      const unsigned dur = (unsigned)x.R.y & 0xffffff00u, allocated = offset >> 16 & 0xffu, freed = offset >> 24;
-      const bool transfer = kind - (unsigned)kO < 2u, reload = kind == (unsigned)kL;
-      // a B item waits for the reload of its activation, which may still run if it is among the last transfers (one further
-      // back than copy_depth has finished before the device got here, so a match there changes nothing); a transfer is handed
-      // over when the engine is done with the one copy_depth transfers back
-      unsigned start = max(x.free_at, ready);
-      const unsigned reloaded = kind == (unsigned)kB ? key : 0x10000u;
+    const unsigned kind = x.j_slot >> 15, key = __builtin_amdgcn_ubfe(x.j_slot, 2u, 13u);
+    const Lanes transfers = moved & lanes(kind - (unsigned)kO < 2u), computes = moved & ~transfers;
+    unsigned start = max(x.free_at, ready);
+    // a B item waits for the reload of its activation, which may still run if it is among the last transfers (one copy_depth or
+    // more back has finished before the device got here, so a match there changes nothing)
+    const Lanes reloaded = computes & lanes(kind == (unsigned)kB) & lanes(x.copy_end[0] > start);
+    if (reloaded != 0ull) {
 #pragma unroll
-      for (int i = 0; i < kTransfers; ++i) {
-        const bool waits = transfer ? T.copy_depth == i + 1 : x.copy_key[i] == reloaded;
-        start = max(start, waits ? x.copy_end[i] : 0u);
-      }
-      const unsigned val = start + (unsigned)x.R.y;
-      x.free_at = transfer ? start : val & 0xffffff00u;
-      if (!transfer) lds_write<uint32_t>(at_slot, val);
-      pass_events(x, x.free_at, start, transfer ? 0 : (int)allocated);
-      if (transfer) {
-        // a reload allocates when it starts, an offload releases when it ends
-        const unsigned begin = max(start, x.copy_end[0]), end = begin + dur;
-        const unsigned event = reload ? begin | allocated : end | freed;
-#pragma unroll
-        for (int i = kTransfers - 1; i > 0; --i) { x.copy_end[i] = x.copy_end[i - 1]; x.copy_key[i] = x.copy_key[i - 1]; }
-        x.copy_end[0] = end;
-        x.copy_key[0] = reload ? key : ~0u;
-#pragma unroll
-        for (int i = 0; i < kTransfers; ++i) x.event[i] = x.n_events == (unsigned)i ? event : x.event[i];
-        x.event_adds |= (reload ? 1u : 0u) << x.n_events;
-        ++x.n_events;
-      } else {
-        x.mem -= (int)freed;
-      }
-      const unsigned behind = (unsigned)x.R.z >> 14 & ~15u;
-      if (behind != 0u) {
-        x.R = lds_read<lds_int4>(tables + behind);
-      } else {
-        decode(x, x.w_next);
-        x.pos = (x.pos | kPosBetween) + 2u;
-        x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
-      }
+      for (int i = 0; i < kTransfers; ++i)
+        start = in(reloaded & lanes(x.copy_key[i] == key)) ? max(start, x.copy_end[i]) : start;
     }
+    // a transfer is handed over when the engine is done with the one copy_depth transfers back
+    if (transfers != 0ull) {
+      const unsigned gate = T.copy_depth == 1 ? x.copy_end[0] : (T.copy_depth == 2 ? x.copy_end[kTransfers > 1 ? 1 : 0] : x.copy_end[kTransfers - 1]);
+      start = in(transfers) ? max(start, gate) : start;
+    }
+    unsigned val;
+    asm volatile("s_mov_b64 exec, %[computes]\n\t"
+                 "v_add_u32 %[val], %[start], %[cost]\n\t"
+                 "ds_write_b32 %[at], %[val]\n\t"
+                 "v_and_b32 %[free], 0xffffff00, %[val]\n\t"
+                 "s_mov_b64 exec, %[transfers]\n\t"
+                 "v_mov_b32 %[free], %[start]\n\t"
+                 "s_mov_b64 exec, -1"
+                 : [val] "=&v"(val), [free] "+&v"(x.free_at)
+                 : [start] "v"(start), [cost] "v"(x.R.y), [at] "v"(at_slot), [computes] "s"(computes), [transfers] "s"(transfers)
+                 : "memory");
+    // the memory in front of the op's start and up to its end, with the op's own
+    const Lanes passes = moved & lanes(x.event[0] < x.free_at);
+    if (in(passes)) pass_events(x, x.free_at, start, in(computes) ? (int)__builtin_amdgcn_ubfe(offset, 16u, 8u) : 0);
+    asm volatile("s_mov_b64 exec, %[alone]\n\t"
+                 "v_add_u32_sdwa %[mem], %[mem], %[units] dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_2\n\t"
+                 "v_max_i32 %[pk], %[pk], %[mem]\n\t"
+                 "s_mov_b64 exec, %[computes]\n\t"
+                 "v_sub_u32_sdwa %[mem], %[mem], %[units] dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_3\n\t"
+                 "s_mov_b64 exec, -1"
+                 : [mem] "+&v"(x.mem), [pk] "+&v"(x.pk)
+                 : [units] "v"(offset), [alone] "s"(computes & ~passes), [computes] "s"(computes));
+    if (in(transfers)) {
+      // a reload allocates when it starts, an offload releases when it ends
+      const bool reload = kind == (unsigned)kL;
+      const unsigned begin = max(start, x.copy_end[0]), end = begin + ((unsigned)x.R.y & 0xffffff00u);
+      const unsigned event = reload ? begin | __builtin_amdgcn_ubfe(offset, 16u, 8u) : end | offset >> 24;
+#pragma unroll
+      for (int i = kTransfers - 1; i > 0; --i) { x.copy_end[i] = x.copy_end[i - 1]; x.copy_key[i] = x.copy_key[i - 1]; }
+      x.copy_end[0] = end;
+      x.copy_key[0] = reload ? key : ~0u;
+#pragma unroll
+      for (int i = 0; i < kEvents; ++i) x.event[i] = x.n_events == (unsigned)i ? event : x.event[i];
+      x.event_adds |= (reload ? 1u : 0u) << x.n_events;
+      ++x.n_events;
+    }
+    const Lanes followed = moved & lanes((unsigned)x.R.z > 0x3ffffu);
+    if (in(moved & ~followed)) {
+      decode(x, x.w_next);
+      x.pos = (x.pos | kPosBetween) + 2u;
+      x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
+    }
+    if (in(followed)) x.R = lds_read<lds_int4>(tables + ((unsigned)x.R.z >> 14 & ~15u));
     return moved;
   };
   // SYNC, every fourth round: the devices at an item of a group of micro-batches (their rows never issue and name another
