@@ -69,7 +69,10 @@ struct fpsched_problem {
   // what the variants' tables are made from: as ltab and its image, second edges as the variants read them
   ListTables variants_tab{};
   std::vector<int32_t> variants_image;
-  ListVariant lists_links, lists_mb, lists_both, lists_sync, lists_copy;
+  ListVariant lists_links, lists_mb, lists_both, lists_sync, lists_copy, lists_copy_deep;
+  // (an engine of more than kCopyShallow transfers is a form of its own)
+  ListVariant& copy_lists(int depth) { return depth > kCopyShallow ? lists_copy_deep : lists_copy; }
+  const ListVariant& copy_lists(int depth) const { return depth > kCopyShallow ? lists_copy_deep : lists_copy; }
   ListVariant lists_times;                 // the lists without their W items, first pass of the sliding pass
   // costs per micro-batch (fpsched_problem_set_microbatch_costs)
   int64_t max_comm = 0;
@@ -252,18 +255,20 @@ using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long lo
 template <bool DEG2>
 TimeKernel time_kernel_of(const ListTables& T, bool wide) {
   const bool links = T.link_words > 0;
-  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false, false>;
-  if (T.mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false, false> : &time_lists_kernel<DEG2, false, false, 1, false, false, false>;
-  if (T.mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false, false> : &time_lists_kernel<DEG2, false, false, 2, false, false, false>;
-  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false, false> : &time_lists_kernel<DEG2, false, false, 0, false, false, false>;
+  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false, 0>;
+  if (T.mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false, 0> : &time_lists_kernel<DEG2, false, false, 1, false, false, 0>;
+  if (T.mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false, 0> : &time_lists_kernel<DEG2, false, false, 2, false, false, 0>;
+  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false, 0> : &time_lists_kernel<DEG2, false, false, 0, false, false, 0>;
 }
 // the form that reads these tables
 TimeKernel time_kernel_of(const ListTables& T, bool deg2, bool wide) {
-  if (T.off_sync > 0) return &time_lists_kernel<true, false, false, 0, true, false, false>;
-  if (T.copy_depth > 0) return &time_lists_kernel<true, false, false, 0, false, false, true>;
+  if (T.off_sync > 0) return &time_lists_kernel<true, false, false, 0, true, false, 0>;
+  if (T.copy_depth > 4) return &time_lists_kernel<true, false, false, 0, false, false, FPSCHED_MAX_COPY_DEPTH>;
+  if (T.copy_depth > kCopyShallow) return &time_lists_kernel<true, false, false, 0, false, false, 4>;
+  if (T.copy_depth > 0) return &time_lists_kernel<true, false, false, 0, false, false, kCopyShallow>;
   return deg2 ? time_kernel_of<true>(T, wide) : time_kernel_of<false>(T, wide);
 }
-TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true, false>; }
+TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true, 0>; }
 
 // What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
 struct StageEdge { int32_t cls, tag, latency; };
@@ -274,7 +279,7 @@ WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
   for (int cpw = 64 / ((T->D + 1) / 2); cpw >= 1; --cpw) {
     T->cands_per_wave = cpw;   // (rings are 32-byte aligned)
     T->wave_bytes = (int32_t)((kTimeWindowBytes + 512ll * T->link_words + (int64_t)cpw * slot_bytes * T->cand_slots + 31) & ~31ll);
-    const WorkgroupShape shape = T->copy_depth > 0 ? workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds, kTimeCopyMaxThreads / 64, kTimeCopyWavesPerSimd)
+    const WorkgroupShape shape = T->copy_depth > 0 ? workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds, kTimeCopyMaxThreads / 64, kTimeCopyWavesPerSimd, T->copy_depth > kCopyShallow)
                                                    : workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds);
     if (shape.waves >= 1) return shape;
   }
@@ -502,7 +507,7 @@ int install_list_variant(fpsched_problem* p, ListTables T, const std::vector<int
   v->ok = true;
   if (getenv("FPSCHED_VERBOSE"))
     fprintf(stderr, "[fpsched] list evaluation%s%s%s: %d x %d wavefronts per compute unit (plain: %d x %d), %d candidates each\n",
-            T.copy_depth > 0 ? ", copy engine" : T.link_words > 0 ? ", links" : "", T.mb_bytes > 0 ? ", costs per micro-batch" : "", T.off_sync > 0 ? ", synchronisation" : "",
+            T.copy_depth > kCopyShallow ? ", deep copy engine" : T.copy_depth > 0 ? ", copy engine" : T.link_words > 0 ? ", links" : "", T.mb_bytes > 0 ? ", costs per micro-batch" : "", T.off_sync > 0 ? ", synchronisation" : "",
             shape.groups, shape.waves, p->time_grid / std::max(p->n_cu, 1), p->time_waves, T.cands_per_wave);
   return FPSCHED_OK;
 }
@@ -608,8 +613,9 @@ int build_list_variant(fpsched_problem* p, bool links, const int32_t* mb, ListVa
 // The tables of the copy-engine form: the plain ones, with the units in the rows of the ops themselves; transfers are no
 // busy time.
 int build_copy_variant(fpsched_problem* p, int depth) {
-  p->lists_copy.ok = false;
-  if (!p->lists_ok || p->lists_wide || depth >= kCopyTransfers) return FPSCHED_EUNSUPPORTED;
+  ListVariant& v = p->copy_lists(depth);
+  v.ok = false;
+  if (!p->lists_ok || p->lists_wide) return FPSCHED_EUNSUPPORTED;
   ListTables T = p->ltab;
   std::vector<int32_t> J = p->list_image;
   const int D = p->D;
@@ -624,7 +630,7 @@ int build_copy_variant(fpsched_problem* p, int depth) {
         t[3] |= (int32_t)((uint32_t)o[0] & 0xffff0000u);
         if (kind == kO || kind == kL) o[1] = 0;
       }
-  return install_list_variant(p, T, J, true, 1, &p->lists_copy);
+  return install_list_variant(p, T, J, true, 1, &v);
 }
 
 // The tables of the lists without their W items: a W word is a no-op, an activation is consumed by its B item.
@@ -1150,7 +1156,7 @@ void fpsched_problem_destroy(fpsched_problem* p) {
     if (p->d_times_ints) (void)hipFree(p->d_times_ints);
     if (p->d_mb_raw) (void)hipFree(p->d_mb_raw);
     if (p->d_mb_rows) (void)hipFree(p->d_mb_rows);
-    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync, &p->lists_copy, &p->lists_times})
+    for (ListVariant* v : {&p->lists_links, &p->lists_mb, &p->lists_both, &p->lists_sync, &p->lists_copy, &p->lists_copy_deep, &p->lists_times})
       if (v->d_image) (void)hipFree(v->d_image);
     if (p->d_times_links_image) (void)hipFree(p->d_times_links_image);
     if (p->d_slide_links_image) (void)hipFree(p->d_slide_links_image);
@@ -1266,24 +1272,21 @@ static int max_chunks_of(const fpsched_problem* p) {
   return max_chunks;
 }
 
-// Copy engine: the two passes or the one kernel.  The two passes have the cheaper steps, on half the lanes, and an order pass
-// and a launch more; the one kernel has its candidates side by side in wavefronts until the chip is full (`resident`), and
-// takes another turn for the rest.  Measured over 2 to 64 devices, 6 to 150 micro-batches, 1 to 4 stages per device, depths
-// 1 to 3, 64 to 131,072 candidates, one kernel / two passes:
-//   more than one turn: 1.0 to 2.4 times; but 0.72 to 1.2 beyond four turns on rows below some 96 items (65,536 of 32 x 8 x 1:
-//   0.72, of 32 x 24 x 1: 0.89, of 16 x 16 x 1: 0.95; of 32 x 32 x 2: 1.24, two towers on 16 devices, 64 micro-batches: 1.16);
-//   one turn, two or more stages per device: 1.0 to 1.3 (256 of 32 x 128 x 2: 1982 and 1630 us, 2,048 of 8 x 32 x 2: 590 and
-//   500, of 16 x 4 x 2: 83 and 75); but 0.94 to 0.99 on 3 x 6 x 2, and 0.9 to 1.0 on two devices, which are a lane per candidate in
-//   the one and two in the other (2,048 of 2 x 8 x 4: 0.92);
-//   one turn, one stage per device: on rows of 96 items and more 0.9 to 1.15 up to half a chip (2,048 of the towers with 45
-//   micro-batches 281 and 247 us, of 16 x 48 x 1: 1.06, of 24 x 48 x 1: 0.93), 0.9 to 1.03 beyond (4,096 of 24 x 48 x 1: 0.89, 8,192
-//   of 16 x 48 x 1: 0.91); on shorter rows 0.98 to 1.08 up to half a chip on four to eight devices (256 of 4 x 16 x 1: 115 and 111
-//   us), 0.85 to 1.06 on more (4,096 of the towers with 8 micro-batches 57 and 67 us); 0.93 to 1.02 on two devices (2 x 60 x 1).
+// Copy engine: the two passes or the one kernel.  The two passes have the cheaper steps, the more so the fewer transfers a lane keeps,
+// on half the lanes, and an order pass and a launch more; the one kernel has its candidates side by side in wavefronts until the chip
+// is full (`resident`), and takes another turn for the rest.  Measured over 2 to 40 devices, 6 to 64 micro-batches, 1 to 4 stages per
+// device, 256 to 65,536 candidates, one kernel / two passes, depths up to 3, 4, and 5 to 7:
+//   more than one turn: 1.1 (65,536 of 32 x 8 x 1) to 2.6, 1.07 to 2.4, 0.99 (32 x 8 x 1) to 2.1;
+//   one turn, rows of 96 items and more: 1.04 to 1.36, 0.97 (8,192 of 16 x 48 x 1: 1.00) to 1.31, and at two or more stages per device 1.0 to
+//   1.18, at one 0.83 to 1.02; two devices, which are a lane per candidate in the one and two in the other: 1.0 to 1.03, 0.96 to 1.01, 0.83 to 0.87;
+//   one turn, shorter rows: 0.99 (3 x 6 x 2) to 1.13, 0.95 to 1.09, 0.82 to 0.96; but 0.92 to 1.02 where some stage has a second input or output
+//   (towers with 8 micro-batches), and 0.88 to 0.98 on two devices.
 static bool copy_takes_two_passes(const fpsched_problem* p, int64_t n_cand) {
   const int64_t resident = (int64_t)p->copy_grid * p->copy_waves * p->stab_copy.cands_per_wave;
   const bool long_rows = (int64_t)max_chunks_of(p) * p->m * (p->has_w ? 3 : 2) >= 96;
-  if (n_cand > resident) return long_rows || n_cand <= 4 * resident;
-  return max_chunks_of(p) > 1 ? p->D > (long_rows ? 2 : 3) : p->D > 3 && (long_rows || p->D <= 8) && 2 * n_cand <= resident;
+  if (n_cand > resident) return true;
+  if (p->D <= 2) return false;
+  return p->copy_depth <= kCopyShallow ? long_rows || !p->lists_deg2 : long_rows && (p->copy_depth == 4 || max_chunks_of(p) > 1);
 }
 
 int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_cand,
@@ -1323,8 +1326,9 @@ int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 15)) return FPSCHED_EINVAL;
     if (workspace_bytes < 256) return FPSCHED_ENOMEM;
     unsigned long long* counter = static_cast<unsigned long long*>(d_workspace);
-    if (copy_on_slots && two_passes && p->lists_copy.ok && copy_takes_two_passes(p, n_cand))
-      return run_list_evaluation(p, &p->lists_copy, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
+    const ListVariant& copy_lists = p->copy_lists(p->copy_depth);
+    if (copy_on_slots && two_passes && copy_lists.ok && copy_takes_two_passes(p, n_cand))
+      return run_list_evaluation(p, &copy_lists, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (sync_on_slots && p->lists_sync.ok)
       return run_list_evaluation(p, &p->lists_sync, d_ops, n_cand, stride_words, out, counter, static_cast<hipStream_t>(hip_stream));
     if (!copy_on_slots && !sync_on_slots) {
@@ -1981,7 +1985,7 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
     p->copy_slots_ok = false;
     // the two-pass evaluation takes it where times fit 24 bits and few transfers are in the engine at a time (without its
     // tables the slot kernel stays in use)
-    p->lists_copy.ok = false;
+    p->copy_lists(depth).ok = false;
     if (p->slots_ok && build_copy_variant(p, depth) != FPSCHED_OK) (void)hipGetLastError();
     if (p->slots_ok) {
       const SlotTables& PT = p->stab;

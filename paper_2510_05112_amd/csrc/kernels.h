@@ -73,12 +73,12 @@ __global__ void eval_slot_kernel(SlotTables T, const uint16_t* ops, long long n_
 // rows than resident wavefronts, taken draw_blocks at a time, the further ones from counter[1]; else it sets *counter for the timing pass.
 // time_lists_kernel: reads out_info from out_idle, writes the results.  DEG2 = some stage has two inputs or outputs;
 // WIDE = times beyond 24 bits; MB: bytes of a value of the cost table (0: none);
-// COPY: copy engine (T.copy_depth < kCopyTransfers).
+// COPY: copy engine, transfers that a lane keeps (3, 4, 7; T.copy_depth <= COPY; 0: another form).
 constexpr int kCheckMaxThreads = 512;
 constexpr int kCheckWavesPerSimd = 3;
 constexpr int kTimeMaxThreads = 1024;
+constexpr int kCopyShallow = 3;   // copy engine: transfers that a lane keeps in the form with few registers
 constexpr int kTimeCopyMaxThreads = 512, kTimeCopyWavesPerSimd = 3;   // copy-engine form (up to 168 registers)
-constexpr int kCopyTransfers = 4;   // ... transfers and events that a lane keeps
 constexpr int kTimeMaxStride = (1 << 23) - 32;   // longest rows that the timing pass has positions for
 constexpr int kTimeWindowBytes = 2 * 64 * 32;   // op windows of a wavefront of the timing pass
 // VBITS 0, 1, 2: up to 1, 2, 4 stages per device.  NO_W: W items are no-ops that only have to be in range (tables: their
@@ -95,7 +95,7 @@ struct StartTimes {
   int32_t* stops;       // [n_cand][D]
   int32_t escape_cap, lanes;
 };
-template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, bool COPY>
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int COPY>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block,

@@ -68,6 +68,8 @@
 // 20,011 candidates of 16 devices (two towers), 45 micro-batches, depth 3: 0.72 ms as a form of the slot kernel, all devices
 // in every round; 1.43 ms here with rings in LDS, 0.50 (and 0.05 for the order pass) with registers, 0.32 with conditions as sets
 // of lanes and state changes on the lanes they are for (110 vector instructions a step as the compiler made them of selects).
+// (COPY transfers are kept, and an event more: 65,536 of them, 64 micro-batches, 1.54, 1.68 and 1.90 ms with three, four and seven, 2.77
+// ms as the slot kernel.)
 //
 // TIMES, the first pass of the weight-gradient sliding (wslide.hip) on problems of the plain form: the lists without their W
 // items (a W word is an op of the device's own without a cost), of which it leaves the low sixteen bits of each op's start
@@ -361,12 +363,12 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED                                              \
                : "memory", "scc", "v48", "v49", "v50", "v51")
 
-template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, bool COPY>
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int COPY>
 __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : 4))) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block, float draw_share, StartTimes starts) {
-  static_assert(!WIDE || !(LINKS || MB || SYNC || COPY), "these forms have times of 24 bits");
+  static_assert(!WIDE || !(LINKS || MB || SYNC || COPY != 0), "these forms have times of 24 bits");
   static_assert(!COPY || (DEG2 && !LINKS && !MB && !SYNC && !TIMES), "rows that follow others");
   static_assert(!SYNC || (DEG2 && !LINKS && !MB), "rows that follow others");
   static_assert(!TIMES || !(DEG2 || WIDE || LINKS || MB || SYNC), "");
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   const unsigned stride2 = (unsigned)stride * 2u, stride_pos = position_of((unsigned)stride);
 
   // (a transfer more may have its memory event to come than may be unfinished: of equal times the compute event is first)
-  constexpr int kTransfers = COPY ? kCopyTransfers - 1 : 1, kEvents = COPY ? kCopyTransfers : 1;
+  constexpr int kTransfers = COPY ? COPY : 1, kEvents = COPY ? COPY + 1 : 1;
   // one device of the lane: its op window, and the op under its cursor, decoded.  A device without an op looks at its
   // own word with an L that keeps it waiting.
   struct Device {
@@ -708,7 +710,9 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     }
     // a transfer is handed over when the engine is done with the one copy_depth transfers back
     if (transfers != 0ull) {
-      const unsigned gate = T.copy_depth == 1 ? x.copy_end[0] : (T.copy_depth == 2 ? x.copy_end[kTransfers > 1 ? 1 : 0] : x.copy_end[kTransfers - 1]);
+      unsigned gate = x.copy_end[0];
+#pragma unroll
+      for (int i = 1; i < kTransfers; ++i) gate = T.copy_depth > i ? x.copy_end[i] : gate;
       start = in(transfers) ? max(start, gate) : start;
     }
     unsigned val;
@@ -1008,18 +1012,20 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY>(ListTables, const uint16_t*, long long, int, long long*, \
                                                                     long long*, int*, unsigned char*, unsigned long long*, int, float, StartTimes);
 #define FPSCHED_INSTANTIATE_MODELS(DEG2)                            \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false, false)   \
-  FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 0, false, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 1, false, false, false)   \
-  FPSCHED_INSTANTIATE(DEG2, false, false, 2, false, false, false)   \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 1, false, false, false)    \
-  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false, false)
+  FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false, 0)   \
+  FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false, 0)    \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 0, false, false, 0)    \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 1, false, false, 0)   \
+  FPSCHED_INSTANTIATE(DEG2, false, false, 2, false, false, 0)   \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 1, false, false, 0)    \
+  FPSCHED_INSTANTIATE(DEG2, false, true, 2, false, false, 0)
 FPSCHED_INSTANTIATE_MODELS(false)
 FPSCHED_INSTANTIATE_MODELS(true)
-FPSCHED_INSTANTIATE(true, false, false, 0, true, false, false)
-FPSCHED_INSTANTIATE(false, false, false, 0, false, true, false)
-FPSCHED_INSTANTIATE(true, false, false, 0, false, false, true)
+FPSCHED_INSTANTIATE(true, false, false, 0, true, false, 0)
+FPSCHED_INSTANTIATE(false, false, false, 0, false, true, 0)
+FPSCHED_INSTANTIATE(true, false, false, 0, false, false, kCopyShallow)
+FPSCHED_INSTANTIATE(true, false, false, 0, false, false, 4)
+FPSCHED_INSTANTIATE(true, false, false, 0, false, false, 7)
 #undef FPSCHED_INSTANTIATE_MODELS
 #undef FPSCHED_INSTANTIATE
 
