@@ -1279,14 +1279,15 @@ static int max_chunks_of(const fpsched_problem* p) {
 //   more than one turn: 1.1 (65,536 of 32 x 8 x 1) to 2.6, 1.07 to 2.4, 0.99 (32 x 8 x 1) to 2.1;
 //   one turn, rows of 96 items and more: 1.04 to 1.36, 0.97 (8,192 of 16 x 48 x 1: 1.00) to 1.31, and at two or more stages per device 1.0 to
 //   1.18, at one 0.83 to 1.02; two devices, which are a lane per candidate in the one and two in the other: 1.0 to 1.03, 0.96 to 1.01, 0.83 to 0.87;
-//   one turn, shorter rows: 0.99 (3 x 6 x 2) to 1.13, 0.95 to 1.09, 0.82 to 0.96; but 0.92 to 1.02 where some stage has a second input or output
-//   (towers with 8 micro-batches), and 0.88 to 0.98 on two devices.
+//   one turn, shorter rows: 0.99 (3 x 6 x 2) to 1.13, 0.95 to 1.09, 0.82 to 0.96; but where some stage has a second input or output, at depths
+//   up to 3, 0.92 to 1.0 below 64 items and 1.03 to 1.07 from there on (towers with 8 to 18, and 24 and 30 micro-batches), and 0.88 to
+//   0.98 on two devices.
 static bool copy_takes_two_passes(const fpsched_problem* p, int64_t n_cand) {
   const int64_t resident = (int64_t)p->copy_grid * p->copy_waves * p->stab_copy.cands_per_wave;
-  const bool long_rows = (int64_t)max_chunks_of(p) * p->m * (p->has_w ? 3 : 2) >= 96;
+  const int64_t items = (int64_t)max_chunks_of(p) * p->m * (p->has_w ? 3 : 2);
   if (n_cand > resident) return true;
   if (p->D <= 2) return false;
-  return p->copy_depth <= kCopyShallow ? long_rows || !p->lists_deg2 : long_rows && (p->copy_depth == 4 || max_chunks_of(p) > 1);
+  return p->copy_depth <= kCopyShallow ? items >= 64 || !p->lists_deg2 : items >= 96 && (p->copy_depth == 4 || max_chunks_of(p) > 1);
 }
 
 int fpsched_evaluate(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_cand,
