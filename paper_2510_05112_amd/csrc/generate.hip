@@ -25,7 +25,8 @@
 // timed in the step behind its own, before which nothing waits for LDS that the next step does not wait for as well.
 // 16,384 sets of 32 devices, 2 stages each, 128 micro-batches (2,657 steps a set, 8,884 the longest): sliding form 4.84 ms
 // with 73 instructions, conditions as masks in vector registers, and 12 wavefronts per compute unit in one workgroup, 4.22
-// with 57 instructions, 3.97 with larger rings, 3.89 now (fpsched_api.hip, gen_shape); results only 5.49, 4.66, then 3.42,
+// with 57 instructions, 3.97 with larger rings, 3.89 with fewer wavefronts (fpsched_api.hip, gen_shape), 3.82 since the placing of W items
+// has its conditions as sets of lanes too (some 35 instead of 48 vector instructions a round); results only 5.49, 4.66, then 3.42,
 // lists 5.04, 3.96, then 2.94; 4,096 sets of 16 devices, 64 micro-batches (the longest sets' chain): 0.77 and 0.75, 0.74 and
 // 0.67, 0.66 and 0.54 ms; 65,536 of 8 devices, 32 micro-batches: 0.90 and 0.81, 0.77 and 0.72, 0.78 and 0.67 ms.
 // Priorities (Section 5.2; Table of built-in values): computation type traversal priority
@@ -58,7 +59,7 @@ constexpr unsigned kBothSigns = 0x80008000u;
 // are combined.
 __device__ __forceinline__ unsigned mask_of(bool b) { return b ? ~0u : 0u; }
 __device__ __forceinline__ unsigned choose(unsigned mask, unsigned a, unsigned b) { return (a & mask) | (b & ~mask); }
-// The steps' conditions are sets of lanes in scalar registers, combined there, beside the vector instructions.
+// Conditions are sets of lanes in scalar registers, combined there, beside the vector instructions.
 typedef unsigned long long Lanes;
 __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ballot_w64(l); }
 template <class A>
@@ -262,7 +263,9 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   auto on_ring = [&](unsigned at) -> unsigned { return (at & (ring_bytes - 256u)) | ring; };
   unsigned ring_in = ring, ring_out = ring, gap = 0u, q_in = 0u, q_out = 0u, q_tail = 0u;
   int w_placed = 0;
-  unsigned event = 0u, has_event = 0u;   // (mask)
+  unsigned event = 0u;
+  Lanes has_event = 0;
+  const unsigned ring_mask = ring_bytes - 256u;
   // one round: the oldest stashed W item runs if what is left of the gap has room for it; else the gap's item starts, and
   // the next one's gap opens
   auto settle = [&]() {
@@ -271,10 +274,10 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
     if constexpr (V > 1) {
       const unsigned word = lds_read<unsigned>(queue + q_out / kQueueEntries * 256u);
       if constexpr (V == 2) {
-        const unsigned second = (unsigned)((int)(word << (31u - q_out % 32u)) >> 31);
-        dur = choose(second, (unsigned)w_dur[V - 1], dur);
-        freed = choose(second, (unsigned)w_free[V - 1], freed);
-        units = choose((unsigned)((int)(event << 31) >> 31), (unsigned)f_units[V - 1], units);
+        const Lanes second = __ballot(__builtin_amdgcn_ubfe(word, q_out, 1u) != 0u), of_second = __ballot((event & 1u) != 0u);
+        dur = of(second, (unsigned)w_dur[V - 1], dur);
+        freed = of(second, (unsigned)w_free[V - 1], freed);
+        units = of(of_second, (unsigned)f_units[V - 1], units);
       } else {
         const unsigned c = word >> (q_out % kQueueEntries * kQueueBits) & 3u;
         dur = (unsigned)gen_pick<V>(w_dur, c);
@@ -282,23 +285,52 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         units = (unsigned)gen_pick<V>(f_units, event & 3u);
       }
     }
-    const unsigned run_w = mask_of((q_in != q_out) & (dur <= gap)), start = has_event & ~run_w;
-    w_placed += (int)(dur & run_w);
-    q_out -= run_w;
-    const unsigned b = (unsigned)((int)(event << 29) >> 31);
-    mem += (int)(units & start & ~b) - (int)(freed & run_w);
-    peak = max(peak, mem);
-    if constexpr (V > 1) {   // a B item's W item is stashed
-      q_tail |= (event & 3u & b & start) << (q_in % kQueueEntries * kQueueBits);
-      lds_write<unsigned>(queue + q_in / kQueueEntries * 256u, q_tail);
+    const Lanes run_w = __ballot(q_in != q_out) & __ballot(dur <= gap), start = has_event & ~run_w, is_b = __ballot((event & 4u) != 0u);
+    const Lanes more = __ballot(ring_in != ring_out);
+    [[maybe_unused]] unsigned scratch;
+    // a B item's W item is stashed
+    if constexpr (V > 1) {
+      const unsigned shift = q_in * kQueueBits, at = queue + q_in / kQueueEntries * 256u, chunk = event & 3u;   // (of a shift five bits are looked at)
+      asm volatile("s_mov_b64 exec, %[stashes]\n\t"
+                   "v_lshl_or_b32 %[tail], %[chunk], %[shift], %[tail]\n\t"
+                   "v_add_u32 %[in], 1, %[in]\n\t"
+                   "ds_write_b32 %[at], %[tail]\n\t"
+                   "v_and_b32 %[left], %[last], %[in]\n\t"
+                   "v_cmp_ne_u32 vcc, 0, %[left]\n\t"
+                   "s_andn2_b64 exec, exec, vcc\n\t"
+                   "v_mov_b32 %[tail], 0\n\t"
+                   "s_mov_b64 exec, -1"
+                   : [tail] "+&v"(q_tail), [in] "+&v"(q_in), [left] "=&v"(scratch)
+                   : [chunk] "v"(chunk), [shift] "v"(shift), [at] "v"(at), [last] "s"(kQueueEntries - 1u), [stashes] "s"(start & is_b)
+                   : "memory", "vcc", "scc");
+    } else {
+      asm volatile("s_mov_b64 exec, %[stashes]\n\t"
+                   "v_add_u32 %[in], 1, %[in]\n\t"
+                   "s_mov_b64 exec, -1"
+                   : [in] "+&v"(q_in) : [stashes] "s"(start & is_b));
     }
-    q_in -= b & start;
-    if constexpr (V > 1) q_tail = q_in % kQueueEntries == 0u ? 0u : q_tail;
-    const unsigned more = mask_of(ring_in != ring_out);
-    gap = choose(run_w, gap - dur, next >> 3 & more);
-    event = choose(run_w, event, next);
-    has_event = choose(run_w, has_event, more);
-    ring_out = on_ring(ring_out + (256u & more & ~run_w));
+    asm volatile("s_mov_b64 exec, %[runs]\n\t"
+                 "v_add_u32 %[placed], %[placed], %[dur]\n\t"
+                 "v_add_u32 %[out], 1, %[out]\n\t"
+                 "v_sub_u32 %[mem], %[mem], %[freed]\n\t"
+                 "v_sub_u32 %[gap], %[gap], %[dur]\n\t"
+                 "s_mov_b64 exec, %[starts]\n\t"
+                 "v_add_u32 %[mem], %[mem], %[units]\n\t"
+                 "v_max_i32 %[peak], %[peak], %[mem]\n\t"
+                 "s_mov_b64 exec, %[opens]\n\t"
+                 "v_mov_b32 %[gap], 0\n\t"
+                 "s_and_b64 exec, exec, %[more]\n\t"
+                 "v_lshrrev_b32 %[gap], 3, %[next]\n\t"
+                 "v_mov_b32 %[event], %[next]\n\t"
+                 "v_add_u32 %[at], 0x100, %[at]\n\t"
+                 "v_and_or_b32 %[at], %[at], %[mask], %[ring]\n\t"
+                 "s_mov_b64 exec, -1"
+                 : [placed] "+&v"(w_placed), [out] "+&v"(q_out), [mem] "+&v"(mem), [peak] "+&v"(peak), [gap] "+&v"(gap), [event] "+&v"(event),
+                   [at] "+&v"(ring_out)
+                 : [dur] "v"(dur), [freed] "v"(freed), [units] "v"(units), [next] "v"(next), [ring] "v"(ring), [mask] "s"(ring_mask), [runs] "s"(run_w),
+                   [starts] "s"(start & ~is_b), [opens] "s"(~run_w), [more] "s"(more)
+                 : "scc");
+    has_event = (has_event & run_w) | (more & ~run_w);
   };
 
   // the actor's own counters, two stages per register
@@ -363,6 +395,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   for (unsigned long long look = 0; look < bound; ++look) {
     const unsigned step_0 = (unsigned)look * kStepsPerLook;
     if (__ballot(fresh) != 0ull) {
+      has_event &= ~__ballot(fresh);
       // ---- segments that finished write their schedule out and start on the next set
       if (fresh) {
         fresh = false;
@@ -479,7 +512,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         first_step = step_0; steps = 0; next_step = step_0;
         status = set_bad ? 4 : 0; len = 0; stored = 0;
         free_at = 0; mem = 0; peak = 0;
-        ring_in = ring; ring_out = ring; has_event = 0u; event = 0u; gap = 0u; q_in = 0u; q_out = 0u; q_tail = 0u; w_placed = 0;
+        ring_in = ring; ring_out = ring; event = 0u; gap = 0u; q_in = 0u; q_out = 0u; q_tail = 0u; w_placed = 0;
         if (!TIMED) row = ops + (size_t)(has_row ? set * D + d : 0) * (size_t)stride;
         fresh = has_set && !live;   // nothing to schedule (a bad set, no stages): written out next time round
       }
@@ -713,9 +746,9 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
     }
     if (SLIDE) {
       // (a look adds at most kStepsPerLook items, and one place of the ring stays empty)
-      const bool ended = live && !any_pick;
-      while (__ballot(((ring_in - ring_out) & (ring_bytes - 1u)) > ring_bytes - (1 + kStepsPerLook) * 256u ||
-                      (ended && (has_event != 0u || ring_in != ring_out))) != 0ull)
+      const Lanes ended = __ballot(live && !any_pick);
+      while ((__ballot(((ring_in - ring_out) & (ring_bytes - 1u)) > ring_bytes - (1 + kStepsPerLook) * 256u) |
+              (ended & (has_event | __ballot(ring_in != ring_out)))) != 0ull)
 #pragma unroll
         for (int i = 0; i < kRoundsPerLook; ++i) settle();
     }
