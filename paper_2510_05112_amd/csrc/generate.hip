@@ -54,9 +54,7 @@ typedef short pair16 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned bits_of(pair16 v) { return __builtin_bit_cast(unsigned, v); }
 __device__ __forceinline__ pair16 pair_of(unsigned v) { return __builtin_bit_cast(pair16, v); }
 constexpr unsigned kBothSigns = 0x80008000u;
-// settle keeps per-lane conditions that select several values as masks (all ones or 0) in a vector register: a select
-// is then one bit-field insert, where a comparison's result in a scalar register goes through 0 / 1 values when conditions
-// are combined.
+// Four stages per actor: which pair of them, as a mask (all ones or 0) that is also combined with values.
 __device__ __forceinline__ unsigned mask_of(bool b) { return b ? ~0u : 0u; }
 __device__ __forceinline__ unsigned choose(unsigned mask, unsigned a, unsigned b) { return (a & mask) | (b & ~mask); }
 // Conditions are sets of lanes in scalar registers, combined there, beside the vector instructions.

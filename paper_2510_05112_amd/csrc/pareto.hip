@@ -14,8 +14,10 @@
 // never qualify again, so every cursor only moves forward.  All steps are pure functions of the
 // values, independent of workgroup scheduling.
 //
-// What bounds both: the latency of the sort on one compute unit (block_sort.h).  65,536 candidates of 8 devices: tiles
-// 25 us, merge 10 us (61 and 22 us with a barrier after each stage of the sort and only the walk).
+// What bounds both: the latency of dependent steps on one compute unit, most of all the sort's (block_sort.h).  So a tile
+// first drops what cannot be on its front, and sorts what is left, on evaluated schedules a few dozen of 2,048 candidates.  65,536
+// candidates of 8 devices: tiles 16.8 us, merge 9.1 us (25 and 10 us where all of a tile was sorted and one thread fetched a
+// tile's front).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -83,12 +85,92 @@ __device__ __forceinline__ int sorted_front(FrontElem a, FrontElem b, int size, 
   return total;
 }
 
+// Classes of peaks for the candidates that a tile drops before it sorts: ascending in the peak, 32 per factor of two, so that
+// peaks below 64 have one each.  (float rounds in order; 2^31 - 1 becomes 2^31 and class 993.)
+constexpr int kPeakClasses = kTile / 2;
+__device__ __forceinline__ int peak_class(unsigned peak) {
+  return peak == 0u ? 0 : (int)(__float_as_uint((float)peak) >> 18) - 127 * 32 + 1;
+}
+static_assert((158 - 127) * 32 + 1 < kPeakClasses, "");
+
+// Drops entries that are not on the front of the workgroup's and puts the others next to each other, in any order, into
+// buf.key and buf.pos; returns their number.  Of a class stays what is faster than all of the classes in front of it, and of that the
+// best (makespan, peak, index) and whatever has a smaller peak than it.  All threads call this.
+__device__ __forceinline__ int drop_dominated(const FrontElem& a, const FrontElem& b, FrontBuffer& buf, unsigned long long (&wave_fastest)[kTile / 128], int& held) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned long long* const fastest = buf.key;                    // of a class: its smallest makespan,
+  unsigned long long* const ahead = buf.key + kPeakClasses;       // that of the classes in front of it,
+  unsigned long long* const best = buf.pos;                       // the first (peak, index) of the former
+  fastest[tid] = ~0ull;
+  best[tid] = ~0ull;
+  if (tid == 0) held = 0;
+  __syncthreads();
+  const bool have_a = a.pos != kNoEntry, have_b = b.pos != kNoEntry;
+  const int class_a = have_a ? peak_class((unsigned)(a.pos >> 32)) : 0, class_b = have_b ? peak_class((unsigned)(b.pos >> 32)) : 0;
+  // (a look first: lanes at one address take turns)
+  if (have_a && a.key < *(volatile unsigned long long*)&fastest[class_a]) atomicMin(&fastest[class_a], a.key);
+  if (have_b && b.key < *(volatile unsigned long long*)&fastest[class_b]) atomicMin(&fastest[class_b], b.key);
+  __syncthreads();
+  if (have_a && a.key == fastest[class_a]) atomicMin(&best[class_a], a.pos);
+  if (have_b && b.key == fastest[class_b]) atomicMin(&best[class_b], b.pos);
+  unsigned long long least = fastest[tid];
+#pragma unroll
+  for (int step = 1; step < 64; step <<= 1) {
+    const unsigned long long o = __shfl_up(least, step);
+    if (lane >= step) least = min(least, o);
+  }
+  if (lane == 63) wave_fastest[wave] = least;
+  __syncthreads();
+  unsigned long long before = __shfl_up(least, 1);
+  if (lane == 0) before = ~0ull;
+  for (int w = 0; w < wave; ++w) before = min(before, wave_fastest[w]);
+  ahead[tid] = before;
+  __syncthreads();
+  auto stays = [&](const FrontElem& e, int c) {
+    const unsigned long long first = best[c];
+    return (e.key < ahead[c] || e.key == ~0ull) && (e.pos == first || e.pos >> 32 < first >> 32);
+  };
+  const bool keep_a = have_a && stays(a, class_a), keep_b = have_b && stays(b, class_b);
+  const unsigned long long kept_a = __ballot(keep_a), kept_b = __ballot(keep_b);
+  int at = 0;
+  if (lane == 0 && (kept_a | kept_b) != 0ull) at = atomicAdd(&held, __popcll(kept_a) + __popcll(kept_b));
+  at = __shfl(at, 0);
+  __syncthreads();   // (everyone has looked at the classes, whose place the entries take)
+  const unsigned long long lower = (1ull << lane) - 1ull;
+  if (keep_a) {
+    const int to = at + __popcll(kept_a & lower);
+    buf.key[to] = a.key;
+    buf.pos[to] = a.pos;
+  }
+  if (keep_b) {
+    const int to = at + __popcll(kept_a) + __popcll(kept_b & lower);
+    buf.key[to] = b.key;
+    buf.pos[to] = b.pos;
+  }
+  __syncthreads();
+  return held;
+}
+
+// The front of the first `held` entries of buf, as sorted_front hands it out.
+template <typename Emit>
+__device__ __forceinline__ int front_of_held(int held, FrontBuffer& buf, Emit emit) {
+  auto load = [&](int i) { return i < held ? FrontElem{buf.key[i], buf.pos[i]} : FrontElem{kNoEntry, kNoEntry}; };
+  const int ia = (threadIdx.x >> 6) * 128 + (threadIdx.x & 63);
+  const FrontElem a = load(ia), b = load(ia + 64);
+  int size = 128;
+  while (size < held) size <<= 1;
+  __syncthreads();
+  return sorted_front(a, b, size, buf, emit);
+}
+
 }  // namespace
 
 __global__ __launch_bounds__(kTile / 2) void pareto_tile_kernel(
     const long long* __restrict__ makespan, const int* __restrict__ peak, const unsigned char* __restrict__ flags,
     long long n, int D, Key* __restrict__ front_keys, int* __restrict__ front_peak, int* __restrict__ tile_count) {
   __shared__ FrontBuffer buf;
+  __shared__ unsigned long long wave_fastest[kTile / 128];
+  __shared__ int held;
   const long long base = (long long)blockIdx.x * kTile;
   auto load = [&](int i) {
     const long long g = base + i;
@@ -101,7 +183,8 @@ __global__ __launch_bounds__(kTile / 2) void pareto_tile_kernel(
     return e;
   };
   const FrontElem a = load(threadIdx.x), b = load(threadIdx.x + kTile / 2);
-  const int total = sorted_front(a, b, kTile, buf, [&](int at, const FrontElem& e) {
+  const int left = drop_dominated(a, b, buf, wave_fastest, held);
+  const int total = front_of_held(left, buf, [&](int at, const FrontElem& e) {
     front_keys[base + at] = Key{(long long)(e.key ^ (1ull << 63)), (long long)(unsigned)e.pos};
     front_peak[base + at] = (int)(e.pos >> 32);
   });
@@ -120,32 +203,30 @@ __global__ __launch_bounds__(kParetoMergeThreads) void pareto_merge_kernel(
   __shared__ int held;
   if (threadIdx.x == 0) held = 0;
   __syncthreads();
+  // (as many lanes of a wavefront to a tile as there are, so that its entries come side by side)
+  int per_tile = 64;
+  while (per_tile > 1 && tiles * per_tile > kParetoMergeThreads) per_tile >>= 1;
+  const int of_tile = threadIdx.x & (per_tile - 1), first_tile = threadIdx.x / per_tile, tile_step = kParetoMergeThreads / per_tile;
   int mine = 0;
-  for (int t = threadIdx.x; t < tiles; t += kParetoMergeThreads) mine += tile_count[t];
-  const int my_first = mine > 0 ? atomicAdd(&held, mine) : 0;
+  for (int t = first_tile; t < tiles; t += tile_step) mine += tile_count[t];
+  int my_first = of_tile == 0 && mine > 0 ? atomicAdd(&held, mine) : 0;
+  my_first = __shfl(my_first, (threadIdx.x & 63) - of_tile);
   __syncthreads();
   if (held <= kTile) {
     int at = my_first;
-    for (int t = threadIdx.x; t < tiles; t += kParetoMergeThreads) {
+    for (int t = first_tile; t < tiles; t += tile_step) {
       const long long base = (long long)t * kTile;
       const int cnt = tile_count[t];
-      for (int i = 0; i < cnt; ++i, ++at) {
+      for (int i = of_tile; i < cnt; i += per_tile) {
         const Key k = front_keys[base + i];
         const FrontElem e = front_elem(k.makespan, front_peak[base + i], (unsigned)k.idx);
-        lds.front.key[at] = e.key;
-        lds.front.pos[at] = e.pos;
+        lds.front.key[at + i] = e.key;
+        lds.front.pos[at + i] = e.pos;
       }
+      at += cnt;
     }
     __syncthreads();
-    auto load = [&](int i) {
-      return i < held ? FrontElem{lds.front.key[i], lds.front.pos[i]} : FrontElem{kNoEntry, kNoEntry};
-    };
-    const int ia = (threadIdx.x >> 6) * 128 + (threadIdx.x & 63);
-    const FrontElem a = load(ia), b = load(ia + 64);
-    int size = 128;
-    while (size < held) size <<= 1;
-    __syncthreads();
-    const int total = sorted_front(a, b, size, lds.front, [&](int to, const FrontElem& e) {
+    const int total = front_of_held(held, lds.front, [&](int to, const FrontElem& e) {
       if (to >= kmax) return;
       out_idx[to] = (long long)(unsigned)e.pos;
       out_makespan[to] = (long long)(e.key ^ (1ull << 63));
