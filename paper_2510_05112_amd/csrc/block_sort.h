@@ -56,6 +56,17 @@ __device__ __forceinline__ void merge_lanes(SortElem<P>& e, bool up) {
   if (FROM >= 2) sort_stage<2>(e, ((lane & 2) == 0) == up);
   sort_stage<1>(e, ((lane & 1) == 0) == up);
 }
+// one element per lane of a wavefront, ascending
+template <typename P>
+__device__ __forceinline__ void sort_lanes(SortElem<P>& e) {
+  const int lane = threadIdx.x & 63;
+  merge_lanes<1>(e, (lane & 2) == 0);
+  merge_lanes<2>(e, (lane & 4) == 0);
+  merge_lanes<4>(e, (lane & 8) == 0);
+  merge_lanes<8>(e, (lane & 16) == 0);
+  merge_lanes<16>(e, (lane & 32) == 0);
+  merge_lanes<32>(e, true);
+}
 template <typename P>
 __device__ __forceinline__ void merge_pair(SortElem<P>& a, SortElem<P>& b, bool up) {
   if (elem_less(b, a) == up) { const SortElem<P> t = a; a = b; b = t; }

@@ -6,9 +6,12 @@
 // Each workgroup selects the k smallest of its part of the candidates, further launches the k smallest of what those left,
 // the last one with one workgroup (a batch of one part needs one launch).  A workgroup collects candidates in LDS and sorts
 // when the room is used up (block_sort.h); from then on only candidates in front of the k-th of the last sort
-// are collected, of values in random order about k ln(part / first sort) more, so that a part is sorted
-// a few times.  The index is part of the key, so the result is a pure function of the values and does not
-// depend on workgroup scheduling.
+// are collected.  Before the first sort only those are that are not behind a bar which the first four batches give: each
+// wavefront sorts its lanes' smallest, of which its share of k are in front of one, and the last of these is not in front of the
+// k-th of all.  Of values in random order two to three times k get past it, so that a part is mostly sorted once, and all that
+// it holds then: 4,096 candidates 15.6 -> 12.3 us at k = 1 and 18.3 -> 14.2 at k = 128, 65,536 at k = 16 18.0 -> 14.5, 262,144 at k = 64
+// 34.5 -> 27.7 (all launches).  Not where a wavefront's share is more than a quarter of its lanes: the bar then drops too few
+// (share of 64: 262,144 at k = 512 96.0 -> 100.6; of 16: at k = 128 49.1 -> 47.9).
 //
 // The time must not depend on the order of the values: a search that appends better and better candidates hands in falling
 // ones, of which every element displaces the ones before it.  So a part is not walked from front to back but in strides of
@@ -17,8 +20,8 @@
 // any order.  Walked from the front, in at most 64 parts however large the batch, 1,048,576 values took 116 us (random
 // order) and 702 us (falling) at k = 128, 1.2 ms (either) at k = 1024; now 68 and 72 us, 172 and 89 us.
 //
-// What bounds it: the latency of a few dependent steps on one compute unit (load, sort, launch): 20 us for 4,096
-// candidates, 24 for 262,144 at k = 1, 55 at k = 128, 136 for 16,777,216 at k = 128.
+// What bounds it: the latency of a few dependent steps on one compute unit (load, sort, launch): 12 us for 4,096
+// candidates, 15 for 262,144 at k = 1, 48 at k = 128 (back to back; among other work a launch also waits for its code).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -74,6 +77,7 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
     held = min(held, k);
     sorted = true;
   };
+  const bool rough = n > 128u && 4 * k <= threads;
   int turn = 0;               // the counter of this try; those of the next two are 0 or about to be
   const unsigned stride = step * threads, wrap = batches * threads;
   unsigned at = 0;            // the batch's first element
@@ -105,6 +109,27 @@ __device__ bool select_smallest(const TopkSource& src, long long first, unsigned
         e[i].key = (unsigned long long)value ^ (1ull << 63);
         e[i].pos = pos;
       }
+    }
+    if (done == 0 && rough) {
+      // a first bar: the waves' share of k-th smallest lanes' smallest elements, the largest of them.  k elements are not
+      // behind it.
+      SortElem<P> least = none;
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i)
+        if (have[i] && elem_less(e[i], least)) least = e[i];
+      sort_lanes(least);
+      const int waves = threads >> 6, share = (k + waves - 1) / waves;   // (k <= threads: a lane's number)
+      if (lane == share - 1) buf.put(tid >> 6, least);
+      __syncthreads();
+      bar = buf.get(0);
+      for (int w = 1; w < waves; ++w) {
+        const SortElem<P> o = buf.get(w);
+        if (elem_less(bar, o)) bar = o;
+      }
+      // (the element itself is in front of the bar)
+      if constexpr (kPacked) bar.key += bar.key != none.key ? 1ull : 0ull;
+      else bar.pos += bar.pos != none.pos ? 1u : 0u;
+      __syncthreads();
     }
     // the elements of a batch in front of the bar: a place for each in lane 0's `base`, and, a barrier later, their number
     int base = 0;
