@@ -40,24 +40,25 @@ def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
 
 # the list evaluation (order pass and timing pass): plain, with costs per micro-batch (--mb-costs), with link occupancy
 # (--links), with both
-MEASURED = {("cfg4", 65536): counted(1.069e10, 1.055e9, 2.807, "list_evaluation.md")}
+MEASURED = {("cfg4", 65536): counted(1.068e10, 1.058e9, 2.787, "list_evaluation.md")}
 MEASURED_MB = {("cfg4", 65536): counted(None, 1.276e9, 3.437, "list_evaluation.md")}
 MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.736, "list_evaluation.md")}
 MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.589e9, 4.466, "list_evaluation.md")}
 # the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
-MEASURED_SYNC = {("sync4", 65536): counted(None, 2.380e8, 0.916, "list_evaluation.md")}
+MEASURED_SYNC = {("sync4", 65536): counted(None, 2.492e8, 0.864, "list_evaluation.md")}
 MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}
-# the copy engine (--config 5 --copy-engine 4: the slot kernel; up to a depth of 3: two passes)
-MEASURED_COPY = {("cfg5", 131072): counted(None, 1.850e9, 5.120, "eval_sync_kernel.md")}
-MEASURED_COPY_LISTS = {("cfg5", 131072): counted(None, 1.523e9, 4.438, "list_evaluation.md")}
+# the copy engine (--config 5 --copy-engine DEPTH), two passes; of the depths that share a form the one that was profiled
+MEASURED_COPY = {3: {("cfg5", 131072): counted(None, 1.171e9, 2.698, "list_evaluation.md")},
+                 4: {("cfg5", 131072): counted(None, 1.265e9, 2.939, "list_evaluation.md")},
+                 7: {("cfg5", 131072): counted(None, 1.562e9, 3.290, "list_evaluation.md")}}
 # the sliding pass (--mode wslide), all of its kernels, and without its lists (--no-lists): one kernel
-MEASURED_WSLIDE = {("cfg4", 65536): counted(3.79e10, 4.990e9, 13.18, "wslide_kernel_cfg4.md")}
+MEASURED_WSLIDE = {("cfg4", 65536): counted(3.73e10, 4.226e9, 11.10, "wslide_kernel_cfg4.md")}
 MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.814e9, 10.77, "wslide_kernel_cfg4.md")}
 # the generator (--mode generate; traffic: WRITE_SIZE x 1024 plus the parameter sets read), generator and evaluator in one
 # kernel (--mode search --fused), the same with the sliding pass in it (--slide)
 MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.763e9, 9.23, "generate_kernel_cfg4.md")}
 MEASURED_FUSED = {("cfg4", 65536): counted(None, 6.020e9, 10.14, "generate_kernel_cfg4.md")}
-MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 7.327e9, 11.66, "generate_kernel_cfg4.md")}
+MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 6.836e9, 11.23, "generate_kernel_cfg4.md")}
 
 
 def rooflines(alg_bytes, kernel_ms, kernel_name, figures, units=None):
@@ -617,13 +618,11 @@ def main() -> int:
     # algorithmic bytes of one evaluation launch: 2 B per op word actually needed, plus the
     # per-candidate outputs (makespan 8 + idle 8D + peak 4D + flags 1)
     alg_bytes = 2 * n_ops + C * (8 + 8 * D + 4 * D + 1)
-    copy_on_lists = 0 < args.copy_engine <= 3   # (batches of a configuration's size)
-    figures = ({} if args.table_kernel else (MEASURED_COPY_LISTS if copy_on_lists else MEASURED_COPY) if args.copy_engine else MEASURED_BOTH if args.links and args.mb_costs
+    figures = ({} if args.table_kernel else MEASURED_COPY.get(args.copy_engine, {}) if args.copy_engine else MEASURED_BOTH if args.links and args.mb_costs
                else MEASURED_LINKS if args.links else MEASURED_MB if args.mb_costs else MEASURED)
     roofline, issue = rooflines(alg_bytes, eval_ms,
                                 "fpsched evaluation kernel, table form" + (" (eval_sync_kernel, copy-engine form)" if args.copy_engine else " (eval_general_kernel)")
-                                if args.table_kernel else "fpsched evaluation kernel (eval_slot_kernel, copy-engine mode)" if args.copy_engine and not copy_on_lists
-                                else "fpsched evaluation, two passes (check_rows_kernel + time_lists_kernel)",
+                                if args.table_kernel else "fpsched evaluation, two passes (check_rows_kernel + time_lists_kernel)",
                                 figures.get((f"cfg{spec.index}", C)), units=n_ops)
     flags = res["flags"].cpu().numpy()
     makespan = res["makespan"].cpu().numpy()

@@ -236,7 +236,7 @@ int fpsched_problem_set_sync(fpsched_problem *p, const int32_t *group, int32_t n
  * handle keeps what it had.  Synchronous; allocates two tables of device memory at most; works on a
  * host-only handle (validation only).  FPSCHED_KERNEL_SLOTS and _GENERAL both have a form of this
  * model, the former for problems whose times stay below 2^24 and latencies below 2^16: the two passes of the
- * plain model up to a depth of 3, or one kernel (deeper engines, and batches that it finishes sooner); it runs
+ * plain model, or one kernel (batches that it finishes sooner); it runs
  * where it fits (fpsched_problem_select_kernel chooses as for the plain
  * model), and then fpsched_evaluate needs its workspace as in the plain model. */
 #define FPSCHED_MAX_COPY_DEPTH 7

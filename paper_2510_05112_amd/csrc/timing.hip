@@ -75,7 +75,7 @@
 // items (a W word is an op of the device's own without a cost), of which it leaves the low sixteen bits of each op's start
 // time, the ops that waited 2^16 time units or more, and where the lists stop.  A start time takes the place of the op's
 // word in the ring and leaves eight at a time when the next piece lands there, so that a step has four vector instructions
-// more and no store.  32,768 candidates of 16 devices, 64 micro-batches, 2 chunks: 0.15 ms (order pass) + 0.59 ms; 1.46 ms
+// more and no store.  32,768 candidates of 16 devices, 64 micro-batches, 2 chunks: 0.15 ms (order pass) + 0.51 ms; 1.46 ms
 // as a form of the slot kernel, with all devices in every round.
 //
 // Start rule (paper Section 5.1 "Data dependency"; estimator sketch after Section 6): start = max(device free, finish
