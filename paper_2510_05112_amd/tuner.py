@@ -182,7 +182,9 @@ def tune(handle, problem, circular: bool, k: int = 8, inflight_options=None, for
         main, side = torch.cuda.current_stream(handle.device), torch.cuda.Stream(handle.device)
         ready = main.record_event()
         try:
-            handle.generate_evaluate(d_pol, d_inf, results=half(n), slide=True)
+            # (both forms' memory is held to the end: given back earlier, one's would be the other's while both run)
+            main_workspace = handle.alloc_workspace(n, 0)
+            main_out = handle.generate_evaluate(d_pol, d_inf, results=half(n), workspace=main_workspace, slide=True)
             side.wait_event(ready)
             side_workspace = handle.alloc_workspace(n, 0)
             side_out = handle.generate_evaluate(d_pol, d_inf, results=half(0), workspace=side_workspace, stream=side)
