@@ -108,8 +108,9 @@ __device__ __forceinline__ int drop_dominated(const FrontElem& a, const FrontEle
   const bool have_a = a.pos != kNoEntry, have_b = b.pos != kNoEntry;
   const int class_a = have_a ? peak_class((unsigned)(a.pos >> 32)) : 0, class_b = have_b ? peak_class((unsigned)(b.pos >> 32)) : 0;
   // (a look first: lanes at one address take turns)
-  if (have_a && a.key < *(volatile unsigned long long*)&fastest[class_a]) atomicMin(&fastest[class_a], a.key);
-  if (have_b && b.key < *(volatile unsigned long long*)&fastest[class_b]) atomicMin(&fastest[class_b], b.key);
+  auto fastest_yet = [&](int c) { return __hip_atomic_load(&fastest[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+  if (have_a && a.key < fastest_yet(class_a)) atomicMin(&fastest[class_a], a.key);
+  if (have_b && b.key < fastest_yet(class_b)) atomicMin(&fastest[class_b], b.key);
   __syncthreads();
   if (have_a && a.key == fastest[class_a]) atomicMin(&best[class_a], a.pos);
   if (have_b && b.key == fastest[class_b]) atomicMin(&best[class_b], b.pos);
