@@ -251,7 +251,7 @@ CheckKernel check_kernel_of(int vbits, bool no_w, bool shared) {
               : (shared ? check_kernel_of<false, true>(vbits) : check_kernel_of<false, false>(vbits));
 }
 
-using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, float, StartTimes);
+using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long long*, long long*, int*, unsigned char*, unsigned long long*, int, unsigned, StartTimes);
 template <bool DEG2>
 TimeKernel time_kernel_of(const ListTables& T, bool wide) {
   const bool links = T.link_words > 0;
@@ -1219,7 +1219,9 @@ static int draws_at_a_time(const fpsched_problem* p, int32_t stride_words, int c
 // a third / half / three quarters / all of the share: 262,144 of 16 x 64 x 2 2659 / 2459 / 2458 / 2487 / 2484 us; 60,000 of
 // 24 x 40 x 2 - / 745 / 747 / 724 / 729; 65,536 with synchronisation 887 / 862 / 865 / 919 / 946; 65,536 of 32 x 128 x 2 2610 / 2613 /
 // 2714 / 2713 / 2668.
-static float drawn_share(const fpsched_problem* p, int32_t stride_words) { return (int64_t)p->D * stride_words <= 16384 ? 0.5f : 0.f; }
+static uint32_t drawn_share(const fpsched_problem* p, int32_t stride_words, int64_t waves) {   // (times 2^32)
+  return (int64_t)p->D * stride_words <= 16384 ? (uint32_t)(((1ll << 31) + waves - 1) / waves) : 0u;
+}
 
 // the two-pass list evaluation: the order pass over all rows, then the timing pass on a persistent grid
 // (variant: its tables and launch shape under link occupancy or costs per micro-batch; null: the plain model; starts: what
@@ -1262,7 +1264,7 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(T, variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
-                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), drawn_share(p, stride_words), starts ? *starts : StartTimes{});
+                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), drawn_share(p, stride_words, time_blocks * tw), starts ? *starts : StartTimes{});
   return check_hip(hipGetLastError());
 }
 

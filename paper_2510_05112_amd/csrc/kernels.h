@@ -99,7 +99,7 @@ template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int C
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block,
-                                  float draw_share, StartTimes starts);
+                                  unsigned draw_share, StartTimes starts);
 
 // counter[0] = value, counter[1] = value2
 __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2 = 0);

@@ -367,7 +367,7 @@ template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int C
 __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : 4))) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
-    unsigned long long* __restrict__ next_candidate, int draw_block, float draw_share, StartTimes starts) {
+    unsigned long long* __restrict__ next_candidate, int draw_block, unsigned draw_share, StartTimes starts) {
   static_assert(!WIDE || !(LINKS || MB || SYNC || COPY != 0), "these forms have times of 24 bits");
   static_assert(!COPY || (DEG2 && !LINKS && !MB && !SYNC && !TIMES), "rows that follow others");
   static_assert(!SYNC || (DEG2 && !LINKS && !MB), "rows that follow others");
@@ -485,16 +485,14 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   bool any_stuck = false;           // wave-uniform: the list of some device stops at an op that may not issue
   unsigned long long idle_lanes = ~0ull;
   bool first_draw = true;
-  unsigned long long pool_next = 0ull, pool_end = 0ull;
-  // The counter may still have candidates to hand out.  (Where there are no more of them than segments nothing is ever drawn, and
-  // a segment that ends changes nothing for the others: a draw that comes back empty costs the wavefront some 4,500 clocks, which
+  // Drawn from the counter and not handed to a segment: [pool_next, pool_end); behind a draw that reached past the last candidate
+  // pool_end is there too, and nothing is drawn any more.  (Where there are no more candidates than segments nothing is ever drawn,
+  // and a segment that ends changes nothing for the others: a draw that comes back empty costs the wavefront some 4,500 clocks, which
   // were 8 to 13 % of the pass on such batches.)
-  // Drawn at a time: draw_share of this wavefront's share of those that were left at its last draw, up to one a segment, and
-  // draw_block at least.
-  const unsigned n_waves = gridDim.x * (blockDim.x >> 6);
-  unsigned long long handed_out = (unsigned long long)n_waves * (unsigned)cpw;   // as far as this wavefront knows
-  const float share = draw_share / (float)n_waves;
-  bool draws = handed_out < (unsigned long long)n_cand;
+  // Drawn at a time: draw_share / 2^32 of the candidates that were left at this wavefront's last draw, up to one a segment, and
+  // draw_block at least.  All of it is worked out on the scalar unit: the SYNC form has no vector register left (with what every
+  // lane agrees on in vector registers it kept four in memory; 65,536 candidates of 12 devices, the whole evaluation: 850 and 837 us).
+  unsigned long long pool_next = (unsigned long long)gridDim.x * (blockDim.x >> 6) * (unsigned)cpw, pool_end = pool_next;
 
   // fetch the row of the word that comes under the cursor; what follows from the row is worked out when the device's
   // next step begins, so that the other half's step covers the wait for it
@@ -836,24 +834,19 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       const unsigned long long want = __ballot(fresh && !first_draw && pair == 0 && lane_ok);
       unsigned long long from_pool = 0ull;
       if (want != 0ull) {
-        const int n_want = __popcll(want);
-        const int have = (int)(pool_end - pool_next);
-        const bool drew = n_want > have && draws;
-        unsigned long long new_base = (unsigned long long)n_cand;
-        int amount = 0;
-        if (drew) {
-          amount = max(max(draw_block, n_want - have), (int)fminf((float)((unsigned long long)n_cand - handed_out) * share, (float)cpw));
-          if (lane == 0) new_base = atomicAdd(next_candidate, (unsigned long long)amount);
-          new_base = (unsigned long long)of_first_lane((long long)new_base);
-          handed_out = new_base + (unsigned)amount;
-          draws = handed_out < (unsigned long long)n_cand;
-        }
+        const int n_want = __popcll(want), have = (int)(pool_end - pool_next), lacking = n_want - have;
         const int rank = __popcll(want & ((1ull << lane) - 1ull));   // among the asking segments
-        from_pool = rank < have ? pool_next + (unsigned)rank : (drew ? new_base + (unsigned)(rank - have) : (unsigned long long)n_cand);
-        if (drew) {
-          pool_next = new_base + (unsigned)(n_want - have);
-          pool_end = new_base + (unsigned)amount;
+        if (lacking > 0 && pool_end < (unsigned long long)n_cand) {
+          const unsigned left = (unsigned)min((unsigned long long)n_cand - pool_end, 0xffffffffull);
+          const int amount = max(max(draw_block, lacking), min((int)__umulhi(left, draw_share), cpw));
+          unsigned long long base = 0ull;
+          if (lane == 0) base = atomicAdd(next_candidate, (unsigned long long)amount);
+          base = (unsigned long long)of_first_lane((long long)base);
+          from_pool = (rank < have ? pool_next : base - (unsigned)have) + (unsigned)rank;
+          pool_next = base + (unsigned)lacking;
+          pool_end = base + (unsigned)amount;
         } else {
+          from_pool = rank < have ? pool_next + (unsigned)rank : (unsigned long long)n_cand;
           pool_next += (unsigned)min(n_want, have);
         }
       }
@@ -945,7 +938,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     const unsigned long long x = moved_even | moved_odd | idle_lanes;
     if (((x - base_bits) & ~x & high_bits) != 0ull) {
       const bool ended = running && !priming && !any_in_segment(x);
-      const bool more = draws || (pool_next < pool_end && pool_next < (unsigned long long)n_cand);
+      const bool more = pool_next < (unsigned long long)n_cand;   // (of the pool or the counter)
       // (a device that a lane does not have counts as one whose list is exhausted)
       const unsigned even_issued = word_at(even.pos) - 1u, odd_issued = has_odd ? word_at(odd.pos) - 1u : 0u;
       const unsigned both = even.info | odd.info;
@@ -1010,7 +1003,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
 
 #define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY)                                                        \
   template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY>(ListTables, const uint16_t*, long long, int, long long*, \
-                                                                    long long*, int*, unsigned char*, unsigned long long*, int, float, StartTimes);
+                                                                    long long*, int*, unsigned char*, unsigned long long*, int, unsigned, StartTimes);
 #define FPSCHED_INSTANTIATE_MODELS(DEG2)                            \
   FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false, 0)   \
   FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false, 0)    \
