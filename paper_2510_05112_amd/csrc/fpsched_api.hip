@@ -1214,13 +1214,21 @@ static int draws_at_a_time(const fpsched_problem* p, int32_t stride_words, int c
 }
 
 // ... and the timing pass, while many are left: a draw is a wait of some 4,500 clocks for a wavefront, whose segments need
-// one every sixth of their top-ups or so; so half of the wavefront's share of what is left is drawn at a time, up to one a segment.
-// Candidates of more than 16 K words are worth the wait and better drawn one by one.  Whole evaluation, one draw per 12 K words /
-// a third / half / three quarters / all of the share: 262,144 of 16 x 64 x 2 2659 / 2459 / 2458 / 2487 / 2484 us; 60,000 of
-// 24 x 40 x 2 - / 745 / 747 / 724 / 729; 65,536 with synchronisation 887 / 862 / 865 / 919 / 946; 65,536 of 32 x 128 x 2 2610 / 2613 /
-// 2714 / 2713 / 2668.
-static uint32_t drawn_share(const fpsched_problem* p, int32_t stride_words, int64_t waves) {   // (times 2^32)
-  return (int64_t)p->D * stride_words <= 16384 ? (uint32_t)(((1ll << 31) + waves - 1) / waves) : 0u;
+// one every sixth of their top-ups or so; so a part of the wavefront's share of what is left is drawn at a time, up to one a segment:
+// half of it, or a quarter where a step also asks for link words and has no branches (such a step waits for more than the draw
+// gives back, and a wavefront that has drawn more than its equals ends later).  Candidates of more than 16 K words are worth the wait
+// and better drawn one by one.  Whole evaluation against one draw per 12 K words, a quarter / half / three quarters of the share,
+// mean over batches of 1.3 to 9 candidates a segment, 14 problems of 2 to 32 devices, 20 to 64 micro-batches:
+//   plain model 0.96 to 1.00 / 0.93 to 1.005 / 0.91 to 1.003 (16 x 64 x 2 0.980 / 0.958 / 0.952; 262,144 of it 2605, 2408, 2395,
+//   2412 us); at worst, 1.3 a segment of 2 x 64 x 1, 1.03 / 1.06 / 1.05;
+//   links, with and without costs, no second edges 0.993 to 1.003 / 0.987 to 1.026 / 0.98 to 1.035 (configuration 3 3004, 2969, 2996, 3028
+//   us, with costs 3353, 3328, 3381, 3415; at worst 1.02 / 1.08 / 1.09), with second edges 0.98 to 0.99 / 0.98 to 0.99 / 0.97 to 0.99;
+//   costs per micro-batch 0.975 to 1.001 / 0.955 to 1.013 (12 x 40 x 4; 11 x 45 x 3 1.006) / 0.94 to 1.02;
+//   synchronisation 1.00 / 0.995 to 1.0 / 1.0, copy engine 0.99 to 1.00 / 0.99 to 1.00 / 0.98 to 1.00.
+// 65,536 of 32 x 128 x 2: 2597, 2586, 2663, 2661 us, under links 3657, 3674, 3771, 3839.
+static uint32_t drawn_share(const fpsched_problem* p, const ListTables& T, bool deg2, int32_t stride_words, int64_t waves) {   // (times 2^32)
+  const int64_t part = (int64_t)p->D * stride_words > 16384 ? 0 : 1ll << (T.link_words > 0 && !deg2 ? 30 : 31);
+  return (uint32_t)((part + waves - 1) / waves);
 }
 
 // the two-pass list evaluation: the order pass over all rows, then the timing pass on a persistent grid
@@ -1261,10 +1269,11 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
                      (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
-  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(T, variant ? variant->deg2 : p->lists_deg2, p->lists_wide && !variant), dim3((unsigned)time_blocks),
+  const bool deg2 = variant ? variant->deg2 : p->lists_deg2;
+  hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(T, deg2, p->lists_wide && !variant), dim3((unsigned)time_blocks),
                      dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
-                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), drawn_share(p, stride_words, time_blocks * tw), starts ? *starts : StartTimes{});
+                     out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), drawn_share(p, T, deg2, stride_words, time_blocks * tw), starts ? *starts : StartTimes{});
   return check_hip(hipGetLastError());
 }
 

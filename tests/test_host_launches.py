@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import paper_2510_05112_amd as fp
+import workloads
 from workloads.problem import F, L, O, chain_problem
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -44,6 +45,8 @@ class Device:
     def launched(self, rc=0, what=0):
         assert rc == what, rc
         names = [self.stub.stub_launched(i).decode() for i in range(self.stub.stub_launches())]
+        self.waves = [self.stub.stub_grid(i) * self.stub.stub_block(i) // 64 for i in range(len(names))]
+        self.words = [self.stub.stub_word(i) & 0xffffffff for i in range(len(names))]
         self.stub.stub_reset()
         return [re.search(r"\d([a-z_]+_kernel)", n).group(1) for n in names]
 
@@ -145,3 +148,37 @@ def no_memory_for_some_table(dev):
 @pytest.mark.parametrize("what", ["no_memory_for_copy_tables", "no_memory_for_some_table"])
 def test_no_memory_for_a_faster_form(what, stub):
     run(stub, what)
+
+
+DRAW_SHARE = 10   # (its place among the timing pass's arguments)
+
+
+def share_of_a_draw(dev):
+    dev.stub.stub_watch(b"time_lists_kernel", DRAW_SHARE)
+
+    def share(prob, stride, set_model=lambda h: None, n=1 << 17):
+        h = fp.Problem(prob, stride, device=0)
+        set_model(h)
+        assert dev.evaluate(h, stride, n)[-2:] == TWO_PASSES
+        h.close()
+        got = dev.words[-1] * dev.waves[-1] / 2**32   # (of a wavefront, rounded up)
+        return round(got, 3) if got < 1 else got
+
+    def links(h):
+        h.set_link_occupancy(True)
+    chain = chain_problem(8, 64, v=2, f=3, b=4, w=2, comm=1)
+    towers = workloads.config(5, 1).problem
+
+    def with_costs(prob):
+        return lambda h: h.set_microbatch_costs(workloads.microbatch_costs(prob))
+    both = {name: (lambda h, prob=prob: (with_costs(prob)(h), links(h))) for name, prob in (("chain", chain), ("towers", towers))}
+    assert share(chain, 384) == share(chain, 384, with_costs(chain)) == 0.5
+    assert share(chain, 384, links) == share(chain, 384, both["chain"]) == 0.25
+    assert share(towers, 256) == share(towers, 256, links) == share(towers, 256, both["towers"]) == 0.5
+    # the longest candidates that more than one of are drawn at a time
+    assert (share(chain, 2048), share(chain, 2056)) == (0.5, 0)
+    assert (share(chain, 2048, links), share(chain, 2056, links)) == (0.25, 0)
+
+
+def test_share_of_a_draw(stub):
+    run(stub, "share_of_a_draw")
