@@ -114,11 +114,12 @@ def _grid_arrays(types, n_devices, inflight_options, empty=np.empty):
     other in one array of empty(size, int32)."""
     limits = np.asarray([np.asarray(x, np.int32) for x in inflight_options], np.int32)
     rows = np.asarray([t.policy_row() for t in types], np.int32)
-    n, S = len(rows) * len(limits), limits.shape[1]
-    both = empty(n * (n_devices * 8 + S), np.int32)
-    pol, inf = both[:n * n_devices * 8].reshape(n, n_devices, 8), both[n * n_devices * 8:].reshape(n, S)
-    pol.reshape(len(rows), len(limits), n_devices, 8)[:] = rows[:, None, None, :]
-    inf.reshape(len(rows), len(limits), S)[:] = limits
+    n, of_policies = len(rows) * len(limits), len(rows) * len(limits) * n_devices * 8
+    limits = np.atleast_2d(limits)   # (no option at all: an empty grid)
+    both = empty(of_policies + len(rows) * limits.size, np.int32)
+    pol, inf = both[:of_policies].reshape(n, n_devices, 8), both[of_policies:].reshape(len(rows) * len(limits), limits.shape[1])
+    pol.reshape(len(rows), n // len(rows), n_devices, 8)[:] = rows[:, None, None, :]
+    inf.reshape(len(rows), *limits.shape)[:] = limits
     return pol, inf
 
 

@@ -70,6 +70,21 @@ def test_grid_follows_the_papers_rules():
     assert np.all(inf >= 1)
 
 
+@pytest.mark.parametrize("options", [[], np.zeros((0, 8)), [np.arange(8)], [[3] * 8, np.full(8, 5, np.int64)], np.ones((3, 8))])
+def test_grid_arrays_are_every_type_times_every_option(options):
+    """No option at all is an empty grid, as a repeat of every type's row and a tile of the options make it."""
+    prob = chain(4, 2, 6, "circular")
+    types = tuner.schedule_types(4, True)
+    labels, pol, inf = tuner.grid(prob, True, options)
+    limits = np.asarray([np.asarray(x, np.int32) for x in options], np.int32)
+    rows = np.repeat([t.policy_row() for t in types], len(limits), axis=0)
+    assert len(labels) == len(pol) == len(rows)
+    assert pol.dtype == inf.dtype == np.int32 and pol.flags.c_contiguous and inf.flags.c_contiguous
+    assert pol.shape == (len(rows), 4, 8) and np.array_equal(pol, np.repeat(rows[:, None, :], 4, axis=1))
+    assert np.array_equal(inf, np.tile(limits, (len(types), 1)))
+
+
+
 @pytest.mark.gpu
 def test_gpu_search_with_sliding_and_bidirectional_placement_matches_the_oracles():
     import paper_2510_05112_amd as fp
