@@ -2470,14 +2470,16 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   }
   // pass 2: every row places its W items on its own, by a lane, whose steps wait for each other, or by a wavefront, of which
   // a compute unit has few: so where rows are few, and the more so the longer they are.  Both passes, a lane / a wavefront per
-  // row, at 12,288 and 16,384 rows, 26 shapes: below 128 items 0.95 (20 x 10 x 1) to 1.05 and 0.88 to 0.98, four devices aside
-  // (4 x 16 x 1: 1.23 and 1.12, at 24,576 0.99); of 180 to 384 items 1.07 (30 x 60 x 1) to 1.74 and 0.98 (16 x 64 x 2, 615 and
-  // 628 us) to 1.65, at 24,576 0.85 to 1.04 (2 x 60 x 1 aside: 1.56); of 450 items and more 1.2 to 1.87 and 1.13 to 1.75, at 24,576 1.02 (20 x 50 x 3) to 1.51, at 32,768 0.89 to 1.34
-  // (32 x 128 x 2: 2352 and 2179 us; 4 x 200 x 4: 4139 and 3960).
+  // row, 28 shapes, at 8,192, 12,288, 16,384 and 24,576 rows:
+  //   up to 384 items 1.01 (24 x 24 x 2, 30 x 60 x 1) to 1.20 (8 x 32 x 2), 0.91 (20 x 10 x 1) to 1.09 (16 x 64 x 2 545 and 541 us, 16 x 8 x 2
+  //   93 and 95), 0.84 to 1.03 (16 x 64 x 2 546 and 598), 0.74 to 0.92; on up to four devices 1.17 to 1.67, 1.10 to 1.58, 0.99
+  //   (4 x 16 x 1) to 1.51 (2 x 60 x 1), 0.88 to 1.41;
+  //   450 items and more 1.23 to 1.89, 1.10 to 1.72, 1.05 (20 x 50 x 3) to 1.54, 0.94 (20 x 50 x 3; 32 x 50 x 3 1.00) to 1.35 (32 x 128 x
+  //   2 2104 and 1851 us), at 32,768 0.82 to 1.16 (32 x 128 x 2 1.02).
   const int stash = (int)std::min<int64_t>((int64_t)max_chunks_of(p) * p->m, stride_words);
   const int64_t rows_shared = place_rows_bytes + 4ll * 4 * kMaxDevices, rows_wave = slide_rows_wave_bytes(stride_out_words, stash);
   const int64_t rows_waves = std::min<int64_t>({(p->max_lds - rows_shared) / rows_wave, kSlideThreads / 64, p->D});
-  const int64_t items = 3ll * max_chunks_of(p) * p->m, few_rows = items >= 448 ? 24576 : items >= 128 || p->D <= 4 ? 16384 : 12288;
+  const int64_t items = 3ll * max_chunks_of(p) * p->m, few_rows = items >= 448 ? 24576 : p->D <= 4 ? 16384 : 12288;
   if (n_cand * p->D <= few_rows && rows_waves >= std::min(p->D, 4)) {
     hipLaunchKernelGGL(wslide_place_rows_kernel, dim3((unsigned)n_cand), dim3(64 * (unsigned)rows_waves),
                        (size_t)(rows_shared + rows_waves * rows_wave), st, p->stab, d_ops, (int)stride_words, starts, escapes,

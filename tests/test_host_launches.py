@@ -53,9 +53,9 @@ class Device:
     def evaluate(self, h, stride, n=1, what=0):
         return self.launched(self.lib.fpsched_evaluate(h._h, 4096, n, stride, self.results, 4096, 1 << 20, None), what)
 
-    def wslide(self, h, stride):
-        size = self.lib.fpsched_wslide_workspace_bytes(h._h, 1, stride)
-        return self.launched(self.lib.fpsched_wslide(h._h, 4096, 1, stride, 4096, 64, self.results, 4096, size, None))
+    def wslide(self, h, stride, n=1, stride_out=64):
+        size = self.lib.fpsched_wslide_workspace_bytes(h._h, n, stride)
+        return self.launched(self.lib.fpsched_wslide(h._h, 4096, n, stride, 4096, stride_out, self.results, 4096, size, None))
 
 
 LONGEST = (1 << 23) - 32   # rows that the timing pass has positions for
@@ -182,3 +182,24 @@ def share_of_a_draw(dev):
 
 def test_share_of_a_draw(stub):
     run(stub, "share_of_a_draw")
+
+
+def placement_by_rows(dev):
+    def placed_by(D, m, v, rows):
+        prob = chain_problem(D, m, v=v, f=2, b=3, w=1, comm=1)
+        stride = -(-3 * m * v // 8) * 8
+        h = fp.Problem(prob, stride, device=0)
+        got = dev.wslide(h, stride, rows // D, stride)
+        h.close()
+        assert got[-3:-1] == TWO_PASSES
+        return {"wslide_place_rows_kernel": "wavefront", "wslide_place_kernel": "lane"}[got[-1]]
+    # a row's items: up to 447 (on up to four devices, and on more), 448 and more
+    for shape, most in (((4, 4, 1), 16384), ((4, 74, 2), 16384), ((5, 4, 1), 12288), ((8, 16, 1), 12288), ((16, 64, 2), 12288), ((32, 149, 1), 12288),
+                        ((16, 75, 2), 24576), ((4, 75, 2), 24576), ((32, 128, 2), 24576)):
+        D = shape[0]
+        assert placed_by(*shape, most // D * D) == "wavefront", shape
+        assert placed_by(*shape, most // D * D + D) == "lane", shape
+
+
+def test_placement_by_rows(stub):
+    run(stub, "placement_by_rows")
