@@ -123,64 +123,48 @@ def test_configuration_five_reduced_batch_and_switching():
     free.close()
 
 
-def forms_of(said):
-    """What set_copy_engine printed: (the two passes are there, candidates that the one kernel has side by side)"""
+def resident_of(prob, stride, depth, capfd):
+    """Candidates that the one kernel has side by side; more of them go to the two passes, which are there."""
     import re
-    shape = re.search(r"slot kernel, copy engine: (\d+) x (\d+) wavefronts per compute unit, (\d+) candidates", said)
-    groups, waves, candidates = map(int, shape.groups())
-    return "list evaluation, copy engine" in said, groups * waves * candidates * torch.cuda.get_device_properties(0).multi_processor_count
-
-
-def takes_two_passes(prob, n, resident):
-    """The rule of fpsched_evaluate for depths that the two passes have."""
-    chunks = int(np.bincount(prob.stage_device).max())
-    long_rows = chunks * prob.n_microbatches * (3 if prob.has_w else 2) >= 96
-    if n > resident:
-        return long_rows or n <= 4 * resident
-    if chunks > 1:
-        return prob.n_devices > (2 if long_rows else 3)
-    return prob.n_devices > 3 and (long_rows or prob.n_devices <= 8) and 2 * n <= resident
-
-
-def few_and_many(prob, words, depth, capfd):
-    """The batch as it is and filled up to where the one kernel would take another turn: (two passes there, copies, both sizes run in
-    which form)"""
     capfd.readouterr()
-    h = fp.Problem(prob, words.shape[2], device=0)
+    h = fp.Problem(prob, stride, device=0)
     h.set_copy_engine(depth)
     h.close()
-    there, resident = forms_of(capfd.readouterr().err)
-    copies = resident // words.shape[0] + 1
-    return there, copies, [there and takes_two_passes(prob, n, resident) for n in (words.shape[0], copies * words.shape[0])]
+    said = capfd.readouterr().err
+    assert f"list evaluation, {'deep ' if depth > 3 else ''}copy engine" in said
+    groups, waves, candidates = map(int, re.search(r"slot kernel, copy engine: (\d+) x (\d+) wavefronts per compute unit, (\d+) candidates", said).groups())
+    return groups * waves * candidates * torch.cuda.get_device_properties(0).multi_processor_count
 
 
-@pytest.mark.parametrize("depth", [1, 2, 3, 4])
-def test_two_pass_and_one_kernel_forms(depth, monkeypatch, capfd):
-    """Both forms at the depths that the two passes take and the first one beyond, short and long transfers, batches on either
-    side of the lines between the forms."""
-    monkeypatch.setenv("FPSCHED_VERBOSE", "1")
-    rng = np.random.default_rng(depth)
+def form_problems():
     long_rows = chain_problem(7, 33, v=1, f=2, b=3, w=1, comm=1)
     long_rows.dur[O], long_rows.dur[L] = 3, 2
     interleaved = [chain_problem(d, 5, v=2, f=3, b=4, w=2, comm=1) for d in (2, 4)]
     for prob in interleaved:
         prob.dur[O], prob.dur[L] = 2, 5
-    seen = set()
-    for i, prob in enumerate(transfer_problems() + [long_rows] + interleaved):
+    return transfer_problems() + [long_rows] + interleaved
+
+
+FORM_LISTS = 48   # lists of a problem; and so many copies of them that the one kernel would take another turn
+
+
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+def test_two_pass_and_one_kernel_forms(depth, monkeypatch, capfd):
+    """Depths with the fewest registers and the first one beyond, short and long transfers, batches on either side of the
+    lines between the forms (which form each of them is launched as: test_host_launches.py)."""
+    monkeypatch.setenv("FPSCHED_VERBOSE", "1")
+    rng = np.random.default_rng(depth)
+    for i, prob in enumerate(form_problems()):
         lists = []
-        for t in range(24):
+        for t in range(FORM_LISTS // 2):
             base = random_valid_lists(prob, rng, 0.3 * (t % 2), 0.3 + 0.3 * ((t // 2) % 2))
             lists += [base, perturb(base, rng, 1 + t % 3)]
         words = batch_from_lists(lists)
-        there, copies, forms = few_and_many(prob, words, depth, capfd)
-        assert there == (depth < 4)
-        for times, two in zip((1, copies), forms):
-            ref = oracle.evaluate_copy(prob, words, depth=depth, threads=8)
+        ref = oracle.evaluate_copy(prob, words, depth=depth, threads=8)
+        for times in (1, resident_of(prob, words.shape[2], depth, capfd) // len(words) + 1):
             out, _ = gpu_copy(prob, np.tile(words, (times, 1, 1)), depth)
             many = {name: np.tile(a, (times,) + (1,) * (a.ndim - 1)) for name, a in ref.items()}
-            assert_same(out, many, f"problem {i}, {times} times, {'two passes' if two else 'one kernel'}")
-            seen.add((times > 1, two))
-    assert seen == ({(False, False), (False, True), (True, True)} if depth < 4 else {(False, False), (True, False)})
+            assert_same(out, many, f"problem {i}, {times} times, depth {depth}")
 
 
 @pytest.mark.parametrize("seed", range(6))
@@ -196,8 +180,7 @@ def test_two_passes_on_random_problems(seed, monkeypatch, capfd):
             lists += [base, perturb(base, rng, 1 + t % 3)]
         words = batch_from_lists(lists)
         depth = int(rng.integers(1, 4))
-        _, copies, forms = few_and_many(prob, words, depth, capfd)
-        assert forms[1]
+        copies = resident_of(prob, words.shape[2], depth, capfd) // len(words) + 1
         ref = oracle.evaluate_copy(prob, words, depth=depth, threads=8)
         many = {name: np.tile(a, (copies,) + (1,) * (a.ndim - 1)) for name, a in ref.items()}
         assert_same(gpu_copy(prob, np.tile(words, (copies, 1, 1)), depth)[0], many, f"{seed} {i} depth {depth}")

@@ -1,6 +1,7 @@
 """The order pass where four lanes read each other's rows (more than eight wavefronts of rows per compute unit, rows of 64
 words and more): rows that end in every part of a request, batches whose last rows leave lanes of the four without one,
-one to four stages per device, with and without W items, blocks that are drawn."""
+one to four stages per device, with and without W items, blocks that are drawn.  (That these batches are launched as that form:
+test_host_launches.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -14,23 +15,33 @@ from workloads.problem import chain_problem
 pytestmark = pytest.mark.gpu
 
 
+PADDINGS = (0, 8, 16, 24)
+EVALUATED = ((1, 1, 22, 140001), (3, 1, 27, 140002), (5, 2, 11, 140005), (7, 4, 6, 140007), (2, 1, 40, 140002))   # devices, stages per device, micro-batches, rows
+WITHOUT_W = ((3, 1, 27, 140002), (5, 2, 11, 140005), (7, 4, 6, 140007))
+DRAWN = (9, 2, 12, 64 * 3072 * 10)
+
+
+def problem_of(D, v, m, padding):
+    """... and its rows' words"""
+    return chain_problem(D, m, v=v, f=3, b=5, w=2, comm=1, mem_cap=max(2, D)), -(-3 * v * m // 8) * 8 + padding
+
+
 def batch(D, v, m, padding, n_rows, seed):
-    prob = chain_problem(D, m, v=v, f=3, b=5, w=2, comm=1, mem_cap=max(2, D))
-    longest = -(-3 * v * m // 8) * 8
-    spec = workloads.Spec(0, prob, 200, longest + padding, 8, cap_units=max(2, D), seed=seed, deadlock_per_mille=60)
+    prob, stride = problem_of(D, v, m, padding)
+    spec = workloads.Spec(0, prob, 200, stride, 8, cap_units=max(2, D), seed=seed, deadlock_per_mille=60)
     base = workloads.generate(spec, threads=8)
     return prob, np.tile(base, (-(-n_rows // (200 * D)), 1, 1))[:-(-n_rows // D)]
 
 
-@pytest.mark.parametrize("padding", [0, 8, 16, 24])
-@pytest.mark.parametrize("D,v,m,n_rows", [(1, 1, 22, 140001), (3, 1, 27, 140002), (5, 2, 11, 140005), (7, 4, 6, 140007), (2, 1, 40, 140002)])
+@pytest.mark.parametrize("padding", PADDINGS)
+@pytest.mark.parametrize("D,v,m,n_rows", EVALUATED)
 def test_rows_of_four_lanes(D, v, m, n_rows, padding):
     prob, words = batch(D, v, m, padding, n_rows, D + padding)
     assert words.shape[2] >= 64
     check_batch(prob, words, 8, f"{D} {v} {m} + {padding}", threads=16, kernels=("slots",))
 
 
-@pytest.mark.parametrize("D,v,m,n_rows", [(3, 1, 27, 140002), (5, 2, 11, 140005), (7, 4, 6, 140007)])
+@pytest.mark.parametrize("D,v,m,n_rows", WITHOUT_W)
 def test_without_w_items(D, v, m, n_rows):
     prob, words = batch(D, v, m, 8, n_rows, D)
     stride = words.shape[2]
@@ -45,5 +56,5 @@ def test_without_w_items(D, v, m, n_rows):
 
 
 def test_blocks_that_are_drawn():
-    prob, words = batch(9, 2, 12, 8, 64 * 3072 * 10, 3)
+    prob, words = batch(*DRAWN[:3], 8, DRAWN[3], 3)
     check_batch(prob, words[:-1], 16, "more than eight blocks to a wavefront", threads=16, kernels=("slots",))

@@ -2,6 +2,7 @@
 (hip_stub.c) comes before the real one, so that launches are only noted."""
 import ctypes
 import os
+import pickle
 import re
 import shutil
 import subprocess
@@ -12,6 +13,7 @@ import pytest
 
 import paper_2510_05112_amd as fp
 import workloads
+from helpers import two_tower_problem
 from workloads.problem import F, L, O, chain_problem
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -26,11 +28,12 @@ def stub(tmp_path_factory):
     return path
 
 
-def run(stub, what):
-    """Runs the function `what` of this file in a new process, with the stand-in."""
-    code = f"import sys; sys.path[:0] = [{HERE!r}, {os.path.dirname(HERE)!r}]; import test_host_launches as t; t.{what}(t.Device({stub!r}))"
-    done = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert done.returncode == 0, done.stdout
+def run(stub, what, *args):
+    """Runs the function `what` of this file in a new process, with the stand-in (and without torch, which brings the runtime)."""
+    code = (f"import pickle, sys; sys.path[:0] = [{HERE!r}, {os.path.dirname(HERE)!r}]; import test_host_launches as t; "
+            f"t.{what}(t.Device({stub!r}), *pickle.loads(sys.stdin.buffer.read()))")
+    done = subprocess.run([sys.executable, "-c", code], input=pickle.dumps(args), stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    assert done.returncode == 0, done.stdout.decode()
 
 
 class Device:
@@ -45,6 +48,7 @@ class Device:
     def launched(self, rc=0, what=0):
         assert rc == what, rc
         names = [self.stub.stub_launched(i).decode() for i in range(self.stub.stub_launches())]
+        self.forms = [tuple(int(x) for x in re.findall(r"L[bi](\d+)E", n)) for n in names]   # (template arguments)
         self.waves = [self.stub.stub_grid(i) * self.stub.stub_block(i) // 64 for i in range(len(names))]
         self.words = [self.stub.stub_word(i) & 0xffffffff for i in range(len(names))]
         self.stub.stub_reset()
@@ -57,9 +61,29 @@ class Device:
         size = self.lib.fpsched_wslide_workspace_bytes(h._h, n, stride)
         return self.launched(self.lib.fpsched_wslide(h._h, 4096, n, stride, 4096, stride_out, self.results, 4096, size, None))
 
+    def copy_form(self, h, stride, n):
+        """What the copy engine is timed by: "one kernel", or the transfers that the two passes keep."""
+        got = self.evaluate(h, stride, n)
+        if got == ["reset_counter_kernel", "eval_slot_kernel"]:
+            return "one kernel"
+        assert got[-2:] == TWO_PASSES
+        return self.forms[-1][-1]
+
+    def one_turn(self, h, stride):
+        """The largest batch that the one kernel takes (on a problem that goes to it up to a full chip)."""
+        least, beyond = 1, 1 << 24
+        assert self.copy_form(h, stride, least) == "one kernel" != self.copy_form(h, stride, beyond)
+        while beyond - least > 1:
+            n = (least + beyond) // 2
+            least, beyond = (n, beyond) if self.copy_form(h, stride, n) == "one kernel" else (least, n)
+        self.copy_form(h, stride, least)
+        assert self.waves[-1] % 256 == 0 and least % self.waves[-1] == 0   # (every wavefront of every compute unit has its candidates)
+        return least
+
 
 LONGEST = (1 << 23) - 32   # rows that the timing pass has positions for
 TWO_PASSES = ["check_rows_kernel", "time_lists_kernel"]
+KEPT = {1: 3, 2: 3, 3: 3, 4: 4, 5: 7, 6: 7, 7: 7}   # copy engine: transfers that the two passes keep at each depth
 
 
 def long_rows(dev):
@@ -108,15 +132,18 @@ def test_rows_beyond_the_positions_of_the_timing_pass(stub):
 def no_memory_for_copy_tables(dev):
     prob = chain_problem(8, 16, v=2, f=3, b=4, w=2, comm=1)
     prob.dur[O], prob.dur[L] = 2, 2
-    h = fp.Problem(prob, 128, device=0)
-    h.set_copy_engine(4)   # (deeper than the two passes go)
-    dev.stub.stub_fail_malloc(1)
-    h.set_copy_engine(3)
-    assert dev.stub.stub_fail_malloc(0) == 0
-    assert dev.evaluate(h, 128, 1 << 16) == ["reset_counter_kernel", "eval_slot_kernel"]
-    h.set_copy_engine(3)
-    assert dev.evaluate(h, 128, 1 << 16)[-2:] == TWO_PASSES
-    h.close()
+    for there, depth in ((4, 3), (7, 2), (3, 4), (1, 7)):   # (engines of more than three transfers have tables of their own)
+        h = fp.Problem(prob, 128, device=0)
+        h.set_copy_engine(there)
+        dev.stub.stub_fail_malloc(1)
+        h.set_copy_engine(depth)
+        assert dev.stub.stub_fail_malloc(0) == 0
+        assert dev.copy_form(h, 128, 1 << 16) == "one kernel"
+        h.set_copy_engine(depth)
+        assert dev.copy_form(h, 128, 1 << 16) == KEPT[depth]
+        h.set_copy_engine(there)
+        assert dev.copy_form(h, 128, 1 << 16) == KEPT[there]
+        h.close()
 
 
 def no_memory_for_some_table(dev):
@@ -203,3 +230,115 @@ def placement_by_rows(dev):
 
 def test_placement_by_rows(stub):
     run(stub, "placement_by_rows")
+
+
+def copy_rule(dev):
+    def engine(prob, depth, stride=256):
+        prob.dur[O], prob.dur[L] = 2, 3
+        h = fp.Problem(prob, stride, device=0)
+        h.set_copy_engine(depth)
+        return h
+
+    def chain(D, m, v=1, has_w=1):
+        return chain_problem(D, m, v=v, f=3, b=4, w=2 if has_w else None, comm=1)
+    # more than one turn of the one kernel, whatever the problem; one turn of two devices
+    for depth in KEPT:
+        for prob in (chain(2, 6, 2), chain(1, 40), chain(2, 40, 4)):
+            h = engine(prob, depth, 640)
+            most = dev.one_turn(h, 640)
+            assert [dev.copy_form(h, 640, n) for n in (1, most, most + 1)] == ["one kernel", "one kernel", KEPT[depth]]
+            h.close()
+    # one turn of more devices: the forms of each side of a row's items, the second edges, the depth and the stages per device
+    towers = [two_tower_problem(m=m, has_w=has_w, comm=2, mem_cap=3) for m, has_w in ((21, 1), (31, 0), (22, 1), (32, 0))]
+    for depth, prob, form in [(3, chain(3, 2), 3), (1, chain(40, 2), 3),
+                              (1, towers[0], "one kernel"), (3, towers[1], "one kernel"), (1, towers[2], 3), (3, towers[3], 3),
+                              (4, chain(3, 31), "one kernel"), (4, chain(3, 32), 4), (4, chain(3, 47, 1, 0), "one kernel"), (4, chain(3, 48, 1, 0), 4),
+                              (4, towers[2], "one kernel"),
+                              (5, chain(3, 32), "one kernel"), (7, chain(9, 80), "one kernel"), (5, chain(3, 16, 2), 7), (7, chain(3, 15, 2), "one kernel")]:
+        h = engine(prob, depth)
+        assert dev.copy_form(h, 256, 1) == form, (prob.name, depth)
+        if form == "one kernel":
+            most = dev.one_turn(h, 256)
+            assert dev.copy_form(h, 256, most + 1) == KEPT[depth]
+        else:
+            assert dev.copy_form(h, 256, 1 << 22) == form
+        h.close()
+
+
+def test_copy_engine_forms(stub):
+    run(stub, "copy_rule")
+
+
+def copy_forms_of(dev, problems, depth, lists, want):
+    seen = set()
+    for prob in problems:
+        h = fp.Problem(prob, 256, device=0)
+        h.set_copy_engine(depth)
+        seen.add(dev.copy_form(h, 256, lists))
+        # (a copy more than fills the chip goes to the two passes: copy_rule)
+        assert dev.copy_form(h, 256, 1 << 22) == want[-1]
+        h.close()
+    assert seen == set(want), seen
+
+
+@pytest.mark.parametrize("depth", [1, 2, 3, 4, 5, 7])
+def test_forms_that_the_tests_of_the_copy_engine_run(depth, stub):
+    import test_gpu_copy
+    import test_gpu_copy_deep
+    if depth <= 4:
+        run(stub, "copy_forms_of", test_gpu_copy.form_problems(), depth, test_gpu_copy.FORM_LISTS, ["one kernel", KEPT[depth]])
+    if depth in test_gpu_copy_deep.DEPTHS:
+        run(stub, "copy_forms_of", test_gpu_copy_deep.form_problems(), depth, test_gpu_copy.FORM_LISTS, ["one kernel", KEPT[depth]])
+
+
+def rows_shared(dev, evaluated, without_w, drawn):
+    SHARED = 2   # (of the order pass's template arguments)
+
+    def order_pass(prob, stride, rows):
+        h = fp.Problem(prob, stride, device=0)
+        got = dev.evaluate(h, stride, -(-rows // prob.n_devices))
+        h.close()
+        assert got[-2:] == TWO_PASSES
+        return dev.forms[-2][SHARED], "reset_counter_kernel" in got
+    for prob, stride, rows in evaluated:
+        assert order_pass(prob, stride, rows) == (1, False)
+    for prob, stride, rows in without_w:
+        h = fp.Problem(prob, stride, device=0)
+        assert dev.wslide(h, stride, -(-rows // prob.n_devices), stride)[:2] == TWO_PASSES
+        h.close()
+        assert dev.forms[0][1:] == (1, 1)
+    assert order_pass(*drawn) == (1, True)
+    # either side of the lines: eight wavefronts of rows per compute unit, rows of 64 words, wavefronts that the states leave room for
+    one, stride = chain_problem(1, 24, v=1, f=3, b=5, w=2, comm=1), 72
+    assert [order_pass(one, stride, 64 * 2048 + more)[0] for more in (0, 1)] == [0, 1]
+    assert [order_pass(one, stride, 1 << 20)[0] for stride in (56, 64, 72)] == [0, 1, 1]
+    assert [order_pass(chain_problem(32, m, v=2, f=3, b=5, w=2, comm=1), 768, 1 << 20)[0] for m in (64, 128)] == [1, 0]
+
+
+def test_rows_that_four_lanes_share(stub):
+    import test_gpu_rows_shared as t
+    run(stub, "rows_shared", [(*t.problem_of(*case[:3], padding), case[3]) for case in t.EVALUATED for padding in t.PADDINGS],
+        [(*t.problem_of(*case[:3], 8), case[3]) for case in t.WITHOUT_W], (*t.problem_of(*t.DRAWN[:3], 8), t.DRAWN[3]))
+
+
+def draws(dev, cases):
+    LEAST = 9   # (its place among the timing pass's arguments)
+    for prob, stride, waves, least, most, factors in cases:
+        h = fp.Problem(prob, stride, device=0)
+        cpw = h.info()["candidates_per_wave"]
+        segments = 256 * waves * cpw
+        word = {}
+        for argument in (LEAST, DRAW_SHARE):
+            dev.stub.stub_watch(b"time_lists_kernel", argument)
+            dev.evaluate(h, stride, segments + 1)
+            assert dev.waves[-1] == 256 * waves
+            word[argument] = dev.words[-1]
+        h.close()
+        # a wavefront's first draw of the largest batch
+        left = int(segments * max(factors)) - segments
+        assert word[LEAST] == least and max(least, min(left * word[DRAW_SHARE] >> 32, cpw)) == most
+
+
+def test_draws(stub):
+    import test_gpu_draws as t
+    run(stub, "draws", [(*t.problem_of(*case[:3]), *case[3:]) for case in t.CASES])
