@@ -174,7 +174,17 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   [S##_free] "+&v"(S.free_at), [S##_next] "+&v"(S.w_next), [S##_j] "+&v"(S.j_slot), [S##_pos] "+&v"(S.pos),               \
   [S##_row] "+&{" FPSCHED_##S##_ROW "}"(S.R), [S##_at] "=&v"(at_##S), [S##_moved] "=&s"(moved_##S)
 #define FPSCHED_PLACES(S) [S##_rows] "v"(S.meta), [S##_ring] "v"(S.win)
-#define FPSCHED_SHARED [stride] "s"(row_stride), [mask] "s"(kPosMask), [slots] "v"(slot_base)
+#define FPSCHED_SHARED [stride] "s"(row_stride), [mask] "s"(kPosMask), [slots] "v"(slot_base), [form] "n"(kForm)
+// Where the rounds begin in memory, set in front of the loop that they are in.  Instructions arrive 32 bytes at a time, and the few
+// wavefronts of a small batch wait for those that lie across two such pieces.  Of the eight places that four bytes more in front of the
+// loop give, best and worst: plain form 1005 us at a multiple of 32 bytes, 1017 sixteen behind one (462 candidates of 36 x 117 x 4, the
+// whole evaluation); times of two words 189 and 191 (8,192 of 16 x 64 x 2), links with costs 588 and 591 (20,011 of 11 x 45 x 3), the best place
+// the same; synchronisation, whose two statements lie apart, 820 sixteen bytes behind it, 838 eight behind it (65,536 of 12 devices).
+#define FPSCHED_BEGIN ".ifndef .Lrounds_%c[form]\n\t.Lrounds_%c[form]:\n\t.endif\n\t"
+#define FPSCHED_PLACE_ROUNDS(AT)                                                                                         \
+  asm volatile(".p2align 5\n\t"                                                                                         \
+               ".fill ((%c[at] - (.Lrounds_%c[form] - .Lplace_%c[form])) & 31) / 4, 4, 0xbf800000\n\t" /* (s_nop 0) */    \
+               ".Lplace_%c[form]:" :: [form] "n"(kForm), [at] "n"(AT))
 
 // ... the plain form.  (FOLLOW: for rows that another row follows in the place of the next word's, in the form with second
 // edges)
@@ -218,7 +228,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "1:\n\t"
 #define FPSCHED_FOLLOW_STEP(S, AHEAD) FPSCHED_STEP(S, AHEAD, FPSCHED_FOLLOW(S), "s_andn2_b64 exec, exec, vcc\n\t")
 #define FPSCHED_ROUNDS(TEXT)                                                                                             \
-  asm volatile(TEXT                                                                                                      \
+  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd), [t] "=&v"(scratch) \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [tables] "s"(tables)        \
                : "memory", "vcc", "scc")
@@ -268,7 +278,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 #define FPSCHED_LEFT(S)                                                                                                  \
   [S##_own] "+&v"(S.own_place), [S##_at_next] "+&v"(S.next_place), [S##_escape] "+&v"(S.escape), [S##_room] "+&v"(S.escape_room)
 #define FPSCHED_TIMES_ROUNDS(TEXT)                                                                                       \
-  asm volatile(TEXT                                                                                                      \
+  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
                  FPSCHED_LEFT(even), FPSCHED_LEFT(odd), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited) \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [most] "s"(0xffffffu)       \
@@ -324,7 +334,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   [S##_link] "+&v"(S.link), [S##_busy] "+&v"(S.busy), [S##_link_at] "=&v"(link_at_##S), [S##_sent] "=&v"(sent_##S),       \
   [S##_cost] "=&v"(cost_##S)
 #define FPSCHED_COST_ROUNDS(TEXT)                                                                                        \
-  asm volatile(TEXT                                                                                                      \
+  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
                  FPSCHED_COST_STATE(even), FPSCHED_COST_STATE(odd), [t] "=&v"(scratch), [u] "=&v"(scratch2)             \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [byte] "s"(0xffu),          \
@@ -358,7 +368,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "v_add_u32 %[" #O "_at], %[" #O "_at], %[slots]\n\t"                                                                  \
   "ds_read_b64 " FPSCHED_##O##_SLOT ", %[" #O "_at]\n\t"
 #define FPSCHED_WIDE_ROUNDS(TEXT)                                                                                        \
-  asm volatile(TEXT                                                                                                      \
+  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [t] "=&v"(scratch)                                            \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED                                              \
                : "memory", "scc", "v48", "v49", "v50", "v51")
@@ -379,6 +389,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
   constexpr int kPieces = STRAIGHT ? 4 : 2;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
+  [[maybe_unused]] constexpr int kForm = (DEG2 ? 1 : 0) + (WIDE ? 2 : 0) + (LINKS ? 4 : 0) + 8 * MB + (SYNC ? 32 : 0) + (TIMES ? 64 : 0);
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
@@ -814,6 +825,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   // (SYNC: an op takes in at most 2 m values, in every fourth round)
   const unsigned long long bound = (3ull * (unsigned)D * (unsigned)stride * (SYNC ? 4ull * (unsigned)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
+  if constexpr (STRAIGHT) FPSCHED_PLACE_ROUNDS(SYNC ? 16 : 0);
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
     // (vmcnt(0): the requests of the last top-up.  Waited for behind the first start times that leave, they would take these
     // stores with them, which have only just been issued.)
