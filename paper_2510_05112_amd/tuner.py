@@ -115,7 +115,8 @@ def _grid_arrays(types, n_devices, inflight_options, empty=np.empty):
     limits = np.asarray([np.asarray(x, np.int32) for x in inflight_options], np.int32)
     rows = np.asarray([t.policy_row() for t in types], np.int32)
     n, of_policies = len(rows) * len(limits), len(rows) * len(limits) * n_devices * 8
-    limits = np.atleast_2d(limits)   # (no option at all: an empty grid)
+    if limits.ndim == 1:   # (no option at all: an empty grid)
+        limits = limits[None]
     both = empty(of_policies + len(rows) * limits.size, np.int32)
     pol, inf = both[:of_policies].reshape(n, n_devices, 8), both[of_policies:].reshape(len(rows) * len(limits), limits.shape[1])
     pol.reshape(len(rows), n // len(rows), n_devices, 8)[:] = rows[:, None, None, :]
