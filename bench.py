@@ -40,20 +40,20 @@ def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
 
 # the list evaluation (order pass and timing pass): plain, with costs per micro-batch (--mb-costs), with link occupancy
 # (--links), with both
-MEASURED = {("cfg4", 65536): counted(1.068e10, 1.058e9, 2.787, "list_evaluation.md")}
-MEASURED_MB = {("cfg4", 65536): counted(None, 1.276e9, 3.437, "list_evaluation.md")}
-MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.736, "list_evaluation.md")}
-MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.589e9, 4.466, "list_evaluation.md")}
+MEASURED = {("cfg4", 65536): counted(1.068e10, 1.058e9, 2.768, "list_evaluation.md")}
+MEASURED_MB = {("cfg4", 65536): counted(None, 1.276e9, 3.447, "list_evaluation.md")}
+MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.794, "list_evaluation.md")}
+MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.589e9, 4.493, "list_evaluation.md")}
 # the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
-MEASURED_SYNC = {("sync4", 65536): counted(None, 2.492e8, 0.864, "list_evaluation.md")}
+MEASURED_SYNC = {("sync4", 65536): counted(None, 2.490e8, 0.839, "list_evaluation.md")}
 MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}
 # the copy engine (--config 5 --copy-engine DEPTH), two passes; of the depths that share a form the one that was profiled
-MEASURED_COPY = {3: {("cfg5", 131072): counted(None, 1.171e9, 2.698, "list_evaluation.md")},
-                 4: {("cfg5", 131072): counted(None, 1.265e9, 2.939, "list_evaluation.md")},
-                 7: {("cfg5", 131072): counted(None, 1.562e9, 3.290, "list_evaluation.md")}}
+MEASURED_COPY = {3: {("cfg5", 131072): counted(None, 1.171e9, 2.665, "list_evaluation.md")},
+                 4: {("cfg5", 131072): counted(None, 1.265e9, 2.948, "list_evaluation.md")},
+                 7: {("cfg5", 131072): counted(None, 1.562e9, 3.279, "list_evaluation.md")}}
 # the sliding pass (--mode wslide), all of its kernels, and without its lists (--no-lists): one kernel
-MEASURED_WSLIDE = {("cfg4", 65536): counted(3.73e10, 4.226e9, 11.10, "wslide_kernel_cfg4.md")}
-MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.814e9, 10.77, "wslide_kernel_cfg4.md")}
+MEASURED_WSLIDE = {("cfg4", 65536): counted(3.73e10, 4.226e9, 11.11, "wslide_kernel_cfg4.md")}
+MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.814e9, 10.78, "wslide_kernel_cfg4.md")}
 # the generator (--mode generate; traffic: WRITE_SIZE x 1024 plus the parameter sets read), generator and evaluator in one
 # kernel (--mode search --fused), the same with the sliding pass in it (--slide)
 MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.763e9, 9.23, "generate_kernel_cfg4.md")}

@@ -1995,8 +1995,7 @@ int fpsched_problem_set_copy_engine(fpsched_problem* p, int32_t depth) {
     // the slot kernel has a form of this model too: the plain tables, 32 more dwords of LDS per lane for
     // the rings of the copy timeline
     p->copy_slots_ok = false;
-    // the two-pass evaluation takes it where times fit 24 bits and few transfers are in the engine at a time (without its
-    // tables the slot kernel stays in use)
+    // the two-pass evaluation takes it where times fit 24 bits, at every depth (without its tables the slot kernel stays in use)
     p->copy_lists(depth).ok = false;
     if (p->slots_ok && build_copy_variant(p, depth) != FPSCHED_OK) (void)hipGetLastError();
     if (p->slots_ok) {
