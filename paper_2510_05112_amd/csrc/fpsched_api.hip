@@ -1215,19 +1215,21 @@ static int draws_at_a_time(const fpsched_problem* p, int32_t stride_words, int c
 
 // ... and the timing pass, while many are left: a draw is a wait of some 4,500 clocks for a wavefront, whose segments need
 // one every sixth of their top-ups or so; so a part of the wavefront's share of what is left is drawn at a time, up to one a segment:
-// half of it, or a quarter where a step also asks for link words and has no branches (such a step waits for more than the draw
-// gives back, and a wavefront that has drawn more than its equals ends later).  Candidates of more than 16 K words are worth the wait
-// and better drawn one by one.  Whole evaluation against one draw per 12 K words, a quarter / half / three quarters of the share,
-// mean over batches of 1.3 to 9 candidates a segment, 14 problems of 2 to 32 devices, 20 to 64 micro-batches:
+// half of it, or a quarter on rows of 192 words and more where a step also asks for link words and has no branches (such a step waits
+// for more than the draw gives back, and a wavefront that has drawn more than its equals ends later, the more so the longer its
+// candidates).  Candidates of more than 16 K words are worth the wait and better drawn one by one.  Whole evaluation against one draw
+// per 12 K words, a quarter / half / three quarters of the share, mean over batches of 1.3 to 9 candidates a segment, 14 problems of 2
+// to 32 devices, 20 to 64 micro-batches:
 //   plain model 0.96 to 1.00 / 0.93 to 1.005 / 0.91 to 1.003 (16 x 64 x 2 0.980 / 0.958 / 0.952; 262,144 of it 2605, 2408, 2395,
 //   2412 us); at worst, 1.3 a segment of 2 x 64 x 1, 1.03 / 1.06 / 1.05;
-//   links, with and without costs, no second edges 0.993 to 1.003 / 0.987 to 1.026 / 0.98 to 1.035 (configuration 3 3004, 2969, 2996, 3028
-//   us, with costs 3353, 3328, 3381, 3415; at worst 1.02 / 1.08 / 1.09), with second edges 0.98 to 0.99 / 0.98 to 0.99 / 0.97 to 0.99;
+//   links, with and without costs, no second edges, rows of 192 words and more 0.993 to 1.003 / 0.991 to 1.026 / 0.993 to 1.035
+//   (configuration 3 3004, 2969, 2996, 3028 us, with costs 3353, 3328, 3381, 3415; at worst 1.02 / 1.08 / 1.09), of 120 words 0.994 to 1.003 /
+//   0.987 to 1.001 / 0.98 to 1.002; with second edges 0.98 to 0.99 / 0.98 to 0.99 / 0.97 to 0.99;
 //   costs per micro-batch 0.975 to 1.001 / 0.955 to 1.013 (12 x 40 x 4; 11 x 45 x 3 1.006) / 0.94 to 1.02;
 //   synchronisation 1.00 / 0.995 to 1.0 / 1.0, copy engine 0.99 to 1.00 / 0.99 to 1.00 / 0.98 to 1.00.
 // 65,536 of 32 x 128 x 2: 2597, 2586, 2663, 2661 us, under links 3657, 3674, 3771, 3839.
 static uint32_t drawn_share(const fpsched_problem* p, const ListTables& T, bool deg2, int32_t stride_words, int64_t waves) {   // (times 2^32)
-  const int64_t part = (int64_t)p->D * stride_words > 16384 ? 0 : 1ll << (T.link_words > 0 && !deg2 ? 30 : 31);
+  const int64_t part = (int64_t)p->D * stride_words > 16384 ? 0 : 1ll << (T.link_words > 0 && !deg2 && stride_words >= 192 ? 30 : 31);
   return (uint32_t)((part + waves - 1) / waves);
 }
 

@@ -202,6 +202,7 @@ def share_of_a_draw(dev):
     assert share(chain, 384) == share(chain, 384, with_costs(chain)) == 0.5
     assert share(chain, 384, links) == share(chain, 384, both["chain"]) == 0.25
     assert share(towers, 256) == share(towers, 256, links) == share(towers, 256, both["towers"]) == 0.5
+    assert [share(chain, stride, links) for stride in (184, 192)] == [0.5, 0.25]
     # the longest candidates that more than one of are drawn at a time
     assert (share(chain, 2048), share(chain, 2056)) == (0.5, 0)
     assert (share(chain, 2048, links), share(chain, 2056, links)) == (0.25, 0)
