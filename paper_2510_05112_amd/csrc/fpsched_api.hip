@@ -2472,15 +2472,17 @@ int fpsched_wslide(const fpsched_problem* p, const uint16_t* d_ops, int64_t n_ca
   // pass 2: every row places its W items on its own, by a lane, whose steps wait for each other, or by a wavefront, of which
   // a compute unit has few: so where rows are few, and the more so the longer they are.  Both passes, a lane / a wavefront per
   // row, 28 shapes, at 8,192, 12,288, 16,384 and 24,576 rows:
-  //   up to 384 items 1.01 (24 x 24 x 2, 30 x 60 x 1) to 1.20 (8 x 32 x 2), 0.91 (20 x 10 x 1) to 1.09 (16 x 64 x 2 545 and 541 us, 16 x 8 x 2
-  //   93 and 95), 0.84 to 1.03 (16 x 64 x 2 546 and 598), 0.74 to 0.92; on up to four devices 1.17 to 1.67, 1.10 to 1.58, 0.99
-  //   (4 x 16 x 1) to 1.51 (2 x 60 x 1), 0.88 to 1.41;
+  //   up to 120 items 1.03 to 1.16, 0.91 (20 x 10 x 1) to 1.09 (12 x 30 x 1; 16 x 8 x 2 93 and 95 us), 0.84 to 1.03, 0.74 to 0.92; on four
+  //   devices 1.17, 1.10, 0.99, 0.88;
+  //   144 to 384 items on more than eight devices 1.01 (24 x 24 x 2, 30 x 60 x 1) to 1.14, 0.97 to 1.03 (16 x 64 x 2 545 and 541), 0.90 to 0.96
+  //   (16 x 64 x 2 546 and 598), 0.78 to 0.86; on five and eight 1.19 and 1.20, 1.07 and 1.09 (8 x 32 x 2 220 and 202), 0.95 and 1.00, 0.77 and 0.87;
+  //   on two and three 1.67 and 1.27, 1.58 and 1.13, 1.51 and 1.05, 1.41 and 0.88;
   //   450 items and more 1.23 to 1.89, 1.10 to 1.72, 1.05 (20 x 50 x 3) to 1.54, 0.94 (20 x 50 x 3; 32 x 50 x 3 1.00) to 1.35 (32 x 128 x
   //   2 2104 and 1851 us), at 32,768 0.82 to 1.16 (32 x 128 x 2 1.02).
   const int stash = (int)std::min<int64_t>((int64_t)max_chunks_of(p) * p->m, stride_words);
   const int64_t rows_shared = place_rows_bytes + 4ll * 4 * kMaxDevices, rows_wave = slide_rows_wave_bytes(stride_out_words, stash);
   const int64_t rows_waves = std::min<int64_t>({(p->max_lds - rows_shared) / rows_wave, kSlideThreads / 64, p->D});
-  const int64_t items = 3ll * max_chunks_of(p) * p->m, few_rows = items >= 448 ? 24576 : p->D <= 4 ? 16384 : 12288;
+  const int64_t items = 3ll * max_chunks_of(p) * p->m, few_rows = items >= 448 ? 24576 : p->D <= (items >= 128 ? 8 : 4) ? 16384 : 12288;
   if (n_cand * p->D <= few_rows && rows_waves >= std::min(p->D, 4)) {
     hipLaunchKernelGGL(wslide_place_rows_kernel, dim3((unsigned)n_cand), dim3(64 * (unsigned)rows_waves),
                        (size_t)(rows_shared + rows_waves * rows_wave), st, p->stab, d_ops, (int)stride_words, starts, escapes,

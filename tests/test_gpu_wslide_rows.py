@@ -1,5 +1,5 @@
 """The second kernel of the sliding pass in its two forms, a wavefront per row for few rows and a lane per row for many (beyond
-12,288 rows, 16,384 on up to four devices, 24,576 where they are longer), on the same lists: long and short rows, chunks out of order,
+12,288 rows, 16,384 on few devices, 24,576 where they are longer), on the same lists: long and short rows, chunks out of order,
 waits of 2^16 time units and more, lists that stop early, rows of the new lists that are too short."""
 import numpy as np
 import pytest

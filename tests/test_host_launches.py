@@ -221,9 +221,9 @@ def placement_by_rows(dev):
         h.close()
         assert got[-3:-1] == TWO_PASSES
         return {"wslide_place_rows_kernel": "wavefront", "wslide_place_kernel": "lane"}[got[-1]]
-    # a row's items: up to 447 (on up to four devices, and on more), 448 and more
-    for shape, most in (((4, 4, 1), 16384), ((4, 74, 2), 16384), ((5, 4, 1), 12288), ((8, 16, 1), 12288), ((16, 64, 2), 12288), ((32, 149, 1), 12288),
-                        ((16, 75, 2), 24576), ((4, 75, 2), 24576), ((32, 128, 2), 24576)):
+    # a row's items: up to 127, up to 447, 448 and more, and the devices
+    for shape, most in (((4, 4, 1), 16384), ((5, 4, 1), 12288), ((8, 42, 1), 12288), ((8, 43, 1), 16384), ((9, 43, 1), 12288), ((4, 74, 2), 16384),
+                        ((8, 149, 1), 16384), ((16, 64, 2), 12288), ((32, 149, 1), 12288), ((16, 75, 2), 24576), ((4, 75, 2), 24576), ((32, 128, 2), 24576)):
         D = shape[0]
         assert placed_by(*shape, most // D * D) == "wavefront", shape
         assert placed_by(*shape, most // D * D + D) == "lane", shape
