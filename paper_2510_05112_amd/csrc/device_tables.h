@@ -153,6 +153,10 @@ struct ListTables {
   int32_t cand_slots;       // slots per candidate, a multiple of 4
   int32_t wave_bytes;       // LDS of one wavefront of the timing pass: op windows, link words, slots
   int32_t n_time_ints;      // timing rows, padded to a multiple of 8
+  int32_t chunks;           // most stages of a device
+  int32_t row_step;         // timing rows in LDS: bytes from one (kind, chunk) to the next,
+  int32_t odd_at;           // ... from the even devices' rows to the odd ones',
+  int32_t row_bytes;        // ... and in all
   int32_t off_links;        // links form: link rows, one int per timing row in the same order, in ints
   int32_t link_words;       // links form: words per lane and half (one behind the links for ops that send nothing)
   int32_t copy_depth;       // copy-engine form: transfers the engine holds at most, else 0
@@ -169,6 +173,11 @@ struct ListTables {
   const int32_t* ints;      // DEVICE
 };
 constexpr unsigned kRowTwoOut = 1u << 30;
+// LDS of the timing pass's tables, and where what stands behind the rows is: an offset in `ints` counts from here on
+constexpr int list_dense_row_bytes(const ListTables& T) { return kNKinds * kMaxChunks * 16 * T.D; }
+constexpr int list_behind_rows(const ListTables& T) { return T.row_bytes - list_dense_row_bytes(T); }
+constexpr int list_table_bytes(const ListTables& T) { return list_behind_rows(T) + 4 * T.n_time_ints; }
+constexpr int kRowColumns = 16;   // of 16 bytes, all banks (timing.hip); column c is of the pair of devices c modulo their number
 constexpr int kGroupRow = -1;
 constexpr unsigned kGroupIn = 1u << 16, kGroupOut = 1u << 17;
 constexpr unsigned kWideNever = 0xffu << 8;   // wide form: the tag of an empty slot, expected on a device's own word
@@ -178,7 +187,8 @@ constexpr unsigned kNoState = 15u;
 constexpr unsigned kPadState = 14u;   // order pass: state of the bytes behind a chunk's last item
 // the upper half of what the order pass leaves per row: the position at which the list stops (its END word, the end
 // of the row, or the first op that may not issue there), and
-constexpr unsigned kRowStop = 0x0fffffffu;
+constexpr unsigned kRowStop = 0x07ffffffu;
+constexpr unsigned kRowPlant = 1u << 27;       // the END word that the list stops at is of a third or fourth stage: its row may be another word's
 constexpr unsigned kRowStuck = 1u << 28;       // the list stops at an op that can never issue
 constexpr unsigned kRowMalformed = 1u << 29;   // ... whose word is malformed
 constexpr unsigned kRowIncomplete = 1u << 30;  // not every activation is consumed at the stop

@@ -276,12 +276,28 @@ struct StageEdges { std::vector<StageEdge> in[2], out[2]; };
 
 // timing pass: as many candidates per wavefront as its lanes and LDS hold (waves 0: it does not fit)
 WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
-  for (int cpw = 64 / ((T->D + 1) / 2); cpw >= 1; --cpw) {
+  const int pairs = (T->D + 1) / 2;
+  for (int cpw = 64 / pairs; cpw >= 1; --cpw) {
     T->cands_per_wave = cpw;   // (rings are 32-byte aligned)
     T->wave_bytes = (int32_t)((kTimeWindowBytes + 512ll * T->link_words + (int64_t)cpw * slot_bytes * T->cand_slots + 31) & ~31ll);
-    const WorkgroupShape shape = T->copy_depth > 0 ? workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds, kTimeCopyMaxThreads / 64, kTimeCopyWavesPerSimd, T->copy_depth > kCopyShallow)
-                                                   : workgroup_shape(4ll * T->n_time_ints, T->wave_bytes, max_lds);
-    if (shape.waves >= 1) return shape;
+    auto place = [&](bool columns) {
+      // (where no device has more than two stages, the odd devices' rows take the place of the third and fourth stage's)
+      T->row_step = columns ? 16 * kRowColumns : 16 * T->D;
+      T->odd_at = !columns ? 16 * pairs : (T->chunks <= 2 ? 2 : kNKinds * kMaxChunks) * T->row_step;
+      T->row_bytes = kNKinds * kMaxChunks * T->row_step * (columns && T->chunks > 2 ? 2 : 1);
+      const int64_t tables = list_table_bytes(*T);
+      return T->copy_depth > 0 ? workgroup_shape(tables, T->wave_bytes, max_lds, kTimeCopyMaxThreads / 64, kTimeCopyWavesPerSimd, T->copy_depth > kCopyShallow)
+                               : workgroup_shape(tables, T->wave_bytes, max_lds);
+    };
+    const WorkgroupShape dense = place(false);
+    // Columns where the lanes of a candidate divide them, so that a lane's column is its number's, and where they cost no wavefront
+    // (a wavefront in fourteen is worth about what half of a row read is).
+    if (kRowColumns % pairs == 0) {
+      const WorkgroupShape shape = place(true);
+      if (shape.waves >= 1 && shape.waves * shape.groups >= dense.waves * dense.groups) return shape;
+      (void)place(false);
+    }
+    if (dense.waves >= 1) return dense;
   }
   return WorkgroupShape{0, 1};
 }
@@ -334,6 +350,7 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
   ListTables& T = *tables;
   T = ListTables{};
   T.D = D; T.m = m;
+  for (int d = 0; d < D; ++d) T.chunks = std::max(T.chunks, p->n_chunks[d]);
   T.n_time_ints = (kNKinds * kMaxChunks * D * row_ints + n_second * 4 + 7) & ~7;
   if (4ll * T.n_time_ints > 0xffff) return false;
   int second_at = kNKinds * kMaxChunks * D * row_ints;
@@ -1273,7 +1290,7 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   const bool deg2 = variant ? variant->deg2 : p->lists_deg2;
   hipLaunchKernelGGL(starts ? times_kernel() : time_kernel_of(T, deg2, p->lists_wide && !variant), dim3((unsigned)time_blocks),
-                     dim3(64 * tw), (size_t)(4ll * T.n_time_ints + (int64_t)tw * T.wave_bytes), st, T, d_ops,
+                     dim3(64 * tw), (size_t)(list_table_bytes(T) + (int64_t)tw * T.wave_bytes), st, T, d_ops,
                      (long long)n_cand, (int)stride_words, reinterpret_cast<long long*>(out.makespan), idle, out.peak,
                      out.flags, counter, draws_at_a_time(p, stride_words, T.cands_per_wave), drawn_share(p, T, deg2, stride_words, time_blocks * tw), starts ? *starts : StartTimes{});
   return check_hip(hipGetLastError());

@@ -273,6 +273,8 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
       // (an END word ends the list whatever its low bits are)
       if ((stop_word >> 13) != 0u)
         status = kRowStuck | ((((stop_row >> 8) & 0xffu) == kNoState || (int)(stop_word & 0x7ffu) >= items_of((stop_word >> 11) & 3u)) ? kRowMalformed : 0u);
+      else if ((stop_word & 0x1000u) != 0u)
+        status = kRowPlant;
       stop = at + first_bad;
       alive = false;
     }

@@ -230,7 +230,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 #define FPSCHED_ROUNDS(TEXT)                                                                                             \
   asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd), [t] "=&v"(scratch) \
-               : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [tables] "s"(tables)        \
+               : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [tables] "s"(behind)        \
                : "memory", "vcc", "scc")
 
 // ... the form that leaves start times: an op's start goes where its own word was in the ring (own: that place; at_next: the
@@ -338,7 +338,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
                  FPSCHED_COST_STATE(even), FPSCHED_COST_STATE(odd), [t] "=&v"(scratch), [u] "=&v"(scratch2)             \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [byte] "s"(0xffu),          \
-                 [link_stride] "s"(row_stride / 4u), [even_link_rows] "v"(even.link_rows), [odd_link_rows] "v"(odd.link_rows), \
+                 [link_stride] "s"(4u * (unsigned)D), [even_link_rows] "v"(even.link_rows), [odd_link_rows] "v"(odd.link_rows), \
                  [even_links] "v"(even.links), [odd_links] "v"(odd.links)                                               \
                : "memory", "scc")
 
@@ -393,16 +393,32 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
-  // LDS: [op windows of all wavefronts][tables][per wavefront: link words, slots]
+  // LDS: [op windows of all wavefronts][rows][the tables behind them][per wavefront: link words, slots]
   const unsigned lds0 = lds_address(lds), tables = lds0 + (blockDim.x >> 6) * (unsigned)kTimeWindowBytes;
-  // (MB: where the costs begin, in the rows' second words, becomes an LDS address)
-  for (int i = tid; i < T.n_time_ints; i += blockDim.x)
-    lds_write<int>(tables + (unsigned)i * 4u, T.ints[i] + (MB != 0 && (i & 3) == 1 && i < kNKinds * kMaxChunks * 4 * T.D ? (int)(tables << 8) : 0));
+  const unsigned behind = tables + (unsigned)list_behind_rows(T);   // (of an offset in the image)
+  // Rows with columns (fpsched_api.hip, timing_shape): a row read of sixteen bytes is served for sixteen lanes at a time, without bank
+  // conflicts if these read sixteen different columns of 256 bytes, whatever kind and chunk each of them reads.  As dense as in the
+  // image the rows of two candidates met in a bank at 16 devices, those of four at 8: 8 and 10 clocks a read instead of 4.7, in a pass
+  // that LDS is busy in for 90 % of its time (whole evaluation: 262,144 candidates of 16 devices, 64 micro-batches, two chunks 2478 and
+  // 2313 us; 65,536 of 8, 32 micro-batches 311 and 299 us; 32 devices are dense in the same columns, no change).
+  const bool columns = T.odd_at != 16 * P;
+  const int n_rows = T.row_bytes / 16, image_rows = kNKinds * kMaxChunks * D;
+  for (int i = tid; i < n_rows; i += blockDim.x) {
+    int from = i;
+    if (columns) {
+      const int row = (i >> 4) & 31, k = T.chunks <= 2 ? row >> 1 & 1 : i >> 9;
+      from = (T.chunks <= 2 ? row & ~2 : row) * D + min(k * P + ((i & 15) & (P - 1)), D - 1);
+    }
+    lds_int4 R = reinterpret_cast<const lds_int4*>(T.ints)[from];
+    if (MB != 0) R.y += (int)(behind << 8);   // (where the costs begin becomes an LDS address)
+    lds_write<lds_int4>(tables + (unsigned)i * 16u, R);
+  }
+  for (int i = 4 * image_rows + tid; i < T.n_time_ints; i += blockDim.x) lds_write<int>(behind + (unsigned)i * 4u, T.ints[i]);
   const int seg = lane / P, pair = lane - seg * P;
   const bool lane_ok = seg < cpw;
   const int d0 = 2 * pair;
   const bool has_odd = d0 + 1 < D;
-  const unsigned wave_at = tables + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)(T.wave_bytes - kTimeWindowBytes);
+  const unsigned wave_at = behind + (unsigned)T.n_time_ints * 4u + (unsigned)wave * (unsigned)(T.wave_bytes - kTimeWindowBytes);
   const unsigned links_bytes = LINKS ? (unsigned)T.link_words * 512u : 0u;   // of the wavefront: [half][link][lane]
   unsigned slot_base = wave_at + links_bytes + (unsigned)(lane_ok ? seg : 0) * (unsigned)T.cand_slots * kSlotBytes;
   asm volatile("" : "+v"(slot_base));   // one register, not a sum to be re-associated every round
@@ -426,7 +442,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     return (((unsigned)ballot & seg_lo) | ((unsigned)(ballot >> 32) & seg_hi)) != 0u;
   };
 
-  const unsigned row_stride = (unsigned)D * kRowBytes;
+  const unsigned row_stride = (unsigned)T.row_step;
   const unsigned stride2 = (unsigned)stride * 2u, stride_pos = position_of((unsigned)stride);
 
   // (a transfer more may have its memory event to come than may be unfinished: of equal times the compute event is first)
@@ -475,8 +491,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   };
   auto set_up = [&](Device& x, int k) {
     x.win = lds0 + (unsigned)wave * (unsigned)kTimeWindowBytes + (unsigned)k * kWindowBytes + (unsigned)lane * 4u;
-    x.meta = tables + (unsigned)(k * P + pair) * kRowBytes;
-    x.link_rows = LINKS ? tables + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
+    x.meta = tables + (unsigned)(k * T.odd_at) + (unsigned)(columns ? lane & 15 : pair) * kRowBytes;
+    x.link_rows = LINKS ? behind + (unsigned)T.off_links * 4u + (unsigned)(k * P + pair) * 4u : 0u;
     x.links = LINKS ? wave_at + (unsigned)k * (links_bytes / 2u) + (unsigned)lane * 4u : 0u;
     x.free_at = 0u; x.j_slot = 0u; x.w_next = 0u; x.busy = 0u;
     x.cap = COPY && (k == 0 || has_odd) && lane_ok ? T.ints[T.off_dev + 2 * (d0 + k) + 1] : 0x7fffffff;
@@ -493,7 +509,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   const char* row = reinterpret_cast<const char*>(ops);   // of the even device; the odd one's follows it
   bool running = false, fresh = true, priming = false;
   bool any_special = true;          // wave-uniform: some segment starts, or has just started, a candidate
-  bool any_stuck = false;           // wave-uniform: the list of some device stops at an op that may not issue
+  bool any_stuck = false;           // wave-uniform: some device's list stops at a word that is not to be looked at
   unsigned long long idle_lanes = ~0ull;
   bool first_draw = true;
   // Drawn from the counter and not handed to a segment: [pool_next, pool_end); behind a draw that reached past the last candidate
@@ -511,7 +527,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     const unsigned at = __umul24(word >> 11, row_stride) + x.meta;
     x.j_slot = word * kSlotBytes;
     x.R = lds_read<lds_int4>(at);
-    if (LINKS) x.link = lds_read<unsigned>(__umul24(word >> 11, row_stride / 4u) + x.link_rows);
+    if (LINKS) x.link = lds_read<unsigned>(__umul24(word >> 11, 4u * (unsigned)D) + x.link_rows);
   };
   // address of a position in the device's ring (the windows of a wavefront begin at a multiple of their size)
   auto in_ring = [&](const Device& x, unsigned pos) -> unsigned {
@@ -608,7 +624,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   };
   // where the second row of an op with a second input or output is
   auto second_row = [&](int w) -> unsigned {
-    return tables + (WIDE ? ((unsigned)w >> 12) & 0xfff0u : (unsigned)w & 0xffffu);
+    return behind + (WIDE ? ((unsigned)w >> 12) & 0xfff0u : (unsigned)w & 0xffffu);
   };
   // one step of one half of the devices with second edges in the wide form and under link occupancy or costs per
   // micro-batch; returns the lanes that issued
@@ -766,7 +782,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       x.pos = (x.pos | kPosBetween) + 2u;
       x.w_next = lds_read<uint16_t>(in_ring(x, x.pos));
     }
-    if (in(followed)) x.R = lds_read<lds_int4>(tables + ((unsigned)x.R.z >> 14 & ~15u));
+    if (in(followed)) x.R = lds_read<lds_int4>(behind + ((unsigned)x.R.z >> 14 & ~15u));
     return moved;
   };
   // SYNC, every fourth round: the devices at an item of a group of micro-batches (their rows never issue and name another
@@ -778,7 +794,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     if (at_group == 0ull) return 0ull;
     unsigned long long moved = 0ull;
     if (__builtin_amdgcn_inverse_ballot_w64(at_group)) {
-      const unsigned at = tables + ((unsigned)x.R.z >> 14);
+      const unsigned at = behind + ((unsigned)x.R.z >> 14);
       const lds_int4 first = lds_read<lds_int4>(at), second = lds_read<lds_int4>(at + 16u);
       const unsigned n = (unsigned)first.z & 0xffffu;
       const unsigned first_j = __umul24((x.j_slot >> 2) & 0x7ffu, n), n_slots = min(n, (unsigned)T.m - first_j);
@@ -840,7 +856,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
         join(even, 0);
         if (has_odd) join(odd, 1);
       }
-      any_stuck = __ballot(running && ((even.info | odd.info) & kRowStuck) != 0u) != 0ull;
+      any_stuck = __ballot(running && ((even.info | odd.info) & (kRowStuck | kRowPlant)) != 0u) != 0ull;
       priming = false;
       // hand the segments that ask for one (lane 0 of each speaks for it) their next candidate
       const unsigned long long want = __ballot(fresh && !first_draw && pair == 0 && lane_ok);
