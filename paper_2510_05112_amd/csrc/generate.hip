@@ -258,7 +258,6 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   // left of its gap, the queue (entries in and out, the word being filled)
   const unsigned ring = lds_address(lds) + wave * ring_bytes + lane * 4;   // entry i at + i * 256; a multiple of its size + lane * 4
   const unsigned queue = lds_address(counts + n_count_ints + cpw * slot_words) + lane * 4;   // word i at + i * 256
-  auto on_ring = [&](unsigned at) -> unsigned { return (at & (ring_bytes - 256u)) | ring; };
   unsigned ring_in = ring, ring_out = ring, gap = 0u, q_in = 0u, q_out = 0u, q_tail = 0u;
   int w_placed = 0;
   unsigned event = 0u;
@@ -347,6 +346,26 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   // where the actor's counters are: of chunk 0, and how much further that of the last chunk is (V == 2)
   const unsigned own_f = own_at[0], own_b = own_at[0] + 4u * (unsigned)S;
   const int own_step = (int)(own_at[V - 1] - own_at[0]);
+
+  // The neighbouring stages' counters (DEG > 0: two of each pair, as they stand in LDS), requested as soon as a step's own counters
+  // have been stored: on their way while the step's items are timed.
+  short ahead_f[NP][2 * (DEG > 0 ? DEG : 1)], ahead_b[NP][2 * (DEG > 0 ? DEG : 1)];
+  auto look_ahead = [&]() {
+    if constexpr (DEG > 0) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        constexpr int kLast = V - 1;
+        const int c0 = 2 * i, c1 = min(2 * i + 1, kLast);
+#pragma unroll
+        for (int k = 0; k < DEG; ++k) {
+          ahead_f[i][2 * k] = *reinterpret_cast<const short*>(&counts[pred_at[c0][k]]);
+          ahead_f[i][2 * k + 1] = *reinterpret_cast<const short*>(&counts[pred_at[c1][k]]);
+          ahead_b[i][2 * k] = *reinterpret_cast<const short*>(&counts[succ_at[c0][k]]);
+          ahead_b[i][2 * k + 1] = *reinterpret_cast<const short*>(&counts[succ_at[c1][k]]);
+        }
+      }
+    }
+  };
 
   // per-set state
   long long set = ((long long)blockIdx.x * waves_per_block + wave) * cpw + seg;   // the first set of a segment is its global index
@@ -525,6 +544,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         else if (longest == 1) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
       }
+      look_ahead();
     }
     Lanes picked = 0;
     auto take_step = [&](const unsigned step, Item& now, const Item& last) {
@@ -537,18 +557,12 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         constexpr int kLast = V - 1;
         const int c0 = 2 * i, c1 = min(2 * i + 1, kLast);
         if (DEG > 0) {
-          auto both = [&](int at0, int at1) {
-            pair16 v;
-            v.x = *reinterpret_cast<const short*>(&counts[at0]);
-            v.y = *reinterpret_cast<const short*>(&counts[at1]);
-            return v;
-          };
-          f_ahead[i] = both(pred_at[c0][0], pred_at[c1][0]);
-          b_ahead[i] = both(succ_at[c0][0], succ_at[c1][0]);
+          f_ahead[i] = pair16{ahead_f[i][0], ahead_f[i][1]};
+          b_ahead[i] = pair16{ahead_b[i][0], ahead_b[i][1]};
 #pragma unroll
           for (int k = 1; k < DEG; ++k) {
-            f_ahead[i] = __builtin_elementwise_min(f_ahead[i], both(pred_at[c0][k], pred_at[c1][k]));
-            b_ahead[i] = __builtin_elementwise_min(b_ahead[i], both(succ_at[c0][k], succ_at[c1][k]));
+            f_ahead[i] = __builtin_elementwise_min(f_ahead[i], pair16{ahead_f[i][2 * k], ahead_f[i][2 * k + 1]});
+            b_ahead[i] = __builtin_elementwise_min(b_ahead[i], pair16{ahead_b[i][2 * k], ahead_b[i][2 * k + 1]});
           }
         } else {
           int fa[2], ba[2];
@@ -592,7 +606,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
       picked = SLIDE ? some_fb : __ballot((any_fb | any_w) != 0u);
       const Lanes picked_f = some_fb & is_f, picked_b = some_fb & ~is_f;
       // the interleaved priority's turn
-      turn_at -= of(hit, 1, 0);
+      asm volatile("v_subb_co_u32 %0, vcc, %0, 0, %1" : "+v"(turn_at) : "s"(hit) : "vcc");   // (less 1 where it is)
       turn_at = turn_at < turn_end ? turn_begin : turn_at;
       auto by_type = [&](unsigned f, unsigned b, unsigned w) {
         const unsigned fb = of(is_f, f, b);
@@ -657,67 +671,90 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         own += first - own_at[0];
       }
       const unsigned j = V > 1 ? __builtin_amdgcn_ubfe(old, half, 16u) : old & 0xffffu, behind = j + 1u;
-      auto count = [&](unsigned& f, unsigned& b, unsigned& bl, unsigned& w, unsigned by) {
-        asm volatile("s_mov_b64 exec, %[is_b]\n\t"
-                     "v_add_u32 %[b], %[b], %[by]\n\t"
-                     "v_add_u32 %[bl], %[bl], %[by]\n\t"
-                     "s_mov_b64 exec, %[is_f]\n\t"
-                     "v_add_u32 %[f], %[f], %[by]\n\t"
-                     "s_mov_b64 exec, -1"
-                     : [b] "+&v"(b), [bl] "+&v"(bl), [f] "+&v"(f) : [by] "v"(by), [is_b] "s"(picked_b), [is_f] "s"(picked_f));
-        if constexpr (!SLIDE) w += of(picked & is_w, by, 0u);
-      };
-      if constexpr (V <= 2) {
-        count(n_f[0], n_b[0], n_bl[0], n_w[0], one);
-      } else {
-        count(n_f[0], n_b[0], n_bl[0], n_w[0], one & ~hi);
-        count(n_f[NP - 1], n_b[NP - 1], n_bl[NP - 1], n_w[NP - 1], one & hi);
+#define FPSCHED_COUNT                                                                                                    \
+  "s_mov_b64 exec, %[is_b]\n\t"                                                                                          \
+  "v_add_u32 %[b], %[b], %[by]\n\t"                                                                                     \
+  "v_add_u32 %[bl], %[bl], %[by]\n\t"                                                                                   \
+  "s_mov_b64 exec, %[is_f]\n\t"                                                                                          \
+  "v_add_u32 %[f], %[f], %[by]\n\t"                                                                                     \
+  "s_mov_b64 exec, -1"
+      if constexpr (V > 2) {
+        const unsigned by = one & ~hi;
+        asm volatile(FPSCHED_COUNT : [b] "+&v"(n_b[0]), [bl] "+&v"(n_bl[0]), [f] "+&v"(n_f[0]) : [by] "v"(by), [is_b] "s"(picked_b), [is_f] "s"(picked_f));
+        if constexpr (!SLIDE) n_w[0] += of(picked & is_w, by, 0u);
       }
+      const unsigned by = V > 2 ? one & hi : one;
       const Lanes counted = SLIDE ? picked : some_fb;
-      asm volatile("s_mov_b64 exec, %[counted]\n\t"
-                   "ds_write_b32 %[own], %[behind]\n\t"
-                   "s_mov_b64 exec, -1"
-                   : : [own] "v"(own), [behind] "v"(behind), [counted] "s"(counted) : "memory");
       if constexpr (SLIDE) {
         asm volatile("s_mov_b64 exec, %[all]\n\t"
+                     "ds_write_b32 %[own], %[behind]\n\t"
                      "v_lshl_add_u32 %[slot], %[j], 2, %[slots]\n\t"
                      "v_max_u32 %[next], %[step], %[next]\n\t"
-                     "v_add_u32 %[next], 1, %[next]\n\t"
-                     "s_mov_b64 exec, %[is_b]\n\t"
-                     "v_add_u32 %[next], 1, %[next]\n\t"
-                     "s_mov_b64 exec, -1"
-                     : [next] "+&v"(next_step), [slot] "+&v"(now.slot)
-                     : [j] "v"(j), [slots] "v"(slot), [step] "s"(step), [all] "s"(picked), [is_b] "s"(picked_b));
+                     "v_addc_co_u32 %[next], vcc, 1, %[next], %[is_b]\n\t" FPSCHED_COUNT
+                     : [b] "+&v"(n_b[NP - 1]), [bl] "+&v"(n_bl[NP - 1]), [f] "+&v"(n_f[NP - 1]), [next] "+&v"(next_step), [slot] "+&v"(now.slot)
+                     : [by] "v"(by), [own] "v"(own), [behind] "v"(behind), [j] "v"(j), [slots] "v"(slot), [step] "s"(step), [all] "s"(counted),
+                       [is_b] "s"(picked_b), [is_f] "s"(picked_f)
+                     : "memory", "vcc");
       } else {
+        asm volatile("s_mov_b64 exec, %[all]\n\t"
+                     "ds_write_b32 %[own], %[behind]\n\t" FPSCHED_COUNT
+                     : [b] "+&v"(n_b[NP - 1]), [bl] "+&v"(n_bl[NP - 1]), [f] "+&v"(n_f[NP - 1])
+                     : [by] "v"(by), [own] "v"(own), [behind] "v"(behind), [all] "s"(counted), [is_b] "s"(picked_b), [is_f] "s"(picked_f)
+                     : "memory");
+        n_w[NP - 1] += of(picked & is_w, by, 0u);
         next_step = of(picked, step + 1u, next_step);
         if (TIMED) now.slot = of(picked, slot + j * 4u, now.slot);
       }
+#undef FPSCHED_COUNT
+      look_ahead();
       if constexpr (TIMED) {
-        // the new item's row is on its way while the last step's is timed: cost, where its inputs' finish times
-        // are and where its own goes (byte offsets), memory
+        // the last step's items are timed
+        ready += last.a.z;
+        if (DEG > 1) ready = max(ready, ready2 + last.b.w);
+        const unsigned out_at = last.slot + ((unsigned)last.a.y >> 16), out_at2 = DEG > 1 ? last.slot + ((unsigned)last.b.z >> 16) : 0u;
+        if constexpr (SLIDE) {
+          [[maybe_unused]] unsigned wait;
+          // (all W items of an actor together cost less than 2^29)
+#define FPSCHED_TIME                                                                                                     \
+  "s_mov_b64 exec, %[timed]\n\t"                                                                                         \
+  "v_max_i32 %[start], %[free], %[start]\n\t"                                                                           \
+  "v_sub_u32 %[wait], %[start], %[free]\n\t"                                                                            \
+  "v_min_u32 %[wait], 0x1fffffff, %[wait]\n\t"                                                                          \
+  "v_lshl_or_b32 %[wait], %[wait], 3, %[event]\n\t"                                                                     \
+  "v_add_u32 %[free], %[start], %[cost]\n\t"                                                                            \
+  "ds_write_b32 %[at], %[wait]\n\t"                                                                                     \
+  "v_add_u32 %[at], 0x100, %[at]\n\t"                                                                                   \
+  "ds_write_b32 %[out], %[free]\n\t"
+          if constexpr (DEG > 1) {
+            asm volatile(FPSCHED_TIME
+                         "ds_write_b32 %[out2], %[free]\n\t"
+                         "v_and_or_b32 %[at], %[at], %[mask], %[ring]\n\t"
+                         "s_mov_b64 exec, -1"
+                         : [start] "+&v"(ready), [free] "+&v"(free_at), [at] "+&v"(ring_in), [wait] "=&v"(wait)
+                         : [event] "v"(last.a.w), [cost] "v"(last.a.x), [out] "v"(out_at), [out2] "v"(out_at2), [mask] "s"(ring_mask), [ring] "v"(ring), [timed] "s"(timed)
+                         : "memory");
+          } else {
+            asm volatile(FPSCHED_TIME
+                         "v_and_or_b32 %[at], %[at], %[mask], %[ring]\n\t"
+                         "s_mov_b64 exec, -1"
+                         : [start] "+&v"(ready), [free] "+&v"(free_at), [at] "+&v"(ring_in), [wait] "=&v"(wait)
+                         : [event] "v"(last.a.w), [cost] "v"(last.a.x), [out] "v"(out_at), [mask] "s"(ring_mask), [ring] "v"(ring), [timed] "s"(timed)
+                         : "memory");
+          }
+#undef FPSCHED_TIME
+        } else if (in(timed)) {
+          free_at = max(free_at, ready) + last.a.x;
+          lds_write<int>(out_at, free_at);
+          if (DEG > 1) lds_write<int>(out_at2, free_at);
+          mem += last.b.x;
+          peak = max(peak, mem);
+          mem -= last.b.y;
+        }
+        // the new item's row is on its way until the next step: cost, where its inputs' finish times are and where its own goes
+        // (byte offsets), memory
         const unsigned next_row = __umul24(pick, (unsigned)D) + by_type(row_f, row_b, row_b + V * D * 16);
         now.a = lds_read<int4>(next_row);
         if (kSecondHalves) now.b = lds_read<int4>(next_row + n_rows * 16);
-        if (in(timed)) {
-          const int4 a = last.a, b = last.b;
-          ready += a.z;
-          if (DEG > 1) ready = max(ready, ready2 + b.w);
-          const int start = max(free_at, ready);
-          if (SLIDE) {
-            // (all W items of an actor together cost less than 2^29)
-            const unsigned wait = min((unsigned)(start - free_at), 0x1fffffffu);
-            lds_write<unsigned>(ring_in, wait << 3 | (unsigned)a.w);
-            ring_in = on_ring(ring_in + 256u);
-          }
-          free_at = start + a.x;
-          lds_write<int>(last.slot + ((unsigned)a.y >> 16), free_at);
-          if (DEG > 1) lds_write<int>(last.slot + ((unsigned)b.z >> 16), free_at);
-          if (!SLIDE) {
-            mem += b.x;
-            peak = max(peak, mem);
-            mem -= b.y;
-          }
-        }
       } else {
         if (in(picked)) {
           const unsigned word = (by_type(1u, 2u, 3u) << 13) | (pick >> kPositionBit << 11) | j;
