@@ -684,6 +684,17 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         if constexpr (!SLIDE) n_w[0] += of(picked & is_w, by, 0u);
       }
       const unsigned by = V > 2 ? one & hi : one;
+      if constexpr (TIMED) {
+        // The new item's row is on its way until the next step: cost, where its inputs' finish times are and where its own goes
+        // (byte offsets), memory.  (What is read in front of the counters is there when it is asked for; behind them it would be
+        // waited for with them.)
+        const unsigned next_row = __umul24(pick, (unsigned)D) + by_type(row_f, row_b, row_b + V * D * 16);
+        now.a = lds_read<int4>(next_row);
+        if (kSecondHalves) now.b = lds_read<int4>(next_row + n_rows * 16);
+        // (not before the row's place is known: the inputs' times are on their way until here)
+        asm volatile("v_add_u32 %0, %0, %1" : "+v"(ready) : "v"(last.a.z), "v"(next_row), "v"(behind));
+        if (DEG > 1) ready = max(ready, ready2 + last.b.w);
+      }
       const Lanes counted = SLIDE ? picked : some_fb;
       if constexpr (SLIDE) {
         asm volatile("s_mov_b64 exec, %[all]\n\t"
@@ -709,8 +720,6 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
       look_ahead();
       if constexpr (TIMED) {
         // the last step's items are timed
-        ready += last.a.z;
-        if (DEG > 1) ready = max(ready, ready2 + last.b.w);
         const unsigned out_at = last.slot + ((unsigned)last.a.y >> 16), out_at2 = DEG > 1 ? last.slot + ((unsigned)last.b.z >> 16) : 0u;
         if constexpr (SLIDE) {
           [[maybe_unused]] unsigned wait;
@@ -750,11 +759,6 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           peak = max(peak, mem);
           mem -= last.b.y;
         }
-        // the new item's row is on its way until the next step: cost, where its inputs' finish times are and where its own goes
-        // (byte offsets), memory
-        const unsigned next_row = __umul24(pick, (unsigned)D) + by_type(row_f, row_b, row_b + V * D * 16);
-        now.a = lds_read<int4>(next_row);
-        if (kSecondHalves) now.b = lds_read<int4>(next_row + n_rows * 16);
       } else {
         if (in(picked)) {
           const unsigned word = (by_type(1u, 2u, 3u) << 13) | (pick >> kPositionBit << 11) | j;
