@@ -263,26 +263,34 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   unsigned event = 0u;
   Lanes has_event = 0;
   const unsigned ring_mask = ring_bytes - 256u;
-  // one round: the oldest stashed W item runs if what is left of the gap has room for it; else the gap's item starts, and
-  // the next one's gap opens
+  // one round: the oldest stashed W item runs if what is left of the gap has room for it; unless there is room for the one behind it
+  // too, the gap's item starts, and the next one's gap opens
   auto settle = [&]() {
     const unsigned next = lds_read<unsigned>(ring_out);
-    unsigned dur = (unsigned)w_dur[0], freed = (unsigned)w_free[0], units = (unsigned)f_units[0];
+    unsigned dur = (unsigned)w_dur[0], freed = (unsigned)w_free[0], units = (unsigned)f_units[0], dur_behind = dur;
+    const unsigned q_behind = q_out + 1u;
+    Lanes unseen = 0;   // the one behind it is in the queue's next word: looked at in the next round
     if constexpr (V > 1) {
       const unsigned word = lds_read<unsigned>(queue + q_out / kQueueEntries * 256u);
       if constexpr (V == 2) {
         const Lanes second = __ballot(__builtin_amdgcn_ubfe(word, q_out, 1u) != 0u), of_second = __ballot((event & 1u) != 0u);
+        const Lanes second_behind = __ballot(__builtin_amdgcn_ubfe(word, q_behind, 1u) != 0u);
+        dur_behind = of(second_behind, (unsigned)w_dur[V - 1], dur);
         dur = of(second, (unsigned)w_dur[V - 1], dur);
         freed = of(second, (unsigned)w_free[V - 1], freed);
         units = of(of_second, (unsigned)f_units[V - 1], units);
       } else {
         const unsigned c = word >> (q_out % kQueueEntries * kQueueBits) & 3u;
+        dur_behind = (unsigned)gen_pick<V>(w_dur, word >> q_behind % kQueueEntries * kQueueBits & 3u);
         dur = (unsigned)gen_pick<V>(w_dur, c);
         freed = (unsigned)gen_pick<V>(w_free, c);
         units = (unsigned)gen_pick<V>(f_units, event & 3u);
       }
+      unseen = __ballot(q_behind % kQueueEntries == 0u);
     }
-    const Lanes run_w = __ballot(q_in != q_out) & __ballot(dur <= gap), start = has_event & ~run_w, is_b = __ballot((event & 4u) != 0u);
+    const Lanes run_w = __ballot(q_in != q_out) & __ballot(dur <= gap);
+    const Lanes stay = run_w & (unseen | (__ballot(q_in != q_behind) & __ballot(dur + dur_behind <= gap)));
+    const Lanes start = has_event & ~stay, is_b = __ballot((event & 4u) != 0u);
     const Lanes more = __ballot(ring_in != ring_out);
     [[maybe_unused]] unsigned scratch;
     // a B item's W item is stashed
@@ -325,9 +333,9 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
                  : [placed] "+&v"(w_placed), [out] "+&v"(q_out), [mem] "+&v"(mem), [peak] "+&v"(peak), [gap] "+&v"(gap), [event] "+&v"(event),
                    [at] "+&v"(ring_out)
                  : [dur] "v"(dur), [freed] "v"(freed), [units] "v"(units), [next] "v"(next), [ring] "v"(ring), [mask] "s"(ring_mask), [runs] "s"(run_w),
-                   [starts] "s"(start & ~is_b), [opens] "s"(~run_w), [more] "s"(more)
+                   [starts] "s"(start & ~is_b), [opens] "s"(~stay), [more] "s"(more)
                  : "scc");
-    has_event = (has_event & run_w) | (more & ~run_w);
+    has_event = (has_event & stay) | (more & ~stay);
   };
 
   // the actor's own counters, two stages per register
@@ -605,9 +613,6 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
       const Lanes some_fb = __ballot(any_fb != 0u), is_w = SLIDE ? 0ull : ~some_fb;
       picked = SLIDE ? some_fb : __ballot((any_fb | any_w) != 0u);
       const Lanes picked_f = some_fb & is_f, picked_b = some_fb & ~is_f;
-      // the interleaved priority's turn
-      asm volatile("v_subb_co_u32 %0, vcc, %0, 0, %1" : "+v"(turn_at) : "s"(hit) : "vcc");   // (less 1 where it is)
-      turn_at = turn_at < turn_end ? turn_begin : turn_at;
       auto by_type = [&](unsigned f, unsigned b, unsigned w) {
         const unsigned fb = of(is_f, f, b);
         return SLIDE ? fb : of(is_w, w, fb);
@@ -617,9 +622,10 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
       // ... then the stage.  (From here on all lanes do what those with an item need; where that changes the actor's state
       // it is done for those only.  A branch around it would make the items' timing wait for what stands behind it.)
       unsigned pick = 0u;   // chunk << kPositionBit
+      [[maybe_unused]] unsigned walk = 0u;
+      [[maybe_unused]] Lanes move = 0;
       if constexpr (V > 1) {
-        const unsigned walk = by_type(walk_f, walk_b, kOneItem);
-        Lanes move;
+        walk = by_type(walk_f, walk_b, kOneItem);
         if constexpr (V == 2) {
           // the eligible ones with the position's half in the low half: it is taken unless it is not eligible or has had
           // its items and the other one is eligible
@@ -647,10 +653,6 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           pick = ((unsigned)of(move, moved_to, p0) & 3u) << kPositionBit;
         }
         asm("" : "+v"(pick));   // (not taken apart again)
-        const unsigned left = of(move, of(is_f, again_f, again_b), walk - kOneItem);
-        const unsigned walked = (left & ~kPosition) | pick;
-        walk_f = of(moving_f & picked_f, walked, walk_f);
-        walk_b = of(moving_b & picked_b, walked, walk_b);
       }
       // ---- write phase: the choice becomes visible for the next step; the counter's old value is the micro-batch of the
       // item.  Counts go up with the lanes of each type in turn, one instruction each.  (next_step: SLIDE, a step in which
@@ -765,6 +767,15 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           reinterpret_cast<uint16_t*>(staging + ((len >> 1) & (kStagingWords - 1)) * 64)[len & 1] = (uint16_t)word;
           len += 1;
         }
+      }
+      // The traversal's and the interleaved priority's next state: while the counters are on their way (not before them).
+      asm volatile("v_subb_co_u32 %0, vcc, %0, 0, %2" : "+v"(turn_at), "+v"(walk) : "s"(hit) : "vcc");   // (less 1 where it is)
+      turn_at = turn_at < turn_end ? turn_begin : turn_at;
+      if constexpr (V > 1) {
+        const unsigned left = of(move, of(is_f, again_f, again_b), walk - kOneItem);
+        const unsigned walked = (left & ~kPosition) | pick;
+        walk_f = of(moving_f & picked_f, walked, walk_f);
+        walk_b = of(moving_b & picked_b, walked, walk_b);
       }
       __builtin_amdgcn_wave_barrier();
     };
