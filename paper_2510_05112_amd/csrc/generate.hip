@@ -192,6 +192,9 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   // 32-byte pieces, not a quarter of that.  They are stored between the steps: the lanes fill up at different steps, and in
   // most steps some lane would.
   uint32_t* staging = reinterpret_cast<uint32_t*>(counts + n_count_ints) + lane;   // dword i at + i * 64
+  // (a lane's place in them: the dword from bit 8 on, its half in bit 1; what stands between is not looked at)
+  const unsigned staging_at = lds_address(staging);
+  constexpr unsigned kPlaceMask = (unsigned)(kStagingWords - 1) << 8 | 2u;
   // TIMED: slots never hold anything but finish times (an item without an input reads some word of
   // them and adds -2^30)
   if (TIMED)
@@ -388,7 +391,9 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   // turn: an item of the type whose turn it is counts down from unit_f - 1 to -unit_b and then begins anew
   int turn_at = 0, turn_end = 0, turn_begin = 0;
   bool live = false;   // the set's process is still running
-  int status = 0, len = 0, stored = 0;
+  int status = 0, stored = 0;
+  unsigned place = 0u;   // of the next op word
+  auto words_at = [](unsigned p) -> int { return (int)(p >> 8 << 1 | (p >> 1 & 1u)); };
   unsigned first_step = 0u;   // the loop's step counter when the set's process began
   // the step behind the one in which this actor scheduled its last item so far (first_step: none).  SLIDE: the step behind
   // the last W item if those up to here filled the steps from then on in which nothing else is eligible
@@ -447,6 +452,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           }
         } else if (has_set && has_dev) {
           // rows are END-padded to the stride; words still staged (less than 16) go out with the padding
+          const int len = words_at(place);
           int at = len & ~15;
           if (len & 15) {
             for (int i = len & 15; i < 16; ++i) reinterpret_cast<uint16_t*>(staging + (((at + i) >> 1) & (kStagingWords - 1)) * 64)[i & 1] = 0;
@@ -535,7 +541,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           for (int i = 0; i < NP; ++i) { n_f[i] = n_b[i] = n_w[i] = (unsigned)m * 0x00010001u; }
         live = any_in_segment(__ballot(any_item));
         first_step = step_0; steps = 0; next_step = step_0;
-        status = set_bad ? 4 : 0; len = 0; stored = 0;
+        status = set_bad ? 4 : 0; place = 0u; stored = 0;
         free_at = 0; mem = 0; peak = 0;
         ring_in = ring; ring_out = ring; event = 0u; gap = 0u; q_in = 0u; q_out = 0u; q_tail = 0u; w_placed = 0;
         if (!TIMED) row = ops + (size_t)(has_row ? set * D + d : 0) * (size_t)stride;
@@ -715,8 +721,10 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
                      : [by] "v"(by), [own] "v"(own), [behind] "v"(behind), [all] "s"(counted), [is_b] "s"(picked_b), [is_f] "s"(picked_f)
                      : "memory");
         n_w[NP - 1] += of(picked & is_w, by, 0u);
-        next_step = of(picked, step + 1u, next_step);
-        if (TIMED) now.slot = of(picked, slot + j * 4u, now.slot);
+        if (TIMED) {
+          next_step = of(picked, step + 1u, next_step);
+          now.slot = of(picked, slot + j * 4u, now.slot);
+        }
       }
 #undef FPSCHED_COUNT
       look_ahead();
@@ -762,11 +770,14 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           mem -= last.b.y;
         }
       } else {
-        if (in(picked)) {
-          const unsigned word = (by_type(1u, 2u, 3u) << 13) | (pick >> kPositionBit << 11) | j;
-          reinterpret_cast<uint16_t*>(staging + ((len >> 1) & (kStagingWords - 1)) * 64)[len & 1] = (uint16_t)word;
-          len += 1;
-        }
+        const unsigned word = (pick << (11u - kPositionBit) | by_type(1u << 13, 2u << 13, 3u << 13)) | j, at = (place & kPlaceMask) + staging_at;
+        asm volatile("s_mov_b64 exec, %[all]\n\t"
+                     "ds_write_b16 %[at], %[word]\n\t"
+                     "v_or_b32 %[place], 0xfc, %[place]\n\t"
+                     "v_add_u32 %[place], 2, %[place]\n\t"
+                     "v_mov_b32 %[next], %[behind]\n\t"
+                     "s_mov_b64 exec, -1"
+                     : [place] "+&v"(place), [next] "+&v"(next_step) : [at] "v"(at), [word] "v"(word), [behind] "s"(step + 1u), [all] "s"(picked) : "memory");
       }
       // The traversal's and the interleaved priority's next state: while the counters are on their way (not before them).
       asm volatile("v_subb_co_u32 %0, vcc, %0, 0, %2" : "+v"(turn_at), "+v"(walk) : "s"(hit) : "vcc");   // (less 1 where it is)
@@ -787,7 +798,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
     // later step can then; SLIDE: W items, on which nothing depends, aside), and stays ended, so the few steps a segment
     // runs on change nothing, and the number of steps the process took is one more than the step of its last item.
     const bool any_pick = any_in_segment(picked);
-    if (!TIMED && len - stored >= 16) {
+    if (!TIMED && words_at(place) - stored >= 16) {
       const uint32_t* w = staging + ((stored >> 1) & (kStagingWords - 1)) * 64;
       uint4* dst = reinterpret_cast<uint4*>(row + stored);
       dst[0] = make_uint4(w[0], w[64], w[128], w[192]);
