@@ -2123,6 +2123,26 @@ static GenShape gen_shape(const fpsched_problem* p, int64_t n_sets, int64_t sets
                   4 * (shared_ints + best_waves * wave_ints)};
 }
 
+// What a device's two stages wait for, forward and backward, is on one other device each (kGenOneNeighbour): a chain laid round the
+// devices, but not up and down again.
+static bool one_neighbour(const fpsched_problem* p) {
+  if (max_chunks_of(p) != 2 || p->max_degree > 1) return false;
+  const std::vector<int32_t>& I = p->host_ints;
+  const DevTables& G = p->tables;
+  for (int d = 0; d < p->D; ++d)
+    for (int dir = 0; dir < 2; ++dir) {
+      int other = -1;
+      for (int c = 0; c < p->n_chunks[d]; ++c) {
+        const int off = dir == 0 ? G.off_pred_off : G.off_succ_off, s = p->local_stage[(size_t)d * kMaxChunks + c];
+        if (I[off + s] >= I[off + s + 1]) continue;
+        const int of = p->stage_device[I[(dir == 0 ? G.off_pred_stage : G.off_succ_stage) + I[off + s]]];
+        if (other >= 0 && other != of) return false;
+        other = of;
+      }
+    }
+  return true;
+}
+
 static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_policy, const int32_t* d_inflight,
                  const int64_t* d_select, int64_t n_src, int64_t n_sets, int32_t stride_words, uint16_t* d_ops, int32_t* d_steps,
                  uint8_t* d_status, void* d_workspace, size_t workspace_bytes, void* hip_stream) {
@@ -2156,7 +2176,7 @@ static int run_generate(const fpsched_problem* p, const fpsched_actor_policy* d_
       {&generate_kernel<1, 0, kGenPlain>, &generate_kernel<1, 1, kGenPlain>, &generate_kernel<1, 2, kGenPlain>},
       {&generate_kernel<2, 0, kGenPlain>, &generate_kernel<2, 1, kGenPlain>, &generate_kernel<2, 2, kGenPlain>},
       {&generate_kernel<4, 0, kGenPlain>, &generate_kernel<4, 1, kGenPlain>, &generate_kernel<4, 2, kGenPlain>}};
-  const GenKernel kernel = table[V == 1 ? 0 : (V == 2 ? 1 : 2)][deg];
+  const GenKernel kernel = one_neighbour(p) ? &generate_kernel<2, kGenOneNeighbour, kGenPlain> : table[V == 1 ? 0 : (V == 2 ? 1 : 2)][deg];
   if (shape.lds_bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                           p->max_lds) != hipSuccess)
@@ -2249,7 +2269,8 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
       {{&generate_kernel<1, 1, kGenSlide>, &generate_kernel<1, 2, kGenSlide>},
        {&generate_kernel<2, 1, kGenSlide>, &generate_kernel<2, 2, kGenSlide>},
        {&generate_kernel<4, 1, kGenSlide>, &generate_kernel<4, 2, kGenSlide>}}};
-  const GenKernel kernel = table[slide ? 1 : 0][V == 1 ? 0 : (V == 2 ? 1 : 2)][deg - 1];
+  const GenKernel kernel = V == 2 && one_neighbour(p) ? (slide ? &generate_kernel<2, kGenOneNeighbour, kGenSlide> : &generate_kernel<2, kGenOneNeighbour, kGenTimed>)
+                                                      : table[slide ? 1 : 0][V == 1 ? 0 : (V == 2 ? 1 : 2)][deg - 1];
   if (shape.lds_bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                           p->max_lds) != hipSuccess)

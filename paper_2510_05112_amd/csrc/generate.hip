@@ -117,6 +117,10 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 // V = bound on the stages per device (1, 2, 4).  DEG = bound on the DAG in- and out-degree of a
 // stage (1 or 2): the LDS addresses of the neighbours' counters are then kept in registers;
 // DEG = 0 walks the edge lists in LDS instead (any degree).
+// GRAPH: DEG, or kGenOneNeighbour (V = 2, DEG = 1): what an actor's two stages wait for in a direction is on one actor, as in a chain
+// laid round the devices.  An actor's two counters of a direction are then one word, read with one instruction instead of two, its
+// halves put in order for the reader (a stage that waits for nothing finds m): 32,768 sets of 16 x 64 x 2 through lists 3012 and 2996 us,
+// 16,384 of 32 x 128 x 2, sliding, with the winners 4480 and 4441 us.
 //
 // The grid is persistent: a segment (the lanes of one parameter set) that finishes its schedule
 // writes it out, draws the next set from a global counter and starts over while the other segments
@@ -150,12 +154,15 @@ __global__ void generate_order_kernel(DevTables T, const int32_t* __restrict__ i
 // some lane's ring is nearly full: its rounds are then full of work, where in the step itself a few lanes' W items
 // would be waited for by all.  The stash is a queue of log2(V) bits per entry
 // (the chunk) in LDS: an actor stashes no more than V * m items, so entry i simply stands in word i * log2(V) / 32.
-template <int V, int DEG, int FORM>
+template <int V, int GRAPH, int FORM>
 __global__ __launch_bounds__(kGenThreads) void generate_kernel(
     DevTables T, const int32_t* __restrict__ policy, const int32_t* __restrict__ inflight,
     const long long* __restrict__ select, long long n_src, long long n_sets, int n_classes, int stride,
     uint16_t* __restrict__ ops, int32_t* __restrict__ out_steps, unsigned char* out_status,
     unsigned long long* __restrict__ next_set, GenResults R) {
+  constexpr bool ONE_NEIGHBOUR = GRAPH == kGenOneNeighbour;
+  constexpr int DEG = ONE_NEIGHBOUR ? 1 : GRAPH;
+  static_assert(!ONE_NEIGHBOUR || V == 2, "");
   constexpr bool TIMED = FORM != kGenPlain;
   constexpr bool SLIDE = FORM == kGenSlide;
   constexpr int NP = (V + 1) / 2;   // pairs of stages
@@ -228,6 +235,30 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         if (se < T.ints[T.off_succ_off + s + 1]) succ_at[c][k] = base + S + T.ints[T.off_succ_stage + se];
       }
     }
+  }
+
+  // ONE_NEIGHBOUR: counters [direction][device] instead, and where the neighbours' are; which bytes of such a word and of m the stages'
+  // counters are (v_perm)
+  unsigned ahead_at[2] = {lds_address(counts + at_m), lds_address(counts + at_m)}, ahead_bytes[2] = {0x01000100u, 0x01000100u};
+  const unsigned both_m = (unsigned)m * 0x00010001u;
+  if constexpr (ONE_NEIGHBOUR) {
+    // (where each stage is, in the place of the counters until the first set)
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+      if (c < nch) counts[base + stage[c]] = d * kMaxChunks + c;
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+#pragma unroll
+      for (int dir = 0; dir < 2; ++dir) {
+        if (c >= nch) continue;
+        const int first = dir == 0 ? T.off_pred_off : T.off_succ_off, s = stage[c];
+        if (T.ints[first + s] >= T.ints[first + s + 1]) continue;
+        const int other = T.ints[(dir == 0 ? T.off_pred_stage : T.off_succ_stage) + T.ints[first + s]];
+        const int at = counts[base + other];
+        ahead_at[dir] = lds_address(counts + base + dir * D + at / kMaxChunks);
+        ahead_bytes[dir] = (ahead_bytes[dir] & ~(0xffffu << 16 * c)) | (at % kMaxChunks == 0 ? 0x0504u : 0x0706u) << 16 * c;
+      }
+    own_at[0] = lds_address(counts + (has_dev ? base + d : at_m));
   }
 
   // TIMED: what the actor's items cost together, and its memory cap
@@ -355,14 +386,18 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   Item items_of[2] = {{make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0), slot}, {make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0), slot}};
   Lanes items = 0;
   // where the actor's counters are: of chunk 0, and how much further that of the last chunk is (V == 2)
-  const unsigned own_f = own_at[0], own_b = own_at[0] + 4u * (unsigned)S;
+  const unsigned own_f = own_at[0], own_b = own_at[0] + 4u * (unsigned)(ONE_NEIGHBOUR ? D : S);
   const int own_step = (int)(own_at[V - 1] - own_at[0]);
 
   // The neighbouring stages' counters (DEG > 0: two of each pair, as they stand in LDS), requested as soon as a step's own counters
   // have been stored: on their way while the step's items are timed.
   short ahead_f[NP][2 * (DEG > 0 ? DEG : 1)], ahead_b[NP][2 * (DEG > 0 ? DEG : 1)];
+  unsigned ahead_words[2] = {0u, 0u};
   auto look_ahead = [&]() {
-    if constexpr (DEG > 0) {
+    if constexpr (ONE_NEIGHBOUR) {
+      ahead_words[0] = lds_read<unsigned>(ahead_at[0]);
+      ahead_words[1] = lds_read<unsigned>(ahead_at[1]);
+    } else if constexpr (DEG > 0) {
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         constexpr int kLast = V - 1;
@@ -570,7 +605,10 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
       for (int i = 0; i < NP; ++i) {
         constexpr int kLast = V - 1;
         const int c0 = 2 * i, c1 = min(2 * i + 1, kLast);
-        if (DEG > 0) {
+        if (ONE_NEIGHBOUR) {
+          f_ahead[i] = pair_of(__builtin_amdgcn_perm(ahead_words[0], both_m, ahead_bytes[0]));
+          b_ahead[i] = pair_of(__builtin_amdgcn_perm(ahead_words[1], both_m, ahead_bytes[1]));
+        } else if (DEG > 0) {
           f_ahead[i] = pair16{ahead_f[i][0], ahead_f[i][1]};
           b_ahead[i] = pair16{ahead_b[i][0], ahead_b[i][1]};
 #pragma unroll
@@ -669,7 +707,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
       if constexpr (V <= 2) {
         old = by_type(n_f[0], n_b[0], n_w[0]);
         // (the second chunk's counter: the upper half of `one` is 1)
-        if constexpr (V == 2) asm("v_mad_i32_i16 %0, %1, %2, %0 op_sel:[1,0,0,0]" : "+v"(own) : "v"(one), "v"(own_step));
+        if constexpr (V == 2 && !ONE_NEIGHBOUR) asm("v_mad_i32_i16 %0, %1, %2, %0 op_sel:[1,0,0,0]" : "+v"(own) : "v"(one), "v"(own_step));
       } else {
         hi = mask_of((pick & 32u) != 0u);
         old = choose(hi, by_type(n_f[NP - 1], n_b[NP - 1], n_w[NP - 1]), by_type(n_f[0], n_b[0], n_w[0]));
@@ -678,7 +716,7 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         for (int c = 1; c < V; ++c) first = pick == (unsigned)c << kPositionBit ? own_at[c] : first;
         own += first - own_at[0];
       }
-      const unsigned j = V > 1 ? __builtin_amdgcn_ubfe(old, half, 16u) : old & 0xffffu, behind = j + 1u;
+      const unsigned j = V > 1 ? __builtin_amdgcn_ubfe(old, half, 16u) : old & 0xffffu, behind = ONE_NEIGHBOUR ? old + one : j + 1u;
 #define FPSCHED_COUNT                                                                                                    \
   "s_mov_b64 exec, %[is_b]\n\t"                                                                                          \
   "v_add_u32 %[b], %[b], %[by]\n\t"                                                                                     \
@@ -845,6 +883,9 @@ FPSCHED_INSTANTIATE(4, 1, true)
 FPSCHED_INSTANTIATE(1, 2, true)
 FPSCHED_INSTANTIATE(2, 2, true)
 FPSCHED_INSTANTIATE(4, 2, true)
+FPSCHED_INSTANTIATE(2, kGenOneNeighbour, kGenPlain)
+FPSCHED_INSTANTIATE(2, kGenOneNeighbour, kGenTimed)
+FPSCHED_INSTANTIATE(2, kGenOneNeighbour, kGenSlide)
 FPSCHED_INSTANTIATE(1, 1, kGenSlide)
 FPSCHED_INSTANTIATE(2, 1, kGenSlide)
 FPSCHED_INSTANTIATE(4, 1, kGenSlide)

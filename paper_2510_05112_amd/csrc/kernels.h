@@ -123,6 +123,7 @@ constexpr int kGenThreads = 256;   // of a workgroup: a wavefront per SIMD
 constexpr int kGenPlain = 0, kGenTimed = 1, kGenSlide = 2;
 constexpr int kGenFewEvents = 16, kGenMoreEvents = 32;   // kGenSlide: items noted per lane (T.gen_events)
 constexpr int kGenStagingWords = 16;   // kGenPlain: dwords of op words staged per lane
+constexpr int kGenOneNeighbour = 3;   // GRAPH of generate_kernel: two stages per actor, whose neighbours in a direction are on one actor
 template <int V, int DEG, int FORM>
 __global__ void generate_kernel(DevTables T, const int32_t* policy, const int32_t* inflight, const long long* select,
                                 long long n_src, long long n_sets, int n_classes, int stride, uint16_t* ops,
