@@ -2242,6 +2242,14 @@ static int run_generate_evaluate(const fpsched_problem* p, const fpsched_actor_p
   const int64_t lds_ints = p->max_lds / 4;
   int cpw = 64 / p->D;
   while (cpw > 1 && shared_ints + wave_ints_of(cpw) + 64 > lds_ints) --cpw;
+  // Sliding: the rounds in which items are settled are made for all lanes when some lane's ring is full, so a set is done sooner the
+  // fewer others its wavefront has; up to two sets per SIMD there is a wavefront for each SIMD's share.  Full wavefronts and these, 32
+  // to 1,024 sets: 2 x 32 x 2 124 and 102 to 110 us, 8 x 32 x 2 230 to 244 and 189 to 207, 8 x 48 x 1 121 to 135 and 103 to 115, 16 x 64 x 2
+  // 628 to 658 and 560 to 615, 16 x 32 x 4 1270 to 1321 and 1190 to 1297, 32 x 128 x 2 2023 to 2220 and 1937 to 2101 (at 512 sets 2075
+  // and 2101); 2,048 sets: 8 x 32 x 2 243 and 226, 16 x 64 x 2 704 and 650, 2 x 32 x 2 124 and 125; 4,096 (as many, so four each) 8 x 32 x
+  // 2 258 and 241, but 4 x 24 x 1 57.5 and 59.2, 2 x 32 x 2 124 and 127.  (Results without sliding: no difference.)
+  const int64_t n_simds = 4ll * p->n_cu;
+  if (slide && n_sets <= 2 * n_simds) cpw = (int)std::clamp<int64_t>((n_sets + n_simds - 1) / n_simds, 1, cpw);
   if (shared_ints + wave_ints_of(cpw) > lds_ints) return FPSCHED_EUNSUPPORTED;
   tables.gen_sets = cpw;
   GenShape shape = gen_shape(p, n_sets, cpw, shared_ints, wave_ints_of(cpw));
