@@ -189,18 +189,18 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 // ... the plain form.  (FOLLOW: for rows that another row follows in the place of the next word's, in the form with second
 // edges)
 #define FPSCHED_STEP(S, AHEAD, FOLLOW, NOT_FOLLOWED)                                                                     \
-  "s_waitcnt lgkmcnt(2)\n\t"                                                                                            \
-  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                       \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                             \
+  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                        \
   "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
-  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t"                                                                    \
-  "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"                                                                       \
-  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                 \
-  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"                                                                      \
-  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
-  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
-  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                          \
-  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t" FOLLOW                                                      \
-  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t" NOT_FOLLOWED                                                           \
+  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t"                                                                     \
+  "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"                                                                        \
+  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                  \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                         \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                  \
+  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"                                                                       \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                           \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t" FOLLOW                                                       \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t" NOT_FOLLOWED                                                            \
   FPSCHED_NEXT_WORD(S)
 #define FPSCHED_NEXT_WORD(S)                                                                                             \
   "v_or_b32 %[" #S "_pos], 0xfc, %[" #S "_pos]\n\t"                                                                     \
@@ -216,7 +216,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "v_add3_u32 %[" #O "_at], %[" #O "_at], " FPSCHED_##O##_W ", %[slots]\n\t"                                            \
   "ds_read_b32 %[" #O "_in], %[" #O "_at]\n\t"
 #define FPSCHED_PLAIN_STEP(S, AHEAD) FPSCHED_STEP(S, AHEAD, "", "")
-#define FPSCHED_PLAIN_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "1")
+#define FPSCHED_PLAIN_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2")
 // lanes whose row (its mask) has another one behind it fetch that and stay at their word
 #define FPSCHED_FOLLOW(S)                                                                                                \
   "v_cmp_lt_u32 vcc, 0x3ffff, " FPSCHED_##S##_Z "\n\t"                                                                  \
@@ -237,42 +237,42 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 // place of the word behind it, read already).  The few ops that waited 2^16 time units or more cannot be rebuilt from the low
 // half of their start times and go to the row's escape list, while that has room: position << 8 | wait >> 16.
 #define FPSCHED_TIMES_STEP(S, AHEAD)                                                                                     \
-  "s_waitcnt lgkmcnt(2)\n\t"                                                                                            \
-  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                       \
+  "s_waitcnt lgkmcnt(3)\n\t"                                                                                             \
+  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                        \
   "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
-  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t"                                                                    \
-  "v_lshrrev_b32 %[start], 8, %[t]\n\t"                                                                                 \
-  "v_sub_u32 %[wait], %[t], %[" #S "_free]\n\t"                                                                         \
-  "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"                                                                       \
-  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                 \
-  "ds_write_b16 %[" #S "_own], %[start]\n\t"                                                                            \
-  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"                                                                      \
-  "v_cmp_lt_u32 vcc, %[most], %[wait]\n\t"                                                                              \
-  "s_mov_b64 exec, vcc\n\t"                                                                                             \
-  "s_cbranch_execz 1f\n\t"                                                                                              \
-  "v_cmp_lt_i32 vcc, 0, %[" #S "_room]\n\t"                                                                             \
-  "s_mov_b64 exec, vcc\n\t"                                                                                             \
-  "v_lshrrev_b32 %[t], 8, %[" #S "_pos]\n\t"                                                                            \
-  "v_bfe_u32 %[start], %[" #S "_pos], 1, 1\n\t"                                                                         \
-  "v_lshl_or_b32 %[t], %[t], 1, %[start]\n\t"                                                                           \
-  "v_add_u32 %[t], -1, %[t]\n\t"                                                                                        \
-  "v_lshrrev_b32 %[wait], 24, %[wait]\n\t"                                                                              \
-  "v_lshl_or_b32 %[t], %[t], 8, %[wait]\n\t"                                                                            \
-  "global_store_dword %[" #S "_escape], %[t], off\n\t"                                                                  \
-  "v_lshl_add_u64 %[" #S "_escape], %[" #S "_escape], 0, 4\n\t"                                                         \
-  "v_add_u32 %[" #S "_room], -1, %[" #S "_room]\n\t"                                                                    \
-  "1:\n\t"                                                                                                              \
-  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
-  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
-  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                          \
-  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                             \
-  "v_mov_b32 %[" #S "_own], %[" #S "_at_next]\n\t"                                                                      \
-  "v_or_b32 %[" #S "_pos], 0xfc, %[" #S "_pos]\n\t"                                                                     \
-  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                        \
-  "v_add_u32 %[" #S "_pos], 2, %[" #S "_pos]\n\t"                                                                       \
-  "v_bitop3_b32 %[" #S "_at_next], %[" #S "_pos], %[mask], %[" #S "_ring] bitop3:0x6a\n\t"                              \
-  "v_lshlrev_b32 %[" #S "_j], 2, %[" #S "_next]\n\t"                                                                    \
-  "ds_read_u16 %[" #S "_next], %[" #S "_at_next]\n\t"                                                                   \
+  "v_max_u32 %[start], %[" #S "_free], %[" #S "_in]\n\t"                                                                 \
+  "v_add_u32 %[t], %[start], " FPSCHED_##S##_Y "\n\t"                                                                    \
+  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                  \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                         \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                  \
+  "v_sub_u32 %[wait], %[start], %[" #S "_free]\n\t"                                                                      \
+  "v_lshrrev_b32 %[start], 8, %[start]\n\t"                                                                              \
+  "ds_write_b16 %[" #S "_own], %[start]\n\t"                                                                             \
+  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"                                                                       \
+  "v_cmp_lt_u32 vcc, %[most], %[wait]\n\t"                                                                               \
+  "s_cbranch_vccz 1f\n\t"                                                                                                \
+  "v_cmp_lt_i32 %[far], 0, %[" #S "_room]\n\t"                                                                          \
+  "s_and_b64 exec, vcc, %[far]\n\t"                                                                                     \
+  "v_lshrrev_b32 %[t], 8, %[" #S "_pos]\n\t"                                                                             \
+  "v_bfe_u32 %[start], %[" #S "_pos], 1, 1\n\t"                                                                          \
+  "v_lshl_or_b32 %[t], %[t], 1, %[start]\n\t"                                                                            \
+  "v_add_u32 %[t], -1, %[t]\n\t"                                                                                         \
+  "v_lshrrev_b32 %[wait], 24, %[wait]\n\t"                                                                               \
+  "v_lshl_or_b32 %[t], %[t], 8, %[wait]\n\t"                                                                             \
+  "global_store_dword %[" #S "_escape], %[t], off\n\t"                                                                   \
+  "v_lshl_add_u64 %[" #S "_escape], %[" #S "_escape], 0, 4\n\t"                                                          \
+  "v_add_u32 %[" #S "_room], -1, %[" #S "_room]\n\t"                                                                     \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                  \
+  "1:\n\t"                                                                                                               \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t"                                                                           \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                              \
+  "v_mov_b32 %[" #S "_own], %[" #S "_at_next]\n\t"                                                                       \
+  "v_or_b32 %[" #S "_pos], 0xfc, %[" #S "_pos]\n\t"                                                                      \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                         \
+  "v_add_u32 %[" #S "_pos], 2, %[" #S "_pos]\n\t"                                                                        \
+  "v_bitop3_b32 %[" #S "_at_next], %[" #S "_pos], %[mask], %[" #S "_ring] bitop3:0x6a\n\t"                               \
+  "v_lshlrev_b32 %[" #S "_j], 2, %[" #S "_next]\n\t"                                                                     \
+  "ds_read_u16 %[" #S "_next], %[" #S "_at_next]\n\t"                                                                    \
   "s_mov_b64 exec, -1\n\t"
 #define FPSCHED_TIMES_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2")
 #define FPSCHED_LEFT(S)                                                                                                  \
@@ -280,37 +280,39 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 #define FPSCHED_TIMES_ROUNDS(TEXT)                                                                                       \
   asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
-                 FPSCHED_LEFT(even), FPSCHED_LEFT(odd), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited) \
+                 FPSCHED_LEFT(even), FPSCHED_LEFT(odd), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited), [far] "=&s"(long_waits) \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [most] "s"(0xffffffu)       \
                : "memory", "vcc", "scc")
 
 // ... the forms with link occupancy and costs per micro-batch.  COST: how the op's cost and tag are added to its start; SEND:
 // when the value leaves over the link, and until when that keeps the link busy; LINK_ROW: the next op's link row is fetched in
 // front of its row.  With the slot, the other half's link word and cost are read ahead.
-#define FPSCHED_COST_STEP(S, AHEAD, COST, SEND, REQUESTED, LINK_ROW)                                                     \
-  "s_waitcnt lgkmcnt(" REQUESTED ")\n\t"                                                                                \
-  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                       \
+#define FPSCHED_COST_STEP(S, AHEAD, COST, LEAVE, BUSY, SEND, REQUESTED, LINK_ROW)                                        \
+  "s_waitcnt lgkmcnt(" REQUESTED ")\n\t"                                                                                 \
+  "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                        \
   "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
-  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t" COST                                                               \
-  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t" SEND                                                                 \
-  "ds_write_b32 %[" #S "_at], %[t]\n\t"                                                                                 \
-  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                        \
-  "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
-  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t" LINK_ROW                                                                 \
-  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                             \
-  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                        \
+  "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t" COST LEAVE                                                          \
+  "s_mov_b64 exec, -1\n\t" AHEAD                                                                                         \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t" BUSY                                                                             \
+  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t" SEND                                                                  \
+  "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t" LINK_ROW                                                                  \
+  "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                              \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                         \
   FPSCHED_NEXT_WORD(S)
 #define FPSCHED_COST_PLAIN(S) "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"
 #define FPSCHED_COST_TABLE(S)                                                                                            \
-  "v_add_u32 %[" #S "_busy], %[" #S "_busy], %[" #S "_cost]\n\t"                                                        \
-  "v_lshl_add_u32 %[t], %[" #S "_cost], 8, %[t]\n\t"                                                                    \
+  "v_lshl_add_u32 %[t], %[" #S "_cost], 8, %[t]\n\t"                                                                     \
   "v_add_u32_sdwa %[t], %[t], " FPSCHED_##S##_Y " dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+#define FPSCHED_COST_BUSY(S) "v_add_u32 %[" #S "_busy], %[" #S "_busy], %[" #S "_cost]\n\t"
+#define FPSCHED_LEAVE(S) "ds_write_b32 %[" #S "_at], %[t]\n\t"
+#define FPSCHED_LEAVE_LINK(S)                                                                                            \
+  "v_and_or_b32 %[u], " FPSCHED_##S##_Y ", %[byte], %[" #S "_sent]\n\t"                                                  \
+  "v_max_u32 %[" #S "_in], %[t], %[u]\n\t"                                                                               \
+  "ds_write_b32 %[" #S "_at], %[" #S "_in]\n\t"
 #define FPSCHED_SEND_LINK(S)                                                                                             \
-  "v_and_or_b32 %[u], " FPSCHED_##S##_Y ", %[byte], %[" #S "_sent]\n\t"                                                 \
-  "v_max_u32 %[t], %[t], %[u]\n\t"                                                                                      \
-  "v_lshrrev_b32 %[" #S "_sent], 16, %[" #S "_link]\n\t"                                                                \
-  "v_and_b32 %[u], 0xffffff00, %[t]\n\t"                                                                                \
-  "v_lshl_add_u32 %[u], %[" #S "_sent], 8, %[u]\n\t"                                                                    \
+  "v_lshrrev_b32 %[" #S "_sent], 16, %[" #S "_link]\n\t"                                                                 \
+  "v_and_b32 %[u], 0xffffff00, %[" #S "_in]\n\t"                                                                         \
+  "v_lshl_add_u32 %[u], %[" #S "_sent], 8, %[u]\n\t"                                                                     \
   "ds_write_b32 %[" #S "_link_at], %[u]\n\t"
 #define FPSCHED_LINK_ROW(S)                                                                                              \
   "v_mad_u32_u24 %[u], %[t], %[link_stride], %[" #S "_link_rows]\n\t"                                                   \
@@ -320,14 +322,14 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "ds_read_b32 %[" #O "_sent], %[" #O "_link_at]\n\t"
 #define FPSCHED_AHEAD_COST(O, SHIFT, READ)                                                                               \
   "v_lshrrev_b32 %[" #O "_cost], 8, " FPSCHED_##O##_Y "\n\t"                                                            \
-  "v_bfe_u32 %[t], %[" #O "_j], 2, 11\n\t"                                                                              \
-  "v_lshl_add_u32 %[" #O "_cost], %[t], " SHIFT ", %[" #O "_cost]\n\t" READ " %[" #O "_cost], %[" #O "_cost]\n\t"
-#define FPSCHED_LINKS_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_PLAIN(S), FPSCHED_SEND_LINK(S), "3", FPSCHED_LINK_ROW(S))
+  "v_bfe_u32 %[u], %[" #O "_j], 2, 11\n\t"                                                                              \
+  "v_lshl_add_u32 %[" #O "_cost], %[u], " SHIFT ", %[" #O "_cost]\n\t" READ " %[" #O "_cost], %[" #O "_cost]\n\t"
+#define FPSCHED_LINKS_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_PLAIN(S), FPSCHED_LEAVE_LINK(S), "", FPSCHED_SEND_LINK(S), "4", FPSCHED_LINK_ROW(S))
 #define FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_LINK(O)
-#define FPSCHED_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), "", "2", "")
-#define FPSCHED_MB1_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "1") FPSCHED_AHEAD_COST(O, "0", "ds_read_u8")
-#define FPSCHED_MB2_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "1") FPSCHED_AHEAD_COST(O, "1", "ds_read_u16")
-#define FPSCHED_LINKS_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_SEND_LINK(S), "3", FPSCHED_LINK_ROW(S))
+#define FPSCHED_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_LEAVE(S), FPSCHED_COST_BUSY(S), "", "2", "")
+#define FPSCHED_MB1_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_COST(O, "0", "ds_read_u8")
+#define FPSCHED_MB2_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_COST(O, "1", "ds_read_u16")
+#define FPSCHED_LINKS_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_LEAVE_LINK(S), FPSCHED_COST_BUSY(S), FPSCHED_SEND_LINK(S), "4", FPSCHED_LINK_ROW(S))
 #define FPSCHED_LINKS_MB1_AHEAD(O) FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_COST(O, "0", "ds_read_u8")
 #define FPSCHED_LINKS_MB2_AHEAD(O) FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_COST(O, "1", "ds_read_u16")
 #define FPSCHED_COST_STATE(S)                                                                                            \
@@ -362,7 +364,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "ds_read_u16 %[" #S "_next], %[t]\n\t"                                                                                \
   "s_mov_b64 exec, -1\n\t"
 #define FPSCHED_WIDE_AHEAD(O)                                                                                            \
-  "s_waitcnt lgkmcnt(1)\n\t"                                                                                            \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                             \
   "v_and_b32 %[" #O "_at], %[" #O "_j], " FPSCHED_##O##_Z "\n\t"                                                        \
   "v_add_u32_sdwa %[" #O "_at], %[" #O "_at], " FPSCHED_##O##_W " dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"     \
   "v_add_u32 %[" #O "_at], %[" #O "_at], %[slots]\n\t"                                                                  \
@@ -925,6 +927,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     unsigned long long moved_even = 0ull, moved_odd = 0ull;
     if constexpr (STRAIGHT) {
       [[maybe_unused]] unsigned in_even, in_odd, at_even, at_odd, scratch, scratch2, start_time, waited;
+      [[maybe_unused]] unsigned long long long_waits;
       [[maybe_unused]] unsigned link_at_even, link_at_odd, sent_even, sent_odd, cost_even, cost_odd;
       if constexpr (SYNC) {
 #pragma unroll
