@@ -164,6 +164,7 @@ struct ListTables {
   int32_t off_sync;         // synchronisation form: group rows, in ints (0: another form)
   int32_t off_check;        // order rows, in ints
   int32_t n_check_ints;
+  int32_t check_columns;    // order rows in LDS: columns of each (kind, chunk), a power of two from D on; 0: device by device
   int32_t check_shared_bytes;   // order rows and dev rows in LDS, a multiple of 16
   int32_t off_dev;          // in ints
   int32_t state_bytes;      // states of one row in the order pass: an odd number of dwords
@@ -177,6 +178,7 @@ constexpr unsigned kRowTwoOut = 1u << 30;
 constexpr int list_dense_row_bytes(const ListTables& T) { return kNKinds * kMaxChunks * 16 * T.D; }
 constexpr int list_behind_rows(const ListTables& T) { return T.row_bytes - list_dense_row_bytes(T); }
 constexpr int list_table_bytes(const ListTables& T) { return list_behind_rows(T) + 4 * T.n_time_ints; }
+constexpr int kCheckColumns = 32;   // of 8 bytes, all banks
 constexpr int kRowColumns = 16;   // of 16 bytes, all banks (timing.hip); column c is of the pair of devices c modulo their number
 constexpr int kGroupRow = -1;
 constexpr unsigned kGroupIn = 1u << 16, kGroupOut = 1u << 17;

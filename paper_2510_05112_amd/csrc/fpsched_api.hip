@@ -302,6 +302,36 @@ WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
   return WorkgroupShape{0, 1};
 }
 
+// The launch shape of the order pass, with as many rows per wavefront as the states leave room for, and where its table stands.
+// Columns of eight bytes, a power of two of them for each (kind, chunk): as many as are all banks, with the devices over and
+// over in them where they are a power of two themselves, so that no two lanes of half a wavefront that are at different rows
+// read the same bank.  Fewer columns where those would cost a wavefront, and the rows of a device side by side, which take no
+// more than the rows themselves, where these would too.  (Columns against rows [kind][chunk][device], the row found by a
+// multiplication: 65,536 candidates of 32 devices, 128 micro-batches, two chunks, 2,588 and 2,575 us; of 16 devices and 64,
+// 2,298 and 2,276 us.  Device by device on the same two: 2,601 and 2,342 us.)
+WorkgroupShape check_shape(ListTables* T, int64_t max_lds, int* rows) {
+  WorkgroupShape best{0, 1};
+  for (*rows = 64; *rows >= 4; *rows >>= 1) {
+    T->check_wave_bytes = (*rows * T->state_bytes + 15) & ~15;
+    for (int columns : {0, next_pow2(T->D), std::max(next_pow2(T->D), kCheckColumns)}) {
+      const int shared = (4 * (2 * kNKinds * kMaxChunks * (columns > 0 ? columns : T->D) + 2 * T->D) + 15) & ~15;
+      const WorkgroupShape shape = workgroup_shape(shared, T->check_wave_bytes, max_lds, kCheckMaxThreads / 64, kCheckWavesPerSimd, true);
+      if (shape.waves < 1 || shape.waves * shape.groups < best.waves * best.groups) continue;
+      best = shape;
+      T->check_columns = columns;
+      T->check_shared_bytes = shared;
+    }
+    if (best.waves >= 1) break;
+  }
+  return best;
+}
+
+void take_check_place(const ListTables& from, ListTables* to) {
+  to->check_columns = from.check_columns;
+  to->check_shared_bytes = from.check_shared_bytes;
+  to->check_wave_bytes = from.check_wave_bytes;
+}
+
 // Edge slots of an op: an input and the output that continues its class share one, an output (or input) of a class of its
 // own has one.
 struct EdgeSlot { int32_t cls; const StageEdge* in; bool out; };
@@ -357,7 +387,6 @@ bool fill_list_image(const fpsched_problem* p, const std::vector<StageEdges>& ed
   T.off_check = T.n_time_ints;
   T.n_check_ints = kNKinds * kMaxChunks * D * 2;
   T.off_dev = T.off_check + T.n_check_ints;
-  T.check_shared_bytes = (4 * (T.n_check_ints + 2 * D) + 15) & ~15;
   T.cand_slots = (int32_t)cand_slots;
   T.terminal = p->has_w ? kDone : kBDone;
   T.unit_scale = (int32_t)unit_scale;
@@ -477,17 +506,11 @@ void build_list_tables(fpsched_problem* p, const std::vector<StageEdges>& edges,
   p->variants_tab = T;
   p->variants_image = *image;
   if (deg2 && !wide && !fill_list_image(p, edges, n_classes, n_classes, wide, true, items, &T, &deg2, image)) return;
-  // order pass: as many rows per wavefront as the states leave room for
-  WorkgroupShape check{0, 1};
   int rows = 64;
-  for (; rows >= 4; rows >>= 1) {
-    T.check_wave_bytes = (rows * T.state_bytes + 15) & ~15;
-    check = workgroup_shape(T.check_shared_bytes, T.check_wave_bytes, p->max_lds, kCheckMaxThreads / 64, kCheckWavesPerSimd, true);
-    if (check.waves >= 1) break;
-  }
+  const WorkgroupShape check = check_shape(&T, p->max_lds, &rows);
   const WorkgroupShape time = timing_shape(&T, slot_bytes, p->max_lds);
   if (check.waves < 1 || time.waves < 1) return;
-  p->variants_tab.check_wave_bytes = T.check_wave_bytes;
+  take_check_place(T, &p->variants_tab);
   p->check_rows_per_wave = rows;
   p->check_waves = check.waves;
   p->check_grid = p->n_cu * check.groups;
@@ -1278,6 +1301,10 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   const int64_t check_waves = check_blocks * cw, per_wave = (row_waves + check_waves - 1) / check_waves;
   const int draw_blocks = (int)(per_wave <= 8 ? per_wave : per_wave / 4);
   const bool dynamic = row_waves > check_waves * draw_blocks;
+  // (Copies of the columns cost a workgroup more than they save in one block of rows: 1,024 candidates of 4 devices, whole
+  // evaluation, 24.3 and 24.0 us)
+  ListTables check = T;
+  if (row_waves <= check_waves) check.check_columns = std::min(T.check_columns, next_pow2(T.D));
   // (How the rows are read, see there)
   const bool shared = (row_waves + draw_blocks - 1) / draw_blocks > 8 * (int64_t)p->n_cu && check_waves > 8 * (int64_t)p->n_cu && stride_words >= 64;
   if (dynamic) {
@@ -1285,7 +1312,7 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
     if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   }
   hipLaunchKernelGGL(check_kernel_of(p->check_vbits, starts != nullptr, shared), dim3((unsigned)check_blocks), dim3(64 * cw),
-                     (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, T, d_ops, (long long)n_rows,
+                     (size_t)(T.check_shared_bytes + (int64_t)cw * T.check_wave_bytes), st, check, d_ops, (long long)n_rows,
                      (int)stride_words, (int)rpw, idle, out.peak, counter, first_drawn, draw_blocks, (int)dynamic);
   if (hipGetLastError() != hipSuccess) return FPSCHED_EHIP;
   const bool deg2 = variant ? variant->deg2 : p->lists_deg2;
@@ -1826,7 +1853,7 @@ static void build_sync_slot_tables(fpsched_problem* p, const std::vector<int32_t
             rows.insert(rows.end(), of_group, of_group + 8);
           }
       rows.resize((rows.size() + 7) & ~(size_t)7, 0);
-      LT.check_wave_bytes = p->ltab.check_wave_bytes;   // (the order pass is launched as for the plain model)
+      take_check_place(p->ltab, &LT);   // (the order pass is launched as for the plain model)
       LT.off_sync = old_ints;
       LT.n_time_ints += (int32_t)rows.size();
       LT.off_check += (int32_t)rows.size();

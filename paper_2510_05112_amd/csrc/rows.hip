@@ -83,7 +83,21 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   // where the timing pass draws its candidates from (dynamic: set, with the counter of this pass behind it, by a kernel
   // in front of this one)
   if (!dynamic && blockIdx.x == 0 && tid == 0) *counter = counter_value;
-  for (int i = tid; i < T.n_check_ints + 2 * T.D; i += blockDim.x) lds[i] = T.ints[T.off_check + i];
+  // The order rows, in columns or device by device (check_shape), and the dev rows.  The number of columns is a power of two:
+  // the row of a word is where a shift and a mask leave the word's top five bits.
+  constexpr int kRows = kNKinds * kMaxChunks;
+  const int columns = T.check_columns, n_row_ints = 2 * kRows * (columns > 0 ? columns : T.D);
+  const bool repeated = (T.D & (T.D - 1)) == 0;   // column c is of device c modulo D
+  for (int i = tid; i < (kRows + 1) * T.D; i += blockDim.x) {
+    const int2 from = reinterpret_cast<const int2*>(T.ints + T.off_check)[i];
+    const int row = repeated ? i >> __builtin_ctz(T.D) : (int)((unsigned)i / (unsigned)T.D), of = i - row * T.D;
+    int at = columns > 0 ? row * columns + of : of * kRows + (row ^ (of & (kRows - 1))), n = repeated && columns > 0 ? columns : 1;
+    if (row == kRows) at = n_row_ints / 2 + of, n = 1;
+    for (int c = 0; c < n; c += T.D, at += T.D) {
+      lds[2 * at] = from.x;
+      lds[2 * at + 1] = from.y;
+    }
+  }
   const unsigned lds0 = lds_address(lds);
   const int m = T.m;
   // the states of this wavefront's rows, then of this lane's: one byte per (chunk, micro-batch), m + 1 bytes per chunk
@@ -94,8 +108,11 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   // workgroup per few blocks, a compute unit's LDS stays with the workgroup until its last row has ended, and with equal
   // shares the slowest wavefronts took a third longer than the average one.
   const long long n_blocks = (n_rows + rows_per_wave - 1) / rows_per_wave;
-  const unsigned row_bytes = (unsigned)T.D * 8u;
-  const unsigned dev_table = lds0 + (unsigned)T.n_check_ints * 4u;
+  const unsigned row_bytes = columns > 0 ? (unsigned)columns * 8u : 8u;
+  const unsigned dev_table = lds0 + (unsigned)n_row_ints * 4u;
+  // (from vector registers: an operand from a scalar one doubles what the instruction costs)
+  unsigned shift_low = 11u - (unsigned)__builtin_ctz(row_bytes), shift_high = shift_low + 16u, row_mask = 31u * row_bytes;
+  asm volatile("" : "+v"(shift_low), "+v"(shift_high), "+v"(row_mask));
   // The row that this lane walks, and the words of it or of the next one that are on their way or in registers: 64 bytes of
   // each row at a time, requested when the walk of those in front of them begins.  SHARED: by the row's four neighbouring
   // lanes, sixteen bytes each, row after row; what has arrived is then handed round among them.
@@ -160,9 +177,9 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   for (int i = lane * 16; i < T.check_wave_bytes; i += 1024) lds_write<lds_int4>(wave_states + i, lds_int4{0, 0, 0, 0});
   const lds_int2 dev = lds_read<lds_int2>(dev_table + (unsigned)d * 8u);
   const int n_chunks = dev.x, cap = dev.y;
-  const unsigned meta = lds0 + (unsigned)d * 8u;
+  const unsigned meta = lds0 + (columns > 0 ? (unsigned)(d + (repeated ? lane & (columns - 1) & -T.D : 0)) * 8u : (unsigned)d * 256u + ((unsigned)d & 31u) * 8u);
   // (the items of a chunk's stage stand in its row of kind 0: m, or fewer where an item is a group of micro-batches)
-  auto items_of = [&](unsigned c) -> int { return lds_read<int>(c * row_bytes + meta + 4u); };
+  auto items_of = [&](unsigned c) -> int { return lds_read<int>((c * row_bytes ^ meta) + 4u); };
   auto pad = [&](unsigned value) {
     for (int c = 0; c < n_chunks; ++c)
       for (int i = items_of((unsigned)c); i <= m; ++i) lds_write<uint8_t>(state + c * (m + 1) + i, (uint8_t)value);
@@ -185,7 +202,9 @@ __global__ __launch_bounds__(kCheckMaxThreads) __attribute__((amdgpu_waves_per_e
   auto word_of = [&](const uint4& q, int k) -> unsigned { return (k & 1) ? pair_word(q, k) >> 16 : pair_word(q, k) & 0xffffu; };
   const u16_pair per_chunk = {(unsigned short)(m + 1), (unsigned short)(m + 1)};
   const u16_pair limit = {(unsigned short)m, (unsigned short)m};
-  auto row_of = [&](const uint4& q, int k) -> unsigned { return __umul24(word_of(q, k) >> 11, row_bytes) + meta; };
+  auto row_of = [&](const uint4& q, int k) -> unsigned {
+    return __builtin_amdgcn_bitop3_b32(pair_word(q, k) >> ((k & 1) ? shift_high : shift_low), row_mask, meta, 0x6a);   // (a & b) ^ c
+  };
   auto fetch = [&](Group& G, const uint4& q) {
     G.q = q;
 #pragma unroll
