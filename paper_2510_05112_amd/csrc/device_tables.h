@@ -108,7 +108,7 @@ struct SlotTables {
   const int32_t* ints;      // DEVICE
 };
 
-// Tables of the two-pass list evaluation (rows.hip, timing.hip).  `ints` = [timing rows][link or group rows]
+// Tables of the two-pass list evaluation (rows.h, timing.hip).  `ints` = [timing rows][link or group rows]
 // [cost table][order rows][dev], those in the middle in their forms only:
 //   timing rows [kNKinds * 4][D, the even devices first] x 4 ints, addressed by the top five bits of the op word and
 //   the device:
@@ -178,6 +178,9 @@ constexpr unsigned kRowTwoOut = 1u << 30;
 constexpr int list_dense_row_bytes(const ListTables& T) { return kNKinds * kMaxChunks * 16 * T.D; }
 constexpr int list_behind_rows(const ListTables& T) { return T.row_bytes - list_dense_row_bytes(T); }
 constexpr int list_table_bytes(const ListTables& T) { return list_behind_rows(T) + 4 * T.n_time_ints; }
+// LDS of the order pass in a workgroup that does both passes; the timing pass's is behind it, from a multiple of the bytes of a
+// half's op windows on
+constexpr int alone_check_bytes(const ListTables& T, int waves) { return (T.check_shared_bytes + waves * T.check_wave_bytes + 2047) & ~2047; }
 constexpr int kCheckColumns = 32;   // of 8 bytes, all banks
 constexpr int kRowColumns = 16;   // of 16 bytes, all banks (timing.hip); column c is of the pair of devices c modulo their number
 constexpr int kGroupRow = -1;

@@ -1,5 +1,5 @@
 // Slot evaluation kernel: the variants of the cost model and the sliding pass (the modes below; the plain model is
-// rows.hip and timing.hip).  Any per-device op order, any stage DAG with at most two inputs and two outputs per
+// rows.h and timing.hip).  Any per-device op order, any stage DAG with at most two inputs and two outputs per
 // stage, a few KB of LDS per candidate.
 //
 // Mapping: a wavefront carries `cands_per_wave` candidate segments, lane = device inside

@@ -255,20 +255,29 @@ using TimeKernel = void (*)(ListTables, const uint16_t*, long long, int, long lo
 template <bool DEG2>
 TimeKernel time_kernel_of(const ListTables& T, bool wide) {
   const bool links = T.link_words > 0;
-  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false, 0>;
-  if (T.mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false, 0> : &time_lists_kernel<DEG2, false, false, 1, false, false, 0>;
-  if (T.mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false, 0> : &time_lists_kernel<DEG2, false, false, 2, false, false, 0>;
-  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false, 0> : &time_lists_kernel<DEG2, false, false, 0, false, false, 0>;
+  if (wide) return &time_lists_kernel<DEG2, true, false, 0, false, false, 0, 0>;
+  if (T.mb_bytes == 1) return links ? &time_lists_kernel<DEG2, false, true, 1, false, false, 0, 0> : &time_lists_kernel<DEG2, false, false, 1, false, false, 0, 0>;
+  if (T.mb_bytes == 2) return links ? &time_lists_kernel<DEG2, false, true, 2, false, false, 0, 0> : &time_lists_kernel<DEG2, false, false, 2, false, false, 0, 0>;
+  return links ? &time_lists_kernel<DEG2, false, true, 0, false, false, 0, 0> : &time_lists_kernel<DEG2, false, false, 0, false, false, 0, 0>;
 }
 // the form that reads these tables
 TimeKernel time_kernel_of(const ListTables& T, bool deg2, bool wide) {
-  if (T.off_sync > 0) return &time_lists_kernel<true, false, false, 0, true, false, 0>;
-  if (T.copy_depth > 4) return &time_lists_kernel<true, false, false, 0, false, false, FPSCHED_MAX_COPY_DEPTH>;
-  if (T.copy_depth > kCopyShallow) return &time_lists_kernel<true, false, false, 0, false, false, 4>;
-  if (T.copy_depth > 0) return &time_lists_kernel<true, false, false, 0, false, false, kCopyShallow>;
+  if (T.off_sync > 0) return &time_lists_kernel<true, false, false, 0, true, false, 0, 0>;
+  if (T.copy_depth > 4) return &time_lists_kernel<true, false, false, 0, false, false, 0, FPSCHED_MAX_COPY_DEPTH>;
+  if (T.copy_depth > kCopyShallow) return &time_lists_kernel<true, false, false, 0, false, false, 0, 4>;
+  if (T.copy_depth > 0) return &time_lists_kernel<true, false, false, 0, false, false, 0, kCopyShallow>;
   return deg2 ? time_kernel_of<true>(T, wide) : time_kernel_of<false>(T, wide);
 }
-TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true, 0>; }
+// both passes in one launch (null: second edges and times of two words, whose step has branches)
+template <bool DEG2, bool WIDE>
+TimeKernel alone_kernel_of(int vbits) {
+  return vbits == 0 ? &time_lists_kernel<DEG2, WIDE, false, 0, false, false, 1, 0>
+                    : (vbits == 1 ? &time_lists_kernel<DEG2, WIDE, false, 0, false, false, 2, 0> : &time_lists_kernel<DEG2, WIDE, false, 0, false, false, 3, 0>);
+}
+TimeKernel alone_kernel_of(int vbits, bool deg2, bool wide) {
+  return wide ? (deg2 ? nullptr : alone_kernel_of<false, true>(vbits)) : (deg2 ? alone_kernel_of<true, false>(vbits) : alone_kernel_of<false, false>(vbits));
+}
+TimeKernel times_kernel() { return &time_lists_kernel<false, false, false, 0, false, true, 0, 0>; }
 
 // What the list evaluation needs to know about one stage: per direction (0 forward, 1 backward) its inputs and outputs.
 struct StageEdge { int32_t cls, tag, latency; };
@@ -1086,8 +1095,9 @@ int fpsched_problem_create(const fpsched_problem_desc* desc, int device_id, int3
            hipMemcpy(p->d_list_ints, list_image.data(), list_image.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
       for (const void* kernel : {reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, false, false)),
                                  reinterpret_cast<const void*>(check_kernel_of(p->check_vbits, false, true)),
+                                 reinterpret_cast<const void*>(alone_kernel_of(p->check_vbits, p->lists_deg2, p->lists_wide)),
                                  reinterpret_cast<const void*>(time_kernel_of(p->ltab, p->lists_deg2, p->lists_wide))})
-        ok = ok && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess;
+        ok = ok && (!kernel || hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->max_lds) == hipSuccess);
       p->ltab.ints = p->d_list_ints;
       p->list_image = list_image;
     }
@@ -1279,13 +1289,42 @@ static uint32_t drawn_share(const fpsched_problem* p, const ListTables& T, bool 
 static int run_list_evaluation(const fpsched_problem* p, const ListVariant* variant, const uint16_t* d_ops, int64_t n_cand, int32_t stride_words,
                                const fpsched_results& out, unsigned long long* counter, hipStream_t st,
                                const StartTimes* starts = nullptr) {
-  const ListTables& T = variant ? variant->tab : p->ltab;
+  ListTables T = variant ? variant->tab : p->ltab;
   const int64_t n_rows = n_cand * p->D, rpw = p->check_rows_per_wave;
+  const int64_t n_cu = std::max(p->n_cu, 1), each = (n_cand + 4 * n_cu - 1) / (4 * n_cu);   // candidates for each SIMD
+  // Both passes in one launch where every wavefront has room for the rows and the lanes of its share, with one wavefront per SIMD, or two.  Two
+  // launches / one, 1,024 to 16,384 candidates, one wavefront per SIMD: 1.00 to 1.14 on 2 to 12 devices (at worst 0.99, 4 x 32 x 2), 1.01 to
+  // 1.06 on 16, 1.04 to 1.11 on 24 to 40.  Two: 1.04 to 1.15 where the timing rows have no columns (12, 24, 40 devices), 1.1 on
+  // 4 x 8 x 1; with columns and rows of 192 words and more 0.98 (8 x 32 x 2), 0.99 and 1.00 (16 x 64 x 2), 0.99 and 1.00 (32 x 128 x 2), 1.06 (32 x 64 x
+  // 1).  (A handful of candidates, which is no batch, stays with the two.)
+  const TimeKernel alone = variant ? nullptr : alone_kernel_of(p->check_vbits, p->lists_deg2, p->lists_wide);
+  const int64_t together = std::min<int64_t>({each, 64 / p->D, T.cands_per_wave});
+  const bool columns = T.odd_at != 16 * ((T.D + 1) / 2);
+  if (alone && n_cand >= kAloneLeast && n_cand <= together * n_cu * (columns && stride_words > 128 ? 4 : 8)) {
+    ListTables A = T;
+    const int64_t wavefronts = (n_cand + together - 1) / together;
+    const int waves = (int)((wavefronts + n_cu - 1) / n_cu);
+    A.cands_per_wave = (int)together;
+    A.check_columns = std::min(T.check_columns, next_pow2(T.D));
+    A.check_wave_bytes = ((int)together * T.D * T.state_bytes + 15) & ~15;
+    A.wave_bytes = (kTimeWindowBytes + (int)together * (p->lists_wide ? 8 : 4) * T.cand_slots + 31) & ~31;
+    const int64_t lds = alone_check_bytes(A, waves) + list_table_bytes(T) + (int64_t)waves * A.wave_bytes;
+    if (lds <= p->max_lds) {
+      hipLaunchKernelGGL(alone, dim3((unsigned)((wavefronts + waves - 1) / waves)), dim3(64 * waves), (size_t)lds, st, A, d_ops, (long long)n_cand,
+                         (int)stride_words, reinterpret_cast<long long*>(out.makespan), reinterpret_cast<long long*>(out.idle), out.peak, out.flags, (unsigned long long*)nullptr,
+                         1, 0u, StartTimes{});
+      return check_hip(hipGetLastError());
+    }
+  }
+  // (One candidate to a wavefront where there are no more than SIMDs: 800 of 11 x 45 x 2, links 163 and 152 us, costs 146 and 134, in
+  // microseconds 128 and 119; with two for each SIMD no such gain, 2,048 of 4 x 32 x 2 67.6 and 68.9.)
+  const int64_t grid = variant ? variant->grid : p->time_grid, max_waves = variant ? variant->waves : p->time_waves;
+  if (each == 1 && n_cand <= grid * max_waves) T.cands_per_wave = 1;
   // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
   const int64_t row_waves = (n_rows + rpw - 1) / rpw;
   const int cw = (int)std::clamp<int64_t>((row_waves + p->check_grid - 1) / p->check_grid, 1, p->check_waves);
   const int64_t check_blocks = std::min<int64_t>((row_waves + cw - 1) / cw, p->check_grid);
-  const int64_t cpw = T.cands_per_wave, grid = variant ? variant->grid : p->time_grid, max_waves = variant ? variant->waves : p->time_waves;
+  const int64_t cpw = T.cands_per_wave;
   const int tw = (int)std::clamp<int64_t>((n_cand + cpw * grid - 1) / (cpw * grid), 1, max_waves);
   const int64_t time_blocks = std::min<int64_t>((n_cand + cpw * tw - 1) / (cpw * tw), grid);
   long long* idle = reinterpret_cast<long long*>(out.idle);

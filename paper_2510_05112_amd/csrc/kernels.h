@@ -95,12 +95,14 @@ struct StartTimes {
   int32_t* stops;       // [n_cand][D]
   int32_t escape_cap, lanes;
 };
-template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int COPY>
+// ALONE: 1 + VBITS: both passes in one launch, from a batch of kAloneLeast candidates to as many as the wavefronts hold, T.cands_per_wave each, whose
+// rows are a lane's each (0: the timing pass only).
+constexpr int kAloneMaxThreads = 512, kAloneLeast = 64;
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int ALONE, int COPY>
 __global__ void time_lists_kernel(ListTables T, const uint16_t* ops, long long n_cand, int stride,
                                   long long* out_makespan, long long* out_idle, int* out_peak,
                                   unsigned char* out_flags, unsigned long long* next_candidate, int draw_block,
                                   unsigned draw_share, StartTimes starts);
-
 // counter[0] = value, counter[1] = value2
 __global__ void reset_counter_kernel(unsigned long long* counter, unsigned long long value, unsigned long long value2 = 0);
 

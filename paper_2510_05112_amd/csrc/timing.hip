@@ -1,4 +1,4 @@
-// Timing pass of the list evaluation: start and finish times across the devices, for lists the order pass (rows.hip)
+// Timing pass of the list evaluation: start and finish times across the devices, for lists the order pass (rows.h)
 // has walked.  Any per-device op order, any stage DAG with at most two inputs and two outputs per stage.
 //
 // Mapping: lane = (candidate, pair of neighbouring devices), ceil(D / 2) lanes per candidate, as many candidates per
@@ -89,7 +89,7 @@
 // to decode the next word; in LDS the slot read (random addresses: half of it bank conflicts), the row, the next word
 // and the slot written.  The row is fetched when the device issues and first looked at in its next step, so the other
 // half's step covers the wait.  That batch took 4.88 ms when one kernel with all devices in every round did the order
-// pass's work as well; then 1.10 ms (rows.hip) + 2.05 ms; the pass takes 1.72 ms since the step of the plain form is
+// pass's work as well; then 1.10 ms (rows.h) + 2.05 ms; the pass takes 1.72 ms since the step of the plain form is
 // without branches (FPSCHED_STEP below: half of the gain), the rings are read without bank conflicts and requests are
 // twice as large.
 //
@@ -107,6 +107,7 @@
 
 #include "kernels.h"
 #include "lds_access.h"
+#include "rows.h"
 
 namespace fpsched {
 
@@ -180,10 +181,11 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 // loop give, best and worst: plain form 1005 us at a multiple of 32 bytes, 1017 sixteen behind one (462 candidates of 36 x 117 x 4, the
 // whole evaluation); times of two words 189 and 191 (8,192 of 16 x 64 x 2), links with costs 588 and 591 (20,011 of 11 x 45 x 3), the best place
 // the same; synchronisation, whose two statements lie apart, 820 sixteen bytes behind it, 838 eight behind it (65,536 of 12 devices).
-#define FPSCHED_BEGIN ".ifndef .Lrounds_%c[form]\n\t.Lrounds_%c[form]:\n\t.endif\n\t"
-#define FPSCHED_PLACE_ROUNDS(AT)                                                                                         \
+// NAME: rounds, or alone in the kernel that does both passes.
+#define FPSCHED_BEGIN(NAME) ".ifndef .L" NAME "_%c[form]\n\t.L" NAME "_%c[form]:\n\t.endif\n\t"
+#define FPSCHED_PLACE_ROUNDS(NAME, AT)                                                                                         \
   asm volatile(".p2align 5\n\t"                                                                                         \
-               ".fill ((%c[at] - (.Lrounds_%c[form] - .Lplace_%c[form])) & 31) / 4, 4, 0xbf800000\n\t" /* (s_nop 0) */    \
+               ".fill ((%c[at] - (.L" NAME "_%c[form] - .Lplace_%c[form])) & 31) / 4, 4, 0xbf800000\n\t" /* (s_nop 0) */  \
                ".Lplace_%c[form]:" :: [form] "n"(kForm), [at] "n"(AT))
 
 // ... the plain form.  (FOLLOW: for rows that another row follows in the place of the next word's, in the form with second
@@ -227,8 +229,8 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "s_mov_b64 exec, %[" #S "_moved]\n\t"                                                                                 \
   "1:\n\t"
 #define FPSCHED_FOLLOW_STEP(S, AHEAD) FPSCHED_STEP(S, AHEAD, FPSCHED_FOLLOW(S), "s_andn2_b64 exec, exec, vcc\n\t")
-#define FPSCHED_ROUNDS(TEXT)                                                                                             \
-  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
+#define FPSCHED_ROUNDS(NAME, TEXT)                                                                                       \
+  asm volatile(FPSCHED_BEGIN(NAME) TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd), [t] "=&v"(scratch) \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [tables] "s"(behind)        \
                : "memory", "vcc", "scc")
@@ -278,7 +280,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 #define FPSCHED_LEFT(S)                                                                                                  \
   [S##_own] "+&v"(S.own_place), [S##_at_next] "+&v"(S.next_place), [S##_escape] "+&v"(S.escape), [S##_room] "+&v"(S.escape_room)
 #define FPSCHED_TIMES_ROUNDS(TEXT)                                                                                       \
-  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
+  asm volatile(FPSCHED_BEGIN("rounds") TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
                  FPSCHED_LEFT(even), FPSCHED_LEFT(odd), [t] "=&v"(scratch), [start] "=&v"(start_time), [wait] "=&v"(waited), [far] "=&s"(long_waits) \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [most] "s"(0xffffffu)       \
@@ -336,7 +338,7 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   [S##_link] "+&v"(S.link), [S##_busy] "+&v"(S.busy), [S##_link_at] "=&v"(link_at_##S), [S##_sent] "=&v"(sent_##S),       \
   [S##_cost] "=&v"(cost_##S)
 #define FPSCHED_COST_ROUNDS(TEXT)                                                                                        \
-  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
+  asm volatile(FPSCHED_BEGIN("rounds") TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [even_in] "=&v"(in_even), [odd_in] "=&v"(in_odd),             \
                  FPSCHED_COST_STATE(even), FPSCHED_COST_STATE(odd), [t] "=&v"(scratch), [u] "=&v"(scratch2)             \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [byte] "s"(0xffu),          \
@@ -369,14 +371,20 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "v_add_u32_sdwa %[" #O "_at], %[" #O "_at], " FPSCHED_##O##_W " dst_sel:DWORD src0_sel:DWORD src1_sel:WORD_1\n\t"     \
   "v_add_u32 %[" #O "_at], %[" #O "_at], %[slots]\n\t"                                                                  \
   "ds_read_b64 " FPSCHED_##O##_SLOT ", %[" #O "_at]\n\t"
-#define FPSCHED_WIDE_ROUNDS(TEXT)                                                                                        \
-  asm volatile(FPSCHED_BEGIN TEXT                                                                                        \
+#define FPSCHED_WIDE_ROUNDS(NAME, TEXT)                                                                                  \
+  asm volatile(FPSCHED_BEGIN(NAME) TEXT                                                                                        \
                : FPSCHED_STATE(even), FPSCHED_STATE(odd), [t] "=&v"(scratch)                                            \
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED                                              \
                : "memory", "scc", "v48", "v49", "v50", "v51")
 
-template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int COPY>
-__global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : 4))) void time_lists_kernel(
+// ALONE: both passes in one launch, behind the order pass of the same candidates, no more of them than segments (1 + VBITS of that pass, or
+// 0); for batches that leave the GPU one or two wavefronts per SIMD.  Such a batch takes as long as a candidate does: the start of a
+// kernel, its tables and the first words of the rows, in both of two kernels, are a part of it that is not small, and a step waits less
+// for LDS with fewer lanes in it, so the candidates are spread over all SIMDs.  Each wavefront walks the rows of its own candidates and
+// then times them.  Two launches / this one: 1,024 candidates of 4 x 8 x 1 19.0 and 15.5 us, 4,096 18.2 and 16.8, 1,024 of 8 x 32 x 2 108.9
+// and 101.3, of 16 x 64 x 2 162.4 and 155.2, 4,096 172.5 and 163.5, 2,048 of 24 x 30 x 2 100.0 and 90.2.
+template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int ALONE, int COPY>
+__global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : (ALONE ? kAloneMaxThreads : kTimeMaxThreads)) __attribute__((amdgpu_waves_per_eu(COPY ? kTimeCopyWavesPerSimd : (ALONE ? 2 : 4)))) void time_lists_kernel(
     ListTables T, const uint16_t* __restrict__ ops, long long n_cand, int stride, long long* __restrict__ out_makespan,
     long long* __restrict__ out_idle, int* __restrict__ out_peak, unsigned char* __restrict__ out_flags,
     unsigned long long* __restrict__ next_candidate, int draw_block, unsigned draw_share, StartTimes starts) {
@@ -391,12 +399,13 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   // pieces of a request.  (The 128-byte lines mostly do not stay in the L2 cache from one request to the next.)
   constexpr int kPieces = STRAIGHT ? 4 : 2;
   constexpr unsigned kSlotBytes = WIDE ? 8u : 4u;
-  [[maybe_unused]] constexpr int kForm = (DEG2 ? 1 : 0) + (WIDE ? 2 : 0) + (LINKS ? 4 : 0) + 8 * MB + (SYNC ? 32 : 0) + (TIMES ? 64 : 0);
+  [[maybe_unused]] constexpr int kForm = (DEG2 ? 1 : 0) + (WIDE ? 2 : 0) + (LINKS ? 4 : 0) + 8 * MB + (SYNC ? 32 : 0) + (TIMES ? 64 : 0) + 128 * ALONE;
   extern __shared__ int32_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int D = T.D, cpw = T.cands_per_wave, P = (D + 1) >> 1;
   // LDS: [op windows of all wavefronts][rows][the tables behind them][per wavefront: link words, slots]
-  const unsigned lds0 = lds_address(lds), tables = lds0 + (blockDim.x >> 6) * (unsigned)kTimeWindowBytes;
+  const unsigned lds_from = ALONE ? (unsigned)alone_check_bytes(T, (int)(blockDim.x >> 6)) : 0u;
+  const unsigned lds0 = lds_address(lds) + lds_from, tables = lds0 + (blockDim.x >> 6) * (unsigned)kTimeWindowBytes;
   const unsigned behind = tables + (unsigned)list_behind_rows(T);   // (of an offset in the image)
   // Rows with columns (fpsched_api.hip, timing_shape): a row read of sixteen bytes is served for sixteen lanes at a time, without bank
   // conflicts if these read sixteen different columns of 256 bytes, whatever kind and chunk each of them reads.  As dense as in the
@@ -416,6 +425,10 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     lds_write<lds_int4>(tables + (unsigned)i * 16u, R);
   }
   for (int i = 4 * image_rows + tid; i < T.n_time_ints; i += blockDim.x) lds_write<int>(behind + (unsigned)i * 4u, T.ints[i]);
+  if constexpr (ALONE != 0) {
+    check_rows<ALONE - 1, false, false>(T, ops, n_cand * D, stride, cpw * D, out_idle, out_peak, nullptr, 0ull, 1, 0, (int)blockDim.x);
+    __syncthreads();   // (what the rows' lanes have left in memory is read by the candidates')
+  }
   const int seg = lane / P, pair = lane - seg * P;
   const bool lane_ok = seg < cpw;
   const int d0 = 2 * pair;
@@ -843,7 +856,8 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   // (SYNC: an op takes in at most 2 m values, in every fourth round)
   const unsigned long long bound = (3ull * (unsigned)D * (unsigned)stride * (SYNC ? 4ull * (unsigned)T.m : 1ull) + 16ull) * ((unsigned long long)n_cand + 1ull);
   const unsigned max_rounds = bound > 0xfffffff0ull ? 0xfffffff0u : (unsigned)bound;
-  if constexpr (STRAIGHT) FPSCHED_PLACE_ROUNDS(SYNC ? 16 : 0);
+  if constexpr (ALONE != 0) FPSCHED_PLACE_ROUNDS("alone", 0);
+  else if constexpr (STRAIGHT) FPSCHED_PLACE_ROUNDS("rounds", SYNC ? 16 : 0);
   for (unsigned round = 0; round < max_rounds; round += kRounds) {
     // (vmcnt(0): the requests of the last top-up.  Waited for behind the first start times that leave, they would take these
     // stores with them, which have only just been issued.)
@@ -924,6 +938,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
     }
     ask(even, row);
     ask(odd, row + stride2);
+    if (ALONE != 0 && idle_lanes == ~0ull) continue;   // (the first words of all its candidates are on their way)
     unsigned long long moved_even = 0ull, moved_odd = 0ull;
     if constexpr (STRAIGHT) {
       [[maybe_unused]] unsigned in_even, in_odd, at_even, at_odd, scratch, scratch2, start_time, waited;
@@ -932,14 +947,15 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       if constexpr (SYNC) {
 #pragma unroll
         for (unsigned sub = 0; sub < kRounds; sub += 4u) {
-          FPSCHED_ROUNDS(FPSCHED_FOUR_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
+          FPSCHED_ROUNDS("rounds", FPSCHED_FOUR_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
           moved_even |= groups(even, moved_even);
           moved_odd |= groups(odd, moved_odd);
         }
       } else if constexpr (TIMES) {
         FPSCHED_TIMES_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_TIMES_STEP, FPSCHED_TIMES_AHEAD));
       } else if constexpr (WIDE) {
-        FPSCHED_WIDE_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_WIDE_STEP, FPSCHED_WIDE_AHEAD));
+        if constexpr (ALONE != 0) FPSCHED_WIDE_ROUNDS("alone", FPSCHED_EIGHT_ROUNDS(FPSCHED_WIDE_STEP, FPSCHED_WIDE_AHEAD));
+        else FPSCHED_WIDE_ROUNDS("rounds", FPSCHED_EIGHT_ROUNDS(FPSCHED_WIDE_STEP, FPSCHED_WIDE_AHEAD));
       } else if constexpr (LINKS && MB == 0) {
         FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_LINKS_STEP, FPSCHED_LINKS_AHEAD));
       } else if constexpr (LINKS && MB == 1) {
@@ -951,9 +967,11 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
       } else if constexpr (MB == 2) {
         FPSCHED_COST_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_MB_STEP, FPSCHED_MB2_AHEAD));
       } else if constexpr (DEG2) {
-        FPSCHED_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
+        if constexpr (ALONE != 0) FPSCHED_ROUNDS("alone", FPSCHED_EIGHT_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
+        else FPSCHED_ROUNDS("rounds", FPSCHED_EIGHT_ROUNDS(FPSCHED_FOLLOW_STEP, FPSCHED_PLAIN_AHEAD));
       } else {
-        FPSCHED_ROUNDS(FPSCHED_EIGHT_ROUNDS(FPSCHED_PLAIN_STEP, FPSCHED_PLAIN_AHEAD));
+        if constexpr (ALONE != 0) FPSCHED_ROUNDS("alone", FPSCHED_EIGHT_ROUNDS(FPSCHED_PLAIN_STEP, FPSCHED_PLAIN_AHEAD));
+        else FPSCHED_ROUNDS("rounds", FPSCHED_EIGHT_ROUNDS(FPSCHED_PLAIN_STEP, FPSCHED_PLAIN_AHEAD));
       }
     } else {
 #pragma unroll
@@ -1003,7 +1021,7 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
           if (pair == 0) out_flags[cand] = (unsigned char)(flags & (kDeadlock | kIncomplete));
         } else {
           // the latest finish, in a word that was cleared when the segment started
-          atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0)), max(even.free_at, odd.free_at));
+          atomicMax(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds) + (at_max - lds0 + lds_from)), max(even.free_at, odd.free_at));
           const unsigned ms = lds_read<uint32_t>(at_max) >> (WIDE ? 0 : 8);
           const bool failed = (flags & (kDeadlock | kIncomplete)) != 0u;
           const long long r = cand * D + d0;
@@ -1032,9 +1050,14 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : kTimeMaxThreads) __att
   }
 }
 
-#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY)                                                        \
-  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY>(ListTables, const uint16_t*, long long, int, long long*, \
+#define FPSCHED_INSTANTIATE_FORM(DEG2, WIDE, LINKS, MB, SYNC, TIMES, ALONE, COPY)                                                   \
+  template __global__ void time_lists_kernel<DEG2, WIDE, LINKS, MB, SYNC, TIMES, ALONE, COPY>(ListTables, const uint16_t*, long long, int, long long*, \
                                                                     long long*, int*, unsigned char*, unsigned long long*, int, unsigned, StartTimes);
+#define FPSCHED_INSTANTIATE(DEG2, WIDE, LINKS, MB, SYNC, TIMES, COPY) FPSCHED_INSTANTIATE_FORM(DEG2, WIDE, LINKS, MB, SYNC, TIMES, 0, COPY)
+#define FPSCHED_INSTANTIATE_ALONE(DEG2, WIDE)                              \
+  FPSCHED_INSTANTIATE_FORM(DEG2, WIDE, false, 0, false, false, 1, 0)       \
+  FPSCHED_INSTANTIATE_FORM(DEG2, WIDE, false, 0, false, false, 2, 0)       \
+  FPSCHED_INSTANTIATE_FORM(DEG2, WIDE, false, 0, false, false, 3, 0)
 #define FPSCHED_INSTANTIATE_MODELS(DEG2)                            \
   FPSCHED_INSTANTIATE(DEG2, false, false, 0, false, false, 0)   \
   FPSCHED_INSTANTIATE(DEG2, true, false, 0, false, false, 0)    \
@@ -1050,6 +1073,11 @@ FPSCHED_INSTANTIATE(false, false, false, 0, false, true, 0)
 FPSCHED_INSTANTIATE(true, false, false, 0, false, false, kCopyShallow)
 FPSCHED_INSTANTIATE(true, false, false, 0, false, false, 4)
 FPSCHED_INSTANTIATE(true, false, false, 0, false, false, 7)
+FPSCHED_INSTANTIATE_ALONE(false, false)
+FPSCHED_INSTANTIATE_ALONE(true, false)
+FPSCHED_INSTANTIATE_ALONE(false, true)
+#undef FPSCHED_INSTANTIATE_ALONE
+#undef FPSCHED_INSTANTIATE_FORM
 #undef FPSCHED_INSTANTIATE_MODELS
 #undef FPSCHED_INSTANTIATE
 

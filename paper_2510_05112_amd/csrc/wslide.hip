@@ -10,7 +10,7 @@
 // Because a stashed item only runs where it delays nothing, every item of the list starts exactly
 // when it would start if there were no W items at all.  So the pass splits in two:
 //   1. the lists are timed without their W items -- the only part with dependencies between devices -- by the order and
-//      timing passes of the list evaluation in their forms for it (rows.hip, timing.hip), or where those do not take the
+//      timing passes of the list evaluation in their forms for it (rows.h, timing.hip), or where those do not take the
 //      problem or the model by the slot kernel in its TIMES form (eval_slots.hip); that leaves each op's start time and the
 //      position at which each list stopped;
 //   2. this kernel places the W items: one lane per (candidate, device) row, no interaction
