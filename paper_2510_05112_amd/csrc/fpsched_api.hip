@@ -2190,9 +2190,9 @@ static GenShape gen_shape(const fpsched_problem* p, int64_t n_sets, int64_t sets
 }
 
 // What a device's two stages wait for, forward and backward, is on one other device each (kGenOneNeighbour): a chain laid round the
-// devices, but not up and down again.
+// devices, but not up and down again.  (Its counters are by device in the place of those by stage: no more devices than stages.)
 static bool one_neighbour(const fpsched_problem* p) {
-  if (max_chunks_of(p) != 2 || p->max_degree > 1) return false;
+  if (max_chunks_of(p) != 2 || p->max_degree > 1 || p->D > p->S) return false;
   const std::vector<int32_t>& I = p->host_ints;
   const DevTables& G = p->tables;
   for (int d = 0; d < p->D; ++d)

@@ -1,6 +1,6 @@
 """Generator, two stages per actor: what an actor's stages wait for on one other actor, with the counters of both in one word
-(halves in order and swapped, an actor with one stage, actors that wait for nothing, an actor that is its own neighbour), and on two
-other actors; lists, results and results after sliding against the oracles."""
+(halves in order and swapped, an actor with one stage, actors that wait for nothing, an actor that is its own neighbour, as many actors
+as stages), on two other actors, and with more actors than stages; lists, results and results after sliding against the oracles."""
 import numpy as np
 import pytest
 
@@ -21,6 +21,9 @@ def problems():
     yield "one device with one stage", dag_problem([(s, s + 1) for s in range(6)], 7, [s % 4 for s in range(7)], 4, m=6)
     yield "two chains", dag_problem([(0, 1), (1, 2), (3, 4), (4, 5)], 6, [0, 1, 2, 0, 1, 2], 3, m=6)
     yield "two chains, halves swapped", dag_problem([(0, 4), (4, 2), (3, 1), (1, 5)], 6, [0, 1, 2, 0, 1, 2], 3, m=6)
+    yield "as many devices as stages", dag_problem([(0, 2), (1, 3)], 4, [3, 3, 1, 1], 4, m=6)
+    yield "three stages on four devices", dag_problem([(0, 2)], 3, [0, 0, 3], 4, m=6)
+    yield "two stages on the last of 21 devices", dag_problem([(0, 1)], 2, [20, 20], 21, m=6)
     yield "forward from one actor, backward from two", dag_problem([(0, 2), (1, 3)], 4, [0, 0, 1, 2], 3, m=6)
 
 

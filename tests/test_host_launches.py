@@ -343,3 +343,17 @@ def draws(dev, cases):
 def test_draws(stub):
     import test_gpu_draws as t
     run(stub, "draws", [(*t.problem_of(*case[:3]), *case[3:]) for case in t.CASES])
+
+
+def generator_forms(dev, problems):
+    ONE_NEIGHBOUR = 3   # (of the template arguments, the second)
+    for name, prob, want in problems:
+        h = fp.Problem(prob, 256, device=0)
+        dev.launched(dev.lib.fpsched_generate(h._h, 4096, 4096, 100, 256, 4096, 4096, 4096, 4096, 1 << 20, None))
+        h.close()
+        assert (dev.forms[-1][1] == ONE_NEIGHBOUR) == want, name
+
+
+def test_generator_forms(stub):
+    import test_gpu_generate_neighbours as t
+    run(stub, "generator_forms", [(name, prob, not name.startswith(("up and down", "three stages", "two stages", "forward"))) for name, prob in t.problems()])
