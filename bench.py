@@ -40,25 +40,25 @@ def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
 
 # the list evaluation (order pass and timing pass): plain, with costs per micro-batch (--mb-costs), with link occupancy
 # (--links), with both
-MEASURED = {("cfg4", 65536): counted(1.068e10, 1.058e9, 2.768, "list_evaluation.md")}
-MEASURED_MB = {("cfg4", 65536): counted(None, 1.276e9, 3.447, "list_evaluation.md")}
-MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.794, "list_evaluation.md")}
-MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.589e9, 4.493, "list_evaluation.md")}
+MEASURED = {("cfg4", 65536): counted(1.066e10, 1.058e9, 2.700, "list_evaluation.md")}
+MEASURED_MB = {("cfg4", 65536): counted(None, 1.284e9, 3.305, "list_evaluation.md")}
+MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.550, "list_evaluation.md")}
+MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.588e9, 4.183, "list_evaluation.md")}
 # the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
-MEASURED_SYNC = {("sync4", 65536): counted(None, 2.490e8, 0.839, "list_evaluation.md")}
+MEASURED_SYNC = {("sync4", 65536): counted(None, 2.485e8, 0.828, "list_evaluation.md")}
 MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}
 # the copy engine (--config 5 --copy-engine DEPTH), two passes; of the depths that share a form the one that was profiled
-MEASURED_COPY = {3: {("cfg5", 131072): counted(None, 1.171e9, 2.665, "list_evaluation.md")},
-                 4: {("cfg5", 131072): counted(None, 1.265e9, 2.948, "list_evaluation.md")},
-                 7: {("cfg5", 131072): counted(None, 1.562e9, 3.279, "list_evaluation.md")}}
+MEASURED_COPY = {3: {("cfg5", 131072): counted(None, 1.171e9, 2.634, "list_evaluation.md")},
+                 4: {("cfg5", 131072): counted(None, 1.265e9, 2.911, "list_evaluation.md")},
+                 7: {("cfg5", 131072): counted(None, 1.562e9, 3.241, "list_evaluation.md")}}
 # the sliding pass (--mode wslide), all of its kernels, and without its lists (--no-lists): one kernel
-MEASURED_WSLIDE = {("cfg4", 65536): counted(3.73e10, 4.226e9, 11.11, "wslide_kernel_cfg4.md")}
+MEASURED_WSLIDE = {("cfg4", 65536): counted(3.73e10, 4.222e9, 10.73, "wslide_kernel_cfg4.md")}
 MEASURED_WSLIDE_EVAL = {("cfg4", 65536): counted(4.64e9, 5.814e9, 10.78, "wslide_kernel_cfg4.md")}
 # the generator (--mode generate; traffic: WRITE_SIZE x 1024 plus the parameter sets read), generator and evaluator in one
 # kernel (--mode search --fused), the same with the sliding pass in it (--slide)
-MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.763e9, 9.23, "generate_kernel_cfg4.md")}
-MEASURED_FUSED = {("cfg4", 65536): counted(None, 6.020e9, 10.14, "generate_kernel_cfg4.md")}
-MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 6.836e9, 11.23, "generate_kernel_cfg4.md")}
+MEASURED_GENERATE = {("cfg4", 65536): counted(5.56e9, 5.273e9, 8.34, "generate_kernel_cfg4.md")}
+MEASURED_FUSED = {("cfg4", 65536): counted(None, 5.842e9, 9.67, "generate_kernel_cfg4.md")}
+MEASURED_FUSED_SLIDE = {("cfg4", 65536): counted(None, 6.544e9, 10.66, "generate_kernel_cfg4.md")}
 
 
 def rooflines(alg_bytes, kernel_ms, kernel_name, figures, units=None):

@@ -16,7 +16,7 @@
 //
 // What bounds it: per 64 words twelve vector instructions and twelve clocks of LDS, and the op words once from HBM; none
 // of the three is at its limit (65,536 candidates of 32 devices, 128 micro-batches, two chunks, profiles/list_evaluation.md:
-// vector units 54 % busy, LDS 57 %, 3.8 GB at 3.5 TB/s in 1.09 ms), what is left are waits with eight wavefronts per compute
+// vector units 55 % busy, LDS 58 %, 3.8 GB at 3.7 TB/s in 1.03 ms), what is left are waits with eight wavefronts per compute
 // unit.  A row is read 64 bytes at a time.  (Fourteen vector instructions, the places of the states worked out word
 // by word: 1.15 ms in the same run.  States without bank conflicts, a dword of all rows side by side: LDS 32 % busy, one
 // instruction more, 1.14 ms.  128 bytes at a time: 5 % less on long batches of 16 devices, none on 32, 2 to 3 % more on

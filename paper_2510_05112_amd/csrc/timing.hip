@@ -89,7 +89,7 @@
 // to decode the next word; in LDS the slot read (random addresses: half of it bank conflicts), the row, the next word
 // and the slot written.  The row is fetched when the device issues and first looked at in its next step, so the other
 // half's step covers the wait.  That batch took 4.88 ms when one kernel with all devices in every round did the order
-// pass's work as well; then 1.10 ms (rows.h) + 2.05 ms; the pass takes 1.72 ms since the step of the plain form is
+// pass's work as well; then 1.10 ms (rows.h) + 2.05 ms; the pass takes 1.67 ms since the step of the plain form is
 // without branches (FPSCHED_STEP below: half of the gain), the rings are read without bank conflicts and requests are
 // twice as large.
 //
@@ -100,7 +100,7 @@
 // its own: read in lanes' own 32 bytes, some eight lanes shared their banks (6.6 clocks a read instead of 2.2).  Words are
 // requested 64 bytes (forms with the compiler's step: 32) at a time, as soon as the registers they arrive in are free: with the rows of a
 // compute unit's candidates in flight the 128-byte lines mostly do not stay in the L2 cache from one request to the next
-// (12.8 GB fetched for that batch of 3.76 GB with 32 bytes, 6.9 with 64).  (Rings of 32 words leave room for 11 instead
+// (12.8 GB fetched for that batch of 3.76 GB with 32 bytes, 6.8 with 64).  (Rings of 32 words leave room for 11 instead
 // of 16 wavefronts per compute unit: 3.3 ms.  Top-ups every fourth round: 2.19 ms.  Loads that bypass L2: 2.8 ms.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
