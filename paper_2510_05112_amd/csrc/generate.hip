@@ -242,10 +242,12 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   unsigned ahead_at[2] = {lds_address(counts + at_m), lds_address(counts + at_m)}, ahead_bytes[2] = {0x01000100u, 0x01000100u};
   const unsigned both_m = (unsigned)m * 0x00010001u;
   if constexpr (ONE_NEIGHBOUR) {
-    // (where each stage is, in the place of the counters until the first set)
+    // (where each stage is, in the place of the counters until the first set.  A lane reads what others have written: not before
+    // all of them have, whichever way the compiler lays out the conditions)
 #pragma unroll
     for (int c = 0; c < V; ++c)
       if (c < nch) counts[base + stage[c]] = d * kMaxChunks + c;
+    __syncthreads();
 #pragma unroll
     for (int c = 0; c < V; ++c)
 #pragma unroll

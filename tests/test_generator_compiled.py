@@ -1,0 +1,26 @@
+"""What the compiler makes of the generator where its lanes hand one another values through LDS."""
+import re
+
+import pytest
+
+from test_inline_asm import compiled, pytestmark  # noqa: F401
+
+
+@pytest.fixture(scope="module")
+def generator():
+    return compiled("generate.hip", "-emit-llvm")
+
+
+def kernels(text):
+    return re.findall(r"define [^\n]*@\w*generate_kernelILi(\d)ELi(\d)ELi(\d)E[^\n]*\n(.*?)\n}\n", text, re.S)
+
+
+def test_where_the_stages_are_is_read_behind_a_barrier(generator):
+    found = [body for v, graph, _, body in kernels(generator) if (v, graph) == ("2", "3")]
+    assert len(found) == 3
+    for body in found:
+        parts = body.split("call void @llvm.amdgcn.s.barrier()")
+        assert len(parts) == 3
+        accesses = re.findall(r"(load|store) i32\b[^\n]*ptr addrspace\(3\)", parts[1])
+        assert len(accesses) >= 2 and set(accesses) == {"store"}   # (one per stage)
+        assert re.search(r"load i32, ptr addrspace\(3\)", parts[2])
