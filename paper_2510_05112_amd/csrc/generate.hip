@@ -242,12 +242,13 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
   unsigned ahead_at[2] = {lds_address(counts + at_m), lds_address(counts + at_m)}, ahead_bytes[2] = {0x01000100u, 0x01000100u};
   const unsigned both_m = (unsigned)m * 0x00010001u;
   if constexpr (ONE_NEIGHBOUR) {
-    // (where each stage is, in the place of the counters until the first set.  A lane reads what others have written: not before
-    // all of them have, whichever way the compiler lays out the conditions)
+    // (where each stage is, in the place of the counters until the first set.  A lane reads what others of the wavefront have written:
+    // not before all of them have, whichever way the compiler lays out the conditions.  Both lines order, neither is an instruction)
 #pragma unroll
     for (int c = 0; c < V; ++c)
       if (c < nch) counts[base + stage[c]] = d * kMaxChunks + c;
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int c = 0; c < V; ++c)
 #pragma unroll
