@@ -407,10 +407,10 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
         const int c0 = 2 * i, c1 = min(2 * i + 1, kLast);
 #pragma unroll
         for (int k = 0; k < DEG; ++k) {
-          ahead_f[i][2 * k] = *reinterpret_cast<const short*>(&counts[pred_at[c0][k]]);
-          ahead_f[i][2 * k + 1] = *reinterpret_cast<const short*>(&counts[pred_at[c1][k]]);
-          ahead_b[i][2 * k] = *reinterpret_cast<const short*>(&counts[succ_at[c0][k]]);
-          ahead_b[i][2 * k + 1] = *reinterpret_cast<const short*>(&counts[succ_at[c1][k]]);
+          ahead_f[i][2 * k] = lds_read<short>(lds_address(counts + pred_at[c0][k]));
+          ahead_f[i][2 * k + 1] = lds_read<short>(lds_address(counts + pred_at[c1][k]));
+          ahead_b[i][2 * k] = lds_read<short>(lds_address(counts + succ_at[c0][k]));
+          ahead_b[i][2 * k + 1] = lds_read<short>(lds_address(counts + succ_at[c1][k]));
         }
       }
     }
@@ -493,7 +493,8 @@ __global__ __launch_bounds__(kGenThreads) void generate_kernel(
           const int len = words_at(place);
           int at = len & ~15;
           if (len & 15) {
-            for (int i = len & 15; i < 16; ++i) reinterpret_cast<uint16_t*>(staging + (((at + i) >> 1) & (kStagingWords - 1)) * 64)[i & 1] = 0;
+            typedef uint16_t half_of_dword __attribute__((may_alias));   // (stored in halves, read in dwords)
+            for (int i = len & 15; i < 16; ++i) reinterpret_cast<half_of_dword*>(staging + (((at + i) >> 1) & (kStagingWords - 1)) * 64)[i & 1] = 0;
             const uint32_t* w = staging + ((at >> 1) & (kStagingWords - 1)) * 64;
             if (at < stride) *reinterpret_cast<uint4*>(row + at) = make_uint4(w[0], w[64], w[128], w[192]);
             if (at + 8 < stride) *reinterpret_cast<uint4*>(row + at + 8) = make_uint4(w[256], w[320], w[384], w[448]);

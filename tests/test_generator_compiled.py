@@ -26,3 +26,12 @@ def test_where_the_stages_are_is_read_behind_a_barrier(generator):
         accesses = re.findall(r"(load|store) i32\b[^\n]*ptr addrspace\(3\)", parts[0])
         assert len(accesses) >= 2 and set(accesses) == {"store"}   # (one per stage)
         assert re.search(r"load i32, ptr addrspace\(3\)", parts[1])
+
+
+def test_halves_of_words_are_accessed_as_such(generator):
+    # counters and staged op words are stored in dwords and read in halves, or the other way round: of a type the compiler takes to be
+    # anything, so that no such access moves past one of the other kind
+    types = dict(re.findall(r"^(!\d+) = !\{(.*)\}$", generator, re.M))
+    tags = re.findall(r"(?:load|store) i16\b[^\n]*ptr addrspace\(3\)[^\n]*!tbaa (!\d+)", generator)
+    assert len(tags) > 100
+    assert {types[types[tag].split(",")[0]].split(",")[0] for tag in tags} == {'!"omnipotent char"'}
