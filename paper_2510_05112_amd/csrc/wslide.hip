@@ -196,7 +196,8 @@ __global__ __launch_bounds__(kSlideThreads) void wslide_place_kernel(
   const char* const meta_d = reinterpret_cast<const char*>(meta + d);
   const unsigned meta_row = (unsigned)lpc * 8u;
   auto meta_of = [&](unsigned top) -> int2 { return *reinterpret_cast<const int2*>(meta_d + __umul24(top, meta_row)); };
-  auto put = [&](int at, unsigned word) { reinterpret_cast<uint16_t*>(staging + ((at >> 1) & (kOut / 2 - 1)) * 64)[at & 1] = (uint16_t)word; };
+  typedef uint16_t half_of_dword __attribute__((may_alias));   // (stored in halves, read in dwords)
+  auto put = [&](int at, unsigned word) { reinterpret_cast<half_of_dword*>(staging + ((at >> 1) & (kOut / 2 - 1)) * 64)[at & 1] = (uint16_t)word; };
   auto staged4 = [&](int at) {   // eight words from a multiple of eight on
     const uint32_t* w = staging + ((at >> 1) & (kOut / 2 - 1)) * 64;
     return make_uint4(w[0], w[64], w[128], w[192]);

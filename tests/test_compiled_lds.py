@@ -1,4 +1,4 @@
-"""What the compiler makes of the generator where its lanes hand one another values through LDS."""
+"""What the compiler makes of kernels where lanes hand one another values through LDS, or store in halves and read in dwords."""
 import re
 
 import pytest
@@ -28,10 +28,22 @@ def test_where_the_stages_are_is_read_behind_a_barrier(generator):
         assert re.search(r"load i32, ptr addrspace\(3\)", parts[1])
 
 
+def types_of_halves(text):
+    types = dict(re.findall(r"^(!\d+) = !\{(.*)\}$", text, re.M))
+    tags = re.findall(r"(?:load|store) i16\b[^\n]*ptr addrspace\(3\)[^\n]*!tbaa (!\d+)", text)
+    return [types[types[tag].split(",")[0]].split(",")[0] for tag in tags]
+
+
 def test_halves_of_words_are_accessed_as_such(generator):
     # counters and staged op words are stored in dwords and read in halves, or the other way round: of a type the compiler takes to be
     # anything, so that no such access moves past one of the other kind
-    types = dict(re.findall(r"^(!\d+) = !\{(.*)\}$", generator, re.M))
-    tags = re.findall(r"(?:load|store) i16\b[^\n]*ptr addrspace\(3\)[^\n]*!tbaa (!\d+)", generator)
-    assert len(tags) > 100
-    assert {types[types[tag].split(",")[0]].split(",")[0] for tag in tags} == {'!"omnipotent char"'}
+    found = types_of_halves(generator)
+    assert len(found) > 100 and set(found) == {'!"omnipotent char"'}
+    # the placement's lanes store a row's words in halves, and read them in dwords
+    whole = compiled("wslide.hip", "-emit-llvm")
+    types = whole[whole.index("\n!0 = "):]
+    kernels_there = re.findall(r"define [^\n]*@\w*wslide_place_kernelILb\dE[^\n]*\n(.*?)\n}\n", whole, re.S)
+    assert len(kernels_there) == 2
+    for body in kernels_there:
+        found = types_of_halves(body + types)
+        assert len(found) >= 10 and set(found) == {'!"omnipotent char"'}
