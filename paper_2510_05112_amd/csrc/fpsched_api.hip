@@ -1317,9 +1317,16 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
     }
   }
   // (One candidate to a wavefront where there are no more than SIMDs: 800 of 11 x 45 x 2, links 163 and 152 us, costs 146 and 134, in
-  // microseconds 128 and 119; with two for each SIMD no such gain, 2,048 of 4 x 32 x 2 67.6 and 68.9.)
-  const int64_t grid = variant ? variant->grid : p->time_grid, max_waves = variant ? variant->waves : p->time_waves;
-  if (each == 1 && n_cand <= grid * max_waves) T.cands_per_wave = 1;
+  // microseconds 128 and 119; with two for each SIMD no such gain, 2,048 of 4 x 32 x 2 67.6 and 68.9.  One workgroup to a compute unit,
+  // whose wavefronts have a SIMD each, which those of two workgroups of two have not: 1,024 with costs, full wavefronts, two workgroups
+  // and one, 7 x 20 x 3 122, 127 and 116 us, 5 x 20 x 3 98.7, 104.6 and 95.8, 9 x 24 x 3 168, 176 and 159; 600 of two towers, copy engine,
+  // 245, 219 and 210.  It has no more wavefronts than a compute unit had room for in several workgroups.)
+  int64_t grid = variant ? variant->grid : p->time_grid, max_waves = variant ? variant->waves : p->time_waves;
+  if (each == 1 && n_cand <= grid * max_waves) {
+    T.cands_per_wave = 1;
+    grid = n_cu;
+    max_waves = std::max(max_waves, (n_cand + n_cu - 1) / n_cu);
+  }
   // (a small batch is spread over the compute units: fewer wavefronts per workgroup)
   const int64_t row_waves = (n_rows + rpw - 1) / rpw;
   const int cw = (int)std::clamp<int64_t>((row_waves + p->check_grid - 1) / p->check_grid, 1, p->check_waves);

@@ -50,6 +50,7 @@ class Device:
         names = [self.stub.stub_launched(i).decode() for i in range(self.stub.stub_launches())]
         self.forms = [tuple(int(x) for x in re.findall(r"L[bi](\d+)E", n)) for n in names]   # (template arguments)
         self.waves = [self.stub.stub_grid(i) * self.stub.stub_block(i) // 64 for i in range(len(names))]
+        self.shapes = [(self.stub.stub_grid(i), self.stub.stub_block(i)) for i in range(len(names))]
         self.words = [self.stub.stub_word(i) & 0xffffffff for i in range(len(names))]
         self.stub.stub_reset()
         return [re.search(r"\d([a-z_]+_kernel)", n).group(1) for n in names]
@@ -357,3 +358,35 @@ def generator_forms(dev, problems):
 def test_generator_forms(stub):
     import test_gpu_generate_neighbours as t
     run(stub, "generator_forms", [(name, prob, not name.startswith(("up and down", "three stages", "two stages", "forward"))) for name, prob in t.problems()])
+
+
+def small_batches_of_variants(dev, problems):
+    # up to four candidates for each of 256 compute units: one to a wavefront, one workgroup to a compute unit, however many
+    # workgroups a large batch has there
+    groups = set()
+    for prob, set_model in problems:
+        stride = -(-3 * prob.n_microbatches * 4 // 8) * 8 + 8
+        h = fp.Problem(prob, stride, device=0)
+        if set_model == "costs":
+            h.set_microbatch_costs(workloads.microbatch_costs(prob))
+        elif set_model == "links":
+            h.set_link_occupancy(True)
+        else:
+            h.set_copy_engine(4)
+        assert dev.evaluate(h, stride, 1 << 18)[-2:] == TWO_PASSES
+        groups.add(dev.shapes[-1][0] // 256)
+        for n in (1, 255, 256, 257, 512, 513, 1000, 1024):
+            assert dev.evaluate(h, stride, n) == TWO_PASSES, (prob.name, set_model, n)
+            waves = -(-n // 256)
+            assert dev.shapes[-1] == (-(-n // waves), 64 * waves), (prob.name, set_model, n)
+        assert dev.evaluate(h, stride, 1025) == TWO_PASSES
+        assert dev.waves[-1] < 1025 / 2
+        h.close()
+    assert groups >= {1, 2}
+
+
+def test_small_batches_of_variants(stub):
+    chains = [chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2) for D, m, v in ((7, 20, 3), (11, 45, 3), (3, 6, 1))]
+    copy = chain_problem(3, 40, v=1, f=3, b=4, w=2, comm=1)
+    copy.dur[O], copy.dur[L] = 2, 3
+    run(stub, "small_batches_of_variants", [(prob, model) for prob in chains for model in ("costs", "links")] + [(copy, "copy")])
