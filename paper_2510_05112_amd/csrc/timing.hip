@@ -286,36 +286,39 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
                : FPSCHED_PLACES(even), FPSCHED_PLACES(odd), FPSCHED_SHARED, [zero] "v"(0u), [most] "s"(0xffffffu)       \
                : "memory", "vcc", "scc")
 
-// ... the forms with link occupancy and costs per micro-batch.  COST: how the op's cost and tag are added to its start; SEND:
-// when the value leaves over the link, and until when that keeps the link busy; LINK_ROW: the next op's link row is fetched in
-// front of its row.  With the slot, the other half's link word and cost are read ahead.
-#define FPSCHED_COST_STEP(S, AHEAD, COST, LEAVE, BUSY, SEND, REQUESTED, LINK_ROW)                                        \
+// ... the forms with link occupancy and costs per micro-batch.  COST: how the op's cost and tag are added to its start; LEAVE: when
+// the value leaves, over the link, and until when that keeps the link busy, in front of the other half's requests, whose row is on its
+// way meanwhile; OWN: what else only the own device needs; SEND: the link's word, behind the request for the next row, which the
+// device waits for; LINK_ROW: the next op's link row is fetched in front of its row.  With the slot, the other half's link word and cost
+// are read ahead.  (All of the link's word in front of the slot / behind the other half's requests and in front of the own / as it is, the
+// pass: 4,096 candidates of 4 x 32 x 2 73.2, 75.4 and 73.3 us, of 7 x 20 x 3 112.0, 115.6 and 112.2; 20,000 of 16 x 64 x 2 301, 290 and 286,
+// 20,011 of 11 x 45 x 3 479, 462 and 455, with costs 541, 527 and 517.)
+#define FPSCHED_COST_STEP(S, AHEAD, COST, LEAVE, OWN, SEND, REQUESTED, LINK_ROW)                                         \
   "s_waitcnt lgkmcnt(" REQUESTED ")\n\t"                                                                                 \
   "v_add_u32 %[" #S "_in], %[" #S "_in], " FPSCHED_##S##_X "\n\t"                                                        \
   "v_cmpx_eq_u32_sdwa %[" #S "_moved], %[" #S "_in], %[zero] src0_sel:BYTE_0 src1_sel:DWORD\n\t"                         \
   "v_max_u32 %[t], %[" #S "_free], %[" #S "_in]\n\t" COST LEAVE                                                          \
   "s_mov_b64 exec, -1\n\t" AHEAD                                                                                         \
-  "s_mov_b64 exec, %[" #S "_moved]\n\t" BUSY                                                                             \
-  "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t" SEND                                                                  \
+  "s_mov_b64 exec, %[" #S "_moved]\n\t" OWN                                                                              \
   "v_lshrrev_b32 %[t], 11, %[" #S "_next]\n\t" LINK_ROW                                                                  \
   "v_mad_u32_u24 %[t], %[t], %[stride], %[" #S "_rows]\n\t"                                                              \
-  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t"                                                                         \
+  "ds_read_b128 " FPSCHED_##S##_ROW ", %[t]\n\t" SEND                                                                    \
   FPSCHED_NEXT_WORD(S)
 #define FPSCHED_COST_PLAIN(S) "v_add_u32 %[t], %[t], " FPSCHED_##S##_Y "\n\t"
 #define FPSCHED_COST_TABLE(S)                                                                                            \
   "v_lshl_add_u32 %[t], %[" #S "_cost], 8, %[t]\n\t"                                                                     \
   "v_add_u32_sdwa %[t], %[t], " FPSCHED_##S##_Y " dst_sel:DWORD src0_sel:DWORD src1_sel:BYTE_0\n\t"
 #define FPSCHED_COST_BUSY(S) "v_add_u32 %[" #S "_busy], %[" #S "_busy], %[" #S "_cost]\n\t"
+#define FPSCHED_COST_FREE(S) "v_and_b32 %[" #S "_free], 0xffffff00, %[t]\n\t"
 #define FPSCHED_LEAVE(S) "ds_write_b32 %[" #S "_at], %[t]\n\t"
 #define FPSCHED_LEAVE_LINK(S)                                                                                            \
   "v_and_or_b32 %[u], " FPSCHED_##S##_Y ", %[byte], %[" #S "_sent]\n\t"                                                  \
   "v_max_u32 %[" #S "_in], %[t], %[u]\n\t"                                                                               \
-  "ds_write_b32 %[" #S "_at], %[" #S "_in]\n\t"
-#define FPSCHED_SEND_LINK(S)                                                                                             \
+  "ds_write_b32 %[" #S "_at], %[" #S "_in]\n\t" FPSCHED_COST_FREE(S)                                                     \
   "v_lshrrev_b32 %[" #S "_sent], 16, %[" #S "_link]\n\t"                                                                 \
   "v_and_b32 %[u], 0xffffff00, %[" #S "_in]\n\t"                                                                         \
-  "v_lshl_add_u32 %[u], %[" #S "_sent], 8, %[u]\n\t"                                                                     \
-  "ds_write_b32 %[" #S "_link_at], %[u]\n\t"
+  "v_lshl_add_u32 %[" #S "_sent], %[" #S "_sent], 8, %[u]\n\t"
+#define FPSCHED_SEND_LINK(S) "ds_write_b32 %[" #S "_link_at], %[" #S "_sent]\n\t"
 #define FPSCHED_LINK_ROW(S)                                                                                              \
   "v_mad_u32_u24 %[u], %[t], %[link_stride], %[" #S "_link_rows]\n\t"                                                   \
   "ds_read_b32 %[" #S "_link], %[u]\n\t"
@@ -327,8 +330,8 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
   "v_bfe_u32 %[u], %[" #O "_j], 2, 11\n\t"                                                                              \
   "v_lshl_add_u32 %[" #O "_cost], %[u], " SHIFT ", %[" #O "_cost]\n\t" READ " %[" #O "_cost], %[" #O "_cost]\n\t"
 #define FPSCHED_LINKS_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_PLAIN(S), FPSCHED_LEAVE_LINK(S), "", FPSCHED_SEND_LINK(S), "4", FPSCHED_LINK_ROW(S))
-#define FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_LINK(O)
-#define FPSCHED_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_LEAVE(S), FPSCHED_COST_BUSY(S), "", "2", "")
+#define FPSCHED_LINKS_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "3") FPSCHED_AHEAD_LINK(O)
+#define FPSCHED_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_LEAVE(S), FPSCHED_COST_BUSY(S) FPSCHED_COST_FREE(S), "", "2", "")
 #define FPSCHED_MB1_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_COST(O, "0", "ds_read_u8")
 #define FPSCHED_MB2_AHEAD(O) FPSCHED_AHEAD_SLOT(O, "2") FPSCHED_AHEAD_COST(O, "1", "ds_read_u16")
 #define FPSCHED_LINKS_MB_STEP(S, AHEAD) FPSCHED_COST_STEP(S, AHEAD, FPSCHED_COST_TABLE(S), FPSCHED_LEAVE_LINK(S), FPSCHED_COST_BUSY(S), FPSCHED_SEND_LINK(S), "4", FPSCHED_LINK_ROW(S))
