@@ -300,8 +300,11 @@ WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
     };
     const WorkgroupShape dense = place(false);
     // Columns where the lanes of a candidate divide them, so that a lane's column is its number's, and where they cost no wavefront
-    // (a wavefront in fourteen is worth about what half of a row read is).
-    if (kRowColumns % pairs == 0) {
+    // (a wavefront in fourteen is worth about what half of a row read is).  On one or two devices the rows of the image are eight to a
+    // turn of the banks, about as many as a list has kinds of words, and in columns they only take longer to set up (the pass, in columns
+    // and as in the image: 3,465 candidates of 2 x 8 x 2, links 21.4 and 20.3 us, costs 19.4 and 18.4; 74,761 of 2 x 60 x 2 180 either way);
+    // with times of two words columns are worth it there too (whole evaluation, 40,000 of 2 x 32 x 2, 84 and 87 us).
+    if ((pairs > 1 || slot_bytes == 8) && kRowColumns % pairs == 0) {
       const WorkgroupShape shape = place(true);
       if (shape.waves >= 1 && shape.waves * shape.groups >= dense.waves * dense.groups) return shape;
       (void)place(false);
@@ -1299,7 +1302,8 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   // 1).  (A handful of candidates, which is no batch, stays with the two.)
   const TimeKernel alone = variant ? nullptr : alone_kernel_of(p->check_vbits, p->lists_deg2, p->lists_wide);
   const int64_t together = std::min<int64_t>({each, 64 / p->D, T.cands_per_wave});
-  const bool columns = T.odd_at != 16 * ((T.D + 1) / 2);
+  // (One or two devices are with those with columns: their rows are not in each other's way either)
+  const bool columns = T.D <= 2 || T.odd_at != 16 * ((T.D + 1) / 2);
   if (alone && n_cand >= kAloneLeast && n_cand <= together * n_cu * (columns && stride_words > 128 ? 4 : 8)) {
     ListTables A = T;
     const int64_t wavefronts = (n_cand + together - 1) / together;

@@ -9,7 +9,7 @@
 enum { kMost = 4096 };
 static struct { const void* host; const char* name; } kernels[kMost];
 static const char* launches[kMost];
-static struct { unsigned grid, block, word; } shapes[kMost];
+static struct { unsigned grid, block, lds, word; } shapes[kMost];
 static int n_kernels, n_launches, mallocs_to_failure;
 static hipError_t last_error;
 
@@ -24,6 +24,7 @@ int stub_launches(void) { return n_launches; }
 const char* stub_launched(int i) { return launches[i]; }
 unsigned stub_grid(int i) { return shapes[i].grid; }
 unsigned stub_block(int i) { return shapes[i].block; }
+unsigned stub_lds(int i) { return shapes[i].lds; }
 /* of launches of kernels with this in their names, the first four bytes of an argument */
 static const char* watched_kernel;
 static int watched_argument;
@@ -82,11 +83,12 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* host, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t stream) {
-  (void)lds; (void)stream;
+  (void)stream;
   for (int i = 0; i < n_kernels; ++i)
     if (kernels[i].host == host && n_launches < kMost) {
       shapes[n_launches].grid = grid.x;
       shapes[n_launches].block = block.x;
+      shapes[n_launches].lds = (unsigned)lds;
       shapes[n_launches].word = 0;
       if (watched_kernel && strstr(kernels[i].name, watched_kernel)) memcpy(&shapes[n_launches].word, args[watched_argument], 4);
       launches[n_launches++] = kernels[i].name;

@@ -51,6 +51,7 @@ class Device:
         self.forms = [tuple(int(x) for x in re.findall(r"L[bi](\d+)E", n)) for n in names]   # (template arguments)
         self.waves = [self.stub.stub_grid(i) * self.stub.stub_block(i) // 64 for i in range(len(names))]
         self.shapes = [(self.stub.stub_grid(i), self.stub.stub_block(i)) for i in range(len(names))]
+        self.lds = [self.stub.stub_lds(i) for i in range(len(names))]
         self.words = [self.stub.stub_word(i) & 0xffffffff for i in range(len(names))]
         self.stub.stub_reset()
         return [re.search(r"\d([a-z_]+_kernel)", n).group(1) for n in names]
@@ -390,3 +391,28 @@ def test_small_batches_of_variants(stub):
     copy = chain_problem(3, 40, v=1, f=3, b=4, w=2, comm=1)
     copy.dur[O], copy.dur[L] = 2, 3
     run(stub, "small_batches_of_variants", [(prob, model) for prob in chains for model in ("costs", "links")] + [(copy, "copy")])
+
+
+def where_rows_stand(dev, problems):
+    # of a workgroup with one wavefront and one with two, what both have is the rows and, under links, a word for each of the image's
+    with_columns = set()
+    for prob in problems:
+        D, v = prob.n_devices, max(np.bincount(prob.stage_device))
+        h = fp.Problem(prob, 512, device=0)
+        h.set_link_occupancy(True)
+        lds = []
+        for n in (1, 257):
+            assert dev.evaluate(h, 512, n) == TWO_PASSES
+            lds.append(dev.lds[-1])
+        h.close()
+        rows = 2 * lds[0] - lds[1] - 32 * D * 4
+        if rows != 32 * D * 16:   # (not as in the image: sixteen columns, of both halves in one from three stages on)
+            assert D > 2 and 16 % ((D + 1) // 2) == 0 and rows == 32 * 16 * 16 * (1 if v <= 2 else 2), (prob.name, rows)
+            with_columns.add((D, v <= 2))
+    # (16 devices of one or two stages take as much either way)
+    assert with_columns >= {(4, True), (8, True), (8, False), (16, False), (32, True)}, with_columns
+
+
+def test_where_the_rows_of_the_timing_pass_stand(stub):
+    run(stub, "where_rows_stand", [chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2)
+                                   for D in (1, 2, 3, 4, 5, 7, 8, 12, 15, 16, 32, 33, 40) for v in (1, 2, 3, 4) for m in (5, 20, 30)])
