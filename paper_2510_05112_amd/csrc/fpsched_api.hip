@@ -1296,15 +1296,21 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   const int64_t n_rows = n_cand * p->D, rpw = p->check_rows_per_wave;
   const int64_t n_cu = std::max(p->n_cu, 1), each = (n_cand + 4 * n_cu - 1) / (4 * n_cu);   // candidates for each SIMD
   // Both passes in one launch where every wavefront has room for the rows and the lanes of its share, with one wavefront per SIMD, or two.  Two
-  // launches / one, 1,024 to 16,384 candidates, one wavefront per SIMD: 1.00 to 1.14 on 2 to 12 devices (at worst 0.99, 4 x 32 x 2), 1.01 to
+  // launches / one, 1,024 to 16,384 candidates, one wavefront per SIMD: 1.00 to 1.14 on 2 to 12 devices (at worst 0.99, 4 x 32 x 2; four stages: below), 1.01 to
   // 1.06 on 16, 1.04 to 1.11 on 24 to 40.  Two: 1.04 to 1.15 where the timing rows have no columns (12, 24, 40 devices), 1.1 on
   // 4 x 8 x 1; with columns and rows of 192 words and more 0.98 (8 x 32 x 2), 0.99 and 1.00 (16 x 64 x 2), 0.99 and 1.00 (32 x 128 x 2), 1.06 (32 x 64 x
   // 1).  (A handful of candidates, which is no batch, stays with the two.)
   const TimeKernel alone = variant ? nullptr : alone_kernel_of(p->check_vbits, p->lists_deg2, p->lists_wide);
-  const int64_t together = std::min<int64_t>({each, 64 / p->D, T.cands_per_wave});
+  // Candidates of a wavefront: a SIMD's share; a compute unit's with four stages on up to six devices and no more than sixteen for each
+  // (a step of one candidate costs LDS as much as one of four, and the chain of so many ops waits for it.  Two launches / one with a SIMD's
+  // share / with a compute unit's, 1,024 of 4 x 80 x 4 282, 287 and 277 us, of 2 x 60 x 4 176, 177 and 171, 4,096 288, 294 and 285, 180, 182
+  // and 176; 1,024 of 6 x 60 x 4 under links 362, 370 and 360; but of 3 x 40 x 3 121, 118 and 117, of 6 x 40 x 3 168, 159 and 163, of 4 x 60 x 2
+  // 139, 129 and 130, of 8 x 40 x 3 204, 192 and 198, and 6,000 of 3 x 60 x 4 231, 217 and 223.)
+  const int64_t share = T.chunks > 3 && T.D <= 6 && n_cand <= 16 * n_cu ? (n_cand + n_cu - 1) / n_cu : each;
+  const int64_t room = std::min<int64_t>(64 / p->D, T.cands_per_wave), together = std::min(share, room);
   // (One or two devices are with those with columns: their rows are not in each other's way either)
   const bool columns = T.D <= 2 || T.odd_at != 16 * ((T.D + 1) / 2);
-  if (alone && n_cand >= kAloneLeast && n_cand <= together * n_cu * (columns && stride_words > 128 ? 4 : 8)) {
+  if (alone && n_cand >= kAloneLeast && n_cand <= std::min(each, room) * n_cu * (columns && stride_words > 128 ? 4 : 8)) {
     ListTables A = T;
     const int64_t wavefronts = (n_cand + together - 1) / together;
     const int waves = (int)((wavefronts + n_cu - 1) / n_cu);
@@ -1320,14 +1326,14 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
       return check_hip(hipGetLastError());
     }
   }
-  // (One candidate to a wavefront where there are no more than SIMDs: 800 of 11 x 45 x 2, links 163 and 152 us, costs 146 and 134, in
+  // (A wavefront's share, one candidate mostly, where there are no more than SIMDs: 800 of 11 x 45 x 2, links 163 and 152 us, costs 146 and 134, in
   // microseconds 128 and 119; with two for each SIMD no such gain, 2,048 of 4 x 32 x 2 67.6 and 68.9.  One workgroup to a compute unit,
   // whose wavefronts have a SIMD each, which those of two workgroups of two have not: 1,024 with costs, full wavefronts, two workgroups
   // and one, 7 x 20 x 3 122, 127 and 116 us, 5 x 20 x 3 98.7, 104.6 and 95.8, 9 x 24 x 3 168, 176 and 159; 600 of two towers, copy engine,
   // 245, 219 and 210.  It has no more wavefronts than a compute unit had room for in several workgroups.)
   int64_t grid = variant ? variant->grid : p->time_grid, max_waves = variant ? variant->waves : p->time_waves;
   if (each == 1 && n_cand <= grid * max_waves) {
-    T.cands_per_wave = 1;
+    T.cands_per_wave = (int)std::min<int64_t>(share, T.cands_per_wave);
     grid = n_cu;
     max_waves = std::max(max_waves, (n_cand + n_cu - 1) / n_cu);
   }

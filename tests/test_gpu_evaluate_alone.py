@@ -48,3 +48,18 @@ def test_second_edges():
     prob = two_tower_problem()
     spec = workloads.Spec(0, prob, 70, -(-3 * prob.n_microbatches * 4 // 8) * 8 + 8, 8, cap_units=6, seed=5, deadlock_per_mille=50)
     check(prob, workloads.generate(spec, threads=8), "two towers")
+
+
+@pytest.mark.parametrize("D,m", [(2, 6), (6, 5)])
+def test_sizes_at_which_a_compute_unit_has_one_wavefront(D, m):
+    # (four stages per device: a wavefront has all of a compute unit's candidates, up to sixteen)
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    prob, words = batch(D, 4, m, n=70)
+    ref = oracle.evaluate(prob, words, threads=8)
+    links = oracle.evaluate(prob, words, threads=8, links=True)
+    for n in (cu, cu + 1, 3 * cu + 1, 4 * cu, 4 * cu + 1, 16 * cu - 1, 16 * cu, 16 * cu + 1):
+        which = np.arange(n) % len(words)
+        gpu, _ = gpu_evaluate(prob, words[which], kernel="slots")
+        assert_same(gpu, {name: v[which] for name, v in ref.items()}, f"D={D} n={n}")
+        gpu, _ = gpu_evaluate(prob, words[which], kernel="slots", links=True)
+        assert_same(gpu, {name: v[which] for name, v in links.items()}, f"links D={D} n={n}")

@@ -362,8 +362,8 @@ def test_generator_forms(stub):
 
 
 def small_batches_of_variants(dev, problems):
-    # up to four candidates for each of 256 compute units: one to a wavefront, one workgroup to a compute unit, however many
-    # workgroups a large batch has there
+    # up to four candidates for each of 256 compute units: one to a wavefront, or where up to six devices have four stages all of a
+    # compute unit's; one workgroup to a compute unit, however many workgroups a large batch has there
     groups = set()
     for prob, set_model in problems:
         stride = -(-3 * prob.n_microbatches * 4 // 8) * 8 + 8
@@ -378,8 +378,9 @@ def small_batches_of_variants(dev, problems):
         groups.add(dev.shapes[-1][0] // 256)
         for n in (1, 255, 256, 257, 512, 513, 1000, 1024):
             assert dev.evaluate(h, stride, n) == TWO_PASSES, (prob.name, set_model, n)
-            waves = -(-n // 256)
-            assert dev.shapes[-1] == (-(-n // waves), 64 * waves), (prob.name, set_model, n)
+            wavefronts = -(-n // -(-n // 256)) if prob.n_devices <= 6 and prob.n_stages > 3 * prob.n_devices else n
+            waves = -(-wavefronts // 256)
+            assert dev.shapes[-1] == (-(-wavefronts // waves), 64 * waves), (prob.name, set_model, n)
         assert dev.evaluate(h, stride, 1025) == TWO_PASSES
         assert dev.waves[-1] < 1025 / 2
         h.close()
@@ -387,25 +388,27 @@ def small_batches_of_variants(dev, problems):
 
 
 def test_small_batches_of_variants(stub):
-    chains = [chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2) for D, m, v in ((7, 20, 3), (11, 45, 3), (3, 6, 1))]
+    chains = [chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2) for D, m, v in ((7, 20, 3), (11, 45, 3), (3, 6, 1), (6, 20, 3), (2, 30, 4), (6, 12, 4), (7, 12, 4))]
     copy = chain_problem(3, 40, v=1, f=3, b=4, w=2, comm=1)
     copy.dur[O], copy.dur[L] = 2, 3
     run(stub, "small_batches_of_variants", [(prob, model) for prob in chains for model in ("costs", "links")] + [(copy, "copy")])
 
 
 def where_rows_stand(dev, problems):
-    # of a workgroup with one wavefront and one with two, what both have is the rows and, under links, a word for each of the image's
+    # of a workgroup with one wavefront and one with more, what both have is the rows and, under links, a word for each of the image's
     with_columns = set()
     for prob in problems:
         D, v = prob.n_devices, max(np.bincount(prob.stage_device))
         h = fp.Problem(prob, 512, device=0)
         h.set_link_occupancy(True)
-        lds = []
-        for n in (1, 257):
-            assert dev.evaluate(h, 512, n) == TWO_PASSES
+        lds, waves = [], []
+        for n in (1, 1 << 20):
+            assert dev.evaluate(h, 512, n)[-2:] == TWO_PASSES
             lds.append(dev.lds[-1])
+            waves.append(dev.shapes[-1][1] // 64)
         h.close()
-        rows = 2 * lds[0] - lds[1] - 32 * D * 4
+        assert waves[0] == 1 < waves[1]
+        rows = lds[0] - (lds[1] - lds[0]) // (waves[1] - 1) - 32 * D * 4
         if rows != 32 * D * 16:   # (not as in the image: sixteen columns, of both halves in one from three stages on)
             assert D > 2 and 16 % ((D + 1) // 2) == 0 and rows == 32 * 16 * 16 * (1 if v <= 2 else 2), (prob.name, rows)
             with_columns.add((D, v <= 2))
