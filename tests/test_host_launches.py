@@ -419,3 +419,130 @@ def where_rows_stand(dev, problems):
 def test_where_the_rows_of_the_timing_pass_stand(stub):
     run(stub, "where_rows_stand", [chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2)
                                    for D in (1, 2, 3, 4, 5, 7, 8, 12, 15, 16, 32, 33, 40) for v in (1, 2, 3, 4) for m in (5, 20, 30)])
+
+
+ALONE = 6   # (of the timing pass's template arguments: 1 + the bits of the chunk field that select a chunk's states, both passes in one launch)
+
+
+def both_passes_in_one_launch(dev, cases):
+    CU = 256
+    for prob, stride, per_cu in cases:
+        D, bits = prob.n_devices, {1: 0, 2: 1, 3: 2, 4: 2}[max(np.bincount(prob.stage_device))]
+        h = fp.Problem(prob, stride, device=0)
+        room = min(64 // D, h.info()["candidates_per_wave"])
+        most = room * CU * per_cu
+        for n in (1, 63, most + 1, 2 * most):
+            assert dev.evaluate(h, stride, n)[-2:] == TWO_PASSES and dev.forms[-1][ALONE] == 0, (prob.name, n)
+        for n in (64, 65, CU, CU + 1, 4 * CU, 4 * CU + 1, 16 * CU, 16 * CU + 1, most // 2 + 1, most):
+            if n > most:
+                continue
+            assert dev.evaluate(h, stride, n) == ["time_lists_kernel"] and dev.forms[-1][ALONE] == 1 + bits, (prob.name, n)
+            # a SIMD's share of the candidates to a wavefront, or a compute unit's; one workgroup to a compute unit
+            share = -(-n // CU) if bits == 2 and prob.n_stages == 4 * D and D <= 6 and n <= 16 * CU else -(-n // (4 * CU))
+            wavefronts = -(-n // min(share, room))
+            waves = -(-wavefronts // CU)
+            assert dev.shapes[-1] == (-(-wavefronts // waves), 64 * waves), (prob.name, n, dev.shapes[-1])
+            assert dev.lds[-1] <= 160 * 1024
+        h.close()
+
+
+def test_both_passes_in_one_launch(stub):
+    def chain(D, m, v):
+        return chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2)
+    # with columns, or one or two devices, rows of more than 128 words and no more; without
+    run(stub, "both_passes_in_one_launch", [(chain(8, 32, 2), 200, 4), (chain(8, 32, 2), 128, 8), (chain(1, 40, 2), 256, 4), (chain(2, 20, 1), 64, 8),
+                                            (chain(16, 64, 2), 392, 4), (chain(12, 40, 2), 256, 8), (chain(24, 30, 2), 192, 8), (chain(5, 8, 4), 136, 8),
+                                            (chain(4, 8, 4), 96, 8), (two_tower_problem(m=6), 64, 8)])
+
+
+def one_launch_does_not_fit(dev, prob, stride):
+    h = fp.Problem(prob, stride, device=0)
+    assert h.info()["candidates_per_wave"] >= 8 == 64 // prob.n_devices   # (up to 8,192 candidates there would be one launch)
+    for n, want in ((256, ["time_lists_kernel"]), (4096, ["time_lists_kernel"]), (8192, TWO_PASSES)):   # (one, four, eight to a wavefront)
+        assert dev.evaluate(h, stride, n) == want, n
+    h.close()
+
+
+def test_one_launch_that_does_not_fit(stub):
+    run(stub, "one_launch_does_not_fit", chain_problem(8, 150, v=4, f=3, b=5, w=2, comm=2), 1808)
+
+
+def models_that_keep_two_launches(dev, prob, costs):
+    wide = chain_problem(6, 8, v=2, f=3, b=5, w=2, comm=2)
+    wide.dur[:] = wide.dur * 100_000
+    h = fp.Problem(wide, 64, device=0)
+    assert dev.evaluate(h, 64, 500) == ["time_lists_kernel"] and dev.forms[-1][1] == 1
+    h.close()
+    h = fp.Problem(prob, 64, device=0)
+    assert dev.evaluate(h, 64, 500) == ["time_lists_kernel"]
+    h.set_link_occupancy(True)
+    assert dev.evaluate(h, 64, 500) == TWO_PASSES
+    h.set_microbatch_costs(costs)
+    assert dev.evaluate(h, 64, 500) == TWO_PASSES
+    h.set_link_occupancy(False)
+    assert dev.evaluate(h, 64, 500) == TWO_PASSES
+    h.close()
+
+
+def test_models_that_keep_two_launches(stub):
+    prob = chain_problem(6, 8, v=2, f=3, b=5, w=2, comm=2)
+    run(stub, "models_that_keep_two_launches", prob, workloads.microbatch_costs(prob))
+
+
+def sliding_generator(dev, full, problems, orders):
+    N_CLASSES = 6   # (its place among the generator's arguments)
+    dev.stub.stub_watch(b"generate_kernel", N_CLASSES)
+
+    def launched(prob, n):
+        h = fp.Problem(prob, 256, device=0)
+        dev.launched(dev.lib.fpsched_generate_slide_evaluate(h._h, 4096, 4096, n, dev.results, 4096, 4096, 4096, 1 << 20, None))
+        h.close()
+        return dev.waves[-1]
+    for prob in problems:
+        # as many sets to a wavefront as there are lanes for; up to a set for each SIMD, one
+        assert launched(prob, full) == -(-full // (64 // prob.n_devices)), prob.name
+        degree = max(np.bincount(prob.edge_src).max(), np.bincount(prob.edge_dst).max())
+        assert dev.forms[-1][2] == 2 and (dev.forms[-1][1] == 2) == (degree == 2), prob.name
+        assert launched(prob, 1024) == 1024, prob.name
+    os.environ["FPSCHED_GEN_WAVES"] = "1"
+    for prob, n, per_wave, classes in orders:
+        assert launched(prob, n) == min(256, -(-n // per_wave)), (prob.name, n)
+        assert dev.words[-1] == classes, (prob.name, n, dev.words[-1])
+
+
+def test_sliding_generator(stub):
+    import test_gpu_generate_slide_shared as t
+    run(stub, "sliding_generator", t.FULL, [prob for _, prob in t.graphs()] + [prob for _, prob in t.deep_stashes()],
+        [(t.placed_chain(D, v, m, 1, seed=D), n, per_wave, classes) for D, v, m, n, per_wave, classes in t.ORDERS])
+
+
+def segments(dev, rows, device_by_device, spread):
+    for prob, stride, beyond in rows:
+        h = fp.Problem(prob, stride, device=0)
+        room = h.info()["candidates_per_wave"]
+        n = beyond(prob.n_devices, room)
+        assert dev.evaluate(h, stride, n)[-2:] == TWO_PASSES and room >= min(64 // -(-prob.n_devices // 2), 16)   # (lanes are of two devices)
+        blocks, threads = dev.shapes[-1]
+        assert (blocks - 1) * threads // 64 * room < n, (prob.name, dev.shapes[-1], room)
+        for set_model in (lambda: h.set_link_occupancy(True), lambda: h.set_microbatch_costs(workloads.microbatch_costs(prob)), lambda: h.set_link_occupancy(False)):
+            set_model()
+            assert dev.evaluate(h, stride, spread + 300) == TWO_PASSES
+            assert dev.waves[-1] <= (spread + 300) / min(64 // -(-prob.n_devices // 2), 16) + 256, (prob.name, dev.waves[-1])
+        h.close()
+    for prob, stride in device_by_device:
+        h = fp.Problem(prob, stride, device=0)
+        for n in (64, 300, spread):
+            assert dev.evaluate(h, stride, n) == ["time_lists_kernel"], (prob.name, n)
+        # in two launches: the LDS of the order pass is a wavefront's states, and the rows and two words more of each device, no columns
+        D, m = prob.n_devices, prob.n_microbatches
+        assert dev.evaluate(h, stride, 1 << 20)[-2:] == TWO_PASSES
+        waves = dev.shapes[-2][1] // 64
+        states = 64 * 4 * (-(-(m + 1) * (2 if prob.n_stages <= 2 * D else 4) // 4) | 1)
+        assert dev.lds[-2] - waves * states == -(-(2 * 32 * D + 2 * D) * 4 // 16) * 16, prob.name
+        h.close()
+
+
+def test_several_candidates_to_a_wavefront(stub):
+    import test_gpu_list_segments as t
+    chains = [(chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2), -(-3 * v * m // 8) * 8 + 8, t.beyond_one_launch) for D, v, m in t.ROWS]
+    run(stub, "segments", chains, [(chain_problem(D, m, v=v, f=3, b=5, w=2, comm=2), -(-3 * v * m // 8) * 8 + 8) for D, v, m in t.DEVICE_BY_DEVICE], t.SPREAD)
