@@ -43,7 +43,7 @@ def counted(traffic_bytes, valu_wave_instructions, profile_kernel_ms, profile):
 MEASURED = {("cfg4", 65536): counted(1.066e10, 1.058e9, 2.700, "list_evaluation.md")}
 MEASURED_MB = {("cfg4", 65536): counted(None, 1.284e9, 3.305, "list_evaluation.md")}
 MEASURED_LINKS = {("cfg4", 65536): counted(None, 1.374e9, 3.550, "list_evaluation.md")}
-MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.588e9, 4.183, "list_evaluation.md")}
+MEASURED_BOTH = {("cfg4", 65536): counted(None, 1.588e9, 4.139, "list_evaluation.md")}
 # the evaluation with synchronisation stages (--mode sync): two passes, and the table kernel (--table-kernel)
 MEASURED_SYNC = {("sync4", 65536): counted(None, 2.485e8, 0.828, "list_evaluation.md")}
 MEASURED_SYNC_TABLE = {("sync4", 65536): counted(None, 1.068e9, 6.903, "eval_sync_kernel.md")}

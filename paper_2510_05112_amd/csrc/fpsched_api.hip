@@ -318,9 +318,12 @@ WorkgroupShape timing_shape(ListTables* T, int slot_bytes, int64_t max_lds) {
 // Columns of eight bytes, a power of two of them for each (kind, chunk): as many as are all banks, with the devices over and
 // over in them where they are a power of two themselves, so that no two lanes of half a wavefront that are at different rows
 // read the same bank.  Fewer columns where those would cost a wavefront, and the rows of a device side by side, which take no
-// more than the rows themselves, where these would too.  (Columns against rows [kind][chunk][device], the row found by a
-// multiplication: 65,536 candidates of 32 devices, 128 micro-batches, two chunks, 2,588 and 2,575 us; of 16 devices and 64,
-// 2,298 and 2,276 us.  Device by device on the same two: 2,601 and 2,342 us.)
+// more than the rows themselves, where these would too: on devices that are no power of two, 9 % of 2 to 40 devices, 6 to 160
+// micro-batches and one to four stages.  (Columns against rows [kind][chunk][device], the row found by a multiplication: 262,144
+// candidates of 16 devices, 64 micro-batches, two chunks, whole evaluation 2,298 and 2,276 us, the first the multiplication; 32 devices the
+// same.  Device by device against that, the pass, both twice: 24 x 119 x 2 130 and 127 us, 33 x 74 x 2 96.8 and 95.0, 9 x 55 x 3 99.3 and 97.7,
+// 11 x 47 x 4 113.0 and 111.9, 17 x 75 x 3 101.8 and 100.5, 3 x 118 x 2 114.0 and 112.1; 5 x 98 x 2, 12 x 105 x 4, 23 x 86 x 2, 36 x 148 x 2 and
+// 40 x 70 x 2 within 1 %.)
 WorkgroupShape check_shape(ListTables* T, int64_t max_lds, int* rows) {
   WorkgroupShape best{0, 1};
   for (*rows = 64; *rows >= 4; *rows >>= 1) {
@@ -1357,8 +1360,8 @@ static int run_list_evaluation(const fpsched_problem* p, const ListVariant* vari
   const int64_t check_waves = check_blocks * cw, per_wave = (row_waves + check_waves - 1) / check_waves;
   const int draw_blocks = (int)(per_wave <= 8 ? per_wave : per_wave / 4);
   const bool dynamic = row_waves > check_waves * draw_blocks;
-  // (Copies of the columns cost a workgroup more than they save in one block of rows: 1,024 candidates of 4 devices, whole
-  // evaluation, 24.3 and 24.0 us)
+  // (Copies of the columns cost a workgroup more than they save in one block of rows: the pass, with and without them, 1,024 candidates of
+  // 4 x 8 x 1 under links 5.5 and 5.1 us, 20,000 of 2 x 32 x 2 17.2 and 16.0, 8,192 of 4 x 32 x 2 14.6 and 14.2, on 16 and 32 devices the same)
   ListTables check = T;
   if (row_waves <= check_waves) check.check_columns = std::min(T.check_columns, next_pow2(T.D));
   // (How the rows are read, see there)

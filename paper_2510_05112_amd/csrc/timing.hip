@@ -414,7 +414,9 @@ __global__ __launch_bounds__(COPY ? kTimeCopyMaxThreads : (ALONE ? kAloneMaxThre
   // conflicts if these read sixteen different columns of 256 bytes, whatever kind and chunk each of them reads.  As dense as in the
   // image the rows of two candidates met in a bank at 16 devices, those of four at 8: 8 and 10 clocks a read instead of 4.7, in a pass
   // that LDS is busy in for 90 % of its time (whole evaluation: 262,144 candidates of 16 devices, 64 micro-batches, two chunks 2478 and
-  // 2313 us; 65,536 of 8, 32 micro-batches 311 and 299 us; 32 devices are dense in the same columns, no change).
+  // 2313 us; 65,536 of 8, 32 micro-batches 311 and 299 us).  On 32 devices the rows are the same columns; of two stages they take half as
+  // much, which is a wavefront more for each compute unit where tables are large (the pass, 65,536 of 128 micro-batches: links 2.78 and 2.57
+  // ms, costs 2.44 and 2.31, both 3.50 and 3.20; plain the same).
   const bool columns = T.odd_at != 16 * P;
   const int n_rows = T.row_bytes / 16, image_rows = kNKinds * kMaxChunks * D;
   for (int i = tid; i < n_rows; i += blockDim.x) {
