@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 # one wavefront per compute unit: 256 x (64 / p) segments; p, v, m: 15 x 3 v m (1 + v) steps, by class from one per segment on
+# (lists; the sliding form has fewer sets in a wavefront here, and its orders in test_gpu_generate_slide_shared.py)
 @pytest.mark.parametrize("p,v,m,sets_per_segment", [(20, 2, 2, 2.5), (20, 2, 3, 1.9), (20, 2, 3, 2.0), (20, 2, 3, 2.7), (20, 1, 8, 2.1),
                                                     (20, 1, 9, 2.1), (40, 4, 4, 1.3), (40, 4, 4, 6.1), (7, 3, 5, 3.3), (7, 3, 4, 3.3)])
 def test_both_orders(p, v, m, sets_per_segment, monkeypatch):

@@ -1,6 +1,7 @@
 """Timing pass, where its rows stand in LDS: numbers of devices whose pairs divide the sixteen columns and others, one to four stages
 per device (the odd devices' rows in the place of the third and fourth stage's, or behind), lists that end in a word with a chunk,
-tables that leave no room for columns, and the forms with tables behind the rows."""
+tables that leave no room for columns, and the forms with tables behind the rows.  (Batches of one candidate to a wavefront; of as
+many as a large batch has: test_gpu_list_segments.py.)"""
 import numpy as np
 import pytest
 
