@@ -383,7 +383,8 @@ __device__ __forceinline__ bool in(Lanes l) { return __builtin_amdgcn_inverse_ba
 // ALONE: both passes in one launch, behind the order pass of the same candidates, no more of them than segments (1 + VBITS of that pass, or
 // 0); for batches that leave the GPU one or two wavefronts per SIMD.  Such a batch takes as long as a candidate does: the start of a
 // kernel, its tables and the first words of the rows, in both of two kernels, are a part of it that is not small, and a step waits less
-// for LDS with fewer lanes in it, so the candidates are spread over all SIMDs.  Each wavefront walks the rows of its own candidates and
+// for LDS with fewer lanes in it, so the candidates are spread over all SIMDs (with four stages on a few devices over the compute units,
+// run_list_evaluation).  Each wavefront walks the rows of its own candidates and
 // then times them.  Two launches / this one: 1,024 candidates of 4 x 8 x 1 19.0 and 15.5 us, 4,096 18.2 and 16.8, 1,024 of 8 x 32 x 2 108.9
 // and 101.3, of 16 x 64 x 2 162.4 and 155.2, 4,096 172.5 and 163.5, 2,048 of 24 x 30 x 2 100.0 and 90.2.
 template <bool DEG2, bool WIDE, bool LINKS, int MB, bool SYNC, bool TIMES, int ALONE, int COPY>
